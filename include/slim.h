@@ -269,8 +269,9 @@ slim_status slim_unpack_zeros(slim_ctx* ctx, const uint32_t* zpacked, int64_t ld
  *            multiple of 1/2 within +-511 takes the fastest path (Eq. 1 gives integers, the sign form of width 1 uses
  *            1/2); any other finite zero (Eq. 1 does not bound -round(w_min / delta0): a group of one sign with a narrow
  *            range has a large one) is accepted and costs that (row, group) a correction term
- *   X        t_x x m, F16 or BF16, channels contiguous (ldx >= m);  t_x >= 1 tokens, taken 16 at a time (the kernels are
- *            built for the few tokens of a decoding step; more tokens are a sequence of such steps on the stream)
+ *   X        t_x x m, F16 or BF16, channels contiguous (ldx >= m);  t_x >= 1 tokens: up to 64 are taken 16 at a time by
+ *            kernels built for the few tokens of a decoding step, more in one launch of a kernel for many tokens (where X
+ *            is 16-byte aligned with ldx a multiple of 8, as the conventions above demand)
  *   Y        t_x x n fp32 (ldy >= n), overwritten
  *   beta     a multiple of 32 that divides m
  *   bit_base as given to slim_pack; 1 or 2 (widths up to 5), anything else is SLIM_ERR_UNSUPPORTED.  A group whose

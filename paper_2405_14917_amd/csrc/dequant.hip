@@ -17,34 +17,17 @@
 
 #include <mutex>
 
+#include "dequant_device.h"
 #include "slim_device.h"
 #include "slim_internal.h"
 
 namespace {
 
 using namespace slimdev;
+using namespace slimdq;
 
 constexpr int DQ_THREADS = 256;
 constexpr int DQ_MAX_T = 16;
-
-struct DqArgs {
-  const uint32_t* packed;
-  int64_t ldp;
-  const uint32_t* gbits;
-  const int32_t* row_off;
-  const double* scale;   // n x k
-  const double* zero;    // n x k
-  int n, m, beta, k;
-  int bit_base;          // the width that the 2-bit group value 0 stands for
-  const void* X;         // t_x x m, 16-bit
-  int x_bf16;
-  int t_x;
-  int64_t ldx;
-  int gper;              // groups per workgroup along grid.y
-  float* out;            // Y (one split) or the partial sums [split][T][n]
-  int64_t ldo;           // leading dimension of `out` per token
-  int64_t split_stride;  // elements between the partial sums of two splits (0 when writing Y)
-};
 
 __device__ __forceinline__ float widen16(uint16_t h, int bf16) {
   if (bf16) return __uint_as_float((unsigned)h << 16);
@@ -167,10 +150,6 @@ __global__ __launch_bounds__(256) void dequant_reduce(const float* __restrict__ 
 // register, and the activations are stored in LDS in that order (0 4 1 5 2 6 3 7) to match.  Products are exact
 // (11-bit by 6-bit), the sums are fp32 in the matrix core, the scale is applied per group in fp32.
 // With up to 32 tokens served by the same instructions, the kernel is a stream over the packed weights.
-typedef _Float16 half2v __attribute__((ext_vector_type(2)));
-typedef _Float16 half8v __attribute__((ext_vector_type(8)));
-typedef float float16v __attribute__((ext_vector_type(16)));
-
 constexpr int DM_WAVES = 4, DM_ROWS = 32 * DM_WAVES, DM_TOK = 32, DM_PAD = 8;
 
 // the 8 B-bit codes in the low bits of v -> four registers of packed fp16 pairs (1024 + 2 c_j, 1024 + 2 c_{j+4})
@@ -288,16 +267,10 @@ __global__ __launch_bounds__(64 * DM_WAVES) void dequant_matmul_mfma(DqArgs a) {
   const int prow = (wave * 32 + l32) * gcount;
 
   const int nsub = a.beta / SUB, units = (g1 - g0) * nsub;
-  auto width = [&](int g) { return (int)((a.gbits[g >> 4] >> (2 * (g & 15))) & 3u) + a.bit_base; };
   // fetch of unit u: the words of the lane's row
-  // 0 for a group whose start rows disagree with its width: such a group is skipped and none of its words is read
-  auto checked_width = [&](int g) {
-    const int b = width(g);
-    return ((a.row_off[g + 1] - a.row_off[g]) * 32 == a.beta * b) ? b : 0;
-  };
   auto fetch = [&](int u, unsigned (&w)[MAXW]) {
     const int g = g0 + u / nsub, sb = u - (u / nsub) * nsub;
-    const int nwu = SUB * checked_width(g) / 32;
+    const int nwu = SUB * checked_width(a, g) / 32;
     const uint32_t* p = a.packed + (int64_t)(a.row_off[g] + sb * nwu) * a.ldp + row;
 #pragma unroll
     for (int i = 0; i < MAXW; ++i) w[i] = (i < nwu) ? p[(int64_t)i * a.ldp] : 0u;
@@ -320,7 +293,7 @@ __global__ __launch_bounds__(64 * DM_WAVES) void dequant_matmul_mfma(DqArgs a) {
     zz[0] = zc;
     zz[1] = zc;
     const _Float16* xu = xs + (g - g0) * a.beta + sb * SUB;
-    switch (checked_width(g)) {                    // the same for the whole workgroup
+    switch (checked_width(a, g)) {                    // the same for the whole workgroup
       case 0: break;
       case 1: acc = subblock_mfma<1, SUB, MAXW>(wc, h, zz, xu, acc); break;
       case 2: acc = subblock_mfma<2, SUB, MAXW>(wc, h, zz, xu, acc); break;
@@ -332,7 +305,7 @@ __global__ __launch_bounds__(64 * DM_WAVES) void dequant_matmul_mfma(DqArgs a) {
     }
     if (sb == nsub - 1) {                          // the group is complete: its scale (times the 1/2 of the doubled codes)
       const float rest = zr[prow + (g - g0)];
-      if (__builtin_amdgcn_ballot_w64(rest != 0.f) != 0 && checked_width(g) != 0) {
+      if (__builtin_amdgcn_ballot_w64(rest != 0.f) != 0 && checked_width(a, g) != 0) {
         // some row of this wavefront has a zero that the fp16 form does not hold: the part it does not hold times
         // the sum of the group's activations, per token (the order of the tile's columns does not matter for a sum)
 #pragma unroll 1
@@ -399,22 +372,53 @@ int dq_splits(int n, int m, int beta, int t_x, int cus, bool mfma, int& gper) {
   return slim_cdiv(k, gper);
 }
 
-// The whole call.  `fixed` = nullptr: partial sums go to the context's workspace (grown if needed); otherwise to
-// `fixed`, which holds `fixed_floats` floats, and nothing is allocated.
-slim_status dequant_matmul_run(slim_ctx* ctx, const char* fn, const uint32_t* packed, int64_t ldp,
-                               const uint32_t* gbits, const int32_t* row_off, const double* scale, const double* zero,
-                               int n, int m, int beta, int bit_base, const void* X, slim_dtype x_dtype, int t_x,
-                               int64_t ldx, float* Y, int64_t ldy, float* fixed, size_t fixed_floats) {
-  SLIM_REQUIRE(ctx, packed && gbits && row_off && scale && zero && X && Y, "%s: null pointer", fn);
-  SLIM_REQUIRE(ctx, n > 0 && m > 0 && beta > 0 && m % beta == 0, "%s: need n, m > 0 and beta | m", fn);
-  SLIM_REQUIRE(ctx, beta % 32 == 0, "%s: beta must be a multiple of 32 (got %d)", fn, beta);
-  SLIM_REQUIRE(ctx, t_x >= 1 && t_x <= DQ_MAX_T, "%s: t_x must be in 1..%d (got %d)", fn, DQ_MAX_T, t_x);
-  SLIM_REQUIRE(ctx, ldp >= n && ldx >= m && ldy >= n, "%s: leading dimension too small", fn);
+// What both forms of the call are refused for; nothing has been launched then.
+slim_status dq_check(slim_ctx* ctx, const char* fn, const DqArgs& a, slim_dtype x_dtype, int64_t t_x, int64_t ldy) {
+  SLIM_REQUIRE(ctx, a.packed && a.gbits && a.row_off && a.scale && a.zero && a.X && a.out, "%s: null pointer", fn);
+  SLIM_REQUIRE(ctx, a.n > 0 && a.m > 0 && a.beta > 0 && a.m % a.beta == 0, "%s: need n, m > 0 and beta | m", fn);
+  SLIM_REQUIRE(ctx, a.beta % 32 == 0, "%s: beta must be a multiple of 32 (got %d)", fn, a.beta);
+  SLIM_REQUIRE(ctx, t_x >= 1, "%s: t_x must be at least 1 (got %lld)", fn, (long long)t_x);
+  SLIM_REQUIRE(ctx, a.ldp >= a.n && a.ldx >= a.m && ldy >= a.n, "%s: leading dimension too small", fn);
   if (x_dtype != SLIM_F16 && x_dtype != SLIM_BF16)
     return slim_fail(ctx, SLIM_ERR_UNSUPPORTED, "%s: X must be F16 or BF16", fn);
-  if (bit_base != 1 && bit_base != 2)
-    return slim_fail(ctx, SLIM_ERR_UNSUPPORTED, "%s: bit_base must be 1 or 2 (widths up to 5), got %d", fn, bit_base);
-  const int k = m / beta;
+  if (a.bit_base != 1 && a.bit_base != 2)
+    return slim_fail(ctx, SLIM_ERR_UNSUPPORTED, "%s: bit_base must be 1 or 2 (widths up to 5), got %d", fn, a.bit_base);
+  return SLIM_OK;
+}
+
+// Where the kernel writes: Y itself with one group range, else partial sums, which go to the context's workspace (grown
+// if needed) or, if `fixed` is given, to `fixed`, which holds `fixed_floats` floats (nothing is allocated then).
+slim_status dq_partials(slim_ctx* ctx, const char* fn, DqArgs& a, int splits, float* fixed, size_t fixed_floats) {
+  if (splits <= 1) return SLIM_OK;
+  const size_t part_floats = (size_t)splits * a.t_x * a.n;
+  if (fixed) {
+    if (part_floats > fixed_floats)
+      return slim_fail(ctx, SLIM_ERR_UNSUPPORTED,
+                       "%s: this layer needs %zu floats of partial sums (%d group ranges x %d tokens x %d rows), the "
+                       "fixed buffer holds %zu: fewer tokens per call, or slim_dequant_matmul", fn, part_floats,
+                       splits, a.t_x, a.n, fixed_floats);
+    a.out = fixed;
+  } else {
+    slim_status st = slim_ws_reserve(ctx, slim_ws_need_dequant(a.n, a.m, a.beta, a.t_x, std::max(1, ctx->num_cus)));
+    if (st != SLIM_OK) return st;
+    a.out = static_cast<float*>(slim_ws_alloc(ctx, sizeof(float) * part_floats));
+  }
+  a.ldo = a.n;
+  a.split_stride = (int64_t)a.t_x * a.n;
+  return SLIM_OK;
+}
+
+slim_status dq_reduce(slim_ctx* ctx, const DqArgs& a, int splits, float* Y, int64_t ldy) {
+  if (splits > 1)
+    SLIM_LAUNCH(ctx, "dequant_reduce", dequant_reduce, dim3(slim_cdiv((int64_t)a.t_x * a.n, 256)), dim3(256), 0, a.out,
+                splits, a.split_stride, a.t_x, a.n, Y, ldy);
+  return SLIM_OK;
+}
+
+// Up to DQ_MAX_T tokens (arguments checked).
+slim_status dequant_matmul_run(slim_ctx* ctx, const char* fn, DqArgs a, int64_t ldy, float* fixed, size_t fixed_floats) {
+  float* const Y = a.out;
+  const int n = a.n, m = a.m, beta = a.beta, t_x = a.t_x;
   int T = 1;
   while (T < t_x) T *= 2;
   // fp16 activations that can be fetched 16 bytes at a time go to the matrix-core kernel
@@ -422,61 +426,20 @@ slim_status dequant_matmul_run(slim_ctx* ctx, const char* fn, const uint32_t* pa
   // for one or two tokens the plain kernel, whose workgroups cover twice the rows, is the quicker one there)
   const int cus = std::max(1, ctx->num_cus);
   const bool small = 2 * slim_cdiv(n, DM_ROWS) < cus;
-  const bool mfma = x_dtype == SLIM_F16 && slim_aligned16(X) && ldx % 8 == 0 &&
+  const bool mfma = !a.x_bf16 && slim_aligned16(a.X) && a.ldx % 8 == 0 &&
                     (beta == 32 || beta == 64 || beta % 128 == 0) && !(small && t_x <= 2);
   size_t smem = sizeof(float) * (size_t)T * beta;   // (the matrix-core kernel's depends on the split, below)
   const int gx = slim_cdiv(n, mfma ? DM_ROWS : DQ_THREADS);
-  int gper = 0;
-  const int splits = dq_splits(n, m, beta, t_x, cus, mfma, gper);
-
-  DqArgs a;
-  a.packed = packed;
-  a.ldp = ldp;
-  a.gbits = gbits;
-  a.row_off = row_off;
-  a.scale = scale;
-  a.zero = zero;
-  a.n = n;
-  a.m = m;
-  a.beta = beta;
-  a.k = k;
-  a.bit_base = bit_base;
-  a.X = X;
-  a.x_bf16 = (x_dtype == SLIM_BF16);
-  a.t_x = t_x;
-  a.ldx = ldx;
-  a.gper = gper;
-  float* part = nullptr;
-  if (splits > 1) {
-    const size_t part_floats = (size_t)splits * t_x * n;
-    if (fixed) {
-      if (part_floats > fixed_floats)
-        return slim_fail(ctx, SLIM_ERR_UNSUPPORTED,
-                         "%s: this layer needs %zu floats of partial sums (%d group ranges x %d tokens x %d rows), the "
-                         "fixed buffer holds %zu: fewer tokens per call, or slim_dequant_matmul", fn, part_floats,
-                         splits, t_x, n, fixed_floats);
-      part = fixed;
-    } else {
-      slim_status st = slim_ws_reserve(ctx, slim_ws_need_dequant(n, m, beta, t_x, cus));
-      if (st != SLIM_OK) return st;
-      part = static_cast<float*>(slim_ws_alloc(ctx, sizeof(float) * part_floats));
-    }
-    a.out = part;
-    a.ldo = n;
-    a.split_stride = (int64_t)t_x * n;
-  } else {
-    a.out = Y;
-    a.ldo = ldy;
-    a.split_stride = 0;
-  }
+  const int splits = dq_splits(n, m, beta, t_x, cus, mfma, a.gper);
+  slim_status st = dq_partials(ctx, fn, a, splits, fixed, fixed_floats);
+  if (st != SLIM_OK) return st;
   const dim3 grid(gx, splits);
-  slim_status st = SLIM_OK;
   if (mfma) {
-    smem = sizeof(uint16_t) * (size_t)(t_x + 1) * ((size_t)gper * beta + DM_PAD) + (size_t)DM_ROWS * gper * 10;
+    smem = sizeof(uint16_t) * (size_t)(t_x + 1) * ((size_t)a.gper * beta + DM_PAD) + (size_t)DM_ROWS * a.gper * 10;
 #define SLIM_DQ_MFMA(SUB, MAXW)                                                                              \
   SLIM_LAUNCH(ctx, "dequant_matmul@dequant_matmul_mfma<" #SUB ", " #MAXW ">", (dequant_matmul_mfma<SUB, MAXW>), grid, \
               dim3(64 * DM_WAVES), smem, a)
-    const bool wide = bit_base + 3 > 4;            // the layer may hold five-bit groups
+    const bool wide = a.bit_base + 3 > 4;          // the layer may hold five-bit groups
     if (beta >= 128) {
       if (wide) SLIM_DQ_MFMA(128, 20); else SLIM_DQ_MFMA(128, 16);
     } else if (beta == 64) {
@@ -494,27 +457,59 @@ slim_status dequant_matmul_run(slim_ctx* ctx, const char* fn, const uint32_t* pa
     default: st = launch<16>(ctx, a, grid, smem); break;
   }
   if (st != SLIM_OK) return st;
-  if (splits > 1)
-    SLIM_LAUNCH(ctx, "dequant_reduce", dequant_reduce, dim3(slim_cdiv((int64_t)t_x * n, 256)), dim3(256), 0, part, splits,
-                a.split_stride, t_x, n, Y, ldy);
-  return SLIM_OK;
+  return dq_reduce(ctx, a, splits, Y, ldy);
 }
 
-// Any number of tokens: DQ_MAX_T at a time, one after the other on the context's stream (the kernels are built for
-// the few tokens of a decoding step; a batch is a sequence of such steps).  Nothing is launched if the first slice,
-// which is the largest, is refused.
+// Any number of tokens: more than 64 in one launch of the kernel for many tokens, fewer DQ_MAX_T at a time, one after
+// the other on the context's stream.  Nothing is launched if the call is refused.
 slim_status dequant_matmul_tokens(slim_ctx* ctx, const char* fn, const uint32_t* packed, int64_t ldp,
                                   const uint32_t* gbits, const int32_t* row_off, const double* scale,
                                   const double* zero, int n, int m, int beta, int bit_base, const void* X,
                                   slim_dtype x_dtype, int64_t t_x, int64_t ldx, float* Y, int64_t ldy, float* fixed,
                                   size_t fixed_floats) {
-  SLIM_REQUIRE(ctx, t_x >= 1, "%s: t_x must be at least 1 (got %lld)", fn, (long long)t_x);
+  DqArgs a;
+  a.packed = packed;
+  a.ldp = ldp;
+  a.gbits = gbits;
+  a.row_off = row_off;
+  a.scale = scale;
+  a.zero = zero;
+  a.n = n;
+  a.m = m;
+  a.beta = beta;
+  a.bit_base = bit_base;
+  a.X = X;
+  a.x_bf16 = (x_dtype == SLIM_BF16);
+  a.ldx = ldx;
+  a.out = Y;
+  a.ldo = ldy;
+  a.split_stride = 0;
+  slim_status st = dq_check(ctx, fn, a, x_dtype, t_x, ldy);
+  if (st != SLIM_OK) return st;
+  a.k = m / beta;
+  a.gper = a.k;
+  const int cus = std::max(1, ctx->num_cus);
+  if (slim_dq_gemm_takes(t_x, m, beta, X, ldx)) {
+    if (fixed) {
+      // the limit of the fixed buffer is stated for slices of DQ_MAX_T tokens, whichever kernel runs
+      a.t_x = DQ_MAX_T;
+      DqArgs b = a;
+      const bool mfma = !a.x_bf16 && (beta == 32 || beta == 64 || beta % 128 == 0);
+      st = dq_partials(ctx, fn, b, dq_splits(n, m, beta, DQ_MAX_T, cus, mfma, b.gper), fixed, fixed_floats);
+      if (st != SLIM_OK) return st;
+    }
+    a.t_x = (int)t_x;
+    const int splits = slim_dq_gemm_splits(n, m, beta, t_x, cus, a.gper);
+    st = dq_partials(ctx, fn, a, splits, fixed, fixed_floats);
+    if (st == SLIM_OK) st = slim_dq_gemm_launch(ctx, a, splits);
+    if (st == SLIM_OK) st = dq_reduce(ctx, a, splits, Y, ldy);
+    return st;
+  }
   for (int64_t t0 = 0; t0 < t_x; t0 += DQ_MAX_T) {
-    const int tc = (int)std::min<int64_t>(DQ_MAX_T, t_x - t0);
-    const void* xs = X ? static_cast<const void*>(static_cast<const uint16_t*>(X) + t0 * ldx) : nullptr;
-    float* ys = Y ? Y + t0 * ldy : nullptr;
-    const slim_status st = dequant_matmul_run(ctx, fn, packed, ldp, gbits, row_off, scale, zero, n, m, beta, bit_base,
-                                              xs, x_dtype, tc, ldx, ys, ldy, fixed, fixed_floats);
+    a.t_x = (int)std::min<int64_t>(DQ_MAX_T, t_x - t0);
+    a.X = static_cast<const uint16_t*>(X) + t0 * ldx;
+    a.out = Y + t0 * ldy;
+    st = dequant_matmul_run(ctx, fn, a, ldy, fixed, fixed_floats);
     if (st != SLIM_OK) return st;
   }
   return SLIM_OK;
@@ -523,8 +518,13 @@ slim_status dequant_matmul_tokens(slim_ctx* ctx, const char* fn, const uint32_t*
 }  // namespace
 
 size_t slim_ws_need_dequant(int n, int m, int beta, int t_x, int ncu) {
-  t_x = std::min(t_x, DQ_MAX_T);
   size_t need = 0;
+  if (t_x > 64) {                              // the kernel for many tokens, or slices where it cannot take the activations
+    int gper = 0;
+    const int splits = slim_dq_gemm_splits(n, m, beta, t_x, std::max(1, ncu), gper);
+    if (splits > 1) need = slim_ws_round(sizeof(float) * (size_t)splits * t_x * n);
+  }
+  t_x = std::min(t_x, DQ_MAX_T);
   for (int mfma = 0; mfma < 2; ++mfma) {       // whichever kernel the activations' type and alignment select
     int gper = 0;
     const int splits = dq_splits(n, m, beta, t_x, std::max(1, ncu), mfma != 0, gper);

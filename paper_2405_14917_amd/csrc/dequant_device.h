@@ -1,0 +1,51 @@
+// Device-side pieces that the kernels of the linear layer on the stored form share.
+#ifndef SLIM_DEQUANT_DEVICE_H
+#define SLIM_DEQUANT_DEVICE_H
+
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "slim_internal.h"
+
+namespace slimdq {
+
+typedef _Float16 half2v __attribute__((ext_vector_type(2)));
+typedef _Float16 half8v __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x8v __attribute__((ext_vector_type(8)));
+typedef float float16v __attribute__((ext_vector_type(16)));
+
+struct DqArgs {
+  const uint32_t* packed;
+  int64_t ldp;
+  const uint32_t* gbits;
+  const int32_t* row_off;
+  const double* scale;   // n x k
+  const double* zero;    // n x k
+  int n, m, beta, k;
+  int bit_base;          // the width that the 2-bit group value 0 stands for
+  const void* X;         // t_x x m, 16-bit
+  int x_bf16;
+  int t_x;
+  int64_t ldx;
+  int gper;              // groups per workgroup along grid.y
+  float* out;            // Y (one split) or the partial sums [split][T][n]
+  int64_t ldo;           // leading dimension of `out` per token
+  int64_t split_stride;  // elements between the partial sums of two splits (0 when writing Y)
+};
+
+// Width of group g, or 0 for a group whose start rows disagree with its width (a stored form read with the wrong
+// bit_base, or a damaged one): such a group is skipped and none of its words is read.
+__device__ __forceinline__ int checked_width(const DqArgs& a, int g) {
+  const int b = (int)((a.gbits[g >> 4] >> (2 * (g & 15))) & 3u) + a.bit_base;
+  return ((a.row_off[g + 1] - a.row_off[g]) * 32 == a.beta * b) ? b : 0;
+}
+
+}  // namespace slimdq
+
+// The linear layer for many tokens (dequant_gemm.hip).  `dq_gemm_takes` tells whether it is built for the call;
+// dq_gemm_splits gives the group ranges the layer is cut into (and groups per range in `gper`).
+bool slim_dq_gemm_takes(int64_t t_x, int m, int beta, const void* X, int64_t ldx);
+int slim_dq_gemm_splits(int n, int m, int beta, int64_t t_x, int cus, int& gper);
+slim_status slim_dq_gemm_launch(slim_ctx* ctx, const slimdq::DqArgs& a, int splits);
+
+#endif

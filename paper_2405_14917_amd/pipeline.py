@@ -93,7 +93,7 @@ class LayerPass:
 def next_layer_input(slim, r, beta, X, n):
     """Calibration activations of the next layer of a chain (Sec. 3.4: every layer inside the GPTQ backbone sees what
     its quantised predecessors emit): the layer of result `r`, applied FROM ITS STORED FORM to the columns of X
-    (m x t, fp16, tokens contiguous) by the library's linear-layer kernel (which takes its tokens 16 at a time), rounded to fp16 and
+    (m x t, fp16, tokens contiguous) by the library's linear-layer kernel for many tokens, rounded to fp16 and
     laid out channels x tokens again.  Only layout changes and the rounding happen here."""
     t = X.shape[1]
     Xn = torch.empty((n, t), dtype=torch.float16, device=X.device)

@@ -1,0 +1,70 @@
+"""The linear layer on the stored form for more than 64 tokens (its own kernel) against the float64 oracle: token and row
+counts around the tiles (128 or 64 tokens x 128 rows), one and several group ranges, both slab widths (group sizes that 64
+divides and that it does not), every code width, both activation types, zero points outside the operand's form, groups
+that are skipped, and activations the kernel cannot fetch (the sliced form takes those)."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import slim_oracle as orc
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def slim():
+    from paper_2405_14917_amd import binding
+    s = binding.Slim("cuda:0")
+    yield s
+    s.close()
+
+
+def stored(slim, rng, n, m, beta, base, odd_zeros):
+    k = m // beta
+    bits = (base + np.arange(k) % (4 if base == 2 else 3)).astype(np.uint8)
+    codes = np.concatenate([rng.integers(0, 2 ** int(b), (n, beta)) for b in bits], axis=1).astype(np.uint8)
+    scale = rng.uniform(0.005, 0.02, (n, k))
+    zero = np.stack([rng.integers(0, 2 ** int(b), n).astype(np.float64) for b in bits], axis=1)
+    zero[:, bits == 1] = 0.5
+    if odd_zeros:
+        zero[: n // 3, 0] = -700.0                    # beyond the fp16 operand's form
+        zero[n // 3: n // 2, -1] = 96.0               # beyond the bf16 operand's form
+        zero[n // 2, k // 2] = 3.3                    # not a multiple of 1/2
+    packed, gbits, row_off, _ = slim.pack(torch.from_numpy(codes).cuda(), torch.from_numpy(bits).cuda(), beta, bit_base=base)
+    What = np.repeat(scale, beta, axis=1) * (codes - np.repeat(zero, beta, axis=1))
+    return packed, gbits, row_off, torch.from_numpy(scale).cuda(), torch.from_numpy(zero).cuda(), What
+
+
+@pytest.mark.parametrize("t,n,m,beta,base,dtype,odd", [
+    (65, 77, 64, 64, 1, torch.float16, False), (128, 128, 512, 128, 1, torch.float16, True),
+    (129, 300, 1024, 128, 2, torch.bfloat16, True), (200, 129, 320, 32, 1, torch.float16, True),
+    (257, 260, 288, 96, 2, torch.bfloat16, False), (70, 1000, 2304, 128, 1, torch.bfloat16, False),
+    (640, 9000, 256, 256, 1, torch.float16, True), (300, 130, 1024, 512, 2, torch.float16, False)])
+def test_many_tokens(slim, t, n, m, beta, base, dtype, odd):
+    rng = np.random.default_rng(t + n)
+    packed, gbits, row_off, scale, zero, What = stored(slim, rng, n, m, beta, base, odd)
+    X = torch.from_numpy(rng.standard_normal((t, m))).to(dtype).cuda()
+    Yw = torch.full((t, n + 5), -1.0, dtype=torch.float32, device="cuda")
+    Y = slim.dequant_matmul(packed, gbits, row_off, scale, zero, beta, X, Y=Yw[:, :n], bit_base=base)
+    Xn = X.double().cpu().numpy()
+    # the bound of the linear layer: fp32 sums of exact products, 1e-5 of the sum of magnitudes (m <= 2304 terms)
+    assert np.all(np.abs(Y.cpu().numpy() - Xn @ What.T) <= 1e-5 * (np.abs(Xn) @ np.abs(What).T) + 1e-30)
+    assert bool((Yw[:, n:] == -1.0).all())
+    assert torch.equal(Y, slim.dequant_matmul(packed, gbits, row_off, scale, zero, beta, X, bit_base=base))
+    # the entry point that allocates nothing: same kernel, same ranges, same bytes
+    Yn = torch.empty((t, n), dtype=torch.float32, device="cuda")
+    slim.dequant_matmul(packed, gbits, row_off, scale, zero, beta, X, Y=Yn, bit_base=base, noalloc=True)
+    assert torch.equal(Y, Yn)
+
+
+def test_skipped_groups_and_unaligned_activations(slim):
+    rng = np.random.default_rng(5)
+    n, m, beta, t = 200, 512, 64, 90
+    packed, gbits, row_off, scale, zero, What = stored(slim, rng, n, m, beta, 1, False)
+    X = torch.from_numpy(rng.standard_normal((t, m)).astype(np.float16)).cuda()
+    assert not bool(slim.dequant_matmul(packed, gbits, row_off, scale, zero, beta, X, bit_base=2).any())
+    Xo = torch.zeros((t, m + 12), dtype=torch.float16, device="cuda")       # a leading dimension that is no multiple of 8
+    Xo[:, :m] = X
+    Y = slim.dequant_matmul(packed, gbits, row_off, scale, zero, beta, Xo[:, :m])
+    Xn = X.double().cpu().numpy()
+    assert np.all(np.abs(Y.cpu().numpy() - Xn @ What.T) <= 1e-5 * (np.abs(Xn) @ np.abs(What).T))
