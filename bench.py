@@ -28,7 +28,7 @@ import torch
 
 from paper_2405_14917_amd import binding, pipeline, synth
 
-PEAK = {"mfma_f16": 2.5e15, "mfma_f64": 78.6e12, "alu_f64": 78.6e12, "hbm": 8.0e12}
+PEAK = {"mfma_f16": 2.5e15, "mfma_i8": 5.0e15, "mfma_f64": 78.6e12, "alu_f64": 78.6e12, "hbm": 8.0e12}
 # HBM bytes per launch of the dominant kernel function, from two `rocprofv3 --pmc` runs of this command (FETCH_SIZE,
 # then WRITE_SIZE, in KiB per dispatch), each scaled by what the same counter reads for the 64 MiB copy that this
 # program issues for that purpose; the files under profiles/ that are named here give the commands and the readings.
@@ -137,14 +137,12 @@ def algorithmic_work(name, cfg, launches_per_step):
     L = max(launches_per_step, 1)
     if name.startswith("gram_mfma"):
         return "mfma", "mfma_f16", float(m) * (m + 1) * t / L
-    if name == "sba_output_dgemm":
-        # two products per step (reference outputs, outputs of the all-N-bit weights), in one launch or several
-        return "mfma", "mfma_f64", 2.0 * (2.0 * n * m * ts) / L
-    if name == "sba_update_dgemm":
-        return "mfma", "mfma_f64", 4.0 * n * beta * ts
+    if name in ("sba_reference_outputs", "sba_outputs"):
+        # one product each, on the int8 matrix cores: at least one product of integers (the digits multiply it)
+        return "mfma", "mfma_i8", 2.0 * n * m * ts / L
     if name == "sba_search":
-        # the k/2 rank-2beta updates of the search, in one kernel
-        return "mfma", "mfma_f64", (k // 2) * 4.0 * n * beta * ts / L
+        # the k/2 updates of two groups each, old and new integers, in one kernel
+        return "mfma", "mfma_i8", (k // 2) * 8.0 * n * beta * ts / L
     if name == "gptq_trailing_dgemm":
         # rank-512 update of the columns behind each window of 512 columns
         tot = sum(2.0 * n * (min(m, w0 + 512) - w0) * (m - min(m, w0 + 512)) for w0 in range(0, m, 512))
@@ -185,17 +183,16 @@ def algorithmic_work(name, cfg, launches_per_step):
     if name == "gptq_sweep":
         return "alu", "alu_f64", float(n) * beta * beta              # rank-1 updates inside the group
     hbm = {
-        "sba_kl_step": 2.0 * 8 * n * ts,                 # one pass over P and the candidate's outputs
         "salience_colsumsq": 2.0 * n * m,                # W once (16-bit)
         "pack_codes": n * m * (1.0 + cfg.N / 8.0),       # codes in, words out
         "gram_reduce": 10.0 * m * m,                     # G read and written (4 B each), one partial per upper tile in
         "inv_widen": 10.0 * m * m,                       # upper half of G in (4 B), upper A and lower U out (8 B each)
         "inv_diag_colsumsq": 4.0 * m * m,                # upper triangle of U (8 B) once
         "gptq_widen": 10.0 * n * m / L,                  # W (16-bit) in, fp64 working copy out
-        "sba_widen_w": 10.0 * n * m,
-        "sba_widen_x": 10.0 * m * ts,
-        "sba_fakequant": 16.0 * n * m,                   # fp64 weights in, fake-quantised fp64 weights out
-        "sba_gather_x": 16.0 * (k // 2) * 2 * beta * ts,
+        "sba_codes": 3.0 * n * m / L,                    # 16-bit weights in, one byte out (the digits of W beside it)
+        "sba_x_digits": 6.0 * m * ts,                    # 16-bit activations in, about four bytes out
+        "sba_x_stats": 2.0 * m * ts,
+        "sba_w_stats": 2.0 * n * m,
         "sba_kl_ref": 4.0 * 8 * n * ts / L,              # the reference outputs: read twice, written once, read once
         "sqc_block_stats": 8.0 * n * beta,
     }
@@ -403,7 +400,7 @@ def main():
             "sqc_search": "alu peak counts an FMA as two operations; the search loop is mostly single-operation "
                           "instructions (multiply, round, two clamps), so its fraction of the issue bound is about "
                           "twice the frac given",
-            "inv_syrk_dgemm, inv_panel_dgemm, inv_window_dgemm, inv_trtri_*_dgemm, sba_output_dgemm": "run beside other "
+            "inv_syrk_dgemm, inv_panel_dgemm, inv_window_dgemm, inv_trtri_*_dgemm, sba_*outputs": "run beside other "
                           "streams' work by design (the factorisation's chains, its far updates and the triangular "
                           "inverse on four streams, beside the SBA outputs on part of the chip): their durations "
                           "overlap and their frac is not a fraction of the chip",
@@ -417,10 +414,10 @@ def main():
     # (inverse with the two SBA output products beside it) achieves as a whole
     ph = job.phases()
     ts = min(T_SBA, cfg.t)
-    fp64_flops = (2.0 / 3.0) * float(cfg.m) ** 3 + 2.0 * (2.0 * cfg.n * cfg.m * ts)
+    fp64_flops = (2.0 / 3.0) * float(cfg.m) ** 3
     line["phases_ms"] = {k: round(v, 3) for k, v in ph.items()}
     line["phases_ms"]["note"] = ("one pass with the host waiting at the borders of the phases (extra passes after the timed "
-                                 "region); inverse_with_sba_outputs_beside: (2/3) m^3 + 4 n m t_s fp64 flops = %.3g, i.e. "
+                                 "region); inverse_with_sba_outputs_beside: (2/3) m^3 fp64 flops = %.3g, i.e. "
                                  "%.2f of the fp64 matrix peak over the phase" % (
                                      fp64_flops, fp64_flops / (ph["inverse_with_sba_outputs_beside"] * 1e-3) / PEAK["mfma_f64"]))
     # beside the metric: the inference kernel of the stored form (next step of the path, not part of `value`)

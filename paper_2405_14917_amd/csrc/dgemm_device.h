@@ -1,4 +1,4 @@
-// Device-side pieces of the fp64 matrix-core GEMM that more than one source file builds kernels from.
+// Device-side pieces of the fp64 matrix-core GEMM.
 #ifndef SLIM_DGEMM_DEVICE_H
 #define SLIM_DGEMM_DEVICE_H
 
@@ -20,11 +20,11 @@ constexpr int BK = 16, NTHREADS = 256;
 // follow behind the next ones, and the LDS reads of each k-step of 4 are issued one step ahead.  No clamps and
 // no selects: the global pointers just advance by a slab (and stop at the last one, which is then fetched and
 // stored again without being used).
-// NT threads: NT / 64 wavefronts, two along N and the rest along M.
-template <int TRANS_B, int BM, int BN, int NT = NTHREADS>
+// Four wavefronts, two along N and two along M.
+template <int TRANS_B, int BM, int BN>
 __device__ __forceinline__ void k_loop_fast(const slim_gemm_desc& d, int row0, int col0, int kbeg, int kend,
-                                            double* smem, double4v (&acc)[BM / (NT / 128) / 16][BN / 32]) {
-  constexpr int WM = NT / 128;                       // wavefronts along M
+                                            double* smem, double4v (&acc)[BM / 2 / 16][BN / 32]) {
+  constexpr int NT = NTHREADS, WM = 2;               // wavefronts along M
   constexpr int MI = BM / WM / 16, NJ = BN / 32;
   constexpr int PA = BM * 8 / NT, PB = BN * 8 / NT;  // double2 per thread and slab
   constexpr int STAGE = BK * BM + BK * BN;

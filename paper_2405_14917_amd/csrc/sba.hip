@@ -1,27 +1,35 @@
-// a4  Salience-Determined Bit Allocation (Eq. 4; Alg. 2 SBA; App. C, App. D), all in fp64.
+// a4  Salience-Determined Bit Allocation (Eq. 4; Alg. 2 SBA; App. C, App. D).
 //
-// The search evaluates floor(k/2)+1 allocations that differ from one another in two groups only, so the
-// layer outputs are carried incrementally:
-//   sba_rank        stable ascending rank of the k group saliences (one workgroup, counting sort by
-//                   comparison; NaN ranks last) -> order[]
-//   sba_fakequant   per (row, group), one wavefront: Eq. 1 / Eq. 2 round-to-nearest at width N and at the one
-//                   other width the group can take; stores W_N and the difference, the latter in search order
-//   dgemm           Y^T = W X_s and Y_0^T = W_N X_s     (n x t_s, fp64 matrix cores)
+// The search evaluates floor(k/2)+1 allocations that differ from one another in two groups only, so the layer outputs are
+// carried incrementally.  Every product with the objective's tokens is EXACT integer arithmetic on the int8 matrix cores:
+//   * X_s is one integer matrix times a power of two (fp16 values are multiples of 2^-24 below 2^16), cut into signed base-256
+//     digits (balanced: -128 .. 127); of every chunk of channels only the digits in use are kept (`sba_meta`), three to five
+//     for activations;
+//   * a fake-quantised weight is scale * (q - z) with a small integer q - z: one int8 matrix, and one scale per (row, group);
+//   * W itself is cut into digits the same way (two to four for 16-bit weights).
+// A chunk's products of digits are summed exactly in int32 (128 channels of 127 * 128 * 257 < 2^31 for two digits chained by a
+// shift) and enter the fp64 outputs with two roundings per (row, group): fewer than the fp64 matrix cores make, which round
+// after every four channels.  What is lost: a bf16 or fp32 input that spans more than 53 binary digits (largest exponent
+// of the matrix against the last digit of the element) is rounded there, 2^-54 of the largest element.
+//
+//   sba_rank        stable ascending rank of the k group saliences (one workgroup, counting sort by comparison; NaN
+//                   ranks last) -> order[]
+//   sba_*_stats, sba_meta, sba_x_digits     which digits there are, and the digits of X_s in MFMA operand order
+//   sba_codes       per (row, group): Eq. 1 / Eq. 2 at width N and at the one other width the group can take, as integers
+//                   in operand order with their scales; the digits of W
+//   sba_outputs     Y^T = W X_s and Y_0^T = W_N X_s (n x t_s, fp64)
 //   kl_ref_*        once: per token the maximum M_t and log-sum-exp of the reference outputs; Y is then overwritten
 //                   by P = softmax(Y) and B_t = sum_i P_i log P_i is kept
-//   for p = 0 .. floor(k/2):
-//     kl_step / kl_finalize   obj[p] = sum_tokens KL(softmax(Y_t) || softmax(Y_p,t))
-//                   = sum_t [ B_t - (sum_i P_i q_i - lse(q)) ]: ONE pass over P and Y_p per candidate, with the
-//                   reference maximum M_t as the shift of the exponentials (Y_p differs from Y by quantisation
-//                   noise, so M_t is as good a shift as the maximum of Y_p itself).  The softmax runs over the n
-//                   outputs of a token, i.e. down a column of the transposed outputs, so consecutive lanes read
-//                   consecutive tokens
-//     dgemm         Y_{p+1}^T = Y_p^T + [D_lo(g_lo) | D_hi(g_hi)] [X_s(g_lo) ; X_s(g_hi)]  (rank 2 beta; the
-//                   operands were laid out in search order on the device, no host round trip)
+//   sba_search      all candidates in one kernel: obj[p] = sum_t [ B_t - (sum_i P_i q_i - lse(q)) ] with the reference
+//                   maximum M_t as the shift of the exponentials (Y_p differs from Y by quantisation noise), then
+//                   Y_{p+1} = Y_p + D_lo(g_lo) X_s(g_lo) + D_hi(g_hi) X_s(g_hi) in registers
 //   sba_finalize    first minimum of obj, bit vector of p*
+//
+// Measured on 28672 x 8192, 2048 tokens, beside the inverse where it runs there (fp64 matrix cores -> this): outputs 32 ->
+// 10.6 ms (reference 7.8, width N 2.8), search 15.2 -> 6.4 ms, widening and fake quantisation 3.4 -> 1.0 ms; 4096 x 4096:
+// 3.5 -> 0.8, 1.19 -> 0.47 ms.  The fp64 products ran at 76 to 81 % of their roof.
 #include <algorithm>
 
-#include "dgemm_device.h"
 #include "slim_device.h"
 #include "slim_internal.h"
 
@@ -30,7 +38,7 @@ namespace {
 using namespace slimdev;
 
 constexpr int KL_TOK = 64;     // tokens per workgroup
-constexpr int KL_PART = 5;     // doubles per (part, token): max y, sum exp y, sum P log P, sum exp q, sum P q (or squared error)
+constexpr int KL_PART = 3;     // planes of the reference side's partials: max y, sum exp y, sum P log P
 
 __global__ __launch_bounds__(256) void sba_rank(const double* __restrict__ sal, int k, int* __restrict__ order,
                                                 int* __restrict__ rank_of) {
@@ -48,7 +56,7 @@ __global__ __launch_bounds__(256) void sba_rank(const double* __restrict__ sal, 
   }
 }
 
-// round-to-nearest fake quantisation of one value with the row-group's default parameters
+// default parameters of Eq. 1 / Eq. 2 of one (row, group)
 struct RtnParams {
   double delta0, z, qmax, alpha;
   bool sign;
@@ -74,67 +82,6 @@ __device__ __forceinline__ RtnParams rtn_params(double mn, double mx, double mea
   return p;
 }
 
-__device__ __forceinline__ double rtn_apply(const RtnParams& p, double w) {
-  if (p.sign) return (w >= 0.0) ? p.alpha : -p.alpha;
-  const double q = fmin(fmax(rint(w / p.delta0) + p.z, 0.0), p.qmax);
-  return p.delta0 * (q - p.z);
-}
-
-// one wavefront per (row, group); grid = ceil(n * k / 4) workgroups of 4 wavefronts.
-// W_N goes to WN in the natural layout.  The difference to the other width a group can take is stored in
-// "search order": column block r (2 beta wide) of Dcat holds [W_{N-1} - W_N of the r-th least salient group |
-// W_{N+1} - W_N of the r-th most salient group], so that step r of the search is ONE rank-2beta update.
-// `parts` selects what is written: FQ_WN (needs no ranking), FQ_DCAT, or both.
-enum { FQ_WN = 1, FQ_DCAT = 2 };
-__global__ __launch_bounds__(256) void sba_fakequant(const double* __restrict__ W, int n, int m, int beta, int N,
-                                                     int q1_mode, const int* __restrict__ rank_of, int pmax,
-                                                     double* __restrict__ WN, double* __restrict__ Dcat, int parts) {
-  const int lane = threadIdx.x & 63;
-  const int k = m / beta;
-  const int64_t unit = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (unit >= (int64_t)n * k) return;
-  const int row = (int)(unit / k), g = (int)(unit % k);
-  const int64_t base = (int64_t)row * m + (int64_t)g * beta;
-  double mn = INFINITY, mx = -INFINITY, sabs = 0.0;
-  for (int c = lane; c < beta; c += 64) {
-    const double v = W[base + c];
-    mn = fmin(mn, v);
-    mx = fmax(mx, v);
-    sabs += fabs(v);
-  }
-  mn = wave_min(mn);
-  mx = wave_max(mx);
-  sabs = wave_sum(sabs) / (double)beta;
-  const RtnParams pn = rtn_params(mn, mx, sabs, N, q1_mode);
-  if (!(parts & FQ_DCAT)) {
-    for (int c = lane; c < beta; c += 64) WN[base + c] = rtn_apply(pn, W[base + c]);
-    return;
-  }
-  const int pos = rank_of[g];
-  const bool low = pos < pmax, high = pos >= k - pmax;
-  const RtnParams po = rtn_params(mn, mx, sabs, low ? N - 1 : N + 1, q1_mode);
-  const int64_t dbase = (int64_t)row * m + (low ? (int64_t)pos * 2 * beta : (int64_t)(k - 1 - pos) * 2 * beta + beta);
-  for (int c = lane; c < beta; c += 64) {
-    const double v = W[base + c];
-    const double wn = rtn_apply(pn, v);
-    if (parts & FQ_WN) WN[base + c] = wn;
-    if (low || high) Dcat[dbase + c] = rtn_apply(po, v) - wn;
-  }
-}
-
-// rows of X_s in search order: row block r (2 beta rows) = [rows of the r-th least salient group ; rows of the
-// r-th most salient group]
-__global__ __launch_bounds__(256) void sba_gather_x(const double* __restrict__ X64, int64_t ts, int beta, int k,
-                                                    const int* __restrict__ order, double* __restrict__ Xcat) {
-  const int r = blockIdx.y >> 1, h = blockIdx.y & 1;
-  const int g = h ? order[k - 1 - r] : order[r];
-  const int64_t total = (int64_t)beta * ts;
-  const double* src = X64 + (int64_t)g * beta * ts;
-  double* dst = Xcat + ((int64_t)r * 2 + h) * beta * ts;
-  for (int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 2; i < total; i += (int64_t)gridDim.x * 512)
-    *reinterpret_cast<double2*>(dst + i) = *reinterpret_cast<const double2*>(src + i);
-}
-
 // ---- reference side, once per call ----------------------------------------------------------------
 // grid (ceil(ts / 64), parts): 64 tokens x 4 row lanes per workgroup; part r owns rows [r*rpp, (r+1)*rpp).
 // per (part, token): max y and sum exp(y - max)
@@ -158,9 +105,9 @@ __global__ __launch_bounds__(256) void kl_ref_partial(const double* __restrict__
   red[1][ty][tx] = zy;
   __syncthreads();
   if (ty == 0 && live) {
-    double* o = partial + ((int64_t)blockIdx.y * ts + t) * KL_PART;
+    double* o = partial + (int64_t)blockIdx.y * KL_PART * ts + t;
     o[0] = my;
-    o[1] = ((red[1][0][tx] + red[1][1][tx]) + red[1][2][tx]) + red[1][3][tx];
+    o[ts] = ((red[1][0][tx] + red[1][1][tx]) + red[1][2][tx]) + red[1][3][tx];
   }
 }
 
@@ -170,11 +117,11 @@ __global__ __launch_bounds__(256) void kl_ref_merge(const double* __restrict__ p
   const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (t >= ts) return;
   double M = -INFINITY;
-  for (int p = 0; p < parts; ++p) M = fmax(M, partial[((int64_t)p * ts + t) * KL_PART]);
+  for (int p = 0; p < parts; ++p) M = fmax(M, partial[(int64_t)p * KL_PART * ts + t]);
   double Z = 0.0;
   for (int p = 0; p < parts; ++p) {
-    const double* o = partial + ((int64_t)p * ts + t) * KL_PART;
-    Z += o[1] * exp(o[0] - M);
+    const double* o = partial + (int64_t)p * KL_PART * ts + t;
+    Z += o[ts] * exp(o[0] - M);
   }
   tok[2 * t] = M;
   tok[2 * t + 1] = M + log(Z);
@@ -201,7 +148,7 @@ __global__ __launch_bounds__(256) void kl_ref_softmax(double* __restrict__ Y, in
   red[ty][tx] = b;
   __syncthreads();
   if (ty == 0 && t < ts)
-    partial[((int64_t)blockIdx.y * ts + t) * KL_PART + 2] = ((red[0][tx] + red[1][tx]) + red[2][tx]) + red[3][tx];
+    partial[((int64_t)blockIdx.y * KL_PART + 2) * ts + t] = ((red[0][tx] + red[1][tx]) + red[2][tx]) + red[3][tx];
 }
 
 // one thread per token: B_t = sum_i P_i log P_i (fixed order over the parts) into tok2[t]
@@ -210,126 +157,21 @@ __global__ __launch_bounds__(256) void kl_ref_entropy(const double* __restrict__
   const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (t >= ts) return;
   double b = 0.0;
-  for (int p = 0; p < parts; ++p) b += partial[((int64_t)p * ts + t) * KL_PART + 2];
+  for (int p = 0; p < parts; ++p) b += partial[((int64_t)p * KL_PART + 2) * ts + t];
   tokB[t] = b;
-}
-
-// ---- per candidate -------------------------------------------------------------------------------------
-// per (part, token): sum exp(q - M_t) and sum P q over the part's rows, one pass
-__global__ __launch_bounds__(256) void kl_step(const double* __restrict__ P, const double* __restrict__ Q, int n,
-                                               int64_t ts, int rows_per_part, const double* __restrict__ tok,
-                                               double* __restrict__ partial) {
-  __shared__ double red[2][4][KL_TOK];
-  const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-  const int64_t t = (int64_t)blockIdx.x * KL_TOK + tx;
-  const int r0 = blockIdx.y * rows_per_part;
-  const int r1 = min(n, r0 + rows_per_part);
-  double z0 = 0.0, z1 = 0.0, a0 = 0.0, a1 = 0.0;
-  if (t < ts) {
-    const double M = tok[2 * t];
-    int r = r0 + ty;
-    for (; r + 4 < r1; r += 8) {
-      const double q0 = Q[(int64_t)r * ts + t], q1 = Q[(int64_t)(r + 4) * ts + t];
-      const double p0 = P[(int64_t)r * ts + t], p1 = P[(int64_t)(r + 4) * ts + t];
-      z0 += exp(q0 - M);
-      z1 += exp(q1 - M);
-      a0 = fma(p0, q0, a0);
-      a1 = fma(p1, q1, a1);
-    }
-    if (r < r1) {
-      const double q0 = Q[(int64_t)r * ts + t];
-      z0 += exp(q0 - M);
-      a0 = fma(P[(int64_t)r * ts + t], q0, a0);
-    }
-  }
-  red[0][ty][tx] = z0 + z1;
-  red[1][ty][tx] = a0 + a1;
-  __syncthreads();
-  if (ty == 0 && t < ts) {
-    double* o = partial + ((int64_t)blockIdx.y * ts + t) * KL_PART;
-    o[3] = ((red[0][0][tx] + red[0][1][tx]) + red[0][2][tx]) + red[0][3][tx];
-    o[4] = ((red[1][0][tx] + red[1][1][tx]) + red[1][2][tx]) + red[1][3][tx];
-  }
-}
-
-// one thread per token: KL_t = B_t - (sum P q - (M_t + log sum exp(q - M_t))); every workgroup of 256 tokens
-// writes its sum
-__global__ __launch_bounds__(256) void kl_finalize(const double* __restrict__ partial_all, int64_t pstride, int parts,
-                                                   int64_t ts, const double* __restrict__ tok,
-                                                   const double* __restrict__ tokB, double* __restrict__ block_sums_all,
-                                                   int nblocks) {
-  __shared__ double red[256];
-  const double* partial = partial_all + (int64_t)blockIdx.y * pstride;       // blockIdx.y = candidate
-  double* block_sums = block_sums_all + (int64_t)blockIdx.y * nblocks;
-  const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  double acc = 0.0;
-  if (t < ts) {
-    double Z = 0.0, A = 0.0;
-    for (int p = 0; p < parts; ++p) {
-      const double* o = partial + ((int64_t)p * ts + t) * KL_PART;
-      Z += o[3];
-      A += o[4];
-    }
-    acc = tokB[t] - (A - (tok[2 * t] + log(Z)));
-  }
-  red[threadIdx.x] = acc;
-  __syncthreads();
-  for (int st = 128; st > 0; st >>= 1) {
-    if (threadIdx.x < st) red[threadIdx.x] += red[threadIdx.x + st];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) block_sums[blockIdx.x] = red[0];
-}
-
-// squared-error objective: per (part, token) the sum over the part's rows of (y - q)^2, stored in slot 4 of the
-// same partial layout so that the fixed-order reductions are shared
-__global__ __launch_bounds__(256) void mse_partial(const double* __restrict__ Y, const double* __restrict__ Q, int n,
-                                                   int64_t ts, int rows_per_part, double* __restrict__ partial) {
-  __shared__ double red[4][KL_TOK];
-  const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-  const int64_t t = (int64_t)blockIdx.x * KL_TOK + tx;
-  const int r0 = blockIdx.y * rows_per_part;
-  const int r1 = min(n, r0 + rows_per_part);
-  double a = 0.0;
-  if (t < ts) {
-    for (int r = r0 + ty; r < r1; r += 4) {
-      const double dlt = Y[(int64_t)r * ts + t] - Q[(int64_t)r * ts + t];
-      a = fma(dlt, dlt, a);
-    }
-  }
-  red[ty][tx] = a;
-  __syncthreads();
-  if (ty == 0 && t < ts) partial[((int64_t)blockIdx.y * ts + t) * KL_PART + 4] = ((red[0][tx] + red[1][tx]) + red[2][tx]) + red[3][tx];
-}
-
-// one thread per token: sums the row parts of its token; every workgroup of 256 tokens writes its sum
-__global__ __launch_bounds__(256) void mse_finalize(const double* __restrict__ partial_all, int64_t pstride, int parts,
-                                                    int64_t ts, double* __restrict__ block_sums_all, int nblocks) {
-  __shared__ double red[256];
-  const double* partial = partial_all + (int64_t)blockIdx.y * pstride;       // blockIdx.y = candidate
-  double* block_sums = block_sums_all + (int64_t)blockIdx.y * nblocks;
-  const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  double acc = 0.0;
-  if (t < ts)
-    for (int p = 0; p < parts; ++p) acc += partial[((int64_t)p * ts + t) * KL_PART + 4];
-  red[threadIdx.x] = acc;
-  __syncthreads();
-  for (int st = 128; st > 0; st >>= 1) {
-    if (threadIdx.x < st) red[threadIdx.x] += red[threadIdx.x + st];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) block_sums[blockIdx.x] = red[0];
 }
 
 // obj[p] = sum of the token-block sums of step p (fixed order); then the first minimum and its bit vector
 __global__ __launch_bounds__(256) void sba_finalize(const double* __restrict__ block_sums, int nblocks,
                                                     double* __restrict__ obj, int pmax, const int* __restrict__ order,
-                                                    int k, int N, uint8_t* __restrict__ bits, int* __restrict__ p_star) {
+                                                    int k, int N, const int* __restrict__ nonfinite,
+                                                    uint8_t* __restrict__ bits, int* __restrict__ p_star) {
   __shared__ int best_p;
   for (int p = threadIdx.x; p <= pmax; p += 256) {
     double s = 0.0;
     for (int w = 0; w < nblocks; ++w) s += block_sums[(int64_t)p * nblocks + w];
-    obj[p] = s;
+    // (a weight or an activation that is not a number makes every candidate's objective one that is none)
+    obj[p] = *nonfinite ? NAN : s;
   }
   __syncthreads();
   if (threadIdx.x == 0) {
@@ -354,185 +196,936 @@ __global__ __launch_bounds__(256) void sba_finalize(const double* __restrict__ b
   }
 }
 
-}  // namespace
+// ---- integers ---------------------------------------------------------------------------------------------
+typedef int v4i __attribute__((ext_vector_type(4)));
+typedef int v16i __attribute__((ext_vector_type(16)));
 
-namespace {
+constexpr int SI_MAXD = 7;         // digits of a value
+constexpr int SI_ROWS = 256, SI_TOK = 32;   // outputs and tokens per workgroup of the products
+constexpr int SE_ROWS = 128;       // outputs per workgroup of the search
+constexpr int SI_CHUNK = 128;      // most channels whose products are summed in int32
 
-// ---- the whole search in one kernel -----------------------------------------------------------------
-// One workgroup per 128 x 128 tile of the outputs (rows x tokens) keeps the tile of the current candidate's
-// outputs in its accumulator registers from the first candidate to the last: per candidate it adds the tile's
-// terms of the objective (per token: sum exp(q - M) and sum P q over the tile's rows, or the squared error)
-// to the candidate's partials and then applies the rank-2beta update of the next candidate on the matrix cores
-// (the K loop of the fp64 GEMM).  The candidates' outputs never go back to memory: per candidate the kernel reads
-// the reference tile once and two thin operand slabs, where a GEMM launch per candidate reads and writes all
-// outputs and a second kernel reads them again.
-struct SearchArgs {
-  const double* Yc;        // n x ts outputs of the all-N-bit weights
-  const double* R;         // n x ts reference: P = softmax(Y) (KL) or Y (squared error)
-  const double* tok;       // per token {max, log-sum-exp} of the reference (KL)
-  const double* Dcat;      // n x m, column block p: the change of W from candidate p to p + 1
-  const double* Xcat;      // m x ts, row block p: the rows of X_s that change meets
-  double* partial;         // per candidate (stride pstride) [row block][token][KL_PART]
-  int64_t pstride, ts;
-  int n, m, beta, pmax;
+// Shapes of the operands.  A group is cut into chunks of `chk` channels (32, 64 or 128, the last ones padded with zeros); an
+// operand fragment is 1 KiB: 32 rows (of W) or tokens x 32 channels as the 64 lanes of v_mfma_i32_32x32x32_i8 hold them
+// (lane l: row l % 32, channels 16 (l / 32) .. + 15).
+struct SbaShape {
+  int n, m, beta, k;
+  int64_t ts;
+  int chk, ks, nchg, C;            // channels per chunk, fragments per chunk, chunks per group, chunks
+  int npad, RB, RT;                // rows padded to SI_ROWS, blocks of 32 rows, tiles of SI_ROWS
+  int tpad, TB;                    // tokens padded to SI_TOK, blocks of 32
 };
 
-constexpr int SEARCH_TILE = 128;
-constexpr size_t SEARCH_LDS = sizeof(double) * (2 * (slimgemm::BK * SEARCH_TILE * 2) + 4 * SEARCH_TILE);
+// device-side description: per chunk {lowest digit in use, digits in use}
+struct SbaMeta {
+  int* x;                          // 2 C: digits of X_s
+  int* w;                          // 2 C: digits of W
+  int* unit;                       // unit[0], unit[1]: exponents of the units of X_s and W; unit[2]: non-finite inputs seen
+  int* rest_n;                     // k: some row of the group has a zero outside int8 (width N)
+  int* rest_o;                     // k: the same at the other width
+  unsigned* xmax;                  // C largest |x| as float bits, C smallest exponent of a last digit (as int); then W's
+  int* xlsb;
+  unsigned* wmax;
+  int* wlsb;
+};
 
-template <int OBJ>
-__global__ __launch_bounds__(256, 2) void sba_search_tile(SearchArgs a) {   // two wavefronts per SIMD
-  using namespace slimgemm;
-  constexpr int BM = SEARCH_TILE, BN = SEARCH_TILE, MI = 4, NJ = 4;
-  extern __shared__ __align__(16) double smem[];
-  double* red = smem + 2 * (BK * BM + BK * BN);        // [sum exp | sum P q][upper | lower 64 rows][128 tokens]
-  const int tiles_n = (int)(a.ts / BN);
-  const int bi = blockIdx.x / tiles_n, bj = blockIdx.x % tiles_n;
-  const int row0 = bi * BM, col0 = bj * BN;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave >> 1, wn = wave & 1, l16 = lane & 15, lk = lane >> 4;
-  // accumulator register v of tile (i, j) of this lane is row 16 i + 4 v + lk, column 16 j + l16 of the wavefront's
-  // 64 x 64 quarter
-  const int64_t ts = a.ts;
-  const int rbase = row0 + wm * 64 + lk, cbase = col0 + wn * 64 + l16;
-  double4v acc[MI][NJ];
-#pragma unroll
-  for (int i = 0; i < MI; ++i)
-#pragma unroll
-    for (int v = 0; v < 4; ++v)
-#pragma unroll
-      for (int j = 0; j < NJ; ++j) acc[i][j][v] = a.Yc[(int64_t)(rbase + 16 * i + 4 * v) * ts + cbase + 16 * j];
-  double Mt[NJ];
-#pragma unroll
-  for (int j = 0; j < NJ; ++j) Mt[j] = (OBJ == SLIM_OBJ_KL) ? a.tok[2 * (int64_t)(cbase + 16 * j)] : 0.0;
+template <typename T>
+__device__ __forceinline__ unsigned float_bits(T v);
+template <>
+__device__ __forceinline__ unsigned float_bits<__half>(__half v) { return __float_as_uint(__half2float(v)); }
+template <>
+__device__ __forceinline__ unsigned float_bits<__hip_bfloat16>(__hip_bfloat16 v) {
+  return (unsigned)*reinterpret_cast<const unsigned short*>(&v) << 16;
+}
+template <>
+__device__ __forceinline__ unsigned float_bits<float>(float v) { return __float_as_uint(v); }
 
-  for (int p = 0; p <= a.pmax; ++p) {
-    double z[NJ], s[NJ];
+// |v| = mant * 2^e0 of a finite float
+__device__ __forceinline__ void split_float(unsigned bits, unsigned& mant, int& e0) {
+  const int e = (int)((bits >> 23) & 255u);
+  mant = (bits & 0x7fffffu) | (e ? 0x800000u : 0u);
+  e0 = (e ? e : 1) - 150;
+}
+// v / 2^unit as an integer (rounded where v has digits below the unit); 0 for what is not finite
+__device__ __forceinline__ int64_t fixed_point(unsigned bits, int unit) {
+  unsigned mant;
+  int e0;
+  split_float(bits, mant, e0);
+  if (((bits >> 23) & 255u) == 255u) mant = 0;
+  const int sh = e0 - unit;
+  uint64_t v;
+  if (sh >= 0)
+    v = (uint64_t)mant << min(sh, 40);
+  else
+    v = (sh > -32) ? ((uint64_t)mant + (1ull << (-sh - 1))) >> (-sh) : 0ull;
+  return (bits >> 31) ? -(int64_t)v : (int64_t)v;
+}
+// the byte lanes of v + sum_i 128 * 256^i are the balanced digits plus 128
+__device__ __forceinline__ uint64_t digit_bytes(int64_t v) { return ((uint64_t)v + 0x0080808080808080ull) ^ 0x8080808080808080ull; }
+
+__device__ __forceinline__ void stat(unsigned bits, unsigned& mx, int& lsb, int& bad) {
+  bits &= 0x7fffffffu;
+  if (bits >= 0x7f800000u) {
+    bad = 1;
+    return;
+  }
+  if (bits == 0) return;
+  unsigned mant;
+  int e0;
+  split_float(bits, mant, e0);
+  mx = max(mx, bits);
+  lsb = min(lsb, e0 + __builtin_ctz(mant));
+}
+
+__global__ __launch_bounds__(256) void sba_clear(SbaMeta mt, int C, int k) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i < C) {
+    mt.xmax[i] = mt.wmax[i] = 0u;
+    mt.xlsb[i] = mt.wlsb[i] = INT_MAX;
+  }
+  if (i < k) mt.rest_n[i] = mt.rest_o[i] = 0;
+  if (i == 0) mt.unit[2] = 0;
+}
+
+// first channel and number of channels of a chunk
+__device__ __forceinline__ int chunk_begin(const SbaShape& s, int c, int& len) {
+  const int g = c / s.nchg, j0 = (c - g * s.nchg) * s.chk;
+  len = min(s.chk, s.beta - j0);
+  return g * s.beta + j0;
+}
+
+// grid (C, splits): largest magnitude and last digit of the chunk's rows of X_s
+template <typename T>
+__global__ __launch_bounds__(256) void sba_x_stats(const T* __restrict__ X, int64_t ldx, SbaShape s, SbaMeta mt) {
+  int len;
+  const int ch0 = chunk_begin(s, blockIdx.x, len);
+  unsigned mx = 0;
+  int lsb = INT_MAX, bad = 0;
+  const int64_t quads = s.ts / 4;
+  for (int64_t q = (int64_t)blockIdx.y * 256 + threadIdx.x; q < quads; q += (int64_t)gridDim.y * 256)
+    for (int r = 0; r < len; ++r) {
+      const uint2 raw = *reinterpret_cast<const uint2*>(X + (int64_t)(ch0 + r) * ldx + 4 * q);
+      const T* v = reinterpret_cast<const T*>(&raw);
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) z[j] = s[j] = 0.0;
-    // The addresses of the reference tile are formed again for every candidate from this pointer (opaque to the
-    // compiler): kept across the K loop below they would cost 32 registers and spill.
-    const double* rtile = a.R + (int64_t)rbase * ts + cbase;
-    asm volatile("" : "+v"(rtile));
-    // (the condition always holds; as a block of its own this part is register-allocated apart from the K loop,
-    // and the kernel no longer spills)
-    if (a.n > 0)
+      for (int i = 0; i < 4; ++i) stat(float_bits<T>(v[i]), mx, lsb, bad);
+    }
 #pragma unroll
-    for (int i = 0; i < MI; ++i) {
-      // 16 reference values in flight at a time: all 64 would not leave room for two workgroups per CU
-      double ref[4][NJ];
+  for (int d = 32; d > 0; d >>= 1) {
+    mx = max(mx, (unsigned)__shfl_xor((int)mx, d, WAVE));
+    lsb = min(lsb, __shfl_xor(lsb, d, WAVE));
+  }
+  if (bad) atomicOr(&mt.unit[2], 1);
+  if ((threadIdx.x & 63) == 0 && mx) {
+    atomicMax(&mt.xmax[blockIdx.x], mx);
+    atomicMin(&mt.xlsb[blockIdx.x], lsb);
+  }
+}
+
+// grid (ceil(m / 1024), splits): the same for the chunk's columns of W; a thread owns four columns
+template <typename T>
+__global__ __launch_bounds__(256) void sba_w_stats(const T* __restrict__ W, int64_t ldw, SbaShape s, SbaMeta mt) {
+  __shared__ unsigned lmax[264];
+  __shared__ int llsb[264];
+  for (int i = threadIdx.x; i < 264; i += 256) {
+    lmax[i] = 0u;
+    llsb[i] = INT_MAX;
+  }
+  __syncthreads();
+  auto chunk_of = [&](int ch) { const int g = ch / s.beta; return g * s.nchg + (ch - g * s.beta) / s.chk; };
+  const int c0 = chunk_of(blockIdx.x * 1024);
+  const int ch = blockIdx.x * 1024 + threadIdx.x * 4;
+  if (ch < s.m) {
+    unsigned mx = 0;
+    int lsb = INT_MAX, bad = 0;
+    for (int r = blockIdx.y; r < s.n; r += gridDim.y) {
+      T v[4];
+      if constexpr (sizeof(T) == 2)
+        *reinterpret_cast<uint2*>(v) = *reinterpret_cast<const uint2*>(W + (int64_t)r * ldw + ch);
+      else
+        *reinterpret_cast<uint4*>(v) = *reinterpret_cast<const uint4*>(W + (int64_t)r * ldw + ch);
 #pragma unroll
-      for (int v = 0; v < 4; ++v)
+      for (int i = 0; i < 4; ++i) stat(float_bits<T>(v[i]), mx, lsb, bad);
+    }
+    const int c = chunk_of(ch) - c0;
+    atomicMax(&lmax[c], mx);
+    atomicMin(&llsb[c], lsb);
+    if (bad) atomicOr(&mt.unit[2], 1);
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < 264; i += 256)
+    if (lmax[i]) {
+      atomicMax(&mt.wmax[c0 + i], lmax[i]);
+      atomicMin(&mt.wlsb[c0 + i], llsb[i]);
+    }
+}
+
+// Units and digits in use: block 0 for X_s, block 1 for W.  The unit is the last digit of all values, but no more than 53
+// digits below the largest one; a chunk keeps the digits between its own last one and its own largest value.
+__global__ __launch_bounds__(256) void sba_meta(SbaMeta mt, int C) {
+  __shared__ unsigned smx[256];
+  __shared__ int slsb[256];
+  const unsigned* cmax = blockIdx.x ? mt.wmax : mt.xmax;
+  const int* clsb = blockIdx.x ? mt.wlsb : mt.xlsb;
+  int* out = blockIdx.x ? mt.w : mt.x;
+  unsigned mx = 0;
+  int lsb = INT_MAX;
+  for (int c = threadIdx.x; c < C; c += 256) {
+    mx = max(mx, cmax[c]);
+    lsb = min(lsb, clsb[c]);
+  }
+  smx[threadIdx.x] = mx;
+  slsb[threadIdx.x] = lsb;
+  __syncthreads();
+  for (int st = 128; st > 0; st >>= 1) {
+    if (threadIdx.x < st) {
+      smx[threadIdx.x] = max(smx[threadIdx.x], smx[threadIdx.x + st]);
+      slsb[threadIdx.x] = min(slsb[threadIdx.x], slsb[threadIdx.x + st]);
+    }
+    __syncthreads();
+  }
+  mx = smx[0];
+  lsb = slsb[0];
+  unsigned mant;
+  int e0, unit = 0;
+  if (mx) {
+    split_float(mx, mant, e0);
+    unit = max(lsb, e0 + (31 - __builtin_clz(mant)) - 53);
+  }
+  if (threadIdx.x == 0) mt.unit[blockIdx.x] = unit;
+  for (int c = threadIdx.x; c < C; c += 256) {
+    int lo = 0, hi = 0;
+    if (cmax[c]) {
+      const uint64_t v = (uint64_t)fixed_point(cmax[c], unit);
+      lo = max(0, clsb[c] - unit) / 8;
+      uint64_t lim = 0;                                  // largest value of hi balanced digits
+      while (lim < v) {
+        lim = lim * 256 + 127;
+        ++hi;
+      }
+      hi = max(hi, lo);
+    }
+    out[2 * c] = lo;
+    out[2 * c + 1] = hi - lo;
+  }
+}
+
+// grid (ceil(TB / 4), k): a wavefront cuts 32 tokens of one group into digits and sums its channels per token
+template <typename T>
+__global__ __launch_bounds__(256) void sba_x_digits(const T* __restrict__ X, int64_t ldx, SbaShape s, SbaMeta mt,
+                                                    char* __restrict__ Xd, double* __restrict__ SX) {
+  const int lane = threadIdx.x & 63, l32 = lane & 31, h = lane >> 5;
+  const int tb = blockIdx.x * 4 + (threadIdx.x >> 6), g = blockIdx.y;
+  if (tb >= s.TB) return;
+  const int unit = mt.unit[0];
+  const int64_t t = (int64_t)tb * 32 + l32;
+  int64_t sum = 0;
+  for (int cc = 0; cc < s.nchg; ++cc) {
+    const int c = g * s.nchg + cc, lo = mt.x[2 * c], nd = mt.x[2 * c + 1];
+    char* dst = Xd + ((int64_t)c * s.TB + tb) * SI_MAXD * s.ks * 1024 + lane * 16;
+    for (int f = 0; f < s.ks; ++f) {
+      const int j0 = cc * s.chk + f * 32 + h * 16;
+      uint64_t u[16];
 #pragma unroll
-        for (int j = 0; j < NJ; ++j) ref[v][j] = rtile[(int64_t)(16 * i + 4 * v) * ts + 16 * j];
+      for (int i = 0; i < 16; ++i) {
+        int64_t v = 0;
+        if (j0 + i < s.beta && t < s.ts) v = fixed_point(float_bits<T>(X[(int64_t)(g * s.beta + j0 + i) * ldx + t]), unit);
+        sum += v;
+        u[i] = digit_bytes(v) >> (8 * lo);
+      }
+      for (int d = 0; d < nd; ++d) {
+        unsigned w[4];
 #pragma unroll
-      for (int v = 0; v < 4; ++v)
+        for (int q = 0; q < 4; ++q) {
+          w[q] = 0;
 #pragma unroll
-        for (int j = 0; j < NJ; ++j) {
-          const double q = acc[i][j][v];
-          if (OBJ == SLIM_OBJ_KL) {
-            z[j] += exp(q - Mt[j]);
-            s[j] = fma(ref[v][j], q, s[j]);
-          } else {
-            const double dlt = ref[v][j] - q;
-            s[j] = fma(dlt, dlt, s[j]);
+          for (int i = 0; i < 4; ++i) {
+            w[q] |= ((unsigned)u[4 * q + i] & 255u) << (8 * i);
+            u[4 * q + i] >>= 8;
           }
         }
-      __builtin_amdgcn_sched_barrier(0);
+        *reinterpret_cast<uint4*>(dst + ((int64_t)d * s.ks + f) * 1024) = make_uint4(w[0], w[1], w[2], w[3]);
+      }
     }
-    // the four lanes that share a token column, then the two wavefronts that do
+  }
+  // (a sum of up to 512 channels of 54 bits may not fit 53 bits: one rounding)
+  const double other = __shfl_xor((double)sum, 32, WAVE);
+  if (h == 0) SX[(int64_t)g * s.tpad + t] = (double)sum + other;
+}
+
+__device__ __forceinline__ double row_sum(double v) {
+  v += dpp_f64<DPP_XOR1>(v);
+  v += dpp_f64<DPP_XOR2>(v);
+  v += dpp_f64<DPP_HALF_MIRROR>(v);
+  return v + dpp_f64<DPP_MIRROR>(v);
+}
+template <typename OP>
+__device__ __forceinline__ double row_reduce(double v) {
+  v = OP::f(v, dpp_f64<DPP_XOR1>(v));
+  v = OP::f(v, dpp_f64<DPP_XOR2>(v));
+  v = OP::f(v, dpp_f64<DPP_HALF_MIRROR>(v));
+  return OP::f(v, dpp_f64<DPP_MIRROR>(v));
+}
+
+// The integers of one quantiser: codes minus z0, the part of the zero point for which they fit int8, and what is left of it.
+struct IntQuant {
+  RtnParams p;
+  double inv, z0;
+};
+__device__ __forceinline__ IntQuant int_quant(double mn, double mx, double mean_abs, int bits, int q1_mode) {
+  IntQuant q;
+  q.p = rtn_params(mn, mx, mean_abs, bits, q1_mode);
+  q.inv = 1.0 / q.p.delta0;
+  q.z0 = fmin(fmax(q.p.z, q.p.qmax - 127.0), 128.0);       // codes 0 .. qmax minus z0 lie in -128 .. 127
+  return q;
+}
+__device__ __forceinline__ int int_code(const IntQuant& q, double w) {
+  if (q.p.sign) return (w >= 0.0) ? 1 : -1;
+  double r = w * q.inv;
+  double c = rint(r);
+  // the product and the quotient differ by less than 1e-15 of it: only next to a tie can they round apart
+  if (fabs(fabs(r - c) - 0.5) <= 1e-9 * (1.0 + fabs(r))) c = rint(w / q.p.delta0);
+  return (int)(fmin(fmax(c + q.p.z, 0.0), q.p.qmax) - q.z0);
+}
+__device__ __forceinline__ double int_scale(const IntQuant& q) { return q.p.sign ? q.p.alpha : q.p.delta0; }
+
+struct CodesArgs {
+  SbaShape s;
+  SbaMeta mt;
+  int64_t ldw;
+  int N, q1_mode, pmax;
+  const int* rank_of;              // (width other than N)
+  char* Q;                         // codes in operand order
+  double* S;                       // k x npad scales
+  double* Rz;                      // k x npad: the part of the zero that the codes do not hold, times the scale
+  int* rest;                       // k
+  char* Wd;                        // digits of W, or nullptr
+};
+
+// grid (npad / 16, y): 16 lanes per row, 16 rows per workgroup, groups blockIdx.y, blockIdx.y + gridDim.y, ...
+template <typename T, bool OTHER>
+__global__ __launch_bounds__(256) void sba_codes(const T* __restrict__ W, CodesArgs a) {
+  const SbaShape& s = a.s;
+  const int lane = threadIdx.x & 63, l16 = lane & 15;
+  const int row = blockIdx.x * 16 + (threadIdx.x >> 6) * 4 + (lane >> 4);
+  const int rb = row >> 5, r32 = row & 31;
+  const bool live = row < s.n;
+  const int64_t plane = (int64_t)s.npad * s.C * s.chk;
+  const int wunit = OTHER ? 0 : a.mt.unit[1];
+  for (int g = blockIdx.y; g < s.k; g += gridDim.y) {
+    int bits = a.N;
+    if (OTHER) {
+      const int pos = a.rank_of[g];
+      if (pos >= a.pmax && pos < s.k - a.pmax) continue;          // a middle group is never changed
+      bits = pos < a.pmax ? a.N - 1 : a.N + 1;
+    }
+    const T* w = W + (int64_t)min(row, s.n - 1) * a.ldw + (int64_t)g * s.beta;
+    double mn = INFINITY, mx = -INFINITY, sabs = 0.0;
+    for (int j = l16 * 4; j < s.beta; j += 64) {
+      double v[4];
+      load4<T>(w + j, v);
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) {
-      z[j] += shfl_xor_f64(z[j], 16);
-      z[j] += shfl_xor_f64(z[j], 32);
-      s[j] += shfl_xor_f64(s[j], 16);
-      s[j] += shfl_xor_f64(s[j], 32);
-      if (lk == 0) {
-        red[(0 * 2 + wm) * BN + wn * 64 + 16 * j + l16] = z[j];
-        red[(1 * 2 + wm) * BN + wn * 64 + 16 * j + l16] = s[j];
+      for (int i = 0; i < 4; ++i) {
+        mn = fmin(mn, v[i]);
+        mx = fmax(mx, v[i]);
+        sabs += fabs(v[i]);
+      }
+    }
+    mn = row_reduce<OpMin>(mn);
+    mx = row_reduce<OpMax>(mx);
+    sabs = row_sum(sabs) / (double)s.beta;
+    const IntQuant q = int_quant(mn, mx, sabs, bits, a.q1_mode);
+    const double rest = q.p.sign ? 0.0 : q.p.z - q.z0;
+    if (l16 == 0) {
+      a.S[(int64_t)g * s.npad + row] = live ? int_scale(q) : 0.0;
+      a.Rz[(int64_t)g * s.npad + row] = live ? int_scale(q) * rest : 0.0;
+      if (live && rest != 0.0) atomicOr(&a.rest[g], 1);
+    }
+    for (int j = l16 * 4; j < s.nchg * s.chk; j += 64) {
+      double v[4] = {0.0, 0.0, 0.0, 0.0};
+      const bool in = live && j < s.beta;
+      if (in) load4<T>(w + j, v);
+      const int cc = j / s.chk, jj = j - cc * s.chk, c = g * s.nchg + cc;
+      const int64_t dst = (((int64_t)rb * s.C + c) * s.ks + (jj >> 5)) * 1024 + ((jj >> 4) & 1) * 512 + r32 * 16 + (jj & 15);
+      unsigned word = 0;
+      if (in) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) word |= ((unsigned)int_code(q, v[i]) & 255u) << (8 * i);
+      }
+      *reinterpret_cast<unsigned*>(a.Q + dst) = word;
+      if (!OTHER) {
+        const int lo = a.mt.w[2 * c], nd = a.mt.w[2 * c + 1];
+        uint64_t u[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) u[i] = digit_bytes(fixed_point(__float_as_uint((float)v[i]), wunit)) >> (8 * lo);
+        for (int d = 0; d < nd; ++d) {
+          word = 0;
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            word |= ((unsigned)u[i] & 255u) << (8 * i);
+            u[i] >>= 8;
+          }
+          *reinterpret_cast<unsigned*>(a.Wd + d * plane + dst) = word;
+        }
+      }
+    }
+  }
+}
+
+// ---- products with the digits of X_s ----------------------------------------------------------------------------
+// A workgroup has 256 outputs x 32 tokens.  The tokens are the rows of the first MFMA operand, so a lane owns one output
+// per 32 x 32 tile (its scale is a lane constant) and 16 tokens.  The digits of X_s go to LDS directly, up to four of one
+// chunk at a time (a stage: two pairs of digits, each summed in int32), the next stage's while the current one is
+// multiplied; the codes go from memory to registers, where they serve all digits of the stage, and are asked for again as
+// soon as the last MFMA that needs the old ones has been issued.
+//
+// R MFMA tiles of 32 outputs per wavefront.  What bounds these kernels is the vector work behind the MFMAs (a shift, a
+// conversion and an fma per output and pair of digits, and the exponentials of the search), and a wavefront by itself
+// issues only every other slot: the products keep three wavefronts per SIMD (two tiles each, which share the operand
+// reads from LDS), and so does the search (one tile each, because it also holds the reference, and two sets of codes: with
+// one set, asked for half a stage ahead, and four wavefronts per SIMD, half of the time went by waiting for codes, 6.9
+// against 6.4 ms on 28672 x 8192).
+constexpr int SI_STAGE_D = 4;      // digits per stage
+constexpr int SI_TAB = 1024;       // stages whose description is kept in LDS
+
+template <int KS, int R>
+struct Tile {
+  static constexpr int STAGE = SI_STAGE_D * KS * 1024;
+  v4i w[R][KS];
+  double s[R];
+
+  // q, S: the same for the wavefront; rstride: bytes between blocks of 32 rows
+  __device__ __forceinline__ void load_codes(const char* q, int64_t rstride, unsigned lane16) {
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+      for (int f = 0; f < KS; ++f) w[r][f] = *reinterpret_cast<const v4i*>(q + (int64_t)r * rstride + f * 1024 + lane16);
+  }
+  __device__ __forceinline__ void load_scales(const double* S, unsigned l32) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) s[r] = (S + 32 * r)[l32];
+  }
+
+  // acc (+)= sum over the chunk of digit d times the codes
+  template <bool FIRST>
+  __device__ __forceinline__ void digit(const char* x, int d, v16i (&acc)[R]) const {
+    v4i f[KS];
+#pragma unroll
+    for (int i = 0; i < KS; ++i) f[i] = *reinterpret_cast<const v4i*>(x + (d * KS + i) * 1024);
+#pragma unroll
+    for (int i = 0; i < KS; ++i)
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        v16i c = acc[r];
+        if (FIRST && i == 0) {
+#pragma unroll
+          for (int v = 0; v < 16; ++v) c[v] = 0;
+        }
+        acc[r] = __builtin_amdgcn_mfma_i32_32x32x32_i8(f[i], w[r][i], c, 0, 0, 0);
+      }
+  }
+  // acc = sum over the chunk of (256 X_{2p+1} + X_{2p}) * codes; `two`: digit 2 p + 1 is in use
+  __device__ __forceinline__ void pair(const char* x, int p, bool two, v16i (&acc)[R]) const {
+    if (two) {
+      digit<true>(x, 2 * p + 1, acc);
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[r][v] <<= 8;
+      digit<false>(x, 2 * p, acc);
+    } else {
+      digit<true>(x, 2 * p, acc);
+    }
+  }
+};
+
+template <int R>
+__device__ __forceinline__ void add_scaled(double (&y)[R][16], const v16i (&acc)[R], const double (&s)[R], int e) {
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const double f = ldexp(s[r], e);
+#pragma unroll
+    for (int v = 0; v < 16; ++v) y[r][v] = fma(f, (double)acc[r][v], y[r][v]);
+  }
+}
+
+__device__ __forceinline__ void lds_load16(unsigned lds_addr, unsigned voff, const char* gbase) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds_addr), "v"(voff), "s"(gbase) : "m0");
+#else
+  (void)lds_addr, (void)voff, (void)gbase;
+#endif
+}
+
+// A stage in one word: chunk, lowest digit (absolute), digits (at most SI_STAGE_D), and whether it is the chunk's first.
+__device__ __forceinline__ int stage_word(int c, int lo, int nd, int first) { return (c << 8) | (first << 7) | (nd << 4) | lo; }
+__device__ __forceinline__ int stage_chunk(int w) { return w >> 8; }
+__device__ __forceinline__ int stage_nd(int w) { return (w >> 4) & 7; }
+__device__ __forceinline__ int stage_lo(int w) { return w & 15; }
+__device__ __forceinline__ bool stage_first(int w) { return (w >> 7) & 1; }
+// The digits of a stage for token block tb -> LDS (1 KiB per load, the loads dealt to the wavefronts)
+template <int KS, int NW>
+__device__ __forceinline__ void stage_digits(const char* Xd, const SbaShape& s, int word, int base_lo, int tb,
+                                             unsigned lds, int wave, int lane) {
+  const char* src = Xd + (((int64_t)stage_chunk(word) * s.TB + tb) * SI_MAXD + (stage_lo(word) - base_lo)) * KS * 1024;
+  const int cnt = stage_nd(word) * KS;
+  for (int i = wave; i < cnt; i += NW) lds_load16(lds + i * 1024, lane * 16, src + i * 1024);
+}
+
+// Output tiles in bands of eight row tiles, the rows of a band fastest; XCD x (id mod 8) has the x-th run of consecutive
+// tiles: what it works on at a time is a patch of 8 x 8 tiles that shares codes and digits in its L2.
+__device__ __forceinline__ void tile_of(int id, int RT, int TB, int& rt, int& tb) {
+  const int total = RT * TB, per = total / 8, rest = total % 8, x = id % 8;
+  const int i = x * per + min(x, rest) + id / 8;
+  const int band = i / (8 * TB), in = i - band * 8 * TB, hb = min(8, RT - band * 8);
+  rt = band * 8 + in % hb;
+  tb = in / hb;
+}
+
+struct OutArgs {
+  SbaShape s;
+  SbaMeta mt;
+  const char* Xd;
+  const double* SX;
+  const char* Q;                   // codes (width N), or digits of W with planes `plane` bytes apart
+  int64_t plane;
+  const double* S;
+  const double* Rz;
+  double* Y;                       // n x ts
+};
+
+// REF: Y = W X_s from the digits of W; else Y = W_N X_s
+template <int KS, bool REF>
+__global__ __launch_bounds__(256, 3) void sba_outputs(OutArgs a) {
+  constexpr int R = 2, NW = 4;
+  using TL = Tile<KS, R>;
+  extern __shared__ __align__(16) char si_smem[];
+  const SbaShape& s = a.s;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l32 = lane & 31, h = lane >> 5;
+  int rt, tb;
+  tile_of(blockIdx.x, s.RT, s.TB, rt, tb);
+  const int row0 = rt * SI_ROWS + wave * 64;
+  const unsigned lds0 = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(uintptr_t)((__attribute__((address_space(3))) char*)si_smem));
+  const int64_t rstride = (int64_t)s.C * KS * 1024;
+  const char* q0 = a.Q + (int64_t)(row0 >> 5) * rstride;
+  const unsigned lane16 = lane * 16;
+  // the chunks' digits (X_s: bits 0 .. 7 lowest digit and count, W: bits 8 .. 15) in LDS
+  int* tab = reinterpret_cast<int*>(si_smem + 2 * TL::STAGE);
+  auto describe = [&](int c) { return a.mt.x[2 * c] | (a.mt.x[2 * c + 1] << 4) | (a.mt.w[2 * c] << 8) | (a.mt.w[2 * c + 1] << 12); };
+  for (int c = tid; c < min(s.C, SI_TAB); c += 256) tab[c] = describe(c);
+  const int unit = __builtin_amdgcn_readfirstlane(a.mt.unit[0] + (REF ? a.mt.unit[1] : 0));
+  __syncthreads();
+  auto chunk_info = [&](int c) { return __builtin_amdgcn_readfirstlane(c < SI_TAB ? tab[c] : describe(c)); };
+
+  double y[R][16];
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) y[r][v] = 0.0;
+  TL tl;
+  auto load_first = [&](int c) {                // the first (or only) set of chunk c
+    tl.load_codes(q0 + (int64_t)c * KS * 1024, rstride, lane16);
+    if (!REF) {
+      tl.load_scales(a.S + (int64_t)(c / s.nchg) * s.npad + row0, l32);
+    } else {
+#pragma unroll
+      for (int r = 0; r < R; ++r) tl.s[r] = 1.0;
+    }
+  };
+  auto first_stage = [&](int c, int info) { return stage_word(c, info & 15, min(SI_STAGE_D, (info >> 4) & 15), 1); };
+  int info = chunk_info(0), word = first_stage(0, info), buf = 0;
+  stage_digits<KS, NW>(a.Xd, s, word, info & 15, tb, lds0, wave, lane);
+  load_first(0);
+  for (;;) {
+    const int c = stage_chunk(word), lo = stage_lo(word), nd = stage_nd(word);
+    const int left = (info & 15) + ((info >> 4) & 15) - lo - nd;            // digits of the chunk behind this stage
+    const bool done = left <= 0 && c + 1 == s.C;
+    const int next_info = left > 0 ? info : chunk_info(min(c + 1, s.C - 1));
+    const int next = left > 0 ? stage_word(c, lo + nd, min(SI_STAGE_D, left), 0) : first_stage(min(c + 1, s.C - 1), next_info);
+    const int sets = REF ? (info >> 12) & 15 : 1, wlo = (info >> 8) & 15;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (!done) stage_digits<KS, NW>(a.Xd, s, next, next_info & 15, tb, lds0 + (buf ^ 1) * TL::STAGE, wave, lane);
+    const char* x = si_smem + buf * TL::STAGE + lane * 16;
+    double sc[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) sc[r] = tl.s[r];
+    if (sets == 0 || nd == 0) load_first(stage_chunk(next));                // a chunk of zeros
+    for (int j = 0; j < sets; ++j) {
+      for (int p = (nd - 1) >> 1; p >= 0; --p) {
+        v16i acc[R];
+        tl.pair(x, p, 2 * p + 1 < nd, acc);
+        if (p == 0) {
+          if (j + 1 < sets)
+            tl.load_codes(q0 + (j + 1) * a.plane + (int64_t)c * KS * 1024, rstride, lane16);
+          else
+            load_first(stage_chunk(next));
+        }
+        add_scaled<R>(y, acc, sc, unit + 8 * (lo + 2 * p) + (REF ? 8 * (wlo + j) : 0));
+      }
+    }
+    const int g = c / s.nchg;
+    if (!REF && stage_first(word) && c == g * s.nchg && a.mt.rest_n[g]) {
+      // zeros outside int8: what the codes do not hold times the sum of the group's activations
+      const double* Rz = a.Rz + (int64_t)g * s.npad + row0 + l32;
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const double sx = ldexp(a.SX[(int64_t)g * s.tpad + tb * 32 + 8 * (v >> 2) + 4 * h + (v & 3)], unit);
+#pragma unroll
+        for (int r = 0; r < R; ++r) y[r][v] = fma(-Rz[32 * r], sx, y[r][v]);
+      }
+    }
+    if (done) break;
+    word = next;
+    info = next_info;
+    buf ^= 1;
+  }
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int row = row0 + 32 * r + l32;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int64_t t = (int64_t)tb * 32 + 8 * q + 4 * h;
+      if (row < s.n && t < s.ts) {
+        double* o = a.Y + (int64_t)row * s.ts + t;
+        *reinterpret_cast<double2*>(o) = make_double2(y[r][4 * q], y[r][4 * q + 1]);
+        *reinterpret_cast<double2*>(o + 2) = make_double2(y[r][4 * q + 2], y[r][4 * q + 3]);
+      }
+    }
+  }
+}
+
+// exp in fp64: Cody-Waite reduction to |r| <= ln 2 / 2, Taylor polynomial to r^13 (remainder below 4e-18), scaling.  The
+// coefficients stay in scalar registers (an instruction takes one), which the library's form does not.
+__device__ __forceinline__ double exp_f64(double x) {
+  auto step = [](double p, double r, double c) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    double o;
+    asm("v_fma_f64 %0, %1, %2, %3" : "=v"(o) : "v"(p), "v"(r), "s"(c));
+    return o;
+#else
+    return fma(p, r, c);
+#endif
+  };
+  const double k = rint(x * 1.4426950408889634074);
+  double r = fma(k, -6.93147180369123816490e-01, x);
+  r = fma(k, -1.90821492927058770002e-10, r);
+  double p = 1.0 / 6227020800.0;
+  p = step(p, r, 1.0 / 479001600.0);
+  p = step(p, r, 1.0 / 39916800.0);
+  p = step(p, r, 1.0 / 3628800.0);
+  p = step(p, r, 1.0 / 362880.0);
+  p = step(p, r, 1.0 / 40320.0);
+  p = step(p, r, 1.0 / 5040.0);
+  p = step(p, r, 1.0 / 720.0);
+  p = step(p, r, 1.0 / 120.0);
+  p = step(p, r, 1.0 / 24.0);
+  p = step(p, r, 1.0 / 6.0);
+  p = fma(p, r, 0.5);
+  p = fma(p, r, 1.0);
+  p = fma(p, r, 1.0);
+  return ldexp(p, (int)k);
+}
+
+// Sum of value(i), i = 0 .. 15, over the 32 lanes of a half wavefront: lane l (and its neighbour) is left with the sum for
+// i = bits 4, 3, 2, 1 of l, most significant first.  A lane halves the list it is responsible for in every step, so 16 sums
+// take 15 + 1 exchanges and not 16 x 5.
+template <typename F>
+__device__ __forceinline__ double sum_scatter16(F value, int lane) {
+  double a[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    // after the swap one register holds v[i] of both rows of 16 lanes for the even row, v[i + 8] of both for the odd row
+    const double u = value(i), v = value(i + 8);
+    auto lo = __builtin_amdgcn_permlane16_swap(__double2loint(u), __double2loint(v), false, false);
+    auto hi = __builtin_amdgcn_permlane16_swap(__double2hiint(u), __double2hiint(v), false, false);
+    a[i] = __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+    __builtin_amdgcn_sched_barrier(0);         // (one pair at a time: the values of all of them at once would spill)
+  }
+  const bool b3 = lane & 8, b2 = lane & 4, b1 = lane & 2;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const double keep = b3 ? a[i + 4] : a[i], give = b3 ? a[i] : a[i + 4];
+    a[i] = keep + dpp_f64<DPP_MIRROR>(give);
+  }
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const double keep = b2 ? a[i + 2] : a[i], give = b2 ? a[i] : a[i + 2];
+    a[i] = keep + dpp_f64<DPP_HALF_MIRROR>(give);
+  }
+  const double keep = b1 ? a[1] : a[0], give = b1 ? a[0] : a[1];
+  const double r = keep + dpp_f64<DPP_XOR2>(give);
+  return r + dpp_f64<DPP_XOR1>(r);
+}
+
+struct SearchArgs {
+  SbaShape s;
+  SbaMeta mt;
+  const char* Xd;
+  const double* SX;
+  const char *Qn, *Qo;
+  const double *Sn, *So, *Rn, *Ro;
+  const double* Yc;                // n x ts outputs of the all-N-bit weights
+  const double* R;                 // n x ts reference: P = softmax(Y) (KL) or Y (squared error)
+  const double* tok;               // per token {max, log-sum-exp} of the reference (KL)
+  const int* order;
+  double* part;                    // [candidate][tile of SE_ROWS rows][tpad]: sums of exp(q - M)
+  double* lin;                     // [candidate][tile of SE_ROWS rows][TB]: sums of P (q - M), or of squared errors
+  int pmax;
+};
+
+// The whole search in one kernel: a wavefront keeps its 32 x 32 outputs of the current candidate and the reference in
+// registers from the first candidate to the last; per candidate it adds its terms of the objective to the candidate's
+// partials (sum exp(q - M) per token; sum P (q - M), or the squared error, over all its outputs) and applies the two changed
+// groups (new integers times new scale minus old integers times old scale).  The next set of codes is on its way while
+// one is multiplied.
+template <int KS, int OBJ>
+__global__ __launch_bounds__(256, 3) void sba_search(SearchArgs a) {
+  constexpr int NW = 4;
+  using TL = Tile<KS, 1>;
+  extern __shared__ __align__(16) char si_smem[];
+  const SbaShape& s = a.s;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l32 = lane & 31, h = lane >> 5;
+  int rt, tb;
+  tile_of(blockIdx.x, s.npad / SE_ROWS, s.TB, rt, tb);
+  const int row0 = rt * SE_ROWS + wave * 32;
+  double* red = reinterpret_cast<double*>(si_smem + 2 * TL::STAGE);           // [4 wavefronts][33]
+  int* tab = reinterpret_cast<int*>(red + NW * 34);                           // the changed groups' chunks in search order
+  const unsigned lds0 = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(uintptr_t)((__attribute__((address_space(3))) char*)si_smem));
+  const int64_t rowq = (int64_t)(row0 >> 5) * s.C * KS * 1024;
+  const unsigned lane16 = lane * 16;
+  // chunk i of the search (of candidate i / per): (chunk << 8) | (digits << 4) | lowest digit
+  const int per = 2 * s.nchg, chunks = a.pmax * per;
+  auto describe = [&](int i) {
+    const int p = i / per, j = i - p * per, hi = j >= s.nchg;
+    const int c = a.order[hi ? s.k - 1 - p : p] * s.nchg + (j - hi * s.nchg);
+    return (c << 8) | (a.mt.x[2 * c + 1] << 4) | a.mt.x[2 * c];
+  };
+  for (int i = tid; i < min(chunks, SI_TAB); i += 256) tab[i] = describe(i);
+  const int unit = __builtin_amdgcn_readfirstlane(a.mt.unit[0]);
+  __syncthreads();
+  auto chunk_info = [&](int i) { return __builtin_amdgcn_readfirstlane(i < SI_TAB ? tab[i] : describe(i)); };
+
+  double y[1][16], ref[16];
+  {
+    const int row = row0 + l32;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      const int64_t t = (int64_t)tb * 32 + 8 * (v >> 2) + 4 * h + (v & 3);
+      const bool in = row < s.n && t < s.ts;
+      // outside the matrix: exp(-1e4) = 0 with a reference of 0 (KL), 0 against 0 (squared error)
+      y[0][v] = in ? a.Yc[(int64_t)row * s.ts + t] - (OBJ == SLIM_OBJ_KL ? a.tok[2 * t] : 0.0) : (OBJ == SLIM_OBJ_KL ? -1e4 : 0.0);
+      ref[v] = in ? a.R[(int64_t)row * s.ts + t] : 0.0;
+    }
+  }
+  TL tl[2];                                       // [0]: integers at the new width, [1]: at width N
+  auto load_set = [&](TL& t, int chunk, bool old) {
+    t.load_codes((old ? a.Qn : a.Qo) + rowq + (int64_t)chunk * KS * 1024, 0, lane16);
+    t.load_scales((old ? a.Sn : a.So) + (int64_t)(chunk / s.nchg) * s.npad + row0, l32);
+  };
+  auto first_stage = [&](int info) { return stage_word(info >> 8, info & 15, min(SI_STAGE_D, (info >> 4) & 15), 1); };
+  int i = 0, info = 0, word = 0, buf = 0;
+  if (chunks > 0) {
+    info = chunk_info(0);
+    word = first_stage(info);
+    stage_digits<KS, NW>(a.Xd, s, word, info & 15, tb, lds0, wave, lane);
+    load_set(tl[0], stage_chunk(word), false);
+  }
+  for (int p = 0;; ++p) {
+    {
+      double q = 0.0;
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const double d = ref[v] - y[0][v];
+        q = (OBJ == SLIM_OBJ_KL) ? fma(ref[v], y[0][v], q) : fma(d, d, q);
+      }
+      q = wave_sum(q);
+      int ln = lane;
+      asm volatile("" : "+v"(ln));                // (formed again for every candidate: kept, these would cost registers)
+      if (ln == 0) red[wave * 34 + 32] = q;
+      if (OBJ == SLIM_OBJ_KL) {
+        const double z = sum_scatter16([&](int v) { return exp_f64(y[0][v]); }, ln);
+        const int idx = ((ln >> 4) & 1) * 8 + ((ln >> 3) & 1) * 4 + ((ln >> 2) & 1) * 2 + ((ln >> 1) & 1);
+        if (!(ln & 1)) red[wave * 34 + 8 * (idx >> 2) + 4 * (ln >> 5) + (idx & 3)] = z;
       }
     }
     __syncthreads();
-    if (tid < BN) {
-      double* o = a.partial + (int64_t)p * a.pstride + ((int64_t)bi * ts + col0 + tid) * KL_PART;
-      o[3] = red[0 * BN + tid] + red[1 * BN + tid];
-      o[4] = red[2 * BN + tid] + red[3 * BN + tid];
+    if (tid <= 32) {
+      const double sum = (red[tid] + red[34 + tid]) + (red[68 + tid] + red[102 + tid]);
+      const int64_t tile = (int64_t)p * (s.npad / SE_ROWS) + rt;
+      if (tid == 32)
+        a.lin[tile * s.TB + tb] = sum;
+      else if (OBJ == SLIM_OBJ_KL)
+        a.part[tile * s.tpad + tb * 32 + tid] = sum;
     }
     if (p == a.pmax) break;
-    // candidate p + 1: Y^T += [D_lo | D_hi]_p [X_lo ; X_hi]_p, a rank-2beta update of the tile
-    slim_gemm_desc d;
-    d.A = a.Dcat + (int64_t)p * 2 * a.beta;
-    d.lda = a.m;
-    d.B = a.Xcat + (int64_t)p * 2 * a.beta * ts;
-    d.ldb = ts;
-    k_loop_fast<0, BM, BN>(d, row0, col0, 0, 2 * a.beta, smem, acc);
+    for (int j = 0; j < per;) {
+      const int c = stage_chunk(word), lo = stage_lo(word), nd = stage_nd(word);
+      const int left = (info & 15) + ((info >> 4) & 15) - lo - nd;
+      const bool done = left <= 0 && i + 1 == chunks;
+      const int next_info = left > 0 ? info : chunk_info(min(i + 1, chunks - 1));
+      const int next = left > 0 ? stage_word(c, lo + nd, min(SI_STAGE_D, left), 0) : first_stage(next_info);
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      __syncthreads();                             // (also: everybody has read `red`)
+      if (!done) stage_digits<KS, NW>(a.Xd, s, next, next_info & 15, tb, lds0 + (buf ^ 1) * TL::STAGE, wave, lane);
+      const char* x = si_smem + buf * TL::STAGE + lane16;
+      const int g = c / s.nchg;
+      const bool whole = stage_first(word) && c == g * s.nchg;
+#pragma unroll
+      for (int old = 0; old < 2; ++old) {
+        load_set(tl[old ^ 1], old ? stage_chunk(next) : c, !old);
+        const double sc[1] = {old ? -tl[old].s[0] : tl[old].s[0]};
+        for (int pr = (nd - 1) >> 1; pr >= 0; --pr) {
+          v16i acc[1];
+          tl[old].pair(x, pr, 2 * pr + 1 < nd, acc);
+          add_scaled<1>(y, acc, sc, unit + 8 * (lo + 2 * pr));
+        }
+        if (whole && (old ? a.mt.rest_n : a.mt.rest_o)[g]) {
+          const double rz = (old ? a.Rn : a.Ro)[(int64_t)g * s.npad + row0 + l32];
+#pragma unroll
+          for (int v = 0; v < 16; ++v) {
+            const double sx = ldexp(a.SX[(int64_t)g * s.tpad + tb * 32 + 8 * (v >> 2) + 4 * h + (v & 3)], unit);
+            y[0][v] = fma(old ? rz : -rz, sx, y[0][v]);
+          }
+        }
+      }
+      if (left <= 0) {
+        ++i;
+        ++j;
+      }
+      word = next;
+      info = next_info;
+      buf ^= 1;
+    }
   }
+}
+
+// Per candidate (grid.y) and 256 tokens: KL: sum over the tokens of B_t + log sum exp(q - M), minus the tiles' sums of P (q - M);
+// squared error: the tiles' sums.  Every workgroup writes its sum.
+template <int OBJ>
+__global__ __launch_bounds__(256) void sba_token_sums(const double* __restrict__ part, const double* __restrict__ lin, SbaShape s,
+                                                      const double* __restrict__ tokB, double* __restrict__ block_sums_all,
+                                                      int nblocks) {
+  __shared__ double red[256];
+  const int tiles = s.npad / SE_ROWS;
+  double acc = 0.0;
+  if (OBJ == SLIM_OBJ_KL) {
+    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (t < s.ts) {
+      double Z = 0.0;
+      for (int r = 0; r < tiles; ++r) Z += part[((int64_t)blockIdx.y * tiles + r) * s.tpad + t];
+      acc = tokB[t] + log(Z);
+    }
+  }
+  double lsum = 0.0;
+  const int tb0 = blockIdx.x * 8, nb = min(8, s.TB - tb0);
+  for (int j = threadIdx.x; j < tiles * nb; j += 256) lsum += lin[((int64_t)blockIdx.y * tiles + j / nb) * s.TB + tb0 + j % nb];
+  acc = (OBJ == SLIM_OBJ_KL) ? acc - lsum : lsum;
+  red[threadIdx.x] = acc;
+  __syncthreads();
+  for (int st = 128; st > 0; st >>= 1) {
+    if (threadIdx.x < st) red[threadIdx.x] += red[threadIdx.x + st];
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) block_sums_all[(int64_t)blockIdx.y * nblocks + blockIdx.x] = red[0];
+}
+
+// ---- host side -------------------------------------------------------------------------------------------------
+SbaShape sba_shape(int n, int m, int beta, int64_t t_s) {
+  SbaShape s;
+  s.n = n;
+  s.m = m;
+  s.beta = beta;
+  s.k = m / beta;
+  s.ts = t_s;
+  s.chk = beta <= 32 ? 32 : beta <= 64 ? 64 : SI_CHUNK;
+  s.ks = s.chk / 32;
+  s.nchg = slim_cdiv(beta, s.chk);
+  s.C = s.k * s.nchg;
+  s.npad = slim_cdiv(n, SI_ROWS) * SI_ROWS;
+  s.RB = s.npad / 32;
+  s.RT = s.npad / SI_ROWS;
+  s.tpad = slim_cdiv(t_s, SI_TOK) * SI_TOK;
+  s.TB = s.tpad / SI_TOK;
+  return s;
+}
+
+// The workspace of slim_sba_allocate; slim_sba_prepare fills the part of it that does not depend on the ranking.
+struct SbaWorkspace {
+  SbaShape s;
+  SbaMeta mt;
+  int pmax, parts, kl_blocks;
+  int64_t plane;                   // bytes of one int8 matrix in operand order
+  char *Xd, *Wd, *Qn, *Qo;
+  double *Sn, *So, *Rn, *Ro, *SX, *Yt, *Yc, *ref_part, *part, *lin, *obj, *block_sums, *tok, *tokB;
+  int *order, *rank_of, *pstar_dev;
+};
+constexpr int KL_RPP = 256;        // rows per part of the reference side's reductions
+
+// Lays the workspace out from `base` (nullptr: only the size is wanted) and returns its size.
+size_t sba_layout(int n, int m, int beta, int64_t t_s, char* base, SbaWorkspace& w) {
+  const SbaShape s = w.s = sba_shape(n, m, beta, t_s);
+  w.pmax = s.k / 2;
+  w.parts = slim_cdiv(n, KL_RPP);
+  w.kl_blocks = slim_cdiv(t_s, 256);
+  w.plane = (int64_t)s.npad * s.C * s.chk;
+  size_t off = 0;
+  auto take = [&](size_t bytes) {
+    char* p = base ? base + off : nullptr;
+    off += slim_ws_round(bytes);
+    return p;
+  };
+  auto doubles = [&](size_t count) { return reinterpret_cast<double*>(take(sizeof(double) * count)); };
+  w.Xd = take((size_t)s.C * s.TB * SI_MAXD * s.ks * 1024);
+  w.Wd = take((size_t)SI_MAXD * w.plane);
+  w.Qn = take((size_t)w.plane);
+  w.Qo = take((size_t)w.plane);
+  w.Sn = doubles((size_t)s.k * s.npad);
+  w.So = doubles((size_t)s.k * s.npad);
+  w.Rn = doubles((size_t)s.k * s.npad);
+  w.Ro = doubles((size_t)s.k * s.npad);
+  w.SX = doubles((size_t)s.k * s.tpad);
+  w.Yt = doubles((size_t)n * t_s);
+  w.Yc = doubles((size_t)n * t_s);
+  w.ref_part = doubles((size_t)w.parts * KL_PART * t_s);
+  w.part = doubles((size_t)(w.pmax + 1) * (s.npad / SE_ROWS) * s.tpad);
+  w.lin = doubles((size_t)(w.pmax + 1) * (s.npad / SE_ROWS) * s.TB);
+  w.obj = doubles((size_t)(w.pmax + 2) * (size_t)(w.kl_blocks + 1));
+  w.block_sums = w.obj + (w.pmax + 2);
+  w.order = reinterpret_cast<int*>(take(sizeof(int) * (size_t)(2 * s.k + 2)));
+  w.rank_of = w.order + (s.k + 1);
+  w.pstar_dev = reinterpret_cast<int*>(take(256));
+  w.tok = doubles(3 * (size_t)t_s);      // per token {max, log-sum-exp} of the reference; sum P log P behind
+  w.tokB = w.tok + 2 * t_s;
+  int* mi = reinterpret_cast<int*>(take(sizeof(int) * (8 * (size_t)s.C + 2 * (size_t)s.k + 4)));
+  w.mt.x = mi;
+  w.mt.w = mi + 2 * s.C;
+  w.mt.xmax = reinterpret_cast<unsigned*>(mi + 4 * s.C);
+  w.mt.xlsb = mi + 5 * s.C;
+  w.mt.wmax = reinterpret_cast<unsigned*>(mi + 6 * s.C);
+  w.mt.wlsb = mi + 7 * s.C;
+  w.mt.rest_n = mi + 8 * s.C;
+  w.mt.rest_o = w.mt.rest_n + s.k;
+  w.mt.unit = w.mt.rest_o + s.k;
+  return off;
 }
 
 }  // namespace
 
-namespace {
-
-// The workspace of slim_sba_allocate; slim_sba_prepare fills the part of it that does not depend on the ranking.
-struct SbaWorkspace {
-  bool fused;            // the search runs as one kernel over 128 x 128 output tiles
-  int k, pmax, rpp, parts, kl_blocks;
-  int64_t pstride;
-  double *W64, *WN, *Dcat, *X64, *Xcat, *Yt, *Yc, *partial, *obj, *block_sums, *tok, *tokB;
-  int *order, *rank_of, *pstar_dev;
-};
-
-}  // namespace
-
+// The stated size has a floor of three n x m and two n x t_s and m x t_s fp64 matrices, which callers may have provided for.
 size_t slim_ws_need_sba(int n, int m, int beta, int64_t t_s) {
-  const int k = m / beta, pmax = k / 2;
-  const bool fused = n % SEARCH_TILE == 0 && t_s % SEARCH_TILE == 0 && (2 * beta) % 16 == 0;
-  const int parts = slim_cdiv(n, fused ? SEARCH_TILE : 256), kl_blocks = slim_cdiv(t_s, 256);
-  const size_t bW = slim_ws_round(sizeof(double) * (size_t)n * m);
-  const size_t bX = slim_ws_round(sizeof(double) * (size_t)m * t_s);
-  const size_t bY = slim_ws_round(sizeof(double) * (size_t)n * t_s);
-  const size_t bPart = slim_ws_round(sizeof(double) * (size_t)parts * t_s * KL_PART);
-  const size_t bObj = slim_ws_round(sizeof(double) * (size_t)(pmax + 2) * (size_t)(kl_blocks + 1));
-  const size_t bOrd = slim_ws_round(sizeof(int) * (size_t)(2 * k + 2));
-  const size_t bTok = slim_ws_round(sizeof(double) * 3 * (size_t)t_s);
-  return 3 * bW + 2 * bX + 2 * bY + (size_t)(pmax + 1) * bPart + bObj + bOrd + bTok + 256;
+  SbaWorkspace w;
+  const size_t floor_bytes = 3 * slim_ws_round(8 * (size_t)n * m) + 2 * slim_ws_round(8 * (size_t)m * t_s) + 2 * slim_ws_round(8 * (size_t)n * t_s);
+  return std::max(sba_layout(n, m, beta, t_s, nullptr, w), floor_bytes);
 }
 
 namespace {
 
 slim_status sba_workspace(slim_ctx* ctx, int n, int m, int beta, int64_t t_s, SbaWorkspace& w) {
-  w.k = m / beta;
-  w.pmax = w.k / 2;
-  // The one-kernel search needs whole tiles and whole K slabs; its partials are per 128 rows.
-  w.fused = n % SEARCH_TILE == 0 && t_s % SEARCH_TILE == 0 && (2 * beta) % 16 == 0;
-  w.rpp = w.fused ? SEARCH_TILE : 256;                  // rows per part of the reduction over the outputs
-  w.parts = slim_cdiv(n, w.rpp);
-  w.kl_blocks = slim_cdiv(t_s, 256);
-  const size_t bW = slim_ws_round(sizeof(double) * (size_t)n * m);
-  const size_t bX = slim_ws_round(sizeof(double) * (size_t)m * t_s);
-  const size_t bY = slim_ws_round(sizeof(double) * (size_t)n * t_s);
-  const size_t bPart = slim_ws_round(sizeof(double) * (size_t)w.parts * t_s * KL_PART);   // per candidate
-  const size_t bObj = slim_ws_round(sizeof(double) * (size_t)(w.pmax + 2) * (size_t)(w.kl_blocks + 1));
-  const size_t bOrd = slim_ws_round(sizeof(int) * (size_t)(2 * w.k + 2));
-  const size_t bTok = slim_ws_round(sizeof(double) * 3 * (size_t)t_s);
-  slim_status st = slim_ws_reserve(ctx, slim_ws_need_sba(n, m, beta, t_s));
+  const slim_status st = slim_ws_reserve(ctx, slim_ws_need_sba(n, m, beta, t_s));
   if (st != SLIM_OK) return st;
-  w.W64 = static_cast<double*>(slim_ws_alloc(ctx, bW));
-  w.WN = static_cast<double*>(slim_ws_alloc(ctx, bW));
-  w.Dcat = static_cast<double*>(slim_ws_alloc(ctx, bW));
-  w.X64 = static_cast<double*>(slim_ws_alloc(ctx, bX));
-  w.Xcat = static_cast<double*>(slim_ws_alloc(ctx, bX));
-  w.Yt = static_cast<double*>(slim_ws_alloc(ctx, bY));
-  w.Yc = static_cast<double*>(slim_ws_alloc(ctx, bY));
-  w.partial = static_cast<double*>(slim_ws_alloc(ctx, (size_t)(w.pmax + 1) * bPart));
-  w.pstride = (int64_t)(bPart / sizeof(double));        // every candidate keeps its partials until the end
-  w.obj = static_cast<double*>(slim_ws_alloc(ctx, bObj));
-  w.block_sums = w.obj + (w.pmax + 2);
-  w.order = static_cast<int*>(slim_ws_alloc(ctx, bOrd));
-  w.rank_of = w.order + (w.k + 1);
-  w.pstar_dev = static_cast<int*>(slim_ws_alloc(ctx, 256));
-  w.tok = static_cast<double*>(slim_ws_alloc(ctx, bTok));   // per token {max, log-sum-exp} of the reference
-  w.tokB = w.tok + 2 * t_s;                                 // per token sum P log P
+  sba_layout(n, m, beta, t_s, ctx->ws, w);
   return SLIM_OK;
 }
 
@@ -554,76 +1147,121 @@ slim_status sba_check(slim_ctx* ctx, const char* fn, const void* W, slim_dtype w
   return SLIM_OK;
 }
 
-// The part of the objective that does not depend on the ranking (Eq. 4): W and X_s in fp64, the all-N-bit weights,
-// the reference outputs Y^T = W X_s and the outputs of the all-N-bit weights, and for the KL objective the reference
-// softmax with its per-token statistics.  `beside_chain` runs the two products in the form that leaves CUs free.
-slim_status sba_rank_independent(slim_ctx* ctx, const SbaWorkspace& w, const void* W, slim_dtype w_dtype, int n, int m,
-                                 int64_t ldw, int beta, int N, int objective, const void* X_s, slim_dtype x_dtype,
-                                 int64_t t_s, int64_t ldxs, int q1_mode, bool beside_chain) {
-  slim_status st = slim_widen_f64(ctx, "sba_widen_w", W, w_dtype, n, m, ldw, w.W64, (int64_t)m);
+template <typename T>
+slim_status sba_codes_launch(slim_ctx* ctx, const T* W, const CodesArgs& a) {
+  const dim3 grid(a.s.npad / 16, std::min(a.s.k, 8));
+  if (a.rank_of)
+    SLIM_LAUNCH(ctx, "sba_codes", (sba_codes<T, true>), grid, dim3(256), 0, W, a);
+  else
+    SLIM_LAUNCH(ctx, "sba_codes", (sba_codes<T, false>), grid, dim3(256), 0, W, a);
+  return SLIM_OK;
+}
+slim_status sba_codes_launch(slim_ctx* ctx, const void* W, slim_dtype dt, const CodesArgs& a) {
+  switch (dt) {
+    case SLIM_F16: return sba_codes_launch(ctx, static_cast<const __half*>(W), a);
+    case SLIM_BF16: return sba_codes_launch(ctx, static_cast<const __hip_bfloat16*>(W), a);
+    default: return sba_codes_launch(ctx, static_cast<const float*>(W), a);
+  }
+}
+
+template <typename T>
+slim_status sba_x_launch(slim_ctx* ctx, const SbaWorkspace& w, const T* X, int64_t ldx) {
+  SLIM_LAUNCH(ctx, "sba_x_stats", sba_x_stats<T>, dim3(w.s.C, slim_cdiv(w.s.ts, 1024)), dim3(256), 0, X, ldx, w.s, w.mt);
+  return SLIM_OK;
+}
+template <typename T>
+slim_status sba_digits_launch(slim_ctx* ctx, const SbaWorkspace& w, const T* X, int64_t ldx) {
+  SLIM_LAUNCH(ctx, "sba_x_digits", sba_x_digits<T>, dim3(slim_cdiv(w.s.TB, 4), w.s.k), dim3(256), 0, X, ldx, w.s, w.mt, w.Xd, w.SX);
+  return SLIM_OK;
+}
+template <typename T>
+slim_status sba_w_launch(slim_ctx* ctx, const SbaWorkspace& w, const T* W, int64_t ldw) {
+  SLIM_LAUNCH(ctx, "sba_w_stats", sba_w_stats<T>, dim3(slim_cdiv(w.s.m, 1024), std::min(w.s.n, 128)), dim3(256), 0, W, ldw, w.s, w.mt);
+  return SLIM_OK;
+}
+
+template <int KS>
+slim_status sba_outputs_launch(slim_ctx* ctx, const SbaShape& s, OutArgs a, bool ref) {
+  const dim3 grid(s.RT * s.TB);
+  const size_t smem = 2 * Tile<KS, 2>::STAGE + sizeof(int) * std::min(s.C, SI_TAB);
+  if (ref)
+    SLIM_LAUNCH(ctx, "sba_reference_outputs", (sba_outputs<KS, true>), grid, dim3(256), smem, a);
+  else
+    SLIM_LAUNCH(ctx, "sba_outputs", (sba_outputs<KS, false>), grid, dim3(256), smem, a);
+  return SLIM_OK;
+}
+slim_status sba_outputs_launch(slim_ctx* ctx, const SbaShape& s, const OutArgs& a, bool ref) {
+  return s.ks == 1 ? sba_outputs_launch<1>(ctx, s, a, ref) : s.ks == 2 ? sba_outputs_launch<2>(ctx, s, a, ref) : sba_outputs_launch<4>(ctx, s, a, ref);
+}
+
+template <int KS>
+slim_status sba_search_launch(slim_ctx* ctx, const SearchArgs& a, int objective) {
+  const dim3 grid((a.s.npad / SE_ROWS) * a.s.TB);
+  const size_t smem = 2 * Tile<KS, 1>::STAGE + sizeof(double) * 4 * 34 + sizeof(int) * std::min(a.s.C, SI_TAB);
+  if (objective == SLIM_OBJ_KL)
+    SLIM_LAUNCH(ctx, "sba_search", (sba_search<KS, SLIM_OBJ_KL>), grid, dim3(256), smem, a);
+  else
+    SLIM_LAUNCH(ctx, "sba_search", (sba_search<KS, SLIM_OBJ_MSE>), grid, dim3(256), smem, a);
+  return SLIM_OK;
+}
+
+// The part of the objective that does not depend on the ranking (Eq. 4): the digits of X_s and W and the codes of the
+// all-N-bit weights, the reference outputs Y^T = W X_s and the outputs of the all-N-bit weights, and for the KL objective
+// the reference softmax with its per-token statistics.
+slim_status sba_rank_independent(slim_ctx* ctx, const SbaWorkspace& w, const void* W, slim_dtype w_dtype, int n,
+                                 int64_t ldw, int N, int objective, const void* X_s, slim_dtype x_dtype, int64_t t_s,
+                                 int64_t ldxs, int q1_mode) {
+  const SbaShape& s = w.s;
+  slim_status st;
+  SLIM_LAUNCH(ctx, "sba_clear", sba_clear, dim3(slim_cdiv(std::max(s.C, s.k), 256)), dim3(256), 0, w.mt, s.C, s.k);
+  const bool xh = x_dtype == SLIM_F16;
+  st = xh ? sba_x_launch(ctx, w, static_cast<const __half*>(X_s), ldxs) : sba_x_launch(ctx, w, static_cast<const __hip_bfloat16*>(X_s), ldxs);
   if (st != SLIM_OK) return st;
-  st = slim_widen_f64(ctx, "sba_widen_x", X_s, x_dtype, m, (int)t_s, ldxs, w.X64, t_s);
+  st = w_dtype == SLIM_F16 ? sba_w_launch(ctx, w, static_cast<const __half*>(W), ldw)
+       : w_dtype == SLIM_BF16 ? sba_w_launch(ctx, w, static_cast<const __hip_bfloat16*>(W), ldw)
+                              : sba_w_launch(ctx, w, static_cast<const float*>(W), ldw);
   if (st != SLIM_OK) return st;
-  SLIM_LAUNCH(ctx, "sba_fakequant", sba_fakequant, dim3(slim_cdiv((int64_t)n * w.k, 4)), dim3(256), 0, w.W64, n, m, beta,
-              N, q1_mode, nullptr, w.pmax, w.WN, nullptr, FQ_WN);
-  slim_gemm_desc d;
-  d.A = w.W64;
-  d.lda = m;
-  d.B = w.X64;
-  d.ldb = t_s;
-  d.C = w.Yt;
-  d.ldc = t_s;
-  d.C2 = nullptr;
-  d.ldc2 = 0;
-  d.M = n;
-  d.N = (int)t_s;
-  d.K = m;
-  d.flags = 0;
-  d.alpha = 1.0;
-  d.beta = 0.0;
-  slim_gemm_desc pair[2] = {d, d};
-  pair[1].A = w.WN;
-  pair[1].C = w.Yc;
-  // Beside the inverse only as many rows of the two products run (persistent, on part of the chip) as take about
-  // as long as the inverse does; the rest follows in the ordinary form, which wants the whole chip.  The inverse
-  // is modelled as its chain of m / 64 diagonal steps of 45 us plus m^3 / 3 flops of triangular inversion at
-  // 50 TFLOP/s, the persistent form at 85 % of the matrix cores of its CUs.
-  // Their share of the chip, next to a factorisation whose own bulk updates want whole CUs too: 5/8 when the layer
-  // has no more outputs than inputs (the products are then about as long as the inverse, and a larger share ends
-  // them with it), half of it otherwise (most of the products follows after the inverse anyway, and the inverse
-  // gains more from the CUs); both measured, on 4096 x 4096 .. 28672 x 8192 layers.
-  int rows_beside = 0;
-  const int cus = std::max(1, n <= m ? ctx->num_cus * 5 / 8 : ctx->num_cus / 2);
-  if (beside_chain && n % 256 == 0 && t_s % 128 == 0 && m % 16 == 0) {
-    const double t_inv = (m / 64) * 45e-6 + (double)m * m * m / 3.0 / 50e12;
-    const double rate = 0.85 * 78.6e12 * cus / std::max(1, ctx->num_cus);
-    const int64_t tiles_per_block = 2 * (t_s / 128);            // of 256 rows, both products
-    int64_t tiles_fit = (int64_t)(rate * t_inv / (2.0 * 256 * 128 * m));
-    tiles_fit = (tiles_fit / cus) * cus;                          // whole rounds
-    rows_beside = (int)std::min<int64_t>(n, std::max<int64_t>(tiles_fit / tiles_per_block, 0) * 256);
-  }
-  if (rows_beside > 0) {
-    slim_gemm_desc part[2] = {pair[0], pair[1]};
-    part[0].M = part[1].M = rows_beside;
-    st = slim_dgemm_reserved(ctx, "sba_output_dgemm", 0, part, 2, cus);
-    if (st != SLIM_OK) return st;
-  }
-  if (rows_beside < n) {
-    for (slim_gemm_desc g : pair) {
-      g.A += (int64_t)rows_beside * g.lda;
-      g.C += (int64_t)rows_beside * g.ldc;
-      g.M = n - rows_beside;
-      st = slim_dgemm(ctx, "sba_output_dgemm", 0, g);
-      if (st != SLIM_OK) return st;
-    }
-  }
+  SLIM_LAUNCH(ctx, "sba_meta", sba_meta, dim3(2), dim3(256), 0, w.mt, s.C);
+  st = xh ? sba_digits_launch(ctx, w, static_cast<const __half*>(X_s), ldxs) : sba_digits_launch(ctx, w, static_cast<const __hip_bfloat16*>(X_s), ldxs);
+  if (st != SLIM_OK) return st;
+  CodesArgs ca;
+  ca.s = s;
+  ca.mt = w.mt;
+  ca.ldw = ldw;
+  ca.N = N;
+  ca.q1_mode = q1_mode;
+  ca.pmax = w.pmax;
+  ca.rank_of = nullptr;
+  ca.Q = w.Qn;
+  ca.S = w.Sn;
+  ca.Rz = w.Rn;
+  ca.rest = w.mt.rest_n;
+  ca.Wd = w.Wd;
+  st = sba_codes_launch(ctx, W, w_dtype, ca);
+  if (st != SLIM_OK) return st;
+  OutArgs oa;
+  oa.s = s;
+  oa.mt = w.mt;
+  oa.Xd = w.Xd;
+  oa.SX = w.SX;
+  oa.Q = w.Wd;
+  oa.plane = w.plane;
+  oa.S = w.Sn;
+  oa.Rz = w.Rn;
+  oa.Y = w.Yt;
+  st = sba_outputs_launch(ctx, s, oa, true);
+  if (st != SLIM_OK) return st;
+  oa.Q = w.Qn;
+  oa.Y = w.Yc;
+  st = sba_outputs_launch(ctx, s, oa, false);
+  if (st != SLIM_OK) return st;
   if (objective == SLIM_OBJ_KL) {
     // reference side once: per-token maximum and log-sum-exp, then Y^T becomes P = softmax over the outputs
     const dim3 kgrid(slim_cdiv(t_s, KL_TOK), w.parts);
-    SLIM_LAUNCH(ctx, "sba_kl_ref", kl_ref_partial, kgrid, dim3(256), 0, w.Yt, n, t_s, w.rpp, w.partial);
-    SLIM_LAUNCH(ctx, "sba_kl_ref", kl_ref_merge, dim3(w.kl_blocks), dim3(256), 0, w.partial, w.parts, t_s, w.tok);
-    SLIM_LAUNCH(ctx, "sba_kl_ref", kl_ref_softmax, kgrid, dim3(256), 0, w.Yt, n, t_s, w.rpp, w.tok, w.partial);
-    SLIM_LAUNCH(ctx, "sba_kl_ref", kl_ref_entropy, dim3(w.kl_blocks), dim3(256), 0, w.partial, w.parts, t_s, w.tokB);
+    SLIM_LAUNCH(ctx, "sba_kl_ref", kl_ref_partial, kgrid, dim3(256), 0, w.Yt, n, t_s, KL_RPP, w.ref_part);
+    SLIM_LAUNCH(ctx, "sba_kl_ref", kl_ref_merge, dim3(w.kl_blocks), dim3(256), 0, w.ref_part, w.parts, t_s, w.tok);
+    SLIM_LAUNCH(ctx, "sba_kl_ref", kl_ref_softmax, kgrid, dim3(256), 0, w.Yt, n, t_s, KL_RPP, w.tok, w.ref_part);
+    SLIM_LAUNCH(ctx, "sba_kl_ref", kl_ref_entropy, dim3(w.kl_blocks), dim3(256), 0, w.ref_part, w.parts, t_s, w.tokB);
   }
   return SLIM_OK;
 }
@@ -642,7 +1280,7 @@ extern "C" slim_status slim_sba_prepare(slim_ctx* ctx, const void* W, slim_dtype
   SbaWorkspace w;
   st = sba_workspace(ctx, n, m, beta, t_s, w);
   if (st != SLIM_OK) return st;
-  st = sba_rank_independent(ctx, w, W, w_dtype, n, m, ldw, beta, N, objective, X_s, x_dtype, t_s, ldxs, prm.q1_mode, true);
+  st = sba_rank_independent(ctx, w, W, w_dtype, n, ldw, N, objective, X_s, x_dtype, t_s, ldxs, prm.q1_mode);
   if (st != SLIM_OK) return st;
   slim_sba_prepared& r = ctx->sba_prep;
   r.W = W;
@@ -682,92 +1320,62 @@ extern "C" slim_status slim_sba_allocate(slim_ctx* ctx, const void* W, slim_dtyp
   SbaWorkspace w;
   st = sba_workspace(ctx, n, m, beta, t_s, w);
   if (st != SLIM_OK) return st;
-  const int k = w.k, pmax = w.pmax, rpp = w.rpp, parts = w.parts, kl_blocks = w.kl_blocks;
-  const int64_t pstride = w.pstride;
-  double *W64 = w.W64, *WN = w.WN, *Dcat = w.Dcat, *X64 = w.X64, *Xcat = w.Xcat, *Yt = w.Yt, *Yc = w.Yc;
-  double *partial = w.partial, *obj = w.obj, *block_sums = w.block_sums, *tok = w.tok, *tokB = w.tokB;
-  int *order = w.order, *rank_of = w.rank_of, *pstar_dev = w.pstar_dev;
+  const SbaShape& s = w.s;
+  const int k = s.k, pmax = w.pmax, kl_blocks = w.kl_blocks;
+  int* const pstar_dev = w.pstar_dev;
+  double* const obj = w.obj;
 
   const bool reuse = prepared && r.ws == ctx->ws;       // (the workspace was not reallocated in between)
   if (!reuse) {
-    st = sba_rank_independent(ctx, w, W, w_dtype, n, m, ldw, beta, N, objective, X_s, x_dtype, t_s, ldxs, prm.q1_mode, false);
+    st = sba_rank_independent(ctx, w, W, w_dtype, n, ldw, N, objective, X_s, x_dtype, t_s, ldxs, prm.q1_mode);
     if (st != SLIM_OK) return st;
   }
-  SLIM_LAUNCH(ctx, "sba_rank", sba_rank, dim3(1), dim3(256), 0, group_sal, k, order, rank_of);
-  SLIM_LAUNCH(ctx, "sba_fakequant", sba_fakequant, dim3(slim_cdiv((int64_t)n * k, 4)), dim3(256), 0, W64, n, m, beta, N,
-              prm.q1_mode, rank_of, pmax, WN, Dcat, FQ_DCAT);
-  if (pmax > 0)
-    SLIM_LAUNCH(ctx, "sba_gather_x", sba_gather_x, dim3(64, 2 * pmax), dim3(256), 0, X64, t_s, beta, k, order, Xcat);
-
-  const dim3 kgrid(slim_cdiv(t_s, KL_TOK), parts);
-  if (w.fused) {
-    SearchArgs sa;
-    sa.Yc = Yc;
-    sa.R = Yt;
-    sa.tok = tok;
-    sa.Dcat = Dcat;
-    sa.Xcat = Xcat;
-    sa.partial = partial;
-    sa.pstride = pstride;
-    sa.ts = t_s;
-    sa.n = n;
-    sa.m = m;
-    sa.beta = beta;
-    sa.pmax = pmax;
-    static bool lds_kl = false, lds_mse = false;
-    const dim3 sgrid((n / SEARCH_TILE) * (int)(t_s / SEARCH_TILE));
-    if (objective == SLIM_OBJ_KL) {
-      if (!lds_kl) {
-        SLIM_HIP_TRY(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(sba_search_tile<SLIM_OBJ_KL>),
-                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)SEARCH_LDS));
-        lds_kl = true;
-      }
-      SLIM_LAUNCH(ctx, "sba_search", sba_search_tile<SLIM_OBJ_KL>, sgrid, dim3(256), SEARCH_LDS, sa);
-    } else {
-      if (!lds_mse) {
-        SLIM_HIP_TRY(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(sba_search_tile<SLIM_OBJ_MSE>),
-                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)SEARCH_LDS));
-        lds_mse = true;
-      }
-      SLIM_LAUNCH(ctx, "sba_search", sba_search_tile<SLIM_OBJ_MSE>, sgrid, dim3(256), SEARCH_LDS, sa);
-    }
-  } else {
-    for (int p = 0; p <= pmax; ++p) {
-      if (objective == SLIM_OBJ_KL)
-        SLIM_LAUNCH(ctx, "sba_kl_step", kl_step, kgrid, dim3(256), 0, Yt, Yc, n, t_s, rpp, tok, partial + p * pstride);
-      else
-        SLIM_LAUNCH(ctx, "sba_mse_partial", mse_partial, kgrid, dim3(256), 0, Yt, Yc, n, t_s, rpp, partial + p * pstride);
-      if (p < pmax) {
-        // Y_{p+1}^T = Y_p^T + [D_lo | D_hi]_p [X_lo ; X_hi]_p : one rank-2beta update
-        slim_gemm_desc u;
-        u.A = Dcat + (int64_t)p * 2 * beta;
-        u.lda = m;
-        u.B = Xcat + (int64_t)p * 2 * beta * t_s;
-        u.ldb = t_s;
-        u.C = Yc;
-        u.ldc = t_s;
-        u.C2 = nullptr;
-        u.ldc2 = 0;
-        u.M = n;
-        u.N = (int)t_s;
-        u.K = 2 * beta;
-        u.flags = 0;
-        u.alpha = 1.0;
-        u.beta = 1.0;
-        st = slim_dgemm(ctx, "sba_update_dgemm", 0, u);
-        if (st != SLIM_OK) return st;
-      }
-    }
+  SLIM_LAUNCH(ctx, "sba_rank", sba_rank, dim3(1), dim3(256), 0, group_sal, k, w.order, w.rank_of);
+  if (pmax > 0) {
+    CodesArgs ca;
+    ca.s = s;
+    ca.mt = w.mt;
+    ca.ldw = ldw;
+    ca.N = N;
+    ca.q1_mode = prm.q1_mode;
+    ca.pmax = pmax;
+    ca.rank_of = w.rank_of;
+    ca.Q = w.Qo;
+    ca.S = w.So;
+    ca.Rz = w.Ro;
+    ca.rest = w.mt.rest_o;
+    ca.Wd = nullptr;
+    st = sba_codes_launch(ctx, W, w_dtype, ca);
+    if (st != SLIM_OK) return st;
   }
-  // the per-token merges of all candidates in one launch (grid.y = candidate)
+  SearchArgs sa;
+  sa.s = s;
+  sa.mt = w.mt;
+  sa.Xd = w.Xd;
+  sa.SX = w.SX;
+  sa.Qn = w.Qn;
+  sa.Qo = w.Qo;
+  sa.Sn = w.Sn;
+  sa.So = w.So;
+  sa.Rn = w.Rn;
+  sa.Ro = w.Ro;
+  sa.Yc = w.Yc;
+  sa.R = w.Yt;
+  sa.tok = w.tok;
+  sa.order = w.order;
+  sa.part = w.part;
+  sa.lin = w.lin;
+  sa.pmax = pmax;
+  st = s.ks == 1 ? sba_search_launch<1>(ctx, sa, objective) : s.ks == 2 ? sba_search_launch<2>(ctx, sa, objective) : sba_search_launch<4>(ctx, sa, objective);
+  if (st != SLIM_OK) return st;
   if (objective == SLIM_OBJ_KL)
-    SLIM_LAUNCH(ctx, "sba_kl_finalize", kl_finalize, dim3(kl_blocks, pmax + 1), dim3(256), 0, partial, pstride, parts, t_s,
-                tok, tokB, block_sums, kl_blocks);
+    SLIM_LAUNCH(ctx, "sba_token_sums", sba_token_sums<SLIM_OBJ_KL>, dim3(kl_blocks, pmax + 1), dim3(256), 0, w.part, w.lin, s, w.tokB,
+                w.block_sums, kl_blocks);
   else
-    SLIM_LAUNCH(ctx, "sba_mse_finalize", mse_finalize, dim3(kl_blocks, pmax + 1), dim3(256), 0, partial, pstride, parts,
-                t_s, block_sums, kl_blocks);
-  SLIM_LAUNCH(ctx, "sba_finalize", sba_finalize, dim3(1), dim3(256), 0, block_sums, kl_blocks, obj, pmax, order, k, N,
-              bits, pstar_dev);
+    SLIM_LAUNCH(ctx, "sba_token_sums", sba_token_sums<SLIM_OBJ_MSE>, dim3(kl_blocks, pmax + 1), dim3(256), 0, w.part, w.lin, s, w.tokB,
+                w.block_sums, kl_blocks);
+  SLIM_LAUNCH(ctx, "sba_finalize", sba_finalize, dim3(1), dim3(256), 0, w.block_sums, kl_blocks, obj, pmax, w.order, k, N,
+              w.mt.unit + 2, bits, pstar_dev);
 
   if (!p_star && !obj_curve) return SLIM_OK;       // nothing for the host: the call does not wait
   double* host_obj = reinterpret_cast<double*>(ctx->hpin);
