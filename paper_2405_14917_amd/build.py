@@ -15,7 +15,7 @@ LIB = os.path.join(HERE, "libslim.so")
 OBJ_DIR = os.path.join(HERE, "_build")
 
 SOURCES = ["ctx.hip", "util.hip", "dgemm.hip", "gram.hip", "inverse.hip", "salience.hip", "sba.hip", "quant.hip",
-           "pack.hip", "dequant.hip", "dequant_gemm.hip", "lwc.hip"]
+           "pack.hip", "dequant.hip", "dequant_gemm.hip", "int8_products.hip", "lwc.hip"]
 
 # packed-fp32 code generation is switched off for all device code (a device-compiler option; the host
 # pass does not know the feature and says so, which is harmless)
@@ -34,6 +34,7 @@ def hipcc() -> str:
 # compiler shuttles them between the two register files on every K slab and halves the occupancy.
 EXTRA_FLAGS = {"dgemm.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
                "sba.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form", "-Wno-inline-asm"],
+               "int8_products.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form", "-Wno-inline-asm"],
                # gram.hip and dequant_gemm.hip set M0 in inline asm (destination of its direct-to-LDS loads) and say so in the clobber
                # list, which the compiler remarks on
                "gram.hip": ["-Wno-inline-asm"], "dequant_gemm.hip": ["-Wno-inline-asm"]}

@@ -1,0 +1,506 @@
+// Digits of the operands and the output products on the int8 matrix cores; see int8_products.h.
+#include <algorithm>
+
+#include "int8_products.h"
+
+namespace {
+
+using namespace slimint;
+
+__device__ __forceinline__ void stat(unsigned bits, unsigned& mx, int& lsb, int& bad) {
+  bits &= 0x7fffffffu;
+  if (bits >= 0x7f800000u) {
+    bad = 1;
+    return;
+  }
+  if (bits == 0) return;
+  unsigned mant;
+  int e0;
+  split_float(bits, mant, e0);
+  mx = max(mx, bits);
+  lsb = min(lsb, e0 + __builtin_ctz(mant));
+}
+
+__global__ __launch_bounds__(256) void int_clear(IntMeta mt, int C, int* rest, int nrest) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i < C) {
+    mt.xmax[i] = mt.wmax[i] = 0u;
+    mt.xlsb[i] = mt.wlsb[i] = INT_MAX;
+  }
+  if (i < nrest) rest[i] = 0;
+  if (i == 0) mt.unit[2] = 0;
+}
+
+// grid (C, splits): largest magnitude and last digit of the chunk's rows of X_s
+template <typename T>
+__global__ __launch_bounds__(256) void int_x_stats(const T* __restrict__ X, int64_t ldx, IntShape s, IntMeta mt) {
+  int len;
+  const int ch0 = chunk_begin(s, blockIdx.x, len);
+  unsigned mx = 0;
+  int lsb = INT_MAX, bad = 0;
+  const int64_t quads = s.ts / 4;
+  for (int64_t q = (int64_t)blockIdx.y * 256 + threadIdx.x; q < quads; q += (int64_t)gridDim.y * 256)
+    for (int r = 0; r < len; ++r) {
+      const uint2 raw = *reinterpret_cast<const uint2*>(X + (int64_t)(ch0 + r) * ldx + 4 * q);
+      const T* v = reinterpret_cast<const T*>(&raw);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) stat(float_bits<T>(v[i]), mx, lsb, bad);
+    }
+#pragma unroll
+  for (int d = 32; d > 0; d >>= 1) {
+    mx = max(mx, (unsigned)__shfl_xor((int)mx, d, WAVE));
+    lsb = min(lsb, __shfl_xor(lsb, d, WAVE));
+  }
+  if (bad) atomicOr(&mt.unit[2], 1);
+  if ((threadIdx.x & 63) == 0 && mx) {
+    atomicMax(&mt.xmax[blockIdx.x], mx);
+    atomicMin(&mt.xlsb[blockIdx.x], lsb);
+  }
+}
+
+// grid (ceil(m / 1024), splits): the same for the chunk's columns of W; a thread owns four columns
+template <typename T>
+__global__ __launch_bounds__(256) void int_w_stats(const T* __restrict__ W, int64_t ldw, IntShape s, IntMeta mt) {
+  __shared__ unsigned lmax[264];
+  __shared__ int llsb[264];
+  for (int i = threadIdx.x; i < 264; i += 256) {
+    lmax[i] = 0u;
+    llsb[i] = INT_MAX;
+  }
+  __syncthreads();
+  auto chunk_of = [&](int ch) { const int g = ch / s.beta; return g * s.nchg + (ch - g * s.beta) / s.chk; };
+  const int c0 = chunk_of(blockIdx.x * 1024);
+  const int ch = blockIdx.x * 1024 + threadIdx.x * 4;
+  if (ch < s.m) {
+    unsigned mx = 0;
+    int lsb = INT_MAX, bad = 0;
+    for (int r = blockIdx.y; r < s.n; r += gridDim.y) {
+      T v[4];
+      if constexpr (sizeof(T) == 2)
+        *reinterpret_cast<uint2*>(v) = *reinterpret_cast<const uint2*>(W + (int64_t)r * ldw + ch);
+      else
+        *reinterpret_cast<uint4*>(v) = *reinterpret_cast<const uint4*>(W + (int64_t)r * ldw + ch);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) stat(float_bits<T>(v[i]), mx, lsb, bad);
+    }
+    const int c = chunk_of(ch) - c0;
+    atomicMax(&lmax[c], mx);
+    atomicMin(&llsb[c], lsb);
+    if (bad) atomicOr(&mt.unit[2], 1);
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < 264; i += 256)
+    if (lmax[i]) {
+      atomicMax(&mt.wmax[c0 + i], lmax[i]);
+      atomicMin(&mt.wlsb[c0 + i], llsb[i]);
+    }
+}
+
+// Units and digits in use: `which` + block 0 for X_s, 1 for W.  The unit is the last digit of all values, but no more than 53
+// digits below the largest one; a chunk keeps the digits between its own last one and its own largest value.
+__global__ __launch_bounds__(256) void int_meta(IntMeta mt, int C, int which) {
+  which += blockIdx.x;
+  __shared__ unsigned smx[256];
+  __shared__ int slsb[256];
+  const unsigned* cmax = which ? mt.wmax : mt.xmax;
+  const int* clsb = which ? mt.wlsb : mt.xlsb;
+  int* out = which ? mt.w : mt.x;
+  unsigned mx = 0;
+  int lsb = INT_MAX;
+  for (int c = threadIdx.x; c < C; c += 256) {
+    mx = max(mx, cmax[c]);
+    lsb = min(lsb, clsb[c]);
+  }
+  smx[threadIdx.x] = mx;
+  slsb[threadIdx.x] = lsb;
+  __syncthreads();
+  for (int st = 128; st > 0; st >>= 1) {
+    if (threadIdx.x < st) {
+      smx[threadIdx.x] = max(smx[threadIdx.x], smx[threadIdx.x + st]);
+      slsb[threadIdx.x] = min(slsb[threadIdx.x], slsb[threadIdx.x + st]);
+    }
+    __syncthreads();
+  }
+  mx = smx[0];
+  lsb = slsb[0];
+  unsigned mant;
+  int e0, unit = 0;
+  if (mx) {
+    split_float(mx, mant, e0);
+    unit = max(lsb, e0 + (31 - __builtin_clz(mant)) - 53);
+  }
+  if (threadIdx.x == 0) mt.unit[which] = unit;
+  for (int c = threadIdx.x; c < C; c += 256) {
+    int lo = 0, hi = 0;
+    if (cmax[c]) {
+      const uint64_t v = (uint64_t)fixed_point(cmax[c], unit);
+      lo = max(0, clsb[c] - unit) / 8;
+      uint64_t lim = 0;                                  // largest value of hi balanced digits
+      while (lim < v) {
+        lim = lim * 256 + 127;
+        ++hi;
+      }
+      hi = max(hi, lo);
+    }
+    out[2 * c] = lo;
+    out[2 * c + 1] = hi - lo;
+  }
+}
+
+// grid (ceil(TB / 4), k): a wavefront cuts 32 tokens of one group into digits and sums its channels per token
+template <typename T>
+__global__ __launch_bounds__(256) void int_x_digits(const T* __restrict__ X, int64_t ldx, IntShape s, IntMeta mt,
+                                                    char* __restrict__ Xd, double* __restrict__ SX) {
+  const int lane = threadIdx.x & 63, l32 = lane & 31, h = lane >> 5;
+  const int tb = blockIdx.x * 4 + (threadIdx.x >> 6), g = blockIdx.y;
+  if (tb >= s.TB) return;
+  const int unit = mt.unit[0];
+  const int64_t t = (int64_t)tb * 32 + l32;
+  int64_t sum = 0;
+  for (int cc = 0; cc < s.nchg; ++cc) {
+    const int c = g * s.nchg + cc, lo = mt.x[2 * c], nd = mt.x[2 * c + 1];
+    char* dst = Xd + ((int64_t)c * s.TB + tb) * SI_MAXD * s.ks * 1024 + lane * 16;
+    for (int f = 0; f < s.ks; ++f) {
+      const int j0 = cc * s.chk + f * 32 + h * 16;
+      uint64_t u[16];
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        int64_t v = 0;
+        if (j0 + i < s.beta && t < s.ts) v = fixed_point(float_bits<T>(X[(int64_t)(g * s.beta + j0 + i) * ldx + t]), unit);
+        sum += v;
+        u[i] = digit_bytes(v) >> (8 * lo);
+      }
+      for (int d = 0; d < nd; ++d) {
+        unsigned w[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          w[q] = 0;
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            w[q] |= ((unsigned)u[4 * q + i] & 255u) << (8 * i);
+            u[4 * q + i] >>= 8;
+          }
+        }
+        *reinterpret_cast<uint4*>(dst + ((int64_t)d * s.ks + f) * 1024) = make_uint4(w[0], w[1], w[2], w[3]);
+      }
+    }
+  }
+  // (a sum of up to 512 channels of 54 bits may not fit 53 bits: one rounding)
+  const double other = __shfl_xor((double)sum, 32, WAVE);
+  if (h == 0) SX[(int64_t)g * s.tpad + t] = (double)sum + other;
+}
+
+// ---- a unit per token ----------------------------------------------------------------------------------------------
+// grid (ceil(ts / 1024), splits): a thread owns four columns; largest magnitude (as float bits) and last digit of each
+__global__ __launch_bounds__(256) void int_g_stats(const float* __restrict__ G, int64_t ldg, IntShape s, int* __restrict__ work) {
+  const int64_t t = (int64_t)blockIdx.x * 1024 + threadIdx.x * 4;
+  if (t >= s.ts) return;
+  unsigned mx[4] = {0, 0, 0, 0};
+  int lsb[4] = {INT_MAX, INT_MAX, INT_MAX, INT_MAX}, bad[4] = {0, 0, 0, 0};
+  for (int r = blockIdx.y; r < s.m; r += gridDim.y) {
+    const float4 v = *reinterpret_cast<const float4*>(G + (int64_t)r * ldg + t);
+    stat(__float_as_uint(v.x), mx[0], lsb[0], bad[0]);
+    stat(__float_as_uint(v.y), mx[1], lsb[1], bad[1]);
+    stat(__float_as_uint(v.z), mx[2], lsb[2], bad[2]);
+    stat(__float_as_uint(v.w), mx[3], lsb[3], bad[3]);
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    atomicMax(&work[t + i], bad[i] ? INT_MAX : (int)mx[i]);
+    atomicMin(&work[s.ts + t + i], lsb[i]);
+  }
+}
+__global__ __launch_bounds__(256) void int_g_clear(int64_t ts, int* __restrict__ work) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i < ts) {
+    work[i] = 0;
+    work[ts + i] = INT_MAX;
+  }
+}
+// the unit of a column: its last digit, but no more than 53 digits below its largest value
+__global__ __launch_bounds__(256) void int_g_units(int64_t ts, const int* __restrict__ work, int* __restrict__ token_unit) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= ts) return;
+  const int mx = work[i];
+  int unit = 0;
+  if (mx == INT_MAX) {
+    unit = INT_MIN;
+  } else if (mx) {
+    unsigned mant;
+    int e0;
+    split_float((unsigned)mx, mant, e0);
+    unit = max(work[ts + i], e0 + (31 - __builtin_clz(mant)) - 53);
+  }
+  token_unit[i] = unit;
+}
+
+// grid (ceil(TB / 4), k): a wavefront finds the digits in use of 32 columns of every chunk of one group, and cuts them
+__global__ __launch_bounds__(256) void int_g_digits(const float* __restrict__ G, int64_t ldg, IntShape s, int* __restrict__ meta,
+                                                    const int* __restrict__ token_unit, char* __restrict__ Xd, double* __restrict__ SX) {
+  const int lane = threadIdx.x & 63, l32 = lane & 31, h = lane >> 5;
+  const int tb = blockIdx.x * 4 + (threadIdx.x >> 6), g = blockIdx.y;
+  if (tb >= s.TB) return;
+  const int64_t t = (int64_t)tb * 32 + l32;
+  const bool live = t < s.ts;
+  const int unit = live ? token_unit[t] : INT_MIN;
+  auto value = [&](int j) -> int64_t {
+    if (j >= s.beta || unit == INT_MIN) return 0;
+    return fixed_point(__float_as_uint(G[(int64_t)(g * s.beta + j) * ldg + t]), unit);
+  };
+  double sum = 0.0;
+  for (int cc = 0; cc < s.nchg; ++cc) {
+    const int c = g * s.nchg + cc;
+    uint64_t mx = 0, any = 0;
+    for (int f = 0; f < s.ks; ++f)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const int64_t v = value(cc * s.chk + f * 32 + h * 16 + i);
+        const uint64_t av = (uint64_t)(v < 0 ? -v : v);
+        mx = mx > av ? mx : av;
+        any |= av;
+      }
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) {
+      const uint64_t om = ((uint64_t)(unsigned)__shfl_xor((int)(mx >> 32), d, WAVE) << 32) | (unsigned)__shfl_xor((int)mx, d, WAVE);
+      mx = mx > om ? mx : om;
+      any |= ((uint64_t)(unsigned)__shfl_xor((int)(any >> 32), d, WAVE) << 32) | (unsigned)__shfl_xor((int)any, d, WAVE);
+    }
+    int lo = 0, hi = 0;
+    if (mx) {
+      lo = __builtin_ctzll(any) / 8;
+      for (uint64_t lim = 0; lim < mx; ++hi) lim = lim * 256 + 127;       // largest value of hi balanced digits
+      hi = max(hi, lo);
+    }
+    const int nd = hi - lo;
+    if (lane == 0) {
+      meta[2 * ((int64_t)c * s.TB + tb)] = lo;
+      meta[2 * ((int64_t)c * s.TB + tb) + 1] = nd;
+    }
+    char* dst = Xd + ((int64_t)c * s.TB + tb) * SI_MAXD * s.ks * 1024 + lane * 16;
+    for (int f = 0; f < s.ks; ++f) {
+      uint64_t u[16];
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const int64_t v = value(cc * s.chk + f * 32 + h * 16 + i);
+        sum += (double)v;
+        u[i] = digit_bytes(v) >> (8 * lo);
+      }
+      for (int d = 0; d < nd; ++d) {
+        unsigned w[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          w[q] = 0;
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            w[q] |= ((unsigned)u[4 * q + i] & 255u) << (8 * i);
+            u[4 * q + i] >>= 8;
+          }
+        }
+        *reinterpret_cast<uint4*>(dst + ((int64_t)d * s.ks + f) * 1024) = make_uint4(w[0], w[1], w[2], w[3]);
+      }
+    }
+  }
+  sum += __shfl_xor(sum, 32, WAVE);
+  if (h == 0) SX[(int64_t)g * s.tpad + t] = sum;
+}
+
+// REF: Y = W X_s from the digits of W; else Y = W_N X_s
+template <int KS, bool REF>
+__global__ __launch_bounds__(256, 3) void int_outputs(OutArgs a) {
+  constexpr int R = 2, NW = 4;
+  using TL = Tile<KS, R>;
+  extern __shared__ __align__(16) char si_smem[];
+  const IntShape& s = a.s;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l32 = lane & 31, h = lane >> 5;
+  int rt, tb;
+  tile_of(blockIdx.x, s.RT, s.TB, rt, tb);
+  const int row0 = rt * SI_ROWS + wave * 64;
+  const unsigned lds0 = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(uintptr_t)((__attribute__((address_space(3))) char*)si_smem));
+  const int64_t rstride = (int64_t)s.C * KS * 1024;
+  const char* q0 = a.Q + (int64_t)(row0 >> 5) * rstride;
+  const unsigned lane16 = lane * 16;
+  // the chunks' digits (X_s: bits 0 .. 7 lowest digit and count, W: bits 8 .. 15) in LDS
+  int* tab = reinterpret_cast<int*>(si_smem + 2 * TL::STAGE);
+  auto describe = [&](int c) {
+    const int* x = a.mt.x + 2 * ((int64_t)c * a.mstride_c + (int64_t)tb * a.mstride_t);
+    return x[0] | (x[1] << 4) | (REF ? (a.mt.w[2 * c] << 8) | (a.mt.w[2 * c + 1] << 12) : 0);
+  };
+  for (int c = tid; c < min(s.C, SI_TAB); c += 256) tab[c] = describe(c);
+  const int unit = __builtin_amdgcn_readfirstlane((a.token_unit ? 0 : a.mt.unit[0]) + (REF ? a.mt.unit[1] : 0));
+  __syncthreads();
+  auto chunk_info = [&](int c) { return __builtin_amdgcn_readfirstlane(c < SI_TAB ? tab[c] : describe(c)); };
+
+  double y[R][16];
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) y[r][v] = 0.0;
+  TL tl;
+  auto load_first = [&](int c) {                // the first (or only) set of chunk c
+    tl.load_codes(q0 + (int64_t)c * KS * 1024, rstride, lane16);
+    if (!REF) {
+      tl.load_scales(a.S + (int64_t)(c / s.nchg) * s.npad + row0, l32);
+    } else {
+#pragma unroll
+      for (int r = 0; r < R; ++r) tl.s[r] = 1.0;
+    }
+  };
+  auto first_stage = [&](int c, int info) { return stage_word(c, info & 15, min(SI_STAGE_D, (info >> 4) & 15), 1); };
+  int info = chunk_info(0), word = first_stage(0, info), buf = 0;
+  stage_digits<KS, NW>(a.Xd, s, word, info & 15, tb, lds0, wave, lane);
+  load_first(0);
+  for (;;) {
+    const int c = stage_chunk(word), lo = stage_lo(word), nd = stage_nd(word);
+    const int left = (info & 15) + ((info >> 4) & 15) - lo - nd;            // digits of the chunk behind this stage
+    const bool done = left <= 0 && c + 1 == s.C;
+    const int next_info = left > 0 ? info : chunk_info(min(c + 1, s.C - 1));
+    const int next = left > 0 ? stage_word(c, lo + nd, min(SI_STAGE_D, left), 0) : first_stage(min(c + 1, s.C - 1), next_info);
+    const int sets = REF ? (info >> 12) & 15 : 1, wlo = (info >> 8) & 15;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (!done) stage_digits<KS, NW>(a.Xd, s, next, next_info & 15, tb, lds0 + (buf ^ 1) * TL::STAGE, wave, lane);
+    const char* x = si_smem + buf * TL::STAGE + lane * 16;
+    double sc[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) sc[r] = tl.s[r];
+    if (sets == 0 || nd == 0) load_first(stage_chunk(next));                // a chunk of zeros
+    for (int j = 0; j < sets; ++j) {
+      for (int p = (nd - 1) >> 1; p >= 0; --p) {
+        v16i acc[R];
+        tl.pair(x, p, 2 * p + 1 < nd, acc);
+        if (p == 0) {
+          if (j + 1 < sets)
+            tl.load_codes(q0 + (j + 1) * a.plane + (int64_t)c * KS * 1024, rstride, lane16);
+          else
+            load_first(stage_chunk(next));
+        }
+        add_scaled<R>(y, acc, sc, unit + 8 * (lo + 2 * p) + (REF ? 8 * (wlo + j) : 0));
+      }
+    }
+    const int g = c / s.nchg;
+    if (!REF && stage_first(word) && c == g * s.nchg && a.rest[g] >= a.rest_from) {
+      // zeros outside int8: what the codes do not hold times the sum of the group's activations
+      const double* Rz = a.Rz + (int64_t)g * s.npad + row0 + l32;
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const double sx = ldexp(a.SX[(int64_t)g * s.tpad + tb * 32 + 8 * (v >> 2) + 4 * h + (v & 3)], unit);
+#pragma unroll
+        for (int r = 0; r < R; ++r) y[r][v] = fma(-Rz[32 * r], sx, y[r][v]);
+      }
+    }
+    if (done) break;
+    word = next;
+    info = next_info;
+    buf ^= 1;
+  }
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int64_t t = (int64_t)tb * 32 + 8 * q + 4 * h;
+    if (t >= s.ts) continue;
+    int tu[4] = {0, 0, 0, 0};
+    if (a.token_unit) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v) tu[v] = a.token_unit[t + v];
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const int row = row0 + 32 * r + l32;
+      if (row >= s.n) continue;
+      double o[4];
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        o[v] = y[r][4 * q + v];
+        if (a.token_unit) o[v] = tu[v] == INT_MIN ? NAN : ldexp(o[v], tu[v]);
+        if (a.sub) o[v] -= a.sub[(int64_t)row * s.ts + t + v];
+      }
+      double* out = a.Y + (int64_t)row * s.ts + t;
+      *reinterpret_cast<double2*>(out) = make_double2(o[0], o[1]);
+      *reinterpret_cast<double2*>(out + 2) = make_double2(o[2], o[3]);
+    }
+  }
+}
+
+template <int KS>
+slim_status outputs_launch(slim_ctx* ctx, const char* name, const OutArgs& a, bool ref) {
+  const dim3 grid(a.s.RT * a.s.TB);
+  const size_t smem = 2 * Tile<KS, 2>::STAGE + sizeof(int) * std::min(a.s.C, SI_TAB);
+  if (ref)
+    SLIM_LAUNCH(ctx, name, (int_outputs<KS, true>), grid, dim3(256), smem, a);
+  else
+    SLIM_LAUNCH(ctx, name, (int_outputs<KS, false>), grid, dim3(256), smem, a);
+  return SLIM_OK;
+}
+
+template <typename T>
+slim_status x_stats(slim_ctx* ctx, const IntShape& s, const IntMeta& mt, const T* X, int64_t ldx) {
+  SLIM_LAUNCH(ctx, "int_x_stats", int_x_stats<T>, dim3(s.C, slim_cdiv(s.ts, 1024)), dim3(256), 0, X, ldx, s, mt);
+  return SLIM_OK;
+}
+template <typename T>
+slim_status x_digits(slim_ctx* ctx, const IntShape& s, const IntMeta& mt, const T* X, int64_t ldx, char* Xd, double* SX) {
+  SLIM_LAUNCH(ctx, "int_x_digits", int_x_digits<T>, dim3(slim_cdiv(s.TB, 4), s.k), dim3(256), 0, X, ldx, s, mt, Xd, SX);
+  return SLIM_OK;
+}
+template <typename T>
+slim_status w_stats(slim_ctx* ctx, const IntShape& s, const IntMeta& mt, const T* W, int64_t ldw) {
+  SLIM_LAUNCH(ctx, "int_w_stats", int_w_stats<T>, dim3(slim_cdiv(s.m, 1024), std::min(s.n, 128)), dim3(256), 0, W, ldw, s, mt);
+  return SLIM_OK;
+}
+
+}  // namespace
+
+IntShape slim_int_shape(int n, int m, int beta, int64_t t_s) {
+  IntShape s;
+  s.n = n;
+  s.m = m;
+  s.beta = beta;
+  s.k = m / beta;
+  s.ts = t_s;
+  s.chk = beta <= 32 ? 32 : beta <= 64 ? 64 : SI_CHUNK;
+  s.ks = s.chk / 32;
+  s.nchg = slim_cdiv(beta, s.chk);
+  s.C = s.k * s.nchg;
+  s.npad = slim_cdiv(n, SI_ROWS) * SI_ROWS;
+  s.RT = s.npad / SI_ROWS;
+  s.tpad = slim_cdiv(t_s, SI_TOK) * SI_TOK;
+  s.TB = s.tpad / SI_TOK;
+  return s;
+}
+
+slim_status slim_int_clear(slim_ctx* ctx, const IntShape& s, const IntMeta& mt, int* rest, int nrest) {
+  SLIM_LAUNCH(ctx, "int_clear", int_clear, dim3(slim_cdiv(std::max(s.C, nrest), 256)), dim3(256), 0, mt, s.C, rest, nrest);
+  return SLIM_OK;
+}
+slim_status slim_int_x_stats(slim_ctx* ctx, const IntShape& s, const IntMeta& mt, const void* X, slim_dtype dt, int64_t ldx) {
+  return dt == SLIM_F16 ? x_stats(ctx, s, mt, static_cast<const __half*>(X), ldx) : x_stats(ctx, s, mt, static_cast<const __hip_bfloat16*>(X), ldx);
+}
+slim_status slim_int_w_stats(slim_ctx* ctx, const IntShape& s, const IntMeta& mt, const void* W, slim_dtype dt, int64_t ldw) {
+  return dt == SLIM_F16    ? w_stats(ctx, s, mt, static_cast<const __half*>(W), ldw)
+         : dt == SLIM_BF16 ? w_stats(ctx, s, mt, static_cast<const __hip_bfloat16*>(W), ldw)
+                           : w_stats(ctx, s, mt, static_cast<const float*>(W), ldw);
+}
+slim_status slim_int_meta(slim_ctx* ctx, const IntShape& s, const IntMeta& mt) {
+  SLIM_LAUNCH(ctx, "int_meta", int_meta, dim3(2), dim3(256), 0, mt, s.C, 0);
+  return SLIM_OK;
+}
+slim_status slim_int_weight_meta(slim_ctx* ctx, const IntShape& s, const IntMeta& mt) {
+  SLIM_LAUNCH(ctx, "int_meta", int_meta, dim3(1), dim3(256), 0, mt, s.C, 1);
+  return SLIM_OK;
+}
+slim_status slim_int_x_digits(slim_ctx* ctx, const IntShape& s, const IntMeta& mt, const void* X, slim_dtype dt, int64_t ldx, char* Xd, double* SX) {
+  return dt == SLIM_F16 ? x_digits(ctx, s, mt, static_cast<const __half*>(X), ldx, Xd, SX)
+                        : x_digits(ctx, s, mt, static_cast<const __hip_bfloat16*>(X), ldx, Xd, SX);
+}
+slim_status slim_int_g_digits(slim_ctx* ctx, const IntShape& s, const IntMeta& mt, const float* G, int64_t ldg, int* work, int* token_unit,
+                              char* Xd, double* SX) {
+  const dim3 tgrid(slim_cdiv(s.ts, 256)), block(256);
+  SLIM_LAUNCH(ctx, "int_g_clear", int_g_clear, tgrid, block, 0, s.ts, work);
+  SLIM_LAUNCH(ctx, "int_g_stats", int_g_stats, dim3(slim_cdiv(s.ts, 1024), std::min(s.m, 128)), block, 0, G, ldg, s, work);
+  SLIM_LAUNCH(ctx, "int_g_units", int_g_units, tgrid, block, 0, s.ts, work, token_unit);
+  SLIM_LAUNCH(ctx, "int_g_digits", int_g_digits, dim3(slim_cdiv(s.TB, 4), s.k), block, 0, G, ldg, s, mt.x, token_unit, Xd, SX);
+  return SLIM_OK;
+}
+slim_status slim_int_outputs(slim_ctx* ctx, const char* name, const OutArgs& a, bool ref) {
+  return a.s.ks == 1 ? outputs_launch<1>(ctx, name, a, ref) : a.s.ks == 2 ? outputs_launch<2>(ctx, name, a, ref) : outputs_launch<4>(ctx, name, a, ref);
+}

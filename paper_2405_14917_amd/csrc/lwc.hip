@@ -11,22 +11,29 @@
 //     g = dL/dW_hat = 2 (W_hat - W) G / (n T)                                (fp64 matrix cores)
 //     dW_hat_j / d delta = (q_j - z) - w_j / delta   or, clipped,   (q_j - z) - lo / delta
 //     dW_hat_j / d lo at fixed delta = 0   or, clipped,   1
-// Everything is fp64; one wavefront per (row, group) in both elementwise kernels, fixed-order reductions.
+// Everything is fp64.  D G = W_hat G - W G with W_hat = delta (q - z): the first product is one of small integers with G's
+// digits (int8_products.h, a unit per column of G, which G's fp32 entries fit exactly unless they are 2^-30 of their column's
+// largest), the second one does not change and is taken once, from the digits of W.  Two kernels per step: the product,
+// and one pass over W and D G that forms the derivatives, takes the AdamW step and writes the next step's integers, 16
+// lanes per (row, group), fixed-order reductions.
+// The difference of the two products loses the digits that W_hat and W share: none that matter at two to five bits (loss
+// curves within 2e-16 of the float64 oracle's either way), but at eight bits with outlier channels 1e-14 instead of 2e-15.
+// Layers with a group of more than five bits therefore multiply W_hat - W itself, on the fp64 matrix cores.
+// What bounds it: the vector work behind the MFMAs of the product (figures at lwc_step).
 #include <cmath>
 
-#include "slim_device.h"
-#include "slim_internal.h"
+#include "int8_products.h"
 
 namespace {
 
-using namespace slimdev;
+using namespace slimint;
 
 struct LwcGroup {
   double M, m_, s_hi, s_lo, lo, delta, z, Q;
   bool live;
 };
 
-// parameters of one (row, group) from its extreme values and clipping strengths; wavefront-uniform
+// parameters of one (row, group) from its extreme values and clipping strengths; the same in the lanes of a row
 __device__ __forceinline__ LwcGroup lwc_group(double M, double m_, double gamma, double betap, int bits) {
   LwcGroup p;
   p.M = M;
@@ -42,21 +49,24 @@ __device__ __forceinline__ LwcGroup lwc_group(double M, double m_, double gamma,
   return p;
 }
 
+
 struct LwcArgs {
-  const double* W;        // n x m fp64 (ld = m)
-  int n, m, beta;
+  IntShape s;             // n x m weights against the m columns of G
+  IntMeta mt;
+  int64_t ldw;
   const uint8_t* bits;    // k
-  double* gamma;          // n x k each
-  double* betap;
-  double* m1g;
-  double* vg;
-  double* m1b;
-  double* vb;
-  double* D;              // n x m: W_hat - W
+  double *M, *mn;         // k x npad each: extreme values, strengths, moments
+  double *gamma, *betap, *m1g, *vg, *m1b, *vb;
+  char* Q;                // integers of the next product, in operand order
+  double *S, *Rz;         // k x npad: their scales, and the scale times what the zero has beyond the integers
+  int* rest;              // k: last step at which some row of the group had such a part
+  char* Wd;               // digits of W
+  double* D;              // n x m: W_hat - W in place of the integers (layers with wide groups), else nullptr
   const double* DG;       // n x m: D G
-  double* lp;             // n x k: sum_j D_j DG_j of the (row, group)
+  double* lp;             // the workgroups' sums of D_j (D G)_j
   double gscale;          // 2 / (n T)
-  double lr, b1, b2, eps, c1, c2;   // AdamW; c1 = 1 - b1^step, c2 = 1 - b2^step
+  double init, lr, b1, b2, eps, c1, c2;   // AdamW; c1 = 1 - b1^step, c2 = 1 - b2^step
+  int step;               // of the integers that are written
   // final quantisation
   uint8_t* codes;         // n x m (ld = m)
   double* scale;          // n x k
@@ -65,128 +75,303 @@ struct LwcArgs {
   int what_f64;
 };
 
-__device__ __forceinline__ void lwc_extremes(const double* w, int beta, int lane, double& M, double& m_) {
-  double mx = -INFINITY, mn = INFINITY;
-  for (int c = lane; c < beta; c += 64) {
-    const double v = w[c];
-    mx = fmax(mx, v);
-    mn = fmin(mn, v);
-  }
-  M = wave_max(mx);
-  m_ = wave_min(mn);
+// rint(w / delta): the product with the reciprocal differs from the quotient by less than 1e-15 of it, so the two can round
+// apart only next to a tie
+__device__ __forceinline__ double rint_quotient(double w, const LwcGroup& p, double inv) {
+  const double r = w * inv;
+  double c = rint(r);
+  if (fabs(fabs(r - c) - 0.5) <= 1e-9 * (1.0 + fabs(r))) c = rint(w / p.delta);
+  return c;
 }
 
-// MODE 0: D = W_hat - W.   MODE 1: the final quantisation (codes, scale, zero, W_hat).
-template <int MODE>
-__global__ __launch_bounds__(256) void lwc_forward_kernel(LwcArgs a) {
-  const int lane = threadIdx.x & 63;
-  const int k = a.m / a.beta;
-  const int64_t unit = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (unit >= (int64_t)a.n * k) return;
-  const int row = (int)(unit / k), g = (int)(unit % k);
-  const int64_t base = (int64_t)row * a.m + (int64_t)g * a.beta;
-  const double* w = a.W + base;
-  double M, m_;
-  lwc_extremes(w, a.beta, lane, M, m_);
-  const int bits = min(max((int)a.bits[g], 1), 8);
-  const LwcGroup p = lwc_group(M, m_, a.gamma[unit], a.betap[unit], bits);
-  for (int c = lane; c < a.beta; c += 64) {
-    const double wv = w[c];
-    const double q = fmin(fmax(rint(wv / p.delta) + p.z, 0.0), p.Q);
-    const double what = p.delta * (q - p.z);
-    if (MODE == 0) {
-      a.D[base + c] = what - wv;
-    } else {
-      a.codes[base + c] = (uint8_t)q;
-      if (a.What) {
-        if (a.what_f64)
-          static_cast<double*>(a.What)[base + c] = what;
-        else
-          static_cast<float*>(a.What)[base + c] = (float)what;
+// the integers, scale and zero's rest of one (row, group)
+template <typename T>
+__device__ __forceinline__ void write_integers(const LwcArgs& a, const T* w, int row, int g, int l16, bool live, const LwcGroup& p) {
+  const IntShape& s = a.s;
+  const double inv = 1.0 / p.delta;
+  if (a.D) {
+    double* d = a.D + (int64_t)row * s.m + (int64_t)g * s.beta;
+    for (int j = l16 * 4; live && j < s.beta; j += 64) {
+      double v[4];
+      load4<T>(w + j, v);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) v[i] = p.delta * (fmin(fmax(rint_quotient(v[i], p, inv) + p.z, 0.0), p.Q) - p.z) - v[i];
+      *reinterpret_cast<double2*>(d + j) = make_double2(v[0], v[1]);
+      *reinterpret_cast<double2*>(d + j + 2) = make_double2(v[2], v[3]);
+    }
+    return;
+  }
+  const double z0 = fmin(fmax(p.z, p.Q - 127.0), 128.0);
+  if (l16 == 0) {
+    a.S[(int64_t)g * s.npad + row] = live ? p.delta : 0.0;
+    a.Rz[(int64_t)g * s.npad + row] = live ? p.delta * (p.z - z0) : 0.0;
+    if (live && p.z != z0) atomicMax(&a.rest[g], a.step);
+  }
+  for (int j = l16 * 4; j < s.nchg * s.chk; j += 64) {
+    int c;
+    const int64_t dst = operand_offset(s, row, g, j, c);
+    unsigned word = 0;
+    if (live && j < s.beta) {
+      double v[4];
+      load4<T>(w + j, v);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const double q = fmin(fmax(rint_quotient(v[i], p, inv) + p.z, 0.0), p.Q);
+        word |= ((unsigned)(int)(q - z0) & 255u) << (8 * i);
       }
     }
-  }
-  if (MODE == 1 && lane == 0) {
-    a.scale[unit] = p.delta;
-    a.zero[unit] = p.z;
+    *reinterpret_cast<unsigned*>(a.Q + dst) = word;
   }
 }
 
-// derivatives of the (row, group)'s two strengths, their AdamW step, and the (row, group)'s share of the loss
-__global__ __launch_bounds__(256) void lwc_backward_adam(LwcArgs a) {
-  const int lane = threadIdx.x & 63;
-  const int k = a.m / a.beta;
-  const int64_t unit = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (unit >= (int64_t)a.n * k) return;
-  const int row = (int)(unit / k), g = (int)(unit % k);
-  const int64_t base = (int64_t)row * a.m + (int64_t)g * a.beta;
-  const double* w = a.W + base;
-  double M, m_;
-  lwc_extremes(w, a.beta, lane, M, m_);
-  const int bits = min(max((int)a.bits[g], 1), 8);
-  const double gamma = a.gamma[unit], betap = a.betap[unit];
-  const LwcGroup p = lwc_group(M, m_, gamma, betap, bits);
-  double s1 = 0.0, s2 = 0.0, lsum = 0.0;
-  for (int c = lane; c < a.beta; c += 64) {
-    const double wv = w[c];
-    const double u = rint(wv / p.delta) + p.z;
-    const double q = fmin(fmax(u, 0.0), p.Q);
-    const bool inside = (u >= 0.0) && (u <= p.Q);
-    const double dg = a.DG[base + c];
-    const double gj = a.gscale * dg;
-    const double dwd = inside ? (q - p.z) - wv / p.delta : (q - p.z) - p.lo / p.delta;
-    s1 += gj * dwd;
-    s2 += inside ? 0.0 : gj;
-    lsum += a.D[base + c] * dg;
-  }
-  s1 = wave_sum(s1);
-  s2 = wave_sum(s2);
-  lsum = wave_sum(lsum);
-  if (lane != 0) return;
-  a.lp[unit] = lsum;
-  const double d_hi = p.live ? s1 / p.Q : 0.0;
-  const double d_lo = p.live ? -s1 / p.Q + s2 : 0.0;
-  const double gg = d_hi * p.M * p.s_hi * (1.0 - p.s_hi);
-  const double gb = d_lo * p.m_ * p.s_lo * (1.0 - p.s_lo);
-  {
-    const double m1 = a.b1 * a.m1g[unit] + (1.0 - a.b1) * gg;
-    const double v = a.b2 * a.vg[unit] + (1.0 - a.b2) * gg * gg;
-    a.m1g[unit] = m1;
-    a.vg[unit] = v;
-    a.gamma[unit] = gamma - a.lr * (m1 / a.c1) / (sqrt(v / a.c2) + a.eps);
-  }
-  {
-    const double m1 = a.b1 * a.m1b[unit] + (1.0 - a.b1) * gb;
-    const double v = a.b2 * a.vb[unit] + (1.0 - a.b2) * gb * gb;
-    a.m1b[unit] = m1;
-    a.vb[unit] = v;
-    a.betap[unit] = betap - a.lr * (m1 / a.c1) / (sqrt(v / a.c2) + a.eps);
+// grid (npad / 16, y): 16 lanes per row, groups blockIdx.y, + gridDim.y, ...: extremes, start values, the digits of W and the
+// first integers
+template <typename T>
+__global__ __launch_bounds__(256) void lwc_init(const T* __restrict__ W, LwcArgs a) {
+  const IntShape& s = a.s;
+  const int lane = threadIdx.x & 63, l16 = lane & 15;
+  const int row = blockIdx.x * 16 + (threadIdx.x >> 6) * 4 + (lane >> 4);
+  const bool live = row < s.n;
+  const int64_t plane = (int64_t)s.npad * s.C * s.chk;
+  const int wunit = a.mt.unit[1];
+  for (int g = blockIdx.y; g < s.k; g += gridDim.y) {
+    const T* w = W + (int64_t)min(row, s.n - 1) * a.ldw + (int64_t)g * s.beta;
+    double mx = -INFINITY, mn = INFINITY;
+    for (int j = l16 * 4; j < s.beta; j += 64) {
+      double v[4];
+      load4<T>(w + j, v);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        mx = fmax(mx, v[i]);
+        mn = fmin(mn, v[i]);
+      }
+    }
+    mx = row_reduce<OpMax>(mx);
+    mn = row_reduce<OpMin>(mn);
+    const int64_t u = (int64_t)g * s.npad + row;
+    if (l16 == 0) {
+      a.M[u] = mx;
+      a.mn[u] = mn;
+      a.gamma[u] = a.betap[u] = a.init;
+      a.m1g[u] = a.vg[u] = a.m1b[u] = a.vb[u] = 0.0;
+    }
+    for (int j = l16 * 4; !a.D && j < s.nchg * s.chk; j += 64) {
+      int c;
+      const int64_t dst = operand_offset(s, row, g, j, c);
+      double v[4] = {0.0, 0.0, 0.0, 0.0};
+      if (live && j < s.beta) load4<T>(w + j, v);
+      const unsigned bits4[4] = {__float_as_uint((float)v[0]), __float_as_uint((float)v[1]), __float_as_uint((float)v[2]),
+                                 __float_as_uint((float)v[3])};
+      store_digits(a.Wd, plane, dst, bits4, wunit, a.mt.w[2 * c], a.mt.w[2 * c + 1]);
+    }
+    const LwcGroup p = lwc_group(mx, mn, a.init, a.init, min(max((int)a.bits[g], 1), 8));
+    write_integers<T>(a, w, row, g, l16, live, p);
   }
 }
 
-// the (row, group)'s share of the loss alone (after the last step)
-__global__ __launch_bounds__(256) void lwc_loss_kernel(LwcArgs a) {
-  const int lane = threadIdx.x & 63;
-  const int k = a.m / a.beta;
-  const int64_t unit = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (unit >= (int64_t)a.n * k) return;
-  const int64_t base = (unit / k) * a.m + (unit % k) * a.beta;
-  double lsum = 0.0;
-  for (int c = lane; c < a.beta; c += 64) lsum += a.D[base + c] * a.DG[base + c];
-  lsum = wave_sum(lsum);
-  if (lane == 0) a.lp[unit] = lsum;
+__device__ __forceinline__ double row_first(double v, int lane) {
+  return __hiloint2double(__shfl(__double2hiint(v), lane & 48, WAVE), __shfl(__double2loint(v), lane & 48, WAVE));
 }
 
-__global__ __launch_bounds__(256) void lwc_fill(double* p, int64_t n, double v) {
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) p[i] = v;
+// The (row, group)'s share of the loss and, with TRAIN, the derivatives of its two strengths, their AdamW step, and the
+// integers of the next product.  4096 x 4096 (20 steps 11.6 instead of 42 ms): this pass 78 us, the product 505 us; on the fp64
+// matrix cores the product took 1.9 ms, and the two passes over fp64 copies of W, W_hat - W and D G 0.2 ms.
+template <typename T, bool TRAIN>
+__global__ __launch_bounds__(256) void lwc_step(const T* __restrict__ W, LwcArgs a) {
+  __shared__ double red[16];
+  const IntShape& s = a.s;
+  const int lane = threadIdx.x & 63, l16 = lane & 15;
+  const int slot = (threadIdx.x >> 6) * 4 + (lane >> 4), row = blockIdx.x * 16 + slot;
+  const bool live = row < s.n;
+  double loss = 0.0;
+  for (int g = blockIdx.y; g < s.k; g += gridDim.y) {
+    const int64_t u = (int64_t)g * s.npad + row;
+    const T* w = W + (int64_t)min(row, s.n - 1) * a.ldw + (int64_t)g * s.beta;
+    const double* dgp = a.DG + (int64_t)min(row, s.n - 1) * s.m + (int64_t)g * s.beta;
+    const int bits = min(max((int)a.bits[g], 1), 8);
+    double gamma = a.gamma[u], betap = a.betap[u];
+    const double M = a.M[u], mn = a.mn[u];
+    const LwcGroup p = lwc_group(M, mn, gamma, betap, bits);
+    const double inv = 1.0 / p.delta, clipped = p.lo * inv;
+    double s1 = 0.0, s2 = 0.0, lsum = 0.0;
+    for (int j = l16 * 4; j < s.beta; j += 64) {
+      double v[4];
+      load4<T>(w + j, v);
+      const double2 d0 = *reinterpret_cast<const double2*>(dgp + j), d1 = *reinterpret_cast<const double2*>(dgp + j + 2);
+      const double dg[4] = {d0.x, d0.y, d1.x, d1.y};
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const double un = rint_quotient(v[i], p, inv) + p.z;
+        const double q = fmin(fmax(un, 0.0), p.Q);
+        const bool inside = (un >= 0.0) && (un <= p.Q);
+        lsum += (p.delta * (q - p.z) - v[i]) * dg[i];
+        if (TRAIN) {
+          const double gj = a.gscale * dg[i];
+          s1 += gj * ((q - p.z) - (inside ? v[i] * inv : clipped));
+          s2 += inside ? 0.0 : gj;
+        }
+      }
+    }
+    lsum = row_sum(lsum);
+    if (live) loss += lsum;
+    if (TRAIN) {
+      s1 = row_sum(s1);
+      s2 = row_sum(s2);
+      const double d_hi = p.live ? s1 / p.Q : 0.0;
+      const double d_lo = p.live ? -s1 / p.Q + s2 : 0.0;
+      const double gg = d_hi * M * p.s_hi * (1.0 - p.s_hi);
+      const double gb = d_lo * mn * p.s_lo * (1.0 - p.s_lo);
+      const double m1g = a.b1 * a.m1g[u] + (1.0 - a.b1) * gg, vg = a.b2 * a.vg[u] + (1.0 - a.b2) * gg * gg;
+      const double m1b = a.b1 * a.m1b[u] + (1.0 - a.b1) * gb, vb = a.b2 * a.vb[u] + (1.0 - a.b2) * gb * gb;
+      gamma -= a.lr * (m1g / a.c1) / (sqrt(vg / a.c2) + a.eps);
+      betap -= a.lr * (m1b / a.c1) / (sqrt(vb / a.c2) + a.eps);
+      if (l16 == 0) {
+        a.m1g[u] = m1g;
+        a.vg[u] = vg;
+        a.m1b[u] = m1b;
+        a.vb[u] = vb;
+        a.gamma[u] = gamma;
+        a.betap[u] = betap;
+      }
+      const LwcGroup pn = lwc_group(M, mn, row_first(gamma, lane), row_first(betap, lane), bits);
+      write_integers<T>(a, w, row, g, l16, live, pn);
+    }
+  }
+  if (l16 == 0) red[slot] = loss;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double t = 0.0;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) t += red[i];
+    a.lp[(int64_t)blockIdx.y * gridDim.x + blockIdx.x] = t;
+  }
+}
+
+// codes, scale, zero and W_hat with the final strengths
+template <typename T>
+__global__ __launch_bounds__(256) void lwc_final(const T* __restrict__ W, LwcArgs a) {
+  const IntShape& s = a.s;
+  const int lane = threadIdx.x & 63, l16 = lane & 15;
+  const int row = blockIdx.x * 16 + (threadIdx.x >> 6) * 4 + (lane >> 4);
+  if (row >= s.n) return;
+  for (int g = blockIdx.y; g < s.k; g += gridDim.y) {
+    const int64_t u = (int64_t)g * s.npad + row, base = (int64_t)row * s.m + (int64_t)g * s.beta;
+    const T* w = W + (int64_t)row * a.ldw + (int64_t)g * s.beta;
+    const LwcGroup p = lwc_group(a.M[u], a.mn[u], a.gamma[u], a.betap[u], min(max((int)a.bits[g], 1), 8));
+    const double inv = 1.0 / p.delta;
+    for (int j = l16 * 4; j < s.beta; j += 64) {
+      double v[4];
+      load4<T>(w + j, v);
+      unsigned word = 0;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const double q = fmin(fmax(rint_quotient(v[i], p, inv) + p.z, 0.0), p.Q);
+        word |= (unsigned)q << (8 * i);
+        v[i] = p.delta * (q - p.z);
+      }
+      *reinterpret_cast<unsigned*>(a.codes + base + j) = word;
+      if (a.What) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          if (a.what_f64)
+            static_cast<double*>(a.What)[base + j + i] = v[i];
+          else
+            static_cast<float*>(a.What)[base + j + i] = (float)v[i];
+        }
+      }
+    }
+    if (l16 == 0) {
+      a.scale[(int64_t)row * s.k + g] = p.delta;
+      a.zero[(int64_t)row * s.k + g] = p.z;
+    }
+  }
+}
+
+struct LwcWorkspace {
+  IntShape s;
+  IntMeta mt;
+  int64_t plane;
+  int blocks_x, blocks_y;
+  char *Xd, *Wd, *Q;
+  double *SX, *WG, *DG, *lp, *loss;
+  double* par[10];
+  int *rest, *work, *token_unit;
+};
+
+size_t lwc_layout(int n, int m, int beta, int steps, char* base, LwcWorkspace& w) {
+  const IntShape s = w.s = slim_int_shape(n, m, beta, m);
+  w.plane = slim_int_plane(s);
+  w.blocks_x = s.npad / 16;
+  w.blocks_y = std::min(s.k, 8);
+  size_t off = 0;
+  auto take = [&](size_t bytes) {
+    char* p = base ? base + off : nullptr;
+    off += slim_ws_round(bytes);
+    return p;
+  };
+  auto doubles = [&](size_t count) { return reinterpret_cast<double*>(take(sizeof(double) * count)); };
+  w.Xd = take(std::max(slim_int_digits_bytes(s), sizeof(double) * (size_t)m * m));      // digits of G, or G in fp64
+  w.Wd = take((size_t)SI_MAXD * w.plane);
+  w.Q = take((size_t)w.plane);
+  w.SX = doubles((size_t)s.k * s.tpad);
+  w.WG = doubles((size_t)n * m);
+  w.DG = doubles((size_t)n * m);
+  w.lp = doubles((size_t)w.blocks_x * w.blocks_y);
+  w.loss = doubles((size_t)steps + 1);
+  for (double*& p : w.par) p = doubles((size_t)s.k * s.npad);
+  int* mi = reinterpret_cast<int*>(take(sizeof(int) * (2 * (size_t)s.C * s.TB + 6 * (size_t)s.C + (size_t)s.k + 4 + 3 * (size_t)m)));
+  w.mt.x = mi;
+  mi += 2 * (size_t)s.C * s.TB;
+  w.mt.w = mi;
+  w.mt.xmax = reinterpret_cast<unsigned*>(mi + 2 * s.C);
+  w.mt.xlsb = mi + 3 * s.C;
+  w.mt.wmax = reinterpret_cast<unsigned*>(mi + 4 * s.C);
+  w.mt.wlsb = mi + 5 * s.C;
+  w.rest = mi + 6 * s.C;
+  w.mt.unit = w.rest + s.k;
+  w.work = w.mt.unit + 4;
+  w.token_unit = w.work + 2 * m;
+  return off;
+}
+
+template <typename T>
+slim_status lwc_run(slim_ctx* ctx, const LwcWorkspace& w, const T* W, LwcArgs& a, OutArgs& oa, const slim_gemm_desc& wide,
+                    int steps, double beta1, double beta2) {
+  const dim3 grid(w.blocks_x, w.blocks_y), block(256);
+  SLIM_LAUNCH(ctx, "lwc_init", lwc_init<T>, grid, block, 0, W, a);
+  oa.Q = w.Wd;
+  oa.Y = w.WG;
+  oa.sub = nullptr;
+  slim_status st = SLIM_OK;
+  if (!a.D) st = slim_int_outputs(ctx, "lwc_wg_product", oa, true);
+  if (st != SLIM_OK) return st;
+  oa.Q = w.Q;
+  oa.Y = w.DG;
+  oa.sub = w.WG;
+  for (int it = 1; it <= steps + 1; ++it) {
+    oa.rest_from = it;
+    st = a.D ? slim_dgemm(ctx, "lwc_grad_dgemm", 0, wide) : slim_int_outputs(ctx, "lwc_grad_product", oa, false);
+    if (st != SLIM_OK) return st;
+    if (it <= steps) {
+      a.c1 = 1.0 - std::pow(beta1, (double)it);
+      a.c2 = 1.0 - std::pow(beta2, (double)it);
+      a.step = it + 1;
+      SLIM_LAUNCH(ctx, "lwc_step", (lwc_step<T, true>), grid, block, 0, W, a);
+    } else {
+      SLIM_LAUNCH(ctx, "lwc_loss", (lwc_step<T, false>), grid, block, 0, W, a);
+    }
+    st = slim_sum_f64(ctx, "lwc_loss_sum", w.lp, w.blocks_x * w.blocks_y, w.loss + (it - 1));
+    if (st != SLIM_OK) return st;
+  }
+  SLIM_LAUNCH(ctx, "lwc_final", lwc_final<T>, grid, block, 0, W, a);
+  return SLIM_OK;
 }
 
 }  // namespace
 
 size_t slim_ws_need_lwc(int n, int m, int beta, int steps) {
-  const size_t nk = (size_t)n * (m / beta);
-  return 3 * slim_ws_round(sizeof(double) * (size_t)n * m) + slim_ws_round(sizeof(double) * (size_t)m * m) +
-         7 * slim_ws_round(sizeof(double) * nk) + slim_ws_round(sizeof(double) * (size_t)(steps + 1));
+  LwcWorkspace w;
+  return lwc_layout(n, m, beta, steps, nullptr, w);
 }
 
 extern "C" slim_status slim_lwc_quantize(slim_ctx* ctx, const void* W, slim_dtype w_dtype, int n, int m, int64_t ldw,
@@ -219,58 +404,16 @@ extern "C" slim_status slim_lwc_quantize(slim_ctx* ctx, const void* W, slim_dtyp
 
   slim_status st = slim_ws_reserve(ctx, slim_ws_need_lwc(n, m, beta, steps));
   if (st != SLIM_OK) return st;
-  const size_t nk = (size_t)n * k;
-  double* W64 = static_cast<double*>(slim_ws_alloc(ctx, sizeof(double) * (size_t)n * m));
-  double* D = static_cast<double*>(slim_ws_alloc(ctx, sizeof(double) * (size_t)n * m));
-  double* DG = static_cast<double*>(slim_ws_alloc(ctx, sizeof(double) * (size_t)n * m));
-  double* G64 = static_cast<double*>(slim_ws_alloc(ctx, sizeof(double) * (size_t)m * m));
-  double* par[6];
-  for (double*& p : par) p = static_cast<double*>(slim_ws_alloc(ctx, sizeof(double) * nk));
-  double* lp = static_cast<double*>(slim_ws_alloc(ctx, sizeof(double) * nk));
-  double* loss = static_cast<double*>(slim_ws_alloc(ctx, sizeof(double) * (size_t)(steps + 1)));
-
-  st = slim_widen_f64(ctx, "lwc_widen_w", W, w_dtype, n, m, ldw, W64, (int64_t)m);
-  if (st != SLIM_OK) return st;
-  st = slim_widen_f64(ctx, "lwc_widen_g", G, SLIM_F32, m, m, ldg, G64, (int64_t)m);
-  if (st != SLIM_OK) return st;
-  const int fgrid = (int)std::min<size_t>((nk + 255) / 256, 65536);
-  SLIM_LAUNCH(ctx, "lwc_init", lwc_fill, dim3(fgrid), dim3(256), 0, par[0], (int64_t)nk, init);
-  SLIM_LAUNCH(ctx, "lwc_init", lwc_fill, dim3(fgrid), dim3(256), 0, par[1], (int64_t)nk, init);
-  for (int i = 2; i < 6; ++i) SLIM_LAUNCH(ctx, "lwc_init", lwc_fill, dim3(fgrid), dim3(256), 0, par[i], (int64_t)nk, 0.0);
-
-  LwcArgs a;
-  a.W = W64;
-  a.n = n;
-  a.m = m;
-  a.beta = beta;
-  a.bits = bits;
-  a.gamma = par[0];
-  a.betap = par[1];
-  a.m1g = par[2];
-  a.vg = par[3];
-  a.m1b = par[4];
-  a.vb = par[5];
-  a.D = D;
-  a.DG = DG;
-  a.lp = lp;
-  a.gscale = 2.0 / ((double)n * (double)n_tokens);
-  a.lr = lr;
-  a.b1 = beta1;
-  a.b2 = beta2;
-  a.eps = eps;
-  a.c1 = a.c2 = 1.0;
-  a.codes = codes;
-  a.scale = scale;
-  a.zero = zero;
-  a.What = What;
-  a.what_f64 = (what_dtype == SLIM_F64);
-  const dim3 grid(slim_cdiv((int64_t)nk, 4)), block(256);
+  LwcWorkspace w;
+  lwc_layout(n, m, beta, steps, ctx->ws, w);
+  bool wide = false;
+  for (int g = 0; g < k; ++g) wide = wide || bits_h[g] > 5;
   slim_gemm_desc d;
-  d.A = D;
+  d.A = w.WG;
   d.lda = m;
-  d.B = G64;
+  d.B = reinterpret_cast<const double*>(w.Xd);
   d.ldb = m;
-  d.C = DG;
+  d.C = w.DG;
   d.ldc = m;
   d.C2 = nullptr;
   d.ldc2 = 0;
@@ -280,24 +423,70 @@ extern "C" slim_status slim_lwc_quantize(slim_ctx* ctx, const void* W, slim_dtyp
   d.flags = 0;
   d.alpha = 1.0;
   d.beta = 0.0;
-  for (int it = 1; it <= steps + 1; ++it) {
-    SLIM_LAUNCH(ctx, "lwc_forward", lwc_forward_kernel<0>, grid, block, 0, a);
-    st = slim_dgemm(ctx, "lwc_grad_dgemm", 0, d);
-    if (st != SLIM_OK) return st;
-    if (it <= steps) {
-      a.c1 = 1.0 - std::pow(beta1, (double)it);
-      a.c2 = 1.0 - std::pow(beta2, (double)it);
-      SLIM_LAUNCH(ctx, "lwc_backward_adam", lwc_backward_adam, grid, block, 0, a);
-    } else {
-      SLIM_LAUNCH(ctx, "lwc_loss", lwc_loss_kernel, grid, block, 0, a);
-    }
-    st = slim_sum_f64(ctx, "lwc_loss_sum", lp, (int)nk, loss + (it - 1));
-    if (st != SLIM_OK) return st;
+  if (wide) {
+    st = slim_widen_f64(ctx, "lwc_widen_g", G, SLIM_F32, m, m, ldg, reinterpret_cast<double*>(w.Xd), (int64_t)m);
+  } else {
+    st = slim_int_clear(ctx, w.s, w.mt, w.rest, w.s.k);
+    if (st == SLIM_OK) st = slim_int_w_stats(ctx, w.s, w.mt, W, w_dtype, ldw);
+    if (st == SLIM_OK) st = slim_int_weight_meta(ctx, w.s, w.mt);
+    if (st == SLIM_OK) st = slim_int_g_digits(ctx, w.s, w.mt, G, ldg, w.work, w.token_unit, w.Xd, w.SX);
   }
-  SLIM_LAUNCH(ctx, "lwc_final", lwc_forward_kernel<1>, grid, block, 0, a);
+  if (st != SLIM_OK) return st;
+
+  LwcArgs a;
+  a.s = w.s;
+  a.mt = w.mt;
+  a.ldw = ldw;
+  a.bits = bits;
+  a.M = w.par[0];
+  a.mn = w.par[1];
+  a.gamma = w.par[2];
+  a.betap = w.par[3];
+  a.m1g = w.par[4];
+  a.vg = w.par[5];
+  a.m1b = w.par[6];
+  a.vb = w.par[7];
+  a.Q = w.Q;
+  a.S = w.par[8];
+  a.Rz = w.par[9];
+  a.rest = w.rest;
+  a.Wd = w.Wd;
+  a.D = wide ? w.WG : nullptr;
+  a.DG = w.DG;
+  a.lp = w.lp;
+  a.gscale = 2.0 / ((double)n * (double)n_tokens);
+  a.init = init;
+  a.lr = lr;
+  a.b1 = beta1;
+  a.b2 = beta2;
+  a.eps = eps;
+  a.c1 = a.c2 = 1.0;
+  a.step = 1;
+  a.codes = codes;
+  a.scale = scale;
+  a.zero = zero;
+  a.What = What;
+  a.what_f64 = (what_dtype == SLIM_F64);
+  OutArgs oa;
+  oa.s = w.s;
+  oa.mt = w.mt;
+  oa.mstride_c = w.s.TB;
+  oa.mstride_t = 1;
+  oa.Xd = w.Xd;
+  oa.SX = w.SX;
+  oa.plane = w.plane;
+  oa.S = a.S;
+  oa.Rz = a.Rz;
+  oa.rest = w.rest;
+  oa.rest_from = 1;
+  oa.token_unit = w.token_unit;
+  st = w_dtype == SLIM_F16    ? lwc_run(ctx, w, static_cast<const __half*>(W), a, oa, d, steps, beta1, beta2)
+       : w_dtype == SLIM_BF16 ? lwc_run(ctx, w, static_cast<const __hip_bfloat16*>(W), a, oa, d, steps, beta1, beta2)
+                              : lwc_run(ctx, w, static_cast<const float*>(W), a, oa, d, steps, beta1, beta2);
+  if (st != SLIM_OK) return st;
   if (!loss_curve) return SLIM_OK;                 // nothing for the host: the call does not wait
   double* host = reinterpret_cast<double*>(ctx->hpin);
-  SLIM_HIP_TRY(ctx, hipMemcpyAsync(host, loss, sizeof(double) * (size_t)(steps + 1), hipMemcpyDeviceToHost, ctx->stream));
+  SLIM_HIP_TRY(ctx, hipMemcpyAsync(host, w.loss, sizeof(double) * (size_t)(steps + 1), hipMemcpyDeviceToHost, ctx->stream));
   SLIM_HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
   const double norm = (double)n * (double)n_tokens;
   for (int i = 0; i <= steps; ++i) loss_curve[i] = host[i] / norm;

@@ -1,0 +1,47 @@
+"""The integer products of the learnable weight clipping where they can go wrong: padded and chunked group sizes, rows and
+columns around the tiles, columns of G that span many digits (outlier channels), eight-bit codes, zero points outside int8, and
+every type of W; against the float64 oracle."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import slim_oracle as orc
+from paper_2405_14917_amd import binding
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def slim():
+    s = binding.Slim("cuda:0")
+    yield s
+    s.close()
+
+
+@pytest.mark.parametrize("n,m,beta,dtype,outlier,widths", [
+    (5, 64, 32, torch.float16, 1.0, (1, 2)), (257, 300, 100, torch.float32, 300.0, (2, 3, 8)),
+    (70, 640, 160, torch.bfloat16, 50.0, (2, 4)), (33, 1024, 512, torch.float16, 1000.0, (8, 7)),
+    (128, 144, 36, torch.float32, 1.0, (1, 5))])
+def test_lwc_against_the_oracle(slim, n, m, beta, dtype, outlier, widths):
+    g = torch.Generator().manual_seed(n + m)
+    W = (torch.randn((n, m), generator=g) * 0.05).to(dtype)
+    W[1, :beta] = (W[1, :beta].abs() * 0.05 + 0.4).to(dtype)              # one sign: a zero point outside int8
+    W[2, :beta] = 0
+    X = torch.randn((m, 2 * m), generator=g, dtype=torch.float64)
+    X = X + 0.5 * X[torch.randperm(m, generator=g)]
+    X[3:7] *= outlier
+    G = (X @ X.t()).to(torch.float32)
+    k = m // beta
+    bits = np.array((list(widths) * k)[:k], dtype=np.uint8)
+    steps = 6
+    ref = orc.lwc_quantize(W.double().numpy(), G.double().numpy(), 2 * m, bits, beta, steps=steps)
+    out = slim.lwc_quantize(W.cuda(), G.cuda(), 2 * m, torch.from_numpy(bits).cuda(), beta, steps=steps, want_what=torch.float64)
+    # (the bounds of the other tests of this entry point)
+    assert np.allclose(out["loss_curve"], ref["loss_curve"], rtol=1e-9)
+    ok = ref["round_margin"].min(axis=1) > 1e-6
+    assert ok.mean() > 0.7
+    assert np.array_equal(out["codes"].cpu().numpy()[ok], ref["codes"][ok])
+    assert np.allclose(out["scale"].cpu().numpy(), ref["scale"], rtol=1e-9)
+    assert np.array_equal(out["zero"].cpu().numpy()[ok], ref["zero"][ok])
+    again = slim.lwc_quantize(W.cuda(), G.cuda(), 2 * m, torch.from_numpy(bits).cuda(), beta, steps=steps)
+    assert np.array_equal(again["loss_curve"], out["loss_curve"]) and torch.equal(again["codes"], out["codes"])
