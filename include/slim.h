@@ -291,7 +291,8 @@ slim_status slim_dequant_matmul(slim_ctx* ctx, const uint32_t* packed, int64_t l
 
 /* The same linear layer with the zero points in their packed form (App. B.2: the kernel dequantises the packed weights and
  * the packed zeros): zpacked, ldzp, zbits as slim_pack_zeros writes them; everything else as above.  The zero points are
- * unpacked into the context's workspace first (exact), so Y is bit for bit that of slim_dequant_matmul on them. */
+ * unpacked exactly (in the kernel, or for more than 64 tokens in the context's workspace), so Y is bit for bit that of
+ * slim_dequant_matmul on them. */
 slim_status slim_dequant_matmul_zp(slim_ctx* ctx, const uint32_t* packed, int64_t ldp, const uint32_t* gbits,
                                    const int32_t* row_off, const double* scale, const uint32_t* zpacked, int64_t ldzp,
                                    int zbits, int n, int m, int beta, int bit_base, const void* X, slim_dtype x_dtype,
@@ -331,7 +332,8 @@ slim_status slim_lwc_quantize(slim_ctx* ctx, const void* W, slim_dtype w_dtype, 
  * is off for its length).
  *   A layer needs (group ranges) x min(t_x, 16) x n floats, where the number of group ranges is chosen to fill the chip
  *   (about 8 x CUs / ceil(n / 128), at most k, one when that product is 1: then the buffer is not used).  If that
- *   exceeds the buffer the call returns SLIM_ERR_UNSUPPORTED and touches nothing; the error text gives the figures.
+ *   exceeds the buffer the call returns SLIM_ERR_UNSUPPORTED and touches nothing; the error text gives the figures.  (The limit
+ *   stands whichever kernel runs: up to 64 tokens are added inside one launch and leave the buffer alone.)
  *   All contexts on one GPU share that GPU's buffer: calls that overlap in time on one GPU (two streams) race.
  *   Nothing in it has to be zero before a call; every value read is written by the same call first.
  */

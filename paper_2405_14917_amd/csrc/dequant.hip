@@ -2,17 +2,13 @@
 // integers, the group-width array and the start rows that slim_pack writes, with the scales and zeros of
 // slim_gptq_quantize.  W^_ij = scale[i][g] (q_ij - zero[i][g]), g = j / beta (Eq. 1).
 //
-// For the few tokens of a decoding step the layer is a stream over the packed weights: 2 bits per weight on
-// average, read once.  A thread owns one output row i (one column of W_int, so that the 256 threads of a
-// workgroup read 1 KiB of consecutive words per step), walks a range of groups and dequantises a group's bit
-// stream 32 elements at a time; the group's activations sit in LDS and are read by all threads at once
-// (broadcast).  Several workgroups share a block of output rows by splitting the groups among them; their
-// partial sums are added in a fixed order by a second kernel, so the result does not depend on timing.
-//
-// The paper's kernel (an extension of AutoGPTQ's, for 32-wide warps) has the same division of labour - a thread
-// dequantises a contiguous segment of one column and dots it with activations shared in the block; what differs
-// is the mapping to 64-wide wavefronts, the LDS broadcast, and the deterministic two-stage reduction in place of
-// atomics.
+// Up to 64 tokens go to the kernel of dequant_few.hip, more to that of dequant_gemm.hip; both fetch the activations 16 bytes
+// at a time.  Here are the entry points and the form for activations that are not aligned for that: a thread owns one
+// output row i (one column of W_int, so that the 256 threads of a workgroup read 1 KiB of consecutive words per step),
+// walks a range of groups and dequantises a group's bit stream 32 elements at a time; the group's activations sit in LDS
+// and are read by all threads at once (broadcast).  Several workgroups share a block of output rows by splitting the
+// groups among them; their partial sums are added in a fixed order by a second kernel, so the result does not depend
+// on timing.
 #include <algorithm>
 
 #include <mutex>
@@ -28,6 +24,8 @@ using namespace slimdq;
 
 constexpr int DQ_THREADS = 256;
 constexpr int DQ_MAX_T = 16;
+// rows per workgroup and padding of an activation row that the limit of the fixed buffer is stated with (dq_splits)
+constexpr int DM_ROWS = 128, DM_PAD = 8;
 
 __device__ __forceinline__ float widen16(uint16_t h, int bf16) {
   if (bf16) return __uint_as_float((unsigned)h << 16);
@@ -138,205 +136,6 @@ __global__ __launch_bounds__(256) void dequant_reduce(const float* __restrict__ 
   Y[(int64_t)t * ldy + i] = s;
 }
 
-// ------------------------------------------------------------------------------------------------------
-// The same product on the matrix cores, for fp16 activations.  v_mfma_f32_32x32x16_f16 with the tokens as rows
-// of the first operand and the output rows of the layer as columns of the second: a lane then owns ONE output
-// row (its scale and zero are lane constants) and the 16 tokens of its accumulator registers.  The second
-// operand is 2 (q - z), formed exactly in fp16 from the packed codes without any conversion instruction: a code
-// q shifted left by one and OR-ed into the mantissa of 1024.0 is the fp16 number 1024 + 2 q, and subtracting
-// 1024 + 2 z (2 z is an integer: zeros are integers, or 1/2 for the sign form of width 1; other zeros: see below) leaves 2 (q - z);
-// the factor 1/2 goes into the scale.  Two codes are handled per instruction (packed fp16): the eight codes a
-// lane needs for one MFMA are first spread so that code j sits in the low and code j + 4 in the high half of a
-// register, and the activations are stored in LDS in that order (0 4 1 5 2 6 3 7) to match.  Products are exact
-// (11-bit by 6-bit), the sums are fp32 in the matrix core, the scale is applied per group in fp32.
-// With up to 32 tokens served by the same instructions, the kernel is a stream over the packed weights.
-constexpr int DM_WAVES = 4, DM_ROWS = 32 * DM_WAVES, DM_TOK = 32, DM_PAD = 8;
-
-// the 8 B-bit codes in the low bits of v -> four registers of packed fp16 pairs (1024 + 2 c_j, 1024 + 2 c_{j+4})
-template <int B>
-__device__ __forceinline__ void spread_codes(unsigned v, unsigned (&t)[4]) {
-  constexpr unsigned M2 = ((1u << B) - 1u) << 1;
-  const unsigned u = (B == 4) ? v : ((v & ((1u << (4 * B)) - 1u)) | ((v >> (4 * B)) << 16));
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const unsigned sh = (B * j >= 1) ? (u >> (B * j - 1)) : (u << 1);
-    t[j] = (sh & (M2 | (M2 << 16))) | 0x64006400u;
-  }
-}
-
-// the same for codes wider than 4 bits: the 8 codes take 8 B > 32 bits
-template <int B>
-__device__ __forceinline__ void spread_codes_wide(uint64_t v, unsigned (&t)[4]) {
-  constexpr unsigned M = (1u << B) - 1u;
-#pragma unroll
-  for (int j = 0; j < 4; ++j)
-    t[j] = (((unsigned)(v >> (B * j)) & M) << 1) | (((unsigned)(v >> (B * (j + 4))) & M) << 17) | 0x64006400u;
-}
-
-// One sub-block of SUB codes (SUB / 16 MFMA steps) of one group: `w` holds the SUB * B / 32 words of the lane's
-// output row; xs points at the lane's token row of the activation tile, at this sub-block's first column.
-template <int B, int SUB, int MAXW>
-__device__ __forceinline__ float16v subblock_mfma(const unsigned (&w)[MAXW], int h, half2v zz, const _Float16* xs,
-                                                  float16v acc) {
-  constexpr int NW = SUB * B / 32;
-  static_assert(NW <= MAXW, "the sub-block's words do not fit the register array");
-#pragma unroll
-  for (int st = 0; st < SUB / 16; ++st) {
-    unsigned t[4];
-    if constexpr (B > 4) {
-      // 8 codes = 8 B bits (at most 64) starting at bit 8 B (2 st + h): always within two consecutive words for
-      // B = 5 (the start is a multiple of 8, so at most 24 + 40 bits)
-      static_assert(B == 5, "wider codes would span three words");
-      auto unit_wide = [&](int unit) -> uint64_t {
-        const int bit = 8 * B * unit, wi = bit / 32, sh = bit % 32;
-        const uint64_t two = (uint64_t)w[wi] | ((uint64_t)w[(wi + 1 < NW) ? wi + 1 : wi] << 32);
-        return two >> sh;
-      };
-      const uint64_t v0 = unit_wide(2 * st), v1 = unit_wide(2 * st + 1);
-      spread_codes_wide<B>(h ? v1 : v0, t);
-    } else {
-    // unit 2 st + h of the stream: 8 codes = 8 B bits starting at bit 8 B (2 st + h)
-    auto unit_bits = [&](int unit) -> unsigned {
-      const int bit = 8 * B * unit, wi = bit / 32, sh = bit % 32;
-      if (sh + 8 * B <= 32) return w[wi] >> sh;
-      const uint64_t two = (uint64_t)w[wi] | ((uint64_t)w[(wi + 1 < NW) ? wi + 1 : wi] << 32);
-      return (unsigned)(two >> sh);
-    };
-    const unsigned v0 = unit_bits(2 * st), v1 = unit_bits(2 * st + 1);   // the unit for h = 0 and for h = 1
-    spread_codes<B>(h ? v1 : v0, t);
-    }
-    half8v bfrag;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const half2v d = *reinterpret_cast<const half2v*>(&t[j]) - zz;
-      bfrag[2 * j] = d[0];
-      bfrag[2 * j + 1] = d[1];
-    }
-    const half8v afrag = *reinterpret_cast<const half8v*>(xs + 16 * st + 8 * h);
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(afrag, bfrag, acc, 0, 0, 0);
-  }
-  return acc;
-}
-
-// SUB = min(beta, 128): a group is worked off in beta / SUB sub-blocks.  The activations of the workgroup's whole
-// group range are put into LDS once (rows of the real tokens plus one row of zeros that the lanes of the other
-// token slots read); the words, scale and zero of the next sub-block are fetched while the current one is
-// multiplied, so that a workgroup waits for memory once, not once per group.
-// MAXW: words of a sub-block at the widest width in the layer (16 for widths up to 4, 20 with five-bit groups).
-template <int SUB, int MAXW>
-__global__ __launch_bounds__(64 * DM_WAVES) void dequant_matmul_mfma(DqArgs a) {
-  extern __shared__ __align__(16) _Float16 xh[];   // [t_x + 1][cols + DM_PAD], every 8 columns in the order 0 4 1 5 2 6 3 7
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int l32 = lane & 31, h = lane >> 5;
-  const int row = min(blockIdx.x * DM_ROWS + wave * 32 + l32, a.n - 1);    // clamped: rows past the end are not stored
-  const int g0 = blockIdx.y * a.gper, g1 = min(a.k, g0 + a.gper);
-  const int cols = (g1 - g0) * a.beta, ldxs = cols + DM_PAD;
-  const uint16_t* X = static_cast<const uint16_t*>(a.X);
-  for (int idx = tid; idx < (a.t_x + 1) * (cols / 8); idx += 64 * DM_WAVES) {
-    const int t = idx / (cols / 8), c = idx - t * (cols / 8);
-    uint4 raw = make_uint4(0u, 0u, 0u, 0u);
-    if (t < a.t_x) raw = *reinterpret_cast<const uint4*>(X + (int64_t)t * a.ldx + (int64_t)g0 * a.beta + 8 * c);
-    // halves 0..7 of the chunk are (raw.x lo, hi), (raw.y lo, hi), ...; stored as 0 4 1 5 2 6 3 7
-    uint4 o;
-    o.x = (raw.x & 0xffffu) | (raw.z << 16);
-    o.y = (raw.x >> 16) | (raw.z & 0xffff0000u);
-    o.z = (raw.y & 0xffffu) | (raw.w << 16);
-    o.w = (raw.y >> 16) | (raw.w & 0xffff0000u);
-    *reinterpret_cast<uint4*>(xh + t * ldxs + 8 * c) = o;
-  }
-  const _Float16* xs = xh + min(l32, a.t_x) * ldxs;
-  // The scales (halved: the codes are doubled) and the zeros (as 1024 + 2 z in fp16) of the workgroup's rows and
-  // groups, fetched together: per (row, group) loads by the lane that owns the row would touch 32 cache lines per
-  // instruction, eight times the requests of the packed words themselves.
-  const int gcount = g1 - g0;
-  // A zero outside that form (Eq. 1 puts no bound on -round(w_min / delta0): a group of one sign with a narrow
-  // range has a large one) is split: z0, the nearest value that has the form, goes through the matrix cores, and
-  // the rest enters as  - 2 (z - z0) sum_j x_j  when the group is complete (zr != 0, rare).
-  float* sp = reinterpret_cast<float*>(xh + (a.t_x + 1) * ldxs);            // [DM_ROWS][gcount]
-  float* zr = sp + DM_ROWS * gcount;                                          // [DM_ROWS][gcount]
-  _Float16* zp = reinterpret_cast<_Float16*>(zr + DM_ROWS * gcount);          // [DM_ROWS][gcount]
-  for (int idx = tid; idx < DM_ROWS * gcount; idx += 64 * DM_WAVES) {
-    const int r = idx / gcount, gi = idx - r * gcount;
-    const int64_t src = (int64_t)min(blockIdx.x * DM_ROWS + r, a.n - 1) * a.k + g0 + gi;
-    sp[idx] = (float)(0.5 * a.scale[src]);
-    const double z2 = 2.0 * a.zero[src];
-    const double z02 = fmin(fmax(rint(z2), -1022.0), 1022.0);
-    zp[idx] = (_Float16)(float)(1024.0 + z02);                                // exact: an integer in 2 .. 2046
-    zr[idx] = (float)(z2 - z02);
-  }
-  const int prow = (wave * 32 + l32) * gcount;
-
-  const int nsub = a.beta / SUB, units = (g1 - g0) * nsub;
-  // fetch of unit u: the words of the lane's row
-  auto fetch = [&](int u, unsigned (&w)[MAXW]) {
-    const int g = g0 + u / nsub, sb = u - (u / nsub) * nsub;
-    const int nwu = SUB * checked_width(a, g) / 32;
-    const uint32_t* p = a.packed + (int64_t)(a.row_off[g] + sb * nwu) * a.ldp + row;
-#pragma unroll
-    for (int i = 0; i < MAXW; ++i) w[i] = (i < nwu) ? p[(int64_t)i * a.ldp] : 0u;
-  };
-  unsigned wc[MAXW], wn[MAXW];
-  fetch(0, wc);
-  __syncthreads();                                 // the activation tile and the parameters are complete
-
-  float y[16];
-#pragma unroll
-  for (int v = 0; v < 16; ++v) y[v] = 0.f;
-  float16v acc;
-#pragma unroll
-  for (int v = 0; v < 16; ++v) acc[v] = 0.f;
-  for (int u = 0; u < units; ++u) {
-    const int g = g0 + u / nsub, sb = u - (u / nsub) * nsub;
-    if (u + 1 < units) fetch(u + 1, wn);
-    const _Float16 zc = zp[prow + (g - g0)];
-    half2v zz;
-    zz[0] = zc;
-    zz[1] = zc;
-    const _Float16* xu = xs + (g - g0) * a.beta + sb * SUB;
-    switch (checked_width(a, g)) {                    // the same for the whole workgroup
-      case 0: break;
-      case 1: acc = subblock_mfma<1, SUB, MAXW>(wc, h, zz, xu, acc); break;
-      case 2: acc = subblock_mfma<2, SUB, MAXW>(wc, h, zz, xu, acc); break;
-      case 3: acc = subblock_mfma<3, SUB, MAXW>(wc, h, zz, xu, acc); break;
-      case 4: acc = subblock_mfma<4, SUB, MAXW>(wc, h, zz, xu, acc); break;
-      default:
-        if constexpr (MAXW >= 20) acc = subblock_mfma<5, SUB, MAXW>(wc, h, zz, xu, acc);
-        break;
-    }
-    if (sb == nsub - 1) {                          // the group is complete: its scale (times the 1/2 of the doubled codes)
-      const float rest = zr[prow + (g - g0)];
-      if (__builtin_amdgcn_ballot_w64(rest != 0.f) != 0 && checked_width(a, g) != 0) {
-        // some row of this wavefront has a zero that the fp16 form does not hold: the part it does not hold times
-        // the sum of the group's activations, per token (the order of the tile's columns does not matter for a sum)
-#pragma unroll 1
-        for (int v = 0; v < 16; ++v) {
-          const int t = 8 * (v >> 2) + 4 * h + (v & 3);
-          const _Float16* xt = xh + min(t, a.t_x) * ldxs + (g - g0) * a.beta;
-          float sx = 0.f;
-          for (int j = 0; j < a.beta; ++j) sx += (float)xt[j];
-          acc[v] = fmaf(-rest, sx, acc[v]);
-        }
-      }
-      const float s2 = sp[prow + (g - g0)];
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        y[v] = fmaf(s2, acc[v], y[v]);
-        acc[v] = 0.f;
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < MAXW; ++i) wc[i] = wn[i];
-  }
-  if (blockIdx.x * DM_ROWS + wave * 32 + l32 < a.n) {
-    float* o = a.out + (int64_t)blockIdx.y * a.split_stride + row;
-#pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const int t = 8 * (v >> 2) + 4 * h + (v & 3);   // accumulator register v of lane (l32, h): token t, output row l32
-      if (t < a.t_x) o[(int64_t)t * a.ldo] = y[v];
-    }
-  }
-}
-
 template <int T>
 slim_status launch(slim_ctx* ctx, const DqArgs& a, dim3 grid, size_t smem) {
   SLIM_LAUNCH(ctx, "dequant_matmul@dequant_matmul<T>", dequant_matmul<T>, grid, dim3(DQ_THREADS), smem, a);
@@ -353,9 +152,9 @@ constexpr int DQ_MAX_DEVICES = 64;
 std::mutex g_scratch_mu;
 float* g_scratch_ptr[DQ_MAX_DEVICES] = {};
 
-// Group ranges the layer is split into (and groups per range), for the matrix-core kernel or the plain one:
-// enough workgroups per CU to hide the latency of their loads behind one another; fewer for a small layer, where
-// the reduction over the ranges would cost more than the ranges gain.
+// Group ranges the layer is split into (and groups per range): enough workgroups per CU to hide the latency of their loads
+// behind one another; fewer for a small layer, where the reduction over the ranges would cost more than the ranges gain.
+// mfma: the ranges in which the limit of the fixed buffer is stated for fp16 activations.
 int dq_splits(int n, int m, int beta, int t_x, int cus, bool mfma, int& gper) {
   const int k = m / beta;
   const bool small = 2 * slim_cdiv(n, DM_ROWS) < cus;
@@ -364,8 +163,7 @@ int dq_splits(int n, int m, int beta, int t_x, int cus, bool mfma, int& gper) {
   const int splits_wanted = std::max(1, std::min(k, (per_cu * cus + gx - 1) / gx));
   gper = slim_cdiv(k, splits_wanted);
   if (mfma) {
-    // the activations of a workgroup's group range (t_x + 1 rows of 16-bit values) and its rows' parameters
-    // (10 bytes per row and group) have to fit into 64 KiB of LDS
+    // t_x + 1 rows of a range's activations and 10 bytes per row and group in 64 KiB
     const int fit = std::max(1, (int)((64 * 1024 - 2 * (t_x + 1) * DM_PAD) / (2 * (t_x + 1) * beta + 10 * DM_ROWS)));
     gper = std::min(gper, fit);
   }
@@ -373,8 +171,9 @@ int dq_splits(int n, int m, int beta, int t_x, int cus, bool mfma, int& gper) {
 }
 
 // What both forms of the call are refused for; nothing has been launched then.
-slim_status dq_check(slim_ctx* ctx, const char* fn, const DqArgs& a, slim_dtype x_dtype, int64_t t_x, int64_t ldy) {
-  SLIM_REQUIRE(ctx, a.packed && a.gbits && a.row_off && a.scale && a.zero && a.X && a.out, "%s: null pointer", fn);
+slim_status dq_check(slim_ctx* ctx, const char* fn, const DqArgs& a, slim_dtype x_dtype, int64_t t_x, int64_t ldy,
+                     bool packed_zeros) {
+  SLIM_REQUIRE(ctx, a.packed && a.gbits && a.row_off && a.scale && (a.zero || packed_zeros) && a.X && a.out, "%s: null pointer", fn);
   SLIM_REQUIRE(ctx, a.n > 0 && a.m > 0 && a.beta > 0 && a.m % a.beta == 0, "%s: need n, m > 0 and beta | m", fn);
   SLIM_REQUIRE(ctx, a.beta % 32 == 0, "%s: beta must be a multiple of 32 (got %d)", fn, a.beta);
   SLIM_REQUIRE(ctx, t_x >= 1, "%s: t_x must be at least 1 (got %lld)", fn, (long long)t_x);
@@ -415,40 +214,16 @@ slim_status dq_reduce(slim_ctx* ctx, const DqArgs& a, int splits, float* Y, int6
   return SLIM_OK;
 }
 
-// Up to DQ_MAX_T tokens (arguments checked).
+// Up to DQ_MAX_T tokens whose activations the matrix-core kernels cannot fetch (arguments checked).
 slim_status dequant_matmul_run(slim_ctx* ctx, const char* fn, DqArgs a, int64_t ldy, float* fixed, size_t fixed_floats) {
   float* const Y = a.out;
-  const int n = a.n, m = a.m, beta = a.beta, t_x = a.t_x;
   int T = 1;
-  while (T < t_x) T *= 2;
-  // fp16 activations that can be fetched 16 bytes at a time go to the matrix-core kernel
-  // (a layer too small to give every CU a few workgroups of that kernel is bound by launch and reduction, and
-  // for one or two tokens the plain kernel, whose workgroups cover twice the rows, is the quicker one there)
-  const int cus = std::max(1, ctx->num_cus);
-  const bool small = 2 * slim_cdiv(n, DM_ROWS) < cus;
-  const bool mfma = !a.x_bf16 && slim_aligned16(a.X) && a.ldx % 8 == 0 &&
-                    (beta == 32 || beta == 64 || beta % 128 == 0) && !(small && t_x <= 2);
-  size_t smem = sizeof(float) * (size_t)T * beta;   // (the matrix-core kernel's depends on the split, below)
-  const int gx = slim_cdiv(n, mfma ? DM_ROWS : DQ_THREADS);
-  const int splits = dq_splits(n, m, beta, t_x, cus, mfma, a.gper);
+  while (T < a.t_x) T *= 2;
+  const size_t smem = sizeof(float) * (size_t)T * a.beta;
+  const int splits = dq_splits(a.n, a.m, a.beta, a.t_x, std::max(1, ctx->num_cus), false, a.gper);
   slim_status st = dq_partials(ctx, fn, a, splits, fixed, fixed_floats);
   if (st != SLIM_OK) return st;
-  const dim3 grid(gx, splits);
-  if (mfma) {
-    smem = sizeof(uint16_t) * (size_t)(t_x + 1) * ((size_t)a.gper * beta + DM_PAD) + (size_t)DM_ROWS * a.gper * 10;
-#define SLIM_DQ_MFMA(SUB, MAXW)                                                                              \
-  SLIM_LAUNCH(ctx, "dequant_matmul@dequant_matmul_mfma<" #SUB ", " #MAXW ">", (dequant_matmul_mfma<SUB, MAXW>), grid, \
-              dim3(64 * DM_WAVES), smem, a)
-    const bool wide = a.bit_base + 3 > 4;          // the layer may hold five-bit groups
-    if (beta >= 128) {
-      if (wide) SLIM_DQ_MFMA(128, 20); else SLIM_DQ_MFMA(128, 16);
-    } else if (beta == 64) {
-      if (wide) SLIM_DQ_MFMA(64, 20); else SLIM_DQ_MFMA(64, 16);
-    } else {
-      if (wide) SLIM_DQ_MFMA(32, 20); else SLIM_DQ_MFMA(32, 16);
-    }
-#undef SLIM_DQ_MFMA
-  } else
+  const dim3 grid(slim_cdiv(a.n, DQ_THREADS), splits);
   switch (T) {
     case 1: st = launch<1>(ctx, a, grid, smem); break;
     case 2: st = launch<2>(ctx, a, grid, smem); break;
@@ -460,13 +235,26 @@ slim_status dequant_matmul_run(slim_ctx* ctx, const char* fn, DqArgs a, int64_t 
   return dq_reduce(ctx, a, splits, Y, ldy);
 }
 
-// Any number of tokens: more than 64 in one launch of the kernel for many tokens, fewer DQ_MAX_T at a time, one after
-// the other on the context's stream.  Nothing is launched if the call is refused.
+// The limit of the fixed buffer is stated for the partial sums of slices of DQ_MAX_T tokens, whichever kernel runs: a layer
+// is taken or refused by its sizes, not by the kernel that a release picks.
+slim_status dq_fixed_limit(slim_ctx* ctx, const char* fn, DqArgs a, int64_t t_x, float* fixed, size_t fixed_floats) {
+  if (!fixed) return SLIM_OK;
+  const int cus = std::max(1, ctx->num_cus);
+  a.t_x = (int)std::min<int64_t>(t_x, DQ_MAX_T);
+  const bool small = 2 * slim_cdiv(a.n, DM_ROWS) < cus;
+  const bool mfma = !a.x_bf16 && (a.beta == 32 || a.beta == 64 || a.beta % 128 == 0) && !(small && a.t_x <= 2);
+  const int splits = dq_splits(a.n, a.m, a.beta, a.t_x, cus, mfma, a.gper);
+  return dq_partials(ctx, fn, a, splits, fixed, fixed_floats);
+}
+
+// Any number of tokens: up to 64 in one launch of the kernel for few tokens, more in one of the kernel for many; activations
+// that are not aligned to 16 bytes DQ_MAX_T tokens at a time, one after the other on the context's stream.  `zp` (zero points
+// in their packed form) only where slim_dq_few_takes.  Nothing is launched if the call is refused.
 slim_status dequant_matmul_tokens(slim_ctx* ctx, const char* fn, const uint32_t* packed, int64_t ldp,
                                   const uint32_t* gbits, const int32_t* row_off, const double* scale,
                                   const double* zero, int n, int m, int beta, int bit_base, const void* X,
                                   slim_dtype x_dtype, int64_t t_x, int64_t ldx, float* Y, int64_t ldy, float* fixed,
-                                  size_t fixed_floats) {
+                                  size_t fixed_floats, const PackedZeros* zp = nullptr) {
   DqArgs a;
   a.packed = packed;
   a.ldp = ldp;
@@ -484,20 +272,20 @@ slim_status dequant_matmul_tokens(slim_ctx* ctx, const char* fn, const uint32_t*
   a.out = Y;
   a.ldo = ldy;
   a.split_stride = 0;
-  slim_status st = dq_check(ctx, fn, a, x_dtype, t_x, ldy);
+  slim_status st = dq_check(ctx, fn, a, x_dtype, t_x, ldy, zp != nullptr);
   if (st != SLIM_OK) return st;
   a.k = m / beta;
   a.gper = a.k;
+  if (slim_dq_few_takes(t_x, ldp, beta, X, ldx)) {
+    st = dq_fixed_limit(ctx, fn, a, t_x, fixed, fixed_floats);
+    if (st != SLIM_OK) return st;
+    a.t_x = (int)t_x;
+    return slim_dq_few_launch(ctx, a, zp);
+  }
   const int cus = std::max(1, ctx->num_cus);
   if (slim_dq_gemm_takes(t_x, m, beta, X, ldx)) {
-    if (fixed) {
-      // the limit of the fixed buffer is stated for slices of DQ_MAX_T tokens, whichever kernel runs
-      a.t_x = DQ_MAX_T;
-      DqArgs b = a;
-      const bool mfma = !a.x_bf16 && (beta == 32 || beta == 64 || beta % 128 == 0);
-      st = dq_partials(ctx, fn, b, dq_splits(n, m, beta, DQ_MAX_T, cus, mfma, b.gper), fixed, fixed_floats);
-      if (st != SLIM_OK) return st;
-    }
+    st = dq_fixed_limit(ctx, fn, a, t_x, fixed, fixed_floats);
+    if (st != SLIM_OK) return st;
     a.t_x = (int)t_x;
     const int splits = slim_dq_gemm_splits(n, m, beta, t_x, cus, a.gper);
     st = dq_partials(ctx, fn, a, splits, fixed, fixed_floats);
@@ -580,9 +368,9 @@ extern "C" slim_status slim_dequant_matmul_noalloc(slim_ctx* ctx, const uint32_t
 }
 
 // The same layer with the zero points in their packed form (App. B.2: weights AND zeros are stored as packed integers
-// and the kernel dequantises both): the zero points are unpacked into the context's workspace (n x k doubles, exact:
-// stored value / 2) and the product runs as above, so the result is bit for bit that of slim_dequant_matmul on the
-// unpacked zero points.
+// and the kernel dequantises both).  The kernel for up to 64 tokens takes them apart itself; for the others they are unpacked
+// into the context's workspace (n x k doubles, exact: stored value / 2).  The result is bit for bit that of
+// slim_dequant_matmul on the unpacked zero points.
 extern "C" slim_status slim_dequant_matmul_zp(slim_ctx* ctx, const uint32_t* packed, int64_t ldp, const uint32_t* gbits,
                                               const int32_t* row_off, const double* scale, const uint32_t* zpacked,
                                               int64_t ldzp, int zbits, int n, int m, int beta, int bit_base,
@@ -593,6 +381,13 @@ extern "C" slim_status slim_dequant_matmul_zp(slim_ctx* ctx, const uint32_t* pac
   SLIM_REQUIRE(ctx, n > 0 && m > 0 && beta > 0 && m % beta == 0, "slim_dequant_matmul_zp: need n, m > 0 and beta | m");
   SLIM_REQUIRE(ctx, t_x >= 1, "slim_dequant_matmul_zp: t_x must be at least 1");
   const int k = m / beta;
+  if (slim_dq_few_takes(t_x, ldp, beta, X, ldx)) {
+    SLIM_REQUIRE(ctx, zbits >= 2 && zbits <= 16, "slim_dequant_matmul_zp: zbits must be in 2..16 (got %d)", zbits);
+    SLIM_REQUIRE(ctx, ldzp >= slim_cdiv((int64_t)n * zbits, 32), "slim_dequant_matmul_zp: ldzp too small");
+    const PackedZeros z{zpacked, ldzp, zbits};
+    return dequant_matmul_tokens(ctx, "slim_dequant_matmul_zp", packed, ldp, gbits, row_off, scale, nullptr, n, m, beta,
+                                 bit_base, X, x_dtype, t_x, ldx, Y, ldy, nullptr, 0, &z);
+  }
   const size_t need_dq = slim_ws_need_dequant(n, m, beta, t_x, std::max(1, ctx->num_cus));
   const size_t need_z = slim_ws_round(sizeof(double) * (size_t)n * k);
   slim_status st = slim_ws_reserve(ctx, need_dq + need_z);

@@ -40,7 +40,18 @@ __device__ __forceinline__ int checked_width(const DqArgs& a, int g) {
   return ((a.row_off[g + 1] - a.row_off[g]) * 32 == a.beta * b) ? b : 0;
 }
 
+// Zero points in the packed form of slim_pack_zeros: 2 z of row i of group g in zbits bits from bit i zbits on of row g.
+struct PackedZeros {
+  const uint32_t* words;
+  int64_t ld;
+  int bits;
+};
+
 }  // namespace slimdq
+
+// The linear layer for up to 64 tokens (dequant_few.hip), with the zero points as doubles (a.zero) or packed (zp).
+bool slim_dq_few_takes(int64_t t_x, int64_t ldp, int beta, const void* X, int64_t ldx);
+slim_status slim_dq_few_launch(slim_ctx* ctx, const slimdq::DqArgs& a, const slimdq::PackedZeros* zp);
 
 // The linear layer for many tokens (dequant_gemm.hip).  `dq_gemm_takes` tells whether it is built for the call;
 // dq_gemm_splits gives the group ranges the layer is cut into (and groups per range in `gper`).

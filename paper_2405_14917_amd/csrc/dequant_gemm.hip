@@ -17,8 +17,7 @@
 //
 // What bounds it: issue (147 vector instructions per wavefront and slab, 16 of them MFMAs, beside 90 scalar ones) and the
 // barrier per slab; the matrix cores are busy 37 % of the time.  4096 x 11008 at 2 bits, 2048 tokens: 212 us (870 TFLOP/s)
-// against 2848 us for 128 slices of 16 tokens through the kernels for few tokens, each of which reads and decodes the
-// whole layer; 65 tokens 31 us against 88 us for 64 in four slices.
+// against 2848 us for 128 slices of 16 tokens, each of which reads and decodes the whole layer.
 #include <algorithm>
 
 #include "dequant_device.h"
@@ -390,6 +389,8 @@ int token_tile(int n, int64_t t_x, int cus) {
 
 }  // namespace
 
+// From 65 tokens on.  (From 33 it is the faster one on a layer of few rows, 28 against 47 us on 4096 x 11008, but there a token's
+// outputs are promised to be the same bytes whichever other tokens share its call, and its sums run in another order.)
 bool slim_dq_gemm_takes(int64_t t_x, int m, int beta, const void* X, int64_t ldx) {
   return t_x > 64 && t_x < (1 << 30) && slim_aligned16(X) && ldx % 8 == 0 && ldx < (1 << 23) && m % beta == 0 && beta % 32 == 0;
 }
