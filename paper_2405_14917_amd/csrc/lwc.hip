@@ -8,7 +8,7 @@
 // squared error of the layer's outputs over the T calibration tokens (Eq. 3), taken full batch: it depends on X only
 // through G = X X^T, so one step sees all tokens.  The backward pass takes the rounding as the identity and lets the
 // clamp pass derivatives where it does not clip:
-//     g = dL/dW_hat = 2 (W_hat - W) G / (n T)                                (fp64 matrix cores)
+//     g = dL/dW_hat = 2 (W_hat - W) G / (n T)
 //     dW_hat_j / d delta = (q_j - z) - w_j / delta   or, clipped,   (q_j - z) - lo / delta
 //     dW_hat_j / d lo at fixed delta = 0   or, clipped,   1
 // Everything is fp64.  D G = W_hat G - W G with W_hat = delta (q - z): the first product is one of small integers with G's

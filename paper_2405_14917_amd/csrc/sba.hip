@@ -3,7 +3,7 @@
 // The search evaluates floor(k/2)+1 allocations that differ from one another in two groups only, so the layer outputs are
 // carried incrementally.  Every product with the objective's tokens is EXACT integer arithmetic on the int8 matrix cores:
 //   * X_s is one integer matrix times a power of two (fp16 values are multiples of 2^-24 below 2^16), cut into signed base-256
-//     digits (balanced: -128 .. 127); of every chunk of channels only the digits in use are kept (`sba_meta`), three to five
+//     digits (balanced: -128 .. 127); of every chunk of channels only the digits in use are kept (`int_meta`), three to five
 //     for activations;
 //   * a fake-quantised weight is scale * (q - z) with a small integer q - z: one int8 matrix, and one scale per (row, group);
 //   * W itself is cut into digits the same way (two to four for 16-bit weights).
@@ -14,10 +14,10 @@
 //
 //   sba_rank        stable ascending rank of the k group saliences (one workgroup, counting sort by comparison; NaN
 //                   ranks last) -> order[]
-//   sba_*_stats, sba_meta, sba_x_digits     which digits there are, and the digits of X_s in MFMA operand order
+//   int_*_stats, int_meta, int_x_digits     which digits there are, and the digits of X_s in MFMA operand order
 //   sba_codes       per (row, group): Eq. 1 / Eq. 2 at width N and at the one other width the group can take, as integers
 //                   in operand order with their scales; the digits of W
-//   sba_outputs     Y^T = W X_s and Y_0^T = W_N X_s (n x t_s, fp64)
+//   int_outputs     Y^T = W X_s and Y_0^T = W_N X_s (n x t_s, fp64)
 //   kl_ref_*        once: per token the maximum M_t and log-sum-exp of the reference outputs; Y is then overwritten
 //                   by P = softmax(Y) and B_t = sum_i P_i log P_i is kept
 //   sba_search      all candidates in one kernel: obj[p] = sum_t [ B_t - (sum_i P_i q_i - lse(q)) ] with the reference
