@@ -7,12 +7,11 @@
 //  * Workgroup tile 256 x 256, 256 threads = 4 wavefronts in 2 x 2, each owning 128 x 128 as 4 x 4 MFMA
 //    tiles of 32 x 32 (256 fp32 accumulators per lane).  Per K step of 16 a wavefront reads 8 operand
 //    fragments from LDS for 16 MFMAs, which keeps LDS at about half of its bandwidth.
-//  * K advances in slabs of 64 tokens (128 bytes per row = one cache line).  General kernel (partial tiles,
-//    ragged token counts): two LDS stages, the next slab fetched into registers while the current one is
-//    multiplied, rows padded to 72 halves so that the 16-byte operand reads of consecutive rows fall into
-//    different banks.  Fast path (whole tiles, whole slabs; every benchmark shape): slabs go from memory to LDS
-//    directly, swizzled, into a ring of five 32 KiB units that keeps two and a half slabs on the chip
-//    (gram_kernel_ring).
+//  * K advances in slabs of 64 tokens (128 bytes per row = one cache line).  Slabs go from memory to LDS directly,
+//    swizzled, into a ring of five 32 KiB units that keeps two and a half slabs on the chip (gram_kernel_ring), for any
+//    number of rows and tokens.  Rows more than 2^32 bytes / 255 apart are left to gram_kernel: two LDS stages, the next slab
+//    fetched into registers while the current one is multiplied, rows padded to 72 halves so that the 16-byte operand
+//    reads of consecutive rows fall into different banks.
 //  * Split-K: every tile is cut into S token ranges.  Workgroup ids run over the tiles fastest, so the chip works
 //    on one or two token ranges at a time and all XCDs stream through the same narrow band of X together; which
 //    tiles are on the chip together, and on which XCD, is decode_work's business.
@@ -182,11 +181,6 @@ __device__ __forceinline__ uint4 load_chunk(const uint16_t* rowp, int64_t k, int
   return *reinterpret_cast<const uint4*>(rowp + min(k, klast8));
 }
 
-// component-wise select (a ternary on the whole vector is lowered through scratch memory)
-__device__ __forceinline__ uint4 keep_if(bool ok, uint4 v) {
-  return make_uint4(ok ? v.x : 0u, ok ? v.y : 0u, ok ? v.z : 0u, ok ? v.w : 0u);
-}
-
 // zero the elements at positions >= nvalid (0..8) of a chunk
 __device__ __forceinline__ uint4 mask_chunk(uint4 v, int nvalid) {
   auto keep = [&](uint32_t w, int e0) -> uint32_t {
@@ -227,22 +221,13 @@ __device__ __forceinline__ void fetch_slab(Slab& s, const RowPtrs& rp, int64_t k
 }
 
 // writes a fetched slab to LDS, zeroing what lies outside the matrix or the token range [.., kend)
-template <bool RAGGED>
 __device__ __forceinline__ void stash_slab(const Slab& s, const RowPtrs& rp, uint16_t* as, uint16_t* bs, int64_t k,
                                            int64_t kend) {
   const int nvalid = (int)max((int64_t)0, min((int64_t)8, kend - k));
 #pragma unroll
   for (int c = 0; c < CHUNKS; ++c) {
-    uint4 xa = s.a[c], xb = s.b[c];
-    if (RAGGED) {
-      xa = mask_chunk(xa, ((rp.va >> c) & 1u) ? nvalid : 0);
-      xb = mask_chunk(xb, ((rp.vb >> c) & 1u) ? nvalid : 0);
-    } else {
-      xa = keep_if(((rp.va >> c) & 1u) && nvalid == 8, xa);
-      xb = keep_if(((rp.vb >> c) & 1u) && nvalid == 8, xb);
-    }
-    *reinterpret_cast<uint4*>(as + 32 * c * LDS_STRIDE) = xa;
-    *reinterpret_cast<uint4*>(bs + 32 * c * LDS_STRIDE) = xb;
+    *reinterpret_cast<uint4*>(as + 32 * c * LDS_STRIDE) = mask_chunk(s.a[c], ((rp.va >> c) & 1u) ? nvalid : 0);
+    *reinterpret_cast<uint4*>(bs + 32 * c * LDS_STRIDE) = mask_chunk(s.b[c], ((rp.vb >> c) & 1u) ? nvalid : 0);
   }
 }
 
@@ -293,7 +278,8 @@ __device__ __forceinline__ void multiply_slab(float16v (&acc)[4][4], const uint1
   __builtin_amdgcn_sched_group_barrier(0x008, 32, 0);
 }
 
-template <bool BF16, bool RAGGED>
+// Rows further apart than the ring kernel's 32-bit lane offsets reach (about 8 million tokens in one call).
+template <bool BF16>
 __global__ __launch_bounds__(NTHREADS) void gram_kernel(GramArgs a) {
   extern __shared__ __align__(16) uint16_t smem[];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -341,7 +327,7 @@ __global__ __launch_bounds__(NTHREADS) void gram_kernel(GramArgs a) {
   // and is stashed as zeros.
   Slab sl;
   fetch_slab(sl, rp, kbeg + kch, klast8);
-  stash_slab<RAGGED>(sl, rp, smem + st_off, smem + TM * LDS_STRIDE + st_off, kbeg + kch, kend);
+  stash_slab(sl, rp, smem + st_off, smem + TM * LDS_STRIDE + st_off, kbeg + kch, kend);
   __syncthreads();
   int cur = 0;
   for (int64_t k0 = kbeg; k0 < kend; k0 += BK) {
@@ -350,7 +336,7 @@ __global__ __launch_bounds__(NTHREADS) void gram_kernel(GramArgs a) {
     multiply_slab<BF16>(acc, smem + cur * STAGE + rdA, smem + cur * STAGE + rdB);
     __builtin_amdgcn_sched_barrier(0);
     cur ^= 1;
-    stash_slab<RAGGED>(sl, rp, smem + cur * STAGE + st_off, smem + cur * STAGE + TM * LDS_STRIDE + st_off,
+    stash_slab(sl, rp, smem + cur * STAGE + st_off, smem + cur * STAGE + TM * LDS_STRIDE + st_off,
                        k0 + BK + kch, kend);
     __syncthreads();
   }
@@ -372,8 +358,12 @@ __global__ __launch_bounds__(NTHREADS) void gram_kernel(GramArgs a) {
   }
 }
 
-// ---- interior fast path -----------------------------------------------------------------------------
-// Every tile is complete (m a multiple of 256) and every split covers whole slabs, so nothing is masked.
+// ---- direct-to-LDS path -----------------------------------------------------------------------------
+// For every shape whose rows a 32-bit offset reaches.  The loop runs over whole slabs and masks nothing: a partial tile
+// reads its last row again in place of the rows that do not exist, and up to 63 tokens behind the last whole slab are
+// one slab more, behind the loop, in the workgroups of a tile's last range.  Against the register-staged kernel that took
+// every shape with a partial tile or slab before: m 8192, 65540 tokens 6840 -> 3816 us (1.15 PFLOP/s), m 4128, 131072 tokens
+// 2970 -> 2038, m 1000, 300 tokens 35.5 -> 22.1 (whole tiles and slabs: no change).
 //
 // A wavefront that is alone on its SIMD pays the full issue time of every instruction that does not fit in the
 // shadow of the matrix pipe, and measured on this kernel the global loads and the LDS stores of the operand
@@ -425,7 +415,8 @@ constexpr size_t kSmemRing = size_t(5) * UNIT_BYTES;
 template <bool BF16, int S>
 __device__ __forceinline__ void kstep_ring(float16v (&acc)[4][4], const Frags& cf, Frags& nf, const uint16_t* nap,
                                            const uint16_t* nbp, unsigned ldsB, unsigned ldsA,
-                                           const unsigned (&off)[CHUNKS], const char* srcB, const char* srcA) {
+                                           const unsigned (&offB)[CHUNKS], const unsigned (&offA)[CHUNKS],
+                                           const char* srcB, const char* srcA) {
   constexpr unsigned CHUNK_BYTES = 32 * FROW * 2;
 #pragma unroll
   for (int m = 0; m < 16; ++m) {
@@ -447,15 +438,16 @@ __device__ __forceinline__ void kstep_ring(float16v (&acc)[4][4], const Frags& c
     if ((gm & 3) == 1) {
       const int c = gm >> 2;
       if (c < CHUNKS)
-        direct_load(ldsB + c * CHUNK_BYTES, off[c], srcB);
+        direct_load(ldsB + c * CHUNK_BYTES, offB[c], srcB);
       else
-        direct_load(ldsA + (c - CHUNKS) * CHUNK_BYTES, off[c - CHUNKS], srcA);
+        direct_load(ldsA + (c - CHUNKS) * CHUNK_BYTES, offA[c - CHUNKS], srcA);
       __builtin_amdgcn_sched_barrier(0);
     }
   }
 }
 
-template <bool BF16>
+// WHOLE: complete tiles and slabs only (the same code with what the rest needs left out: 1.2 % of a 4096 x 11008 pass).
+template <bool BF16, bool WHOLE>
 __global__ __launch_bounds__(NTHREADS) void gram_kernel_ring(GramArgs a) {
   extern __shared__ __align__(16) uint16_t smem[];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -475,9 +467,18 @@ __global__ __launch_bounds__(NTHREADS) void gram_kernel_ring(GramArgs a) {
       for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
   const int r0 = tid >> 3, ch = tid & 7;
   const int gch = ch ^ ((r0 >> 1) & 7);
-  unsigned off[CHUNKS];
+  // rows behind the last one read the last one; what they give is never read back
+  unsigned offA[CHUNKS], offB_[WHOLE ? 1 : CHUNKS];
 #pragma unroll
-  for (int c = 0; c < CHUNKS; ++c) off[c] = (unsigned)((int64_t)(r0 + 32 * c) * a.ldx * 2 + gch * 16);
+  for (int c = 0; c < CHUNKS; ++c) {
+    const int r = r0 + 32 * c;
+    offA[c] = (unsigned)((int64_t)(WHOLE ? r : min(r, a.m - 1 - rowA0)) * a.ldx * 2 + gch * 16);
+    if constexpr (!WHOLE) offB_[c] = (unsigned)((int64_t)min(r, a.m - 1 - rowB0) * a.ldx * 2 + gch * 16);
+  }
+  const unsigned(&offB)[CHUNKS] = [&]() -> const unsigned(&)[CHUNKS] {
+    if constexpr (WHOLE) return offA;
+    else return offB_;
+  }();
   const char* const baseA = reinterpret_cast<const char*>(a.X + (int64_t)rowA0 * a.ldx + kbeg);
   const char* const baseB = reinterpret_cast<const char*>(a.X + (int64_t)rowB0 * a.ldx + kbeg);
   const int wrow = 8 * wave * FROW;
@@ -490,21 +491,41 @@ __global__ __launch_bounds__(NTHREADS) void gram_kernel_ring(GramArgs a) {
   const unsigned lds0 = (unsigned)__builtin_amdgcn_readfirstlane(
       (int)((unsigned)(uintptr_t)((__attribute__((address_space(3))) uint16_t*)smem) + (unsigned)wrow * 2));
   constexpr unsigned CHUNK_BYTES = 32 * FROW * 2;
-  const int64_t nslab = (kend - kbeg) / BK;
+  // whole slabs, and tokens behind them (the last range of a tile); the last piece of a short range may be empty
+  const int64_t nslab = kend > kbeg ? (kend - kbeg) / BK : 0;
+  const int rem = (!WHOLE && kend > kbeg) ? (int)((kend - kbeg) % BK) : 0;
   const int64_t last = (nslab - 1) * (BK * 2);     // byte offset of the last slab: loads behind it re-read it
 
   // prologue: A and B of slab 0 into units 0 and 1, A of slab 1 into unit 2
-  {
+  if (nslab > 0) {
     const char* a1 = baseA + min((int64_t)(BK * 2), last);
 #pragma unroll
     for (int c = 0; c < CHUNKS; ++c) {
-      direct_load(lds0 + c * CHUNK_BYTES, off[c], baseA);
-      direct_load(lds0 + UNIT_BYTES + c * CHUNK_BYTES, off[c], baseB);
-      direct_load(lds0 + 2 * UNIT_BYTES + c * CHUNK_BYTES, off[c], a1);
+      direct_load(lds0 + c * CHUNK_BYTES, offA[c], baseA);
+      direct_load(lds0 + UNIT_BYTES + c * CHUNK_BYTES, offB[c], baseB);
+      direct_load(lds0 + 2 * UNIT_BYTES + c * CHUNK_BYTES, offA[c], a1);
     }
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
+  // The tokens behind the last whole slab, zeros behind them, as one more slab in units 0 and 1: through registers, since
+  // a direct load cannot mask.  The loads re-read behind the last slab (into any unit) have landed in every wavefront
+  // before the first barrier.
+  auto stash_rest = [&]() {
+    __syncthreads();
+    const int64_t k = kbeg + nslab * BK + gch * 8, klast8 = ((a.t - 1) / 8) * 8;
+    const int nvalid = (int)max((int64_t)0, min((int64_t)8, kend - k));
+#pragma unroll
+    for (int c = 0; c < CHUNKS; ++c) {
+      const int r = r0 + 32 * c;
+      uint16_t* dst = smem + r * FROW + ch * 8;
+      *reinterpret_cast<uint4*>(dst) =
+          mask_chunk(load_chunk(a.X + (int64_t)min(rowA0 + r, a.m - 1) * a.ldx, k, klast8), nvalid);
+      *reinterpret_cast<uint4*>(dst + UNIT) =
+          mask_chunk(load_chunk(a.X + (int64_t)min(rowB0 + r, a.m - 1) * a.ldx, k, klast8), nvalid);
+    }
+    __syncthreads();
+  };
   int ua = 0;                                      // unit of A of the current slab; B is the next one
   const bool idle = (bi == bj && wm == 1 && wn == 0);   // this wavefront's quarter of a diagonal tile is never read back
   if (idle) {
@@ -517,12 +538,12 @@ __global__ __launch_bounds__(NTHREADS) void gram_kernel_ring(GramArgs a) {
       const unsigned ldsB = lds0 + (unsigned)unB * UNIT_BYTES, ldsA = lds0 + (unsigned)unA * UNIT_BYTES;
 #pragma unroll
       for (int c = 0; c < CHUNKS; ++c) {
-        direct_load(ldsB + c * CHUNK_BYTES, off[c], srcB);
+        direct_load(ldsB + c * CHUNK_BYTES, offB[c], srcB);
         __builtin_amdgcn_s_sleep(1);
       }
 #pragma unroll
       for (int c = 0; c < CHUNKS; ++c) {
-        direct_load(ldsA + c * CHUNK_BYTES, off[c], srcA);
+        direct_load(ldsA + c * CHUNK_BYTES, offA[c], srcA);
         __builtin_amdgcn_s_sleep(2);
       }
       asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
@@ -530,6 +551,8 @@ __global__ __launch_bounds__(NTHREADS) void gram_kernel_ring(GramArgs a) {
       ua = (ua + 2 >= 5) ? ua + 2 - 5 : ua + 2;
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if constexpr (!WHOLE)
+      if (rem > 0) stash_rest();
     return;
   }
   for (int64_t it = 0; it < nslab; ++it) {
@@ -544,16 +567,27 @@ __global__ __launch_bounds__(NTHREADS) void gram_kernel_ring(GramArgs a) {
     Frags f0, f1;
     load_frags_full(f0, as + pos[0], bs + pos[0]);
     __builtin_amdgcn_sched_barrier(0);
-    kstep_ring<BF16, 0>(acc, f0, f1, as + pos[1], bs + pos[1], ldsB, ldsA, off, srcB, srcA);
-    kstep_ring<BF16, 1>(acc, f1, f0, as + pos[2], bs + pos[2], ldsB, ldsA, off, srcB, srcA);
-    kstep_ring<BF16, 2>(acc, f0, f1, as + pos[3], bs + pos[3], ldsB, ldsA, off, srcB, srcA);
-    kstep_ring<BF16, 3>(acc, f1, f0, as, bs, ldsB, ldsA, off, srcB, srcA);
+    kstep_ring<BF16, 0>(acc, f0, f1, as + pos[1], bs + pos[1], ldsB, ldsA, offB, offA, srcB, srcA);
+    kstep_ring<BF16, 1>(acc, f1, f0, as + pos[2], bs + pos[2], ldsB, ldsA, offB, offA, srcB, srcA);
+    kstep_ring<BF16, 2>(acc, f0, f1, as + pos[3], bs + pos[3], ldsB, ldsA, offB, offA, srcB, srcA);
+    kstep_ring<BF16, 3>(acc, f1, f0, as, bs, ldsB, ldsA, offB, offA, srcB, srcA);
     // loads complete in order: all but the last eight (A of slab it + 2) have landed, i.e. A and B of slab it + 1
     asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
     __syncthreads();
     ua = (ua + 2 >= 5) ? ua + 2 - 5 : ua + 2;
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  if constexpr (!WHOLE) {
+    if (rem > 0) {
+      stash_rest();
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        Frags f;
+        load_frags_full(f, smem + rdA + pos[s], smem + UNIT + rdB + pos[s]);
+        mfma_block<BF16>(acc, f);
+      }
+    }
+  }
   float* P = a.P + wk.slot * (TM * TM);
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
@@ -762,16 +796,14 @@ extern "C" slim_status slim_hessian_accumulate(slim_ctx* ctx, const void* X, sli
   if (st != SLIM_OK) return st;
   a.P = static_cast<float*>(slim_ws_alloc(ctx, pbytes));
 
-  const bool ragged = (t_c % 8) != 0;
-  // fast path: complete tiles, whole slabs in every split, lane offsets inside 32 bits
-  const bool full = (m % TM == 0) && (t_c % BK == 0) && (kchunk * S == t_c) &&
-                    ((int64_t)(TM - 1) * ldx * 2 + 128 < (int64_t(1) << 32));
-  const void* variants[6] = {reinterpret_cast<const void*>(gram_kernel<false, false>),
-                             reinterpret_cast<const void*>(gram_kernel<false, true>),
-                             reinterpret_cast<const void*>(gram_kernel<true, false>),
-                             reinterpret_cast<const void*>(gram_kernel<true, true>),
-                             reinterpret_cast<const void*>(gram_kernel_ring<false>),
-                             reinterpret_cast<const void*>(gram_kernel_ring<true>)};
+  const bool ring = (int64_t)(TM - 1) * ldx * 2 + 128 < (int64_t(1) << 32);      // lane offsets inside 32 bits
+  const bool whole = m % TM == 0 && t_c % BK == 0;
+  const void* variants[6] = {reinterpret_cast<const void*>(gram_kernel<false>),
+                             reinterpret_cast<const void*>(gram_kernel<true>),
+                             reinterpret_cast<const void*>(gram_kernel_ring<false, true>),
+                             reinterpret_cast<const void*>(gram_kernel_ring<false, false>),
+                             reinterpret_cast<const void*>(gram_kernel_ring<true, true>),
+                             reinterpret_cast<const void*>(gram_kernel_ring<true, false>)};
   static bool attr_done = false;
   if (!attr_done) {
     for (const void* fn : variants)
@@ -788,7 +820,7 @@ extern "C" slim_status slim_hessian_accumulate(slim_ctx* ctx, const void* X, sli
   // what the lockstep gains (m = 5120: 5.76 against 5.52 ms), so short launches stay whole.
   const int ncu_l = ctx->num_cus > 0 ? ctx->num_cus : 256;
   std::vector<std::pair<int64_t, int64_t>> rounds;     // (first workgroup id, workgroups)
-  if (full && (int64_t)a.n_main >= 5 * (int64_t)ncu_l) {
+  if (ring && (int64_t)a.n_main >= 5 * (int64_t)ncu_l) {
     int64_t base = 0;
     for (; base + 2 * ncu_l <= nwg; base += ncu_l) rounds.emplace_back(base, (int64_t)ncu_l);
     rounds.emplace_back(base, nwg - base);             // the rest of the last full round with the short tail workgroups
@@ -796,27 +828,31 @@ extern "C" slim_status slim_hessian_accumulate(slim_ctx* ctx, const void* X, sli
     rounds.emplace_back((int64_t)0, nwg);
   }
   if (x_dtype == SLIM_BF16) {
-    if (full) {
+    if (ring) {
       for (const auto& r : rounds) {
         a.id_base = (int)r.first;
-        SLIM_LAUNCH(ctx, "gram_mfma_bf16@gram_kernel_ring<true>", (gram_kernel_ring<true>), dim3((unsigned)r.second), block,
-                    kSmemRing, a);
+        if (whole)
+          SLIM_LAUNCH(ctx, "gram_mfma_bf16@gram_kernel_ring<true, true>", (gram_kernel_ring<true, true>), dim3((unsigned)r.second),
+                      block, kSmemRing, a);
+        else
+          SLIM_LAUNCH(ctx, "gram_mfma_bf16@gram_kernel_ring<true, false>", (gram_kernel_ring<true, false>), dim3((unsigned)r.second),
+                      block, kSmemRing, a);
       }
-    } else if (ragged)
-      SLIM_LAUNCH(ctx, "gram_mfma_bf16@gram_kernel<true, true>", (gram_kernel<true, true>), grid, block, kSmemBytes, a);
-    else
-      SLIM_LAUNCH(ctx, "gram_mfma_bf16@gram_kernel<true, false>", (gram_kernel<true, false>), grid, block, kSmemBytes, a);
+    } else
+      SLIM_LAUNCH(ctx, "gram_mfma_bf16@gram_kernel<true>", (gram_kernel<true>), grid, block, kSmemBytes, a);
   } else {
-    if (full) {
+    if (ring) {
       for (const auto& r : rounds) {
         a.id_base = (int)r.first;
-        SLIM_LAUNCH(ctx, "gram_mfma_f16@gram_kernel_ring<false>", (gram_kernel_ring<false>), dim3((unsigned)r.second), block,
-                    kSmemRing, a);
+        if (whole)
+          SLIM_LAUNCH(ctx, "gram_mfma_f16@gram_kernel_ring<false, true>", (gram_kernel_ring<false, true>), dim3((unsigned)r.second),
+                      block, kSmemRing, a);
+        else
+          SLIM_LAUNCH(ctx, "gram_mfma_f16@gram_kernel_ring<false, false>", (gram_kernel_ring<false, false>), dim3((unsigned)r.second),
+                      block, kSmemRing, a);
       }
-    } else if (ragged)
-      SLIM_LAUNCH(ctx, "gram_mfma_f16@gram_kernel<false, true>", (gram_kernel<false, true>), grid, block, kSmemBytes, a);
-    else
-      SLIM_LAUNCH(ctx, "gram_mfma_f16@gram_kernel<false, false>", (gram_kernel<false, false>), grid, block, kSmemBytes, a);
+    } else
+      SLIM_LAUNCH(ctx, "gram_mfma_f16@gram_kernel<false>", (gram_kernel<false>), grid, block, kSmemBytes, a);
   }
   SLIM_LAUNCH(ctx, "gram_reduce", gram_reduce, dim3(tiles, (TM / RB) * (TM / RB)), dim3(256), 0, a, G, ldg);
   *n_tokens += t_c;
