@@ -53,6 +53,8 @@ struct GramArgs {
   int f;               // sub-splits per split of a tail tile
   int64_t subchunk;    // tokens per sub-split (multiple of BK)
   float* P;            // partial tiles: [slot][TM][TM]
+  float* G;            // the small tiles add to it themselves
+  int64_t ldg;
   int interleave;      // how the tiles are dealt to the XCDs: 0 runs, 1 interleaved, 2 patches per round (decode_work)
   int super;           // tile order: edge of a supertile in tiles, or, negative, minus the height of a band (decode_tile)
   int id_base;         // id of the launch's first workgroup (the ring kernel may be launched round by round)
@@ -395,12 +397,18 @@ __device__ __forceinline__ void direct_load(unsigned lds_addr, unsigned voff, co
 #endif
 }
 
-// operand fragments of K step s: `ap` / `bp` already point at this lane's row and swizzled chunk
-__device__ __forceinline__ void load_frags_full(Frags& f, const uint16_t* ap, const uint16_t* bp) {
+// operand fragments of a K step, 2 or 4 tiles of 32 rows a side
+template <int FI>
+struct FragsOf {
+  uint4 a[FI], b[FI];
+};
+// `ap` / `bp` already point at this lane's row and swizzled chunk
+template <int FI>
+__device__ __forceinline__ void load_frags_full(FragsOf<FI>& f, const uint16_t* ap, const uint16_t* bp) {
 #pragma unroll
-  for (int i = 0; i < 4; ++i) f.a[i] = *reinterpret_cast<const uint4*>(ap + i * 32 * FROW);
+  for (int i = 0; i < FI; ++i) f.a[i] = *reinterpret_cast<const uint4*>(ap + i * 32 * FROW);
 #pragma unroll
-  for (int j = 0; j < 4; ++j) f.b[j] = *reinterpret_cast<const uint4*>(bp + j * 32 * FROW);
+  for (int j = 0; j < FI; ++j) f.b[j] = *reinterpret_cast<const uint4*>(bp + j * 32 * FROW);
 }
 
 // ---- the operand slabs in a ring of five units ----------------------------------------------------------
@@ -409,46 +417,99 @@ __device__ __forceinline__ void load_frags_full(Frags& f, const uint16_t* ap, co
 // unit 2s + 1 mod 5.  While slab s is multiplied, the two units that slab s - 1 has just freed take B of slab s + 1
 // and A of slab s + 2, so half of the loads are on their way a whole slab longer than with two stages, and the
 // other half can go out in the first quarter of the slab without the second half crowding the address path.
-constexpr unsigned UNIT_BYTES = TM * FROW * 2;                         // 32 KiB
-constexpr size_t kSmemRing = size_t(5) * UNIT_BYTES;
+//
+// Tiles of 256 x 256, or of 128 x 128 for launches of few tokens (EDGE): units of 16 KiB then, two workgroups per CU.
+template <int EDGE>
+constexpr size_t kSmemRing = size_t(5) * EDGE * FROW * 2;
 
-template <bool BF16, int S>
-__device__ __forceinline__ void kstep_ring(float16v (&acc)[4][4], const Frags& cf, Frags& nf, const uint16_t* nap,
+template <bool BF16, int S, int FI>
+__device__ __forceinline__ void kstep_ring(float16v (&acc)[FI][FI], const FragsOf<FI>& cf, FragsOf<FI>& nf, const uint16_t* nap,
                                            const uint16_t* nbp, unsigned ldsB, unsigned ldsA,
-                                           const unsigned (&offB)[CHUNKS], const unsigned (&offA)[CHUNKS],
-                                           const char* srcB, const char* srcA) {
+                                           const unsigned (&offB)[2 * FI], const unsigned (&offA)[2 * FI], const char* srcB,
+                                           const char* srcA) {
   constexpr unsigned CHUNK_BYTES = 32 * FROW * 2;
+  constexpr int NM = FI * FI, CH = 2 * FI;
 #pragma unroll
-  for (int m = 0; m < 16; ++m) {
-    acc[m >> 2][m & 3] = mfma<BF16>(cf.a[m >> 2], cf.b[m & 3], acc[m >> 2][m & 3]);
+  for (int m = 0; m < NM; ++m) {
+    acc[m / FI][m % FI] = mfma<BF16>(cf.a[m / FI], cf.b[m % FI], acc[m / FI][m % FI]);
     __builtin_amdgcn_sched_barrier(0);
-    if (S < 3 && (m & 1) == 0) {
-      const int q = m >> 1;
-      if (q < 4)
+    if (S < 3 && m % (FI / 2) == 0) {
+      const int q = m / (FI / 2);
+      if (q < FI)
         nf.a[q] = *reinterpret_cast<const uint4*>(nap + q * 32 * FROW);
       else
-        nf.b[q - 4] = *reinterpret_cast<const uint4*>(nbp + (q - 4) * 32 * FROW);
+        nf.b[q - FI] = *reinterpret_cast<const uint4*>(nbp + (q - FI) * 32 * FROW);
       __builtin_amdgcn_sched_barrier(0);
     }
-    const int gm = 16 * S + m;             // index of this MFMA in the iteration
-    // One direct load per four MFMAs over the whole slab: B of the next slab in the first half, A of the slab after
+    const int gm = NM * S + m;             // index of this MFMA in the iteration
+    // One direct load per four (two) MFMAs over the whole slab: B of the next slab in the first half, A of the slab after
     // it in the second.  Measured against loads crowded into the first half or quarter of the slab (one per MFMA or
     // per two, as two stages force them to be): the even rate is 1 to 3 % faster, and the ring as a whole 3.5 % (m =
     // 11008) to 7 % (m = 4096) faster than two stages.
-    if ((gm & 3) == 1) {
-      const int c = gm >> 2;
-      if (c < CHUNKS)
+    if (gm % FI == 1) {
+      const int c = gm / FI;
+      if (c < CH)
         direct_load(ldsB + c * CHUNK_BYTES, offB[c], srcB);
       else
-        direct_load(ldsA + (c - CHUNKS) * CHUNK_BYTES, offA[c - CHUNKS], srcA);
+        direct_load(ldsA + (c - CH) * CHUNK_BYTES, offA[c - CH], srcA);
       __builtin_amdgcn_sched_barrier(0);
     }
   }
 }
 
+// Adds a wavefront's sums (FI x FI tiles of 32 x 32 at row, col) to G and, mirrored, to the other triangle.  On the diagonal
+// only the upper triangle of the sums counts.  A lane holds one column and runs of four rows: 128-byte lines per half
+// wavefront in the block itself, 16 bytes per lane in the mirror (its lines are completed by the next three instructions).
+template <int FI>
+__device__ __forceinline__ void add_to_gram(const float16v (&acc)[FI][FI], float* __restrict__ G, int64_t ldg, int m, int row,
+                                            int col, int lane) {
+  const int l32 = lane & 31, lh = lane >> 5;
+#pragma unroll
+  for (int i = 0; i < FI; ++i)
+#pragma unroll
+    for (int j = 0; j < FI; ++j) {
+      const int r0 = row + i * 32 + 4 * lh, c = col + j * 32 + l32;
+      if (row + i * 32 > col + j * 32 + 31) continue;          // below the diagonal
+      const bool edge = row + i * 32 + 31 >= col + j * 32;     // on it
+      if (c >= m) continue;
+      if (!edge && ldg % 4 == 0) {
+        float g[16];
+        float4 h[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          if (r0 + 8 * q < m) {                                // m is a multiple of 8: four rows are inside or outside
+#pragma unroll
+            for (int e = 0; e < 4; ++e) g[4 * q + e] = G[(int64_t)(r0 + 8 * q + e) * ldg + c];
+            h[q] = *reinterpret_cast<const float4*>(G + (int64_t)c * ldg + r0 + 8 * q);
+          }
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          if (r0 + 8 * q < m) {
+            const float16v& v = acc[i][j];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) G[(int64_t)(r0 + 8 * q + e) * ldg + c] = g[4 * q + e] + v[4 * q + e];
+            *reinterpret_cast<float4*>(G + (int64_t)c * ldg + r0 + 8 * q) =
+                make_float4(h[q].x + v[4 * q], h[q].y + v[4 * q + 1], h[q].z + v[4 * q + 2], h[q].w + v[4 * q + 3]);
+          }
+      } else {
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+          const int r = r0 + 8 * (e >> 2) + (e & 3);
+          if (r > c || r >= m) continue;
+          G[(int64_t)r * ldg + c] += acc[i][j][e];
+          if (r < c) G[(int64_t)c * ldg + r] += acc[i][j][e];
+        }
+      }
+    }
+}
+
 // WHOLE: complete tiles and slabs only (the same code with what the rest needs left out: 1.2 % of a 4096 x 11008 pass).
-template <bool BF16, bool WHOLE>
-__global__ __launch_bounds__(NTHREADS) void gram_kernel_ring(GramArgs a) {
+template <bool BF16, int EDGE, bool WHOLE>
+__global__ __launch_bounds__(NTHREADS, 256 / EDGE) void gram_kernel_ring(GramArgs a) {
+  constexpr int FI = EDGE / 64, CHUNKS = 2 * FI;
+  constexpr int TM = EDGE;
+  constexpr unsigned UNIT_BYTES = TM * FROW * 2;
+  using Frags = FragsOf<FI>;
   extern __shared__ __align__(16) uint16_t smem[];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave >> 1, wn = wave & 1;
@@ -458,11 +519,11 @@ __global__ __launch_bounds__(NTHREADS) void gram_kernel_ring(GramArgs a) {
   const int rowA0 = bi * TM, rowB0 = bj * TM;
   const int64_t kbeg = wk.kbeg, kend = wk.kend;
   constexpr int UNIT = TM * FROW;         // halves per unit
-  float16v acc[4][4];
+  float16v acc[FI][FI];
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < FI; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
+    for (int j = 0; j < FI; ++j)
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
   const int r0 = tid >> 3, ch = tid & 7;
@@ -484,7 +545,7 @@ __global__ __launch_bounds__(NTHREADS) void gram_kernel_ring(GramArgs a) {
   const int wrow = 8 * wave * FROW;
   const int l32 = lane & 31, lh = lane >> 5;
   const int xm = (l32 >> 1) & 7;
-  const int rdA = (wm * 128 + l32) * FROW, rdB = (wn * 128 + l32) * FROW;     // inside a unit
+  const int rdA = (wm * (EDGE / 2) + l32) * FROW, rdB = (wn * (EDGE / 2) + l32) * FROW;     // inside a unit
   int pos[4];
 #pragma unroll
   for (int s = 0; s < 4; ++s) pos[s] = ((2 * s + lh) ^ xm) * 8;
@@ -546,7 +607,7 @@ __global__ __launch_bounds__(NTHREADS) void gram_kernel_ring(GramArgs a) {
         direct_load(ldsA + c * CHUNK_BYTES, offA[c], srcA);
         __builtin_amdgcn_s_sleep(2);
       }
-      asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(CHUNKS) : "memory");
       __syncthreads();
       ua = (ua + 2 >= 5) ? ua + 2 - 5 : ua + 2;
     }
@@ -555,7 +616,28 @@ __global__ __launch_bounds__(NTHREADS) void gram_kernel_ring(GramArgs a) {
       if (rem > 0) stash_rest();
     return;
   }
+  // The small tile's sums are folded every 512 tokens, so that not splitting its tokens costs no precision.
+  constexpr int FOLD = 8;
+  float16v sum[EDGE == 128 ? FI : 1][EDGE == 128 ? FI : 1];
+  if constexpr (EDGE == 128) {
+#pragma unroll
+    for (int i = 0; i < FI; ++i)
+#pragma unroll
+      for (int j = 0; j < FI; ++j) sum[i][j] = acc[i][j];
+  }
   for (int64_t it = 0; it < nslab; ++it) {
+    if constexpr (EDGE == 128) {
+      if (it % FOLD == 0) {
+#pragma unroll
+        for (int i = 0; i < FI; ++i)
+#pragma unroll
+          for (int j = 0; j < FI; ++j) {
+            sum[i][j] += acc[i][j];
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+          }
+      }
+    }
     const int ub = (ua + 1 >= 5) ? ua + 1 - 5 : ua + 1;
     const int unB = (ua + 3 >= 5) ? ua + 3 - 5 : ua + 3;     // takes B of slab it + 1
     const int unA = (ua + 4 >= 5) ? ua + 4 - 5 : ua + 4;     // takes A of slab it + 2
@@ -567,12 +649,12 @@ __global__ __launch_bounds__(NTHREADS) void gram_kernel_ring(GramArgs a) {
     Frags f0, f1;
     load_frags_full(f0, as + pos[0], bs + pos[0]);
     __builtin_amdgcn_sched_barrier(0);
-    kstep_ring<BF16, 0>(acc, f0, f1, as + pos[1], bs + pos[1], ldsB, ldsA, offB, offA, srcB, srcA);
-    kstep_ring<BF16, 1>(acc, f1, f0, as + pos[2], bs + pos[2], ldsB, ldsA, offB, offA, srcB, srcA);
-    kstep_ring<BF16, 2>(acc, f0, f1, as + pos[3], bs + pos[3], ldsB, ldsA, offB, offA, srcB, srcA);
-    kstep_ring<BF16, 3>(acc, f1, f0, as, bs, ldsB, ldsA, offB, offA, srcB, srcA);
-    // loads complete in order: all but the last eight (A of slab it + 2) have landed, i.e. A and B of slab it + 1
-    asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+    kstep_ring<BF16, 0, FI>(acc, f0, f1, as + pos[1], bs + pos[1], ldsB, ldsA, offB, offA, srcB, srcA);
+    kstep_ring<BF16, 1, FI>(acc, f1, f0, as + pos[2], bs + pos[2], ldsB, ldsA, offB, offA, srcB, srcA);
+    kstep_ring<BF16, 2, FI>(acc, f0, f1, as + pos[3], bs + pos[3], ldsB, ldsA, offB, offA, srcB, srcA);
+    kstep_ring<BF16, 3, FI>(acc, f1, f0, as, bs, ldsB, ldsA, offB, offA, srcB, srcA);
+    // loads complete in order: all but the last CHUNKS (A of slab it + 2) have landed, i.e. A and B of slab it + 1
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(CHUNKS) : "memory");
     __syncthreads();
     ua = (ua + 2 >= 5) ? ua + 2 - 5 : ua + 2;
   }
@@ -584,18 +666,29 @@ __global__ __launch_bounds__(NTHREADS) void gram_kernel_ring(GramArgs a) {
       for (int s = 0; s < 4; ++s) {
         Frags f;
         load_frags_full(f, smem + rdA + pos[s], smem + UNIT + rdB + pos[s]);
-        mfma_block<BF16>(acc, f);
+#pragma unroll
+        for (int i = 0; i < FI; ++i)
+#pragma unroll
+          for (int j = 0; j < FI; ++j) acc[i][j] = mfma<BF16>(f.a[i], f.b[j], acc[i][j]);
       }
     }
   }
+  if constexpr (EDGE == 128) {
+#pragma unroll
+    for (int i = 0; i < FI; ++i)
+#pragma unroll
+      for (int j = 0; j < FI; ++j) acc[i][j] += sum[i][j];
+    add_to_gram<FI>(acc, a.G, a.ldg, a.m, rowA0 + wm * 64, rowB0 + wn * 64, lane);
+    return;
+  }
   float* P = a.P + wk.slot * (TM * TM);
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
+  for (int i = 0; i < FI; ++i) {
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
-      const int rl = wm * 128 + i * 32 + 8 * (v >> 2) + 4 * lh + (v & 3);
+      const int rl = wm * (EDGE / 2) + i * 32 + 8 * (v >> 2) + 4 * lh + (v & 3);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) P[rl * TM + wn * 128 + j * 32 + l32] = acc[i][j][v];
+      for (int j = 0; j < FI; ++j) P[rl * TM + wn * (EDGE / 2) + j * 32 + l32] = acc[i][j][v];
     }
   }
 }
@@ -798,19 +891,46 @@ extern "C" slim_status slim_hessian_accumulate(slim_ctx* ctx, const void* X, sli
 
   const bool ring = (int64_t)(TM - 1) * ldx * 2 + 128 < (int64_t(1) << 32);      // lane offsets inside 32 bits
   const bool whole = m % TM == 0 && t_c % BK == 0;
-  const void* variants[6] = {reinterpret_cast<const void*>(gram_kernel<false>),
+  const void* variants[8] = {reinterpret_cast<const void*>(gram_kernel<false>),
                              reinterpret_cast<const void*>(gram_kernel<true>),
-                             reinterpret_cast<const void*>(gram_kernel_ring<false, true>),
-                             reinterpret_cast<const void*>(gram_kernel_ring<false, false>),
-                             reinterpret_cast<const void*>(gram_kernel_ring<true, true>),
-                             reinterpret_cast<const void*>(gram_kernel_ring<true, false>)};
+                             reinterpret_cast<const void*>(gram_kernel_ring<false, 256, true>),
+                             reinterpret_cast<const void*>(gram_kernel_ring<false, 256, false>),
+                             reinterpret_cast<const void*>(gram_kernel_ring<true, 256, true>),
+                             reinterpret_cast<const void*>(gram_kernel_ring<true, 256, false>),
+                             reinterpret_cast<const void*>(gram_kernel_ring<false, 128, false>),
+                             reinterpret_cast<const void*>(gram_kernel_ring<true, 128, false>)};
   static bool attr_done = false;
   if (!attr_done) {
     for (const void* fn : variants)
-      SLIM_HIP_TRY(ctx, hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)std::max(kSmemBytes, kSmemRing)));
+      SLIM_HIP_TRY(ctx, hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)std::max(kSmemBytes, kSmemRing<256>)));
     attr_done = true;
   }
   const dim3 grid((unsigned)nwg), block(NTHREADS);
+  // Few tokens and enough tiles of 128 x 128 to fill the chip (two workgroups per CU): those, which add to G themselves.
+  // With 256 x 256 tiles the slots and their reduction are half of such a launch; with more tokens the small tile's twice
+  // as many operand bytes per product cost more than that.  Large / small tiles, us:
+  //   m 2560: 300 tokens 31 / 23, 2048 45 / 39;   m 3328: 2048 56 / 49, 3000 67 / 72;   m 4096: 300 47 / 43, 1000 59 / 60,
+  //   2048 96 / 78, 4096 125 / 125, 8192 179 / 214;   m 6000: 1000 131 / 105, 2048 160 / 132;   m 8192: 2048 304 / 258,
+  //   4096 407 / 404;   m 11008: 2048 484 / 474, 4096 675 / 739;   m 2048 (136 tiles): 2048 37 / 38, 4096 45 / 56.
+  // The error against 64 bits at 2048 tokens: m 4096 1.8e-7 / 1.3e-7, m 8192 2.7e-7 / 1.4e-7 (relative, standard normal X).
+  const int nts = slim_cdiv(m, 128), small_tiles = nts * (nts + 1) / 2;
+  if (ring && small_tiles >= 200 && t_c <= 2048) {
+    a.G = G;
+    a.ldg = ldg;
+    a.kchunk = (t_c + BK - 1) / BK * BK;
+    a.S = 1;
+    a.tiles_main = a.n_main = small_tiles;
+    a.interleave = 0;
+    a.super = 8;
+    if (x_dtype == SLIM_BF16)
+      SLIM_LAUNCH(ctx, "gram_mfma_bf16@gram_kernel_ring<true, 128, false>", (gram_kernel_ring<true, 128, false>), dim3(small_tiles), block,
+                  kSmemRing<128>, a);
+    else
+      SLIM_LAUNCH(ctx, "gram_mfma_f16@gram_kernel_ring<false, 128, false>", (gram_kernel_ring<false, 128, false>), dim3(small_tiles), block,
+                  kSmemRing<128>, a);
+    *n_tokens += t_c;
+    return SLIM_OK;
+  }
   // Launches of the fast path.  Workgroups that share row blocks of X find each other's lines in their XCD's L2 only
   // while they are at the same tokens, i.e. while they have started together; a workgroup that starts when another
   // one ends (diagonal tiles end 14 % early) shares nothing.  With many rounds of workgroups the starts drift apart,
@@ -832,11 +952,11 @@ extern "C" slim_status slim_hessian_accumulate(slim_ctx* ctx, const void* X, sli
       for (const auto& r : rounds) {
         a.id_base = (int)r.first;
         if (whole)
-          SLIM_LAUNCH(ctx, "gram_mfma_bf16@gram_kernel_ring<true, true>", (gram_kernel_ring<true, true>), dim3((unsigned)r.second),
-                      block, kSmemRing, a);
+          SLIM_LAUNCH(ctx, "gram_mfma_bf16@gram_kernel_ring<true, 256, true>", (gram_kernel_ring<true, 256, true>), dim3((unsigned)r.second),
+                      block, kSmemRing<256>, a);
         else
-          SLIM_LAUNCH(ctx, "gram_mfma_bf16@gram_kernel_ring<true, false>", (gram_kernel_ring<true, false>), dim3((unsigned)r.second),
-                      block, kSmemRing, a);
+          SLIM_LAUNCH(ctx, "gram_mfma_bf16@gram_kernel_ring<true, 256, false>", (gram_kernel_ring<true, 256, false>), dim3((unsigned)r.second),
+                      block, kSmemRing<256>, a);
       }
     } else
       SLIM_LAUNCH(ctx, "gram_mfma_bf16@gram_kernel<true>", (gram_kernel<true>), grid, block, kSmemBytes, a);
@@ -845,11 +965,11 @@ extern "C" slim_status slim_hessian_accumulate(slim_ctx* ctx, const void* X, sli
       for (const auto& r : rounds) {
         a.id_base = (int)r.first;
         if (whole)
-          SLIM_LAUNCH(ctx, "gram_mfma_f16@gram_kernel_ring<false, true>", (gram_kernel_ring<false, true>), dim3((unsigned)r.second),
-                      block, kSmemRing, a);
+          SLIM_LAUNCH(ctx, "gram_mfma_f16@gram_kernel_ring<false, 256, true>", (gram_kernel_ring<false, 256, true>), dim3((unsigned)r.second),
+                      block, kSmemRing<256>, a);
         else
-          SLIM_LAUNCH(ctx, "gram_mfma_f16@gram_kernel_ring<false, false>", (gram_kernel_ring<false, false>), dim3((unsigned)r.second),
-                      block, kSmemRing, a);
+          SLIM_LAUNCH(ctx, "gram_mfma_f16@gram_kernel_ring<false, 256, false>", (gram_kernel_ring<false, 256, false>), dim3((unsigned)r.second),
+                      block, kSmemRing<256>, a);
       }
     } else
       SLIM_LAUNCH(ctx, "gram_mfma_f16@gram_kernel<false>", (gram_kernel<false>), grid, block, kSmemBytes, a);

@@ -10,7 +10,8 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
 @pytest.mark.parametrize("m,t", [(8, 1), (8, 63), (248, 64), (256, 65), (264, 127), (504, 200), (512, 1024), (1000, 3001),
-                                 (1504, 4096), (2056, 777), (4096, 8229), (4104, 2048), (5120, 10007)])
+                                 (1504, 4096), (2056, 777), (4096, 8229), (4104, 2048), (5120, 10007),
+                                 (2568, 61), (2696, 2048), (3000, 1100), (4096, 2048), (5000, 513)])
 def test_shapes(m, t, dtype):
     from paper_2405_14917_amd import binding
     ldx = (t + 7) // 8 * 8 + 8
