@@ -315,7 +315,9 @@ slim_status slim_dequant_matmul_zp(slim_ctx* ctx, const uint32_t* packed, int64_
  *   What   optional n x m (ld = m) in what_dtype (F32 or F64), or NULL
  *   loss_curve   host, steps + 1 doubles or NULL: the loss before every step and after the last; NULL: the call does
  *          not wait for its own work
- * All arithmetic is fp64 or exact integers (widths up to 5: W_hat G from integers; wider: on the fp64 matrix cores); a step
+ *   beta   any divisor of m (m, ldw and ldg multiples of 4)
+ * All arithmetic is fp64 or exact integers (widths up to 5: W_hat G from integers; wider, and group sizes that 4 does not
+ * divide: (W_hat - W) G on the fp64 matrix cores); a step
  * costs one n x m x m product and one pass over W.
  */
 slim_status slim_lwc_quantize(slim_ctx* ctx, const void* W, slim_dtype w_dtype, int n, int m, int64_t ldw,

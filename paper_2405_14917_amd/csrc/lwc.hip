@@ -18,7 +18,9 @@
 // lanes per (row, group), fixed-order reductions.
 // The difference of the two products loses the digits that W_hat and W share: none that matter at two to five bits (loss
 // curves within 2e-16 of the float64 oracle's either way), but at eight bits with outlier channels 1e-14 instead of 2e-15.
-// Layers with a group of more than five bits therefore multiply W_hat - W itself, on the fp64 matrix cores.
+// Layers with a group of more than five bits therefore multiply W_hat - W itself, on the fp64 matrix cores.  So do those whose
+// group size 4 does not divide: the passes over W then take one channel per lane in place of four (V), since four would
+// reach into the next group, and the integers' operand order has no place for such a group.
 // What bounds it: the vector work behind the MFMAs of the product (figures at lwc_step).
 #include <cmath>
 
@@ -84,23 +86,37 @@ __device__ __forceinline__ double rint_quotient(double w, const LwcGroup& p, dou
   return c;
 }
 
-// the integers, scale and zero's rest of one (row, group)
-template <typename T>
+// V consecutive weights
+template <typename T, int V>
+__device__ __forceinline__ void load_weights(const T* p, double (&v)[V]) {
+  if constexpr (V == 4)
+    load4<T>(p, v);
+  else
+    v[0] = (double)__uint_as_float(float_bits<T>(*p));
+}
+
+// the integers (with a.D: the differences W_hat - W), scale and zero's rest of one (row, group)
+template <typename T, int V>
 __device__ __forceinline__ void write_integers(const LwcArgs& a, const T* w, int row, int g, int l16, bool live, const LwcGroup& p) {
   const IntShape& s = a.s;
   const double inv = 1.0 / p.delta;
   if (a.D) {
     double* d = a.D + (int64_t)row * s.m + (int64_t)g * s.beta;
-    for (int j = l16 * 4; live && j < s.beta; j += 64) {
-      double v[4];
-      load4<T>(w + j, v);
+    for (int j = l16 * V; live && j < s.beta; j += 16 * V) {
+      double v[V];
+      load_weights<T, V>(w + j, v);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) v[i] = p.delta * (fmin(fmax(rint_quotient(v[i], p, inv) + p.z, 0.0), p.Q) - p.z) - v[i];
-      *reinterpret_cast<double2*>(d + j) = make_double2(v[0], v[1]);
-      *reinterpret_cast<double2*>(d + j + 2) = make_double2(v[2], v[3]);
+      for (int i = 0; i < V; ++i) v[i] = p.delta * (fmin(fmax(rint_quotient(v[i], p, inv) + p.z, 0.0), p.Q) - p.z) - v[i];
+      if constexpr (V == 4) {
+        *reinterpret_cast<double2*>(d + j) = make_double2(v[0], v[1]);
+        *reinterpret_cast<double2*>(d + j + 2) = make_double2(v[2], v[3]);
+      } else {
+        d[j] = v[0];
+      }
     }
     return;
   }
+  if constexpr (V != 4) return;                    // (such groups have no integers: a.D is set)
   const double z0 = fmin(fmax(p.z, p.Q - 127.0), 128.0);
   if (l16 == 0) {
     a.S[(int64_t)g * s.npad + row] = live ? p.delta : 0.0;
@@ -126,7 +142,7 @@ __device__ __forceinline__ void write_integers(const LwcArgs& a, const T* w, int
 
 // grid (npad / 16, y): 16 lanes per row, groups blockIdx.y, + gridDim.y, ...: extremes, start values, the digits of W and the
 // first integers
-template <typename T>
+template <typename T, int V>
 __global__ __launch_bounds__(256) void lwc_init(const T* __restrict__ W, LwcArgs a) {
   const IntShape& s = a.s;
   const int lane = threadIdx.x & 63, l16 = lane & 15;
@@ -137,11 +153,11 @@ __global__ __launch_bounds__(256) void lwc_init(const T* __restrict__ W, LwcArgs
   for (int g = blockIdx.y; g < s.k; g += gridDim.y) {
     const T* w = W + (int64_t)min(row, s.n - 1) * a.ldw + (int64_t)g * s.beta;
     double mx = -INFINITY, mn = INFINITY;
-    for (int j = l16 * 4; j < s.beta; j += 64) {
-      double v[4];
-      load4<T>(w + j, v);
+    for (int j = l16 * V; j < s.beta; j += 16 * V) {
+      double v[V];
+      load_weights<T, V>(w + j, v);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
+      for (int i = 0; i < V; ++i) {
         mx = fmax(mx, v[i]);
         mn = fmin(mn, v[i]);
       }
@@ -155,7 +171,7 @@ __global__ __launch_bounds__(256) void lwc_init(const T* __restrict__ W, LwcArgs
       a.gamma[u] = a.betap[u] = a.init;
       a.m1g[u] = a.vg[u] = a.m1b[u] = a.vb[u] = 0.0;
     }
-    for (int j = l16 * 4; !a.D && j < s.nchg * s.chk; j += 64) {
+    for (int j = l16 * 4; V == 4 && !a.D && j < s.nchg * s.chk; j += 64) {
       int c;
       const int64_t dst = operand_offset(s, row, g, j, c);
       double v[4] = {0.0, 0.0, 0.0, 0.0};
@@ -165,7 +181,7 @@ __global__ __launch_bounds__(256) void lwc_init(const T* __restrict__ W, LwcArgs
       store_digits(a.Wd, plane, dst, bits4, wunit, a.mt.w[2 * c], a.mt.w[2 * c + 1]);
     }
     const LwcGroup p = lwc_group(mx, mn, a.init, a.init, min(max((int)a.bits[g], 1), 8));
-    write_integers<T>(a, w, row, g, l16, live, p);
+    write_integers<T, V>(a, w, row, g, l16, live, p);
   }
 }
 
@@ -176,7 +192,7 @@ __device__ __forceinline__ double row_first(double v, int lane) {
 // The (row, group)'s share of the loss and, with TRAIN, the derivatives of its two strengths, their AdamW step, and the
 // integers of the next product.  4096 x 4096 (20 steps 11.6 instead of 42 ms): this pass 78 us, the product 505 us; on the fp64
 // matrix cores the product took 1.9 ms, and the two passes over fp64 copies of W, W_hat - W and D G 0.2 ms.
-template <typename T, bool TRAIN>
+template <typename T, bool TRAIN, int V>
 __global__ __launch_bounds__(256) void lwc_step(const T* __restrict__ W, LwcArgs a) {
   __shared__ double red[16];
   const IntShape& s = a.s;
@@ -194,13 +210,20 @@ __global__ __launch_bounds__(256) void lwc_step(const T* __restrict__ W, LwcArgs
     const LwcGroup p = lwc_group(M, mn, gamma, betap, bits);
     const double inv = 1.0 / p.delta, clipped = p.lo * inv;
     double s1 = 0.0, s2 = 0.0, lsum = 0.0;
-    for (int j = l16 * 4; j < s.beta; j += 64) {
-      double v[4];
-      load4<T>(w + j, v);
-      const double2 d0 = *reinterpret_cast<const double2*>(dgp + j), d1 = *reinterpret_cast<const double2*>(dgp + j + 2);
-      const double dg[4] = {d0.x, d0.y, d1.x, d1.y};
+    for (int j = l16 * V; j < s.beta; j += 16 * V) {
+      double v[V], dg[V];
+      load_weights<T, V>(w + j, v);
+      if constexpr (V == 4) {
+        const double2 d0 = *reinterpret_cast<const double2*>(dgp + j), d1 = *reinterpret_cast<const double2*>(dgp + j + 2);
+        dg[0] = d0.x;
+        dg[1] = d0.y;
+        dg[2] = d1.x;
+        dg[3] = d1.y;
+      } else {
+        dg[0] = dgp[j];
+      }
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
+      for (int i = 0; i < V; ++i) {
         const double un = rint_quotient(v[i], p, inv) + p.z;
         const double q = fmin(fmax(un, 0.0), p.Q);
         const bool inside = (un >= 0.0) && (un <= p.Q);
@@ -234,7 +257,7 @@ __global__ __launch_bounds__(256) void lwc_step(const T* __restrict__ W, LwcArgs
         a.betap[u] = betap;
       }
       const LwcGroup pn = lwc_group(M, mn, row_first(gamma, lane), row_first(betap, lane), bits);
-      write_integers<T>(a, w, row, g, l16, live, pn);
+      write_integers<T, V>(a, w, row, g, l16, live, pn);
     }
   }
   if (l16 == 0) red[slot] = loss;
@@ -248,7 +271,7 @@ __global__ __launch_bounds__(256) void lwc_step(const T* __restrict__ W, LwcArgs
 }
 
 // codes, scale, zero and W_hat with the final strengths
-template <typename T>
+template <typename T, int V>
 __global__ __launch_bounds__(256) void lwc_final(const T* __restrict__ W, LwcArgs a) {
   const IntShape& s = a.s;
   const int lane = threadIdx.x & 63, l16 = lane & 15;
@@ -259,20 +282,23 @@ __global__ __launch_bounds__(256) void lwc_final(const T* __restrict__ W, LwcArg
     const T* w = W + (int64_t)row * a.ldw + (int64_t)g * s.beta;
     const LwcGroup p = lwc_group(a.M[u], a.mn[u], a.gamma[u], a.betap[u], min(max((int)a.bits[g], 1), 8));
     const double inv = 1.0 / p.delta;
-    for (int j = l16 * 4; j < s.beta; j += 64) {
-      double v[4];
-      load4<T>(w + j, v);
+    for (int j = l16 * V; j < s.beta; j += 16 * V) {
+      double v[V];
+      load_weights<T, V>(w + j, v);
       unsigned word = 0;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
+      for (int i = 0; i < V; ++i) {
         const double q = fmin(fmax(rint_quotient(v[i], p, inv) + p.z, 0.0), p.Q);
         word |= (unsigned)q << (8 * i);
         v[i] = p.delta * (q - p.z);
       }
-      *reinterpret_cast<unsigned*>(a.codes + base + j) = word;
+      if constexpr (V == 4)
+        *reinterpret_cast<unsigned*>(a.codes + base + j) = word;
+      else
+        a.codes[base + j] = (uint8_t)word;
       if (a.What) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < V; ++i) {
           if (a.what_f64)
             static_cast<double*>(a.What)[base + j + i] = v[i];
           else
@@ -310,10 +336,11 @@ size_t lwc_layout(int n, int m, int beta, int steps, char* base, LwcWorkspace& w
     return p;
   };
   auto doubles = [&](size_t count) { return reinterpret_cast<double*>(take(sizeof(double) * count)); };
-  w.Xd = take(std::max(slim_int_digits_bytes(s), sizeof(double) * (size_t)m * m));      // digits of G, or G in fp64
-  w.Wd = take((size_t)SI_MAXD * w.plane);
-  w.Q = take((size_t)w.plane);
-  w.SX = doubles((size_t)s.k * s.tpad);
+  const bool ints = beta % 4 == 0;       // (else the fp64 form)
+  w.Xd = take(std::max(ints ? slim_int_digits_bytes(s) : 0, sizeof(double) * (size_t)m * m));      // digits of G, or G in fp64
+  w.Wd = take(ints ? (size_t)SI_MAXD * w.plane : 0);
+  w.Q = take(ints ? (size_t)w.plane : 0);
+  w.SX = doubles(ints ? (size_t)s.k * s.tpad : 0);
   w.WG = doubles((size_t)n * m);
   w.DG = doubles((size_t)n * m);
   w.lp = doubles((size_t)w.blocks_x * w.blocks_y);
@@ -334,11 +361,11 @@ size_t lwc_layout(int n, int m, int beta, int steps, char* base, LwcWorkspace& w
   return off;
 }
 
-template <typename T>
-slim_status lwc_run(slim_ctx* ctx, const LwcWorkspace& w, const T* W, LwcArgs& a, OutArgs& oa, const slim_gemm_desc& wide,
+template <typename T, int V>
+slim_status lwc_run_v(slim_ctx* ctx, const LwcWorkspace& w, const T* W, LwcArgs& a, OutArgs& oa, const slim_gemm_desc& wide,
                     int steps, double beta1, double beta2) {
   const dim3 grid(w.blocks_x, w.blocks_y), block(256);
-  SLIM_LAUNCH(ctx, "lwc_init", lwc_init<T>, grid, block, 0, W, a);
+  SLIM_LAUNCH(ctx, "lwc_init", (lwc_init<T, V>), grid, block, 0, W, a);
   oa.Q = w.Wd;
   oa.Y = w.WG;
   oa.sub = nullptr;
@@ -356,15 +383,21 @@ slim_status lwc_run(slim_ctx* ctx, const LwcWorkspace& w, const T* W, LwcArgs& a
       a.c1 = 1.0 - std::pow(beta1, (double)it);
       a.c2 = 1.0 - std::pow(beta2, (double)it);
       a.step = it + 1;
-      SLIM_LAUNCH(ctx, "lwc_step", (lwc_step<T, true>), grid, block, 0, W, a);
+      SLIM_LAUNCH(ctx, "lwc_step", (lwc_step<T, true, V>), grid, block, 0, W, a);
     } else {
-      SLIM_LAUNCH(ctx, "lwc_loss", (lwc_step<T, false>), grid, block, 0, W, a);
+      SLIM_LAUNCH(ctx, "lwc_loss", (lwc_step<T, false, V>), grid, block, 0, W, a);
     }
     st = slim_sum_f64(ctx, "lwc_loss_sum", w.lp, w.blocks_x * w.blocks_y, w.loss + (it - 1));
     if (st != SLIM_OK) return st;
   }
-  SLIM_LAUNCH(ctx, "lwc_final", lwc_final<T>, grid, block, 0, W, a);
+  SLIM_LAUNCH(ctx, "lwc_final", (lwc_final<T, V>), grid, block, 0, W, a);
   return SLIM_OK;
+}
+template <typename T>
+slim_status lwc_run(slim_ctx* ctx, const LwcWorkspace& w, const T* W, LwcArgs& a, OutArgs& oa, const slim_gemm_desc& wide,
+                    int steps, double beta1, double beta2) {
+  return a.s.beta % 4 == 0 ? lwc_run_v<T, 4>(ctx, w, W, a, oa, wide, steps, beta1, beta2)
+                           : lwc_run_v<T, 1>(ctx, w, W, a, oa, wide, steps, beta1, beta2);
 }
 
 }  // namespace
@@ -406,7 +439,7 @@ extern "C" slim_status slim_lwc_quantize(slim_ctx* ctx, const void* W, slim_dtyp
   if (st != SLIM_OK) return st;
   LwcWorkspace w;
   lwc_layout(n, m, beta, steps, ctx->ws, w);
-  bool wide = false;
+  bool wide = beta % 4 != 0;
   for (int g = 0; g < k; ++g) wide = wide || bits_h[g] > 5;
   slim_gemm_desc d;
   d.A = w.WG;

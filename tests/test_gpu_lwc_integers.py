@@ -45,3 +45,37 @@ def test_lwc_against_the_oracle(slim, n, m, beta, dtype, outlier, widths):
     assert np.array_equal(out["zero"].cpu().numpy()[ok], ref["zero"][ok])
     again = slim.lwc_quantize(W.cuda(), G.cuda(), 2 * m, torch.from_numpy(bits).cuda(), beta, steps=steps)
     assert np.array_equal(again["loss_curve"], out["loss_curve"]) and torch.equal(again["codes"], out["codes"])
+
+
+@pytest.mark.parametrize("n,m,beta,dtype,widths", [
+    (3, 12, 6, torch.float16, (2, 3)), (17, 36, 1, torch.float32, (1, 2)), (18, 100, 2, torch.bfloat16, (2,)),
+    (5, 132, 33, torch.float16, (3, 8)), (40, 2052, 18, torch.float32, (2, 5)), (16, 60, 5, torch.bfloat16, (4, 2))])
+def test_groups_that_four_does_not_divide(slim, n, m, beta, dtype, widths):
+    """A group takes in no weight of its neighbour, and nothing is written behind the last row."""
+    g = torch.Generator().manual_seed(n * m)
+    W = (torch.randn((n, m), generator=g) * 0.05).to(dtype)
+    X = torch.randn((m, 2 * m), generator=g, dtype=torch.float64)
+    G = (X @ X.t()).to(torch.float32)
+    k, steps = m // beta, 5
+    bits = np.array((list(widths) * k)[:k], dtype=np.uint8)
+    ref = orc.lwc_quantize(W.double().numpy(), G.double().numpy(), 2 * m, bits, beta, steps=steps)
+    Wd, Gd, bd = W.cuda(), G.cuda(), torch.from_numpy(bits).cuda()
+    out = slim.lwc_quantize(Wd, Gd, 2 * m, bd, beta, steps=steps)
+    assert np.allclose(out["loss_curve"], ref["loss_curve"], rtol=1e-9)
+    ok = ref["round_margin"].min(axis=1) > 1e-6
+    assert ok.mean() > 0.7
+    assert np.array_equal(out["codes"].cpu().numpy()[ok], ref["codes"][ok])
+    assert np.allclose(out["scale"].cpu().numpy(), ref["scale"], rtol=1e-9)
+    assert np.array_equal(out["zero"].cpu().numpy()[ok], ref["zero"][ok])
+    # the entry point itself, with guards behind its outputs
+    codes = torch.full((n * m + 64,), 0xA5, dtype=torch.uint8, device="cuda")
+    what = torch.full((n * m + 64,), -7.0, dtype=torch.float64, device="cuda")
+    scale, zero = torch.empty((n, k), dtype=torch.float64, device="cuda"), torch.empty((n, k), dtype=torch.float64, device="cuda")
+    ptr = binding._ptr
+    slim._check(slim.lib.slim_lwc_quantize(slim.ctx, ptr(Wd), binding._DT[dtype], n, m, m, ptr(Gd), m, 2 * m, ptr(bd), beta, steps,
+                                           1e-2, 0.9, 0.999, 1e-8, 4.0, ptr(codes), ptr(scale), ptr(zero), ptr(what),
+                                           binding._DT[torch.float64], None))
+    assert torch.equal(codes[: n * m].view(n, m), out["codes"]) and bool((codes[n * m:] == 0xA5).all())
+    assert bool((what[n * m:] == -7.0).all())
+    expect = (codes[: n * m].view(n, k, beta).double() - zero[:, :, None]) * scale[:, :, None]
+    assert torch.equal(what[: n * m].view(n, k, beta), expect)
