@@ -316,9 +316,9 @@ slim_status slim_dequant_matmul_zp(slim_ctx* ctx, const uint32_t* packed, int64_
  *   loss_curve   host, steps + 1 doubles or NULL: the loss before every step and after the last; NULL: the call does
  *          not wait for its own work
  *   beta   any divisor of m (m, ldw and ldg multiples of 4)
- * All arithmetic is fp64 or exact integers (widths up to 5: W_hat G from integers; wider, and group sizes that 4 does not
- * divide: (W_hat - W) G on the fp64 matrix cores); a step
- * costs one n x m x m product and one pass over W.
+ * All arithmetic is fp64 or exact integers: W_hat G and W G from integers, both summed to twice the precision of fp64 (their
+ * difference loses nothing that fp64 would hold), or, for group sizes that 4 does not divide, (W_hat - W) G on the fp64
+ * matrix cores; a step costs one n x m x m product and one pass over W.
  */
 slim_status slim_lwc_quantize(slim_ctx* ctx, const void* W, slim_dtype w_dtype, int n, int m, int64_t ldw,
                               const float* G, int64_t ldg, int64_t n_tokens, const uint8_t* bits, int beta, int steps,

@@ -42,7 +42,8 @@ struct IntShape {
 struct IntMeta {
   int* x;                          // 2 C (x 2 TB with digits per token block): lowest digit in use and digits in use
   int* w;                          // 2 C: the same of the weights' digits
-  int* unit;                       // unit[0], unit[1]: exponents of the units of X_s and W; unit[2]: non-finite inputs seen
+  int* unit;                       // unit[0], unit[1]: exponents of the units of X_s and W; unit[2]: non-finite inputs seen;
+                                   // unit[3]: every |W| is below 2^unit[3]
   unsigned* xmax;                  // C largest |x| as float bits, C smallest exponent of a last digit (as int); then W's
   int* xlsb;
   unsigned* wmax;
@@ -203,6 +204,18 @@ __device__ __forceinline__ void add_scaled(double (&y)[R][16], const v16i (&acc)
   }
 }
 
+// The same for sums of which the difference of two is wanted: what an addition rounds away is kept in lo.  y starts from a
+// constant above every partial sum (sum_base), so y - y' is exact and lo holds f a - (y' - y) to its own last digits.
+__device__ __forceinline__ void add_compensated(double& y, double& lo, double f, double a) {
+  const double s = fma(f, a, y);
+  lo += fma(f, a, y - s);
+  y = s;
+}
+
+// 1.5 * 2^e, e two above any partial sum of a row's integers times scale (times a token's digits, below 2^54 units): with
+// wexp the exponent above the largest weight, and W_hat and the parts it is summed from within 2^9 of that.
+__device__ __forceinline__ double sum_base(int m, int wexp) { return ldexp(1.5, 54 + (32 - __builtin_clz(m)) + 9 + 2 + wexp); }
+
 __device__ __forceinline__ void lds_load16(unsigned lds_addr, unsigned voff, const char* gbase) {
 #if defined(__HIP_DEVICE_COMPILE__)
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds_addr), "v"(voff), "s"(gbase) : "m0");
@@ -242,6 +255,7 @@ struct OutArgs {
   int mstride_c, mstride_t;        // of mt.x: entries between two chunks and between two token blocks
   const char* Xd;
   const double* SX;                // k x tpad: sums of the group's channels of a token, in units
+  const double* SXlo;              // what their rounding leaves (compensated sums)
   const char* Q;                   // codes, or digits of W with planes `plane` bytes apart
   int64_t plane;
   const double* S;                 // k x npad scales of the codes
@@ -249,8 +263,10 @@ struct OutArgs {
   const int* rest;                 // k: rest[g] >= rest_from: some row of the group has such a part
   int rest_from;
   const int* token_unit;           // exponent of each token's unit (INT_MIN: not finite), or nullptr: unit[0] for all
-  const double* sub;               // n x ts to subtract from the result, or nullptr
   double* Y;                       // n x ts
+  // compensated sums:
+  double* Ylo;                     // n x ts: what Y's rounding leaves (REF)
+  const double *sub, *sublo;       // n x ts: subtracted from the result
 };
 
 }  // namespace slimint
@@ -268,8 +284,9 @@ slim_status slim_int_x_digits(slim_ctx* ctx, const slimint::IntShape& s, const s
                               char* Xd, double* SX);
 // The digits of a fp32 matrix with a unit per token (column): token_unit[ts]; work: 2 ts ints.  mt.x then has 2 C TB entries.
 slim_status slim_int_g_digits(slim_ctx* ctx, const slimint::IntShape& s, const slimint::IntMeta& mt, const float* G, int64_t ldg,
-                              int* work, int* token_unit, char* Xd, double* SX);
-// Y = W X (ref: from the digits of W) or W_hat X (from codes and scales)
-slim_status slim_int_outputs(slim_ctx* ctx, const char* name, const slimint::OutArgs& a, bool ref);
+                              int* work, int* token_unit, char* Xd, double* SX, double* SXlo);
+// Y = W X (ref: from the digits of W) or W_hat X (from codes and scales); `compensated`: Y and Ylo = W X to twice the
+// precision, or W_hat X minus (sub, sublo)
+slim_status slim_int_outputs(slim_ctx* ctx, const char* name, const slimint::OutArgs& a, bool ref, bool compensated);
 
 #endif

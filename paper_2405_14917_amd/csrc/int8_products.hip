@@ -123,13 +123,16 @@ __global__ __launch_bounds__(256) void int_meta(IntMeta mt, int C, int which) {
   }
   mx = smx[0];
   lsb = slsb[0];
-  unsigned mant;
-  int e0, unit = 0;
+  unsigned mant = 0;
+  int e0 = 0, unit = 0;
   if (mx) {
     split_float(mx, mant, e0);
     unit = max(lsb, e0 + (31 - __builtin_clz(mant)) - 53);
   }
-  if (threadIdx.x == 0) mt.unit[which] = unit;
+  if (threadIdx.x == 0) {
+    mt.unit[which] = unit;
+    if (which) mt.unit[3] = mx ? e0 + 32 - __builtin_clz(mant) : 0;
+  }
   for (int c = threadIdx.x; c < C; c += 256) {
     int lo = 0, hi = 0;
     if (cmax[c]) {
@@ -236,7 +239,8 @@ __global__ __launch_bounds__(256) void int_g_units(int64_t ts, const int* __rest
 
 // grid (ceil(TB / 4), k): a wavefront finds the digits in use of 32 columns of every chunk of one group, and cuts them
 __global__ __launch_bounds__(256) void int_g_digits(const float* __restrict__ G, int64_t ldg, IntShape s, int* __restrict__ meta,
-                                                    const int* __restrict__ token_unit, char* __restrict__ Xd, double* __restrict__ SX) {
+                                                    const int* __restrict__ token_unit, char* __restrict__ Xd, double* __restrict__ SX,
+                                                    double* __restrict__ SXlo) {
   const int lane = threadIdx.x & 63, l32 = lane & 31, h = lane >> 5;
   const int tb = blockIdx.x * 4 + (threadIdx.x >> 6), g = blockIdx.y;
   if (tb >= s.TB) return;
@@ -247,10 +251,11 @@ __global__ __launch_bounds__(256) void int_g_digits(const float* __restrict__ G,
     if (j >= s.beta || unit == INT_MIN) return 0;
     return fixed_point(__float_as_uint(G[(int64_t)(g * s.beta + j) * ldg + t]), unit);
   };
-  double sum = 0.0;
+  double sum = 0.0, sumlo = 0.0;
   for (int cc = 0; cc < s.nchg; ++cc) {
     const int c = g * s.nchg + cc;
     uint64_t mx = 0, any = 0;
+    int64_t csum = 0;                      // of this chunk: at most 64 channels of 54 bits
     for (int f = 0; f < s.ks; ++f)
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
@@ -282,7 +287,7 @@ __global__ __launch_bounds__(256) void int_g_digits(const float* __restrict__ G,
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
         const int64_t v = value(cc * s.chk + f * 32 + h * 16 + i);
-        sum += (double)v;
+        csum += v;
         u[i] = digit_bytes(v) >> (8 * lo);
       }
       for (int d = 0; d < nd; ++d) {
@@ -299,23 +304,34 @@ __global__ __launch_bounds__(256) void int_g_digits(const float* __restrict__ G,
         *reinterpret_cast<uint4*>(dst + ((int64_t)d * s.ks + f) * 1024) = make_uint4(w[0], w[1], w[2], w[3]);
       }
     }
+    // both halves of the wavefront's channels, as a double and what it leaves; then two-sum with the chunks before
+    csum += (int64_t)(((uint64_t)(unsigned)__shfl_xor((int)(csum >> 32), 32, WAVE) << 32) | (unsigned)__shfl_xor((int)csum, 32, WAVE));
+    const double c_hi = (double)csum, c_lo = (double)(csum - (int64_t)c_hi);
+    const double both = sum + c_hi, part = both - sum;
+    sumlo += ((sum - (both - part)) + (c_hi - part)) + c_lo;
+    sum = both;
   }
-  sum += __shfl_xor(sum, 32, WAVE);
-  if (h == 0) SX[(int64_t)g * s.tpad + t] = sum;
+  if (h == 0) {
+    SX[(int64_t)g * s.tpad + t] = sum;
+    SXlo[(int64_t)g * s.tpad + t] = sumlo;
+  }
 }
 
-// REF: Y = W X_s from the digits of W; else Y = W_N X_s
-template <int KS, bool REF>
-__global__ __launch_bounds__(256, 3) void int_outputs(OutArgs a) {
-  constexpr int R = 2, NW = 4;
+// REF: Y = W X_s from the digits of W; else Y = W_N X_s.
+// COMP: sums to twice the precision, for W_hat X - W X (add_compensated).  Four vector instructions per output and pair of
+// digits in place of one, and twice the registers, so one tile per wavefront and four wavefronts per SIMD: 4096 x 4096 against
+// 4096 columns 507 -> 692 us (two tiles and two wavefronts 714, one and three 766).
+template <int KS, bool REF, bool COMP>
+__global__ __launch_bounds__(256, COMP ? 4 : 3) void int_outputs(OutArgs a) {
+  constexpr int R = COMP ? 1 : 2, NW = 4;
   using TL = Tile<KS, R>;
   extern __shared__ __align__(16) char si_smem[];
   const IntShape& s = a.s;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, h = lane >> 5;
   int rt, tb;
-  tile_of(blockIdx.x, s.RT, s.TB, rt, tb);
-  const int row0 = rt * SI_ROWS + wave * 64;
+  tile_of(blockIdx.x, s.npad / (128 * R), s.TB, rt, tb);
+  const int row0 = rt * 128 * R + wave * 32 * R;
   const unsigned lds0 = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(uintptr_t)((__attribute__((address_space(3))) char*)si_smem));
   const int64_t rstride = (int64_t)s.C * KS * 1024;
   const char* q0 = a.Q + (int64_t)(row0 >> 5) * rstride;
@@ -331,11 +347,15 @@ __global__ __launch_bounds__(256, 3) void int_outputs(OutArgs a) {
   __syncthreads();
   auto chunk_info = [&](int c) { return __builtin_amdgcn_readfirstlane(c < SI_TAB ? tab[c] : describe(c)); };
 
-  double y[R][16];
+  const double base = COMP ? sum_base(s.m, a.mt.unit[3]) : 0.0;
+  double y[R][16], low[COMP ? R : 1][16];
 #pragma unroll
   for (int r = 0; r < R; ++r)
 #pragma unroll
-    for (int v = 0; v < 16; ++v) y[r][v] = 0.0;
+    for (int v = 0; v < 16; ++v) {
+      y[r][v] = base;
+      low[COMP ? r : 0][v] = 0.0;
+    }
   TL tl;
   auto load_first = [&](int c) {                // the first (or only) set of chunk c
     tl.load_codes(q0 + (int64_t)c * KS * 1024, rstride, lane16);
@@ -375,7 +395,17 @@ __global__ __launch_bounds__(256, 3) void int_outputs(OutArgs a) {
           else
             load_first(stage_chunk(next));
         }
-        add_scaled<R>(y, acc, sc, unit + 8 * (lo + 2 * p) + (REF ? 8 * (wlo + j) : 0));
+        const int e = unit + 8 * (lo + 2 * p) + (REF ? 8 * (wlo + j) : 0);
+        if constexpr (COMP) {
+#pragma unroll
+          for (int r = 0; r < R; ++r) {
+            const double f = ldexp(sc[r], e);
+#pragma unroll
+            for (int v = 0; v < 16; ++v) add_compensated(y[r][v], low[r][v], f, (double)acc[r][v]);
+          }
+        } else {
+          add_scaled<R>(y, acc, sc, e);
+        }
       }
     }
     const int g = c / s.nchg;
@@ -386,7 +416,14 @@ __global__ __launch_bounds__(256, 3) void int_outputs(OutArgs a) {
       for (int v = 0; v < 16; ++v) {
         const double sx = ldexp(a.SX[(int64_t)g * s.tpad + tb * 32 + 8 * (v >> 2) + 4 * h + (v & 3)], unit);
 #pragma unroll
-        for (int r = 0; r < R; ++r) y[r][v] = fma(-Rz[32 * r], sx, y[r][v]);
+        for (int r = 0; r < R; ++r) {
+          if constexpr (COMP) {
+            add_compensated(y[r][v], low[r][v], -Rz[32 * r], sx);
+            low[r][v] = fma(-Rz[32 * r], a.SXlo[(int64_t)g * s.tpad + tb * 32 + 8 * (v >> 2) + 4 * h + (v & 3)], low[r][v]);
+          } else {
+            y[r][v] = fma(-Rz[32 * r], sx, y[r][v]);
+          }
+        }
       }
     }
     if (done) break;
@@ -407,12 +444,21 @@ __global__ __launch_bounds__(256, 3) void int_outputs(OutArgs a) {
     for (int r = 0; r < R; ++r) {
       const int row = row0 + 32 * r + l32;
       if (row >= s.n) continue;
-      double o[4];
+      double o[4], ol[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
-        o[v] = y[r][4 * q + v];
+        o[v] = COMP ? y[r][4 * q + v] - base : y[r][4 * q + v];
         if (a.token_unit) o[v] = tu[v] == INT_MIN ? NAN : ldexp(o[v], tu[v]);
-        if (a.sub) o[v] -= a.sub[(int64_t)row * s.ts + t + v];
+        if constexpr (COMP) {
+          const int64_t at = (int64_t)row * s.ts + t + v;
+          ol[v] = ldexp(low[r][4 * q + v], tu[v] == INT_MIN ? 0 : tu[v]);
+          if (!REF) o[v] = (o[v] - a.sub[at]) + (ol[v] - a.sublo[at]);
+        }
+      }
+      if constexpr (COMP && REF) {
+        double* outlo = a.Ylo + (int64_t)row * s.ts + t;
+        *reinterpret_cast<double2*>(outlo) = make_double2(ol[0], ol[1]);
+        *reinterpret_cast<double2*>(outlo + 2) = make_double2(ol[2], ol[3]);
       }
       double* out = a.Y + (int64_t)row * s.ts + t;
       *reinterpret_cast<double2*>(out) = make_double2(o[0], o[1]);
@@ -422,13 +468,20 @@ __global__ __launch_bounds__(256, 3) void int_outputs(OutArgs a) {
 }
 
 template <int KS>
-slim_status outputs_launch(slim_ctx* ctx, const char* name, const OutArgs& a, bool ref) {
-  const dim3 grid(a.s.RT * a.s.TB);
+slim_status outputs_launch(slim_ctx* ctx, const char* name, const OutArgs& a, bool ref, bool compensated) {
+  const dim3 grid((compensated ? 2 * a.s.RT : a.s.RT) * a.s.TB);
   const size_t smem = 2 * Tile<KS, 2>::STAGE + sizeof(int) * std::min(a.s.C, SI_TAB);
-  if (ref)
-    SLIM_LAUNCH(ctx, name, (int_outputs<KS, true>), grid, dim3(256), smem, a);
-  else
-    SLIM_LAUNCH(ctx, name, (int_outputs<KS, false>), grid, dim3(256), smem, a);
+  if (compensated) {
+    if (ref)
+      SLIM_LAUNCH(ctx, name, (int_outputs<KS, true, true>), grid, dim3(256), smem, a);
+    else
+      SLIM_LAUNCH(ctx, name, (int_outputs<KS, false, true>), grid, dim3(256), smem, a);
+  } else {
+    if (ref)
+      SLIM_LAUNCH(ctx, name, (int_outputs<KS, true, false>), grid, dim3(256), smem, a);
+    else
+      SLIM_LAUNCH(ctx, name, (int_outputs<KS, false, false>), grid, dim3(256), smem, a);
+  }
   return SLIM_OK;
 }
 
@@ -493,14 +546,16 @@ slim_status slim_int_x_digits(slim_ctx* ctx, const IntShape& s, const IntMeta& m
                         : x_digits(ctx, s, mt, static_cast<const __hip_bfloat16*>(X), ldx, Xd, SX);
 }
 slim_status slim_int_g_digits(slim_ctx* ctx, const IntShape& s, const IntMeta& mt, const float* G, int64_t ldg, int* work, int* token_unit,
-                              char* Xd, double* SX) {
+                              char* Xd, double* SX, double* SXlo) {
   const dim3 tgrid(slim_cdiv(s.ts, 256)), block(256);
   SLIM_LAUNCH(ctx, "int_g_clear", int_g_clear, tgrid, block, 0, s.ts, work);
   SLIM_LAUNCH(ctx, "int_g_stats", int_g_stats, dim3(slim_cdiv(s.ts, 1024), std::min(s.m, 128)), block, 0, G, ldg, s, work);
   SLIM_LAUNCH(ctx, "int_g_units", int_g_units, tgrid, block, 0, s.ts, work, token_unit);
-  SLIM_LAUNCH(ctx, "int_g_digits", int_g_digits, dim3(slim_cdiv(s.TB, 4), s.k), block, 0, G, ldg, s, mt.x, token_unit, Xd, SX);
+  SLIM_LAUNCH(ctx, "int_g_digits", int_g_digits, dim3(slim_cdiv(s.TB, 4), s.k), block, 0, G, ldg, s, mt.x, token_unit, Xd, SX, SXlo);
   return SLIM_OK;
 }
-slim_status slim_int_outputs(slim_ctx* ctx, const char* name, const OutArgs& a, bool ref) {
-  return a.s.ks == 1 ? outputs_launch<1>(ctx, name, a, ref) : a.s.ks == 2 ? outputs_launch<2>(ctx, name, a, ref) : outputs_launch<4>(ctx, name, a, ref);
+slim_status slim_int_outputs(slim_ctx* ctx, const char* name, const OutArgs& a, bool ref, bool compensated) {
+  return a.s.ks == 1   ? outputs_launch<1>(ctx, name, a, ref, compensated)
+         : a.s.ks == 2 ? outputs_launch<2>(ctx, name, a, ref, compensated)
+                       : outputs_launch<4>(ctx, name, a, ref, compensated);
 }

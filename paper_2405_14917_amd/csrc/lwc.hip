@@ -13,14 +13,17 @@
 //     dW_hat_j / d lo at fixed delta = 0   or, clipped,   1
 // Everything is fp64.  D G = W_hat G - W G with W_hat = delta (q - z): the first product is one of small integers with G's
 // digits (int8_products.h, a unit per column of G, which G's fp32 entries fit exactly unless they are 2^-30 of their column's
-// largest), the second one does not change and is taken once, from the digits of W.  Two kernels per step: the product,
-// and one pass over W and D G that forms the derivatives, takes the AdamW step and writes the next step's integers, 16
-// lanes per (row, group), fixed-order reductions.
-// The difference of the two products loses the digits that W_hat and W share: none that matter at two to five bits (loss
-// curves within 2e-16 of the float64 oracle's either way), but at eight bits with outlier channels 1e-14 instead of 2e-15.
-// Layers with a group of more than five bits therefore multiply W_hat - W itself, on the fp64 matrix cores.  So do those whose
-// group size 4 does not divide: the passes over W then take one channel per lane in place of four (V), since four would
-// reach into the next group, and the integers' operand order has no place for such a group.
+// largest: those are rounded by 2^-54 of it, as one addition to the fp64 sum would), the second one does not change and is
+// taken once, from the digits of W.  Two kernels per step: the product, and one pass over W and D G that forms the
+// derivatives, takes the AdamW step and writes the next step's integers, 16 lanes per (row, group), fixed-order reductions.
+// The difference of the two products loses the digits that W_hat and W share, so both are summed to twice the precision.
+// Relative error of D G on rows of 1024 channels with outlier channels (model of either form's roundings against exact sums):
+// 5e-17 at every width and for weights of one sign, group sizes 32 to 256.  (W_hat - W) G on the fp64 matrix cores, which
+// round after every four channels: 4e-16 at two bits, 1e-15 at four and five, 4e-15 at eight; the two products in plain fp64
+// sums: 4e-16, 1.6e-15, 2.6e-15 and 1e-14.
+// Group sizes that 4 does not divide multiply W_hat - W on the fp64 matrix cores: the integers' operand order has no place
+// for them, and the passes over W then take one channel per lane in place of four (V), since four would reach into the next
+// group.
 // What bounds it: the vector work behind the MFMAs of the product (figures at lwc_step).
 #include <cmath>
 
@@ -63,7 +66,7 @@ struct LwcArgs {
   double *S, *Rz;         // k x npad: their scales, and the scale times what the zero has beyond the integers
   int* rest;              // k: last step at which some row of the group had such a part
   char* Wd;               // digits of W
-  double* D;              // n x m: W_hat - W in place of the integers (layers with wide groups), else nullptr
+  double* D;              // n x m: W_hat - W in place of the integers (group sizes that 4 does not divide), else nullptr
   const double* DG;       // n x m: D G
   double* lp;             // the workgroups' sums of D_j (D G)_j
   double gscale;          // 2 / (n T)
@@ -190,7 +193,7 @@ __device__ __forceinline__ double row_first(double v, int lane) {
 }
 
 // The (row, group)'s share of the loss and, with TRAIN, the derivatives of its two strengths, their AdamW step, and the
-// integers of the next product.  4096 x 4096 (20 steps 11.6 instead of 42 ms): this pass 78 us, the product 505 us; on the fp64
+// integers of the next product.  4096 x 4096 (20 steps 16 instead of 42 ms): this pass 78 us, the product 690 us; on the fp64
 // matrix cores the product took 1.9 ms, and the two passes over fp64 copies of W, W_hat - W and D G 0.2 ms.
 template <typename T, bool TRAIN, int V>
 __global__ __launch_bounds__(256) void lwc_step(const T* __restrict__ W, LwcArgs a) {
@@ -319,7 +322,7 @@ struct LwcWorkspace {
   int64_t plane;
   int blocks_x, blocks_y;
   char *Xd, *Wd, *Q;
-  double *SX, *WG, *DG, *lp, *loss;
+  double *SX, *SXlo, *WG, *WGlo, *DG, *lp, *loss;
   double* par[10];
   int *rest, *work, *token_unit;
 };
@@ -341,7 +344,9 @@ size_t lwc_layout(int n, int m, int beta, int steps, char* base, LwcWorkspace& w
   w.Wd = take(ints ? (size_t)SI_MAXD * w.plane : 0);
   w.Q = take(ints ? (size_t)w.plane : 0);
   w.SX = doubles(ints ? (size_t)s.k * s.tpad : 0);
+  w.SXlo = doubles(ints ? (size_t)s.k * s.tpad : 0);
   w.WG = doubles((size_t)n * m);
+  w.WGlo = doubles(ints ? (size_t)n * m : 0);
   w.DG = doubles((size_t)n * m);
   w.lp = doubles((size_t)w.blocks_x * w.blocks_y);
   w.loss = doubles((size_t)steps + 1);
@@ -368,16 +373,19 @@ slim_status lwc_run_v(slim_ctx* ctx, const LwcWorkspace& w, const T* W, LwcArgs&
   SLIM_LAUNCH(ctx, "lwc_init", (lwc_init<T, V>), grid, block, 0, W, a);
   oa.Q = w.Wd;
   oa.Y = w.WG;
-  oa.sub = nullptr;
+  oa.Ylo = w.WGlo;
+  oa.sub = oa.sublo = nullptr;
   slim_status st = SLIM_OK;
-  if (!a.D) st = slim_int_outputs(ctx, "lwc_wg_product", oa, true);
+  if (!a.D) st = slim_int_outputs(ctx, "lwc_wg_product", oa, true, true);
   if (st != SLIM_OK) return st;
   oa.Q = w.Q;
   oa.Y = w.DG;
+  oa.Ylo = nullptr;
   oa.sub = w.WG;
+  oa.sublo = w.WGlo;
   for (int it = 1; it <= steps + 1; ++it) {
     oa.rest_from = it;
-    st = a.D ? slim_dgemm(ctx, "lwc_grad_dgemm", 0, wide) : slim_int_outputs(ctx, "lwc_grad_product", oa, false);
+    st = a.D ? slim_dgemm(ctx, "lwc_grad_dgemm", 0, wide) : slim_int_outputs(ctx, "lwc_grad_product", oa, false, true);
     if (st != SLIM_OK) return st;
     if (it <= steps) {
       a.c1 = 1.0 - std::pow(beta1, (double)it);
@@ -439,8 +447,7 @@ extern "C" slim_status slim_lwc_quantize(slim_ctx* ctx, const void* W, slim_dtyp
   if (st != SLIM_OK) return st;
   LwcWorkspace w;
   lwc_layout(n, m, beta, steps, ctx->ws, w);
-  bool wide = beta % 4 != 0;
-  for (int g = 0; g < k; ++g) wide = wide || bits_h[g] > 5;
+  const bool wide = beta % 4 != 0;
   slim_gemm_desc d;
   d.A = w.WG;
   d.lda = m;
@@ -462,7 +469,7 @@ extern "C" slim_status slim_lwc_quantize(slim_ctx* ctx, const void* W, slim_dtyp
     st = slim_int_clear(ctx, w.s, w.mt, w.rest, w.s.k);
     if (st == SLIM_OK) st = slim_int_w_stats(ctx, w.s, w.mt, W, w_dtype, ldw);
     if (st == SLIM_OK) st = slim_int_weight_meta(ctx, w.s, w.mt);
-    if (st == SLIM_OK) st = slim_int_g_digits(ctx, w.s, w.mt, G, ldg, w.work, w.token_unit, w.Xd, w.SX);
+    if (st == SLIM_OK) st = slim_int_g_digits(ctx, w.s, w.mt, G, ldg, w.work, w.token_unit, w.Xd, w.SX, w.SXlo);
   }
   if (st != SLIM_OK) return st;
 
@@ -507,6 +514,7 @@ extern "C" slim_status slim_lwc_quantize(slim_ctx* ctx, const void* W, slim_dtyp
   oa.mstride_t = 1;
   oa.Xd = w.Xd;
   oa.SX = w.SX;
+  oa.SXlo = w.SXlo;
   oa.plane = w.plane;
   oa.S = a.S;
   oa.Rz = a.Rz;

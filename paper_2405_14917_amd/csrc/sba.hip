@@ -689,19 +689,21 @@ slim_status sba_rank_independent(slim_ctx* ctx, const SbaWorkspace& w, const voi
   oa.rest = w.rest_n;
   oa.rest_from = 1;
   oa.token_unit = nullptr;
-  oa.sub = nullptr;
+  oa.Ylo = nullptr;
+  oa.sub = oa.sublo = nullptr;
   oa.Xd = w.Xd;
   oa.SX = w.SX;
+  oa.SXlo = nullptr;
   oa.Q = w.Wd;
   oa.plane = w.plane;
   oa.S = w.Sn;
   oa.Rz = w.Rn;
   oa.Y = w.Yt;
-  st = slim_int_outputs(ctx, "sba_reference_outputs", oa, true);
+  st = slim_int_outputs(ctx, "sba_reference_outputs", oa, true, false);
   if (st != SLIM_OK) return st;
   oa.Q = w.Qn;
   oa.Y = w.Yc;
-  st = slim_int_outputs(ctx, "sba_outputs", oa, false);
+  st = slim_int_outputs(ctx, "sba_outputs", oa, false, false);
   if (st != SLIM_OK) return st;
   if (objective == SLIM_OBJ_KL) {
     // reference side once: per-token maximum and log-sum-exp, then Y^T becomes P = softmax over the outputs
