@@ -122,7 +122,7 @@ __device__ __forceinline__ void write_integers(const LwcArgs& a, const T* w, int
   if constexpr (V != 4) return;                    // (such groups have no integers: a.D is set)
   const double z0 = fmin(fmax(p.z, p.Q - 127.0), 128.0);
   if (l16 == 0) {
-    a.S[(int64_t)g * s.npad + row] = live ? p.delta : 0.0;
+    a.S[(int64_t)g * s.npad + row] = live ? p.delta + (p.M - p.m_) * 0.0 : 0.0;      // (infinite weights: not a number)
     a.Rz[(int64_t)g * s.npad + row] = live ? p.delta * (p.z - z0) : 0.0;
     if (live && p.z != z0) atomicMax(&a.rest[g], a.step);
   }
@@ -155,7 +155,7 @@ __global__ __launch_bounds__(256) void lwc_init(const T* __restrict__ W, LwcArgs
   const int wunit = a.mt.unit[1];
   for (int g = blockIdx.y; g < s.k; g += gridDim.y) {
     const T* w = W + (int64_t)min(row, s.n - 1) * a.ldw + (int64_t)g * s.beta;
-    double mx = -INFINITY, mn = INFINITY;
+    double mx = -INFINITY, mn = INFINITY, none = 0.0;
     for (int j = l16 * V; j < s.beta; j += 16 * V) {
       double v[V];
       load_weights<T, V>(w + j, v);
@@ -163,10 +163,12 @@ __global__ __launch_bounds__(256) void lwc_init(const T* __restrict__ W, LwcArgs
       for (int i = 0; i < V; ++i) {
         mx = fmax(mx, v[i]);
         mn = fmin(mn, v[i]);
+        none += v[i] * 0.0;
       }
     }
     mx = row_reduce<OpMax>(mx);
     mn = row_reduce<OpMin>(mn);
+    none = row_sum(none);
     const int64_t u = (int64_t)g * s.npad + row;
     if (l16 == 0) {
       a.M[u] = mx;
@@ -185,6 +187,8 @@ __global__ __launch_bounds__(256) void lwc_init(const T* __restrict__ W, LwcArgs
     }
     const LwcGroup p = lwc_group(mx, mn, a.init, a.init, min(max((int)a.bits[g], 1), 8));
     write_integers<T, V>(a, w, row, g, l16, live, p);
+    // a weight that is not a number: its integer is one, but (W_hat - W) G of its row is not (nor are the strengths from then on)
+    if (l16 == 0 && live && !a.D && none != 0.0) a.S[u] = NAN;
   }
 }
 

@@ -104,3 +104,21 @@ def test_the_difference_of_the_products_keeps_its_digits(slim, n, m, beta, bits)
     # one rounding per product and the additions of the n m terms in the kernels' order (at most 64 in a row)
     got = L(out["loss_curve"][0]) * n * 2 * m
     assert abs(float(got - exact)) <= 64 * 2.0 ** -53 * terms, float(got - exact) / terms
+
+
+@pytest.mark.parametrize("m,beta", [(64, 32), (60, 6)])
+@pytest.mark.parametrize("value", [float("nan"), float("inf")])
+def test_weights_that_are_not_finite(slim, m, beta, value):
+    """Nothing can be learnt in the row of such a weight: the loss is not a number and the row's quantisers are those of a
+    group without a range (scale 1, zero 0), in both forms of the product; the other rows are as without it."""
+    g = torch.Generator().manual_seed(m)
+    W = (torch.randn((5, m), generator=g) * 0.05).to(torch.float16)
+    X = torch.randn((m, 2 * m), generator=g, dtype=torch.float64)
+    G, bits = (X @ X.t()).to(torch.float32).cuda(), torch.full((m // beta,), 2, dtype=torch.uint8, device="cuda")
+    good = slim.lwc_quantize(W.cuda(), G, 2 * m, bits, beta, steps=3)
+    W[3, 7] = value
+    out = slim.lwc_quantize(W.cuda(), G, 2 * m, bits, beta, steps=3)
+    assert np.isnan(out["loss_curve"]).all()
+    assert bool((out["scale"][3] == 1.0).all()) and bool((out["zero"][3] == 0.0).all())
+    rest = [0, 1, 2, 4]
+    assert torch.equal(out["codes"][rest], good["codes"][rest]) and torch.equal(out["scale"][rest], good["scale"][rest])
