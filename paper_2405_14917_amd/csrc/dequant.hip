@@ -198,7 +198,7 @@ slim_status dq_partials(slim_ctx* ctx, const char* fn, DqArgs& a, int splits, fl
                        splits, a.t_x, a.n, fixed_floats);
     a.out = fixed;
   } else {
-    slim_status st = slim_ws_reserve(ctx, slim_ws_need_dequant(a.n, a.m, a.beta, a.t_x, std::max(1, ctx->num_cus)));
+    slim_status st = slim_ws_reserve(ctx, slim_ws_need_dequant(a.n, a.m, a.beta, a.t_x, ctx->num_cus));
     if (st != SLIM_OK) return st;
     a.out = static_cast<float*>(slim_ws_alloc(ctx, sizeof(float) * part_floats));
   }
@@ -305,17 +305,14 @@ slim_status dequant_matmul_tokens(slim_ctx* ctx, const char* fn, const uint32_t*
 
 }  // namespace
 
+// The requirement does not change from DQ_MAX_T tokens on: a workspace that serves one such call serves every number of tokens.
 size_t slim_ws_need_dequant(int n, int m, int beta, int t_x, int ncu) {
-  size_t need = 0;
-  if (t_x > 64) {                              // the kernel for many tokens, or slices where it cannot take the activations
-    int gper = 0;
-    const int splits = slim_dq_gemm_splits(n, m, beta, t_x, std::max(1, ncu), gper);
-    if (splits > 1) need = slim_ws_round(sizeof(float) * (size_t)splits * t_x * n);
-  }
+  ncu = std::max(1, ncu);
+  size_t need = t_x >= DQ_MAX_T ? slim_dq_gemm_partials(n, m, beta, ncu) : 0;
   t_x = std::min(t_x, DQ_MAX_T);
   for (int mfma = 0; mfma < 2; ++mfma) {       // whichever kernel the activations' type and alignment select
     int gper = 0;
-    const int splits = dq_splits(n, m, beta, t_x, std::max(1, ncu), mfma != 0, gper);
+    const int splits = dq_splits(n, m, beta, t_x, ncu, mfma != 0, gper);
     if (splits > 1) need = std::max(need, slim_ws_round(sizeof(float) * (size_t)splits * t_x * n));
   }
   return need;

@@ -14,6 +14,8 @@ typedef _Float16 half8v __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x8v __attribute__((ext_vector_type(8)));
 typedef float float16v __attribute__((ext_vector_type(16)));
 
+constexpr int DQ_FEW_TOKENS = 64;     // up to here the kernel for few tokens, above that for many
+
 struct DqArgs {
   const uint32_t* packed;
   int64_t ldp;
@@ -57,6 +59,7 @@ slim_status slim_dq_few_launch(slim_ctx* ctx, const slimdq::DqArgs& a, const sli
 // dq_gemm_splits gives the group ranges the layer is cut into (and groups per range in `gper`).
 bool slim_dq_gemm_takes(int64_t t_x, int m, int beta, const void* X, int64_t ldx);
 int slim_dq_gemm_splits(int n, int m, int beta, int64_t t_x, int cus, int& gper);
+size_t slim_dq_gemm_partials(int n, int m, int beta, int cus);
 slim_status slim_dq_gemm_launch(slim_ctx* ctx, const slimdq::DqArgs& a, int splits);
 
 #endif

@@ -34,7 +34,6 @@ using namespace slimdq;
 
 typedef float float4v __attribute__((ext_vector_type(4)));
 
-constexpr int FW_MAX_T = 64;
 constexpr int FW_PARAM_BYTES = 40 * 1024;       // LDS for the parameters of one range of groups
 
 struct FewArgs {
@@ -357,7 +356,7 @@ slim_status launch(slim_ctx* ctx, FewArgs& f) {
 }  // namespace
 
 bool slim_dq_few_takes(int64_t t_x, int64_t ldp, int beta, const void* X, int64_t ldx) {
-  return t_x <= FW_MAX_T && slim_aligned16(X) && ldx % 8 == 0 && beta % 32 == 0 && ldp < (int64_t)1 << 27;
+  return t_x <= DQ_FEW_TOKENS && slim_aligned16(X) && ldx % 8 == 0 && beta % 32 == 0 && ldp < (int64_t)1 << 27;
 }
 
 // The tile by the layer's rows, so that every CU has a workgroup and the activations are not read more often than needed

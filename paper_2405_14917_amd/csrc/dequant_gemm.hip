@@ -392,7 +392,7 @@ int token_tile(int n, int64_t t_x, int cus) {
 // From 65 tokens on.  (From 33 it is the faster one on a layer of few rows, 28 against 47 us on 4096 x 11008, but there a token's
 // outputs are promised to be the same bytes whichever other tokens share its call, and its sums run in another order.)
 bool slim_dq_gemm_takes(int64_t t_x, int m, int beta, const void* X, int64_t ldx) {
-  return t_x > 64 && t_x < (1 << 30) && slim_aligned16(X) && ldx % 8 == 0 && ldx < (1 << 23) && m % beta == 0 && beta % 32 == 0;
+  return t_x > DQ_FEW_TOKENS && t_x < (1 << 30) && slim_aligned16(X) && ldx % 8 == 0 && ldx < (1 << 23) && m % beta == 0 && beta % 32 == 0;
 }
 
 int slim_dq_gemm_splits(int n, int m, int beta, int64_t t_x, int cus, int& gper) {
@@ -402,6 +402,12 @@ int slim_dq_gemm_splits(int n, int m, int beta, int64_t t_x, int cus, int& gper)
   want = std::max<int64_t>(1, std::min<int64_t>(want, (int64_t)SLIM_DEQUANT_NOALLOC_MAX_FLOATS / (t_x * n)));
   gper = slim_cdiv(k, want);
   return slim_cdiv(k, gper);
+}
+
+// Bytes of partial sums that suffice for any number of tokens: none where even the fewest are not split.
+size_t slim_dq_gemm_partials(int n, int m, int beta, int cus) {
+  int gper = 0;
+  return slim_dq_gemm_splits(n, m, beta, DQ_FEW_TOKENS + 1, cus, gper) > 1 ? sizeof(float) * SLIM_DEQUANT_NOALLOC_MAX_FLOATS : 0;
 }
 
 slim_status slim_dq_gemm_launch(slim_ctx* ctx, const DqArgs& d, int splits) {

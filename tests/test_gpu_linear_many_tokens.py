@@ -68,3 +68,20 @@ def test_skipped_groups_and_unaligned_activations(slim):
     Y = slim.dequant_matmul(packed, gbits, row_off, scale, zero, beta, Xo[:, :m])
     Xn = X.double().cpu().numpy()
     assert np.all(np.abs(Y.cpu().numpy() - Xn @ What.T) <= 1e-5 * (np.abs(Xn) @ np.abs(What).T))
+
+
+def test_a_workspace_for_sixteen_tokens_serves_more():
+    from paper_2405_14917_amd import binding
+    rng = np.random.default_rng(11)
+    n, m, beta = 512, 512, 32
+    small = binding.Slim("cuda:0", workspace_bytes=binding.workspace_query(n, m, beta, t_x=16))
+    packed, gbits, row_off, scale, zero, What = stored(small, rng, n, m, beta, 1, False)
+    zp, bad = small.pack_zeros(zero, 4)
+    assert bad == 0
+    for t in (16, 70, 300, 700, 2500):
+        X = torch.from_numpy(rng.standard_normal((t, m))).half().cuda()
+        Y = small.dequant_matmul(packed, gbits, row_off, scale, zero, beta, X)
+        Xn = X.double().cpu().numpy()
+        assert np.all(np.abs(Y.cpu().numpy() - Xn @ What.T) <= 1e-5 * (np.abs(Xn) @ np.abs(What).T))
+        assert torch.equal(Y, small.dequant_matmul_zp(packed, gbits, row_off, scale, zp, 4, beta, X))
+    small.close()

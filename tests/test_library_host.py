@@ -127,3 +127,12 @@ def test_bench_inverse_work_formulas_add_up():
         whole = 2.0 * m ** 3 / 3.0
         # the diagonal kernel's share is about (m / 64) * 64^3 flops: a few parts in ten thousand at these sizes
         assert 0.97 * whole < total < 1.03 * whole, (name, total / whole)
+
+
+def test_workspace_of_the_linear_layer_serves_every_number_of_tokens(binding):
+    """The requirement stays the same from 16 tokens on: a workspace sized for a long prompt, or for a batch of sixteen,
+    serves the calls between and beyond, whichever kernel takes them."""
+    for n, m, beta in ((512, 512, 32), (1024, 512, 64), (128, 1024, 128), (4096, 256, 256), (300, 2048, 32)):
+        need = [binding.workspace_query(n, m, beta, t_x=t, num_cus=256) for t in (16, 17, 64, 65, 100, 128, 500, 2048, 1 << 20)]
+        assert len(set(need)) == 1, (n, m, beta, need)
+        assert binding.workspace_query(n, m, beta, t_x=1, num_cus=256) <= need[0]
