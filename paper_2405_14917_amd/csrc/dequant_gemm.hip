@@ -338,10 +338,12 @@ __global__ __launch_bounds__(PG_THREADS, 2) void dequant_gemm(PgArgs pa) {
     }
     ++gi;
     cmeta = meta_of(min(gi, gcount - 1));
+    if (cd.b != 0) {                              // (a skipped group adds nothing, also where its activations are not finite)
 #pragma unroll
-    for (int i = 0; i < TA; ++i)
+      for (int i = 0; i < TA; ++i)
 #pragma unroll
-      for (int q = 0; q < 16; ++q) y[i][q] = fmaf(s2, acc[i][q], y[i][q]);
+        for (int q = 0; q < 16; ++q) y[i][q] = fmaf(s2, acc[i][q], y[i][q]);
+    }
     if ((gi & 15) == 0 || left == 0) {
 #pragma unroll
       for (int i = 0; i < TA; ++i)

@@ -85,3 +85,20 @@ def test_a_workspace_for_sixteen_tokens_serves_more():
         assert np.all(np.abs(Y.cpu().numpy() - Xn @ What.T) <= 1e-5 * (np.abs(Xn) @ np.abs(What).T))
         assert torch.equal(Y, small.dequant_matmul_zp(packed, gbits, row_off, scale, zp, 4, beta, X))
     small.close()
+
+
+@pytest.mark.parametrize("t,aligned", [(5, True), (90, True), (300, True), (5, False)])
+def test_a_skipped_group_adds_nothing_whatever_its_activations(slim, t, aligned):
+    """A group whose width disagrees with its rows is skipped by every kernel, also where its activations are infinite."""
+    rng = np.random.default_rng(t)
+    n, m, beta = 150, 512, 64
+    packed, gbits, row_off, scale, zero, What = stored(slim, rng, n, m, beta, 1, False)
+    gbits = gbits.clone()
+    gbits[0] ^= 1 << (2 * 2)                          # group 2: another width than its rows hold
+    What[:, 2 * beta: 3 * beta] = 0.0
+    X = torch.zeros((t, m + (0 if aligned else 4)), dtype=torch.float16, device="cuda")[:, :m]
+    X.copy_(torch.from_numpy(rng.standard_normal((t, m))).half())
+    Xn = X.double().cpu().numpy()
+    X[:, 2 * beta: 3 * beta] = float("inf")
+    Y = slim.dequant_matmul(packed, gbits, row_off, scale, zero, beta, X)
+    assert np.all(np.abs(Y.cpu().numpy() - Xn @ What.T) <= 1e-5 * (np.abs(Xn) @ np.abs(What).T) + 1e-30)
