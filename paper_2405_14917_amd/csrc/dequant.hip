@@ -247,8 +247,9 @@ slim_status dq_fixed_limit(slim_ctx* ctx, const char* fn, DqArgs a, int64_t t_x,
   return dq_partials(ctx, fn, a, splits, fixed, fixed_floats);
 }
 
-// Any number of tokens: up to 64 in one launch of the kernel for few tokens, more in one of the kernel for many; activations
-// that are not aligned to 16 bytes DQ_MAX_T tokens at a time, one after the other on the context's stream.  `zp` (zero points
+// Any number of tokens: up to 64 in one launch of the kernel for few tokens, more in one of the kernel for many (or, where that
+// one is not built for the layer, 64 at a time); activations that are not aligned to 16 bytes DQ_MAX_T tokens at a time, one
+// after the other on the context's stream.  `zp` (zero points
 // in their packed form) only where slim_dq_few_takes.  Nothing is launched if the call is refused.
 slim_status dequant_matmul_tokens(slim_ctx* ctx, const char* fn, const uint32_t* packed, int64_t ldp,
                                   const uint32_t* gbits, const int32_t* row_off, const double* scale,
@@ -291,6 +292,16 @@ slim_status dequant_matmul_tokens(slim_ctx* ctx, const char* fn, const uint32_t*
     st = dq_partials(ctx, fn, a, splits, fixed, fixed_floats);
     if (st == SLIM_OK) st = slim_dq_gemm_launch(ctx, a, splits);
     if (st == SLIM_OK) st = dq_reduce(ctx, a, splits, Y, ldy);
+    return st;
+  }
+  if (slim_dq_few_takes(1, ldp, beta, X, ldx)) {
+    st = dq_fixed_limit(ctx, fn, a, t_x, fixed, fixed_floats);
+    for (int64_t t0 = 0; t0 < t_x && st == SLIM_OK; t0 += DQ_FEW_TOKENS) {
+      a.t_x = (int)std::min<int64_t>(DQ_FEW_TOKENS, t_x - t0);
+      a.X = static_cast<const uint16_t*>(X) + t0 * ldx;
+      a.out = Y + t0 * ldy;
+      st = slim_dq_few_launch(ctx, a, zp);
+    }
     return st;
   }
   for (int64_t t0 = 0; t0 < t_x; t0 += DQ_MAX_T) {

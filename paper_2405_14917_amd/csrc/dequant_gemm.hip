@@ -28,6 +28,7 @@ using namespace slimdq;
 
 constexpr int PG_ROWS = 128, PG_THREADS = 256, PG_STAGES = 3, PG_MAXB = 5;
 constexpr int PG_BAND = 8;                       // token tiles per band of the tile order
+constexpr int PG_MAXK = 16384;                   // groups: three stages (at most 69 KiB) and these in 160 KiB of LDS
 
 struct PgArgs {
   DqArgs d;
@@ -393,8 +394,11 @@ int token_tile(int n, int64_t t_x, int cus) {
 
 // From 65 tokens on.  (From 33 it is the faster one on a layer of few rows, 28 against 47 us on 4096 x 11008, but there a token's
 // outputs are promised to be the same bytes whichever other tokens share its call, and its sums run in another order.)
+// Up to PG_MAXK groups: a workgroup holds a word for each of its range in LDS; lane offsets in 32 bits bound the leading
+// dimension.  What lies beyond is taken 64 tokens at a time by the kernel for few tokens.
 bool slim_dq_gemm_takes(int64_t t_x, int m, int beta, const void* X, int64_t ldx) {
-  return t_x > DQ_FEW_TOKENS && t_x < (1 << 30) && slim_aligned16(X) && ldx % 8 == 0 && ldx < (1 << 23) && m % beta == 0 && beta % 32 == 0;
+  return t_x > DQ_FEW_TOKENS && t_x < (1 << 30) && slim_aligned16(X) && ldx % 8 == 0 && ldx < (1 << 23) && m % beta == 0 &&
+         beta % 32 == 0 && m / beta <= PG_MAXK;
 }
 
 int slim_dq_gemm_splits(int n, int m, int beta, int64_t t_x, int cus, int& gper) {

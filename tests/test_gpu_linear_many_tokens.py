@@ -102,3 +102,22 @@ def test_a_skipped_group_adds_nothing_whatever_its_activations(slim, t, aligned)
     X[:, 2 * beta: 3 * beta] = float("inf")
     Y = slim.dequant_matmul(packed, gbits, row_off, scale, zero, beta, X)
     assert np.all(np.abs(Y.cpu().numpy() - Xn @ What.T) <= 1e-5 * (np.abs(Xn) @ np.abs(What).T) + 1e-30)
+
+
+def test_more_groups_than_the_kernel_holds(slim):
+    """Twice the groups of one launch's limit, and so many tokens that nothing is split: taken 64 tokens at a time."""
+    n, beta, k, t = 544, 32, 36864, 3860
+    m = beta * k
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    codes = torch.randint(0, 4, (n, m), generator=gen, device="cuda", dtype=torch.uint8)
+    packed, gbits, row_off, _ = slim.pack(codes, torch.full((k,), 2, dtype=torch.uint8, device="cuda"), beta)
+    del codes
+    scale = torch.full((n, k), 2.0 ** -10, dtype=torch.float64, device="cuda")
+    zero = torch.full((n, k), 1.0, dtype=torch.float64, device="cuda")
+    X = torch.zeros((t, m), dtype=torch.float16, device="cuda")
+    X[:, ::64] = torch.randint(-1, 2, (t, m // 64), generator=gen, device="cuda").half()
+    Y = slim.dequant_matmul(packed, gbits, row_off, scale, zero, beta, X)
+    for t0 in (0, 1984, t - 40):                      # the same as in calls of few tokens, exactly (every sum is exact)
+        part = X[t0: t0 + 40]
+        assert torch.equal(Y[t0: t0 + 40], slim.dequant_matmul(packed, gbits, row_off, scale, zero, beta, part))
+    assert float(Y.abs().max()) > 0.0
