@@ -159,9 +159,10 @@ __global__ __launch_bounds__(256) void int_x_digits(const T* __restrict__ X, int
   if (tb >= s.TB) return;
   const int unit = mt.unit[0];
   const int64_t t = (int64_t)tb * 32 + l32;
-  int64_t sum = 0;
+  double sum = 0.0;
   for (int cc = 0; cc < s.nchg; ++cc) {
     const int c = g * s.nchg + cc, lo = mt.x[2 * c], nd = mt.x[2 * c + 1];
+    int64_t csum = 0;                      // of this chunk: at most 64 channels of 54 bits
     char* dst = Xd + ((int64_t)c * s.TB + tb) * SI_MAXD * s.ks * 1024 + lane * 16;
     for (int f = 0; f < s.ks; ++f) {
       const int j0 = cc * s.chk + f * 32 + h * 16;
@@ -170,7 +171,7 @@ __global__ __launch_bounds__(256) void int_x_digits(const T* __restrict__ X, int
       for (int i = 0; i < 16; ++i) {
         int64_t v = 0;
         if (j0 + i < s.beta && t < s.ts) v = fixed_point(float_bits<T>(X[(int64_t)(g * s.beta + j0 + i) * ldx + t]), unit);
-        sum += v;
+        csum += v;
         u[i] = digit_bytes(v) >> (8 * lo);
       }
       for (int d = 0; d < nd; ++d) {
@@ -187,10 +188,10 @@ __global__ __launch_bounds__(256) void int_x_digits(const T* __restrict__ X, int
         *reinterpret_cast<uint4*>(dst + ((int64_t)d * s.ks + f) * 1024) = make_uint4(w[0], w[1], w[2], w[3]);
       }
     }
+    sum += (double)csum;
   }
-  // (a sum of up to 512 channels of 54 bits may not fit 53 bits: one rounding)
-  const double other = __shfl_xor((double)sum, 32, WAVE);
-  if (h == 0) SX[(int64_t)g * s.tpad + t] = (double)sum + other;
+  const double other = __shfl_xor(sum, 32, WAVE);
+  if (h == 0) SX[(int64_t)g * s.tpad + t] = sum + other;
 }
 
 // ---- a unit per token ----------------------------------------------------------------------------------------------

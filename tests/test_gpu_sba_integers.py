@@ -64,3 +64,17 @@ def test_inputs_that_are_not_finite(slim, where):
     (W if where == "W" else X)[7, 9] = float("nan")
     bits, p, curve = slim.sba_allocate(W.cuda(), d[:4].cuda(), 64, 2, X.cuda())
     assert np.isnan(curve).all() and p == 0 and bool((bits == 2).all())
+
+
+@pytest.mark.parametrize("beta,groups", [(4096, 1), (2048, 2)])
+def test_sums_of_wide_groups(slim, beta, groups):
+    """A zero point outside int8 multiplies the sum of a group's activations: here thousands of integers of 54 bits."""
+    g = torch.Generator().manual_seed(beta)
+    n, m, ts = 6, beta * groups, 32
+    W = (1.0 + torch.rand((n, m), generator=g) / 64).to(torch.float16)         # zero points of about -190
+    X = (1.0 + torch.rand((m, ts), generator=g)).to(torch.bfloat16)
+    X[5, 7] = 2.0 ** -53                                                       # the unit is its own digit
+    gs = np.arange(groups, dtype=np.float64)
+    _, _, obj_o, _ = orc.sba_allocate(W.double().numpy(), gs, beta, 2, X.double().numpy(), objective=orc.OBJ_MSE)
+    _, _, curve = slim.sba_allocate(W.cuda(), torch.from_numpy(gs).cuda(), beta, 2, X.cuda(), objective=1)
+    assert np.allclose(curve, obj_o, rtol=1e-9), (curve, obj_o)
