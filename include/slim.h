@@ -160,8 +160,9 @@ slim_status slim_salience(slim_ctx* ctx, const void* W, slim_dtype w_dtype, int 
  *   p_star    host, or NULL
  *   obj_curve host, floor(k/2)+1 doubles or NULL: the objective for every p
  *   N in 2..7 (widths N - 1 .. N + 1 within 1..8; the paper's settings are N = 2, 3 and, in App. G, 4).  The
- *   products with X_s are exact integer products, the outputs and everything behind them fp64.  (A bf16 or fp32 input
- *   that spans more than 53 binary digits, from its largest element to the last digit of another, is rounded there.)
+ *   products with X_s are exact integer products, the outputs and everything behind them fp64.  (An element
+ *   of a bf16 or fp32 input whose last digit lies more than 53 binary digits below the largest element of its block, 32 tokens
+ *   of up to 128 channels of X_s or up to 128 channels of W, is rounded there, by 2^-54 of that largest element.)
  */
 slim_status slim_sba_allocate(slim_ctx* ctx, const void* W, slim_dtype w_dtype, int n, int m, int64_t ldw,
                               const double* group_sal, int beta, int N, int objective, const void* X_s,

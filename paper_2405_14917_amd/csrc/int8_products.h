@@ -1,10 +1,10 @@
 // Products on the int8 matrix cores whose results are exact up to the rounding of the fp64 accumulation: a matrix of
 // weights as small integers with one scale per (row, group), or as base-256 digits, times a matrix of tokens (activations, or
 // the columns of a Gram matrix) as base-256 digits.
-//   * The token side is one integer matrix times a power of two (or one power of two per token), cut into signed digits
-//     (balanced: -128 .. 127); of every chunk of channels only the digits in use are kept, three to seven.
+//   * The token side is integers times a power of two per 32 tokens of a chunk of channels (or per token), cut into signed
+//     digits (balanced: -128 .. 127); of every such block only the digits in use are kept, one to seven.
 //   * A fake-quantised weight is scale * (q - z) with a small integer q - z: one int8 matrix.  Weights as they are become
-//     digits the same way (two to four for 16-bit weights).
+//     digits the same way, with a power of two per chunk (two to four digits for 16-bit weights).
 //   * A chunk's products of digits are summed exactly in int32 (128 channels of 128 * 128 * 257 < 2^31 for two digits chained by
 //     a shift) and enter the fp64 outputs with one rounding per (row, group) and pair of digits: fewer than the fp64 matrix
 //     cores make, which round after every four channels.
@@ -40,13 +40,10 @@ struct IntShape {
 
 // What the kernels have to know about the digits.
 struct IntMeta {
-  int* x;                          // 2 C (x 2 TB with digits per token block): lowest digit in use and digits in use
-  int* w;                          // 2 C: the same of the weights' digits
-  int* unit;                       // unit[0], unit[1]: exponents of the units of X_s and W; unit[2]: non-finite inputs seen;
-                                   // unit[3]: every |W| is below 2^unit[3]
-  unsigned* xmax;                  // C largest |x| as float bits, C smallest exponent of a last digit (as int); then W's
-  int* xlsb;
-  unsigned* wmax;
+  int* x;                          // 2 C TB: exponent of the lowest digit in use and digits in use, per chunk and token block
+  int* w;                          // 2 C: the same of the weights' digits, per chunk
+  int* flags;                      // flags[0]: non-finite inputs seen; flags[1]: every |W| is below 2^flags[1]
+  unsigned* wmax;                  // C largest |w| as float bits, C smallest exponent of a last digit
   int* wlsb;
 };
 
@@ -67,6 +64,20 @@ __device__ __forceinline__ void split_float(unsigned bits, unsigned& mant, int& 
   mant = (bits & 0x7fffffu) | (e ? 0x800000u : 0u);
   e0 = (e ? e : 1) - 150;
 }
+// The unit of a block of values: their last digit, but no more than 53 digits below the largest one, whose float bits are mx.
+// (Rounding there is by 2^-54 of the block's largest value.)
+__device__ __forceinline__ int block_unit(unsigned mx, int lsb) {
+  unsigned mant;
+  int e0;
+  split_float(mx, mant, e0);
+  return mx ? max(lsb, e0 + (31 - __builtin_clz(mant)) - 53) : 0;
+}
+// balanced digits that hold magnitudes up to v
+__device__ __forceinline__ int digits_for(uint64_t v) {
+  int nd = 0;
+  for (uint64_t lim = 0; lim < v; ++nd) lim = lim * 256 + 127;
+  return nd;
+}
 // v / 2^unit as an integer (rounded where v has digits below the unit); 0 for what is not finite
 __device__ __forceinline__ int64_t fixed_point(unsigned bits, int unit) {
   unsigned mant;
@@ -84,13 +95,6 @@ __device__ __forceinline__ int64_t fixed_point(unsigned bits, int unit) {
 // the byte lanes of v + sum_i 128 * 256^i are the balanced digits plus 128
 __device__ __forceinline__ uint64_t digit_bytes(int64_t v) { return ((uint64_t)v + 0x0080808080808080ull) ^ 0x8080808080808080ull; }
 
-// first channel and number of channels of a chunk
-__device__ __forceinline__ int chunk_begin(const IntShape& s, int c, int& len) {
-  const int g = c / s.nchg, j0 = (c - g * s.nchg) * s.chk;
-  len = min(s.chk, s.beta - j0);
-  return g * s.beta + j0;
-}
-
 __device__ __forceinline__ double row_sum(double v) {
   v += dpp_f64<DPP_XOR1>(v);
   v += dpp_f64<DPP_XOR2>(v);
@@ -105,7 +109,6 @@ __device__ __forceinline__ double row_reduce(double v) {
   return OP::f(v, dpp_f64<DPP_MIRROR>(v));
 }
 
-
 // Byte offset of channel j (of group g) of row `row` in operand order, for four channels at a time
 __device__ __forceinline__ int64_t operand_offset(const IntShape& s, int row, int g, int j, int& chunk) {
   const int cc = j / s.chk, jj = j - cc * s.chk;
@@ -113,10 +116,10 @@ __device__ __forceinline__ int64_t operand_offset(const IntShape& s, int row, in
   return (((int64_t)(row >> 5) * s.C + chunk) * s.ks + (jj >> 5)) * 1024 + ((jj >> 4) & 1) * 512 + (row & 31) * 16 + (jj & 15);
 }
 // the digits of four weights, plane by plane
-__device__ __forceinline__ void store_digits(char* Wd, int64_t plane, int64_t dst, const unsigned (&bits)[4], int unit, int lo, int nd) {
+__device__ __forceinline__ void store_digits(char* Wd, int64_t plane, int64_t dst, const unsigned (&bits)[4], int unit, int nd) {
   uint64_t u[4];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) u[i] = digit_bytes(fixed_point(bits[i], unit)) >> (8 * lo);
+  for (int i = 0; i < 4; ++i) u[i] = digit_bytes(fixed_point(bits[i], unit));
   for (int d = 0; d < nd; ++d) {
     unsigned word = 0;
 #pragma unroll
@@ -224,7 +227,15 @@ __device__ __forceinline__ void lds_load16(unsigned lds_addr, unsigned voff, con
 #endif
 }
 
-// A stage in one word: chunk, lowest digit (absolute), digits (at most SI_STAGE_D), and whether it is the chunk's first.
+// What a chunk's digits are, in one word: digits in use of X (3 bits) and of W (3 bits), exponents of their lowest (13 bits each).
+__device__ __forceinline__ int digits_word(const int* x) { return x[1] | ((x[0] & 8191) << 6); }
+__device__ __forceinline__ int digits_word(const int* x, const int* w) { return digits_word(x) | (w[1] << 3) | (w[0] << 19); }
+__device__ __forceinline__ int digits_x(int d) { return d & 7; }
+__device__ __forceinline__ int digits_w(int d) { return (d >> 3) & 7; }
+__device__ __forceinline__ int exponent_x(int d) { return (d << 13) >> 19; }
+__device__ __forceinline__ int exponent_w(int d) { return d >> 19; }
+
+// A stage in one word: chunk, its first digit, digits (at most SI_STAGE_D), and whether it is the chunk's first.
 __device__ __forceinline__ int stage_word(int c, int lo, int nd, int first) { return (c << 8) | (first << 7) | (nd << 4) | lo; }
 __device__ __forceinline__ int stage_chunk(int w) { return w >> 8; }
 __device__ __forceinline__ int stage_nd(int w) { return (w >> 4) & 7; }
@@ -232,9 +243,8 @@ __device__ __forceinline__ int stage_lo(int w) { return w & 15; }
 __device__ __forceinline__ bool stage_first(int w) { return (w >> 7) & 1; }
 // The digits of a stage for token block tb -> LDS (1 KiB per load, the loads dealt to the wavefronts)
 template <int KS, int NW>
-__device__ __forceinline__ void stage_digits(const char* Xd, const IntShape& s, int word, int base_lo, int tb,
-                                             unsigned lds, int wave, int lane) {
-  const char* src = Xd + (((int64_t)stage_chunk(word) * s.TB + tb) * SI_MAXD + (stage_lo(word) - base_lo)) * KS * 1024;
+__device__ __forceinline__ void stage_digits(const char* Xd, const IntShape& s, int word, int tb, unsigned lds, int wave, int lane) {
+  const char* src = Xd + (((int64_t)stage_chunk(word) * s.TB + tb) * SI_MAXD + stage_lo(word)) * KS * 1024;
   const int cnt = stage_nd(word) * KS;
   for (int i = wave; i < cnt; i += NW) lds_load16(lds + i * 1024, lane * 16, src + i * 1024);
 }
@@ -252,9 +262,8 @@ __device__ __forceinline__ void tile_of(int id, int RT, int TB, int& rt, int& tb
 struct OutArgs {
   IntShape s;
   IntMeta mt;
-  int mstride_c, mstride_t;        // of mt.x: entries between two chunks and between two token blocks
   const char* Xd;
-  const double* SX;                // k x tpad: sums of the group's channels of a token, in units
+  const double* SX;                // k x tpad: sums of the group's channels of a token (with token_unit: in units)
   const double* SXlo;              // what their rounding leaves (compensated sums)
   const char* Q;                   // codes, or digits of W with planes `plane` bytes apart
   int64_t plane;
@@ -262,7 +271,7 @@ struct OutArgs {
   const double* Rz;                // k x npad: the part of the zero the codes do not hold, times the scale
   const int* rest;                 // k: rest[g] >= rest_from: some row of the group has such a part
   int rest_from;
-  const int* token_unit;           // exponent of each token's unit (INT_MIN: not finite), or nullptr: unit[0] for all
+  const int* token_unit;           // exponent of each token's unit (INT_MIN: not finite), which mt.x counts from, or nullptr
   double* Y;                       // n x ts
   // compensated sums:
   double* Ylo;                     // n x ts: what Y's rounding leaves (REF)
@@ -276,13 +285,11 @@ slimint::IntShape slim_int_shape(int n, int m, int beta, int64_t ts);
 inline int64_t slim_int_plane(const slimint::IntShape& s) { return (int64_t)s.npad * s.C * s.chk; }     // bytes of one int8 matrix
 inline size_t slim_int_digits_bytes(const slimint::IntShape& s) { return (size_t)s.C * s.TB * slimint::SI_MAXD * s.ks * 1024; }
 slim_status slim_int_clear(slim_ctx* ctx, const slimint::IntShape& s, const slimint::IntMeta& mt, int* rest, int nrest);
-slim_status slim_int_x_stats(slim_ctx* ctx, const slimint::IntShape& s, const slimint::IntMeta& mt, const void* X, slim_dtype dt, int64_t ldx);
-slim_status slim_int_w_stats(slim_ctx* ctx, const slimint::IntShape& s, const slimint::IntMeta& mt, const void* W, slim_dtype dt, int64_t ldw);
-slim_status slim_int_weight_meta(slim_ctx* ctx, const slimint::IntShape& s, const slimint::IntMeta& mt);      // W alone
-slim_status slim_int_meta(slim_ctx* ctx, const slimint::IntShape& s, const slimint::IntMeta& mt);
+// mt.w and flags[1] of W
+slim_status slim_int_w_meta(slim_ctx* ctx, const slimint::IntShape& s, const slimint::IntMeta& mt, const void* W, slim_dtype dt, int64_t ldw);
 slim_status slim_int_x_digits(slim_ctx* ctx, const slimint::IntShape& s, const slimint::IntMeta& mt, const void* X, slim_dtype dt, int64_t ldx,
                               char* Xd, double* SX);
-// The digits of a fp32 matrix with a unit per token (column): token_unit[ts]; work: 2 ts ints.  mt.x then has 2 C TB entries.
+// The digits of a fp32 matrix with a unit per token (column): token_unit[ts]; work: 2 ts ints.
 slim_status slim_int_g_digits(slim_ctx* ctx, const slimint::IntShape& s, const slimint::IntMeta& mt, const float* G, int64_t ldg,
                               int* work, int* token_unit, char* Xd, double* SX, double* SXlo);
 // Y = W X (ref: from the digits of W) or W_hat X (from codes and scales); `compensated`: Y and Ylo = W X to twice the

@@ -24,41 +24,14 @@ __device__ __forceinline__ void stat(unsigned bits, unsigned& mx, int& lsb, int&
 __global__ __launch_bounds__(256) void int_clear(IntMeta mt, int C, int* rest, int nrest) {
   const int i = blockIdx.x * 256 + threadIdx.x;
   if (i < C) {
-    mt.xmax[i] = mt.wmax[i] = 0u;
-    mt.xlsb[i] = mt.wlsb[i] = INT_MAX;
+    mt.wmax[i] = 0u;
+    mt.wlsb[i] = INT_MAX;
   }
   if (i < nrest) rest[i] = 0;
-  if (i == 0) mt.unit[2] = 0;
+  if (i == 0) mt.flags[0] = 0;
 }
 
-// grid (C, splits): largest magnitude and last digit of the chunk's rows of X_s
-template <typename T>
-__global__ __launch_bounds__(256) void int_x_stats(const T* __restrict__ X, int64_t ldx, IntShape s, IntMeta mt) {
-  int len;
-  const int ch0 = chunk_begin(s, blockIdx.x, len);
-  unsigned mx = 0;
-  int lsb = INT_MAX, bad = 0;
-  const int64_t quads = s.ts / 4;
-  for (int64_t q = (int64_t)blockIdx.y * 256 + threadIdx.x; q < quads; q += (int64_t)gridDim.y * 256)
-    for (int r = 0; r < len; ++r) {
-      const uint2 raw = *reinterpret_cast<const uint2*>(X + (int64_t)(ch0 + r) * ldx + 4 * q);
-      const T* v = reinterpret_cast<const T*>(&raw);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) stat(float_bits<T>(v[i]), mx, lsb, bad);
-    }
-#pragma unroll
-  for (int d = 32; d > 0; d >>= 1) {
-    mx = max(mx, (unsigned)__shfl_xor((int)mx, d, WAVE));
-    lsb = min(lsb, __shfl_xor(lsb, d, WAVE));
-  }
-  if (bad) atomicOr(&mt.unit[2], 1);
-  if ((threadIdx.x & 63) == 0 && mx) {
-    atomicMax(&mt.xmax[blockIdx.x], mx);
-    atomicMin(&mt.xlsb[blockIdx.x], lsb);
-  }
-}
-
-// grid (ceil(m / 1024), splits): the same for the chunk's columns of W; a thread owns four columns
+// grid (ceil(m / 1024), splits): largest magnitude and last digit of the chunk's columns of W; a thread owns four columns
 template <typename T>
 __global__ __launch_bounds__(256) void int_w_stats(const T* __restrict__ W, int64_t ldw, IntShape s, IntMeta mt) {
   __shared__ unsigned lmax[264];
@@ -86,7 +59,7 @@ __global__ __launch_bounds__(256) void int_w_stats(const T* __restrict__ W, int6
     const int c = chunk_of(ch) - c0;
     atomicMax(&lmax[c], mx);
     atomicMin(&llsb[c], lsb);
-    if (bad) atomicOr(&mt.unit[2], 1);
+    if (bad) atomicOr(&mt.flags[0], 1);
   }
   __syncthreads();
   for (int i = threadIdx.x; i < 264; i += 256)
@@ -96,83 +69,67 @@ __global__ __launch_bounds__(256) void int_w_stats(const T* __restrict__ W, int6
     }
 }
 
-// Units and digits in use: `which` + block 0 for X_s, 1 for W.  The unit is the last digit of all values, but no more than 53
-// digits below the largest one; a chunk keeps the digits between its own last one and its own largest value.
-__global__ __launch_bounds__(256) void int_meta(IntMeta mt, int C, int which) {
-  which += blockIdx.x;
+// One workgroup: units and digits in use of the chunks of W, and the largest weight's exponent
+__global__ __launch_bounds__(256) void int_w_meta(IntMeta mt, int C) {
   __shared__ unsigned smx[256];
-  __shared__ int slsb[256];
-  const unsigned* cmax = which ? mt.wmax : mt.xmax;
-  const int* clsb = which ? mt.wlsb : mt.xlsb;
-  int* out = which ? mt.w : mt.x;
   unsigned mx = 0;
-  int lsb = INT_MAX;
   for (int c = threadIdx.x; c < C; c += 256) {
-    mx = max(mx, cmax[c]);
-    lsb = min(lsb, clsb[c]);
+    mx = max(mx, mt.wmax[c]);
+    const int unit = block_unit(mt.wmax[c], mt.wlsb[c]);
+    mt.w[2 * c] = unit;
+    mt.w[2 * c + 1] = digits_for((uint64_t)fixed_point(mt.wmax[c], unit));
   }
   smx[threadIdx.x] = mx;
-  slsb[threadIdx.x] = lsb;
   __syncthreads();
   for (int st = 128; st > 0; st >>= 1) {
-    if (threadIdx.x < st) {
-      smx[threadIdx.x] = max(smx[threadIdx.x], smx[threadIdx.x + st]);
-      slsb[threadIdx.x] = min(slsb[threadIdx.x], slsb[threadIdx.x + st]);
-    }
+    if (threadIdx.x < st) smx[threadIdx.x] = max(smx[threadIdx.x], smx[threadIdx.x + st]);
     __syncthreads();
   }
   mx = smx[0];
-  lsb = slsb[0];
-  unsigned mant = 0;
-  int e0 = 0, unit = 0;
-  if (mx) {
-    split_float(mx, mant, e0);
-    unit = max(lsb, e0 + (31 - __builtin_clz(mant)) - 53);
-  }
-  if (threadIdx.x == 0) {
-    mt.unit[which] = unit;
-    if (which) mt.unit[3] = mx ? e0 + 32 - __builtin_clz(mant) : 0;
-  }
-  for (int c = threadIdx.x; c < C; c += 256) {
-    int lo = 0, hi = 0;
-    if (cmax[c]) {
-      const uint64_t v = (uint64_t)fixed_point(cmax[c], unit);
-      lo = max(0, clsb[c] - unit) / 8;
-      uint64_t lim = 0;                                  // largest value of hi balanced digits
-      while (lim < v) {
-        lim = lim * 256 + 127;
-        ++hi;
-      }
-      hi = max(hi, lo);
-    }
-    out[2 * c] = lo;
-    out[2 * c + 1] = hi - lo;
-  }
+  unsigned mant;
+  int e0;
+  split_float(mx, mant, e0);
+  if (threadIdx.x == 0) mt.flags[1] = mx ? e0 + 32 - __builtin_clz(mant) : 0;
 }
 
-// grid (ceil(TB / 4), k): a wavefront cuts 32 tokens of one group into digits and sums its channels per token
+// grid (ceil(TB / 4), k): a wavefront finds the unit and the digits in use of 32 tokens of every chunk of one group, cuts them
+// into digits, and sums the group's channels per token
 template <typename T>
 __global__ __launch_bounds__(256) void int_x_digits(const T* __restrict__ X, int64_t ldx, IntShape s, IntMeta mt,
                                                     char* __restrict__ Xd, double* __restrict__ SX) {
   const int lane = threadIdx.x & 63, l32 = lane & 31, h = lane >> 5;
   const int tb = blockIdx.x * 4 + (threadIdx.x >> 6), g = blockIdx.y;
   if (tb >= s.TB) return;
-  const int unit = mt.unit[0];
   const int64_t t = (int64_t)tb * 32 + l32;
+  auto value = [&](int j) -> unsigned { return (j < s.beta && t < s.ts) ? float_bits<T>(X[(int64_t)(g * s.beta + j) * ldx + t]) : 0u; };
   double sum = 0.0;
   for (int cc = 0; cc < s.nchg; ++cc) {
-    const int c = g * s.nchg + cc, lo = mt.x[2 * c], nd = mt.x[2 * c + 1];
+    const int c = g * s.nchg + cc;
+    unsigned mx = 0;
+    int lsb = INT_MAX, bad = 0;
+    for (int f = 0; f < s.ks; ++f)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) stat(value(cc * s.chk + f * 32 + h * 16 + i), mx, lsb, bad);
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) {
+      mx = max(mx, (unsigned)__shfl_xor((int)mx, d, WAVE));
+      lsb = min(lsb, __shfl_xor(lsb, d, WAVE));
+    }
+    if (bad) atomicOr(&mt.flags[0], 1);
+    const int unit = block_unit(mx, lsb), nd = digits_for((uint64_t)fixed_point(mx, unit));
+    if (lane == 0) {
+      mt.x[2 * ((int64_t)c * s.TB + tb)] = unit;
+      mt.x[2 * ((int64_t)c * s.TB + tb) + 1] = nd;
+    }
     int64_t csum = 0;                      // of this chunk: at most 64 channels of 54 bits
     char* dst = Xd + ((int64_t)c * s.TB + tb) * SI_MAXD * s.ks * 1024 + lane * 16;
     for (int f = 0; f < s.ks; ++f) {
-      const int j0 = cc * s.chk + f * 32 + h * 16;
       uint64_t u[16];
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
-        int64_t v = 0;
-        if (j0 + i < s.beta && t < s.ts) v = fixed_point(float_bits<T>(X[(int64_t)(g * s.beta + j0 + i) * ldx + t]), unit);
+        const int64_t v = fixed_point(value(cc * s.chk + f * 32 + h * 16 + i), unit);
         csum += v;
-        u[i] = digit_bytes(v) >> (8 * lo);
+        u[i] = digit_bytes(v);
       }
       for (int d = 0; d < nd; ++d) {
         unsigned w[4];
@@ -188,7 +145,7 @@ __global__ __launch_bounds__(256) void int_x_digits(const T* __restrict__ X, int
         *reinterpret_cast<uint4*>(dst + ((int64_t)d * s.ks + f) * 1024) = make_uint4(w[0], w[1], w[2], w[3]);
       }
     }
-    sum += (double)csum;
+    sum += ldexp((double)csum, unit);
   }
   const double other = __shfl_xor(sum, 32, WAVE);
   if (h == 0) SX[(int64_t)g * s.tpad + t] = sum + other;
@@ -226,16 +183,7 @@ __global__ __launch_bounds__(256) void int_g_units(int64_t ts, const int* __rest
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (i >= ts) return;
   const int mx = work[i];
-  int unit = 0;
-  if (mx == INT_MAX) {
-    unit = INT_MIN;
-  } else if (mx) {
-    unsigned mant;
-    int e0;
-    split_float((unsigned)mx, mant, e0);
-    unit = max(work[ts + i], e0 + (31 - __builtin_clz(mant)) - 53);
-  }
-  token_unit[i] = unit;
+  token_unit[i] = mx == INT_MAX ? INT_MIN : block_unit((unsigned)mx, work[ts + i]);
 }
 
 // grid (ceil(TB / 4), k): a wavefront finds the digits in use of 32 columns of every chunk of one group, and cuts them
@@ -271,15 +219,9 @@ __global__ __launch_bounds__(256) void int_g_digits(const float* __restrict__ G,
       mx = mx > om ? mx : om;
       any |= ((uint64_t)(unsigned)__shfl_xor((int)(any >> 32), d, WAVE) << 32) | (unsigned)__shfl_xor((int)any, d, WAVE);
     }
-    int lo = 0, hi = 0;
-    if (mx) {
-      lo = __builtin_ctzll(any) / 8;
-      for (uint64_t lim = 0; lim < mx; ++hi) lim = lim * 256 + 127;       // largest value of hi balanced digits
-      hi = max(hi, lo);
-    }
-    const int nd = hi - lo;
+    const int lo = mx ? __builtin_ctzll(any) / 8 : 0, nd = max(digits_for(mx) - lo, 0);
     if (lane == 0) {
-      meta[2 * ((int64_t)c * s.TB + tb)] = lo;
+      meta[2 * ((int64_t)c * s.TB + tb)] = 8 * lo;
       meta[2 * ((int64_t)c * s.TB + tb) + 1] = nd;
     }
     char* dst = Xd + ((int64_t)c * s.TB + tb) * SI_MAXD * s.ks * 1024 + lane * 16;
@@ -337,18 +279,17 @@ __global__ __launch_bounds__(256, COMP ? 4 : 3) void int_outputs(OutArgs a) {
   const int64_t rstride = (int64_t)s.C * KS * 1024;
   const char* q0 = a.Q + (int64_t)(row0 >> 5) * rstride;
   const unsigned lane16 = lane * 16;
-  // the chunks' digits (X_s: bits 0 .. 7 lowest digit and count, W: bits 8 .. 15) in LDS
+  // what the chunks' digits are, in LDS
   int* tab = reinterpret_cast<int*>(si_smem + 2 * TL::STAGE);
   auto describe = [&](int c) {
-    const int* x = a.mt.x + 2 * ((int64_t)c * a.mstride_c + (int64_t)tb * a.mstride_t);
-    return x[0] | (x[1] << 4) | (REF ? (a.mt.w[2 * c] << 8) | (a.mt.w[2 * c + 1] << 12) : 0);
+    const int* x = a.mt.x + 2 * ((int64_t)c * s.TB + tb);
+    return REF ? digits_word(x, a.mt.w + 2 * c) : digits_word(x);
   };
   for (int c = tid; c < min(s.C, SI_TAB); c += 256) tab[c] = describe(c);
-  const int unit = __builtin_amdgcn_readfirstlane((a.token_unit ? 0 : a.mt.unit[0]) + (REF ? a.mt.unit[1] : 0));
   __syncthreads();
   auto chunk_info = [&](int c) { return __builtin_amdgcn_readfirstlane(c < SI_TAB ? tab[c] : describe(c)); };
 
-  const double base = COMP ? sum_base(s.m, a.mt.unit[3]) : 0.0;
+  const double base = COMP ? sum_base(s.m, a.mt.flags[1]) : 0.0;
   double y[R][16], low[COMP ? R : 1][16];
 #pragma unroll
   for (int r = 0; r < R; ++r)
@@ -367,20 +308,20 @@ __global__ __launch_bounds__(256, COMP ? 4 : 3) void int_outputs(OutArgs a) {
       for (int r = 0; r < R; ++r) tl.s[r] = 1.0;
     }
   };
-  auto first_stage = [&](int c, int info) { return stage_word(c, info & 15, min(SI_STAGE_D, (info >> 4) & 15), 1); };
+  auto first_stage = [&](int c, int info) { return stage_word(c, 0, min(SI_STAGE_D, digits_x(info)), 1); };
   int info = chunk_info(0), word = first_stage(0, info), buf = 0;
-  stage_digits<KS, NW>(a.Xd, s, word, info & 15, tb, lds0, wave, lane);
+  stage_digits<KS, NW>(a.Xd, s, word, tb, lds0, wave, lane);
   load_first(0);
   for (;;) {
     const int c = stage_chunk(word), lo = stage_lo(word), nd = stage_nd(word);
-    const int left = (info & 15) + ((info >> 4) & 15) - lo - nd;            // digits of the chunk behind this stage
+    const int left = digits_x(info) - lo - nd;                              // digits of the chunk behind this stage
     const bool done = left <= 0 && c + 1 == s.C;
     const int next_info = left > 0 ? info : chunk_info(min(c + 1, s.C - 1));
     const int next = left > 0 ? stage_word(c, lo + nd, min(SI_STAGE_D, left), 0) : first_stage(min(c + 1, s.C - 1), next_info);
-    const int sets = REF ? (info >> 12) & 15 : 1, wlo = (info >> 8) & 15;
+    const int sets = REF ? digits_w(info) : 1, unit = exponent_x(info) + (REF ? exponent_w(info) : 0);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
-    if (!done) stage_digits<KS, NW>(a.Xd, s, next, next_info & 15, tb, lds0 + (buf ^ 1) * TL::STAGE, wave, lane);
+    if (!done) stage_digits<KS, NW>(a.Xd, s, next, tb, lds0 + (buf ^ 1) * TL::STAGE, wave, lane);
     const char* x = si_smem + buf * TL::STAGE + lane * 16;
     double sc[R];
 #pragma unroll
@@ -396,7 +337,7 @@ __global__ __launch_bounds__(256, COMP ? 4 : 3) void int_outputs(OutArgs a) {
           else
             load_first(stage_chunk(next));
         }
-        const int e = unit + 8 * (lo + 2 * p) + (REF ? 8 * (wlo + j) : 0);
+        const int e = unit + 8 * (lo + 2 * p) + (REF ? 8 * j : 0);
         if constexpr (COMP) {
 #pragma unroll
           for (int r = 0; r < R; ++r) {
@@ -415,7 +356,7 @@ __global__ __launch_bounds__(256, COMP ? 4 : 3) void int_outputs(OutArgs a) {
       const double* Rz = a.Rz + (int64_t)g * s.npad + row0 + l32;
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
-        const double sx = ldexp(a.SX[(int64_t)g * s.tpad + tb * 32 + 8 * (v >> 2) + 4 * h + (v & 3)], unit);
+        const double sx = a.SX[(int64_t)g * s.tpad + tb * 32 + 8 * (v >> 2) + 4 * h + (v & 3)];
 #pragma unroll
         for (int r = 0; r < R; ++r) {
           if constexpr (COMP) {
@@ -487,11 +428,6 @@ slim_status outputs_launch(slim_ctx* ctx, const char* name, const OutArgs& a, bo
 }
 
 template <typename T>
-slim_status x_stats(slim_ctx* ctx, const IntShape& s, const IntMeta& mt, const T* X, int64_t ldx) {
-  SLIM_LAUNCH(ctx, "int_x_stats", int_x_stats<T>, dim3(s.C, slim_cdiv(s.ts, 1024)), dim3(256), 0, X, ldx, s, mt);
-  return SLIM_OK;
-}
-template <typename T>
 slim_status x_digits(slim_ctx* ctx, const IntShape& s, const IntMeta& mt, const T* X, int64_t ldx, char* Xd, double* SX) {
   SLIM_LAUNCH(ctx, "int_x_digits", int_x_digits<T>, dim3(slim_cdiv(s.TB, 4), s.k), dim3(256), 0, X, ldx, s, mt, Xd, SX);
   return SLIM_OK;
@@ -526,20 +462,12 @@ slim_status slim_int_clear(slim_ctx* ctx, const IntShape& s, const IntMeta& mt, 
   SLIM_LAUNCH(ctx, "int_clear", int_clear, dim3(slim_cdiv(std::max(s.C, nrest), 256)), dim3(256), 0, mt, s.C, rest, nrest);
   return SLIM_OK;
 }
-slim_status slim_int_x_stats(slim_ctx* ctx, const IntShape& s, const IntMeta& mt, const void* X, slim_dtype dt, int64_t ldx) {
-  return dt == SLIM_F16 ? x_stats(ctx, s, mt, static_cast<const __half*>(X), ldx) : x_stats(ctx, s, mt, static_cast<const __hip_bfloat16*>(X), ldx);
-}
-slim_status slim_int_w_stats(slim_ctx* ctx, const IntShape& s, const IntMeta& mt, const void* W, slim_dtype dt, int64_t ldw) {
-  return dt == SLIM_F16    ? w_stats(ctx, s, mt, static_cast<const __half*>(W), ldw)
-         : dt == SLIM_BF16 ? w_stats(ctx, s, mt, static_cast<const __hip_bfloat16*>(W), ldw)
-                           : w_stats(ctx, s, mt, static_cast<const float*>(W), ldw);
-}
-slim_status slim_int_meta(slim_ctx* ctx, const IntShape& s, const IntMeta& mt) {
-  SLIM_LAUNCH(ctx, "int_meta", int_meta, dim3(2), dim3(256), 0, mt, s.C, 0);
-  return SLIM_OK;
-}
-slim_status slim_int_weight_meta(slim_ctx* ctx, const IntShape& s, const IntMeta& mt) {
-  SLIM_LAUNCH(ctx, "int_meta", int_meta, dim3(1), dim3(256), 0, mt, s.C, 1);
+slim_status slim_int_w_meta(slim_ctx* ctx, const IntShape& s, const IntMeta& mt, const void* W, slim_dtype dt, int64_t ldw) {
+  const slim_status st = dt == SLIM_F16    ? w_stats(ctx, s, mt, static_cast<const __half*>(W), ldw)
+                         : dt == SLIM_BF16 ? w_stats(ctx, s, mt, static_cast<const __hip_bfloat16*>(W), ldw)
+                                           : w_stats(ctx, s, mt, static_cast<const float*>(W), ldw);
+  if (st != SLIM_OK) return st;
+  SLIM_LAUNCH(ctx, "int_w_meta", int_w_meta, dim3(1), dim3(256), 0, mt, s.C);
   return SLIM_OK;
 }
 slim_status slim_int_x_digits(slim_ctx* ctx, const IntShape& s, const IntMeta& mt, const void* X, slim_dtype dt, int64_t ldx, char* Xd, double* SX) {

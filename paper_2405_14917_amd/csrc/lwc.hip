@@ -152,7 +152,6 @@ __global__ __launch_bounds__(256) void lwc_init(const T* __restrict__ W, LwcArgs
   const int row = blockIdx.x * 16 + (threadIdx.x >> 6) * 4 + (lane >> 4);
   const bool live = row < s.n;
   const int64_t plane = (int64_t)s.npad * s.C * s.chk;
-  const int wunit = a.mt.unit[1];
   for (int g = blockIdx.y; g < s.k; g += gridDim.y) {
     const T* w = W + (int64_t)min(row, s.n - 1) * a.ldw + (int64_t)g * s.beta;
     double mx = -INFINITY, mn = INFINITY, none = 0.0;
@@ -183,7 +182,7 @@ __global__ __launch_bounds__(256) void lwc_init(const T* __restrict__ W, LwcArgs
       if (live && j < s.beta) load4<T>(w + j, v);
       const unsigned bits4[4] = {__float_as_uint((float)v[0]), __float_as_uint((float)v[1]), __float_as_uint((float)v[2]),
                                  __float_as_uint((float)v[3])};
-      store_digits(a.Wd, plane, dst, bits4, wunit, a.mt.w[2 * c], a.mt.w[2 * c + 1]);
+      store_digits(a.Wd, plane, dst, bits4, a.mt.w[2 * c], a.mt.w[2 * c + 1]);
     }
     const LwcGroup p = lwc_group(mx, mn, a.init, a.init, min(max((int)a.bits[g], 1), 8));
     write_integers<T, V>(a, w, row, g, l16, live, p);
@@ -355,17 +354,15 @@ size_t lwc_layout(int n, int m, int beta, int steps, char* base, LwcWorkspace& w
   w.lp = doubles((size_t)w.blocks_x * w.blocks_y);
   w.loss = doubles((size_t)steps + 1);
   for (double*& p : w.par) p = doubles((size_t)s.k * s.npad);
-  int* mi = reinterpret_cast<int*>(take(sizeof(int) * (2 * (size_t)s.C * s.TB + 6 * (size_t)s.C + (size_t)s.k + 4 + 3 * (size_t)m)));
+  int* mi = reinterpret_cast<int*>(take(sizeof(int) * (2 * (size_t)s.C * s.TB + 4 * (size_t)s.C + (size_t)s.k + 2 + 3 * (size_t)m)));
   w.mt.x = mi;
   mi += 2 * (size_t)s.C * s.TB;
   w.mt.w = mi;
-  w.mt.xmax = reinterpret_cast<unsigned*>(mi + 2 * s.C);
-  w.mt.xlsb = mi + 3 * s.C;
-  w.mt.wmax = reinterpret_cast<unsigned*>(mi + 4 * s.C);
-  w.mt.wlsb = mi + 5 * s.C;
-  w.rest = mi + 6 * s.C;
-  w.mt.unit = w.rest + s.k;
-  w.work = w.mt.unit + 4;
+  w.mt.wmax = reinterpret_cast<unsigned*>(mi + 2 * s.C);
+  w.mt.wlsb = mi + 3 * s.C;
+  w.rest = mi + 4 * s.C;
+  w.mt.flags = w.rest + s.k;
+  w.work = w.mt.flags + 2;
   w.token_unit = w.work + 2 * m;
   return off;
 }
@@ -471,8 +468,7 @@ extern "C" slim_status slim_lwc_quantize(slim_ctx* ctx, const void* W, slim_dtyp
     st = slim_widen_f64(ctx, "lwc_widen_g", G, SLIM_F32, m, m, ldg, reinterpret_cast<double*>(w.Xd), (int64_t)m);
   } else {
     st = slim_int_clear(ctx, w.s, w.mt, w.rest, w.s.k);
-    if (st == SLIM_OK) st = slim_int_w_stats(ctx, w.s, w.mt, W, w_dtype, ldw);
-    if (st == SLIM_OK) st = slim_int_weight_meta(ctx, w.s, w.mt);
+    if (st == SLIM_OK) st = slim_int_w_meta(ctx, w.s, w.mt, W, w_dtype, ldw);
     if (st == SLIM_OK) st = slim_int_g_digits(ctx, w.s, w.mt, G, ldg, w.work, w.token_unit, w.Xd, w.SX, w.SXlo);
   }
   if (st != SLIM_OK) return st;
@@ -514,8 +510,6 @@ extern "C" slim_status slim_lwc_quantize(slim_ctx* ctx, const void* W, slim_dtyp
   OutArgs oa;
   oa.s = w.s;
   oa.mt = w.mt;
-  oa.mstride_c = w.s.TB;
-  oa.mstride_t = 1;
   oa.Xd = w.Xd;
   oa.SX = w.SX;
   oa.SXlo = w.SXlo;

@@ -2,19 +2,20 @@
 //
 // The search evaluates floor(k/2)+1 allocations that differ from one another in two groups only, so the layer outputs are
 // carried incrementally.  Every product with the objective's tokens is EXACT integer arithmetic on the int8 matrix cores:
-//   * X_s is one integer matrix times a power of two (fp16 values are multiples of 2^-24 below 2^16), cut into signed base-256
-//     digits (balanced: -128 .. 127); of every chunk of channels only the digits in use are kept (`int_meta`), three to five
-//     for activations;
+//   * X_s is integers times a power of two per 32 tokens of a chunk of channels (fp16 values are multiples of 2^-24 below 2^16),
+//     cut into signed base-256 digits (balanced: -128 .. 127); of every such block only the digits in use are kept, three to
+//     five for activations;
 //   * a fake-quantised weight is scale * (q - z) with a small integer q - z: one int8 matrix, and one scale per (row, group);
-//   * W itself is cut into digits the same way (two to four for 16-bit weights).
+//   * W itself is cut into digits the same way, with a power of two per chunk (two to four digits for 16-bit weights).
 // A chunk's products of digits are summed exactly in int32 (128 channels of 127 * 128 * 257 < 2^31 for two digits chained by a
 // shift) and enter the fp64 outputs with two roundings per (row, group): fewer than the fp64 matrix cores make, which round
-// after every four channels.  What is lost: a bf16 or fp32 input that spans more than 53 binary digits (largest exponent
-// of the matrix against the last digit of the element) is rounded there, 2^-54 of the largest element.
+// after every four channels.  What is lost: an element of a block (X_s: 32 tokens of up to 128 channels; W: up to 128 channels)
+// of bf16 or fp32 values whose last digit lies more than 53 binary digits below the block's largest element is rounded
+// there, by 2^-54 of that element.
 //
 //   sba_rank        stable ascending rank of the k group saliences (one workgroup, counting sort by comparison; NaN
 //                   ranks last) -> order[]
-//   int_*_stats, int_meta, int_x_digits     which digits there are, and the digits of X_s in MFMA operand order
+//   int_w_stats, int_w_meta, int_x_digits   which digits there are, and the digits of X_s in MFMA operand order
 //   sba_codes       per (row, group): Eq. 1 / Eq. 2 at width N and at the one other width the group can take, as integers
 //                   in operand order with their scales; the digits of W
 //   int_outputs     Y^T = W X_s and Y_0^T = W_N X_s (n x t_s, fp64)
@@ -240,7 +241,6 @@ __global__ __launch_bounds__(256) void sba_codes(const T* __restrict__ W, CodesA
   const int row = blockIdx.x * 16 + (threadIdx.x >> 6) * 4 + (lane >> 4);
   const bool live = row < s.n;
   const int64_t plane = (int64_t)s.npad * s.C * s.chk;
-  const int wunit = OTHER ? 0 : a.mt.unit[1];
   for (int g = blockIdx.y; g < s.k; g += gridDim.y) {
     int bits = a.N;
     if (OTHER) {
@@ -285,7 +285,7 @@ __global__ __launch_bounds__(256) void sba_codes(const T* __restrict__ W, CodesA
       if (!OTHER) {
         const unsigned bits4[4] = {__float_as_uint((float)v[0]), __float_as_uint((float)v[1]), __float_as_uint((float)v[2]),
                                    __float_as_uint((float)v[3])};
-        store_digits(a.Wd, plane, dst, bits4, wunit, a.mt.w[2 * c], a.mt.w[2 * c + 1]);
+        store_digits(a.Wd, plane, dst, bits4, a.mt.w[2 * c], a.mt.w[2 * c + 1]);
       }
     }
   }
@@ -391,15 +391,15 @@ __global__ __launch_bounds__(256, 3) void sba_search(SearchArgs a) {
   const unsigned lds0 = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(uintptr_t)((__attribute__((address_space(3))) char*)si_smem));
   const int64_t rowq = (int64_t)(row0 >> 5) * s.C * KS * 1024;
   const unsigned lane16 = lane * 16;
-  // chunk i of the search (of candidate i / per): (chunk << 8) | (digits << 4) | lowest digit
+  // chunk i of the search (of candidate i / per): (chunk << 12) | (exponent of the lowest digit + 160) << 3 | digits
   const int per = 2 * s.nchg, chunks = a.pmax * per;
   auto describe = [&](int i) {
     const int p = i / per, j = i - p * per, hi = j >= s.nchg;
     const int c = a.order[hi ? s.k - 1 - p : p] * s.nchg + (j - hi * s.nchg);
-    return (c << 8) | (a.mt.x[2 * c + 1] << 4) | a.mt.x[2 * c];
+    const int* x = a.mt.x + 2 * (c * s.TB + tb);                // (C TB blocks of at least 7 KiB: far below 2^30)
+    return (int)((unsigned)c << 12 | (unsigned)(x[0] + 160) << 3 | (unsigned)x[1]);
   };
   for (int i = tid; i < min(chunks, SI_TAB); i += 256) tab[i] = describe(i);
-  const int unit = __builtin_amdgcn_readfirstlane(a.mt.unit[0]);
   __syncthreads();
   auto chunk_info = [&](int i) { return __builtin_amdgcn_readfirstlane(i < SI_TAB ? tab[i] : describe(i)); };
 
@@ -420,12 +420,12 @@ __global__ __launch_bounds__(256, 3) void sba_search(SearchArgs a) {
     t.load_codes((old ? a.Qn : a.Qo) + rowq + (int64_t)chunk * KS * 1024, 0, lane16);
     t.load_scales((old ? a.Sn : a.So) + (int64_t)(chunk / s.nchg) * s.npad + row0, l32);
   };
-  auto first_stage = [&](int info) { return stage_word(info >> 8, info & 15, min(SI_STAGE_D, (info >> 4) & 15), 1); };
+  auto first_stage = [&](int info) { return stage_word((int)((unsigned)info >> 12), 0, min(SI_STAGE_D, info & 7), 1); };
   int i = 0, info = 0, word = 0, buf = 0;
   if (chunks > 0) {
     info = chunk_info(0);
     word = first_stage(info);
-    stage_digits<KS, NW>(a.Xd, s, word, info & 15, tb, lds0, wave, lane);
+    stage_digits<KS, NW>(a.Xd, s, word, tb, lds0, wave, lane);
     load_set(tl[0], stage_chunk(word), false);
   }
   for (int p = 0;; ++p) {
@@ -458,13 +458,13 @@ __global__ __launch_bounds__(256, 3) void sba_search(SearchArgs a) {
     if (p == a.pmax) break;
     for (int j = 0; j < per;) {
       const int c = stage_chunk(word), lo = stage_lo(word), nd = stage_nd(word);
-      const int left = (info & 15) + ((info >> 4) & 15) - lo - nd;
+      const int left = (info & 7) - lo - nd, unit = ((info >> 3) & 511) - 160;
       const bool done = left <= 0 && i + 1 == chunks;
       const int next_info = left > 0 ? info : chunk_info(min(i + 1, chunks - 1));
       const int next = left > 0 ? stage_word(c, lo + nd, min(SI_STAGE_D, left), 0) : first_stage(next_info);
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       __syncthreads();                             // (also: everybody has read `red`)
-      if (!done) stage_digits<KS, NW>(a.Xd, s, next, next_info & 15, tb, lds0 + (buf ^ 1) * TL::STAGE, wave, lane);
+      if (!done) stage_digits<KS, NW>(a.Xd, s, next, tb, lds0 + (buf ^ 1) * TL::STAGE, wave, lane);
       const char* x = si_smem + buf * TL::STAGE + lane16;
       const int g = c / s.nchg;
       const bool whole = stage_first(word) && c == g * s.nchg;
@@ -481,7 +481,7 @@ __global__ __launch_bounds__(256, 3) void sba_search(SearchArgs a) {
           const double rz = (old ? a.Rn : a.Ro)[(int64_t)g * s.npad + row0 + l32];
 #pragma unroll
           for (int v = 0; v < 16; ++v) {
-            const double sx = ldexp(a.SX[(int64_t)g * s.tpad + tb * 32 + 8 * (v >> 2) + 4 * h + (v & 3)], unit);
+            const double sx = a.SX[(int64_t)g * s.tpad + tb * 32 + 8 * (v >> 2) + 4 * h + (v & 3)];
             y[0][v] = fma(old ? rz : -rz, sx, y[0][v]);
           }
         }
@@ -575,16 +575,15 @@ size_t sba_layout(int n, int m, int beta, int64_t t_s, char* base, SbaWorkspace&
   w.pstar_dev = reinterpret_cast<int*>(take(256));
   w.tok = doubles(3 * (size_t)t_s);      // per token {max, log-sum-exp} of the reference; sum P log P behind
   w.tokB = w.tok + 2 * t_s;
-  int* mi = reinterpret_cast<int*>(take(sizeof(int) * (8 * (size_t)s.C + 2 * (size_t)s.k + 4)));
+  int* mi = reinterpret_cast<int*>(take(sizeof(int) * (2 * (size_t)s.C * s.TB + 4 * (size_t)s.C + 2 * (size_t)s.k + 2)));
   w.mt.x = mi;
-  w.mt.w = mi + 2 * s.C;
-  w.mt.xmax = reinterpret_cast<unsigned*>(mi + 4 * s.C);
-  w.mt.xlsb = mi + 5 * s.C;
-  w.mt.wmax = reinterpret_cast<unsigned*>(mi + 6 * s.C);
-  w.mt.wlsb = mi + 7 * s.C;
-  w.rest_n = mi + 8 * s.C;               // per group: some row has a zero outside int8 (width N; the other width)
+  mi += 2 * (size_t)s.C * s.TB;
+  w.mt.w = mi;
+  w.mt.wmax = reinterpret_cast<unsigned*>(mi + 2 * s.C);
+  w.mt.wlsb = mi + 3 * s.C;
+  w.rest_n = mi + 4 * s.C;               // per group: some row has a zero outside int8 (width N; the other width)
   w.rest_o = w.rest_n + s.k;
-  w.mt.unit = w.rest_o + s.k;
+  w.mt.flags = w.rest_o + s.k;
   return off;
 }
 
@@ -661,9 +660,7 @@ slim_status sba_rank_independent(slim_ctx* ctx, const SbaWorkspace& w, const voi
   const IntShape& s = w.s;
   slim_status st;
   st = slim_int_clear(ctx, s, w.mt, w.rest_n, 2 * s.k);
-  if (st == SLIM_OK) st = slim_int_x_stats(ctx, s, w.mt, X_s, x_dtype, ldxs);
-  if (st == SLIM_OK) st = slim_int_w_stats(ctx, s, w.mt, W, w_dtype, ldw);
-  if (st == SLIM_OK) st = slim_int_meta(ctx, s, w.mt);
+  if (st == SLIM_OK) st = slim_int_w_meta(ctx, s, w.mt, W, w_dtype, ldw);
   if (st == SLIM_OK) st = slim_int_x_digits(ctx, s, w.mt, X_s, x_dtype, ldxs, w.Xd, w.SX);
   if (st != SLIM_OK) return st;
   CodesArgs ca;
@@ -684,8 +681,6 @@ slim_status sba_rank_independent(slim_ctx* ctx, const SbaWorkspace& w, const voi
   OutArgs oa;
   oa.s = s;
   oa.mt = w.mt;
-  oa.mstride_c = 1;
-  oa.mstride_t = 0;
   oa.rest = w.rest_n;
   oa.rest_from = 1;
   oa.token_unit = nullptr;
@@ -827,7 +822,7 @@ extern "C" slim_status slim_sba_allocate(slim_ctx* ctx, const void* W, slim_dtyp
     SLIM_LAUNCH(ctx, "sba_token_sums", sba_token_sums<SLIM_OBJ_MSE>, dim3(kl_blocks, pmax + 1), dim3(256), 0, w.part, w.lin, s, w.tokB,
                 w.block_sums, kl_blocks);
   SLIM_LAUNCH(ctx, "sba_finalize", sba_finalize, dim3(1), dim3(256), 0, w.block_sums, kl_blocks, obj, pmax, w.order, k, N,
-              w.mt.unit + 2, bits, pstar_dev);
+              w.mt.flags, bits, pstar_dev);
 
   if (!p_star && !obj_curve) return SLIM_OK;       // nothing for the host: the call does not wait
   double* host_obj = reinterpret_cast<double*>(ctx->hpin);
