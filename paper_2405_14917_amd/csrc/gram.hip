@@ -884,11 +884,6 @@ extern "C" slim_status slim_hessian_accumulate(slim_ctx* ctx, const void* X, sli
   a.super = a.interleave ? -4 : (a.tiles_main >= 192 ? 8 : 6);
   const int64_t nwg = (int64_t)a.n_main + (int64_t)tail_tiles * S * f;
 
-  const size_t pbytes = sizeof(float) * (size_t)nwg * TM * TM;
-  slim_status st = slim_ws_reserve(ctx, slim_ws_need_gram(m, t_c, ctx->num_cus > 0 ? ctx->num_cus : 256));
-  if (st != SLIM_OK) return st;
-  a.P = static_cast<float*>(slim_ws_alloc(ctx, pbytes));
-
   const bool ring = (int64_t)(TM - 1) * ldx * 2 + 128 < (int64_t(1) << 32);      // lane offsets inside 32 bits
   const bool whole = m % TM == 0 && t_c % BK == 0;
   const void* variants[8] = {reinterpret_cast<const void*>(gram_kernel<false>),
@@ -914,7 +909,11 @@ extern "C" slim_status slim_hessian_accumulate(slim_ctx* ctx, const void* X, sli
   //   4096 407 / 404;   m 11008: 2048 484 / 474, 4096 675 / 739;   m 2048 (136 tiles): 2048 37 / 38, 4096 45 / 56.
   // The error against 64 bits at 2048 tokens: m 4096 1.8e-7 / 1.3e-7, m 8192 2.7e-7 / 1.4e-7 (relative, standard normal X).
   const int nts = slim_cdiv(m, 128), small_tiles = nts * (nts + 1) / 2;
-  if (ring && small_tiles >= 200 && t_c <= 2048) {
+  const bool small = ring && small_tiles >= 200 && t_c <= 2048;
+  const size_t pbytes = sizeof(float) * (size_t)nwg * TM * TM;
+  slim_status st = slim_ws_reserve(ctx, small ? 0 : slim_ws_round(pbytes));
+  if (st != SLIM_OK) return st;
+  if (small) {
     a.G = G;
     a.ldg = ldg;
     a.kchunk = (t_c + BK - 1) / BK * BK;
@@ -931,6 +930,7 @@ extern "C" slim_status slim_hessian_accumulate(slim_ctx* ctx, const void* X, sli
     *n_tokens += t_c;
     return SLIM_OK;
   }
+  a.P = static_cast<float*>(slim_ws_alloc(ctx, pbytes));
   // Launches of the fast path.  Workgroups that share row blocks of X find each other's lines in their XCD's L2 only
   // while they are at the same tokens, i.e. while they have started together; a workgroup that starts when another
   // one ends (diagonal tiles end 14 % early) shares nothing.  With many rounds of workgroups the starts drift apart,

@@ -40,3 +40,21 @@ def test_rows_far_apart(m, t):
     Xc = X.double().contiguous()
     assert torch.equal(G.double(), Xc @ Xc.t().contiguous())
     slim.close()
+
+
+@pytest.mark.parametrize("m,t,pad", [(2696, 130, 1), (2600, 2047, 2), (2568, 64, 3), (264, 100, 1)])
+def test_a_leading_dimension_that_four_does_not_divide(m, t, pad):
+    """Tiles that add to G themselves (and those that do not), where the rows of G are not aligned to 16 bytes; what lies
+    beside the matrix stays as it is, and the tiles that add to G need no workspace."""
+    from paper_2405_14917_amd import binding
+    gen = torch.Generator(device="cuda").manual_seed(m)
+    X = torch.zeros((m, (t + 7) // 8 * 8), dtype=torch.bfloat16, device="cuda")[:, :t]
+    X.copy_(torch.randint(-8, 9, (m, t), generator=gen, device="cuda"))
+    G = torch.full((m, m + pad), 3.0, dtype=torch.float32, device="cuda")
+    slim = binding.Slim("cuda:0")
+    slim.hessian_accumulate(X, G[:, :m], 0)
+    Xc = X.double().contiguous()
+    assert torch.equal(G[:, :m].double(), Xc @ Xc.t().contiguous() + 3.0)
+    assert bool((G[:, m:] == 3.0).all())
+    assert (slim.workspace_bytes() == 0) == (m > 2560)
+    slim.close()
