@@ -55,7 +55,7 @@ struct GramArgs {
   float* P;            // partial tiles: [slot][TM][TM]
   float* G;            // the small tiles add to it themselves
   int64_t ldg;
-  int interleave;      // how the tiles are dealt to the XCDs: 0 runs, 1 interleaved, 2 patches per round (decode_work)
+  int patches;         // how the tiles are dealt to the XCDs: 0 runs, 1 patches per round (decode_work)
   int super;           // tile order: edge of a supertile in tiles, or, negative, minus the height of a band (decode_tile)
   int id_base;         // id of the launch's first workgroup (the ring kernel may be launched round by round)
   int ncu;             // workgroups per round (compute units of the device)
@@ -66,15 +66,11 @@ struct GramArgs {
 // are on the chip at the same time then cover every tile for one or two token ranges, so the chip as a whole reads
 // a narrow band of X at a time.  With the token range fastest instead (every XCD on a range of its own, the
 // requests of a moment spread over all of X) the kernel ran 4 % (m = 4096) to 10 % (m = 11008) slower, although its
-// L2s requested less.  Workgroup id mod 8 is the XCD.  Dealings of the tiles to the XCDs (`interleave`):
-//   0  runs         XCD x (ids x, x + 8, ...) is given a run of consecutive tiles of the tile order, a compact set that
-//                   shares its row blocks in that XCD's L2;
-//   1  interleaved  consecutive ids take consecutive tiles, so that every row block is wanted by all XCDs at about
-//                   the same time (what the two-stage kernel before the ring needed: it could not hide the time of a
-//                   first fetch from HBM, and a fetch that another XCD has just made is served by the memory-side
-//                   cache; kept for reference, not chosen by the host any more);
-//   2  patches      for launches that are cut into rounds: round r takes the tiles ncu r .. ncu (r + 1) - 1, XCD x the
-//                   x-th run of ncu / 8 of them, so that the XCDs of a round work on neighbouring patches.
+// L2s requested less.  Workgroup id mod 8 is the XCD.  Dealings of the tiles to the XCDs:
+//   runs       XCD x (ids x, x + 8, ...) is given a run of consecutive tiles of the tile order, a compact set that
+//              shares its row blocks in that XCD's L2;
+//   patches    for launches that are cut into rounds: round r takes the tiles ncu r .. ncu (r + 1) - 1, XCD x the
+//              x-th run of ncu / 8 of them, so that the XCDs of a round work on neighbouring patches.
 struct WorkItem {
   int tile;
   int64_t kbeg, kend;
@@ -87,12 +83,12 @@ __device__ __forceinline__ WorkItem decode_work(const GramArgs& a, int id) {
     const int j = id - split * a.tiles_main;
     // j = c + 8 q: class c owns tiles_main / 8 consecutive tiles (one more for the first tiles_main % 8 classes)
     const int c = j % 8, per = a.tiles_main / 8, rest = a.tiles_main % 8;
-    if (a.interleave == 2) {
+    if (a.patches) {
       // a round of ncu workgroups takes ncu consecutive tiles, XCD c the c-th run of ncu / 8 of them
       const int R = a.ncu, whole = (a.tiles_main / R) * R;
       w.tile = (j < whole) ? (j / R) * R + c * (R / 8) + (j % R) / 8 : j;
     } else {
-      w.tile = a.interleave ? j : c * per + min(c, rest) + j / 8;
+      w.tile = c * per + min(c, rest) + j / 8;
     }
     w.kbeg = (int64_t)split * a.kchunk;
     w.kend = min(a.t, w.kbeg + a.kchunk);
@@ -880,8 +876,8 @@ extern "C" slim_status slim_hessian_accumulate(slim_ctx* ctx, const void* X, sli
   // tiles of the band order, 32 per XCD: a patch of 4 x 8 tiles with 12 row blocks of X.  Measured at m = 11008 with
   // the L2 counters: hit rate 0.69 and 79 GB fetched per pass in 24.9 ms, against 0.58, 105 GB and 25.2 ms for 16 x 16
   // supertiles dealt round the XCDs, and 0.67, 83 GB, 25.1 ms for runs of 8 x 8 supertiles.
-  a.interleave = a.tiles_main >= 700 ? 2 : 0;
-  a.super = a.interleave ? -4 : (a.tiles_main >= 192 ? 8 : 6);
+  a.patches = a.tiles_main >= 700;
+  a.super = a.patches ? -4 : (a.tiles_main >= 192 ? 8 : 6);
   const int64_t nwg = (int64_t)a.n_main + (int64_t)tail_tiles * S * f;
 
   const bool ring = (int64_t)(TM - 1) * ldx * 2 + 128 < (int64_t(1) << 32);      // lane offsets inside 32 bits
@@ -919,7 +915,7 @@ extern "C" slim_status slim_hessian_accumulate(slim_ctx* ctx, const void* X, sli
     a.kchunk = (t_c + BK - 1) / BK * BK;
     a.S = 1;
     a.tiles_main = a.n_main = small_tiles;
-    a.interleave = 0;
+    a.patches = 0;
     a.super = 8;
     if (x_dtype == SLIM_BF16)
       SLIM_LAUNCH(ctx, "gram_mfma_bf16@gram_kernel_ring<true, 128, false>", (gram_kernel_ring<true, 128, false>), dim3(small_tiles), block,
