@@ -121,3 +121,31 @@ def test_more_groups_than_the_kernel_holds(slim):
         part = X[t0: t0 + 40]
         assert torch.equal(Y[t0: t0 + 40], slim.dequant_matmul(packed, gbits, row_off, scale, zero, beta, part))
     assert float(Y.abs().max()) > 0.0
+
+
+def plan(n, m, beta, t):
+    """The kernel's rule: tokens per tile, and groups per workgroup."""
+    cus, k, cdiv = torch.cuda.get_device_properties(0).multi_processor_count, m // beta, lambda a, b: (a + b - 1) // b
+    tile = 64 if cdiv(n, 128) * cdiv(t, 128) < 2 * cus else 128
+    want = min(k, max(1, 2 * cus // (cdiv(n, 128) * cdiv(t, tile))))
+    return tile, cdiv(k, max(1, min(want, 2 ** 22 // (t * n))))
+
+
+@pytest.mark.parametrize("t,n,m,beta,base,dtype,odd,tile,gper", [
+    (2049, 4000, 2304, 128, 1, torch.float16, True, 128, 18),     # a fold at sixteen groups and two behind it, ragged tiles
+    (2049, 4000, 2304, 128, 2, torch.bfloat16, True, 128, 18),
+    (1153, 7200, 1088, 32, 1, torch.bfloat16, False, 128, 34),    # slabs of 32 channels, one a group
+    (1200, 6700, 1536, 96, 2, torch.float16, True, 128, 16),      # three of them a group, exactly one fold
+    (1000, 4100, 2176, 128, 1, torch.bfloat16, True, 64, 17),     # tiles of 64 tokens, several groups
+    (700, 5900, 1024, 64, 2, torch.float16, False, 64, 16),
+    (200, 1000, 2304, 128, 1, torch.float16, True, 64, 2)])       # several ranges of several groups
+def test_groups_of_one_workgroup(slim, t, n, m, beta, base, dtype, odd, tile, gper):
+    """The loop over a workgroup's groups of changing width, with either tile, against the product in fp64."""
+    assert plan(n, m, beta, t) == (tile, gper)
+    rng = np.random.default_rng(t + n)
+    packed, gbits, row_off, scale, zero, What = stored(slim, rng, n, m, beta, base, odd)
+    X = torch.from_numpy(rng.standard_normal((t, m))).to(dtype).cuda()
+    Y = slim.dequant_matmul(packed, gbits, row_off, scale, zero, beta, X, bit_base=base)
+    Xd, Wd = X.double(), torch.from_numpy(What).cuda()
+    bound = 1e-5 * (Xd.abs() @ Wd.abs().t().contiguous()) + 1e-30
+    assert bool(((Y.double() - Xd @ Wd.t().contiguous()).abs() <= bound).all())
