@@ -35,9 +35,9 @@ PEAK = {"mfma_f16": 2.5e15, "mfma_i8": 5.0e15, "mfma_f64": 78.6e12, "alu_f64": 7
 # Keyed by (config, kernel function), in bytes per pass; the line reports them per launch, like `achieved`.  A
 # configuration without such a run reports null.
 TRAFFIC_BYTES = {
-    # profiles/gram_C3_hbm_traffic.md, per PASS (the launches of a pass together): FETCH_SIZE 3.973e7 KiB x 2.0 (the
-    # yardstick's 65536 KiB read as 32778), WRITE_SIZE 5.566e5 KiB x 1.0 (its 65536 KiB written read as 65536)
-    ("C3", "gram_kernel_ring<false, 256, true>"): 2.0 * 3.973e7 * 1024 + 1.0 * 5.566e5 * 1024,
+    # profiles/gram_C3_hbm_traffic.md, per PASS (the launches of a pass together): FETCH_SIZE 3.746e7 KiB x 2.0 (the
+    # yardstick's 65536 KiB read as 32778), WRITE_SIZE 5.036e5 KiB x 1.0 (its 65536 KiB written read as 65536)
+    ("C3", "gram_kernel_ring<false, 256, true>"): 2.0 * 3.746e7 * 1024 + 1.0 * 5.036e5 * 1024,
 }
 SHAPE_NAMES = {"C1": "tiny layer", "C2": "LLaMA-7B q_proj shaped layer", "C3": "LLaMA-7B down_proj shaped layer",
                "C4": "LLaMA-13B up_proj shaped layer", "C5": "LLaMA-70B-shaped MLP layer"}
@@ -190,9 +190,8 @@ def algorithmic_work(name, cfg, launches_per_step):
         "inv_diag_colsumsq": 4.0 * m * m,                # upper triangle of U (8 B) once
         "gptq_widen": 10.0 * n * m / L,                  # W (16-bit) in, fp64 working copy out
         "sba_codes": 3.0 * n * m / L,                    # 16-bit weights in, one byte out (the digits of W beside it)
-        "sba_x_digits": 6.0 * m * ts,                    # 16-bit activations in, about four bytes out
-        "sba_x_stats": 2.0 * m * ts,
-        "sba_w_stats": 2.0 * n * m,
+        "int_x_digits": 6.0 * m * ts,                    # 16-bit activations in, about four bytes out
+        "int_w_stats": 2.0 * n * m,
         "sba_kl_ref": 4.0 * 8 * n * ts / L,              # the reference outputs: read twice, written once, read once
         "sqc_block_stats": 8.0 * n * beta,
     }
@@ -390,7 +389,7 @@ def main():
         "metric": "weights_quantized_per_s", "value": cfg.n * cfg.m / (ms_per_step * 1e-3), "unit": "weights/s",
         "n_gpus": 1, "steps": args.steps, "warmup": args.warmup, "ms_per_step": ms_per_step,
         "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
-        "dtype": "f16 x f16 -> f32 (Gram MFMA), f64 (inverse, salience, SBA, SQC, GPTQ sweep), u8/u32 (pack)",
+        "dtype": "f16 x f16 -> f32 (Gram MFMA), i8 x i8 -> i32 -> f64 (SBA products, exact), f64 (inverse, salience, SQC, GPTQ sweep), u8/u32 (pack)",
         "data": "synthetic",
         "config": {"workload": workload_text(cfg), "p_star": p_star, "m_star": m_star},
         "roofline": roofline,
@@ -402,7 +401,7 @@ def main():
                           "twice the frac given",
             "inv_syrk_dgemm, inv_panel_dgemm, inv_window_dgemm, inv_trtri_*_dgemm, sba_*outputs": "run beside other "
                           "streams' work by design (the factorisation's chains, its far updates and the triangular "
-                          "inverse on four streams, beside the SBA outputs on part of the chip): their durations "
+                          "inverse on four streams, and the SBA's integer products on another): their durations "
                           "overlap and their frac is not a fraction of the chip",
             "hbm entries": "yardsticks on the same chip (plain PyTorch kernels, 1 to 4 GB): fill 6.9 TB/s, copy 4.9 to 5.3 TB/s "
                            "read plus written (0.61 to 0.66 of the peak), read-only sum 4.0 TB/s, fp16 -> fp64 conversion 3.2 TB/s",

@@ -267,23 +267,29 @@ slim_status slim_unpack_zeros(slim_ctx* ctx, const uint32_t* zpacked, int64_t ld
  *   Y[t][i] = sum_j X[t][j] * scale[i][g] * (q_ij - zero[i][g]),   g = j / beta   (Eq. 1),
  *   the codes q_ij decoded from packed / gbits / row_off exactly as slim_pack writes them.
  *   packed   m_star x n words (ld = ldp >= n);  gbits ceil(k/16) words;  row_off k+1 ints   (device)
- *   scale, zero   n x k doubles (ld = k), as written by slim_gptq_quantize (device); a zero that is a
- *            multiple of 1/2 within +-511 takes the fastest path (Eq. 1 gives integers, the sign form of width 1 uses
- *            1/2); any other finite zero (Eq. 1 does not bound -round(w_min / delta0): a group of one sign with a narrow
- *            range has a large one) is accepted and costs that (row, group) a correction term
- *   X        t_x x m, F16 or BF16, channels contiguous (ldx >= m);  t_x >= 1 tokens: up to 64 are taken 16 at a time by
- *            kernels built for the few tokens of a decoding step, more in one launch of a kernel for many tokens (where X
- *            is 16-byte aligned with ldx a multiple of 8, as the conventions above demand)
+ *   scale, zero   n x k doubles (ld = k), as written by slim_gptq_quantize (device).  Any finite zero is accepted.  The matrix
+ *            cores' operand holds code minus zero exactly for these (Eq. 1 gives integers, the sign form of width 1 uses 1/2);
+ *            any other zero (Eq. 1 does not bound -round(w_min / delta0): a group of one sign with a narrow range has a large
+ *            one) costs that (row, group) a correction term:
+ *              up to 64 tokens     integers, at width 1 also halves; |zero| <= 1022 with F16 activations (511 at width 1),
+ *                                  190 with BF16 (95 at width 1)
+ *              more than 64        integers and halves; |zero| <= 511 with F16 activations, 95 with BF16
+ *   X        t_x x m, F16 or BF16, channels contiguous (ldx >= m);  t_x >= 1 tokens: up to 64 in one launch of a kernel for the few
+ *            tokens of a decoding step, more in one launch of a kernel for many tokens (beyond 16384 groups: 64 at a time).  Both
+ *            fetch X 16 bytes at a time; where it is not 16-byte aligned with ldx a multiple of 8, as the conventions above
+ *            demand, a slower kernel takes 16 tokens at a time
  *   Y        t_x x n fp32 (ldy >= n), overwritten
  *   beta     a multiple of 32 that divides m
  *   bit_base as given to slim_pack; 1 or 2 (widths up to 5), anything else is SLIM_ERR_UNSUPPORTED.  A group whose
  *            width (from gbits and bit_base) disagrees with its rows, (row_off[g+1] - row_off[g]) * 32 != beta * width,
  *            is skipped (it adds nothing to Y): no read ever leaves the rows 0 .. row_off[k] - 1 that the stored form
  *            declares, also when it is read with the wrong bit_base
- * Arithmetic: codes and activations are exact; per (row, group) sum (q - z) x in fp32 (for fp16 activations on
- * the matrix cores, with 2 (q - z) formed exactly in fp16), times the scale rounded to fp32; the sums of group
- * ranges are added in a fixed order (deterministic, no atomics).
- * Uses the context's workspace for those partial sums.
+ * Arithmetic: codes, zeros and activations are exact; per (row, group) the sum of (code - zero) x in fp32, times the scale rounded
+ * to fp32; the sums of a row's groups are added in fp32 in a fixed order (deterministic, no atomics).  With up to 64 tokens
+ * a token's outputs are the same bytes whichever other tokens share its call; beyond that the order of its sums follows the
+ * number of tokens.
+ * For more than 64 tokens the groups of a layer that would not fill the chip are shared among workgroups, whose partial
+ * sums go to the context's workspace (and so do those of the slower kernel).
  */
 slim_status slim_dequant_matmul(slim_ctx* ctx, const uint32_t* packed, int64_t ldp, const uint32_t* gbits,
                                 const int32_t* row_off, const double* scale, const double* zero, int n, int m,

@@ -17,8 +17,8 @@
 //    lanes use, coalesced; a packed zero point is taken apart there.
 //  * The loads of a wavefront's next unit are in flight while it decodes the present one.
 //
-// What bounds it: decoding (14 vector instructions per MFMA and 16 x 32 codes, about 20 with the loads' addresses) and the
-// latency of a few loads in a row; a small layer is bound by the launch.  Against the kernels with ranges of groups (and
+// What bounds it: decoding (14 vector instructions per MFMA and 16 x 32 codes; 24 over the whole kernel at 28672 x 8192, counters,
+// with addresses, parameters and scaled sums) and the latency of a few loads in a row; a small layer is bound by the launch.  Against the kernels with ranges of groups (and
 // their reduction): 28672 x 8192 at 2 bits, fp16, 16 tokens: 55.0 -> 35.6 us (2.5 TB/s); 4096 x 11008 at 3 bits, bf16, packed
 // zero points, 5 tokens, which ran without matrix cores and unpacked the zero points in a launch of its own: 47.2 -> 15.2 us;
 // 4096 x 4096, one token: 12.9 -> 9.5 us, of which the way of the call through Python is 9.

@@ -15,8 +15,8 @@
 //  * X, the words and the parameters go from memory to LDS directly, three stages of one slab (64 channels; 32 where 64
 //    does not divide the group), two of them in flight; one wait and one barrier per slab.
 //
-// What bounds it: issue (147 vector instructions per wavefront and slab, 16 of them MFMAs, beside 90 scalar ones) and the
-// barrier per slab; the matrix cores are busy 37 % of the time.  4096 x 11008 at 2 bits, 2048 tokens: 212 us (870 TFLOP/s)
+// What bounds it: issue (counters: 9.5 vector instructions per MFMA, itself included, i.e. 152 per wavefront and slab, beside 97
+// scalar ones) and the barrier per slab; the matrix cores are busy 39 % of the time.  4096 x 11008 at 2 bits, 2048 tokens: 212 us (870 TFLOP/s)
 // against 2848 us for 128 slices of 16 tokens, each of which reads and decodes the whole layer.
 #include <algorithm>
 

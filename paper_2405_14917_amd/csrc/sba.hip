@@ -11,7 +11,9 @@
 // shift) and enter the fp64 outputs with two roundings per (row, group): fewer than the fp64 matrix cores make, which round
 // after every four channels.  What is lost: an element of a block (X_s: 32 tokens of up to 128 channels; W: up to 128 channels)
 // of bf16 or fp32 values whose last digit lies more than 53 binary digits below the block's largest element is rounded
-// there, by 2^-54 of that element.
+// there, by 2^-54 of that element.  Relative error of W X_s on 2048 channels with outlier channels (model of either form's
+// roundings against exact sums, groups of 32 to 128): 16-bit weights none in either form; fp32 weights 5e-17 to 1e-16 in
+// either form.
 //
 //   sba_rank        stable ascending rank of the k group saliences (one workgroup, counting sort by comparison; NaN
 //                   ranks last) -> order[]

@@ -673,7 +673,7 @@ def test_dequant_matmul_after_the_whole_pass(slim):
     Y = host(slim.dequant_matmul(packed, gbits, row_off, out["scale"], out["zero"], 128, Xin))
     Xn, What = host(Xin).astype(np.float64), host(out["What"])
     assert np.all(np.abs(Y - Xn @ What.T) <= 1e-5 * (np.abs(Xn) @ np.abs(What).T))
-    # more than 16 tokens are taken 16 at a time: the same numbers as the slices give one by one
+    # up to 64 tokens: the same numbers whichever other tokens share the call
     Xmany = dev(X)[:, :41].t().contiguous()
     Ymany = slim.dequant_matmul(packed, gbits, row_off, out["scale"], out["zero"], 128, Xmany)
     for t0 in (0, 16, 32):
