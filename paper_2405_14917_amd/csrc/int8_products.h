@@ -42,7 +42,7 @@ struct IntShape {
 struct IntMeta {
   int* x;                          // 2 C TB: exponent of the lowest digit in use and digits in use, per chunk and token block
   int* w;                          // 2 C: the same of the weights' digits, per chunk
-  int* flags;                      // flags[0]: non-finite inputs seen; flags[1]: every |W| is below 2^flags[1]
+  int* nonfinite;                  // non-finite inputs seen
   unsigned* wmax;                  // C largest |w| as float bits, C smallest exponent of a last digit
   int* wlsb;
 };
@@ -216,8 +216,12 @@ __device__ __forceinline__ void add_compensated(double& y, double& lo, double f,
 }
 
 // 1.5 * 2^e, e two above any partial sum of a row's integers times scale (times a token's digits, below 2^54 units): with
-// wexp the exponent above the largest weight, and W_hat and the parts it is summed from within 2^9 of that.
-__device__ __forceinline__ double sum_base(int m, int wexp) { return ldexp(1.5, 54 + (32 - __builtin_clz(m)) + 9 + 2 + wexp); }
+// wexp - ROW_EXP_BIAS the exponent above the row's largest weight, and W_hat and the parts it is summed from within 2^9 of that.
+// (About 2^24 above the sums themselves, which leaves them some 75 bits.)
+constexpr int ROW_EXP_BIAS = 2048;        // (a row of zeros keeps 0)
+__device__ __forceinline__ double sum_base(int m, int wexp) {
+  return ldexp(1.5, 54 + (32 - __builtin_clz(m)) + 9 + 2 + (wexp ? wexp - ROW_EXP_BIAS : 0));
+}
 
 __device__ __forceinline__ void lds_load16(unsigned lds_addr, unsigned voff, const char* gbase) {
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -274,6 +278,7 @@ struct OutArgs {
   const int* token_unit;           // exponent of each token's unit (INT_MIN: not finite), which mt.x counts from, or nullptr
   double* Y;                       // n x ts
   // compensated sums:
+  const int* row_exp;              // npad: exponent above the row's largest weight (sum_base)
   double* Ylo;                     // n x ts: what Y's rounding leaves (REF)
   const double *sub, *sublo;       // n x ts: subtracted from the result
 };
@@ -285,7 +290,7 @@ slimint::IntShape slim_int_shape(int n, int m, int beta, int64_t ts);
 inline int64_t slim_int_plane(const slimint::IntShape& s) { return (int64_t)s.npad * s.C * s.chk; }     // bytes of one int8 matrix
 inline size_t slim_int_digits_bytes(const slimint::IntShape& s) { return (size_t)s.C * s.TB * slimint::SI_MAXD * s.ks * 1024; }
 slim_status slim_int_clear(slim_ctx* ctx, const slimint::IntShape& s, const slimint::IntMeta& mt, int* rest, int nrest);
-// mt.w and flags[1] of W
+// mt.w
 slim_status slim_int_w_meta(slim_ctx* ctx, const slimint::IntShape& s, const slimint::IntMeta& mt, const void* W, slim_dtype dt, int64_t ldw);
 slim_status slim_int_x_digits(slim_ctx* ctx, const slimint::IntShape& s, const slimint::IntMeta& mt, const void* X, slim_dtype dt, int64_t ldx,
                               char* Xd, double* SX);

@@ -28,7 +28,7 @@ __global__ __launch_bounds__(256) void int_clear(IntMeta mt, int C, int* rest, i
     mt.wlsb[i] = INT_MAX;
   }
   if (i < nrest) rest[i] = 0;
-  if (i == 0) mt.flags[0] = 0;
+  if (i == 0) *mt.nonfinite = 0;
 }
 
 // grid (ceil(m / 1024), splits): largest magnitude and last digit of the chunk's columns of W; a thread owns four columns
@@ -59,7 +59,7 @@ __global__ __launch_bounds__(256) void int_w_stats(const T* __restrict__ W, int6
     const int c = chunk_of(ch) - c0;
     atomicMax(&lmax[c], mx);
     atomicMin(&llsb[c], lsb);
-    if (bad) atomicOr(&mt.flags[0], 1);
+    if (bad) atomicOr(mt.nonfinite, 1);
   }
   __syncthreads();
   for (int i = threadIdx.x; i < 264; i += 256)
@@ -69,27 +69,13 @@ __global__ __launch_bounds__(256) void int_w_stats(const T* __restrict__ W, int6
     }
 }
 
-// One workgroup: units and digits in use of the chunks of W, and the largest weight's exponent
+// Units and digits in use of the chunks of W
 __global__ __launch_bounds__(256) void int_w_meta(IntMeta mt, int C) {
-  __shared__ unsigned smx[256];
-  unsigned mx = 0;
-  for (int c = threadIdx.x; c < C; c += 256) {
-    mx = max(mx, mt.wmax[c]);
-    const int unit = block_unit(mt.wmax[c], mt.wlsb[c]);
-    mt.w[2 * c] = unit;
-    mt.w[2 * c + 1] = digits_for((uint64_t)fixed_point(mt.wmax[c], unit));
-  }
-  smx[threadIdx.x] = mx;
-  __syncthreads();
-  for (int st = 128; st > 0; st >>= 1) {
-    if (threadIdx.x < st) smx[threadIdx.x] = max(smx[threadIdx.x], smx[threadIdx.x + st]);
-    __syncthreads();
-  }
-  mx = smx[0];
-  unsigned mant;
-  int e0;
-  split_float(mx, mant, e0);
-  if (threadIdx.x == 0) mt.flags[1] = mx ? e0 + 32 - __builtin_clz(mant) : 0;
+  const int c = blockIdx.x * 256 + threadIdx.x;
+  if (c >= C) return;
+  const int unit = block_unit(mt.wmax[c], mt.wlsb[c]);
+  mt.w[2 * c] = unit;
+  mt.w[2 * c + 1] = digits_for((uint64_t)fixed_point(mt.wmax[c], unit));
 }
 
 // grid (ceil(TB / 4), k): a wavefront finds the unit and the digits in use of 32 tokens of every chunk of one group, cuts them
@@ -115,7 +101,7 @@ __global__ __launch_bounds__(256) void int_x_digits(const T* __restrict__ X, int
       mx = max(mx, (unsigned)__shfl_xor((int)mx, d, WAVE));
       lsb = min(lsb, __shfl_xor(lsb, d, WAVE));
     }
-    if (bad) atomicOr(&mt.flags[0], 1);
+    if (bad) atomicOr(mt.nonfinite, 1);
     const int unit = block_unit(mx, lsb), nd = digits_for((uint64_t)fixed_point(mx, unit));
     if (lane == 0) {
       mt.x[2 * ((int64_t)c * s.TB + tb)] = unit;
@@ -289,13 +275,13 @@ __global__ __launch_bounds__(256, COMP ? 4 : 3) void int_outputs(OutArgs a) {
   __syncthreads();
   auto chunk_info = [&](int c) { return __builtin_amdgcn_readfirstlane(c < SI_TAB ? tab[c] : describe(c)); };
 
-  const double base = COMP ? sum_base(s.m, a.mt.flags[1]) : 0.0;
+  auto base = [&](int r) { return COMP ? sum_base(s.m, a.row_exp[row0 + 32 * r + l32]) : 0.0; };
   double y[R][16], low[COMP ? R : 1][16];
 #pragma unroll
   for (int r = 0; r < R; ++r)
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
-      y[r][v] = base;
+      y[r][v] = base(r);
       low[COMP ? r : 0][v] = 0.0;
     }
   TL tl;
@@ -389,7 +375,7 @@ __global__ __launch_bounds__(256, COMP ? 4 : 3) void int_outputs(OutArgs a) {
       double o[4], ol[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
-        o[v] = COMP ? y[r][4 * q + v] - base : y[r][4 * q + v];
+        o[v] = COMP ? y[r][4 * q + v] - base(r) : y[r][4 * q + v];
         if (a.token_unit) o[v] = tu[v] == INT_MIN ? NAN : ldexp(o[v], tu[v]);
         if constexpr (COMP) {
           const int64_t at = (int64_t)row * s.ts + t + v;
@@ -467,7 +453,7 @@ slim_status slim_int_w_meta(slim_ctx* ctx, const IntShape& s, const IntMeta& mt,
                          : dt == SLIM_BF16 ? w_stats(ctx, s, mt, static_cast<const __hip_bfloat16*>(W), ldw)
                                            : w_stats(ctx, s, mt, static_cast<const float*>(W), ldw);
   if (st != SLIM_OK) return st;
-  SLIM_LAUNCH(ctx, "int_w_meta", int_w_meta, dim3(1), dim3(256), 0, mt, s.C);
+  SLIM_LAUNCH(ctx, "int_w_meta", int_w_meta, dim3(slim_cdiv(s.C, 256)), dim3(256), 0, mt, s.C);
   return SLIM_OK;
 }
 slim_status slim_int_x_digits(slim_ctx* ctx, const IntShape& s, const IntMeta& mt, const void* X, slim_dtype dt, int64_t ldx, char* Xd, double* SX) {

@@ -65,6 +65,7 @@ struct LwcArgs {
   char* Q;                // integers of the next product, in operand order
   double *S, *Rz;         // k x npad: their scales, and the scale times what the zero has beyond the integers
   int* rest;              // k: last step at which some row of the group had such a part
+  int* row_exp;           // npad: exponent above the row's largest weight, biased
   char* Wd;               // digits of W
   double* D;              // n x m: W_hat - W in place of the integers (group sizes that 4 does not divide), else nullptr
   const double* DG;       // n x m: D G
@@ -174,6 +175,12 @@ __global__ __launch_bounds__(256) void lwc_init(const T* __restrict__ W, LwcArgs
       a.mn[u] = mn;
       a.gamma[u] = a.betap[u] = a.init;
       a.m1g[u] = a.vg[u] = a.m1b[u] = a.vb[u] = 0.0;
+      const double top = fmax(fabs(mx), fabs(mn));
+      if (live && !a.D && top > 0.0 && top < INFINITY) {
+        int e;
+        (void)frexp(top, &e);
+        atomicMax(&a.row_exp[row], e + ROW_EXP_BIAS);
+      }
     }
     for (int j = l16 * 4; V == 4 && !a.D && j < s.nchg * s.chk; j += 64) {
       int c;
@@ -327,7 +334,7 @@ struct LwcWorkspace {
   char *Xd, *Wd, *Q;
   double *SX, *SXlo, *WG, *WGlo, *DG, *lp, *loss;
   double* par[10];
-  int *rest, *work, *token_unit;
+  int *rest, *row_exp, *work, *token_unit;
 };
 
 size_t lwc_layout(int n, int m, int beta, int steps, char* base, LwcWorkspace& w) {
@@ -354,15 +361,16 @@ size_t lwc_layout(int n, int m, int beta, int steps, char* base, LwcWorkspace& w
   w.lp = doubles((size_t)w.blocks_x * w.blocks_y);
   w.loss = doubles((size_t)steps + 1);
   for (double*& p : w.par) p = doubles((size_t)s.k * s.npad);
-  int* mi = reinterpret_cast<int*>(take(sizeof(int) * (2 * (size_t)s.C * s.TB + 4 * (size_t)s.C + (size_t)s.k + 2 + 3 * (size_t)m)));
+  int* mi = reinterpret_cast<int*>(take(sizeof(int) * (2 * (size_t)s.C * s.TB + 4 * (size_t)s.C + (size_t)s.k + (size_t)s.npad + 1 + 3 * (size_t)m)));
   w.mt.x = mi;
   mi += 2 * (size_t)s.C * s.TB;
   w.mt.w = mi;
   w.mt.wmax = reinterpret_cast<unsigned*>(mi + 2 * s.C);
   w.mt.wlsb = mi + 3 * s.C;
   w.rest = mi + 4 * s.C;
-  w.mt.flags = w.rest + s.k;
-  w.work = w.mt.flags + 2;
+  w.row_exp = w.rest + s.k;
+  w.mt.nonfinite = w.row_exp + s.npad;
+  w.work = w.mt.nonfinite + 1;
   w.token_unit = w.work + 2 * m;
   return off;
 }
@@ -467,7 +475,7 @@ extern "C" slim_status slim_lwc_quantize(slim_ctx* ctx, const void* W, slim_dtyp
   if (wide) {
     st = slim_widen_f64(ctx, "lwc_widen_g", G, SLIM_F32, m, m, ldg, reinterpret_cast<double*>(w.Xd), (int64_t)m);
   } else {
-    st = slim_int_clear(ctx, w.s, w.mt, w.rest, w.s.k);
+    st = slim_int_clear(ctx, w.s, w.mt, w.rest, w.s.k + w.s.npad);
     if (st == SLIM_OK) st = slim_int_w_meta(ctx, w.s, w.mt, W, w_dtype, ldw);
     if (st == SLIM_OK) st = slim_int_g_digits(ctx, w.s, w.mt, G, ldg, w.work, w.token_unit, w.Xd, w.SX, w.SXlo);
   }
@@ -490,6 +498,7 @@ extern "C" slim_status slim_lwc_quantize(slim_ctx* ctx, const void* W, slim_dtyp
   a.S = w.par[8];
   a.Rz = w.par[9];
   a.rest = w.rest;
+  a.row_exp = w.row_exp;
   a.Wd = w.Wd;
   a.D = wide ? w.WG : nullptr;
   a.DG = w.DG;
@@ -517,6 +526,7 @@ extern "C" slim_status slim_lwc_quantize(slim_ctx* ctx, const void* W, slim_dtyp
   oa.S = a.S;
   oa.Rz = a.Rz;
   oa.rest = w.rest;
+  oa.row_exp = w.row_exp;
   oa.rest_from = 1;
   oa.token_unit = w.token_unit;
   st = w_dtype == SLIM_F16    ? lwc_run(ctx, w, static_cast<const __half*>(W), a, oa, d, steps, beta1, beta2)

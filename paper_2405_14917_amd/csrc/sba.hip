@@ -577,7 +577,7 @@ size_t sba_layout(int n, int m, int beta, int64_t t_s, char* base, SbaWorkspace&
   w.pstar_dev = reinterpret_cast<int*>(take(256));
   w.tok = doubles(3 * (size_t)t_s);      // per token {max, log-sum-exp} of the reference; sum P log P behind
   w.tokB = w.tok + 2 * t_s;
-  int* mi = reinterpret_cast<int*>(take(sizeof(int) * (2 * (size_t)s.C * s.TB + 4 * (size_t)s.C + 2 * (size_t)s.k + 2)));
+  int* mi = reinterpret_cast<int*>(take(sizeof(int) * (2 * (size_t)s.C * s.TB + 4 * (size_t)s.C + 2 * (size_t)s.k + 1)));
   w.mt.x = mi;
   mi += 2 * (size_t)s.C * s.TB;
   w.mt.w = mi;
@@ -585,7 +585,7 @@ size_t sba_layout(int n, int m, int beta, int64_t t_s, char* base, SbaWorkspace&
   w.mt.wlsb = mi + 3 * s.C;
   w.rest_n = mi + 4 * s.C;               // per group: some row has a zero outside int8 (width N; the other width)
   w.rest_o = w.rest_n + s.k;
-  w.mt.flags = w.rest_o + s.k;
+  w.mt.nonfinite = w.rest_o + s.k;
   return off;
 }
 
@@ -686,6 +686,7 @@ slim_status sba_rank_independent(slim_ctx* ctx, const SbaWorkspace& w, const voi
   oa.rest = w.rest_n;
   oa.rest_from = 1;
   oa.token_unit = nullptr;
+  oa.row_exp = nullptr;
   oa.Ylo = nullptr;
   oa.sub = oa.sublo = nullptr;
   oa.Xd = w.Xd;
@@ -824,7 +825,7 @@ extern "C" slim_status slim_sba_allocate(slim_ctx* ctx, const void* W, slim_dtyp
     SLIM_LAUNCH(ctx, "sba_token_sums", sba_token_sums<SLIM_OBJ_MSE>, dim3(kl_blocks, pmax + 1), dim3(256), 0, w.part, w.lin, s, w.tokB,
                 w.block_sums, kl_blocks);
   SLIM_LAUNCH(ctx, "sba_finalize", sba_finalize, dim3(1), dim3(256), 0, w.block_sums, kl_blocks, obj, pmax, w.order, k, N,
-              w.mt.flags, bits, pstar_dev);
+              w.mt.nonfinite, bits, pstar_dev);
 
   if (!p_star && !obj_curve) return SLIM_OK;       // nothing for the host: the call does not wait
   double* host_obj = reinterpret_cast<double*>(ctx->hpin);

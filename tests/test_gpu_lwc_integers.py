@@ -81,15 +81,19 @@ def test_groups_that_four_does_not_divide(slim, n, m, beta, dtype, widths):
     assert torch.equal(what[: n * m].view(n, k, beta), expect)
 
 
-@pytest.mark.parametrize("n,m,beta,bits", [(3, 256, 64, 5), (2, 512, 128, 4), (5, 320, 32, 3), (2, 640, 160, 8)])
-def test_the_difference_of_the_products_keeps_its_digits(slim, n, m, beta, bits):
+@pytest.mark.parametrize("n,m,beta,bits,huge", [(3, 256, 64, 5, 1.0), (2, 512, 128, 4, 1.0), (5, 320, 32, 3, 1.0), (2, 640, 160, 8, 1.0),
+                                                (3, 256, 64, 5, 2.0 ** 36)])
+def test_the_difference_of_the_products_keeps_its_digits(slim, n, m, beta, bits, huge):
     """Weights of one sign, a thousand times their distance from W_hat and all of W_hat - W exact in fp64: the loss is then
-    W_hat G - W G to its last digits, and the digits that the two products share must not cost it any."""
+    W_hat G - W G to its last digits, and the digits that the two products share must not cost it any; nor must a row whose
+    weights are much larger (and lie on their quantiser's values)."""
     rng = np.random.default_rng(m)
     Q = 2 ** bits - 1
     W = 2.0 + rng.integers(0, 4 * Q + 1, (n, m)) * 2.0 ** -13
     W.reshape(n, m // beta, beta)[:, :, 0] = 2.0                             # delta = 4 * 2^-13, the zero point -2 / delta
     W.reshape(n, m // beta, beta)[:, :, 1] = 2.0 + 4 * Q * 2.0 ** -13
+    if huge > 1.0:
+        W[0] = (2.0 + np.rint((W[0] - 2.0) * 2.0 ** 11) * 2.0 ** -11) * huge
     X = rng.standard_normal((m, 2 * m)) * np.exp(rng.standard_normal((m, 1)))
     G = torch.from_numpy(X @ X.T).to(torch.float32)
     Wd = torch.from_numpy(W).to(torch.float32)
@@ -97,7 +101,7 @@ def test_the_difference_of_the_products_keeps_its_digits(slim, n, m, beta, bits)
     # (sigmoid(60) = 1: the whole range, the loss before any step)
     out = slim.lwc_quantize(Wd.cuda(), G.cuda(), 2 * m, widths, beta, steps=0, init=60.0, want_what=torch.float64)
     D = out["What"].cpu().numpy() - W
-    assert 0.0 < np.abs(D).max() <= 2.0 ** -12 and np.array_equal(D * 2.0 ** 13, np.rint(D * 2.0 ** 13))
+    assert 0.0 < np.abs(D).max() <= 2.0 ** -12 and (huge == 1.0 or not D[0].any()) and np.array_equal(D * 2.0 ** 13, np.rint(D * 2.0 ** 13))
     L = np.longdouble
     DG = np.stack([(D[i].astype(L)[:, None] * G.numpy().astype(L)).sum(axis=0) for i in range(n)])
     exact, terms = (D.astype(L) * DG).sum(), float((np.abs(D).astype(L) * np.abs(DG)).sum())
