@@ -191,7 +191,7 @@ def algorithmic_work(name, cfg, launches_per_step):
         "gptq_widen": 10.0 * n * m / L,                  # W (16-bit) in, fp64 working copy out
         "sba_codes": 3.0 * n * m / L,                    # 16-bit weights in, one byte out (the digits of W beside it)
         "int_x_digits": 6.0 * m * ts,                    # 16-bit activations in, about four bytes out
-        "int_w_stats": 2.0 * n * m,
+        "int_w_units": 2.0 * n * m,
         "sba_kl_ref": 4.0 * 8 * n * ts / L,              # the reference outputs: read twice, written once, read once
         "sqc_block_stats": 8.0 * n * beta,
     }

@@ -162,7 +162,7 @@ slim_status slim_salience(slim_ctx* ctx, const void* W, slim_dtype w_dtype, int 
  *   N in 2..7 (widths N - 1 .. N + 1 within 1..8; the paper's settings are N = 2, 3 and, in App. G, 4).  The
  *   products with X_s are exact integer products, the outputs and everything behind them fp64.  (An element
  *   of a bf16 or fp32 input whose last digit lies more than 53 binary digits below the largest element of its block, 32 tokens
- *   of up to 128 channels of X_s or up to 128 channels of W, is rounded there, by 2^-54 of that largest element.)
+ *   of up to 128 channels of X_s or up to 128 channels of a row of W, is rounded there, by 2^-54 of that largest element.)
  */
 slim_status slim_sba_allocate(slim_ctx* ctx, const void* W, slim_dtype w_dtype, int n, int m, int64_t ldw,
                               const double* group_sal, int beta, int N, int objective, const void* X_s,

@@ -4,7 +4,7 @@
 //   * The token side is integers times a power of two per 32 tokens of a chunk of channels (or per token), cut into signed
 //     digits (balanced: -128 .. 127); of every such block only the digits in use are kept, one to seven.
 //   * A fake-quantised weight is scale * (q - z) with a small integer q - z: one int8 matrix.  Weights as they are become
-//     digits the same way, with a power of two per chunk (two to four digits for 16-bit weights).
+//     digits the same way, with a power of two per row and chunk (two to four digits for 16-bit weights).
 //   * A chunk's products of digits are summed exactly in int32 (128 channels of 128 * 128 * 257 < 2^31 for two digits chained by
 //     a shift) and enter the fp64 outputs with one rounding per (row, group) and pair of digits: fewer than the fp64 matrix
 //     cores make, which round after every four channels.
@@ -41,10 +41,9 @@ struct IntShape {
 // What the kernels have to know about the digits.
 struct IntMeta {
   int* x;                          // 2 C TB: exponent of the lowest digit in use and digits in use, per chunk and token block
-  int* w;                          // 2 C: the same of the weights' digits, per chunk
+  int* w;                          // C: digits in use of the weights, per chunk
+  double* wunit;                   // C x npad: 2^(exponent of the lowest digit) of a row's weights in a chunk
   int* nonfinite;                  // non-finite inputs seen
-  unsigned* wmax;                  // C largest |w| as float bits, C smallest exponent of a last digit
-  int* wlsb;
 };
 
 template <typename T>
@@ -115,8 +114,9 @@ __device__ __forceinline__ int64_t operand_offset(const IntShape& s, int row, in
   chunk = g * s.nchg + cc;
   return (((int64_t)(row >> 5) * s.C + chunk) * s.ks + (jj >> 5)) * 1024 + ((jj >> 4) & 1) * 512 + (row & 31) * 16 + (jj & 15);
 }
-// the digits of four weights, plane by plane
-__device__ __forceinline__ void store_digits(char* Wd, int64_t plane, int64_t dst, const unsigned (&bits)[4], int unit, int nd) {
+// the digits of four weights in units of `wunit`, plane by plane
+__device__ __forceinline__ void store_digits(char* Wd, int64_t plane, int64_t dst, const unsigned (&bits)[4], double wunit, int nd) {
+  const int unit = ((__double2hiint(wunit) >> 20) & 2047) - 1023;
   uint64_t u[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) u[i] = digit_bytes(fixed_point(bits[i], unit));
@@ -231,13 +231,11 @@ __device__ __forceinline__ void lds_load16(unsigned lds_addr, unsigned voff, con
 #endif
 }
 
-// What a chunk's digits are, in one word: digits in use of X (3 bits) and of W (3 bits), exponents of their lowest (13 bits each).
-__device__ __forceinline__ int digits_word(const int* x) { return x[1] | ((x[0] & 8191) << 6); }
-__device__ __forceinline__ int digits_word(const int* x, const int* w) { return digits_word(x) | (w[1] << 3) | (w[0] << 19); }
+// What a chunk's digits are, in one word: digits in use of X (3 bits) and of W (3 bits), exponent of X's lowest.
+__device__ __forceinline__ int digits_word(const int* x, int w) { return x[1] | (w << 3) | (x[0] * 64); }
 __device__ __forceinline__ int digits_x(int d) { return d & 7; }
 __device__ __forceinline__ int digits_w(int d) { return (d >> 3) & 7; }
-__device__ __forceinline__ int exponent_x(int d) { return (d << 13) >> 19; }
-__device__ __forceinline__ int exponent_w(int d) { return d >> 19; }
+__device__ __forceinline__ int exponent_x(int d) { return d >> 6; }
 
 // A stage in one word: chunk, its first digit, digits (at most SI_STAGE_D), and whether it is the chunk's first.
 __device__ __forceinline__ int stage_word(int c, int lo, int nd, int first) { return (c << 8) | (first << 7) | (nd << 4) | lo; }
@@ -290,8 +288,8 @@ slimint::IntShape slim_int_shape(int n, int m, int beta, int64_t ts);
 inline int64_t slim_int_plane(const slimint::IntShape& s) { return (int64_t)s.npad * s.C * s.chk; }     // bytes of one int8 matrix
 inline size_t slim_int_digits_bytes(const slimint::IntShape& s) { return (size_t)s.C * s.TB * slimint::SI_MAXD * s.ks * 1024; }
 slim_status slim_int_clear(slim_ctx* ctx, const slimint::IntShape& s, const slimint::IntMeta& mt, int* rest, int nrest);
-// mt.w
-slim_status slim_int_w_meta(slim_ctx* ctx, const slimint::IntShape& s, const slimint::IntMeta& mt, const void* W, slim_dtype dt, int64_t ldw);
+// mt.w and mt.wunit
+slim_status slim_int_w_units(slim_ctx* ctx, const slimint::IntShape& s, const slimint::IntMeta& mt, const void* W, slim_dtype dt, int64_t ldw);
 slim_status slim_int_x_digits(slim_ctx* ctx, const slimint::IntShape& s, const slimint::IntMeta& mt, const void* X, slim_dtype dt, int64_t ldx,
                               char* Xd, double* SX);
 // The digits of a fp32 matrix with a unit per token (column): token_unit[ts]; work: 2 ts ints.

@@ -23,59 +23,53 @@ __device__ __forceinline__ void stat(unsigned bits, unsigned& mx, int& lsb, int&
 
 __global__ __launch_bounds__(256) void int_clear(IntMeta mt, int C, int* rest, int nrest) {
   const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i < C) {
-    mt.wmax[i] = 0u;
-    mt.wlsb[i] = INT_MAX;
-  }
+  if (i < C) mt.w[i] = 0;
   if (i < nrest) rest[i] = 0;
   if (i == 0) *mt.nonfinite = 0;
 }
 
-// grid (ceil(m / 1024), splits): largest magnitude and last digit of the chunk's columns of W; a thread owns four columns
-template <typename T>
-__global__ __launch_bounds__(256) void int_w_stats(const T* __restrict__ W, int64_t ldw, IntShape s, IntMeta mt) {
-  __shared__ unsigned lmax[264];
-  __shared__ int llsb[264];
-  for (int i = threadIdx.x; i < 264; i += 256) {
-    lmax[i] = 0u;
-    llsb[i] = INT_MAX;
-  }
-  __syncthreads();
-  auto chunk_of = [&](int ch) { const int g = ch / s.beta; return g * s.nchg + (ch - g * s.beta) / s.chk; };
-  const int c0 = chunk_of(blockIdx.x * 1024);
-  const int ch = blockIdx.x * 1024 + threadIdx.x * 4;
-  if (ch < s.m) {
-    unsigned mx = 0;
-    int lsb = INT_MAX, bad = 0;
-    for (int r = blockIdx.y; r < s.n; r += gridDim.y) {
-      T v[4];
-      if constexpr (sizeof(T) == 2)
-        *reinterpret_cast<uint2*>(v) = *reinterpret_cast<const uint2*>(W + (int64_t)r * ldw + ch);
-      else
-        *reinterpret_cast<uint4*>(v) = *reinterpret_cast<const uint4*>(W + (int64_t)r * ldw + ch);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) stat(float_bits<T>(v[i]), mx, lsb, bad);
-    }
-    const int c = chunk_of(ch) - c0;
-    atomicMax(&lmax[c], mx);
-    atomicMin(&llsb[c], lsb);
-    if (bad) atomicOr(mt.nonfinite, 1);
-  }
-  __syncthreads();
-  for (int i = threadIdx.x; i < 264; i += 256)
-    if (lmax[i]) {
-      atomicMax(&mt.wmax[c0 + i], lmax[i]);
-      atomicMin(&mt.wlsb[c0 + i], llsb[i]);
-    }
+template <int CTRL>
+__device__ __forceinline__ void row_stat(unsigned& mx, int& lsb) {
+  mx = max(mx, (unsigned)dpp_b32<CTRL>((int)mx));
+  lsb = min(lsb, dpp_b32<CTRL>(lsb));
 }
 
-// Units and digits in use of the chunks of W
-__global__ __launch_bounds__(256) void int_w_meta(IntMeta mt, int C) {
-  const int c = blockIdx.x * 256 + threadIdx.x;
-  if (c >= C) return;
-  const int unit = block_unit(mt.wmax[c], mt.wlsb[c]);
-  mt.w[2 * c] = unit;
-  mt.w[2 * c + 1] = digits_for((uint64_t)fixed_point(mt.wmax[c], unit));
+// grid (npad / 16, y): 16 lanes per row, groups blockIdx.y, + gridDim.y, ...: the unit of every row's chunks and the digits
+// that each chunk's widest row needs
+template <typename T>
+__global__ __launch_bounds__(256) void int_w_units(const T* __restrict__ W, int64_t ldw, IntShape s, IntMeta mt) {
+  const int lane = threadIdx.x & 63, l16 = lane & 15;
+  const int row = blockIdx.x * 16 + (threadIdx.x >> 6) * 4 + (lane >> 4);
+  const bool live = row < s.n;
+  int bad = 0;
+  for (int g = blockIdx.y; g < s.k; g += gridDim.y) {
+    const T* w = W + (int64_t)min(row, s.n - 1) * ldw + (int64_t)g * s.beta;
+    for (int cc = 0; cc < s.nchg; ++cc) {
+      const int c = g * s.nchg + cc;
+      unsigned mx = 0;
+      int lsb = INT_MAX;
+      for (int j = cc * s.chk + l16 * 4; live && j < min(s.beta, (cc + 1) * s.chk); j += 64) {
+        T v[4];
+        if constexpr (sizeof(T) == 2)
+          *reinterpret_cast<uint2*>(v) = *reinterpret_cast<const uint2*>(w + j);
+        else
+          *reinterpret_cast<uint4*>(v) = *reinterpret_cast<const uint4*>(w + j);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) stat(float_bits<T>(v[i]), mx, lsb, bad);
+      }
+      row_stat<DPP_XOR1>(mx, lsb);
+      row_stat<DPP_XOR2>(mx, lsb);
+      row_stat<DPP_HALF_MIRROR>(mx, lsb);
+      row_stat<DPP_MIRROR>(mx, lsb);
+      const int unit = block_unit(mx, lsb);
+      int nd = digits_for((uint64_t)fixed_point(mx, unit));
+      if (l16 == 0) mt.wunit[(int64_t)c * s.npad + row] = ldexp(1.0, unit);
+      nd = max(nd, __shfl_xor(nd, 16, WAVE));
+      nd = max(nd, __shfl_xor(nd, 32, WAVE));
+      if (lane == 0 && nd > mt.w[c]) atomicMax(&mt.w[c], nd);
+    }
+  }
+  if (bad) atomicOr(mt.nonfinite, 1);
 }
 
 // grid (ceil(TB / 4), k): a wavefront finds the unit and the digits in use of 32 tokens of every chunk of one group, cuts them
@@ -269,7 +263,7 @@ __global__ __launch_bounds__(256, COMP ? 4 : 3) void int_outputs(OutArgs a) {
   int* tab = reinterpret_cast<int*>(si_smem + 2 * TL::STAGE);
   auto describe = [&](int c) {
     const int* x = a.mt.x + 2 * ((int64_t)c * s.TB + tb);
-    return REF ? digits_word(x, a.mt.w + 2 * c) : digits_word(x);
+    return digits_word(x, REF ? a.mt.w[c] : 0);
   };
   for (int c = tid; c < min(s.C, SI_TAB); c += 256) tab[c] = describe(c);
   __syncthreads();
@@ -287,12 +281,7 @@ __global__ __launch_bounds__(256, COMP ? 4 : 3) void int_outputs(OutArgs a) {
   TL tl;
   auto load_first = [&](int c) {                // the first (or only) set of chunk c
     tl.load_codes(q0 + (int64_t)c * KS * 1024, rstride, lane16);
-    if (!REF) {
-      tl.load_scales(a.S + (int64_t)(c / s.nchg) * s.npad + row0, l32);
-    } else {
-#pragma unroll
-      for (int r = 0; r < R; ++r) tl.s[r] = 1.0;
-    }
+    tl.load_scales(REF ? a.mt.wunit + (int64_t)c * s.npad + row0 : a.S + (int64_t)(c / s.nchg) * s.npad + row0, l32);
   };
   auto first_stage = [&](int c, int info) { return stage_word(c, 0, min(SI_STAGE_D, digits_x(info)), 1); };
   int info = chunk_info(0), word = first_stage(0, info), buf = 0;
@@ -304,7 +293,7 @@ __global__ __launch_bounds__(256, COMP ? 4 : 3) void int_outputs(OutArgs a) {
     const bool done = left <= 0 && c + 1 == s.C;
     const int next_info = left > 0 ? info : chunk_info(min(c + 1, s.C - 1));
     const int next = left > 0 ? stage_word(c, lo + nd, min(SI_STAGE_D, left), 0) : first_stage(min(c + 1, s.C - 1), next_info);
-    const int sets = REF ? digits_w(info) : 1, unit = exponent_x(info) + (REF ? exponent_w(info) : 0);
+    const int sets = REF ? digits_w(info) : 1, unit = exponent_x(info);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     if (!done) stage_digits<KS, NW>(a.Xd, s, next, tb, lds0 + (buf ^ 1) * TL::STAGE, wave, lane);
@@ -419,8 +408,8 @@ slim_status x_digits(slim_ctx* ctx, const IntShape& s, const IntMeta& mt, const 
   return SLIM_OK;
 }
 template <typename T>
-slim_status w_stats(slim_ctx* ctx, const IntShape& s, const IntMeta& mt, const T* W, int64_t ldw) {
-  SLIM_LAUNCH(ctx, "int_w_stats", int_w_stats<T>, dim3(slim_cdiv(s.m, 1024), std::min(s.n, 128)), dim3(256), 0, W, ldw, s, mt);
+slim_status w_units(slim_ctx* ctx, const IntShape& s, const IntMeta& mt, const T* W, int64_t ldw) {
+  SLIM_LAUNCH(ctx, "int_w_units", int_w_units<T>, dim3(s.npad / 16, std::min(s.k, 8)), dim3(256), 0, W, ldw, s, mt);
   return SLIM_OK;
 }
 
@@ -448,13 +437,10 @@ slim_status slim_int_clear(slim_ctx* ctx, const IntShape& s, const IntMeta& mt, 
   SLIM_LAUNCH(ctx, "int_clear", int_clear, dim3(slim_cdiv(std::max(s.C, nrest), 256)), dim3(256), 0, mt, s.C, rest, nrest);
   return SLIM_OK;
 }
-slim_status slim_int_w_meta(slim_ctx* ctx, const IntShape& s, const IntMeta& mt, const void* W, slim_dtype dt, int64_t ldw) {
-  const slim_status st = dt == SLIM_F16    ? w_stats(ctx, s, mt, static_cast<const __half*>(W), ldw)
-                         : dt == SLIM_BF16 ? w_stats(ctx, s, mt, static_cast<const __hip_bfloat16*>(W), ldw)
-                                           : w_stats(ctx, s, mt, static_cast<const float*>(W), ldw);
-  if (st != SLIM_OK) return st;
-  SLIM_LAUNCH(ctx, "int_w_meta", int_w_meta, dim3(slim_cdiv(s.C, 256)), dim3(256), 0, mt, s.C);
-  return SLIM_OK;
+slim_status slim_int_w_units(slim_ctx* ctx, const IntShape& s, const IntMeta& mt, const void* W, slim_dtype dt, int64_t ldw) {
+  return dt == SLIM_F16    ? w_units(ctx, s, mt, static_cast<const __half*>(W), ldw)
+         : dt == SLIM_BF16 ? w_units(ctx, s, mt, static_cast<const __hip_bfloat16*>(W), ldw)
+                           : w_units(ctx, s, mt, static_cast<const float*>(W), ldw);
 }
 slim_status slim_int_x_digits(slim_ctx* ctx, const IntShape& s, const IntMeta& mt, const void* X, slim_dtype dt, int64_t ldx, char* Xd, double* SX) {
   return dt == SLIM_F16 ? x_digits(ctx, s, mt, static_cast<const __half*>(X), ldx, Xd, SX)

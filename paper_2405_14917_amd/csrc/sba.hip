@@ -6,10 +6,10 @@
 //     cut into signed base-256 digits (balanced: -128 .. 127); of every such block only the digits in use are kept, three to
 //     five for activations;
 //   * a fake-quantised weight is scale * (q - z) with a small integer q - z: one int8 matrix, and one scale per (row, group);
-//   * W itself is cut into digits the same way, with a power of two per chunk (two to four digits for 16-bit weights).
+//   * W itself is cut into digits the same way, with a power of two per row and chunk (two to four digits for 16-bit weights).
 // A chunk's products of digits are summed exactly in int32 (128 channels of 127 * 128 * 257 < 2^31 for two digits chained by a
 // shift) and enter the fp64 outputs with two roundings per (row, group): fewer than the fp64 matrix cores make, which round
-// after every four channels.  What is lost: an element of a block (X_s: 32 tokens of up to 128 channels; W: up to 128 channels)
+// after every four channels.  What is lost: an element of a block (X_s: 32 tokens of up to 128 channels; W: up to 128 channels of a row)
 // of bf16 or fp32 values whose last digit lies more than 53 binary digits below the block's largest element is rounded
 // there, by 2^-54 of that element.  Relative error of W X_s on 2048 channels with outlier channels (model of either form's
 // roundings against exact sums, groups of 32 to 128): 16-bit weights none in either form; fp32 weights 5e-17 to 1e-16 in
@@ -17,7 +17,7 @@
 //
 //   sba_rank        stable ascending rank of the k group saliences (one workgroup, counting sort by comparison; NaN
 //                   ranks last) -> order[]
-//   int_w_stats, int_w_meta, int_x_digits   which digits there are, and the digits of X_s in MFMA operand order
+//   int_w_units, int_x_digits               which digits there are, and the digits of X_s in MFMA operand order
 //   sba_codes       per (row, group): Eq. 1 / Eq. 2 at width N and at the one other width the group can take, as integers
 //                   in operand order with their scales; the digits of W
 //   int_outputs     Y^T = W X_s and Y_0^T = W_N X_s (n x t_s, fp64)
@@ -287,7 +287,7 @@ __global__ __launch_bounds__(256) void sba_codes(const T* __restrict__ W, CodesA
       if (!OTHER) {
         const unsigned bits4[4] = {__float_as_uint((float)v[0]), __float_as_uint((float)v[1]), __float_as_uint((float)v[2]),
                                    __float_as_uint((float)v[3])};
-        store_digits(a.Wd, plane, dst, bits4, a.mt.w[2 * c], a.mt.w[2 * c + 1]);
+        store_digits(a.Wd, plane, dst, bits4, a.mt.wunit[(int64_t)c * s.npad + row], a.mt.w[c]);
       }
     }
   }
@@ -577,13 +577,12 @@ size_t sba_layout(int n, int m, int beta, int64_t t_s, char* base, SbaWorkspace&
   w.pstar_dev = reinterpret_cast<int*>(take(256));
   w.tok = doubles(3 * (size_t)t_s);      // per token {max, log-sum-exp} of the reference; sum P log P behind
   w.tokB = w.tok + 2 * t_s;
-  int* mi = reinterpret_cast<int*>(take(sizeof(int) * (2 * (size_t)s.C * s.TB + 4 * (size_t)s.C + 2 * (size_t)s.k + 1)));
+  w.mt.wunit = doubles((size_t)s.C * s.npad);
+  int* mi = reinterpret_cast<int*>(take(sizeof(int) * (2 * (size_t)s.C * s.TB + (size_t)s.C + 2 * (size_t)s.k + 1)));
   w.mt.x = mi;
   mi += 2 * (size_t)s.C * s.TB;
   w.mt.w = mi;
-  w.mt.wmax = reinterpret_cast<unsigned*>(mi + 2 * s.C);
-  w.mt.wlsb = mi + 3 * s.C;
-  w.rest_n = mi + 4 * s.C;               // per group: some row has a zero outside int8 (width N; the other width)
+  w.rest_n = mi + s.C;                   // per group: some row has a zero outside int8 (width N; the other width)
   w.rest_o = w.rest_n + s.k;
   w.mt.nonfinite = w.rest_o + s.k;
   return off;
@@ -662,7 +661,7 @@ slim_status sba_rank_independent(slim_ctx* ctx, const SbaWorkspace& w, const voi
   const IntShape& s = w.s;
   slim_status st;
   st = slim_int_clear(ctx, s, w.mt, w.rest_n, 2 * s.k);
-  if (st == SLIM_OK) st = slim_int_w_meta(ctx, s, w.mt, W, w_dtype, ldw);
+  if (st == SLIM_OK) st = slim_int_w_units(ctx, s, w.mt, W, w_dtype, ldw);
   if (st == SLIM_OK) st = slim_int_x_digits(ctx, s, w.mt, X_s, x_dtype, ldxs, w.Xd, w.SX);
   if (st != SLIM_OK) return st;
   CodesArgs ca;

@@ -82,7 +82,7 @@ def test_groups_that_four_does_not_divide(slim, n, m, beta, dtype, widths):
 
 
 @pytest.mark.parametrize("n,m,beta,bits,huge", [(3, 256, 64, 5, 1.0), (2, 512, 128, 4, 1.0), (5, 320, 32, 3, 1.0), (2, 640, 160, 8, 1.0),
-                                                (3, 256, 64, 5, 2.0 ** 36)])
+                                                (3, 256, 64, 5, 2.0 ** 36), (3, 256, 64, 5, 2.0 ** 60)])
 def test_the_difference_of_the_products_keeps_its_digits(slim, n, m, beta, bits, huge):
     """Weights of one sign, a thousand times their distance from W_hat and all of W_hat - W exact in fp64: the loss is then
     W_hat G - W G to its last digits, and the digits that the two products share must not cost it any; nor must a row whose

@@ -80,15 +80,19 @@ def test_sums_of_wide_groups(slim, beta, groups):
     assert np.allclose(curve, obj_o, rtol=1e-9), (curve, obj_o)
 
 
-@pytest.mark.parametrize("huge", ["X", "W"])
+@pytest.mark.parametrize("huge", ["X", "W", "row of W"])
 def test_blocks_of_very_different_size(slim, huge):
     """Elements that are a hundred binary digits larger than the others, and that meet zeros: the others keep their digits."""
     n, m, beta, ts = 40, 512, 128, 96
     W, X, d = layer(9, n, m, ts, torch.float32, torch.bfloat16, 0)
     X[m // 2] = torch.randn(ts).to(torch.bfloat16)
-    W[:, beta: 2 * beta] = 0.0
-    X[beta: 2 * beta] = 0.0
-    (X if huge == "X" else W.t())[beta: 2 * beta] = 2.0 ** 100
+    if huge == "row of W":                            # in the same channels as the others' weights
+        W[7], X[beta: beta + 16] = 0.0, 0.0
+        W[7, beta: beta + 16] = 2.0 ** 100
+    else:
+        W[:, beta: 2 * beta] = 0.0
+        X[beta: 2 * beta] = 0.0
+        (X if huge == "X" else W.t())[beta: 2 * beta] = 2.0 ** 100
     gs = d[: m // beta].numpy().copy()
     bits_o, p_o, obj_o, margin = orc.sba_allocate(W.double().numpy(), gs, beta, 2, X.double().numpy(), objective=orc.OBJ_MSE)
     bits, p, curve = slim.sba_allocate(W.cuda(), torch.from_numpy(gs).cuda(), beta, 2, X.cuda(), objective=1)
