@@ -41,7 +41,7 @@ struct IntShape {
 // What the kernels have to know about the digits.
 struct IntMeta {
   int* x;                          // 2 C TB: exponent of the lowest digit in use and digits in use, per chunk and token block
-  int* w;                          // C: digits in use of the weights, per chunk
+  uint8_t* w;                      // C x npad / 16: digits in use of 16 rows of a chunk of W, a bit for each
   double* wunit;                   // C x npad: 2^(exponent of the lowest digit) of a row's weights in a chunk
   int* nonfinite;                  // non-finite inputs seen
 };
@@ -71,11 +71,11 @@ __device__ __forceinline__ int block_unit(unsigned mx, int lsb) {
   split_float(mx, mant, e0);
   return mx ? max(lsb, e0 + (31 - __builtin_clz(mant)) - 53) : 0;
 }
-// balanced digits that hold magnitudes up to v
+// balanced digits that hold magnitudes up to v (of at most 55 bits): nd of them reach 0x7f..7f
 __device__ __forceinline__ int digits_for(uint64_t v) {
-  int nd = 0;
-  for (uint64_t lim = 0; lim < v; ++nd) lim = lim * 256 + 127;
-  return nd;
+  if (v == 0) return 0;
+  const int nd = (64 - __builtin_clzll(v)) / 8 + 1;
+  return nd + (v > 0x007f7f7f7f7f7f7full >> (56 - 8 * min(nd, 7)) ? 1 : 0);
 }
 // v / 2^unit as an integer (rounded where v has digits below the unit); 0 for what is not finite
 __device__ __forceinline__ int64_t fixed_point(unsigned bits, int unit) {
@@ -113,6 +113,13 @@ __device__ __forceinline__ int64_t operand_offset(const IntShape& s, int row, in
   const int cc = j / s.chk, jj = j - cc * s.chk;
   chunk = g * s.nchg + cc;
   return (((int64_t)(row >> 5) * s.C + chunk) * s.ks + (jj >> 5)) * 1024 + ((jj >> 4) & 1) * 512 + (row & 31) * 16 + (jj & 15);
+}
+// digits in use of the weights of the 256 rows around `row` in a chunk
+__device__ __forceinline__ int digits_of_rows(const IntShape& s, const uint8_t* w, int c, int row) {
+  const uint4 m = *reinterpret_cast<const uint4*>(w + (int64_t)c * (s.npad / 16) + (row / SI_ROWS) * (SI_ROWS / 16));
+  unsigned u = (m.x | m.y) | (m.z | m.w);
+  u |= u >> 16;
+  return __popc((u | (u >> 8)) & 255u);
 }
 // the digits of four weights in units of `wunit`, plane by plane
 __device__ __forceinline__ void store_digits(char* Wd, int64_t plane, int64_t dst, const unsigned (&bits)[4], double wunit, int nd) {
@@ -287,7 +294,7 @@ struct OutArgs {
 slimint::IntShape slim_int_shape(int n, int m, int beta, int64_t ts);
 inline int64_t slim_int_plane(const slimint::IntShape& s) { return (int64_t)s.npad * s.C * s.chk; }     // bytes of one int8 matrix
 inline size_t slim_int_digits_bytes(const slimint::IntShape& s) { return (size_t)s.C * s.TB * slimint::SI_MAXD * s.ks * 1024; }
-slim_status slim_int_clear(slim_ctx* ctx, const slimint::IntShape& s, const slimint::IntMeta& mt, int* rest, int nrest);
+slim_status slim_int_clear(slim_ctx* ctx, const slimint::IntMeta& mt, int* rest, int nrest);
 // mt.w and mt.wunit
 slim_status slim_int_w_units(slim_ctx* ctx, const slimint::IntShape& s, const slimint::IntMeta& mt, const void* W, slim_dtype dt, int64_t ldw);
 slim_status slim_int_x_digits(slim_ctx* ctx, const slimint::IntShape& s, const slimint::IntMeta& mt, const void* X, slim_dtype dt, int64_t ldx,

@@ -21,55 +21,60 @@ __device__ __forceinline__ void stat(unsigned bits, unsigned& mx, int& lsb, int&
   lsb = min(lsb, e0 + __builtin_ctz(mant));
 }
 
-__global__ __launch_bounds__(256) void int_clear(IntMeta mt, int C, int* rest, int nrest) {
+__global__ __launch_bounds__(256) void int_clear(IntMeta mt, int* rest, int nrest) {
   const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i < C) mt.w[i] = 0;
   if (i < nrest) rest[i] = 0;
   if (i == 0) *mt.nonfinite = 0;
 }
 
-template <int CTRL>
-__device__ __forceinline__ void row_stat(unsigned& mx, int& lsb) {
-  mx = max(mx, (unsigned)dpp_b32<CTRL>((int)mx));
-  lsb = min(lsb, dpp_b32<CTRL>(lsb));
-}
-
-// grid (npad / 16, y): 16 lanes per row, groups blockIdx.y, + gridDim.y, ...: the unit of every row's chunks and the digits
-// that each chunk's widest row needs
+// grid (npad / 16, y): a wavefront takes 16 rows of a group, 4 lanes each, groups 4 blockIdx.y + wavefront and so on: the unit of
+// every row's chunks, and the digits that the 16 rows of a chunk need.  (With 16 lanes a row and atomics for the digits of
+// a chunk 156 us on 4096 x 4096.)
 template <typename T>
 __global__ __launch_bounds__(256) void int_w_units(const T* __restrict__ W, int64_t ldw, IntShape s, IntMeta mt) {
-  const int lane = threadIdx.x & 63, l16 = lane & 15;
-  const int row = blockIdx.x * 16 + (threadIdx.x >> 6) * 4 + (lane >> 4);
+  const int lane = threadIdx.x & 63, l4 = lane & 3;
+  const int row = blockIdx.x * 16 + (lane >> 2);
   const bool live = row < s.n;
-  int bad = 0;
-  for (int g = blockIdx.y; g < s.k; g += gridDim.y) {
+  unsigned top = 0;
+  for (int g = blockIdx.y * 4 + (threadIdx.x >> 6); g < s.k; g += gridDim.y * 4) {
     const T* w = W + (int64_t)min(row, s.n - 1) * ldw + (int64_t)g * s.beta;
     for (int cc = 0; cc < s.nchg; ++cc) {
       const int c = g * s.nchg + cc;
       unsigned mx = 0;
       int lsb = INT_MAX;
-      for (int j = cc * s.chk + l16 * 4; live && j < min(s.beta, (cc + 1) * s.chk); j += 64) {
+#pragma unroll 8
+      for (int j = cc * s.chk + l4 * 4; j < min(s.beta, (cc + 1) * s.chk); j += 16) {
         T v[4];
         if constexpr (sizeof(T) == 2)
           *reinterpret_cast<uint2*>(v) = *reinterpret_cast<const uint2*>(w + j);
         else
           *reinterpret_cast<uint4*>(v) = *reinterpret_cast<const uint4*>(w + j);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) stat(float_bits<T>(v[i]), mx, lsb, bad);
+        for (int i = 0; i < 4; ++i) {
+          const unsigned bits = float_bits<T>(v[i]) & 0x7fffffffu;
+          unsigned mant;
+          int e0;
+          split_float(bits, mant, e0);
+          mx = max(mx, bits);
+          lsb = min(lsb, bits ? e0 + __builtin_ctz(mant | 0x80000000u) : INT_MAX);
+        }
       }
-      row_stat<DPP_XOR1>(mx, lsb);
-      row_stat<DPP_XOR2>(mx, lsb);
-      row_stat<DPP_HALF_MIRROR>(mx, lsb);
-      row_stat<DPP_MIRROR>(mx, lsb);
+      mx = max(mx, (unsigned)dpp_b32<DPP_XOR1>((int)mx));
+      mx = max(mx, (unsigned)dpp_b32<DPP_XOR2>((int)mx));
+      lsb = min(lsb, dpp_b32<DPP_XOR1>(lsb));
+      lsb = min(lsb, dpp_b32<DPP_XOR2>(lsb));
+      if (!live) mx = 0;
+      top = max(top, mx);
+      // (a row with elements that are not finite has no sums: any unit will do)
       const int unit = block_unit(mx, lsb);
-      int nd = digits_for((uint64_t)fixed_point(mx, unit));
-      if (l16 == 0) mt.wunit[(int64_t)c * s.npad + row] = ldexp(1.0, unit);
-      nd = max(nd, __shfl_xor(nd, 16, WAVE));
-      nd = max(nd, __shfl_xor(nd, 32, WAVE));
-      if (lane == 0 && nd > mt.w[c]) atomicMax(&mt.w[c], nd);
+      unsigned used = (1u << digits_for((uint64_t)fixed_point(mx, unit))) - 1u;
+      if (l4 == 0) mt.wunit[(int64_t)c * s.npad + row] = ldexp(1.0, unit);
+#pragma unroll
+      for (int d = 4; d < 64; d <<= 1) used |= (unsigned)__shfl_xor((int)used, d, WAVE);
+      if (lane == 0) mt.w[(int64_t)c * (s.npad / 16) + blockIdx.x] = (uint8_t)used;
     }
   }
-  if (bad) atomicOr(mt.nonfinite, 1);
+  if (top >= 0x7f800000u) atomicOr(mt.nonfinite, 1);
 }
 
 // grid (ceil(TB / 4), k): a wavefront finds the unit and the digits in use of 32 tokens of every chunk of one group, cuts them
@@ -263,7 +268,7 @@ __global__ __launch_bounds__(256, COMP ? 4 : 3) void int_outputs(OutArgs a) {
   int* tab = reinterpret_cast<int*>(si_smem + 2 * TL::STAGE);
   auto describe = [&](int c) {
     const int* x = a.mt.x + 2 * ((int64_t)c * s.TB + tb);
-    return digits_word(x, REF ? a.mt.w[c] : 0);
+    return digits_word(x, REF ? digits_of_rows(s, a.mt.w, c, row0) : 0);
   };
   for (int c = tid; c < min(s.C, SI_TAB); c += 256) tab[c] = describe(c);
   __syncthreads();
@@ -409,7 +414,7 @@ slim_status x_digits(slim_ctx* ctx, const IntShape& s, const IntMeta& mt, const 
 }
 template <typename T>
 slim_status w_units(slim_ctx* ctx, const IntShape& s, const IntMeta& mt, const T* W, int64_t ldw) {
-  SLIM_LAUNCH(ctx, "int_w_units", int_w_units<T>, dim3(s.npad / 16, std::min(s.k, 8)), dim3(256), 0, W, ldw, s, mt);
+  SLIM_LAUNCH(ctx, "int_w_units", int_w_units<T>, dim3(s.npad / 16, std::min(slim_cdiv(s.k, 4), 8)), dim3(256), 0, W, ldw, s, mt);
   return SLIM_OK;
 }
 
@@ -433,8 +438,8 @@ IntShape slim_int_shape(int n, int m, int beta, int64_t t_s) {
   return s;
 }
 
-slim_status slim_int_clear(slim_ctx* ctx, const IntShape& s, const IntMeta& mt, int* rest, int nrest) {
-  SLIM_LAUNCH(ctx, "int_clear", int_clear, dim3(slim_cdiv(std::max(s.C, nrest), 256)), dim3(256), 0, mt, s.C, rest, nrest);
+slim_status slim_int_clear(slim_ctx* ctx, const IntMeta& mt, int* rest, int nrest) {
+  SLIM_LAUNCH(ctx, "int_clear", int_clear, dim3(slim_cdiv(nrest, 256)), dim3(256), 0, mt, rest, nrest);
   return SLIM_OK;
 }
 slim_status slim_int_w_units(slim_ctx* ctx, const IntShape& s, const IntMeta& mt, const void* W, slim_dtype dt, int64_t ldw) {

@@ -189,7 +189,7 @@ __global__ __launch_bounds__(256) void lwc_init(const T* __restrict__ W, LwcArgs
       if (live && j < s.beta) load4<T>(w + j, v);
       const unsigned bits4[4] = {__float_as_uint((float)v[0]), __float_as_uint((float)v[1]), __float_as_uint((float)v[2]),
                                  __float_as_uint((float)v[3])};
-      store_digits(a.Wd, plane, dst, bits4, a.mt.wunit[(int64_t)c * s.npad + row], a.mt.w[c]);
+      store_digits(a.Wd, plane, dst, bits4, a.mt.wunit[(int64_t)c * s.npad + row], digits_of_rows(s, a.mt.w, c, row));
     }
     const LwcGroup p = lwc_group(mx, mn, a.init, a.init, min(max((int)a.bits[g], 1), 8));
     write_integers<T, V>(a, w, row, g, l16, live, p);
@@ -362,11 +362,11 @@ size_t lwc_layout(int n, int m, int beta, int steps, char* base, LwcWorkspace& w
   w.loss = doubles((size_t)steps + 1);
   for (double*& p : w.par) p = doubles((size_t)s.k * s.npad);
   w.mt.wunit = doubles(ints ? (size_t)s.C * s.npad : 0);
-  int* mi = reinterpret_cast<int*>(take(sizeof(int) * (2 * (size_t)s.C * s.TB + (size_t)s.C + (size_t)s.k + (size_t)s.npad + 1 + 3 * (size_t)m)));
+  w.mt.w = reinterpret_cast<uint8_t*>(take(ints ? (size_t)s.C * (s.npad / 16) : 0));
+  int* mi = reinterpret_cast<int*>(take(sizeof(int) * (2 * (size_t)s.C * s.TB + (size_t)s.k + (size_t)s.npad + 1 + 3 * (size_t)m)));
   w.mt.x = mi;
   mi += 2 * (size_t)s.C * s.TB;
-  w.mt.w = mi;
-  w.rest = mi + s.C;
+  w.rest = mi;
   w.row_exp = w.rest + s.k;
   w.mt.nonfinite = w.row_exp + s.npad;
   w.work = w.mt.nonfinite + 1;
@@ -474,7 +474,7 @@ extern "C" slim_status slim_lwc_quantize(slim_ctx* ctx, const void* W, slim_dtyp
   if (wide) {
     st = slim_widen_f64(ctx, "lwc_widen_g", G, SLIM_F32, m, m, ldg, reinterpret_cast<double*>(w.Xd), (int64_t)m);
   } else {
-    st = slim_int_clear(ctx, w.s, w.mt, w.rest, w.s.k + w.s.npad);
+    st = slim_int_clear(ctx, w.mt, w.rest, w.s.k + w.s.npad);
     if (st == SLIM_OK) st = slim_int_w_units(ctx, w.s, w.mt, W, w_dtype, ldw);
     if (st == SLIM_OK) st = slim_int_g_digits(ctx, w.s, w.mt, G, ldg, w.work, w.token_unit, w.Xd, w.SX, w.SXlo);
   }

@@ -29,8 +29,8 @@
 //   sba_finalize    first minimum of obj, bit vector of p*
 //
 // Measured on 28672 x 8192, 2048 tokens, beside the inverse where it runs there (fp64 matrix cores -> this): outputs 32 ->
-// 10.6 ms (reference 7.8, width N 2.8), search 15.2 -> 6.4 ms, widening and fake quantisation 3.4 -> 1.0 ms; 4096 x 4096:
-// 3.5 -> 0.8, 1.19 -> 0.47 ms.  The fp64 products ran at 76 to 81 % of their roof.
+// 8.9 ms (reference 6.1, width N 2.8), search 15.2 -> 6.0 ms, widening and fake quantisation 3.4 -> 1.6 ms; 4096 x 4096:
+// 3.5 -> 0.7, 1.19 -> 0.43 ms.  The fp64 products ran at 76 to 81 % of their roof.
 #include <algorithm>
 
 #include "int8_products.h"
@@ -287,7 +287,7 @@ __global__ __launch_bounds__(256) void sba_codes(const T* __restrict__ W, CodesA
       if (!OTHER) {
         const unsigned bits4[4] = {__float_as_uint((float)v[0]), __float_as_uint((float)v[1]), __float_as_uint((float)v[2]),
                                    __float_as_uint((float)v[3])};
-        store_digits(a.Wd, plane, dst, bits4, a.mt.wunit[(int64_t)c * s.npad + row], a.mt.w[c]);
+        store_digits(a.Wd, plane, dst, bits4, a.mt.wunit[(int64_t)c * s.npad + row], digits_of_rows(s, a.mt.w, c, row));
       }
     }
   }
@@ -578,11 +578,11 @@ size_t sba_layout(int n, int m, int beta, int64_t t_s, char* base, SbaWorkspace&
   w.tok = doubles(3 * (size_t)t_s);      // per token {max, log-sum-exp} of the reference; sum P log P behind
   w.tokB = w.tok + 2 * t_s;
   w.mt.wunit = doubles((size_t)s.C * s.npad);
-  int* mi = reinterpret_cast<int*>(take(sizeof(int) * (2 * (size_t)s.C * s.TB + (size_t)s.C + 2 * (size_t)s.k + 1)));
+  w.mt.w = reinterpret_cast<uint8_t*>(take((size_t)s.C * (s.npad / 16)));
+  int* mi = reinterpret_cast<int*>(take(sizeof(int) * (2 * (size_t)s.C * s.TB + 2 * (size_t)s.k + 1)));
   w.mt.x = mi;
   mi += 2 * (size_t)s.C * s.TB;
-  w.mt.w = mi;
-  w.rest_n = mi + s.C;                   // per group: some row has a zero outside int8 (width N; the other width)
+  w.rest_n = mi;                         // per group: some row has a zero outside int8 (width N; the other width)
   w.rest_o = w.rest_n + s.k;
   w.mt.nonfinite = w.rest_o + s.k;
   return off;
@@ -660,7 +660,7 @@ slim_status sba_rank_independent(slim_ctx* ctx, const SbaWorkspace& w, const voi
                                  int64_t ldxs, int q1_mode) {
   const IntShape& s = w.s;
   slim_status st;
-  st = slim_int_clear(ctx, s, w.mt, w.rest_n, 2 * s.k);
+  st = slim_int_clear(ctx, w.mt, w.rest_n, 2 * s.k);
   if (st == SLIM_OK) st = slim_int_w_units(ctx, s, w.mt, W, w_dtype, ldw);
   if (st == SLIM_OK) st = slim_int_x_digits(ctx, s, w.mt, X_s, x_dtype, ldxs, w.Xd, w.SX);
   if (st != SLIM_OK) return st;
