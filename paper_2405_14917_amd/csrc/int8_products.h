@@ -6,8 +6,8 @@
 //   * A fake-quantised weight is scale * (q - z) with a small integer q - z: one int8 matrix.  Weights as they are become
 //     digits the same way, with a power of two per row and chunk (two to four digits for 16-bit weights).
 //   * A chunk's products of digits are summed exactly in int32 (128 channels of 128 * 128 * 257 < 2^31 for two digits chained by
-//     a shift) and enter the fp64 outputs with one rounding per (row, group) and pair of digits: fewer than the fp64 matrix
-//     cores make, which round after every four channels.
+//     a shift) and enter the fp64 outputs with one rounding per pair of digits; the fp64 matrix cores round after every four
+//     channels.
 #ifndef SLIM_INT8_PRODUCTS_H
 #define SLIM_INT8_PRODUCTS_H
 

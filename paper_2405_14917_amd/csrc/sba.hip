@@ -8,10 +8,10 @@
 //   * a fake-quantised weight is scale * (q - z) with a small integer q - z: one int8 matrix, and one scale per (row, group);
 //   * W itself is cut into digits the same way, with a power of two per row and chunk (two to four digits for 16-bit weights).
 // A chunk's products of digits are summed exactly in int32 (128 channels of 127 * 128 * 257 < 2^31 for two digits chained by a
-// shift) and enter the fp64 outputs with two roundings per (row, group): fewer than the fp64 matrix cores make, which round
-// after every four channels.  What is lost: an element of a block (X_s: 32 tokens of up to 128 channels; W: up to 128 channels of a row)
+// shift) and enter the fp64 outputs with a rounding per pair of digits; the fp64 matrix cores round after every four channels.
+// What is lost: an element of a block (X_s: 32 tokens of up to 128 channels; W: up to 128 channels of a row)
 // of bf16 or fp32 values whose last digit lies more than 53 binary digits below the block's largest element is rounded
-// there, by 2^-54 of that element.  Relative error of W X_s on 2048 channels with outlier channels (model of either form's
+// there, by 2^-54 of that element (the objective, a sum over tokens and outputs, holds no more of it).  Relative error of W X_s on 2048 channels with outlier channels (model of either form's
 // roundings against exact sums, groups of 32 to 128): 16-bit weights none in either form; fp32 weights 5e-17 to 1e-16 in
 // either form.
 //
