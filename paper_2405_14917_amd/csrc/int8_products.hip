@@ -247,19 +247,23 @@ __global__ __launch_bounds__(256) void int_g_digits(const float* __restrict__ G,
 
 // REF: Y = W X_s from the digits of W; else Y = W_N X_s.
 // COMP: sums to twice the precision, for W_hat X - W X (add_compensated).  Four vector instructions per output and pair of
-// digits in place of one, and twice the registers, so one tile per wavefront and four wavefronts per SIMD: 4096 x 4096 against
-// 4096 columns 507 -> 692 us (two tiles and two wavefronts 714, one and three 766).
+// digits in place of one, and twice the registers, so one tile per wavefront and four wavefronts per SIMD (two tiles and two
+// wavefronts, or one and three, are slower).  Those four leave little to hide a barrier behind, so a stage holds all digits of a
+// chunk, eight wavefronts share it, and a wavefront in its MFMAs goes before one in its sums: 4096 x 4096 against 4096 columns
+// 690 -> 625 us.  What bounds it is the vector work: 491 us with one instruction in place of the four, 590 to 600 without the
+// codes' or the digits' way from memory.
 template <int KS, bool REF, bool COMP>
-__global__ __launch_bounds__(256, COMP ? 4 : 3) void int_outputs(OutArgs a) {
-  constexpr int R = COMP ? 1 : 2, NW = 4;
-  using TL = Tile<KS, R>;
+__global__ __launch_bounds__(COMP ? 512 : 256, COMP ? 4 : 3) void int_outputs(OutArgs a) {
+  constexpr int R = COMP ? 1 : 2, NW = COMP ? 8 : 4;
+  constexpr int SD = COMP ? SI_MAXD : SI_STAGE_D;
+  using TL = Tile<KS, R, SD>;
   extern __shared__ __align__(16) char si_smem[];
   const IntShape& s = a.s;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, h = lane >> 5;
   int rt, tb;
-  tile_of(blockIdx.x, s.npad / (128 * R), s.TB, rt, tb);
-  const int row0 = rt * 128 * R + wave * 32 * R;
+  tile_of(blockIdx.x, s.RT, s.TB, rt, tb);
+  const int row0 = rt * SI_ROWS + wave * 32 * R;
   const unsigned lds0 = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(uintptr_t)((__attribute__((address_space(3))) char*)si_smem));
   const int64_t rstride = (int64_t)s.C * KS * 1024;
   const char* q0 = a.Q + (int64_t)(row0 >> 5) * rstride;
@@ -270,7 +274,7 @@ __global__ __launch_bounds__(256, COMP ? 4 : 3) void int_outputs(OutArgs a) {
     const int* x = a.mt.x + 2 * ((int64_t)c * s.TB + tb);
     return digits_word(x, REF ? digits_of_rows(s, a.mt.w, c, row0) : 0);
   };
-  for (int c = tid; c < min(s.C, SI_TAB); c += 256) tab[c] = describe(c);
+  for (int c = tid; c < min(s.C, SI_TAB); c += 64 * NW) tab[c] = describe(c);
   __syncthreads();
   auto chunk_info = [&](int c) { return __builtin_amdgcn_readfirstlane(c < SI_TAB ? tab[c] : describe(c)); };
 
@@ -288,7 +292,7 @@ __global__ __launch_bounds__(256, COMP ? 4 : 3) void int_outputs(OutArgs a) {
     tl.load_codes(q0 + (int64_t)c * KS * 1024, rstride, lane16);
     tl.load_scales(REF ? a.mt.wunit + (int64_t)c * s.npad + row0 : a.S + (int64_t)(c / s.nchg) * s.npad + row0, l32);
   };
-  auto first_stage = [&](int c, int info) { return stage_word(c, 0, min(SI_STAGE_D, digits_x(info)), 1); };
+  auto first_stage = [&](int c, int info) { return stage_word(c, 0, min(SD, digits_x(info)), 1); };
   int info = chunk_info(0), word = first_stage(0, info), buf = 0;
   stage_digits<KS, NW>(a.Xd, s, word, tb, lds0, wave, lane);
   load_first(0);
@@ -297,7 +301,7 @@ __global__ __launch_bounds__(256, COMP ? 4 : 3) void int_outputs(OutArgs a) {
     const int left = digits_x(info) - lo - nd;                              // digits of the chunk behind this stage
     const bool done = left <= 0 && c + 1 == s.C;
     const int next_info = left > 0 ? info : chunk_info(min(c + 1, s.C - 1));
-    const int next = left > 0 ? stage_word(c, lo + nd, min(SI_STAGE_D, left), 0) : first_stage(min(c + 1, s.C - 1), next_info);
+    const int next = left > 0 ? stage_word(c, lo + nd, min(SD, left), 0) : first_stage(min(c + 1, s.C - 1), next_info);
     const int sets = REF ? digits_w(info) : 1, unit = exponent_x(info);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
@@ -310,7 +314,9 @@ __global__ __launch_bounds__(256, COMP ? 4 : 3) void int_outputs(OutArgs a) {
     for (int j = 0; j < sets; ++j) {
       for (int p = (nd - 1) >> 1; p >= 0; --p) {
         v16i acc[R];
+        if constexpr (COMP) __builtin_amdgcn_s_setprio(1);
         tl.pair(x, p, 2 * p + 1 < nd, acc);
+        if constexpr (COMP) __builtin_amdgcn_s_setprio(0);
         if (p == 0) {
           if (j + 1 < sets)
             tl.load_codes(q0 + (j + 1) * a.plane + (int64_t)c * KS * 1024, rstride, lane16);
@@ -391,18 +397,18 @@ __global__ __launch_bounds__(256, COMP ? 4 : 3) void int_outputs(OutArgs a) {
 
 template <int KS>
 slim_status outputs_launch(slim_ctx* ctx, const char* name, const OutArgs& a, bool ref, bool compensated) {
-  const dim3 grid((compensated ? 2 * a.s.RT : a.s.RT) * a.s.TB);
-  const size_t smem = 2 * Tile<KS, 2>::STAGE + sizeof(int) * std::min(a.s.C, SI_TAB);
+  const dim3 grid(a.s.RT * a.s.TB), block(compensated ? 512 : 256);
+  const size_t smem = 2 * (compensated ? Tile<KS, 1, SI_MAXD>::STAGE : Tile<KS, 2>::STAGE) + sizeof(int) * std::min(a.s.C, SI_TAB);
   if (compensated) {
     if (ref)
-      SLIM_LAUNCH(ctx, name, (int_outputs<KS, true, true>), grid, dim3(256), smem, a);
+      SLIM_LAUNCH(ctx, name, (int_outputs<KS, true, true>), grid, block, smem, a);
     else
-      SLIM_LAUNCH(ctx, name, (int_outputs<KS, false, true>), grid, dim3(256), smem, a);
+      SLIM_LAUNCH(ctx, name, (int_outputs<KS, false, true>), grid, block, smem, a);
   } else {
     if (ref)
-      SLIM_LAUNCH(ctx, name, (int_outputs<KS, true, false>), grid, dim3(256), smem, a);
+      SLIM_LAUNCH(ctx, name, (int_outputs<KS, true, false>), grid, block, smem, a);
     else
-      SLIM_LAUNCH(ctx, name, (int_outputs<KS, false, false>), grid, dim3(256), smem, a);
+      SLIM_LAUNCH(ctx, name, (int_outputs<KS, false, false>), grid, block, smem, a);
   }
   return SLIM_OK;
 }
