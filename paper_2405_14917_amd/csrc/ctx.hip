@@ -52,7 +52,6 @@ slim_status slim_ensure_side(slim_ctx* ctx) {
   if (ctx->side) return SLIM_OK;
   SLIM_HIP_TRY(ctx, hipStreamCreateWithFlags(&ctx->side, hipStreamNonBlocking));
   SLIM_HIP_TRY(ctx, hipStreamCreateWithFlags(&ctx->side2, hipStreamNonBlocking));
-  SLIM_HIP_TRY(ctx, hipStreamCreateWithFlags(&ctx->side3, hipStreamNonBlocking));
   for (hipEvent_t& e : ctx->ev) SLIM_HIP_TRY(ctx, hipEventCreateWithFlags(&e, hipEventDisableTiming));
   return SLIM_OK;
 }
@@ -161,15 +160,13 @@ slim_status slim_destroy(slim_ctx* ctx) {
   }
   for (hipEvent_t ev : ctx->free_events) (void)hipEventDestroy(ev);
   if (ctx->side) {
-    (void)hipStreamSynchronize(ctx->side);
-    for (hipEvent_t e : ctx->ev)
-      if (e) (void)hipEventDestroy(e);
-    (void)hipStreamDestroy(ctx->side);
-    for (hipStream_t st : {ctx->side2, ctx->side3})
+    for (hipStream_t st : {ctx->side, ctx->side2})
       if (st) {
         (void)hipStreamSynchronize(st);
         (void)hipStreamDestroy(st);
       }
+    for (hipEvent_t e : ctx->ev)
+      if (e) (void)hipEventDestroy(e);
   }
   if (ctx->ws && !ctx->ws_external) (void)hipFree(ctx->ws);
   if (ctx->tau_default) (void)hipFree(ctx->tau_default);

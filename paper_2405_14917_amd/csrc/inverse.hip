@@ -6,14 +6,12 @@
 // inverse, (2/3) m^3 flops instead of (4/3) m^3:
 //
 //   1. widen:   A = (2 / n_tokens) G + lambda I,  lambda = percdamp * mean(diag(2 / n_tokens G))
-//   2. for the diagonal blocks J = last .. first (64 columns each; eight of them form a group):
-//        chol_step   one workgroup: applies the last pending rank-64 update to A_JJ itself, factors
-//                    A_JJ = R_JJ R_JJ^T in LDS and inverts R_JJ (V_JJ, written into U)
-//        panel       R[0:J, J] = A[0:J, J] V_JJ^T                            (fp64 MFMA GEMM)
-//        update      rank-64 update of the columns between the start of block J-1's group and block J
-//        group update  rank-512 updates of everything further left, once per group
-//      The factorisation of the diagonal blocks and the GEMMs form two chains on two streams that only
-//      meet two steps apart, see the schedule at the call site.
+//   2. for the diagonal blocks J = last .. first (64 columns each; eight of them form a group), one launch each:
+//        diagonal    one workgroup: applies the last pending rank-64 update to A_JJ itself, factors
+//                    A_JJ = R_JJ R_JJ^T and inverts R_JJ (V_JJ, written into U)
+//        panel       R[0:J+1, J+1] = A[0:J+1, J+1] V^T of the block to the right, beside it
+//        update      rank-64 update with that panel of the columns from the start of block J's group on
+//      and once per group rank-512 updates of everything further left; see the schedule at the call site.
 //   3. triangular inverse U = R^-1 group by group on a further stream, beside the factorisation: inside a group
 //      by recursive doubling (ranges of 2^l inverted diagonal blocks merged pairwise, U12 = -U11 (R12 U22)), the
 //      rows right of the group from T = R[g, S] U[S, S], which is kept up to date for all rows above by one
@@ -23,8 +21,6 @@
 #include "slim_internal.h"
 
 namespace {
-
-using slimdev::read_lane_f64;
 
 constexpr int NB = 64;          // diagonal block
 // Diagonal blocks per group.  With 8 the far updates have rank 512 (64 flops per byte of A they move, against 32 with
@@ -117,6 +113,30 @@ __device__ __forceinline__ double fast_rcp(double x) {
   return r;
 }
 
+// ---- the diagonal block ----------------------------------------------------------------------------------------------
+// One workgroup of eight wavefronts per diagonal block, with tiles of 16 x 16:
+//   prologue  (nprev > 0)  Rn = A[J, J+1] V_{J+1}^T and A_JJ -= Rn Rn^T on the matrix cores: the update with the panel of block
+//             J+1 restricted to this block, so that this kernel does not have to wait for the GEMMs of block J+1
+//   factor    A_JJ = R R^T with R upper triangular, tile column by tile column from the last to the first: sixteen pivots in
+//             registers, then the rank-16 update of the tiles left of them on the matrix cores
+//   invert    V = R^-1, written to Vout
+// A non-positive pivot is recorded in flag[0] (1-based global column); the outputs are then meaningless.
+//
+// The block is a chain of 64 pivots and what bounds it is latency.  A wavefront that owns a tile column eliminates it without
+// LDS or barriers: lane = row, register = column, and the entries of the pivot column come to all lanes of a 16-lane row with
+// the row_newbcast operand of v_fmac_f64_dpp (16 cycles behind the instruction that made them, a dependent fp64 fma 5, a
+// reciprocal 25; an LDS write, barrier and read of eight wavefronts 170).  The diagonal tile lies in all four 16-lane rows.
+// Wavefront 0 eliminates the tile column above it along with it (one lane a row of the block), wavefront 1 repeats the diagonal
+// tile's elimination and turns the identity into the tile's inverse by the same row operations.  The reciprocal of the next
+// pivot is formed between the updates of the columns that it does not need.  The other tiles of
+// A stay in the accumulators of wavefronts 2, 3, 6 and 7, which also put V together while the next tile column is factored:
+//   V_ik = -V_ii T_ik,  T_ik = sum over i < l <= k of R_il V_lk.
+// Cycles (of 2.4 GHz) of the same block: loads 3500, prologue 5200, pivots and updates 24000, rest 1500, 15.9 us a launch back to
+// back, against 4000, 10400, 32300 and 3500 (22.5 us) of a form that published four columns at a time through LDS.
+constexpr int CB_LD = 66;       // rows of the staged 64 x 64 operands
+constexpr int CB_PAN = 48;      // rows of a panel (a column of it after the other)
+constexpr int CB_VLD = 18;      // rows of a tile of V
+
 typedef double double4v __attribute__((ext_vector_type(4)));
 
 struct CholArgs {
@@ -125,231 +145,478 @@ struct CholArgs {
   int nbk;               // width of this block (64, less for a ragged last block)
   int nprev;             // width of block J+1 whose rank-64 update is still pending on this block (0: none)
   const double* Vprev;   // V of block J+1 (in U)
-  double* Vout;          // V of this block (in U)
+  double* Vout;          // V of this block (in U; its tiles below the diagonal ones are zero already)
   int64_t ldv;
   int* flag;
   int col_base;
 };
 
+template <int N>
+__device__ __forceinline__ double newbcast(double x) {
+  return __longlong_as_double(__builtin_amdgcn_update_dpp((long long)0, __double_as_longlong(x), 0x150 + N, 0xf, 0xf, true));
+}
+// Updates of columns with an entry of their 16-lane row, several to a statement: a DPP operand must have been written two
+// instructions before it is read, and the compiler, which does not look into the statements, may put copies in front of one.
+#define CB_FMAC(Y, X, S, N) "\n\tv_fmac_f64_dpp " Y ", " X ", " S " row_newbcast:" N " row_mask:0xf bank_mask:0xf"
+// y[N .. N - M + 1] += (x of lane N, N - 1, ...) * s
+template <int N, int M>
+__device__ __forceinline__ void columns(double (&y)[16], double x, double s) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  if constexpr (M == 1)
+    asm volatile("s_nop 1" CB_FMAC("%0", "%1", "%2", "%3") : "+v"(y[N]) : "v"(x), "v"(s), "n"(N));
+  if constexpr (M == 2)
+    asm volatile("s_nop 1" CB_FMAC("%0", "%2", "%3", "%4") CB_FMAC("%1", "%2", "%3", "%5")
+                 : "+v"(y[N]), "+v"(y[N - 1]) : "v"(x), "v"(s), "n"(N), "n"(N - 1));
+  if constexpr (M == 3)
+    asm volatile("s_nop 1" CB_FMAC("%0", "%3", "%4", "%5") CB_FMAC("%1", "%3", "%4", "%6") CB_FMAC("%2", "%3", "%4", "%7")
+                 : "+v"(y[N]), "+v"(y[N - 1]), "+v"(y[N - 2]) : "v"(x), "v"(s), "n"(N), "n"(N - 1), "n"(N - 2));
+#endif
+}
+// both the tile's columns and those above it: d[N ..] += (x of lane N ..) * sd, o[N ..] += (x of lane N ..) * so
+template <int N, int M>
+__device__ __forceinline__ void columns(double (&d)[16], double (&o)[16], double x, double sd, double so) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  if constexpr (M == 1)
+    asm volatile("s_nop 1" CB_FMAC("%0", "%2", "%3", "%5") CB_FMAC("%1", "%2", "%4", "%5")
+                 : "+v"(d[N]), "+v"(o[N]) : "v"(x), "v"(sd), "v"(so), "n"(N));
+  if constexpr (M == 2)
+    asm volatile("s_nop 1" CB_FMAC("%0", "%4", "%5", "%7") CB_FMAC("%1", "%4", "%6", "%7") CB_FMAC("%2", "%4", "%5", "%8")
+                     CB_FMAC("%3", "%4", "%6", "%8")
+                 : "+v"(d[N]), "+v"(o[N]), "+v"(d[N - 1]), "+v"(o[N - 1]) : "v"(x), "v"(sd), "v"(so), "n"(N), "n"(N - 1));
+#endif
+}
+// e[C .. C + M - 1] += (their own entry in lane N) * s
+template <int N, int C, int M>
+__device__ __forceinline__ void rows(double (&e)[16], double s) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  if constexpr (M == 1) asm volatile("s_nop 1" CB_FMAC("%0", "%0", "%1", "%2") : "+v"(e[C]) : "v"(s), "n"(N));
+  if constexpr (M == 2)
+    asm volatile("s_nop 1" CB_FMAC("%0", "%0", "%2", "%3") CB_FMAC("%1", "%1", "%2", "%3") : "+v"(e[C]), "+v"(e[C + 1]) : "v"(s), "n"(N));
+  if constexpr (M == 3)
+    asm volatile("s_nop 1" CB_FMAC("%0", "%0", "%3", "%4") CB_FMAC("%1", "%1", "%3", "%4") CB_FMAC("%2", "%2", "%3", "%4")
+                 : "+v"(e[C]), "+v"(e[C + 1]), "+v"(e[C + 2]) : "v"(s), "n"(N));
+#endif
+}
+#undef CB_FMAC
+// holds its place among the updates above
+__device__ __forceinline__ void pin(double& x) { asm volatile("" : "+v"(x)); }
 
-// One workgroup (16 wavefronts) per diagonal block:
-//   prologue   (nprev > 0)  Rn = A[J, J+1] V_{J+1}^T and A_JJ -= Rn Rn^T on the matrix cores: the update
-//              with the panel of block J+1 restricted to this block, so that this kernel does not have to
-//              wait for the GEMMs of block J+1
-//   factor     A_JJ = R R^T with R upper triangular, from the last column to the first, and in its shadow
-//   invert     V = R^-1, written to Vout (zeros below the diagonal)
-// A non-positive pivot is recorded in flag[0] (1-based global column); the outputs are then meaningless.
-//
-// With a_j the column of pivot j at the time it is eliminated, p_j its diagonal entry and s_j = a_j / p_j,
-// R = [s_j] diag(sqrt p_j), and R^-1 = diag(1 / sqrt p_j) E where E results from the identity by the row
-// operations row_i -= s_j[i] row_j (i < j) in the order of the elimination.  E has columns, a column c is only
-// touched by pivots j <= c, i.e. once the column c of A is finished: the wavefronts that are done factoring
-// carry the inverse, the others the factorisation, and no separate inversion pass is needed.
-//
-// A lone wavefront issues an instruction every ~8 cycles and a dependent fp64 one every ~32, and an LDS
-// write -> barrier -> read costs ~200 cycles, so the elimination is blocked by four columns: lane = row,
-// wavefront w owns columns 4w .. 4w+3 of A and of E in registers.  The owner of the current four columns reads
-// their 4 x 4 diagonal block with lane reads, runs its elimination on wavefront-uniform values (the serial
-// chain: four reciprocals and the pivot updates between them), finishes the four columns, and publishes them
-// and the s_j through LDS once; the other wavefronts apply a rank-4 update to their columns of A or E:
-// 16 barriers instead of 128.  Entries of A below the diagonal are never read as values that matter.
-__global__ __launch_bounds__(1024) void chol_step(CholArgs g) {
-  constexpr int LD = NB + 1;
-  extern __shared__ __align__(16) double sm[];
-  double* Rs = sm;                 // [64][LD] staging: the block, then A[J, J+1], then Rn; later 1 / sqrt(pivot)
-  double* Xs = sm + NB * LD;       // [64][LD] staging: V_{J+1}, then Rn Rn^T; then the broadcast buffers; then V
-  double* cbA = Xs;                // [2][4][64] published columns
-  double* cbS = Xs + 512;          // [2][4][64] the same divided by their pivots, zero at and below the pivot
-  double* cbE = Xs + 1024;         // [2][4][64] combinations of the latter that drive the inverse
-  double* rsq = Rs;                // [64]
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int nbk = g.nbk, np = g.nprev;
-  const int prior_flag = g.flag[0];
-  // every global load is issued up front, coalesced (lane = column): the block (identity padding of a ragged
-  // one), and for the prologue A[J, J+1] and V_{J+1} (zero padding)
-  double ld_d[4], ld_a[4], ld_v[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int r = w + 16 * i;
-    ld_d[i] = (r == lane) ? 1.0 : 0.0;
-    if (r < nbk && lane < nbk) ld_d[i] = (lane >= r) ? g.A[(int64_t)r * g.lda + lane] : 0.0;
-    ld_a[i] = 0.0;
-    ld_v[i] = 0.0;
-    if (np > 0) {
-      if (lane < np) ld_a[i] = g.A[(int64_t)r * g.lda + NB + lane];
-      if (r < np && lane < np && lane >= r) ld_v[i] = g.Vprev[(int64_t)r * g.ldv + lane];
-    }
+// Pivot T of the diagonal tile d (lane = row, register = column): p and its reciprocal r.  The next pivot's are fetched and
+// formed in five pieces between the updates of the columns left of it.
+struct Pivot {
+  double p, r, e;
+  template <int S>
+  __device__ __forceinline__ void piece() {
+    if constexpr (S == 0) r = __builtin_amdgcn_rcp(p);
+    if constexpr (S == 1 || S == 3) e = fma(-p, r, 1.0);
+    if constexpr (S == 2 || S == 4) r = fma(e, r, r);
+    pin(r);
+    pin(e);
   }
-#pragma unroll
-  for (int i = 0; i < 4; ++i) Rs[(w + 16 * i) * LD + lane] = ld_d[i];
-  __syncthreads();
-  double a[4], e[4];
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    a[q] = Rs[lane * LD + 4 * w + q];
-    e[q] = (lane == 4 * w + q) ? 1.0 : 0.0;
+  template <int N>
+  __device__ __forceinline__ void fetch(double (&d)[16]) {
+    asm volatile("s_nop 1" : "+v"(d[N]));
+    p = newbcast<N>(d[N]);
+    pin(p);
   }
-  if (np > 0) {
-    // Rn = A[J, J+1] V^T, then A_JJ -= Rn Rn^T, as 16 x 16 MFMA tiles.  Operand lane (l16, lk) feeds row / column
-    // l16 at k = 16 lk + s in step s (any assignment of k works as long as both operands share it); result
-    // register v is row 4 v + lk, column l16 of the tile.
-    const int l16 = lane & 15, lk = lane >> 4;
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      Rs[(w + 16 * i) * LD + lane] = ld_a[i];
-      Xs[(w + 16 * i) * LD + lane] = ld_v[i];
-    }
-    __syncthreads();
-    {
-      // tile (ti, tj); V[c][k] = 0 for k < c, so tile column tj needs k >= 16 tj only: lane groups lk >= tj.
-      // Wavefronts that share a SIMD (w mod 4) get different tj, which balances the work.
-      const int ti = w & 3, tj = w >> 2;
-      double4v acc = {0.0, 0.0, 0.0, 0.0};
-      const double* ap = Rs + (16 * ti + l16) * LD + 16 * lk;
-      const double* bp = Xs + (16 * tj + l16) * LD + 16 * lk;
-#pragma unroll
-      for (int s = 0; s < 16; ++s) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(ap[s], bp[s], acc, 0, 0, 0);
-      __syncthreads();
-#pragma unroll
-      for (int v = 0; v < 4; ++v) Rs[(16 * ti + 4 * v + lk) * LD + 16 * tj + l16] = acc[v];
-    }
-    __syncthreads();
-    if (w < 10) {
-      // the ten tiles on and above the diagonal, dealt round the SIMDs
-      const int ti = (w < 4) ? 0 : ((w < 7) ? 1 : ((w < 9) ? 2 : 3));
-      const int tj = (w < 4) ? w : ((w < 7) ? w - 3 : ((w < 9) ? w - 5 : 3));
-      double4v acc = {0.0, 0.0, 0.0, 0.0};
-      const double* ap = Rs + (16 * ti + l16) * LD + 16 * lk;
-      const double* bp = Rs + (16 * tj + l16) * LD + 16 * lk;
-#pragma unroll
-      for (int s = 0; s < 16; ++s) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(ap[s], bp[s], acc, 0, 0, 0);
-#pragma unroll
-      for (int v = 0; v < 4; ++v) Xs[(16 * ti + 4 * v + lk) * LD + 16 * tj + l16] = acc[v];
-    }
-    __syncthreads();
-    // below the diagonal Xs still holds entries of V: finite, and never used as values that matter
-#pragma unroll
-    for (int q = 0; q < 4; ++q) a[q] -= Xs[lane * LD + 4 * w + q];
+};
+// o: the tile column above the tile (lane = row of the block)
+template <int T, int C, int S>
+__device__ __forceinline__ void panel_columns(Pivot& pv, double (&d)[16], double (&o)[16], double sd, double so) {
+  constexpr int M = C >= 1 ? 2 : (C == 0 ? 1 : 0);
+  if constexpr (M > 0) columns<C, M>(d, o, d[T], sd, so);
+  if constexpr (S < 5) pv.piece<S>();
+  if constexpr (C - M >= 0 || S < 4) panel_columns<T, C - M, S + 1>(pv, d, o, sd, so);
+}
+template <int T>
+__device__ __forceinline__ void panel_pivots(Pivot& pv, double (&d)[16], double (&o)[16], double* col, bool write) {
+  const double sd = -d[T] * pv.r, so = -o[T] * pv.r;
+  if (write) col[T * CB_PAN] = o[T];
+  if constexpr (T > 0) {
+    columns<T - 1, 1>(d, o, d[T], sd, so);
+    pv.fetch<T - 1>(d);
+    panel_columns<T, T - 2, 0>(pv, d, o, sd, so);
+    panel_pivots<T - 1>(pv, d, o, col, write);
   }
-  __syncthreads();   // Rs and Xs are free from here on
-  int bad = 0;       // owner only: a non-positive pivot in this lane's column
-
-  // E lags one step behind: in step wj the wavefronts right of the owner apply the row operations of the
-  // pivots of step wj+1, whose owner prepared them after its barrier, off the critical path.
-  auto e_update = [&](const double* bE, int jp) {
-    double sp[4];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) sp[r] = bE[r * 64 + lane];
-#pragma unroll
-    for (int q2 = 0; q2 < 4; ++q2) {
-      const double x0 = read_lane_f64(e[q2], jp), x1 = read_lane_f64(e[q2], jp + 1);
-      const double x2 = read_lane_f64(e[q2], jp + 2), x3 = read_lane_f64(e[q2], jp + 3);
-      e[q2] = fma(-sp[0], x0, fma(-sp[1], x1, fma(-sp[2], x2, fma(-sp[3], x3, e[q2]))));
-    }
-  };
-  for (int wj = 15; wj >= 0; --wj) {
-    double* bA = cbA + (wj & 1) * 256;
-    double* bS = cbS + (wj & 1) * 256;
-    const int jb = 4 * wj;
-    double pj = 1.0, sv0 = 0.0, sv1 = 0.0, sv2 = 0.0, sv3 = 0.0;
-    if (w == wj) {
-      // the 4 x 4 diagonal block of the owner's columns: D_rc = a[c] at row jb + r  (r <= c), uniform values
-      const double D33 = read_lane_f64(a[3], jb + 3), D23 = read_lane_f64(a[3], jb + 2);
-      const double D13 = read_lane_f64(a[3], jb + 1), D03 = read_lane_f64(a[3], jb + 0);
-      const double D22 = read_lane_f64(a[2], jb + 2), D12 = read_lane_f64(a[2], jb + 1);
-      const double D02 = read_lane_f64(a[2], jb + 0), D11 = read_lane_f64(a[1], jb + 1);
-      const double D01 = read_lane_f64(a[1], jb + 0), D00 = read_lane_f64(a[0], jb + 0);
-      // elimination of the block on uniform values; the chain is r3 -> p2 -> r2 -> p1 -> r1 -> p0 -> r0
-      const double r3 = fast_rcp(D33);
-      const double p2 = fma(-(D23 * D23), r3, D22);
-      const double E12 = fma(-(D13 * D23), r3, D12);       // entries after pivot 3
-      const double E02 = fma(-(D03 * D23), r3, D02);
-      const double E11 = fma(-(D13 * D13), r3, D11);
-      const double E01 = fma(-(D03 * D13), r3, D01);
-      const double E00 = fma(-(D03 * D03), r3, D00);
-      const double r2 = fast_rcp(p2);
-      const double p1 = fma(-(E12 * E12), r2, E11);
-      const double F01 = fma(-(E02 * E12), r2, E01);       // entries after pivot 2
-      const double F00 = fma(-(E02 * E02), r2, E00);
-      const double r1 = fast_rcp(p1);
-      const double p0 = fma(-(F01 * F01), r1, F00);
-      const double r0 = fast_rcp(p0);
-      // the four columns as they stand when they are eliminated, and s_j = a_j / p_j
-      const double s3 = a[3] * r3;
-      a[2] = fma(-s3, D23, a[2]);
-      const double s2 = a[2] * r2;
-      a[1] = fma(-s2, E12, fma(-s3, D13, a[1]));
-      const double s1 = a[1] * r1;
-      a[0] = fma(-s1, F01, fma(-s2, E02, fma(-s3, D03, a[0])));
-      const double s0 = a[0] * r0;
-      // rows at and below the pivot take no part in the row operations
-      sv0 = (lane < jb + 0) ? s0 : 0.0;
-      sv1 = (lane < jb + 1) ? s1 : 0.0;
-      sv2 = (lane < jb + 2) ? s2 : 0.0;
-      sv3 = (lane < jb + 3) ? s3 : 0.0;
-      bA[0 * 64 + lane] = a[0];
-      bA[1 * 64 + lane] = a[1];
-      bA[2 * 64 + lane] = a[2];
-      bA[3 * 64 + lane] = a[3];
-      bS[0 * 64 + lane] = sv0;
-      bS[1 * 64 + lane] = sv1;
-      bS[2 * 64 + lane] = sv2;
-      bS[3 * 64 + lane] = sv3;
-      pj = (lane == jb + 3) ? D33 : ((lane == jb + 2) ? p2 : ((lane == jb + 1) ? p1 : p0));
-    }
-    __syncthreads();
-    if (w < wj) {
-      // factorisation: rank-4 update of this wavefront's columns of A
-      double s4[4];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) s4[q] = bS[q * 64 + lane];
-#pragma unroll
-      for (int q = 3; q >= 0; --q) {
-        const double2 c01 = *reinterpret_cast<const double2*>(&bA[q * 64 + 4 * w]);
-        const double2 c23 = *reinterpret_cast<const double2*>(&bA[q * 64 + 4 * w + 2]);
-        a[0] = fma(-s4[q], c01.x, a[0]);
-        a[1] = fma(-s4[q], c01.y, a[1]);
-        a[2] = fma(-s4[q], c23.x, a[2]);
-        a[3] = fma(-s4[q], c23.y, a[3]);
-      }
-    } else if (w == wj) {
-      // Off the chain.  With x_r the entries of a column of E in the pivot rows before this block's row
-      // operations, the rows the four operations use are
-      //   y3 = x3, y2 = x2 - t32 y3, y1 = x1 - t31 y3 - t21 y2, y0 = x0 - t30 y3 - t20 y2 - t10 y1,  t_qr = s_q[jb+r],
-      // and every row i loses sum_q s_q[i] y_q = sum_r s'_r[i] x_r; the s'_r are published for the next step.
-      const double t32 = read_lane_f64(sv3, jb + 2), t31 = read_lane_f64(sv3, jb + 1), t30 = read_lane_f64(sv3, jb);
-      const double t21 = read_lane_f64(sv2, jb + 1), t20 = read_lane_f64(sv2, jb), t10 = read_lane_f64(sv1, jb);
-      const double L13 = fma(t21, t32, -t31);
-      const double L02 = fma(t10, t21, -t20);
-      const double L03 = fma(-t10, L13, fma(t20, t32, -t30));
-      double* bE = cbE + (wj & 1) * 256;
-      bE[0 * 64 + lane] = sv0;
-      bE[1 * 64 + lane] = fma(-t10, sv0, sv1);
-      bE[2 * 64 + lane] = fma(L02, sv0, fma(-t21, sv1, sv2));
-      bE[3 * 64 + lane] = fma(L03, sv0, fma(L13, sv1, fma(-t32, sv2, sv3)));
-      if (lane >= jb && lane < jb + 4) {
-        rsq[lane] = 1.0 / sqrt(pj);                        // for the final scaling
-        if (!(pj > 0.0) && lane < nbk) bad = 1;
-      }
-    } else {
-      e_update(cbE + ((wj + 1) & 1) * 256, jb + 4);
-    }
+}
+// e: the tile's inverse, but for the scale of its rows.  C: the next column of d; E: the next one of e
+template <int T, int C, int E, int S>
+__device__ __forceinline__ void inverse_columns(Pivot& pv, double (&d)[16], double (&e)[16], double sd, double se) {
+  constexpr int M = C >= 2 ? 3 : C + 1, K = M > 0 ? 0 : (E <= 12 ? 3 : 15 - E);
+  if constexpr (M > 0) columns<C, M>(d, d[T], sd);
+  if constexpr (K > 0) rows<T, E, K>(e, se);
+  if constexpr (S < 5) pv.piece<S>();
+  if constexpr (C - M >= 0 || E + K < 15 || S < 4) inverse_columns<T, C - M, E + K, S + 1>(pv, d, e, sd, se);
+}
+template <int T, int END>
+__device__ __forceinline__ void inverse_pivots(Pivot& pv, double (&d)[16], double (&e)[16], double& own_p, double& own_r, int l16) {
+  const double sd = -d[T] * pv.r;
+  const double se = l16 < T ? sd : 0.0;          // rows at and below the pivot take no part in the row operations
+  own_p = l16 == T ? pv.p : own_p;
+  own_r = l16 == T ? pv.r : own_r;
+  if constexpr (T > 0) {
+    columns<T - 1, 1>(d, d[T], sd);
+    rows<T, 15, 1>(e, se);
+    pv.fetch<T - 1>(d);
+    inverse_columns<T, T - 2, T, 0>(pv, d, e, sd, se);
+    if constexpr (T > END) inverse_pivots<T - 1, END>(pv, d, e, own_p, own_r, l16);
   }
-  __syncthreads();
-  e_update(cbE, 0);   // the pivots of the last step (columns 0 .. 3) act on every column
-  // the first failure in elimination order is kept: the highest column of the first block that fails
-  if (bad && prior_flag == 0) atomicMax(g.flag, g.col_base + lane + 1);
-  __syncthreads();   // every wavefront is done with the broadcast buffers, which V now overwrites
-  const double rs = rsq[lane];
-#pragma unroll
-  for (int q = 0; q < 4; ++q) Xs[lane * LD + 4 * w + q] = e[q] * rs;
-  __syncthreads();
-  for (int r = w; r < NB; r += 16)
-    if (r < nbk && lane < nbk) g.Vout[(int64_t)r * g.ldv + lane] = (lane >= r) ? Xs[r * LD + lane] : 0.0;
+}
+// 1 / sqrt(x) for positive finite x, within one unit of its last place: hardware estimate plus two Newton steps
+__device__ __forceinline__ double fast_rsq(double x) {
+  double y = __builtin_amdgcn_rsq(x);
+  y = fma(0.5 * y, fma(-x * y, y, 1.0), y);
+  return fma(0.5 * y, fma(-x * y, y, 1.0), y);
 }
 
-constexpr size_t CHOL_LDS = sizeof(double) * 2 * NB * (NB + 1);
+// acc += A B^T of two staged operands (row = output row / column), columns 8 s0 .. 63
+__device__ __forceinline__ double4v staged_product(const double* a, const double* b, int s0, double4v acc) {
+#pragma unroll
+  for (int s = 0; s < 8; ++s) {
+    if (s < s0) continue;                        // the same for the wavefront
+    const double2 x = *reinterpret_cast<const double2*>(a + 8 * s), y = *reinterpret_cast<const double2*>(b + 8 * s);
+    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(x.x, y.x, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(x.y, y.y, acc, 0, 0, 0);
+  }
+  return acc;
+}
+
+__device__ __forceinline__ void chol_block(const CholArgs& g, double* sm) {
+  double* Ps = sm;                           // [64][CB_LD]: A[J, J+1], then Rn, then the tiles of V and 1 / sqrt(pivot)
+  double* Vs = sm + NB * CB_LD;              // [64][CB_LD]: V_{J+1}, then the tile column in hand, panels and reciprocals
+  double* Dn = Vs;                           // [16][CB_LD]: the next tile column, one column after the other
+  double* rcps = Vs + 16 * CB_LD;            // [64]: reciprocals of the pivots
+  double* pan = rcps + NB;                   // [3][16][CB_PAN]: panels of tile columns 1 to 3 (before their scale 1 / sqrt(pivot))
+  double* rsq = Ps;                          // [64]
+  double* Vt = Ps + NB;                      // [10][16][CB_VLD]: tiles (i, k) of V at vt(i, k)
+  auto vt = [&](int i, int k) { return Vt + (i * 4 - i * (i - 1) / 2 + (k - i)) * 16 * CB_VLD; };
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l16 = lane & 15, lk = lane >> 4;
+  const int nbk = g.nbk, np = g.nprev;
+  const int prior_flag = g.flag[0];
+  // Tiles of A and of V, by wavefront: two of each for 2 and 3, one for 6 and 7.  The wavefronts that share a SIMD with the
+  // pivots (0 and 4, 1 and 5) have none: fp64 MFMAs take the units that fp64 vector instructions need.
+  const bool tiles = (w & 2) != 0;
+  const int owned = w < 4 ? 2 : 1;
+  const int ai[2] = {w == 2 ? 0 : (w == 3 ? 1 : (w == 6 ? 2 : 0)), w == 2 ? 0 : 1};
+  const int ak[2] = {w == 7 ? 0 : 2, 1};
+  const int vi[2] = {w == 7 ? 1 : 0, w == 2 ? 2 : 1};
+  const int vk[2] = {w == 2 ? 1 : (w == 6 ? 3 : 2), 3};
+  // result register v of a lane is row 4 v + lk, column l16 of a tile; identity padding of a ragged block
+  auto load_tile = [&](int i, int k) {
+    double4v t;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int r = 16 * i + 4 * v + lk, c = 16 * k + l16;
+      t[v] = r == c ? 1.0 : 0.0;
+      if (r < nbk && c < nbk) t[v] = c >= r ? g.A[(int64_t)r * g.lda + c] : 0.0;
+    }
+    return t;
+  };
+  double4v first = {0.0, 0.0, 0.0, 0.0}, at[2] = {first, first}, vtile[2] = {first, first};
+  double2 ldp[4], ldv[4];
+  if (np > 0) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int r = (tid >> 5) + 16 * i, c = 2 * (tid & 31);
+      ldp[i] = ldv[i] = make_double2(0.0, 0.0);
+      if (c < np) ldp[i] = *reinterpret_cast<const double2*>(g.A + (int64_t)r * g.lda + NB + c);
+      if (c < np && r < np && c + 1 >= r) ldv[i] = *reinterpret_cast<const double2*>(g.Vprev + (int64_t)r * g.ldv + c);
+    }
+  }
+  if (w < 4) first = load_tile(w, 3);
+  if (tiles) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+      if (j < owned) at[j] = load_tile(ai[j], ak[j]);
+  }
+  if (np > 0) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int at_ = ((tid >> 5) + 16 * i) * CB_LD + 2 * (tid & 31);
+      *reinterpret_cast<double2*>(Ps + at_) = ldp[i];
+      *reinterpret_cast<double2*>(Vs + at_) = ldv[i];
+    }
+    __syncthreads();
+    // Rn: tile column tj needs k >= 16 tj only; every wavefront has 20 MFMAs
+    const int ti = w & 3, tj0 = w < 4 ? 0 : 1, tj1 = w < 4 ? 3 : 2;
+    const double4v zero = {0.0, 0.0, 0.0, 0.0};
+    const double* ap = Ps + (16 * ti + l16) * CB_LD + 2 * lk;
+    const double4v r0 = staged_product(ap, Vs + (16 * tj0 + l16) * CB_LD + 2 * lk, 2 * tj0, zero);
+    const double4v r1 = staged_product(ap, Vs + (16 * tj1 + l16) * CB_LD + 2 * lk, 2 * tj1, zero);
+    __syncthreads();
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      double* row = Ps + (16 * ti + 4 * v + lk) * CB_LD + l16;
+      row[16 * tj0] = r0[v];
+      row[16 * tj1] = r1[v];
+    }
+    __syncthreads();
+    if (w < 4)
+      first -= staged_product(Ps + (16 * w + l16) * CB_LD + 2 * lk, Ps + (48 + l16) * CB_LD + 2 * lk, 0, zero);
+  }
+  auto store_column = [&](int i, const double4v& t) {     // tile (i, .) of the tile column that is next
+#pragma unroll
+    for (int v = 0; v < 4; ++v) Dn[l16 * CB_LD + 16 * i + 4 * v + lk] = t[v];
+  };
+  if (w < 4) store_column(w, first);
+  __syncthreads();
+  if (tiles && np > 0) {                         // beside the pivots of the last tile column
+    const double4v zero = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+      if (j < owned)
+        at[j] -= staged_product(Ps + (16 * ai[j] + l16) * CB_LD + 2 * lk, Ps + (16 * ak[j] + l16) * CB_LD + 2 * lk, 0, zero);
+  }
+  // A operand of step s: row l16, column 4 s + lk
+  auto panel_scaled = [&](int i, int b, int s) {          // R_ib
+    return pan[((b - 1) * 16 + 4 * s + lk) * CB_PAN + 16 * i + l16] * rsq[16 * b + 4 * s + lk];
+  };
+  auto times_tile = [&](double4v acc, int i, int b, const double* B) {   // acc += R_ib B
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(panel_scaled(i, b, s), B[(4 * s + lk) * CB_VLD + l16], acc, 0, 0, 0);
+    return acc;
+  };
+  auto finish_tile = [&](int i, int k, double4v T) {      // V_ik = -V_ii T_ik
+    double4v acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int s = 0; s < 4; ++s) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(-vt(i, i)[l16 * CB_VLD + 4 * s + lk], T[s], acc, 0, 0, 0);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int r = 16 * i + 4 * v + lk, c = 16 * k + l16;
+      vt(i, k)[(4 * v + lk) * CB_VLD + l16] = acc[v];
+      if (r < nbk && c < nbk) g.Vout[(int64_t)r * g.ldv + c] = acc[v];
+    }
+  };
+  auto store_diagonal = [&](int b) {
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int r = 16 * b + 4 * v + lk, c = 16 * b + l16;
+      if (r < nbk && c < nbk) g.Vout[(int64_t)r * g.ldv + c] = vt(b, b)[(4 * v + lk) * CB_VLD + l16];
+    }
+  };
+  int bad = 0;
+#pragma unroll 1
+  for (int b = 3; b >= 0; --b) {
+    double own_p = 1.0, own_r = 1.0;
+    double e[16];
+    if (w == 0 && b > 0) {
+      __builtin_amdgcn_s_setprio(3);
+      double d[16], o[16];
+#pragma unroll
+      for (int c = 0; c < 16; ++c) {
+        d[c] = Dn[c * CB_LD + 16 * b + l16];
+        o[c] = Dn[c * CB_LD + lane];
+      }
+      Pivot pv;
+      pv.e = 0.0;
+      pv.fetch<15>(d);
+      pv.r = fast_rcp(pv.p);
+      panel_pivots<15>(pv, d, o, pan + (b - 1) * 16 * CB_PAN + lane, lane < 16 * b);
+      __builtin_amdgcn_s_setprio(0);
+    } else if (w == 1) {
+      __builtin_amdgcn_s_setprio(3);
+      double d[16];
+#pragma unroll
+      for (int c = 0; c < 16; ++c) {
+        d[c] = Dn[c * CB_LD + 16 * b + l16];
+        e[c] = l16 == c ? 1.0 : 0.0;
+      }
+      Pivot pv;
+      pv.e = 0.0;
+      pv.fetch<15>(d);
+      pv.r = fast_rcp(pv.p);
+      inverse_pivots<15, 8>(pv, d, e, own_p, own_r, l16);
+      if (b == 0) __syncthreads();               // the tiles that the first tile row still needs
+      inverse_pivots<7, 0>(pv, d, e, own_p, own_r, l16);
+      if (lane < 16) rcps[16 * b + lane] = own_r;
+      __builtin_amdgcn_s_setprio(0);
+    } else if (tiles) {
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        if (j >= owned) continue;
+        // T_ik and V_ik as far as the tiles and panels of the tile rows below allow
+        if (b == 2 && vk[j] == 3) vtile[j] = times_tile(vtile[j], vi[j], 3, vt(3, 3));
+        if (b == 1 && vk[j] == 2) vtile[j] = times_tile(vtile[j], vi[j], 2, vt(2, 2));
+        if (b == 1 && vi[j] == 2) finish_tile(2, 3, vtile[j]);
+        if (b == 0) {
+          if (vk[j] == 3 && vi[j] < 2) vtile[j] = times_tile(vtile[j], vi[j], 2, vt(2, 3));
+          if (vk[j] == 1) vtile[j] = times_tile(vtile[j], 0, 1, vt(1, 1));
+          if (vi[j] == 1) finish_tile(1, vk[j], vtile[j]);
+        }
+      }
+      if (b < 3 && w == 7) store_diagonal(b + 1);
+    }
+    if (b == 0) {
+      if (w != 1) __syncthreads();
+      if (tiles && vi[0] == 0 && vk[0] > 1) vtile[0] = times_tile(vtile[0], 0, 1, vt(1, vk[0]));
+    }
+    __syncthreads();
+    if (tiles) {
+      // rank-16 update, with the panel's columns divided by their pivots on one side
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        if (j >= owned || ak[j] >= b) continue;
+        const double* p = pan + ((b - 1) * 16 + lk) * CB_PAN + l16;
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+          at[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(p[4 * s * CB_PAN + 16 * ai[j]],
+                                                       -p[4 * s * CB_PAN + 16 * ak[j]] * rcps[16 * b + 4 * s + lk], at[j], 0, 0, 0);
+        if (ak[j] == b - 1) store_column(ai[j], at[j]);
+      }
+    }
+    if (w == 1) {
+      const double rs = fast_rsq(own_p);
+      if (!(own_p > 0.0) && 16 * b + l16 < nbk) bad = max(bad, 16 * b + l16 + 1);
+      if (lane < 16) {
+        rsq[16 * b + lane] = rs;
+#pragma unroll
+        for (int c = 0; c < 16; c += 2)
+          *reinterpret_cast<double2*>(vt(b, b) + lane * CB_VLD + c) = make_double2(e[c] * rs, e[c + 1] * rs);
+      }
+    }
+    __syncthreads();
+  }
+  if (tiles && vi[0] == 0) finish_tile(0, vk[0], vtile[0]);
+  if (w == 7) store_diagonal(0);
+  // the first failure in elimination order is kept: the highest column of the first block that fails
+  if (bad && prior_flag == 0) atomicMax(g.flag, g.col_base + bad);
+}
+
+constexpr size_t CHOL_LDS = sizeof(double) * 2 * NB * CB_LD;
+
+__global__ __launch_bounds__(512) void chol_step(CholArgs g) {
+  extern __shared__ __align__(16) double sm[];
+  chol_block(g, sm);
+}
+
+struct LinkArgs {
+  CholArgs next;         // the diagonal block left of J
+  double* A;
+  double* R;
+  int64_t lda;
+  const double* V;       // of block J
+  int64_t ldv;
+  int J, nbk;            // block J and its width
+  int wt;                // first block of the window
+};
+
+// One link of the factorisation's chain in one launch: workgroup 0 factors the diagonal block left of J (which needs the panel
+// of J restricted to its own rows only, see chol_block), the others share out the rest of what block J gives:
+//   panel   R[0:j0, J] = A[0:j0, J] V_JJ^T
+//   window  A[r, c] -= R[r, J] R[c, J]^T for the blocks r < J - 1 and wt <= c < J, r <= c
+// A workgroup has one 64 x 64 block (r, c) and forms the two pieces of the panel that it needs itself (their product with the
+// triangular V is 5/8 of a full one), so that nothing in the launch waits for anything else in it; the one with c = J - 1 writes
+// the panel.  With the panel and the window as launches of their own on a second stream, whose events the diagonal steps waited
+// for, a link was five calls of the host, which took 35 us, and 37 us on the chip.  The whole inverse alone on the chip, that
+// form and this one: m = 256 260 and 133 us, 1504 980 and 622, 4096 2760 and 1960, 8192 9650 and 9010.
+__global__ __launch_bounds__(512) void chol_link(LinkArgs g) {
+  extern __shared__ __align__(16) double sm[];
+  if (blockIdx.x == 0) {
+    chol_block(g.next, sm);
+    return;
+  }
+  const int nc = g.J - g.wt;
+  int id = blockIdx.x - 1, r, c;
+  if (id < g.wt * nc) {
+    r = id / nc;
+    c = g.wt + id % nc;
+  } else {
+    id -= g.wt * nc;
+    r = g.wt;
+    while (id >= g.J - r) id -= g.J - r++;       // (at most eight rows)
+    c = r + id;
+  }
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l16 = lane & 15, lk = lane >> 4;
+  const int ti = w & 3, tj0 = w < 4 ? 0 : 1, tj1 = w < 4 ? 3 : 2;
+  const bool same = r == c, update = r < g.J - 1;
+  double* bufr = sm;
+  double* bufc = same ? sm : sm + NB * CB_LD;
+  const int64_t j0 = (int64_t)g.J * NB;
+  double2 ar[4], ac[4], v0[8], v1[8];
+  double4v c0 = {0.0, 0.0, 0.0, 0.0}, c1 = c0;
+  const double4v zero = c0;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int row = (tid >> 5) + 16 * i, col = 2 * (tid & 31);
+    ar[i] = ac[i] = make_double2(0.0, 0.0);
+    if (col < g.nbk) {
+      ar[i] = *reinterpret_cast<const double2*>(g.A + ((int64_t)r * NB + row) * g.lda + j0 + col);
+      if (!same) ac[i] = *reinterpret_cast<const double2*>(g.A + ((int64_t)c * NB + row) * g.lda + j0 + col);
+    }
+  }
+#pragma unroll
+  for (int s = 0; s < 8; ++s) {
+    const int k = 8 * s + 2 * lk, n0 = 16 * tj0 + l16, n1 = 16 * tj1 + l16;
+    v0[s] = v1[s] = make_double2(0.0, 0.0);
+    if (s >= 2 * tj0 && k < g.nbk && n0 < g.nbk) v0[s] = *reinterpret_cast<const double2*>(g.V + (int64_t)n0 * g.ldv + k);
+    if (s >= 2 * tj1 && k < g.nbk && n1 < g.nbk) v1[s] = *reinterpret_cast<const double2*>(g.V + (int64_t)n1 * g.ldv + k);
+  }
+  double* C = g.A + ((int64_t)r * NB + 16 * ti + lk) * g.lda + (int64_t)c * NB + l16;
+  if (update) {
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      c0[v] = C[4 * v * g.lda + 16 * tj0];
+      c1[v] = C[4 * v * g.lda + 16 * tj1];
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int at = ((tid >> 5) + 16 * i) * CB_LD + 2 * (tid & 31);
+    *reinterpret_cast<double2*>(bufr + at) = ar[i];
+    if (!same) *reinterpret_cast<double2*>(bufc + at) = ac[i];
+  }
+  __syncthreads();
+  auto times_v = [&](const double* buf, const double2 (&v)[8], int tj) {       // rows 16 ti of the buffer times V^T
+    const double* a = buf + (16 * ti + l16) * CB_LD + 2 * lk;
+    double4v acc = zero;
+#pragma unroll
+    for (int s = 0; s < 8; ++s) {
+      if (s < 2 * tj) continue;
+      const double2 x = *reinterpret_cast<const double2*>(a + 8 * s);
+      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(x.x, v[s].x, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(x.y, v[s].y, acc, 0, 0, 0);
+    }
+    return acc;
+  };
+  const double4v r0 = times_v(bufr, v0, tj0), r1 = times_v(bufr, v1, tj1);
+  double4v q0 = zero, q1 = zero;
+  if (!same) {
+    q0 = times_v(bufc, v0, tj0);
+    q1 = times_v(bufc, v1, tj1);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const int at = (16 * ti + 4 * v + lk) * CB_LD + l16;
+    bufr[at + 16 * tj0] = r0[v];
+    bufr[at + 16 * tj1] = r1[v];
+    if (!same) {
+      bufc[at + 16 * tj0] = q0[v];
+      bufc[at + 16 * tj1] = q1[v];
+    }
+  }
+  if (c == g.J - 1) {
+    double* R = g.R + ((int64_t)r * NB + 16 * ti + lk) * g.lda + j0 + l16;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      if (16 * tj0 + l16 < g.nbk) R[4 * v * g.lda + 16 * tj0] = r0[v];
+      if (16 * tj1 + l16 < g.nbk) R[4 * v * g.lda + 16 * tj1] = r1[v];
+    }
+  }
+  if (!update) return;
+  __syncthreads();
+  const double* a = bufr + (16 * ti + l16) * CB_LD + 2 * lk;
+  c0 -= staged_product(a, bufc + (16 * tj0 + l16) * CB_LD + 2 * lk, 0, zero);
+  c1 -= staged_product(a, bufc + (16 * tj1 + l16) * CB_LD + 2 * lk, 0, zero);
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    C[4 * v * g.lda + 16 * tj0] = c0[v];
+    C[4 * v * g.lda + 16 * tj1] = c1[v];
+  }
+}
 
 // partial column sums of squares of the upper triangle of U: grid (ceil(m/64), parts); part p owns 256 rows
 __global__ __launch_bounds__(256) void colsumsq_upper(const double* __restrict__ U, int64_t ldu, int m,
@@ -508,17 +775,14 @@ extern "C" slim_status slim_hessian_inverse(slim_ctx* ctx, const float* G, int64
 
   // ---- factorisation from the bottom-right corner upwards.  Blocks of 64 columns, groups of GRP blocks;
   //      "the window of block K" = the columns from the start of the group of block K-1 up to block K.
-  //   s0 (caller's stream)  step(J): the diagonal-block kernel; it applies the update with panel J+1 to A_JJ
-  //                         itself, so it depends on step(J+1) and on the GEMMs of block J+2 only
-  //   s1  gemm(K):          panel R[0:K, K] = A[0:K, K] V_KK^T
-  //                         A[rows above block K-1, window of K] -= R[.., K] R[window, K]^T        (rank 64)
-  //                         and, when K is the second block of its group G (all other panels of G are done):
-  //                         A[0:G, columns of group G-1] -= the panels of G except the first block's
-  //   s2  far(G):           A[left of group G-1]^2 -= all panels of G, upper tiles only            (rank 512)
+  //   s0 (caller's stream)  step of the last block, then for K = last .. 1
+  //        link(K)   the diagonal block K-1 (it applies the update with panel K to itself), panel K and the window of K
+  //        next(G)   when K is the second block of its group G (all other panels of G are done):
+  //                  A[0:G, columns of group G-1] -= the panels of G except the first block's
+  //   s1  far(G):    A[left of group G-1]^2 -= all panels of G, upper tiles only            (rank 512)
   // Every element of A thus receives each panel's contribution exactly once: from far() if it lies two or more
-  // groups to the left, from the group update if one group to the left (the first block's panel comes through
-  // that block's window), from a window update inside the group, and from the diagonal kernel for the
-  // neighbouring diagonal block.  gemm(K) runs while step(K-1) runs; step(K-2) waits for it.
+  // groups to the left, from next() if one group to the left (the first block's panel comes through that block's
+  // window), from a window update inside the group, and from the diagonal kernel for the neighbouring diagonal block.
   st = slim_ensure_side(ctx);
   if (st != SLIM_OK) return st;
   {
@@ -526,18 +790,14 @@ extern "C" slim_status slim_hessian_inverse(slim_ctx* ctx, const float* G, int64
     if (!done) {
       SLIM_HIP_TRY(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(chol_step),
                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)CHOL_LDS));
+      SLIM_HIP_TRY(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(chol_link),
+                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)CHOL_LDS));
       done = true;
     }
   }
-  hipStream_t s0 = ctx->stream, s1 = ctx->side, s2 = ctx->side2, s3 = ctx->side3;
-  hipEvent_t ev_fork = ctx->ev[0];
-  hipEvent_t* ev_step = &ctx->ev[1];   // ring of 4
-  hipEvent_t* ev_gemm = &ctx->ev[5];   // ring of 4
+  hipStream_t s0 = ctx->stream, s1 = ctx->side, s2 = ctx->side2;
+  hipEvent_t* ev_group = &ctx->ev[0];  // ring of 2: the links of a group are done
   hipEvent_t* ev_far = &ctx->ev[9];    // ring of 2
-  SLIM_HIP_TRY(ctx, hipEventRecord(ev_fork, s0));
-  SLIM_HIP_TRY(ctx, hipStreamWaitEvent(s1, ev_fork, 0));
-  SLIM_HIP_TRY(ctx, hipStreamWaitEvent(s2, ev_fork, 0));
-  SLIM_HIP_TRY(ctx, hipStreamWaitEvent(s3, ev_fork, 0));
   struct StreamSwap {
     slim_ctx* c;
     hipStream_t keep;
@@ -554,7 +814,7 @@ extern "C" slim_status slim_hessian_inverse(slim_ctx* ctx, const float* G, int64
     slim_ctx* c;
     ~AttachGuard() { c->attach_event = nullptr; }
   } attach_guard{ctx};
-  // ---- s3: the triangular inverse U = R^-1, group by group behind the factorisation.  With S the columns right of
+  // ---- s2: the triangular inverse U = R^-1, group by group behind the factorisation.  With S the columns right of
   //      group g, U[g, S] = -U[g, g] T[g, S] where T[g, S] = R[g, S] U[S, S] = sum over the groups h in S of
   //      R[g, h] U[h, S]: the term of group h exists as soon as the rows U[h, :] do, for all rows above h at once
   //      (a rank-512 product with a large result, like the far updates of the factorisation), so that the whole
@@ -568,7 +828,6 @@ extern "C" slim_status slim_hessian_inverse(slim_ctx* ctx, const float* G, int64
   //      T lives in A right of the group, where the panels' inputs lay: the last reader of those columns of A is the
   //      diagonal kernel of the block left of the group (its pending rank-64 update), which the caller waits for.
   auto group_inverse = [&](int Gi) -> slim_status {
-    StreamSwap swap(ctx, s3);
     const int64_t g0 = (int64_t)Gi * GRP * NB, g1 = std::min<int64_t>(m, g0 + GRP * NB);
     const int gw = (int)(g1 - g0);
     slim_status rs;
@@ -625,115 +884,77 @@ extern "C" slim_status slim_hessian_inverse(slim_ctx* ctx, const float* G, int64
     }
     return SLIM_OK;
   };
-  bool far_issued = false;
-  int last_far_slot = 0;
-  for (int J = nblk - 1; J >= 0; --J) {
-    const int j0 = J * NB;
-    const int nbk = std::min(NB, m - j0);
-    // ---- s0: diagonal block
-    if (J + 2 <= nblk - 1) SLIM_HIP_TRY(ctx, hipStreamWaitEvent(s0, ev_gemm[(J + 2) & 3], 0));
+  auto block = [&](int J) {              // the diagonal block J
     CholArgs ca;
-    ca.A = A + (int64_t)j0 * lda + j0;
+    const int64_t j0 = (int64_t)J * NB;
+    ca.A = A + j0 * lda + j0;
     ca.lda = lda;
-    ca.nbk = nbk;
-    ca.nprev = (J < nblk - 1) ? std::min(NB, m - (j0 + NB)) : 0;
-    ca.Vprev = U + (int64_t)(j0 + NB) * ldu + (j0 + NB);
-    ca.Vout = U + (int64_t)j0 * ldu + j0;
+    ca.nbk = std::min<int>(NB, m - (int)j0);
+    ca.nprev = (J < nblk - 1) ? std::min<int>(NB, m - (int)j0 - NB) : 0;
+    ca.Vprev = U + (j0 + NB) * ldu + (j0 + NB);
+    ca.Vout = U + j0 * ldu + j0;
     ca.ldv = ldu;
     ca.flag = flag;
-    ca.col_base = j0;
-    // The event that the GEMMs of this block wait for rides on the kernel's own completion signal (a separate record
-    // is one more packet for the command processor between two diagonal steps, whose chain is what the
-    // factorisation takes).
-    if (J > 0) ctx->attach_event = ev_step[J & 3];
-    SLIM_LAUNCH(ctx, "inv_chol_diag", chol_step, dim3(1), dim3(1024), CHOL_LDS, ca);
-    if (J == 0) break;
-    SLIM_HIP_TRY(ctx, slim_attach_flush(ctx));
-    // ---- s3: the group to the right is factored, its panels are complete (GEMMs of its first block), and with this
-    //      diagonal step the last reader of A right of this block is under way
-    if ((J + 1) % GRP == 0 && J + 1 < nblk) {
-      SLIM_HIP_TRY(ctx, hipStreamWaitEvent(s3, ev_gemm[(J + 1) & 3], 0));
-      SLIM_HIP_TRY(ctx, hipStreamWaitEvent(s3, ev_step[J & 3], 0));
-      st = group_inverse((J + 1) / GRP);
-      if (st != SLIM_OK) return st;
-    }
-
-    // ---- s1: GEMMs of block J
+    ca.col_base = (int)j0;
+    return ca;
+  };
+  bool far_issued = false, tri_issued = false;
+  int last_far_slot = 0, group_slot = 0;
+  SLIM_LAUNCH(ctx, "inv_chol_diag", chol_step, dim3(1), dim3(512), CHOL_LDS, block(nblk - 1));
+  for (int J = nblk - 1; J > 0; --J) {
+    const int j0 = J * NB;
     const int G = J / GRP;                          // group of block J
     const int g0 = G * GRP * NB;                    // first column of the group
     const int g1 = std::min(m, g0 + GRP * NB);      // one past its last column
-    const int wstart = ((J - 1) / GRP) * GRP * NB;  // window: from the start of the group of block J-1 ...
-    const int jn = j0 - NB;                         // ... to block J; rows above block J-1 take part
-    {
-      StreamSwap swap(ctx, s1);
-      SLIM_HIP_TRY(ctx, hipStreamWaitEvent(s1, ev_step[J & 3], 0));
+    const bool first = J == G * GRP;                // the group's panels are complete with this link
+    // the window of the first block of a group lies in the group to the left, which far() of the group before this one
+    // also writes
+    if (first && far_issued) SLIM_HIP_TRY(ctx, hipStreamWaitEvent(s0, ev_far[last_far_slot], 0));
+    LinkArgs la;
+    la.next = block(J - 1);
+    la.A = A;
+    la.R = R;
+    la.lda = lda;
+    la.V = U + (int64_t)j0 * ldu + j0;
+    la.ldv = ldu;
+    la.J = J;
+    la.nbk = std::min(NB, m - j0);
+    la.wt = ((J - 1) / GRP) * GRP;
+    const int nc = J - la.wt;
+    if (first) {
+      group_slot ^= 1;
+      ctx->attach_event = ev_group[group_slot];     // (rides on the kernel's own completion signal)
+    }
+    SLIM_LAUNCH(ctx, "inv_chol_diag@chol_link", chol_link, dim3(1 + la.wt * nc + nc * (nc + 1) / 2), dim3(512), CHOL_LDS, la);
+    SLIM_HIP_TRY(ctx, slim_attach_flush(ctx));
+    if (J == G * GRP + 1 && g0 > 0) {
+      // every panel of the group except the first block's is complete: bring the group to the left up to date
+      if (far_issued) SLIM_HIP_TRY(ctx, hipStreamWaitEvent(s0, ev_far[last_far_slot], 0));
+      const int gp = g0 - GRP * NB;               // first column of the group to the left
       slim_gemm_desc d;
-      d.A = A + j0;                       // A[0:j0, j0:j0+nbk]
+      d.A = R + j0;                               // R[0:g0, j0:g1]
       d.lda = lda;
-      d.B = U + (int64_t)j0 * ldu + j0;   // V_JJ, used transposed
-      d.ldb = ldu;
-      d.C = R + j0;
+      d.B = R + (int64_t)gp * lda + j0;
+      d.ldb = lda;
+      d.C = A + gp;
       d.ldc = lda;
       d.C2 = nullptr;
       d.ldc2 = 0;
-      d.M = j0;
-      d.N = nbk;
-      d.K = nbk;
-      d.flags = SLIM_GEMM_CHAIN;
-      d.alpha = 1.0;
-      d.beta = 0.0;
-      // the stage's event goes with its last launch
-      const bool has_window = jn > 0;
-      const bool has_group = J == G * GRP + 1 && g0 > 0;
-      if (!has_window && !has_group) ctx->attach_event = ev_gemm[J & 3];
-      st = slim_dgemm(ctx, "inv_panel_dgemm", 1, d);
+      d.M = g0;
+      d.N = g0 - gp;
+      d.K = g1 - j0;
+      d.flags = 0;
+      d.alpha = -1.0;
+      d.beta = 1.0;
+      st = slim_dgemm(ctx, "inv_group_next_dgemm", 1, d);
       if (st != SLIM_OK) return st;
-      if (has_window) {
-        // the window of the first block of a group lies in the group to the left, which far() of the group
-        // before this one also writes
-        if (wstart < g0 && far_issued) SLIM_HIP_TRY(ctx, hipStreamWaitEvent(s1, ev_far[last_far_slot], 0));
-        d.A = R + j0;                               // rows 0 .. jn of the panel
-        d.lda = lda;
-        d.B = R + (int64_t)wstart * lda + j0;       // rows of the panel that belong to the window
-        d.ldb = lda;
-        d.C = A + wstart;
-        d.ldc = lda;
-        d.M = jn;
-        d.N = j0 - wstart;
-        d.K = nbk;
-        d.alpha = -1.0;
-        d.beta = 1.0;
-        if (!has_group) ctx->attach_event = ev_gemm[J & 3];
-        st = slim_dgemm(ctx, "inv_window_dgemm", 1, d);
-        if (st != SLIM_OK) return st;
-      }
-      if (has_group) {
-        // every panel of the group except the first block's is complete: bring the group to the left up to date
-        const int gp = g0 - GRP * NB;               // first column of the group to the left
-        if (far_issued) SLIM_HIP_TRY(ctx, hipStreamWaitEvent(s1, ev_far[last_far_slot], 0));
-        d.A = R + j0;                               // R[0:g0, j0:g1]
-        d.lda = lda;
-        d.B = R + (int64_t)gp * lda + j0;
-        d.ldb = lda;
-        d.C = A + gp;
-        d.ldc = lda;
-        d.M = g0;
-        d.N = g0 - gp;
-        d.K = g1 - j0;
-        d.flags = 0;
-        d.alpha = -1.0;
-        d.beta = 1.0;
-        ctx->attach_event = ev_gemm[J & 3];
-        st = slim_dgemm(ctx, "inv_group_next_dgemm", 1, d);
-        if (st != SLIM_OK) return st;
-      }
-      SLIM_HIP_TRY(ctx, slim_attach_flush(ctx));
     }
-    // ---- s2: everything two or more groups to the left, once all panels of the group exist
-    if (J == G * GRP && g0 - GRP * NB > 0) {
-      StreamSwap swap(ctx, s2);
+    if (!first) continue;
+    // ---- s1: everything two or more groups to the left
+    if (g0 - GRP * NB > 0) {
+      StreamSwap swap(ctx, s1);
       const int gp = g0 - GRP * NB;
-      SLIM_HIP_TRY(ctx, hipStreamWaitEvent(s2, ev_gemm[J & 3], 0));
+      SLIM_HIP_TRY(ctx, hipStreamWaitEvent(s1, ev_group[group_slot], 0));
       slim_gemm_desc d;
       d.A = R + g0;                                 // R[0:gp, g0:g1]
       d.lda = lda;
@@ -746,8 +967,8 @@ extern "C" slim_status slim_hessian_inverse(slim_ctx* ctx, const float* G, int64
       d.M = gp;
       d.N = gp;
       d.K = g1 - g0;
-      // While this update is short next to the four diagonal steps it runs beside, it runs as a persistent
-      // kernel that leaves some CUs to their kernels; a large one is throughput-bound and takes the whole chip.
+      // While this update is short next to the links it runs beside, it runs as a persistent kernel that leaves some CUs
+      // to them; a large one is throughput-bound and takes the whole chip.
       d.flags = SLIM_GEMM_UPPER_ONLY | (gp <= 4096 ? SLIM_GEMM_ONE_PER_CU : 0);
       d.alpha = -1.0;
       d.beta = 1.0;
@@ -758,6 +979,14 @@ extern "C" slim_status slim_hessian_inverse(slim_ctx* ctx, const float* G, int64
       SLIM_HIP_TRY(ctx, slim_attach_flush(ctx));
       far_issued = true;
     }
+    // ---- s2: the triangular inverse of the group, whose last reader of A right of its first block was this link
+    {
+      StreamSwap swap(ctx, s2);
+      SLIM_HIP_TRY(ctx, hipStreamWaitEvent(s2, ev_group[group_slot], 0));
+      st = group_inverse(G);
+      if (st != SLIM_OK) return st;
+      tri_issued = true;
+    }
   }
   // The pivots are all known once the last diagonal block is done: the flag travels to the host from here, and the
   // call returns when it has arrived, with the triangular inverse still in flight on the stream.
@@ -765,18 +994,16 @@ extern "C" slim_status slim_hessian_inverse(slim_ctx* ctx, const float* G, int64
   hipEvent_t ev_info = ctx->ev[11];
   SLIM_HIP_TRY(ctx, hipMemcpyAsync(host, flag, sizeof(int), hipMemcpyDeviceToHost, s0));
   SLIM_HIP_TRY(ctx, hipEventRecord(ev_info, s0));
-  // the leftmost group's share of the triangular inverse: behind the last diagonal block and the last panels
-  hipEvent_t ev_last = ctx->ev[15], ev_tri = ctx->ev[14];
-  SLIM_HIP_TRY(ctx, hipEventRecord(ev_last, s0));
-  SLIM_HIP_TRY(ctx, hipStreamWaitEvent(s3, ev_last, 0));
-  if (nblk > 1) SLIM_HIP_TRY(ctx, hipStreamWaitEvent(s3, ev_gemm[1 & 3], 0));
+  // every side stream has joined the caller's before the leftmost group's share of the triangular inverse (whose rows need
+  // the other groups' terms), and so before the workspace is reused
+  if (far_issued) SLIM_HIP_TRY(ctx, hipStreamWaitEvent(s0, ev_far[last_far_slot], 0));
+  if (tri_issued) {
+    hipEvent_t ev_tri = ctx->ev[14];
+    SLIM_HIP_TRY(ctx, hipEventRecord(ev_tri, s2));
+    SLIM_HIP_TRY(ctx, hipStreamWaitEvent(s0, ev_tri, 0));
+  }
   st = group_inverse(0);
   if (st != SLIM_OK) return st;
-  SLIM_HIP_TRY(ctx, hipEventRecord(ev_tri, s3));
-  // every side stream has joined the caller's before the call's results are read (and before the workspace is reused)
-  if (nblk > 1) SLIM_HIP_TRY(ctx, hipStreamWaitEvent(s0, ev_gemm[1 & 3], 0));
-  if (far_issued) SLIM_HIP_TRY(ctx, hipStreamWaitEvent(s0, ev_far[last_far_slot], 0));
-  SLIM_HIP_TRY(ctx, hipStreamWaitEvent(s0, ev_tri, 0));
 
   SLIM_LAUNCH(ctx, "inv_diag_colsumsq", colsumsq_upper, dim3(slim_cdiv(m, 64), parts), dim3(256), 0, U, ldu, m, partial);
   SLIM_LAUNCH(ctx, "inv_diag_finalize", colsum_finalize, dim3(slim_cdiv(m, 256)), dim3(256), 0, partial, parts, m, hinv_diag);
