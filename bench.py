@@ -180,6 +180,8 @@ def algorithmic_work(name, cfg, launches_per_step):
         return "latency", None, 0.0                                   # m / 64 dependent diagonal blocks
     if name == "sqc_search":
         return "alu", "alu_f64", 9.0 * cfg.ncand * n * beta          # ~9 fp64 operations per weight and candidate
+    if name == "sqc_sweep":                                           # both in one launch
+        return "alu", "alu_f64", 9.0 * cfg.ncand * n * beta + float(n) * beta * beta
     if name == "gptq_sweep":
         return "alu", "alu_f64", float(n) * beta * beta              # rank-1 updates inside the group
     hbm = {
@@ -396,7 +398,7 @@ def main():
         "whole_pass": whole_pass,
         "kernels": others,
         "kernel_notes": {
-            "sqc_search": "alu peak counts an FMA as two operations; the search loop is mostly single-operation "
+            "sqc_search, sqc_sweep": "alu peak counts an FMA as two operations; the search loop is mostly single-operation "
                           "instructions (multiply, round, two clamps), so its fraction of the issue bound is about "
                           "twice the frac given",
             "inv_syrk_dgemm, inv_panel_dgemm, inv_window_dgemm, inv_trtri_*_dgemm, sba_*outputs": "run beside other "

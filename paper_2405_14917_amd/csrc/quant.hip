@@ -6,7 +6,8 @@
 // are carried at that precision.  CDNA4 runs fp64 vector and matrix work at full rate, so this
 // costs little next to the Hessian.
 //
-// Per group of beta columns four kernels run back to back on the stream:
+// Per group of beta columns four kernels run back to back on the stream (three for layers of up to 16 rows per compute unit, where
+// calibrate_sweep does the work of the two in the middle):
 //   block_stats   shifted sums of the current block (for the block-wide 3-sigma rule), per row slab
 //   sqc_search_fast / sqc_search_weighted   a few rows per workgroup: row min/max/mean|w|, the mask or the loss
 //                 weights, then a few lanes per (row, 4 or 5 candidates) walk the row's weights in LDS;
@@ -321,6 +322,124 @@ __device__ __forceinline__ double fast_rcp(double d) {
   return r;
 }
 
+// The losses of candidates c0 .. c0 + CPT - 1 for one row, this lane's share: the pairs of weights p, p + 4, ... of w and the
+// salient weights p, p + 4, ... of sl.  L = wus * (sum over all) + wdiff * (sum over the salient ones).
+template <int CPT>
+__device__ __forceinline__ void sqc_losses(const double* w, const double* sl, int beta, int ns, int p, bool sign_mode, double delta0,
+                                           double z, double alpha, double qmax, double wus, double wdiff, const double* tgrid, int c0,
+                                           int ncand, double (&L)[CPT]) {
+  double dl[CPT], rd[CPT];
+#pragma unroll
+  for (int i = 0; i < CPT; ++i) {
+    const double tc = tgrid[min(c0 + i, ncand - 1)];
+    L[i] = 0.0;
+    // SIGN: the level tau * alpha; otherwise the step tau * delta0 and its reciprocal.  The loss is continuous
+    // across a rounding tie (both neighbouring codes are equally far), so the candidate losses may use a
+    // reciprocal; the codes themselves are decided with a true division.
+    dl[i] = tc * (sign_mode ? alpha : delta0);
+    asm volatile("" : "+v"(dl[i]));       // rounded in every form: no part of an fma below (two levels around a row's mean
+                                          // magnitude can have losses that are equal but for that)
+    rd[i] = fast_rcp(dl[i]);
+  }
+  if (sign_mode) {
+    // |w - sign(w) level| = ||w| - level|
+    for (int j = 0; j < beta / 8; ++j) {
+      const double2v v2 = *reinterpret_cast<const double2v*>(w + (4 * j + p) * 2);
+#pragma unroll
+      for (int i = 0; i < CPT; ++i) {
+        const double e0 = fabs(v2.x) - dl[i], e1 = fabs(v2.y) - dl[i];
+        L[i] = fma(e0, e0, L[i]);
+        L[i] = fma(e1, e1, L[i]);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < CPT; ++i) L[i] *= wus;
+    for (int j = p; j < ns; j += 4) {
+      const double v = sl[j];
+#pragma unroll
+      for (int i = 0; i < CPT; ++i) {
+        const double e = fabs(v) - dl[i];
+        L[i] = fma(e * wdiff, e, L[i]);
+      }
+    }
+  } else {
+    // clamp(rint(x) + z, 0, qmax) - z == clamp(rint(x), -z, qmax - z): one add and one subtract less per element
+    const double lo = -z, hi = qmax - z;
+    double2v nxt = *reinterpret_cast<const double2v*>(w + p * 2);
+    for (int j = 0; j < beta / 8; ++j) {
+      const double2v v2 = nxt;
+      nxt = *reinterpret_cast<const double2v*>(w + (4 * min(j + 1, beta / 8 - 1) + p) * 2);   // one pair ahead
+      // stage by stage over the candidates' independent chains, so that a wavefront need not wait on
+      // its own results
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const double v = h ? v2.y : v2.x;
+        double x[CPT];
+#pragma unroll
+        for (int i = 0; i < CPT; ++i) x[i] = v * rd[i];
+#pragma unroll
+        for (int i = 0; i < CPT; ++i) x[i] = rint(x[i]);
+#pragma unroll
+        for (int i = 0; i < CPT; ++i) x[i] = fmax(x[i], lo);
+#pragma unroll
+        for (int i = 0; i < CPT; ++i) x[i] = fmin(x[i], hi);
+#pragma unroll
+        for (int i = 0; i < CPT; ++i) x[i] = fma(-dl[i], x[i], v);
+#pragma unroll
+        for (int i = 0; i < CPT; ++i) L[i] = fma(x[i], x[i], L[i]);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < CPT; ++i) L[i] *= wus;
+    for (int j = p; j < ns; j += 4) {
+      const double v = sl[j];
+#pragma unroll
+      for (int i = 0; i < CPT; ++i) {
+        const double q = fmin(fmax(rint(v * rd[i]), lo), hi);
+        const double e = fma(-dl[i], q, v);
+        L[i] = fma(e * wdiff, e, L[i]);
+      }
+    }
+  }
+}
+
+// index of the first smallest of a row's losses (0 where none is below infinity), in lane 0
+__device__ __forceinline__ int first_minimum(const double* loss, int ncand, int lane) {
+        double best = INFINITY;
+        int bi = 0x7fffffff;
+        for (int c = lane; c < ncand; c += 64) {
+          const double L = loss[c];
+          if (L < best) {
+            best = L;
+            bi = c;
+          }
+        }
+#define SQF_ARGMIN_STEP(CTRL)                                                   \
+        {                                                                           \
+          const double ob = dpp_f64<CTRL>(best);                                    \
+          const int oi = dpp_b32<CTRL>(bi);                                         \
+          if (ob < best || (ob == best && oi < bi)) {                               \
+            best = ob;                                                              \
+            bi = oi;                                                                \
+          }                                                                         \
+        }
+        SQF_ARGMIN_STEP(DPP_XOR1)
+        SQF_ARGMIN_STEP(DPP_XOR2)
+        SQF_ARGMIN_STEP(DPP_HALF_MIRROR)
+        SQF_ARGMIN_STEP(DPP_MIRROR)
+#undef SQF_ARGMIN_STEP
+#pragma unroll
+        for (int src = 16; src < 64; src += 16) {
+          const double ob = read_lane_f64(best, src);
+          const int oi = __builtin_amdgcn_readlane(bi, src);
+          if (lane == 0 && (ob < best || (ob == best && oi < bi))) {
+            best = ob;
+            bi = oi;
+          }
+        }
+  return bi == 0x7fffffff ? 0 : bi;
+}
+
 __global__ __launch_bounds__(1024, 5) void sqc_search_fast(SqcArgs a) {
   extern __shared__ __align__(16) double smem[];
   const int beta = a.beta, ncand = a.ncand, RW = a.rows_per_wg;
@@ -472,78 +591,8 @@ __global__ __launch_bounds__(1024, 5) void sqc_search_fast(SqcArgs a) {
       const int ns = reinterpret_cast<const int*>(par + 5)[0];
       // L = wus * (sum over all) + (ws - wus) * (sum over the salient ones)
       const double wus = par[4], wdiff = par[3] - par[4];
-      double L[SQF_CPT], dl[SQF_CPT], rd[SQF_CPT];
-#pragma unroll
-      for (int i = 0; i < SQF_CPT; ++i) {
-        const double tc = tgrid[min(c0 + i, ncand - 1)];
-        L[i] = 0.0;
-        // SIGN: the level tau * alpha; otherwise the step tau * delta0 and its reciprocal.  The loss is continuous
-        // across a rounding tie (both neighbouring codes are equally far), so the candidate losses may use a
-        // reciprocal; the codes themselves are decided with a true division.
-        dl[i] = tc * (sign_mode ? par[2] : par[0]);
-        rd[i] = fast_rcp(dl[i]);
-      }
-      if (sign_mode) {
-        // |w - sign(w) level| = ||w| - level|
-        for (int j = 0; j < beta / 8; ++j) {
-          const double2v v2 = *reinterpret_cast<const double2v*>(w + (4 * j + p) * 2);
-#pragma unroll
-          for (int i = 0; i < SQF_CPT; ++i) {
-            const double e0 = fabs(v2.x) - dl[i], e1 = fabs(v2.y) - dl[i];
-            L[i] = fma(e0, e0, L[i]);
-            L[i] = fma(e1, e1, L[i]);
-          }
-        }
-#pragma unroll
-        for (int i = 0; i < SQF_CPT; ++i) L[i] *= wus;
-        for (int j = p; j < ns; j += 4) {
-          const double v = sl[j];
-#pragma unroll
-          for (int i = 0; i < SQF_CPT; ++i) {
-            const double e = fabs(v) - dl[i];
-            L[i] = fma(e * wdiff, e, L[i]);
-          }
-        }
-      } else {
-        // clamp(rint(x) + z, 0, qmax) - z == clamp(rint(x), -z, qmax - z): one add and one subtract less per element
-        const double z = par[1];
-        const double lo = -z, hi = qmax - z;
-        double2v nxt = *reinterpret_cast<const double2v*>(w + p * 2);
-        for (int j = 0; j < beta / 8; ++j) {
-          const double2v v2 = nxt;
-          nxt = *reinterpret_cast<const double2v*>(w + (4 * min(j + 1, beta / 8 - 1) + p) * 2);   // one pair ahead
-          // stage by stage over the five candidates' independent chains, so that a wavefront need not wait on
-          // its own results
-#pragma unroll
-          for (int h = 0; h < 2; ++h) {
-            const double v = h ? v2.y : v2.x;
-            double x[SQF_CPT];
-#pragma unroll
-            for (int i = 0; i < SQF_CPT; ++i) x[i] = v * rd[i];
-#pragma unroll
-            for (int i = 0; i < SQF_CPT; ++i) x[i] = rint(x[i]);
-#pragma unroll
-            for (int i = 0; i < SQF_CPT; ++i) x[i] = fmax(x[i], lo);
-#pragma unroll
-            for (int i = 0; i < SQF_CPT; ++i) x[i] = fmin(x[i], hi);
-#pragma unroll
-            for (int i = 0; i < SQF_CPT; ++i) x[i] = fma(-dl[i], x[i], v);
-#pragma unroll
-            for (int i = 0; i < SQF_CPT; ++i) L[i] = fma(x[i], x[i], L[i]);
-          }
-        }
-#pragma unroll
-        for (int i = 0; i < SQF_CPT; ++i) L[i] *= wus;
-        for (int j = p; j < ns; j += 4) {
-          const double v = sl[j];
-#pragma unroll
-          for (int i = 0; i < SQF_CPT; ++i) {
-            const double q = fmin(fmax(rint(v * rd[i]), lo), hi);
-            const double e = fma(-dl[i], q, v);
-            L[i] = fma(e * wdiff, e, L[i]);
-          }
-        }
-      }
+      double L[SQF_CPT];
+      sqc_losses<SQF_CPT>(w, sl, beta, ns, p, sign_mode, par[0], par[1], par[2], qmax, wus, wdiff, tgrid, c0, ncand, L);
 #pragma unroll
       for (int i = 0; i < SQF_CPT; ++i) {
         double t = L[i];                                   // this lane's share: the loss is linear in the sums
@@ -554,42 +603,9 @@ __global__ __launch_bounds__(1024, 5) void sqc_search_fast(SqcArgs a) {
     }
     __syncthreads();
 
-    // first minimum per row
     for (int r = wave; r < rows; r += nwaves) {
-      double best = INFINITY;
-      int bi = 0x7fffffff;
-      for (int c = lane; c < ncand; c += 64) {
-        const double L = loss[r * ncand + c];
-        if (L < best) {
-          best = L;
-          bi = c;
-        }
-      }
-#define SQF_ARGMIN_STEP(CTRL)                                                   \
-      {                                                                           \
-        const double ob = dpp_f64<CTRL>(best);                                    \
-        const int oi = dpp_b32<CTRL>(bi);                                         \
-        if (ob < best || (ob == best && oi < bi)) {                               \
-          best = ob;                                                              \
-          bi = oi;                                                                \
-        }                                                                         \
-      }
-      SQF_ARGMIN_STEP(DPP_XOR1)
-      SQF_ARGMIN_STEP(DPP_XOR2)
-      SQF_ARGMIN_STEP(DPP_HALF_MIRROR)
-      SQF_ARGMIN_STEP(DPP_MIRROR)
-#undef SQF_ARGMIN_STEP
-#pragma unroll
-      for (int src = 16; src < 64; src += 16) {
-        const double ob = read_lane_f64(best, src);
-        const int oi = __builtin_amdgcn_readlane(bi, src);
-        if (lane == 0 && (ob < best || (ob == best && oi < bi))) {
-          best = ob;
-          bi = oi;
-        }
-      }
+      const int bi = first_minimum(loss + r * ncand, ncand, lane);
       if (lane == 0) {
-        if (bi == 0x7fffffff) bi = 0;
         const int64_t o = (int64_t)(r0 + r) * a.out_stride;
         const double tc = tgrid[bi];
         if (sign_mode) {
@@ -746,6 +762,77 @@ size_t sweep4_smem_bytes(int beta, int waves) {
   return sizeof(double) * (packed + beta + (size_t)rows * beta) + (size_t)rows * beta;
 }
 
+// The sweep of the rows of one wavefront, from their weights in wr, and their outputs; eb, qb: a row's errors and codes in LDS
+template <int BETA, bool SIGN>
+__device__ __forceinline__ void sweep4_rows(const SweepArgs& a, const double* Us, const double* rdiag, double* eb, uint8_t* qb,
+                                            const double* wr, int row, bool valid, int l16, double sc, double z) {
+  constexpr int NK = BETA / 16;
+  Sweep4<BETA> st;
+  const double qmax = (double)((1 << a.bits) - 1);
+  st.s = sc;
+  st.z = z;
+  st.rs = 1.0 / st.s;
+  st.lo = -st.z;                                   // clamp(rint(x) + z, 0, qmax) - z == clamp(rint(x), lo, hi)
+  st.hi = qmax - st.z;
+  st.e2 = 0.0;
+  st.Ub = Us;
+  st.rdiag = rdiag;
+  st.u0 = 0;
+  st.uh = Sweep4<BETA>::HI;
+  st.l0 = l16;
+  st.lh = l16 + Sweep4<BETA>::HI;
+  asm volatile("" : "+v"(st.u0), "+v"(st.uh), "+v"(st.l0), "+v"(st.lh));
+  st.eb = eb;
+  st.qb = qb;
+#pragma unroll
+  for (int k = 0; k < NK; ++k) st.w[k] = valid ? wr[16 * k + l16] : 0.0;
+#pragma unroll
+  for (int k = 0; k < NK; ++k) st.u[k] = Us[l16 + 16 * k];
+  st.rd = rdiag[0];
+  st.ujn = Us[1];
+  st.wj = bcast_row16<0>(st.w[0]);
+  asm volatile("" : "+v"(st.lo));                  // opaque, or -z is formed again in every step
+  sweep4_all<BETA, SIGN>(st, std::make_integer_sequence<int, NK>{});
+
+  // each lane picks up the errors and codes of its own columns (written by its own wavefront)
+  if (valid) {
+#pragma unroll
+    for (int k = 0; k < NK; ++k) {
+      const int c = 16 * k + l16;
+      const double ev = st.eb[c];
+      const uint8_t code = st.qb[c];
+      a.codes[(int64_t)row * a.ldc + c] = code;
+      a.E[(int64_t)row * a.lde + c] = ev;
+      if (a.What) {
+        const double what = st.s * ((double)code - st.z);
+        if (a.what_f64)
+          static_cast<double*>(a.What)[(int64_t)row * a.ldwh + c] = what;
+        else
+          static_cast<float*>(a.What)[(int64_t)row * a.ldwh + c] = (float)what;
+      }
+    }
+    if (l16 == 0) a.row_e2[row] += st.e2;
+  }
+}
+
+// element e (even) of the packed block of U and the one behind it, as they are in U; jrow, col: row, column in its segment
+template <int BETA>
+__device__ __forceinline__ double2 sweep4_u(const double* U, int64_t ldu, int e, int& jrow, int& col) {
+  int k = 0;
+#pragma unroll
+  for (int kk = 1; kk < BETA / 16; ++kk) k += (e >= sweep4_row_off(BETA, kk, 0)) ? 1 : 0;
+  const int width = BETA - 16 * k, r = e - sweep4_row_off(BETA, k, 0);
+  const int jj = r / width;
+  jrow = 16 * k + jj;
+  col = r - jj * width;                              // column within the segment's range, even
+  return *reinterpret_cast<const double2*>(U + (int64_t)jrow * ldu + 16 * k + col);
+}
+// only the upper triangle is meaningful, and each row is divided by its diagonal element
+__device__ __forceinline__ double2 sweep4_scaled(double2 v, int jrow, int col, double rd) {
+  const int jj = jrow & 15;
+  return make_double2(col >= jj ? v.x * rd : 0.0, col + 1 >= jj ? v.y * rd : 0.0);
+}
+
 template <int BETA, bool SIGN>
 __global__ __launch_bounds__(1024) void gptq_sweep4(SweepArgs a) {
   constexpr int NK = BETA / 16, PACKED = sweep4_row_off(BETA, NK, 0);
@@ -757,8 +844,7 @@ __global__ __launch_bounds__(1024) void gptq_sweep4(SweepArgs a) {
   uint8_t* qbase = reinterpret_cast<uint8_t*>(ebase + rows_per_wg * BETA);
   for (int j = tid; j < BETA; j += nthreads) rdiag[j] = 1.0 / a.U[(int64_t)j * a.ldu + j];
   __syncthreads();
-  // The packed block, two columns at a time: only the upper triangle is meaningful, and each row is divided by
-  // its diagonal element.  Six loads are in flight per thread before the first is used (the block comes from L2,
+  // The packed block, two columns at a time.  Six loads are in flight per thread before the first is used (the block comes from L2,
   // and with few wavefronts per workgroup the fill would otherwise be a string of round trips).
   constexpr int FILL = 6;
   for (int i0 = tid; i0 < PACKED / 2; i0 += FILL * nthreads) {
@@ -768,28 +854,12 @@ __global__ __launch_bounds__(1024) void gptq_sweep4(SweepArgs a) {
     for (int q = 0; q < FILL; ++q) {
       const int e = 2 * (i0 + q * nthreads);       // index in the packed block
       v[q] = make_double2(0.0, 0.0);
-      if (e < PACKED) {
-        int k = 0;
-#pragma unroll
-        for (int kk = 1; kk < NK; ++kk) k += (e >= sweep4_row_off(BETA, kk, 0)) ? 1 : 0;
-        const int width = BETA - 16 * k, r = e - sweep4_row_off(BETA, k, 0);
-        const int jj = r / width;
-        jrow[q] = 16 * k + jj;
-        col[q] = r - jj * width;                   // column within the segment's range, even
-        v[q] = *reinterpret_cast<const double2*>(a.U + (int64_t)jrow[q] * a.ldu + 16 * k + col[q]);
-      }
+      if (e < PACKED) v[q] = sweep4_u<BETA>(a.U, a.ldu, e, jrow[q], col[q]);
     }
 #pragma unroll
     for (int q = 0; q < FILL; ++q) {
       const int e = 2 * (i0 + q * nthreads);
-      if (e < PACKED) {
-        const double rd = rdiag[jrow[q]];
-        const int jj = jrow[q] & 15;
-        double2 o;
-        o.x = (col[q] >= jj) ? v[q].x * rd : 0.0;
-        o.y = (col[q] + 1 >= jj) ? v[q].y * rd : 0.0;
-        *reinterpret_cast<double2*>(Us + e) = o;
-      }
+      if (e < PACKED) *reinterpret_cast<double2*>(Us + e) = sweep4_scaled(v[q], jrow[q], col[q], rdiag[jrow[q]]);
     }
   }
   __syncthreads();
@@ -804,54 +874,185 @@ __global__ __launch_bounds__(1024) void gptq_sweep4(SweepArgs a) {
     if (row0 + wave * SWEEP4_RPW >= a.n) break;
     const bool valid = row < a.n;                    // rows past the end compute on zeros and store nothing
 
-    Sweep4<BETA> st;
-    const double qmax = (double)((1 << a.bits) - 1);
-    st.s = valid ? a.scale[(int64_t)row * a.sz_stride] : 1.0;
-    st.z = valid ? a.zero[(int64_t)row * a.sz_stride] : 0.0;
-    st.rs = 1.0 / st.s;
-    st.lo = -st.z;                                   // clamp(rint(x) + z, 0, qmax) - z == clamp(rint(x), lo, hi)
-    st.hi = qmax - st.z;
-    st.e2 = 0.0;
-    st.Ub = Us;
-    st.rdiag = rdiag;
-    st.u0 = 0;
-    st.uh = Sweep4<BETA>::HI;
-    st.l0 = l16;
-    st.lh = l16 + Sweep4<BETA>::HI;
-    asm volatile("" : "+v"(st.u0), "+v"(st.uh), "+v"(st.l0), "+v"(st.lh));
-    st.eb = ebase + rl * BETA;
-    st.qb = qbase + rl * BETA;
-    const double* wr = a.W + (int64_t)row * a.ldw;
-#pragma unroll
-    for (int k = 0; k < NK; ++k) st.w[k] = valid ? wr[16 * k + l16] : 0.0;
-#pragma unroll
-    for (int k = 0; k < NK; ++k) st.u[k] = Us[l16 + 16 * k];
-    st.rd = rdiag[0];
-    st.ujn = Us[1];
-    st.wj = bcast_row16<0>(st.w[0]);
-    asm volatile("" : "+v"(st.lo));                  // opaque, or -z is formed again in every step
-    sweep4_all<BETA, SIGN>(st, std::make_integer_sequence<int, NK>{});
+    const double sc = valid ? a.scale[(int64_t)row * a.sz_stride] : 1.0;
+    const double z = valid ? a.zero[(int64_t)row * a.sz_stride] : 0.0;
+    sweep4_rows<BETA, SIGN>(a, Us, rdiag, ebase + rl * BETA, qbase + rl * BETA, a.W + (int64_t)row * a.ldw, row, valid, l16, sc, z);
+  }
+}
 
-    // each lane picks up the errors and codes of its own columns (written by its own wavefront)
-    if (valid) {
+// ------------------------------------------------------------------------------------------
+// Calibration and sweep of a group in one launch, for layers that fill the chip with at most 16 rows per workgroup (one round
+// of workgroups).  There both kernels are bound by latencies in a row, launch, block of U, rows, parameters, and the second
+// needs of the first only its own rows.  Here the block of U and the rows come while the block's statistics do; one or two
+// wavefronts search a row (16 quads of lanes, 7 or 4 candidates each, the order of the sums of sqc_search_fast) and every fourth
+// one goes on to sweep four rows from LDS.  Whole pass: 1000 x 1504 in groups of 32 2.23 -> 2.01 ms (4.7 us a group),
+// 4096 x 4096 in groups of 128 8.11 -> 7.80 ms (9.6 us a group of 42).  With more rows than one round takes the two kernels stay:
+// the search shares a CU among 20 wavefronts there and the sweep one block of U among several sets of rows, and what the launch
+// costs is small beside their 110 and 70 us (28672 rows).
+// ------------------------------------------------------------------------------------------
+struct FusedArgs {
+  SqcArgs c;
+  SweepArgs s;
+};
+
+// doubles in LDS: packed U, 1 / diagonal, rows, errors (the salient weights before), losses, tau, parameters, sums; then codes
+size_t fused_smem_bytes(int beta, int rows, int ncand) {
+  const size_t packed = (size_t)sweep4_row_off(beta, beta / 16, 0);
+  return sizeof(double) * (packed + beta + 2 * (size_t)rows * beta + (size_t)rows * ncand + ncand + 2 * rows + 32) + (size_t)rows * beta;
+}
+
+template <int BETA, bool SIGN, int WPR>
+__global__ __launch_bounds__(1024) void calibrate_sweep(FusedArgs f) {
+  constexpr int NK = BETA / 16, PACKED = sweep4_row_off(BETA, NK, 0), CPT = WPR == 1 ? 7 : 4;
+  constexpr int NT = WPR == 1 ? 1024 : 512, FILL = (PACKED / 2 + NT - 1) / NT;     // loads of the block per thread
+  extern __shared__ __align__(16) double Us[];
+  const SqcArgs& a = f.c;
+  const int tid = threadIdx.x, nthreads = blockDim.x, lane = tid & 63, wave = tid >> 6, nwaves = nthreads >> 6;
+  const int rows = nwaves / WPR, ncand = a.ncand;
+  double* rdiag = Us + PACKED;
+  double* wrow = rdiag + BETA;                       // [rows][BETA]
+  double* ebase = wrow + rows * BETA;                // [rows][BETA] errors; before, each row's salient weights
+  double* loss = ebase + rows * BETA;                // [rows][ncand]
+  double* tgrid = loss + rows * ncand;
+  double* par = tgrid + ncand;                       // [rows][2] scale, zero
+  double* red = par + 2 * rows;                      // [2][16]
+  uint8_t* qbase = reinterpret_cast<uint8_t*>(red + 32);
+  const int r0 = blockIdx.x * rows, r = wave / WPR, row = r0 + r;
+  const bool live = row < a.n;
+  const bool need_mask = (a.weight_mode == SLIM_WEIGHT_MASK_MEAN);
+  const bool block_scope = need_mask && a.scope == SLIM_SCOPE_BLOCK;
+
+  // everything that comes from memory is asked for at once
+  double2 u[FILL];
+  int jrow[FILL], col[FILL];
 #pragma unroll
-      for (int k = 0; k < NK; ++k) {
-        const int c = 16 * k + l16;
-        const double ev = st.eb[c];
-        const uint8_t code = st.qb[c];
-        a.codes[(int64_t)row * a.ldc + c] = code;
-        a.E[(int64_t)row * a.lde + c] = ev;
-        if (a.What) {
-          const double what = st.s * ((double)code - st.z);
-          if (a.what_f64)
-            static_cast<double*>(a.What)[(int64_t)row * a.ldwh + c] = what;
-          else
-            static_cast<float*>(a.What)[(int64_t)row * a.ldwh + c] = (float)what;
-        }
-      }
-      if (l16 == 0) a.row_e2[row] += st.e2;
+  for (int q = 0; q < FILL; ++q) {
+    const int e = 2 * (tid + q * nthreads);
+    jrow[q] = col[q] = 0;
+    if (e < PACKED) u[q] = sweep4_u<BETA>(f.s.U, f.s.ldu, e, jrow[q], col[q]);
+  }
+  constexpr int NV = (BETA + 63) / 64;
+  double v[NV];
+#pragma unroll
+  for (int q = 0; q < NV; ++q) {
+    const int c = q * 64 + lane;
+    v[q] = live && c < BETA ? a.W[(int64_t)row * a.ldw + c] : 0.0;
+  }
+  double s1 = 0.0, s2 = 0.0;
+  if (block_scope) {
+    for (int p = tid; p < a.nstat; p += nthreads) {
+      s1 += a.stat_partial[2 * p];
+      s2 += a.stat_partial[2 * p + 1];
     }
   }
+  const double shift = block_scope ? a.W[0] : 0.0;
+  for (int c = tid; c < ncand; c += nthreads) tgrid[c] = a.tau[c];
+  for (int j = tid; j < BETA; j += nthreads) rdiag[j] = 1.0 / f.s.U[(int64_t)j * f.s.ldu + j];
+  if (block_scope) {
+    s1 = wave_allreduce<OpSum>(s1);
+    s2 = wave_allreduce<OpSum>(s2);
+    if (lane == 0) {
+      red[2 * wave] = s1;
+      red[2 * wave + 1] = s2;
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < FILL; ++q) {
+    const int e = 2 * (tid + q * nthreads);
+    if (e < PACKED) *reinterpret_cast<double2*>(Us + e) = sweep4_scaled(u[q], jrow[q], col[q], rdiag[jrow[q]]);
+  }
+
+  // parameters, mask and losses of the wavefront's row (the wavefronts of a row write the same values to LDS)
+  const double qmax = (double)((1 << a.bits) - 1);
+  double d0 = 1.0, z = 0.0, alpha = 0.0;
+  if (live) {
+    double* w = wrow + r * BETA;
+    double* sal = ebase + r * BETA;
+    double mn = INFINITY, mx = -INFINITY, sabs = 0.0, sum = 0.0;
+#pragma unroll
+    for (int q = 0; q < NV; ++q) {
+      const int c = q * 64 + lane;
+      if (c < BETA) {
+        w[c] = v[q];
+        mn = fmin(mn, v[q]);
+        mx = fmax(mx, v[q]);
+        sabs += fabs(v[q]);
+        sum += v[q];
+      }
+    }
+    mn = wave_allreduce<OpMin>(mn);
+    mx = wave_allreduce<OpMax>(mx);
+    sabs = wave_allreduce<OpSum>(sabs);
+    int ns = 0;
+    if (need_mask) {
+      double mu, thr;
+      if (block_scope) {
+        double S1 = 0.0, S2 = 0.0;
+        for (int i = 0; i < nwaves; ++i) {
+          S1 += red[2 * i];
+          S2 += red[2 * i + 1];
+        }
+        const double cnt = (double)a.n * (double)BETA;
+        const double m1 = S1 / cnt;
+        mu = shift + m1;
+        thr = 3.0 * sqrt(fmax(S2 / cnt - m1 * m1, 0.0));
+      } else {
+        mu = wave_allreduce<OpSum>(sum) / (double)BETA;
+        double ss = 0.0;
+#pragma unroll
+        for (int q = 0; q < NV; ++q) {
+          const double d = v[q] - mu;
+          if (q * 64 + lane < BETA) ss += d * d;
+        }
+        thr = 3.0 * sqrt(wave_allreduce<OpSum>(ss) / (double)BETA);
+      }
+#pragma unroll
+      for (int q = 0; q < NV; ++q) {
+        const bool s = q * 64 + lane < BETA && fabs(v[q] - mu) > thr;
+        const unsigned long long b = __ballot(s);
+        const int before = __builtin_amdgcn_mbcnt_hi((unsigned)(b >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)b, 0u));
+        if (s) sal[ns + before] = v[q];
+        ns += __builtin_popcountll(b);
+      }
+    }
+    if (!SIGN) minmax_params(mn, mx, a.bits, d0, z);
+    alpha = sabs / (double)BETA;
+    const int nus = BETA - ns;
+    const double ws = need_mask && ns ? fast_rcp((double)ns) : 0.0;
+    const double wus = need_mask ? (nus ? fast_rcp((double)nus) : 0.0) : 1.0;
+    for (int c0 = ((wave % WPR) * 16 + (lane >> 2)) * CPT; c0 < ncand; c0 += WPR * 16 * CPT) {
+      double L[CPT];
+      sqc_losses<CPT>(w, sal, BETA, ns, lane & 3, SIGN, d0, z, alpha, qmax, wus, ws - wus, tgrid, c0, ncand, L);
+#pragma unroll
+      for (int i = 0; i < CPT; ++i) {
+        double t = L[i];
+        t += dpp_f64<DPP_XOR1>(t);
+        t += dpp_f64<DPP_XOR2>(t);
+        if ((lane & 3) == 0 && c0 + i < ncand) loss[r * ncand + c0 + i] = t;
+      }
+    }
+  }
+  __syncthreads();
+  if (live && wave % WPR == 0) {
+    const int bi = first_minimum(loss + r * ncand, ncand, lane);
+    if (lane == 0) {
+      const double tc = tgrid[bi];
+      const double sc = SIGN ? 2.0 * tc * alpha : tc * d0, zr = SIGN ? 0.5 : z;
+      a.scale[(int64_t)row * a.out_stride] = sc;
+      a.zero[(int64_t)row * a.out_stride] = zr;
+      par[2 * r] = sc;
+      par[2 * r + 1] = zr;
+    }
+  }
+  __syncthreads();
+
+  // no barrier below
+  const int rl = wave * SWEEP4_RPW + (lane >> 4), l16 = lane & 15;
+  if (wave * SWEEP4_RPW >= rows || r0 + wave * SWEEP4_RPW >= a.n) return;
+  const bool valid = r0 + rl < a.n;
+  sweep4_rows<BETA, SIGN>(f.s, Us, rdiag, ebase + rl * BETA, qbase + rl * BETA, wrow + rl * BETA, r0 + rl, valid, l16,
+                          valid ? par[2 * rl] : 1.0, valid ? par[2 * rl + 1] : 0.0);
 }
 
 // Kernels that may need more than the default 64 KiB of dynamic LDS opt in once per process.
@@ -867,7 +1068,8 @@ slim_status allow_big_lds(slim_ctx* ctx, K kernel, bool& done) {
 
 bool beta_supported(int beta) { return beta == 32 || beta == 64 || beta == 128 || beta == 256 || beta == 512; }
 
-slim_status launch_stats_and_sqc(slim_ctx* ctx, SqcArgs a, double* stat_partial) {
+// the statistics of the block that the block-wide 3-sigma rule needs
+slim_status launch_stats(slim_ctx* ctx, SqcArgs& a, double* stat_partial) {
   const bool need_block_stats =
       (a.omega == nullptr && a.weight_mode == SLIM_WEIGHT_MASK_MEAN && a.scope == SLIM_SCOPE_BLOCK);
   a.stat_partial = nullptr;
@@ -877,6 +1079,12 @@ slim_status launch_stats_and_sqc(slim_ctx* ctx, SqcArgs a, double* stat_partial)
     a.stat_partial = stat_partial;
     SLIM_LAUNCH(ctx, "sqc_block_stats", block_stats, dim3(a.nstat), dim3(256), 0, a.W, a.ldw, a.n, a.beta, stat_partial);
   }
+  return SLIM_OK;
+}
+
+slim_status launch_stats_and_sqc(slim_ctx* ctx, SqcArgs a, double* stat_partial) {
+  const slim_status st0 = launch_stats(ctx, a, stat_partial);
+  if (st0 != SLIM_OK) return st0;
   if (a.omega == nullptr && (a.weight_mode == SLIM_WEIGHT_MASK_MEAN || a.weight_mode == SLIM_WEIGHT_UNIFORM)) {
     int threads = 0;
     size_t smem = 0;
@@ -903,6 +1111,33 @@ slim_status launch_stats_and_sqc(slim_ctx* ctx, SqcArgs a, double* stat_partial)
   }
   SLIM_LAUNCH(ctx, "sqc_search", sqc_search_weighted, dim3(slim_cdiv(a.n, a.rows_per_wg)), dim3(SQC_THREADS), smem, a);
   return SLIM_OK;
+}
+
+// Rows per workgroup of calibrate_sweep, 0 where the two kernels take the group: groups wider than a block of the sweep, a loss
+// weight per element, more than 16 rows per compute unit, or more candidates than fit beside the block of U in LDS.
+int fused_rows(const slim_ctx* ctx, int n, int beta, int weight_mode, int ncand) {
+  if (beta > 128 || (weight_mode != SLIM_WEIGHT_MASK_MEAN && weight_mode != SLIM_WEIGHT_UNIFORM)) return 0;
+  int rows = 4;
+  while (rows <= 16 && slim_cdiv(n, rows) > ctx->num_cus) rows *= 2;
+  return rows <= 16 && fused_smem_bytes(beta, rows, ncand) <= 160 * 1024 ? rows : 0;
+}
+
+template <int BETA, bool SIGN, int WPR>
+slim_status launch_fused(slim_ctx* ctx, const FusedArgs& f, int rows) {
+  const size_t smem = fused_smem_bytes(BETA, rows, f.c.ncand);
+  if (smem > 64 * 1024) {
+    static bool done = false;
+    const slim_status st = allow_big_lds(ctx, calibrate_sweep<BETA, SIGN, WPR>, done);
+    if (st != SLIM_OK) return st;
+  }
+  SLIM_LAUNCH(ctx, "sqc_sweep", (calibrate_sweep<BETA, SIGN, WPR>), dim3(slim_cdiv(f.c.n, rows)), dim3(rows * WPR * 64), smem, f);
+  return SLIM_OK;
+}
+template <int BETA>
+slim_status launch_fused(slim_ctx* ctx, const FusedArgs& f, int rows) {
+  const bool sign = (f.c.bits == 1 && f.c.q1_mode == SLIM_Q1_SIGN);
+  if (rows == 16) return sign ? launch_fused<BETA, true, 1>(ctx, f, rows) : launch_fused<BETA, false, 1>(ctx, f, rows);
+  return sign ? launch_fused<BETA, true, 2>(ctx, f, rows) : launch_fused<BETA, false, 2>(ctx, f, rows);
 }
 
 slim_status check_params(slim_ctx* ctx, const slim_params* p, slim_params& out) {
@@ -1044,6 +1279,7 @@ extern "C" slim_status slim_gptq_quantize(slim_ctx* ctx, const void* W, slim_dty
   const int sweep_rows = sweep_waves * SWEEP4_RPW;
   const int sweep_sets = std::min(8, slim_cdiv(n, sweep_rows * ctx->num_cus));
   const size_t sweep_smem = sweep4_smem_bytes(SB, sweep_waves);
+  const int frows = fused_rows(ctx, n, beta, prm.sqc_weight_mode, ncand);
   if (sweep_smem > 64 * 1024) {
     static bool done0 = false, done1 = false;
     st = allow_big_lds(ctx, gptq_sweep4<128, false>, done0);
@@ -1056,8 +1292,8 @@ extern "C" slim_status slim_gptq_quantize(slim_ctx* ctx, const void* W, slim_dty
     const int b0 = sb * SB;
     const int g = b0 / beta;
     const int w0 = (b0 / WINC) * WINC, w1 = std::min(m, w0 + WINC);   // the window of this block
+    SqcArgs a;
     if (b0 % beta == 0) {
-      SqcArgs a;
       a.W = Wc + b0;
       a.ldw = m;
       a.n = n;
@@ -1074,7 +1310,7 @@ extern "C" slim_status slim_gptq_quantize(slim_ctx* ctx, const void* W, slim_dty
       a.zero = zero + g;
       a.out_stride = k;
       a.cand_idx = nullptr;
-      st = launch_stats_and_sqc(ctx, a, stat_partial);
+      st = frows ? launch_stats(ctx, a, stat_partial) : launch_stats_and_sqc(ctx, a, stat_partial);
       if (st != SLIM_OK) return st;
     }
 
@@ -1103,22 +1339,28 @@ extern "C" slim_status slim_gptq_quantize(slim_ctx* ctx, const void* W, slim_dty
                           : static_cast<void*>(static_cast<float*>(What) + b0);
     }
     s.sets = sweep_sets;
-    const dim3 sgrid(slim_cdiv(n, sweep_rows * sweep_sets)), sblock(sweep_waves * 64);
-    const bool sign = (gb[g] == 1 && prm.q1_mode == SLIM_Q1_SIGN);
+    if (frows) {
+      const FusedArgs f{a, s};
+      st = SB == 32 ? launch_fused<32>(ctx, f, frows) : SB == 64 ? launch_fused<64>(ctx, f, frows) : launch_fused<128>(ctx, f, frows);
+      if (st != SLIM_OK) return st;
+    } else {
+      const dim3 sgrid(slim_cdiv(n, sweep_rows * sweep_sets)), sblock(sweep_waves * 64);
+      const bool sign = (gb[g] == 1 && prm.q1_mode == SLIM_Q1_SIGN);
 #define SLIM_SWEEP4(B)                                                                           \
-  do {                                                                                           \
-    if (sign)                                                                                    \
-      SLIM_LAUNCH(ctx, "gptq_sweep", (gptq_sweep4<B, true>), sgrid, sblock, sweep_smem, s);      \
-    else                                                                                         \
-      SLIM_LAUNCH(ctx, "gptq_sweep", (gptq_sweep4<B, false>), sgrid, sblock, sweep_smem, s);     \
-  } while (0)
-    if (SB == 32)
-      SLIM_SWEEP4(32);
-    else if (SB == 64)
-      SLIM_SWEEP4(64);
-    else
-      SLIM_SWEEP4(128);
+    do {                                                                                           \
+      if (sign)                                                                                    \
+        SLIM_LAUNCH(ctx, "gptq_sweep", (gptq_sweep4<B, true>), sgrid, sblock, sweep_smem, s);      \
+      else                                                                                         \
+        SLIM_LAUNCH(ctx, "gptq_sweep", (gptq_sweep4<B, false>), sgrid, sblock, sweep_smem, s);     \
+    } while (0)
+      if (SB == 32)
+        SLIM_SWEEP4(32);
+      else if (SB == 64)
+        SLIM_SWEEP4(64);
+      else
+        SLIM_SWEEP4(128);
 #undef SLIM_SWEEP4
+    }
 
     slim_gemm_desc d;
     d.C2 = nullptr;
