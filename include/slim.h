@@ -296,6 +296,18 @@ slim_status slim_dequant_matmul(slim_ctx* ctx, const uint32_t* packed, int64_t l
                                 int beta, int bit_base, const void* X, slim_dtype x_dtype, int t_x, int64_t ldx,
                                 float* Y, int64_t ldy);
 
+/* The same linear layer as the step between two layers of a chain (Sec. 3.4): Xn (n x t_x fp16, tokens contiguous, ldn >= t_x)
+ * receives its outputs clamped to fp16's range and rounded to nearest even.  Y as above; it is scratch here, of which nothing may
+ * be assumed afterwards. */
+slim_status slim_dequant_matmul_handover(slim_ctx* ctx, const uint32_t* packed, int64_t ldp, const uint32_t* gbits,
+                                         const int32_t* row_off, const double* scale, const double* zero, int n, int m,
+                                         int beta, int bit_base, const void* X, slim_dtype x_dtype, int t_x, int64_t ldx,
+                                         float* Y, int64_t ldy, void* Xn, int64_t ldn);
+
+/* out (cols x rows, ldo >= rows) = X^T of 16-bit elements (X rows x cols, ldx >= cols): activations as the calibration holds them
+ * (channels x tokens) laid out as the linear layer reads them. */
+slim_status slim_transpose_16(slim_ctx* ctx, const void* X, int rows, int cols, int64_t ldx, void* out, int64_t ldo);
+
 /* The same linear layer with the zero points in their packed form (App. B.2: the kernel dequantises the packed weights and
  * the packed zeros): zpacked, ldzp, zbits as slim_pack_zeros writes them; everything else as above.  The zero points are
  * unpacked exactly (in the kernel, or for more than 64 tokens in the context's workspace), so Y is bit for bit that of

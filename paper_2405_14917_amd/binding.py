@@ -29,7 +29,8 @@ EXPORTS = [
     "slim_default_params", "slim_default_tau", "slim_create", "slim_destroy", "slim_last_error",
     "slim_workspace_bytes", "slim_workspace_query", "slim_hessian_accumulate", "slim_hessian_inverse", "slim_salience",
     "slim_sba_allocate", "slim_sba_prepare", "slim_sqc_calibrate", "slim_gptq_quantize", "slim_pack", "slim_dequant_matmul",
-    "slim_dequant_matmul_noalloc", "slim_dequant_matmul_zp", "slim_pack_zeros", "slim_unpack_zeros", "slim_lwc_quantize",
+    "slim_dequant_matmul_noalloc", "slim_dequant_matmul_zp", "slim_dequant_matmul_handover",
+    "slim_transpose_16", "slim_pack_zeros", "slim_unpack_zeros", "slim_lwc_quantize",
     "slim_profile_enable", "slim_profile_collect", "slim_profile_entry", "slim_profile_reset",
 ]
 
@@ -110,6 +111,8 @@ def load() -> ctypes.CDLL:
     lib.slim_dequant_matmul.argtypes = [c_void_p, c_void_p, c_i64, c_void_p, c_void_p, c_void_p, c_void_p, c_int,
                                         c_int, c_int, c_int, c_void_p, c_int, c_int, c_i64, c_void_p, c_i64]
     lib.slim_dequant_matmul_noalloc.argtypes = lib.slim_dequant_matmul.argtypes
+    lib.slim_dequant_matmul_handover.argtypes = lib.slim_dequant_matmul.argtypes + [c_void_p, c_i64]
+    lib.slim_transpose_16.argtypes = [c_void_p, c_void_p, c_int, c_int, c_i64, c_void_p, c_i64]
     lib.slim_dequant_matmul_zp.argtypes = [c_void_p, c_void_p, c_i64, c_void_p, c_void_p, c_void_p, c_void_p, c_i64, c_int,
                                            c_int, c_int, c_int, c_int, c_void_p, c_int, c_int, c_i64, c_void_p, c_i64]
     lib.slim_pack.argtypes = [c_void_p, c_void_p, c_int, c_int, c_i64, c_void_p, c_int, c_int, c_void_p, c_i64,
@@ -395,6 +398,29 @@ class Slim:
                                                     _ptr(scale), _ptr(zpacked), zpacked.stride(0), zbits, n, m, beta,
                                                     bit_base, _ptr(X), _DT[X.dtype], t_x, X.stride(0), _ptr(Y), Y.stride(0)))
         return Y
+
+    def dequant_matmul_handover(self, packed: torch.Tensor, gbits: torch.Tensor, row_off: torch.Tensor, scale: torch.Tensor,
+                                zero: torch.Tensor, beta: int, X: torch.Tensor, Xn: torch.Tensor, Y: torch.Tensor,
+                                bit_base: int = 1):
+        """Xn (n, t_x) float16, tokens contiguous: the outputs for X (t_x, m), clamped and rounded; Y (t_x, n) float32 is
+        scratch."""
+        _need_cuda(packed, gbits, row_off, scale, zero, X, Xn, Y)
+        t_x, m = X.shape
+        n = packed.shape[1]
+        assert scale.dtype == torch.float64 and zero.dtype == torch.float64 and scale.stride(0) == m // beta
+        assert Xn.shape == (n, t_x) and Xn.dtype == torch.float16 and Xn.stride(1) == 1 and Y.shape == (t_x, n)
+        self._check(self.lib.slim_dequant_matmul_handover(self.ctx, _ptr(packed), packed.stride(0), _ptr(gbits), _ptr(row_off),
+                                                          _ptr(scale), _ptr(zero), n, m, beta, bit_base, _ptr(X), _DT[X.dtype],
+                                                          t_x, X.stride(0), _ptr(Y), Y.stride(0), _ptr(Xn), Xn.stride(0)))
+        return Xn
+
+    def transpose_16(self, X: torch.Tensor, out: torch.Tensor):
+        """out (cols, rows) = X (rows, cols) transposed; 16-bit elements, both with contiguous rows."""
+        _need_cuda(X, out)
+        assert X.element_size() == 2 and out.dtype == X.dtype and out.shape == (X.shape[1], X.shape[0])
+        assert X.stride(1) == 1 and out.stride(1) == 1
+        self._check(self.lib.slim_transpose_16(self.ctx, _ptr(X), X.shape[0], X.shape[1], X.stride(0), _ptr(out), out.stride(0)))
+        return out
 
     # ---- measurement aid
     def profile_enable(self, on: bool = True):

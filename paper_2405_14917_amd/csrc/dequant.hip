@@ -255,7 +255,7 @@ slim_status dequant_matmul_tokens(slim_ctx* ctx, const char* fn, const uint32_t*
                                   const uint32_t* gbits, const int32_t* row_off, const double* scale,
                                   const double* zero, int n, int m, int beta, int bit_base, const void* X,
                                   slim_dtype x_dtype, int64_t t_x, int64_t ldx, float* Y, int64_t ldy, float* fixed,
-                                  size_t fixed_floats, const PackedZeros* zp = nullptr) {
+                                  size_t fixed_floats, const PackedZeros* zp = nullptr, __half* hand = nullptr, int64_t ldh = 0) {
   DqArgs a;
   a.packed = packed;
   a.ldp = ldp;
@@ -277,11 +277,15 @@ slim_status dequant_matmul_tokens(slim_ctx* ctx, const char* fn, const uint32_t*
   if (st != SLIM_OK) return st;
   a.k = m / beta;
   a.gper = a.k;
+  // `hand` where Y has been written (the product for many tokens with one range of groups writes it itself)
+  auto handed = [&](slim_status done) {
+    return done == SLIM_OK && hand ? slim_round_transpose(ctx, Y, (int)t_x, n, ldy, hand, ldh) : done;
+  };
   if (slim_dq_few_takes(t_x, ldp, beta, X, ldx)) {
     st = dq_fixed_limit(ctx, fn, a, t_x, fixed, fixed_floats);
     if (st != SLIM_OK) return st;
     a.t_x = (int)t_x;
-    return slim_dq_few_launch(ctx, a, zp);
+    return handed(slim_dq_few_launch(ctx, a, zp));
   }
   const int cus = std::max(1, ctx->num_cus);
   if (slim_dq_gemm_takes(t_x, m, beta, X, ldx)) {
@@ -289,10 +293,15 @@ slim_status dequant_matmul_tokens(slim_ctx* ctx, const char* fn, const uint32_t*
     if (st != SLIM_OK) return st;
     a.t_x = (int)t_x;
     const int splits = slim_dq_gemm_splits(n, m, beta, t_x, cus, a.gper);
+    if (hand && splits == 1) {
+      a.hand = hand;
+      a.ldh = ldh;
+      return slim_dq_gemm_launch(ctx, a, 1);
+    }
     st = dq_partials(ctx, fn, a, splits, fixed, fixed_floats);
     if (st == SLIM_OK) st = slim_dq_gemm_launch(ctx, a, splits);
     if (st == SLIM_OK) st = dq_reduce(ctx, a, splits, Y, ldy);
-    return st;
+    return handed(st);
   }
   if (slim_dq_few_takes(1, ldp, beta, X, ldx)) {
     st = dq_fixed_limit(ctx, fn, a, t_x, fixed, fixed_floats);
@@ -302,7 +311,7 @@ slim_status dequant_matmul_tokens(slim_ctx* ctx, const char* fn, const uint32_t*
       a.out = Y + t0 * ldy;
       st = slim_dq_few_launch(ctx, a, zp);
     }
-    return st;
+    return handed(st);
   }
   for (int64_t t0 = 0; t0 < t_x; t0 += DQ_MAX_T) {
     a.t_x = (int)std::min<int64_t>(DQ_MAX_T, t_x - t0);
@@ -311,7 +320,7 @@ slim_status dequant_matmul_tokens(slim_ctx* ctx, const char* fn, const uint32_t*
     st = dequant_matmul_run(ctx, fn, a, ldy, fixed, fixed_floats);
     if (st != SLIM_OK) return st;
   }
-  return SLIM_OK;
+  return handed(SLIM_OK);
 }
 
 }  // namespace
@@ -356,6 +365,17 @@ extern "C" slim_status slim_dequant_matmul(slim_ctx* ctx, const uint32_t* packed
   if (!ctx) return SLIM_ERR_INVALID_ARG;
   return dequant_matmul_tokens(ctx, "slim_dequant_matmul", packed, ldp, gbits, row_off, scale, zero, n, m, beta,
                                bit_base, X, x_dtype, t_x, ldx, Y, ldy, nullptr, 0);
+}
+
+extern "C" slim_status slim_dequant_matmul_handover(slim_ctx* ctx, const uint32_t* packed, int64_t ldp, const uint32_t* gbits,
+                                                    const int32_t* row_off, const double* scale, const double* zero, int n,
+                                                    int m, int beta, int bit_base, const void* X, slim_dtype x_dtype, int t_x,
+                                                    int64_t ldx, float* Y, int64_t ldy, void* Xn, int64_t ldn) {
+  if (!ctx) return SLIM_ERR_INVALID_ARG;
+  SLIM_REQUIRE(ctx, Xn && (reinterpret_cast<uintptr_t>(Xn) & 1u) == 0, "slim_dequant_matmul_handover: Xn null or misaligned");
+  SLIM_REQUIRE(ctx, ldn >= t_x, "slim_dequant_matmul_handover: ldn < t_x");
+  return dequant_matmul_tokens(ctx, "slim_dequant_matmul_handover", packed, ldp, gbits, row_off, scale, zero, n, m, beta,
+                               bit_base, X, x_dtype, t_x, ldx, Y, ldy, nullptr, 0, nullptr, static_cast<__half*>(Xn), ldn);
 }
 
 extern "C" slim_status slim_dequant_matmul_noalloc(slim_ctx* ctx, const uint32_t* packed, int64_t ldp,

@@ -357,7 +357,32 @@ __global__ __launch_bounds__(PG_THREADS, 2) void dequant_gemm(PgArgs pa) {
   }
 
   const int l32 = lane & 31, h = lane >> 5, row = row0 + wave * 32 + l32;
-  if (row < a.n) {
+  if (row < a.n && a.hand) {
+    // the next layer's calibration activations: a lane has four consecutive tokens of its row at a time (both halves of the
+    // wavefront 16 bytes of a line, which meet in the L2)
+    __half* o = a.hand + (int64_t)row * a.ldh;
+    const bool wide = (reinterpret_cast<uintptr_t>(a.hand) & 7u) == 0 && a.ldh % 4 == 0;
+#pragma unroll
+    for (int i = 0; i < TA; ++i)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int t = tok0 + 32 * i + 8 * q + 4 * h;
+        __half v[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          float f = ysum[i][4 * q + j];
+          f = f > 65504.f ? 65504.f : f < -65504.f ? -65504.f : f;         // (a NaN stays one)
+          v[j] = __float2half_rn(f);
+        }
+        if (wide && t + 4 <= a.t_x) {
+          *reinterpret_cast<uint2*>(o + t) = *reinterpret_cast<const uint2*>(v);
+        } else {
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            if (t + j < a.t_x) o[t + j] = v[j];
+        }
+      }
+  } else if (row < a.n) {
     float* o = a.out + (int64_t)blockIdx.y * a.split_stride + row;
 #pragma unroll
     for (int i = 0; i < TA; ++i)

@@ -94,15 +94,22 @@ def next_layer_input(slim, r, beta, X, n):
     """Calibration activations of the next layer of a chain (Sec. 3.4: every layer inside the GPTQ backbone sees what
     its quantised predecessors emit): the layer of result `r`, applied FROM ITS STORED FORM to the columns of X
     (m x t, fp16, tokens contiguous) by the library's linear-layer kernel for many tokens, rounded to fp16 and
-    laid out channels x tokens again.  Only layout changes and the rounding happen here."""
-    t = X.shape[1]
+    laid out channels x tokens again."""
+    m, t = X.shape
     Xn = torch.empty((n, t), dtype=torch.float16, device=X.device)
-    step = 4096                                      # tokens per call: bounds the size of the transposed copies
-    for t0 in range(0, t, step):
-        xin = X[:, t0:t0 + step].t().contiguous()
-        y = slim.dequant_matmul(r["packed"], r["gbits"], r["row_off"], r["scale"], r["zero"], beta, xin,
-                                bit_base=r["bit_base"])
-        Xn[:, t0:t0 + xin.shape[0]] = y.clamp(-65504.0, 65504.0).to(torch.float16).t()
+    step = min(t, 4096)                              # tokens per call: bounds the size of the transposed copies
+    rows = X.element_size() == 2 and X.stride(1) == 1 and X.stride(0) >= t      # else a copy in any layout comes first
+    xin = torch.empty((step, m), dtype=X.dtype, device=X.device)
+    y = torch.empty((step, n), dtype=torch.float32, device=X.device)
+    for t0 in range(0, t, max(1, step)):
+        cols = X[:, t0:t0 + step]
+        xc = xin[:cols.shape[1]]
+        if rows:
+            slim.transpose_16(cols, xc)
+        else:
+            xc.copy_(cols.t())
+        slim.dequant_matmul_handover(r["packed"], r["gbits"], r["row_off"], r["scale"], r["zero"], beta, xc,
+                                     Xn[:, t0:t0 + step], y[:xc.shape[0]], bit_base=r["bit_base"])
     return Xn
 
 
