@@ -180,8 +180,8 @@ def algorithmic_work(name, cfg, launches_per_step):
         return "latency", None, 0.0                                   # m / 64 dependent diagonal blocks
     if name == "sqc_search":
         return "alu", "alu_f64", 9.0 * cfg.ncand * n * beta          # ~9 fp64 operations per weight and candidate
-    if name == "sqc_sweep":                                           # both in one launch
-        return "alu", "alu_f64", 9.0 * cfg.ncand * n * beta + float(n) * beta * beta
+    if name == "sqc_sweep":                                           # both and the update of the window of 512 in one launch
+        return "alu", "alu_f64", 9.0 * cfg.ncand * n * beta + float(n) * beta * beta + float(n) * beta * max(0, min(m, 512) - beta)
     if name == "gptq_sweep":
         return "alu", "alu_f64", float(n) * beta * beta              # rank-1 updates inside the group
     hbm = {

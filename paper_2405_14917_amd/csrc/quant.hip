@@ -6,8 +6,8 @@
 // are carried at that precision.  CDNA4 runs fp64 vector and matrix work at full rate, so this
 // costs little next to the Hessian.
 //
-// Per group of beta columns four kernels run back to back on the stream (three for layers of up to 16 rows per compute unit, where
-// calibrate_sweep does the work of the two in the middle):
+// Per group of beta columns four kernels run back to back on the stream (one for layers of up to 16 rows per compute unit, where
+// calibrate_sweep does the work of the last three, and of the first for the next group of the window):
 //   block_stats   shifted sums of the current block (for the block-wide 3-sigma rule), per row slab
 //   sqc_search_fast / sqc_search_weighted   a few rows per workgroup: row min/max/mean|w|, the mask or the loss
 //                 weights, then a few lanes per (row, 4 or 5 candidates) walk the row's weights in LDS;
@@ -311,6 +311,7 @@ __device__ __forceinline__ double vmin_f64(double a, double b) {
 // through DPP inside a 16-lane row and lane reads across rows.
 // ------------------------------------------------------------------------------------------
 typedef double double2v __attribute__((ext_vector_type(2)));
+typedef double double4s __attribute__((ext_vector_type(4)));
 constexpr int SQF_CPT = 5;     // candidates per lane
 constexpr int SQF_PAD = 8;     // doubles of padding per LDS row
 
@@ -881,29 +882,36 @@ __global__ __launch_bounds__(1024) void gptq_sweep4(SweepArgs a) {
 }
 
 // ------------------------------------------------------------------------------------------
-// Calibration and sweep of a group in one launch, for layers that fill the chip with at most 16 rows per workgroup (one round
+// Calibration, sweep and window update of a group in one launch, for layers that fill the chip with at most 16 rows per workgroup (one round
 // of workgroups).  There both kernels are bound by latencies in a row, launch, block of U, rows, parameters, and the second
 // needs of the first only its own rows.  Here the block of U and the rows come while the block's statistics do; one or two
 // wavefronts search a row (16 quads of lanes, 7 or 4 candidates each, the order of the sums of sqc_search_fast) and every fourth
-// one goes on to sweep four rows from LDS.  Whole pass: 1000 x 1504 in groups of 32 2.23 -> 2.01 ms (4.7 us a group),
-// 4096 x 4096 in groups of 128 8.11 -> 7.80 ms (9.6 us a group of 42).  With more rows than one round takes the two kernels stay:
+// one goes on to sweep four rows from LDS.  Then all of them update the workgroup's own rows of the window, and sum up the next
+// block's, which saves the product's and the statistics' launches too: the product read U once per 64 rows, and this once per 16
+// from the L2, but waits for nothing.  Whole pass: 1000 x 1504 in groups of 32 2.23 -> 1.71 ms (2.01 without the update),
+// 4096 x 4096 in groups of 128 8.11 -> 7.50 ms (7.80), 256 x 256 415 -> 371 us.  With more rows than one round takes the two kernels stay:
 // the search shares a CU among 20 wavefronts there and the sweep one block of U among several sets of rows, and what the launch
 // costs is small beside their 110 and 70 us (28672 rows).
 // ------------------------------------------------------------------------------------------
 struct FusedArgs {
   SqcArgs c;
   SweepArgs s;
+  const double* wstat;   // the block's sums as the previous launch left them (shift, sum, sum of squares of a workgroup's rows, `rows`
+  int64_t wstat_stride;  // rows of W apart), or null: in c.stat_partial
+  int ncols;             // columns of the window behind the block
+  int next_stats;        // leave the sums of the next block, in the last three columns of this one
 };
 
 // doubles in LDS: packed U, 1 / diagonal, rows, errors (the salient weights before), losses, tau, parameters, sums; then codes
+constexpr int FUSED_EPAD = 2;      // padding of a row of errors: sixteen rows of the update's operand in different banks
 size_t fused_smem_bytes(int beta, int rows, int ncand) {
   const size_t packed = (size_t)sweep4_row_off(beta, beta / 16, 0);
-  return sizeof(double) * (packed + beta + 2 * (size_t)rows * beta + (size_t)rows * ncand + ncand + 2 * rows + 32) + (size_t)rows * beta;
+  return sizeof(double) * (packed + beta + (size_t)rows * (2 * beta + FUSED_EPAD) + (size_t)rows * ncand + ncand + 2 * rows + 32) + (size_t)rows * beta;
 }
 
 template <int BETA, bool SIGN, int WPR>
 __global__ __launch_bounds__(1024) void calibrate_sweep(FusedArgs f) {
-  constexpr int NK = BETA / 16, PACKED = sweep4_row_off(BETA, NK, 0), CPT = WPR == 1 ? 7 : 4;
+  constexpr int NK = BETA / 16, PACKED = sweep4_row_off(BETA, NK, 0), CPT = WPR == 1 ? 7 : 4, ES = BETA + FUSED_EPAD;
   constexpr int NT = WPR == 1 ? 1024 : 512, FILL = (PACKED / 2 + NT - 1) / NT;     // loads of the block per thread
   extern __shared__ __align__(16) double Us[];
   const SqcArgs& a = f.c;
@@ -911,8 +919,8 @@ __global__ __launch_bounds__(1024) void calibrate_sweep(FusedArgs f) {
   const int rows = nwaves / WPR, ncand = a.ncand;
   double* rdiag = Us + PACKED;
   double* wrow = rdiag + BETA;                       // [rows][BETA]
-  double* ebase = wrow + rows * BETA;                // [rows][BETA] errors; before, each row's salient weights
-  double* loss = ebase + rows * BETA;                // [rows][ncand]
+  double* ebase = wrow + rows * BETA;                // [rows][ES] errors; before, each row's salient weights
+  double* loss = ebase + rows * ES;                  // [rows][ncand]
   double* tgrid = loss + rows * ncand;
   double* par = tgrid + ncand;                       // [rows][2] scale, zero
   double* red = par + 2 * rows;                      // [2][16]
@@ -938,14 +946,25 @@ __global__ __launch_bounds__(1024) void calibrate_sweep(FusedArgs f) {
     const int c = q * 64 + lane;
     v[q] = live && c < BETA ? a.W[(int64_t)row * a.ldw + c] : 0.0;
   }
-  double s1 = 0.0, s2 = 0.0;
+  double s1 = 0.0, s2 = 0.0, shift = 0.0;
   if (block_scope) {
-    for (int p = tid; p < a.nstat; p += nthreads) {
-      s1 += a.stat_partial[2 * p];
-      s2 += a.stat_partial[2 * p + 1];
+    if (f.wstat) {
+      // sums about each workgroup's own shift, taken to that of the first
+      shift = f.wstat[0];
+      for (int p = tid; p < (int)gridDim.x; p += nthreads) {
+        const double* q = f.wstat + p * f.wstat_stride;
+        const double d = q[0] - shift, c = (double)(min(rows, a.n - p * rows) * BETA);
+        s1 += fma(c, d, q[1]);
+        s2 += fma(d, fma(c, d, 2.0 * q[1]), q[2]);
+      }
+    } else {
+      shift = a.W[0];
+      for (int p = tid; p < a.nstat; p += nthreads) {
+        s1 += a.stat_partial[2 * p];
+        s2 += a.stat_partial[2 * p + 1];
+      }
     }
   }
-  const double shift = block_scope ? a.W[0] : 0.0;
   for (int c = tid; c < ncand; c += nthreads) tgrid[c] = a.tau[c];
   for (int j = tid; j < BETA; j += nthreads) rdiag[j] = 1.0 / f.s.U[(int64_t)j * f.s.ldu + j];
   if (block_scope) {
@@ -968,7 +987,7 @@ __global__ __launch_bounds__(1024) void calibrate_sweep(FusedArgs f) {
   double d0 = 1.0, z = 0.0, alpha = 0.0;
   if (live) {
     double* w = wrow + r * BETA;
-    double* sal = ebase + r * BETA;
+    double* sal = ebase + r * ES;
     double mn = INFINITY, mx = -INFINITY, sabs = 0.0, sum = 0.0;
 #pragma unroll
     for (int q = 0; q < NV; ++q) {
@@ -1047,12 +1066,82 @@ __global__ __launch_bounds__(1024) void calibrate_sweep(FusedArgs f) {
   }
   __syncthreads();
 
-  // no barrier below
-  const int rl = wave * SWEEP4_RPW + (lane >> 4), l16 = lane & 15;
-  if (wave * SWEEP4_RPW >= rows || r0 + wave * SWEEP4_RPW >= a.n) return;
-  const bool valid = r0 + rl < a.n;
-  sweep4_rows<BETA, SIGN>(f.s, Us, rdiag, ebase + rl * BETA, qbase + rl * BETA, wrow + rl * BETA, r0 + rl, valid, l16,
-                          valid ? par[2 * rl] : 1.0, valid ? par[2 * rl + 1] : 0.0);
+  const int lk = lane >> 4, l16 = lane & 15;
+  if (wave * SWEEP4_RPW < rows && r0 + wave * SWEEP4_RPW < a.n) {
+    const int rl = wave * SWEEP4_RPW + lk;
+    const bool valid = r0 + rl < a.n;
+    sweep4_rows<BETA, SIGN>(f.s, Us, rdiag, ebase + rl * ES, qbase + rl * BETA, wrow + rl * BETA, r0 + rl, valid, l16,
+                            valid ? par[2 * rl] : 1.0, valid ? par[2 * rl + 1] : 0.0);
+  }
+  if (f.ncols == 0) return;                          // (the same for the whole launch)
+
+  // The rest of the window (Alg. 1 line 12): W -= E U on the fp64 matrix cores, 16 columns at a time, the workgroup's rows as one
+  // tile of 16.  U comes from the L2 in the order of the operand, the next tile's behind the MFMAs that use the present one's, the
+  // first while the sweep runs.  Same sums as the product on its own.
+  const int swave = __builtin_amdgcn_readfirstlane(wave);
+  const unsigned uoff = ((unsigned)lk * (unsigned)f.s.ldu + BETA + l16) * 8u;     // (the rest of the address is scalar)
+  const char* ubase = reinterpret_cast<const char*>(f.s.U);
+  const int64_t ustep = f.s.ldu * 32;
+  double* wp = f.s.W + (int64_t)(r0 + lk) * f.s.ldw + BETA + l16;
+  const int tiles = f.ncols / 16;
+  int ct = swave;
+  double ub[BETA / 4];
+  if (ct < tiles) {
+#pragma unroll
+    for (int i = 0; i < BETA / 4; ++i) ub[i] = *reinterpret_cast<const double*>(ubase + ct * 128 + i * ustep + uoff);
+  }
+  const double nshift = f.s.W[(int64_t)r0 * f.s.ldw + BETA];     // before the update: near the block's values is all it has to be
+  __syncthreads();
+  s1 = s2 = 0.0;
+  const double* ea = ebase + min(l16, rows - 1) * ES + lk;
+  for (; ct < tiles; ct += nwaves) {
+    double cold[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const bool mine = 4 * q + lk < rows && r0 + 4 * q + lk < a.n;
+      cold[q] = mine ? wp[(int64_t)(4 * q) * f.s.ldw + ct * 16] : 0.0;
+    }
+    const int nt = min(ct + nwaves, tiles - 1);
+    double4s acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int i = 0; i < BETA / 4; ++i) {
+      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(ea[4 * i], ub[i], acc, 0, 0, 0);
+      ub[i] = *reinterpret_cast<const double*>(ubase + nt * 128 + i * ustep + uoff);
+      if (i % 4 == 3) __builtin_amdgcn_sched_barrier(0);     // (or all operands of the tile are read at once, and spill)
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {                    // acc[q] is row 4 q + lk of column l16
+      if (4 * q + lk < rows && r0 + 4 * q + lk < a.n) {
+        const double nv = cold[q] - acc[q];
+        wp[(int64_t)(4 * q) * f.s.ldw + ct * 16] = nv;
+        if (ct < BETA / 16) {
+          const double d = nv - nshift;
+          s1 += d;
+          s2 = fma(d, d, s2);
+        }
+      }
+    }
+  }
+  if (!f.next_stats) return;
+  s1 = wave_allreduce<OpSum>(s1);
+  s2 = wave_allreduce<OpSum>(s2);
+  if (lane == 0) {
+    red[2 * wave] = s1;
+    red[2 * wave + 1] = s2;
+  }
+  __syncthreads();
+  if (tid == 0) {
+    double S1 = 0.0, S2 = 0.0;
+    for (int i = 0; i < nwaves; ++i) {
+      S1 += red[2 * i];
+      S2 += red[2 * i + 1];
+    }
+    // the swept block's columns of W are not read any more (but for its first element, by launches that start from c.stat_partial)
+    double* o = f.s.W + (int64_t)r0 * f.s.ldw + BETA - 3;
+    o[0] = nshift;
+    o[1] = S1;
+    o[2] = S2;
+  }
 }
 
 // Kernels that may need more than the default 64 KiB of dynamic LDS opt in once per process.
@@ -1114,9 +1203,10 @@ slim_status launch_stats_and_sqc(slim_ctx* ctx, SqcArgs a, double* stat_partial)
 }
 
 // Rows per workgroup of calibrate_sweep, 0 where the two kernels take the group: groups wider than a block of the sweep, a loss
-// weight per element, more than 16 rows per compute unit, or more candidates than fit beside the block of U in LDS.
-int fused_rows(const slim_ctx* ctx, int n, int beta, int weight_mode, int ncand) {
-  if (beta > 128 || (weight_mode != SLIM_WEIGHT_MASK_MEAN && weight_mode != SLIM_WEIGHT_UNIFORM)) return 0;
+// weight per element, more than 16 rows per compute unit, more candidates than fit beside the block of U in LDS, or rows of U further
+// apart than its 32-bit offsets reach.
+int fused_rows(const slim_ctx* ctx, int n, int beta, int weight_mode, int ncand, int64_t ldu) {
+  if (beta > 128 || ldu >= (1 << 26) || (weight_mode != SLIM_WEIGHT_MASK_MEAN && weight_mode != SLIM_WEIGHT_UNIFORM)) return 0;
   int rows = 4;
   while (rows <= 16 && slim_cdiv(n, rows) > ctx->num_cus) rows *= 2;
   return rows <= 16 && fused_smem_bytes(beta, rows, ncand) <= 160 * 1024 ? rows : 0;
@@ -1279,7 +1369,7 @@ extern "C" slim_status slim_gptq_quantize(slim_ctx* ctx, const void* W, slim_dty
   const int sweep_rows = sweep_waves * SWEEP4_RPW;
   const int sweep_sets = std::min(8, slim_cdiv(n, sweep_rows * ctx->num_cus));
   const size_t sweep_smem = sweep4_smem_bytes(SB, sweep_waves);
-  const int frows = fused_rows(ctx, n, beta, prm.sqc_weight_mode, ncand);
+  const int frows = fused_rows(ctx, n, beta, prm.sqc_weight_mode, ncand, ldu);
   if (sweep_smem > 64 * 1024) {
     static bool done0 = false, done1 = false;
     st = allow_big_lds(ctx, gptq_sweep4<128, false>, done0);
@@ -1288,6 +1378,7 @@ extern "C" slim_status slim_gptq_quantize(slim_ctx* ctx, const void* W, slim_dty
     if (st != SLIM_OK) return st;
   }
 
+  const double* wstat = nullptr;       // where calibrate_sweep has left the sums of the block that comes next
   for (int sb = 0; sb < m / SB; ++sb) {
     const int b0 = sb * SB;
     const int g = b0 / beta;
@@ -1310,7 +1401,10 @@ extern "C" slim_status slim_gptq_quantize(slim_ctx* ctx, const void* W, slim_dty
       a.zero = zero + g;
       a.out_stride = k;
       a.cand_idx = nullptr;
-      st = frows ? launch_stats(ctx, a, stat_partial) : launch_stats_and_sqc(ctx, a, stat_partial);
+      if (!frows)
+        st = launch_stats_and_sqc(ctx, a, stat_partial);
+      else if (!wstat)
+        st = launch_stats(ctx, a, stat_partial);
       if (st != SLIM_OK) return st;
     }
 
@@ -1340,7 +1434,9 @@ extern "C" slim_status slim_gptq_quantize(slim_ctx* ctx, const void* W, slim_dty
     }
     s.sets = sweep_sets;
     if (frows) {
-      const FusedArgs f{a, s};
+      FusedArgs f{a, s, wstat, (int64_t)frows * m, w1 - (b0 + SB), 0};
+      f.next_stats = f.ncols > 0 && prm.sqc_weight_mode == SLIM_WEIGHT_MASK_MEAN && prm.mask_scope == SLIM_SCOPE_BLOCK;
+      wstat = f.next_stats ? Wc + b0 + SB - 3 : nullptr;
       st = SB == 32 ? launch_fused<32>(ctx, f, frows) : SB == 64 ? launch_fused<64>(ctx, f, frows) : launch_fused<128>(ctx, f, frows);
       if (st != SLIM_OK) return st;
     } else {
@@ -1372,7 +1468,7 @@ extern "C" slim_status slim_gptq_quantize(slim_ctx* ctx, const void* W, slim_dty
     d.lda = WINC;
     d.ldb = ldu;
     d.ldc = m;
-    if (b0 + SB < w1) {
+    if (b0 + SB < w1 && !frows) {
       // the rest of the window
       d.A = E + (b0 - w0);
       d.B = U + (int64_t)b0 * ldu + (b0 + SB);
@@ -1381,7 +1477,7 @@ extern "C" slim_status slim_gptq_quantize(slim_ctx* ctx, const void* W, slim_dty
       d.K = SB;
       st = slim_dgemm(ctx, "gptq_window_dgemm", 0, d);
       if (st != SLIM_OK) return st;
-    } else if (w1 < m) {
+    } else if (b0 + SB == w1 && w1 < m) {
       // last block of the window: everything behind it
       d.A = E;
       d.B = U + (int64_t)w0 * ldu + w1;

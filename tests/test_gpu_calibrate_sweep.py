@@ -1,5 +1,5 @@
-"""Calibration and sweep in one launch (layers of up to 16 rows per compute unit) against the two kernels that take larger layers:
-with the unweighted loss no row depends on another, so the first rows of a layer that is too large for the one launch are,
+"""Calibration, sweep and window update in one launch (layers of up to 16 rows per compute unit) against the kernels that take larger
+layers: with the unweighted loss no row depends on another, so the first rows of a layer that is too large for the one launch are,
 byte for byte, those rows alone."""
 import numpy as np
 import pytest
@@ -30,13 +30,14 @@ def layer(n, m, seed):
     return torch.from_numpy(W).cuda(), torch.from_numpy(np.ascontiguousarray(U)).cuda()
 
 
-@pytest.mark.parametrize("beta", [32, 64, 128])
-@pytest.mark.parametrize("ncand", [1, 100, 113, 129])
-def test_one_launch_equals_two(slim, beta, ncand):
+@pytest.mark.parametrize("beta,groups,ncand", [(32, 4, 1), (32, 20, 100), (32, 1, 113), (32, 16, 129), (64, 4, 1), (64, 10, 100), (64, 4, 129),
+                                               (128, 4, 1), (128, 7, 100), (128, 2, 113), (128, 5, 129)])
+def test_one_launch_equals_several(slim, beta, groups, ncand):
+    """(windows of 512 columns: whole, several, a last one that is not full, a single block)"""
     cus = torch.cuda.get_device_properties(0).multi_processor_count
-    m = 4 * beta
+    m = groups * beta
     W, U = layer(16 * cus + 1, m, beta + ncand)
-    bits = torch.tensor([1, 2, 3, 5], dtype=torch.uint8, device="cuda")
+    bits = torch.tensor(([1, 2, 3, 5] * groups)[:groups], dtype=torch.uint8, device="cuda")
     tau = 0.9 + 0.2 * torch.arange(ncand, dtype=torch.float64, device="cuda") / ncand
     prm = binding.SlimParams(sqc_weight_mode=UNIFORM)
     whole = slim.gptq_quantize(W, U, bits, beta, params=prm, tau=tau, want_what=torch.float64)
