@@ -618,7 +618,8 @@ __global__ __launch_bounds__(512) void chol_link(LinkArgs g) {
   }
 }
 
-// partial column sums of squares of the upper triangle of U: grid (ceil(m/64), parts); part p owns 256 rows
+// partial column sums of squares of the upper triangle of U: grid (ceil(m/64), parts); part p owns 256 rows.  A thread has 64 of
+// them and sixteen loads in flight (one load after the other took 20 us at 1504 columns, where few workgroups share the chip).
 __global__ __launch_bounds__(256) void colsumsq_upper(const double* __restrict__ U, int64_t ldu, int m,
                                                       double* __restrict__ partial) {
   __shared__ double red[4][64];
@@ -628,9 +629,14 @@ __global__ __launch_bounds__(256) void colsumsq_upper(const double* __restrict__
   double acc = 0.0;
   if (c < m) {
     const int r1 = min(min(m, r0 + 256), c + 1);
-    for (int r = r0 + ty; r < r1; r += 4) {
-      const double v = U[(int64_t)r * ldu + c];
-      acc += v * v;
+    constexpr int UR = 16;
+    for (int r = r0 + ty; r < r1; r += 4 * UR) {
+      double v[UR];
+#pragma unroll
+      for (int u = 0; u < UR; ++u) v[u] = U[(int64_t)min(r + 4 * u, r1 - 1) * ldu + c];
+#pragma unroll
+      for (int u = 0; u < UR; ++u)
+        if (r + 4 * u < r1) acc += v[u] * v[u];
     }
   }
   red[ty][tx] = acc;

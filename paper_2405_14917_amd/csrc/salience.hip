@@ -76,7 +76,14 @@ __global__ __launch_bounds__(1024) void salience_finalize(const double* __restri
     const int c = g * beta + j;
     double s = 0.0;
     if (sl < slices && j < beta)
-      for (int p = sl; p < nparts; p += slices) s += partial[(int64_t)p * m + c];
+      for (int p = sl; p < nparts; p += 8 * slices) {
+        double v8[8];                            // loads first, then the additions in order
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v8[u] = partial[(int64_t)min(p + u * slices, nparts - 1) * m + c];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+          if (p + u * slices < nparts) s += v8[u];
+      }
     __syncthreads();
     red[threadIdx.x] = s;
     __syncthreads();

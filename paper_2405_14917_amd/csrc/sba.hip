@@ -40,6 +40,7 @@ namespace {
 using namespace slimint;
 
 constexpr int KL_TOK = 64;     // tokens per workgroup
+constexpr int KL_UR = 8;        // loads in flight per thread: on small layers few workgroups share the chip
 constexpr int KL_PART = 3;     // planes of the reference side's partials: max y, sum exp y, sum P log P
 
 __global__ __launch_bounds__(256) void sba_rank(const double* __restrict__ sal, int k, int* __restrict__ order,
@@ -97,13 +98,27 @@ __global__ __launch_bounds__(256) void kl_ref_partial(const double* __restrict__
   const bool live = t < ts;
   double my = -INFINITY;
   if (live)
-    for (int r = r0 + ty; r < r1; r += 4) my = fmax(my, Y[(int64_t)r * ts + t]);
+    for (int r = r0 + ty; r < r1; r += 4 * KL_UR) {
+      double v[KL_UR];
+#pragma unroll
+      for (int u = 0; u < KL_UR; ++u) v[u] = Y[(int64_t)min(r + 4 * u, r1 - 1) * ts + t];
+#pragma unroll
+      for (int u = 0; u < KL_UR; ++u)
+        if (r + 4 * u < r1) my = fmax(my, v[u]);
+    }
   red[0][ty][tx] = my;
   __syncthreads();
   my = fmax(fmax(red[0][0][tx], red[0][1][tx]), fmax(red[0][2][tx], red[0][3][tx]));
   double zy = 0.0;
   if (live && my > -INFINITY)
-    for (int r = r0 + ty; r < r1; r += 4) zy += exp(Y[(int64_t)r * ts + t] - my);
+    for (int r = r0 + ty; r < r1; r += 4 * KL_UR) {
+      double v[KL_UR];
+#pragma unroll
+      for (int u = 0; u < KL_UR; ++u) v[u] = Y[(int64_t)min(r + 4 * u, r1 - 1) * ts + t];
+#pragma unroll
+      for (int u = 0; u < KL_UR; ++u)
+        if (r + 4 * u < r1) zy += exp(v[u] - my);
+    }
   red[1][ty][tx] = zy;
   __syncthreads();
   if (ty == 0 && live) {
@@ -140,11 +155,18 @@ __global__ __launch_bounds__(256) void kl_ref_softmax(double* __restrict__ Y, in
   double b = 0.0;
   if (t < ts) {
     const double lse = tok[2 * t + 1];
-    for (int r = r0 + ty; r < r1; r += 4) {
-      const double lp = Y[(int64_t)r * ts + t] - lse;
-      const double pr = exp(lp);
-      Y[(int64_t)r * ts + t] = pr;
-      b = fma(pr, lp, b);
+    for (int r = r0 + ty; r < r1; r += 4 * KL_UR) {
+      double v[KL_UR];
+#pragma unroll
+      for (int u = 0; u < KL_UR; ++u) v[u] = Y[(int64_t)min(r + 4 * u, r1 - 1) * ts + t];
+#pragma unroll
+      for (int u = 0; u < KL_UR; ++u)
+        if (r + 4 * u < r1) {
+          const double lp = v[u] - lse;
+          const double pr = exp(lp);
+          Y[(int64_t)(r + 4 * u) * ts + t] = pr;
+          b = fma(pr, lp, b);
+        }
     }
   }
   red[ty][tx] = b;
