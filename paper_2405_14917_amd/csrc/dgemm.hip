@@ -235,13 +235,6 @@ __global__ __launch_bounds__(NTHREADS) void dgemm_kernel(slim_gemm_desc d) {
   gemm_body<TRANS_B, BM, BN>(d, blockIdx.x, smem);
 }
 
-template <int TRANS_B, int BM, int BN>
-__global__ __launch_bounds__(NTHREADS) void dgemm_batched_kernel(const slim_gemm_desc* descs) {
-  extern __shared__ __align__(16) double smem[];
-  const slim_gemm_desc d = descs[blockIdx.y];
-  gemm_body<TRANS_B, BM, BN>(d, blockIdx.x, smem);
-}
-
 // Persistent form for bulk work beside a latency-critical chain on another stream: fewer workgroups than CUs, each
 // taking tiles in turn, with an LDS request that lets nothing else of any size share their CUs.  The CUs it leaves
 // out stay free for the chain's kernels.  With SLIM_GEMM_UPPER_ONLY (M == N) only the tiles on or above the
@@ -270,8 +263,8 @@ __global__ __launch_bounds__(NTHREADS) void dgemm_reserved_kernel(slim_gemm_desc
 constexpr size_t smem_bytes(int bm, int bn) { return size_t(2) * (BK * bm + BK * bn) * sizeof(double); }
 
 // 64 x 64 tiles when 128 x 128 tiles would leave most of the 256 CUs without work
-bool use_small_tiles(int M, int N, int count) {
-  return (int64_t)slim_cdiv(M, 128) * slim_cdiv(N, 128) * count < 192;
+bool use_small_tiles(int M, int N) {
+  return (int64_t)slim_cdiv(M, 128) * slim_cdiv(N, 128) < 192;
 }
 
 slim_status check_desc(slim_ctx* ctx, const slim_gemm_desc& d) {
@@ -305,7 +298,7 @@ slim_status slim_dgemm(slim_ctx* ctx, const char* name, int trans_b, const slim_
   slim_status st = check_desc(ctx, d);
   if (st != SLIM_OK) return st;
   if (d.M == 0 || d.N == 0) return SLIM_OK;
-  if (use_small_tiles(d.M, d.N, 1)) {
+  if (use_small_tiles(d.M, d.N)) {
     const int tiles = slim_cdiv(d.M, 64) * slim_cdiv(d.N, 64);
     if (trans_b)
       SLIM_LAUNCH(ctx, slim_prof_name(name, "dgemm_kernel<1, 64, 64>"), (dgemm_kernel<1, 64, 64>), dim3(tiles),
@@ -358,31 +351,5 @@ slim_status slim_dgemm(slim_ctx* ctx, const char* name, int trans_b, const slim_
   else
     SLIM_LAUNCH(ctx, slim_prof_name(name, "dgemm_kernel<0, 128, 128>"), (dgemm_kernel<0, 128, 128>), dim3(tiles),
                 dim3(NTHREADS), lds, d);
-  return SLIM_OK;
-}
-
-slim_status slim_dgemm_batched(slim_ctx* ctx, const char* name, int trans_b, const slim_gemm_desc* descs_dev,
-                               int count, int max_M, int max_N) {
-  if (count == 0 || max_M == 0 || max_N == 0) return SLIM_OK;
-  // The products of a batch have triangular operands, so the K ranges of their tiles differ by large factors: up to
-  // two rounds of 128 x 128 tiles would last as long as the longest tile, while many 64 x 64 tiles per CU even out.
-  const bool uneven = (int64_t)slim_cdiv(max_M, 128) * slim_cdiv(max_N, 128) * count <= 2 * (int64_t)ctx->num_cus;
-  if (uneven || use_small_tiles(max_M, max_N, count)) {
-    const int tiles = slim_cdiv(max_M, 64) * slim_cdiv(max_N, 64);
-    if (trans_b)
-      SLIM_LAUNCH(ctx, slim_prof_name(name, "dgemm_batched_kernel<1, 64, 64>"), (dgemm_batched_kernel<1, 64, 64>),
-                  dim3(tiles, count), dim3(NTHREADS), smem_bytes(64, 64), descs_dev);
-    else
-      SLIM_LAUNCH(ctx, slim_prof_name(name, "dgemm_batched_kernel<0, 64, 64>"), (dgemm_batched_kernel<0, 64, 64>),
-                  dim3(tiles, count), dim3(NTHREADS), smem_bytes(64, 64), descs_dev);
-    return SLIM_OK;
-  }
-  const int tiles = slim_cdiv(max_M, 128) * slim_cdiv(max_N, 128);
-  if (trans_b)
-    SLIM_LAUNCH(ctx, slim_prof_name(name, "dgemm_batched_kernel<1, 128, 128>"), (dgemm_batched_kernel<1, 128, 128>),
-                dim3(tiles, count), dim3(NTHREADS), smem_bytes(128, 128), descs_dev);
-  else
-    SLIM_LAUNCH(ctx, slim_prof_name(name, "dgemm_batched_kernel<0, 128, 128>"), (dgemm_batched_kernel<0, 128, 128>),
-                dim3(tiles, count), dim3(NTHREADS), smem_bytes(128, 128), descs_dev);
   return SLIM_OK;
 }

@@ -13,7 +13,7 @@
 //        update      rank-64 update with that panel of the columns from the start of block J's group on
 //      and once per group rank-512 updates of everything further left; see the schedule at the call site.
 //   3. triangular inverse U = R^-1 group by group on a further stream, beside the factorisation: inside a group
-//      by recursive doubling (ranges of 2^l inverted diagonal blocks merged pairwise, U12 = -U11 (R12 U22)), the
+//      strip by strip of 16 columns from the inverted diagonal blocks upwards, in one launch, the
 //      rows right of the group from T = R[g, S] U[S, S], which is kept up to date for all rows above by one
 //      rank-512 product per finished group (see the schedule at the call site).
 //   4. hinv_diag_j = sum_i U_ij^2.
@@ -618,6 +618,86 @@ __global__ __launch_bounds__(512) void chol_link(LinkArgs g) {
   }
 }
 
+// ---- the triangular inverse inside a group -----------------------------------------------------------------------
+// U[i, j] = -U[i, i] sum over k = i + 1 .. j of R[i, k] U[k, j] for the blocks of a group, i upwards from j - 1: a workgroup takes 16
+// columns of a block column j and keeps them in LDS, so that the whole group is one launch.  grid: 4 strips of each block column from
+// the second on, the longest chains first; 4 wavefronts, each 16 rows of the block in hand.
+//
+// What bounds it is the chain of a strip's MFMAs, 28 * 16 + 7 * 16 per wavefront at most, 15 us, on 28 CUs; merging inverted ranges
+// pairwise does the same work in six launches, each a row of load latencies: 78 us for 512 columns beside the factorisation, 65 alone.
+// The rows of R and U come 16 bytes per lane, a block of 64 x 64 ahead of the MFMAs: lane l has row l % 16 and four
+// consecutive k from 4 (l / 16), which are the k of four MFMAs (the contraction may run in any order as long as both operands agree).
+constexpr int GI_XS = 20;        // doubles per LDS row of 16 columns: the four rows that a wavefront reads lie in different banks
+constexpr size_t GI_LDS = sizeof(double) * GI_XS * (GRP * NB + NB);
+
+struct GroupInvArgs {
+  const double* R;               // at (g0, g0)
+  int64_t ldr;
+  double* U;
+  int64_t ldu;
+  int w;                         // columns of the group
+};
+
+__global__ __launch_bounds__(256) void group_inverse_cols(GroupInvArgs a) {
+  extern __shared__ __align__(16) double gi_sm[];
+  double* X = gi_sm;                                 // [64 nb][GI_XS] the strip's columns of U
+  double* T = X + GRP * NB * GI_XS;                  // [64][GI_XS]
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l16 = lane & 15, lk = lane >> 4;
+  const int nb = (a.w + NB - 1) / NB, j = nb - 1 - (int)blockIdx.x / 4, c0 = j * NB + ((int)blockIdx.x & 3) * 16;
+  if (c0 >= a.w) return;                             // (the last block may be narrower)
+  const bool live = c0 + l16 < a.w;
+  for (int e = tid; e < NB * 16; e += 256) {
+    const int r = e >> 4, c = e & 15;
+    X[(j * NB + r) * GI_XS + c] = j * NB + r < a.w && c0 + c < a.w ? a.U[(int64_t)(j * NB + r) * a.ldu + c0 + c] : 0.0;
+  }
+  // this wavefront's 16 rows of the 64 x 64 block at p (row 0 of the block), `lim` columns of it valid: behind them X is zero
+  auto load = [&](const double* p, int64_t ld, int lim, double2 (&f)[8]) {
+    p += (int64_t)(16 * wave + l16) * ld;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) f[q] = *reinterpret_cast<const double2*>(p + min(16 * (q >> 1) + 4 * lk + 2 * (q & 1), lim - 2));
+  };
+  auto multiply = [&](const double2 (&f)[8], const double* x, int from, double4v acc) {
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      if (q < 2 * from) continue;
+      const double* xq = x + (16 * (q >> 1) + 4 * lk + 2 * (q & 1)) * GI_XS + l16;
+      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(f[q].x, xq[0], acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(f[q].y, xq[GI_XS], acc, 0, 0, 0);
+    }
+    return acc;
+  };
+  auto block_r = [&](int i, int k) { return a.R + (int64_t)i * NB * a.ldr + k * NB; };
+  auto width = [&](int k) { return min(NB, a.w - k * NB); };
+  double2 f[8], fn[8], fu[8];
+  load(block_r(j - 1, j), a.ldr, width(j), f);
+  __syncthreads();
+  for (int i = j - 1; i >= 0; --i) {
+    load(a.U + (int64_t)i * NB * (a.ldu + 1), a.ldu, NB, fu);
+    double4v acc = {0.0, 0.0, 0.0, 0.0};
+    for (int k = j; k > i; --k) {                    // (the block column that the last step has finished comes last)
+      if (k > i + 1)
+        load(block_r(i, k - 1), a.ldr, NB, fn);
+      else if (i > 0)
+        load(block_r(i - 1, j), a.ldr, width(j), fn);
+      acc = multiply(f, X + k * NB * GI_XS, 0, acc);
+#pragma unroll
+      for (int q = 0; q < 8; ++q) f[q] = fn[q];
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) T[(16 * wave + 4 * v + lk) * GI_XS + l16] = acc[v];
+    __syncthreads();
+    acc = double4v{0.0, 0.0, 0.0, 0.0};
+    acc = multiply(fu, T, wave, acc);                // (U[i, i] is upper triangular: its columns left of the wavefront's rows are zero)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int r = i * NB + 16 * wave + 4 * v + lk;
+      X[r * GI_XS + l16] = -acc[v];
+      if (live) a.U[(int64_t)r * a.ldu + c0 + l16] = -acc[v];
+    }
+    __syncthreads();
+  }
+}
+
 // partial column sums of squares of the upper triangle of U: grid (ceil(m/64), parts); part p owns 256 rows.  A thread has 64 of
 // them and sixteen loads in flight (one load after the other took 20 us at 1504 columns, where few workgroups share the chip).
 __global__ __launch_bounds__(256) void colsumsq_upper(const double* __restrict__ U, int64_t ldu, int m,
@@ -657,9 +737,8 @@ __global__ __launch_bounds__(256) void colsum_finalize(const double* __restrict_
 }  // namespace
 
 size_t slim_ws_need_inverse(int m) {
-  const int nblk = slim_cdiv(m, NB), parts = slim_cdiv(m, 256);
-  return 2 * slim_ws_round(sizeof(double) * (size_t)m * m) + slim_ws_round(sizeof(double) * (size_t)parts * m) +
-         slim_ws_round(sizeof(slim_gemm_desc) * (size_t)(2 * nblk + 8)) + 256;
+  const int parts = slim_cdiv(m, 256);
+  return 2 * slim_ws_round(sizeof(double) * (size_t)m * m) + slim_ws_round(sizeof(double) * (size_t)parts * m) + 256;
 }
 
 extern "C" slim_status slim_hessian_inverse(slim_ctx* ctx, const float* G, int64_t ldg, int m, int64_t n_tokens,
@@ -676,21 +755,15 @@ extern "C" slim_status slim_hessian_inverse(slim_ctx* ctx, const float* G, int64
   const int nblk = slim_cdiv(m, NB);
   const int64_t lda = m;
   const int parts = slim_cdiv(m, 256);
-  // descriptors of the triangular inverse, built on the host
-  std::vector<slim_gemm_desc> descs;
-  struct Level { int first, count, maxM, maxN; };
-
   // A: the matrix being factored (upper triangle), later the scratch of the triangular inverse.
   // R: the factor, panel by panel (only the blocks above the diagonal are ever written or read).
   const size_t bytes_A = slim_ws_round(sizeof(double) * (size_t)m * m);
   const size_t bytes_part = slim_ws_round(sizeof(double) * (size_t)parts * m);
-  const size_t bytes_desc = slim_ws_round(sizeof(slim_gemm_desc) * (size_t)(2 * nblk + 8));
   slim_status st = slim_ws_reserve(ctx, slim_ws_need_inverse(m));
   if (st != SLIM_OK) return st;
   double* A = static_cast<double*>(slim_ws_alloc(ctx, bytes_A));
   double* R = static_cast<double*>(slim_ws_alloc(ctx, bytes_A));
   double* partial = static_cast<double*>(slim_ws_alloc(ctx, bytes_part));
-  slim_gemm_desc* descs_dev = static_cast<slim_gemm_desc*>(slim_ws_alloc(ctx, bytes_desc));
   double* lam = static_cast<double*>(slim_ws_alloc(ctx, 256));
   int* flag = ctx->dflags + 1;
 
@@ -704,80 +777,6 @@ extern "C" slim_status slim_hessian_inverse(slim_ctx* ctx, const float* G, int64
     SLIM_LAUNCH(ctx, "inv_widen", widen_damp<2>, dim3(slim_cdiv(m, 512), slim_cdiv(m, 8)), dim3(256), 0, G, ldg, m, s, lam, A, lda, U, ldu);
   else
     SLIM_LAUNCH(ctx, "inv_widen", widen_damp<1>, dim3(slim_cdiv(m, 256), slim_cdiv(m, 8)), dim3(256), 0, G, ldg, m, s, lam, A, lda, U, ldu);
-
-  // ---- descriptors of the triangular inverse inside the groups (pairwise merging of inverted diagonal ranges),
-  //      staged first so that no host synchronisation falls inside the factorisation
-  const int ngrp = slim_cdiv(nblk, GRP);
-  std::vector<std::vector<Level>> glevels(ngrp);
-  for (int Gi = 0; Gi < ngrp; ++Gi) {
-    const int64_t g0 = (int64_t)Gi * GRP * NB, g1 = std::min<int64_t>(m, g0 + GRP * NB);
-    for (int64_t sz = NB; sz < g1 - g0; sz *= 2) {
-      Level lv{(int)descs.size(), 0, 0, 0};
-      for (int64_t lo = g0; lo + sz < g1; lo += 2 * sz) {
-        const int64_t mid = lo + sz, hi = std::min<int64_t>(lo + 2 * sz, g1);
-        const int a = (int)sz, b = (int)(hi - mid);
-        slim_gemm_desc d;
-        // T12 = R12 * U22 (into the scratch, at the position of the block)
-        d.A = R + lo * lda + mid;
-        d.lda = lda;
-        d.B = U + mid * ldu + mid;
-        d.ldb = ldu;
-        d.C = A + lo * lda + mid;
-        d.ldc = lda;
-        d.C2 = nullptr;
-        d.ldc2 = 0;
-        d.M = a;
-        d.N = b;
-        d.K = b;
-        d.flags = SLIM_GEMM_B_UPPER;
-        d.alpha = 1.0;
-        d.beta = 0.0;
-        descs.push_back(d);
-        lv.count += 1;
-        lv.maxM = std::max(lv.maxM, a);
-        lv.maxN = std::max(lv.maxN, b);
-      }
-      glevels[Gi].push_back(lv);
-    }
-  }
-  const int n_first = (int)descs.size();
-  // second product of every pair: U12 = -U11 * T12
-  for (int i = 0; i < n_first; ++i) {
-    const slim_gemm_desc& t = descs[i];
-    const int64_t off = t.C - A;   // element offset of the (lo, mid) block
-    const int64_t lo = off / lda, mid = off % lda;
-    slim_gemm_desc d;
-    d.A = U + lo * ldu + lo;
-    d.lda = ldu;
-    d.B = t.C;
-    d.ldb = lda;
-    d.C = U + lo * ldu + mid;
-    d.ldc = ldu;
-    d.C2 = nullptr;
-    d.ldc2 = 0;
-    d.M = t.M;
-    d.N = t.N;
-    d.K = t.M;
-    d.flags = SLIM_GEMM_A_UPPER;
-    d.alpha = -1.0;
-    d.beta = 0.0;
-    descs.push_back(d);
-  }
-  if (!descs.empty()) {
-    if (descs.size() * sizeof(slim_gemm_desc) > (size_t)SLIM_HPIN_BYTES)
-      return slim_fail(ctx, SLIM_ERR_UNSUPPORTED, "slim_hessian_inverse: m too large for the descriptor staging buffer");
-    // The staging buffer may still be read by the copy of an earlier call that ended on an error; every other use
-    // of it has been waited for.  No wait for the stream itself: the launches of the factorisation below are
-    // enqueued while earlier work (the Gram matrix) still runs, so its chain of small kernels finds them ready.
-    st = slim_ensure_side(ctx);
-    if (st != SLIM_OK) return st;
-    if (ctx->staging_copy_pending) SLIM_HIP_TRY(ctx, hipEventSynchronize(ctx->ev[13]));
-    memcpy(ctx->hpin, descs.data(), descs.size() * sizeof(slim_gemm_desc));
-    SLIM_HIP_TRY(ctx, hipMemcpyAsync(descs_dev, ctx->hpin, descs.size() * sizeof(slim_gemm_desc),
-                                     hipMemcpyHostToDevice, ctx->stream));
-    SLIM_HIP_TRY(ctx, hipEventRecord(ctx->ev[13], ctx->stream));
-    ctx->staging_copy_pending = true;
-  }
 
   // ---- factorisation from the bottom-right corner upwards.  Blocks of 64 columns, groups of GRP blocks;
   //      "the window of block K" = the columns from the start of the group of block K-1 up to block K.
@@ -798,6 +797,8 @@ extern "C" slim_status slim_hessian_inverse(slim_ctx* ctx, const float* G, int64
                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)CHOL_LDS));
       SLIM_HIP_TRY(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(chol_link),
                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)CHOL_LDS));
+      SLIM_HIP_TRY(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(group_inverse_cols),
+                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)GI_LDS));
       done = true;
     }
   }
@@ -826,8 +827,7 @@ extern "C" slim_status slim_hessian_inverse(slim_ctx* ctx, const float* G, int64
   //      (a rank-512 product with a large result, like the far updates of the factorisation), so that the whole
   //      inverse runs beside the factorisation, whose second half is a chain of small kernels on a nearly idle chip,
   //      and only the last group's share is left when the last diagonal block is done.  Per group, in this order:
-  //        inside   U[g, g] by recursive doubling: ranges of 2^l inverted diagonal blocks are merged pairwise,
-  //                 U12 = -U11 (R12 U22); all pairs of a level form one batched launch
+  //        inside   U[g, g] column strip by column strip, in one launch (group_inverse_cols)
   //        rows     U[g, S] = -U[g, g] T[g, S]
   //        terms    T[0:g0, g0:m] (+)= R[0:g0, g] U[g, g0:m]   (first term of the columns of g itself, added to the
   //                 columns right of it)
@@ -837,12 +837,10 @@ extern "C" slim_status slim_hessian_inverse(slim_ctx* ctx, const float* G, int64
     const int64_t g0 = (int64_t)Gi * GRP * NB, g1 = std::min<int64_t>(m, g0 + GRP * NB);
     const int gw = (int)(g1 - g0);
     slim_status rs;
-    for (const Level& lv : glevels[Gi]) {
-      if (lv.count == 0) continue;
-      rs = slim_dgemm_batched(ctx, "inv_trtri_dgemm", 0, descs_dev + lv.first, lv.count, lv.maxM, lv.maxN);
-      if (rs != SLIM_OK) return rs;
-      rs = slim_dgemm_batched(ctx, "inv_trtri_dgemm", 0, descs_dev + n_first + lv.first, lv.count, lv.maxM, lv.maxN);
-      if (rs != SLIM_OK) return rs;
+    if (gw > NB) {
+      const GroupInvArgs ga{R + g0 * lda + g0, lda, U + g0 * ldu + g0, ldu, gw};
+      SLIM_LAUNCH(ctx, slim_prof_name("inv_trtri_dgemm", "group_inverse_cols"), group_inverse_cols, dim3(4 * (slim_cdiv(gw, NB) - 1)),
+                  dim3(256), GI_LDS, ga);
     }
     slim_gemm_desc d;
     d.C2 = nullptr;
@@ -1015,7 +1013,6 @@ extern "C" slim_status slim_hessian_inverse(slim_ctx* ctx, const float* G, int64
   SLIM_LAUNCH(ctx, "inv_diag_finalize", colsum_finalize, dim3(slim_cdiv(m, 256)), dim3(256), 0, partial, parts, m, hinv_diag);
 
   SLIM_HIP_TRY(ctx, hipEventSynchronize(ev_info));
-  ctx->staging_copy_pending = false;               // the copy of the descriptors lies before the flag's on the stream
   *info = host[0];
   if (host[0] != 0)
     return slim_fail(ctx, SLIM_ERR_NOT_PD, "slim_hessian_inverse: H + lambda I is not positive definite (pivot at column %d)", host[0]);

@@ -61,7 +61,6 @@ struct slim_ctx {
   // signal instead of a separate record behind it (one packet less between dependent small kernels); the launch
   // clears it.  slim_attach_flush() records it the ordinary way if no launch took it.
   hipEvent_t attach_event = nullptr;
-  bool staging_copy_pending = false;   // a host-to-device copy out of hpin that no one has waited for yet (ev[13])
   slim_sba_prepared sba_prep;
   float* dq_scratch = nullptr;    // this device's copy of the fixed partial-sum buffer of slim_dequant_matmul_noalloc
   // profiling
@@ -173,9 +172,6 @@ struct slim_gemm_desc {
   double alpha, beta;
 };
 slim_status slim_dgemm(slim_ctx* ctx, const char* name, int trans_b, const slim_gemm_desc& d);
-// Batched form: `descs` is a device array of `count` descriptors; max_M / max_N bound the grid.
-slim_status slim_dgemm_batched(slim_ctx* ctx, const char* name, int trans_b, const slim_gemm_desc* descs_dev,
-                               int count, int max_M, int max_N);
 
 // ---- small utilities (util.hip) -----------------------------------------------------------
 // dst (fp64, rows x cols, ldd) = exact widening of src (F16 / BF16 / F32 / F64, lds); cols % 4 == 0.
