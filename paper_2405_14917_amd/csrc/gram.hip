@@ -59,6 +59,7 @@ struct GramArgs {
   int super;           // tile order: edge of a supertile in tiles, or, negative, minus the height of a band (decode_tile)
   int id_base;         // id of the launch's first workgroup (the ring kernel may be launched round by round)
   int ncu;             // workgroups per round (compute units of the device)
+  int pairs;           // small tiles: workgroups, the first ones, that take two diagonal tiles each (pair_sums)
 };
 
 // Which piece of work a workgroup has: tile, token range, and the slot its partial tile goes to.  The slots of one
@@ -509,9 +510,23 @@ __global__ __launch_bounds__(NTHREADS, 256 / EDGE) void gram_kernel_ring(GramArg
   extern __shared__ __align__(16) uint16_t smem[];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave >> 1, wn = wave & 1;
-  const WorkItem wk = decode_work(a, a.id_base + (int)blockIdx.x);
+  const int nt = (a.m + TM - 1) / TM;
+  const bool pair = EDGE == 128 && (int)blockIdx.x < a.pairs;
+  WorkItem wk;
   int bi, bj;
-  decode_tile(wk.tile, (a.m + TM - 1) / TM, bi, bj, a.super);
+  if (pair) {
+    wk = WorkItem{0, 0, a.t, 0};
+    bi = 2 * (int)blockIdx.x;
+    bj = min(bi + 1, nt - 1);
+  } else if (EDGE == 128) {
+    // the tiles right of the diagonal are the upper triangle of a grid with one tile less a side
+    wk = decode_work(a, (int)blockIdx.x - a.pairs);
+    decode_tile(wk.tile, nt - 1, bi, bj, a.super);
+    ++bj;
+  } else {
+    wk = decode_work(a, a.id_base + (int)blockIdx.x);
+    decode_tile(wk.tile, nt, bi, bj, a.super);
+  }
   const int rowA0 = bi * TM, rowB0 = bj * TM;
   const int64_t kbeg = wk.kbeg, kend = wk.kend;
   constexpr int UNIT = TM * FROW;         // halves per unit
@@ -584,7 +599,94 @@ __global__ __launch_bounds__(NTHREADS, 256 / EDGE) void gram_kernel_ring(GramArg
     __syncthreads();
   };
   int ua = 0;                                      // unit of A of the current slab; B is the next one
-  const bool idle = (bi == bj && wm == 1 && wn == 0);   // this wavefront's quarter of a diagonal tile is never read back
+  // The small tile's sums are folded every 512 tokens, so that not splitting its tokens costs no precision.
+  constexpr int FOLD = 8;
+  // Two diagonal tiles at once: their rows are the A and the B slabs, the operands of either product are the same slab, and of
+  // the 16 tiles of 32 x 32 the ten on and above the diagonal are dealt to two wavefronts.  The loads of one workgroup and 5/4
+  // of its products in place of two workgroups: of 4096 rows, 512 workgroups, one round, in place of 528.
+  if constexpr (EDGE == 128) {
+    if (pair) {
+      auto pair_sums = [&](auto half) {
+        constexpr int H = decltype(half)::value;
+        constexpr int TI[5] = {H ? 1 : 0, H ? 1 : 0, H ? 2 : 0, H ? 2 : 0, H ? 3 : 1};
+        constexpr int TJ[5] = {H ? 2 : 0, H ? 3 : 1, H ? 2 : 2, H ? 3 : 3, H ? 3 : 1};
+        float16v part[5], total[5];
+#pragma unroll
+        for (int i = 0; i < 5; ++i)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) part[i][v] = total[i][v] = 0.f;
+        auto rows_of = [&](uint4 (&f)[4], const uint16_t* u) {
+#pragma unroll
+          for (int i = H; i < 4; ++i) f[i] = *reinterpret_cast<const uint4*>(u + i * 32 * FROW);
+        };
+        const int rd = l32 * FROW;
+        for (int64_t it = 0; it < nslab; ++it) {
+          if (it % FOLD == 0) {
+#pragma unroll
+            for (int i = 0; i < 5; ++i) {
+              total[i] += part[i];
+#pragma unroll
+              for (int v = 0; v < 16; ++v) part[i][v] = 0.f;
+            }
+          }
+          const int un = ua + wm >= 5 ? ua + wm - 5 : ua + wm;     // wavefronts 0 and 1: the A slab, 2 and 3: B
+          const int unB = (ua + 3 >= 5) ? ua + 3 - 5 : ua + 3, unA = (ua + 4 >= 5) ? ua + 4 - 5 : ua + 4;
+          const char* srcB = baseB + min((it + 1) * (int64_t)(BK * 2), last);
+          const char* srcA = baseA + min((it + 2) * (int64_t)(BK * 2), last);
+          const unsigned ldsB = lds0 + (unsigned)unB * UNIT_BYTES, ldsA = lds0 + (unsigned)unA * UNIT_BYTES;
+          const uint16_t* u = smem + un * UNIT + rd;
+          uint4 f[2][4];
+          rows_of(f[0], u + pos[0]);
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            if (k < 3) rows_of(f[(k + 1) & 1], u + pos[k + 1]);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int i = 0; i < 5; ++i) {
+              part[i] = mfma<BF16>(f[k & 1][TI[i]], f[k & 1][TJ[i]], part[i]);
+              __builtin_amdgcn_sched_barrier(0);
+              const int gm = 5 * k + i, c = gm / 2;
+              if (gm % 2 == 1 && c < 2 * CHUNKS) {               // in the order of the other tiles: B of the next slab first
+                if (c < CHUNKS)
+                  direct_load(ldsB + c * CHUNK_BYTES, offB[c], srcB);
+                else
+                  direct_load(ldsA + (c - CHUNKS) * CHUNK_BYTES, offA[c - CHUNKS], srcA);
+                __builtin_amdgcn_sched_barrier(0);
+              }
+            }
+          }
+          asm volatile("s_waitcnt vmcnt(%0)" ::"n"(CHUNKS) : "memory");
+          __syncthreads();
+          ua = (ua + 2 >= 5) ? ua + 2 - 5 : ua + 2;
+        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        if (rem > 0) {
+          stash_rest();
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            uint4 f[4];
+            rows_of(f, smem + wm * UNIT + rd + pos[k]);
+#pragma unroll
+            for (int i = 0; i < 5; ++i) part[i] = mfma<BF16>(f[TI[i]], f[TJ[i]], part[i]);
+          }
+        }
+        if (wm == 1 && bi == bj) return;                         // (an odd number of tiles: the last one is alone)
+        const int at = wm ? rowB0 : rowA0;
+#pragma unroll
+        for (int i = 0; i < 5; ++i) {
+          float16v o[1][1] = {{part[i] + total[i]}};
+          add_to_gram<1>(o, a.G, a.ldg, a.m, at + 32 * TI[i], at + 32 * TJ[i], lane);
+        }
+      };
+      if (wn)
+        pair_sums(std::integral_constant<int, 1>());
+      else
+        pair_sums(std::integral_constant<int, 0>());
+      return;
+    }
+  }
+  const bool idle = (EDGE == 256 && bi == bj && wm == 1 && wn == 0);   // this wavefront's quarter of a diagonal tile is never read back
   if (idle) {
     // only fetches its share of the slabs and keeps the barriers
     for (int64_t it = 0; it < nslab; ++it) {
@@ -612,8 +714,6 @@ __global__ __launch_bounds__(NTHREADS, 256 / EDGE) void gram_kernel_ring(GramArg
       if (rem > 0) stash_rest();
     return;
   }
-  // The small tile's sums are folded every 512 tokens, so that not splitting its tokens costs no precision.
-  constexpr int FOLD = 8;
   float16v sum[EDGE == 128 ? FI : 1][EDGE == 128 ? FI : 1];
   if constexpr (EDGE == 128) {
 #pragma unroll
@@ -868,6 +968,7 @@ extern "C" slim_status slim_hessian_accumulate(slim_ctx* ctx, const void* X, sli
   a.f = f;
   a.subchunk = subchunk;
   a.id_base = 0;
+  a.pairs = 0;
   a.ncu = ctx->num_cus > 0 ? ctx->num_cus : 256;
   // Which tiles are on the chip together, and on which XCD (decode_work).  Up to 700 tiles: a run of consecutive
   // tiles of the supertile order per XCD (supertiles of 6 x 6, of 8 x 8 from 192 tiles on; measured with the ring
@@ -914,14 +1015,15 @@ extern "C" slim_status slim_hessian_accumulate(slim_ctx* ctx, const void* X, sli
     a.ldg = ldg;
     a.kchunk = (t_c + BK - 1) / BK * BK;
     a.S = 1;
-    a.tiles_main = a.n_main = small_tiles;
+    a.pairs = (nts + 1) / 2;
+    a.tiles_main = a.n_main = small_tiles - nts;
     a.patches = 0;
     a.super = 8;
     if (x_dtype == SLIM_BF16)
-      SLIM_LAUNCH(ctx, "gram_mfma_bf16@gram_kernel_ring<true, 128, false>", (gram_kernel_ring<true, 128, false>), dim3(small_tiles), block,
+      SLIM_LAUNCH(ctx, "gram_mfma_bf16@gram_kernel_ring<true, 128, false>", (gram_kernel_ring<true, 128, false>), dim3(a.pairs + a.n_main), block,
                   kSmemRing<128>, a);
     else
-      SLIM_LAUNCH(ctx, "gram_mfma_f16@gram_kernel_ring<false, 128, false>", (gram_kernel_ring<false, 128, false>), dim3(small_tiles), block,
+      SLIM_LAUNCH(ctx, "gram_mfma_f16@gram_kernel_ring<false, 128, false>", (gram_kernel_ring<false, 128, false>), dim3(a.pairs + a.n_main), block,
                   kSmemRing<128>, a);
     *n_tokens += t_c;
     return SLIM_OK;
