@@ -518,7 +518,7 @@ __global__ __launch_bounds__(NTHREADS, 256 / EDGE) void gram_kernel_ring(GramArg
     wk = WorkItem{0, 0, a.t, 0};
     bi = 2 * (int)blockIdx.x;
     bj = min(bi + 1, nt - 1);
-  } else if (EDGE == 128) {
+  } else if (EDGE == 128 && a.pairs > 0) {
     // the tiles right of the diagonal are the upper triangle of a grid with one tile less a side
     wk = decode_work(a, (int)blockIdx.x - a.pairs);
     decode_tile(wk.tile, nt - 1, bi, bj, a.super);
@@ -686,7 +686,7 @@ __global__ __launch_bounds__(NTHREADS, 256 / EDGE) void gram_kernel_ring(GramArg
       return;
     }
   }
-  const bool idle = (EDGE == 256 && bi == bj && wm == 1 && wn == 0);   // this wavefront's quarter of a diagonal tile is never read back
+  const bool idle = (bi == bj && wm == 1 && wn == 0);   // this wavefront's quarter of a diagonal tile is never read back
   if (idle) {
     // only fetches its share of the slabs and keeps the barriers
     for (int64_t it = 0; it < nslab; ++it) {
@@ -1015,8 +1015,11 @@ extern "C" slim_status slim_hessian_accumulate(slim_ctx* ctx, const void* X, sli
     a.ldg = ldg;
     a.kchunk = (t_c + BK - 1) / BK * BK;
     a.S = 1;
-    a.pairs = (nts + 1) / 2;
-    a.tiles_main = a.n_main = small_tiles - nts;
+    // Diagonal tiles in pairs where the tiles take more than one round: fewer workgroups and less work in all.  Within one round
+    // a pair would only last longer than the other tiles.  2048 tokens, one by one / in pairs, us: m 2560 (210 tiles) 39 / 43,
+    // 3328 50 / 51; m 4096 (528) 76 / 58, 5120 95 / 90, 6000 131 / 126, 8192 247 / 230, 11008 440 / 433.
+    a.pairs = small_tiles > 2 * a.ncu ? (nts + 1) / 2 : 0;
+    a.tiles_main = a.n_main = a.pairs ? small_tiles - nts : small_tiles;
     a.patches = 0;
     a.super = 8;
     if (x_dtype == SLIM_BF16)

@@ -16,7 +16,7 @@ def slim():
 
 
 @pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
-@pytest.mark.parametrize("m,t", [(2560, 64), (2560, 2048), (2568, 1), (2568, 63), (2568, 65), (2688, 576), (2760, 513), (2816, 2047), (4096, 2048)])
+@pytest.mark.parametrize("m,t", [(2568, 65), (4000, 300), (4096, 64), (4096, 2048), (4104, 1), (4104, 63), (4104, 65), (4224, 576), (4232, 513), (4352, 2047)])
 def test_diagonal_tiles_in_pairs(slim, m, t, dtype):
     gen = torch.Generator(device="cuda").manual_seed(m + t)
     X = torch.randn((m, (t + 7) // 8 * 8), generator=gen, device="cuda").to(dtype)[:, :t]
