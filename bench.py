@@ -130,7 +130,8 @@ def algorithmic_work(name, cfg, launches_per_step):
     """(bound, peak key, work per launch) for every step of the path.  Work is ALGORITHMIC: distinct results
     only (the Gram matrix is credited with its triangle), bytes that have to move at least once.  `bound` is the
     roof that binds the step: "mfma" (flops), "alu" (flops of plain vector arithmetic), "hbm" (bytes), or
-    "latency" for the serial chain of diagonal blocks, which is rated as microseconds per link x links."""
+    "latency" for the serial chain of diagonal blocks, which is rated as microseconds per link x links (its work is that
+    of the products that run in the links' launches)."""
     n, m, t, beta = cfg.n, cfg.m, cfg.t, cfg.beta
     k = m // beta
     ts = min(T_SBA, t)
@@ -162,11 +163,6 @@ def algorithmic_work(name, cfg, launches_per_step):
             tot = sum(float(g1 - g0) ** 2 * (m - g1) for g0, g1 in groups)
         elif name == "inv_trtri_terms_dgemm":  # T[0:g0, g0:m] (+)= R[0:g0, g] U[g, g0:m], U[g, g] triangular
             tot = sum(float(g0) * (g1 - g0) ** 2 + 2.0 * g0 * (g1 - g0) * (m - g1) for g0, g1 in groups)
-        elif name == "inv_panel_dgemm":
-            tot = sum(2.0 * j0 * 64 * 64 / 2 for j0 in range(64, m, 64))
-        elif name == "inv_window_dgemm":
-            tot = sum(2.0 * (j0 - 64) * (j0 - ((j0 // 64 - 1) // INV_GRP) * INV_GRP * 64) * min(64, m - j0)
-                      for j0 in range(128, m, 64))
         elif name == "inv_group_next_dgemm":
             w = INV_GRP * 64
             tot = sum(2.0 * g0 * w * (min(m, g0 + w) - g0 - 64) for g0 in range(w, m, w) if min(m, g0 + w) - g0 > 64)
@@ -177,7 +173,15 @@ def algorithmic_work(name, cfg, launches_per_step):
             tot = 0.0
         return "mfma", "mfma_f64", tot / L
     if name == "inv_chol_diag":
-        return "latency", None, 0.0                                   # m / 64 dependent diagonal blocks
+        # m / 64 dependent diagonal blocks; in the same launches the panel A[0:j0, J] V^T (V triangular) of the block to the
+        # right and its products with itself in the window of blocks wt .. J - 1, on and above the diagonal (but for the
+        # neighbouring diagonal block's, which is that block's own)
+        tot = 0.0
+        for J in range(1, -(-m // 64)):
+            wt, nb = (J - 1) // INV_GRP * INV_GRP, min(64, m - J * 64)
+            tot += 64.0 * J * nb * (nb + 1)
+            tot += sum(64.0 * nb * (128 * min(c, J - 1) + (65 if c < J - 1 else 0)) for c in range(wt, J))
+        return "latency", "mfma_f64", tot / L
     if name == "sqc_search":
         return "alu", "alu_f64", 9.0 * cfg.ncand * n * beta          # ~9 fp64 operations per weight and candidate
     if name == "sqc_sweep":                                           # both and the update of the window of 512 in one launch
@@ -370,18 +374,20 @@ def main():
                         "avg_us": 1e3 * f["ms"] / f["cnt"], "launches_per_step": f["cnt"] / args.profile_steps,
                         "ms_per_step": f["ms"] / args.profile_steps}
     # every step of the path for the record: time, the roof that binds it, the fraction of that roof, and the time
-    # the step would take at the roof (its floor).  The chain of diagonal blocks is rated by its latency.
+    # the step would take at the roof (its floor).  The chain of diagonal blocks is rated by its latency, its floor is that of
+    # the products in its launches.
     others, floor_ms = {}, 0.0
     for name, k in kernels.items():
         entry = {"ms_per_step": round(k["ms_per_step"], 4), "launches_per_step": k["launches_per_step"],
                  "bound": k["bound"]}
         if k["bound"] == "latency":
             entry["latency"] = {"us_per_link": round(k["avg_us"], 2), "links": k["launches_per_step"]}
-        elif k["work_per_step"] > 0:
+        if k["work_per_step"] > 0:
             floor = k["work_per_step"] / PEAK[k["peak_key"]] * 1e3
             floor_ms += floor
             entry["floor_ms"] = round(floor, 4)
-            entry["frac"] = round(floor / k["ms_per_step"], 4)
+            if k["bound"] != "latency":
+                entry["frac"] = round(floor / k["ms_per_step"], 4)
         others[name] = entry
     whole_pass = {"sum_of_floors_ms": floor_ms, "frac": floor_ms / ms_per_step,
                   "note": "sum over the steps of (algorithmic work / peak of the roof that binds the step) against "
@@ -401,10 +407,10 @@ def main():
             "sqc_search, sqc_sweep": "alu peak counts an FMA as two operations; the search loop is mostly single-operation "
                           "instructions (multiply, round, two clamps), so its fraction of the issue bound is about "
                           "twice the frac given",
-            "inv_syrk_dgemm, inv_panel_dgemm, inv_window_dgemm, inv_trtri_*_dgemm, sba_*outputs": "run beside other "
-                          "streams' work by design (the factorisation's chains, its far updates and the triangular "
-                          "inverse on four streams, and the SBA's integer products on another): their durations "
-                          "overlap and their frac is not a fraction of the chip",
+            "inv_chol_diag, inv_syrk_dgemm, inv_trtri_*dgemm, sba_*outputs": "run beside other streams' work by design (the "
+                          "factorisation's chain, its far updates and the triangular inverse on three streams, and the "
+                          "SBA's integer products on another): their durations overlap and their frac is not a fraction "
+                          "of the chip",
             "hbm entries": "yardsticks on the same chip (plain PyTorch kernels, 1 to 4 GB): fill 6.9 TB/s, copy 4.9 to 5.3 TB/s "
                            "read plus written (0.61 to 0.66 of the peak), read-only sum 4.0 TB/s, fp16 -> fp64 conversion 3.2 TB/s",
             "gram_mfma_f16": "power-limited: the same kernel runs at 0.71 of the nominal peak on constant data and at "
