@@ -222,11 +222,6 @@ __device__ __forceinline__ void add_compensated(double& y, double& lo, double f,
   y = s;
 }
 
-// A pair of digits whose lowest stands for at most 2^LOW_PAIR units goes to lo alone, one instruction in place of four.  A
-// chunk adds less than 2^(30 + 16) units to it there, so lo rounds by 2^-7 units at the most (2^-16 as the digits of a Gram
-// matrix fall) where a column's largest value is 2^53 of them: 2^-60 of it, below the rounding of the fp64 result.
-constexpr int LOW_PAIR = 16;
-
 // 1.5 * 2^e, e two above any partial sum of a row's integers times scale (times a token's digits, below 2^54 units): with
 // wexp - ROW_EXP_BIAS the exponent above the row's largest weight, and W_hat and the parts it is summed from within 2^9 of that.
 // (About 2^24 above the sums themselves, which leaves them some 75 bits.)

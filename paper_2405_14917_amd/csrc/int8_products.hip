@@ -264,12 +264,12 @@ __global__ __launch_bounds__(256) void int_g_digits(const float* __restrict__ G,
 // digits in place of one, and twice the registers, so one tile per wavefront and four wavefronts per SIMD (two tiles and two
 // wavefronts, or one and three, are slower).  Those four leave little to hide a barrier behind, so a stage holds all digits of a
 // chunk, eight wavefronts share it, and a wavefront in its MFMAs goes before one in its sums: 4096 x 4096 against 4096 columns
-// 690 -> 625 us, and with the low pairs of digits added to the lower part alone (LOW_PAIR) about 595.  (491 us with one
-// instruction in place of the four throughout, 20 to 30 less without the codes' or the digits' way from memory.)
+// 690 -> 625 us.  What bounds it is the vector work: 491 us with one instruction in place of the four, 590 to 600 without the
+// codes' or the digits' way from memory.
 template <int KS, bool REF, bool COMP>
 __global__ __launch_bounds__(COMP ? 512 : 256, COMP ? 4 : 3) void int_outputs(OutArgs a) {
   constexpr int R = COMP ? 1 : 2, NW = COMP ? 8 : 4;
-  constexpr int SD = COMP ? SI_MAXD : SI_STAGE_D;    // (COMP: every stage starts with a chunk's first digit)
+  constexpr int SD = COMP ? SI_MAXD : SI_STAGE_D;
   using TL = Tile<KS, R, SD>;
   extern __shared__ __align__(16) char si_smem[];
   const IntShape& s = a.s;
@@ -326,7 +326,8 @@ __global__ __launch_bounds__(COMP ? 512 : 256, COMP ? 4 : 3) void int_outputs(Ou
     for (int r = 0; r < R; ++r) sc[r] = tl.s[r];
     if (sets == 0 || nd == 0) load_first(stage_chunk(next));                // a chunk of zeros
     for (int j = 0; j < sets; ++j) {
-      auto multiply = [&](int p, v16i (&acc)[R]) {
+      for (int p = (nd - 1) >> 1; p >= 0; --p) {
+        v16i acc[R];
         if constexpr (COMP) __builtin_amdgcn_s_setprio(1);
         tl.pair(x, p, 2 * p + 1 < nd, acc);
         if constexpr (COMP) __builtin_amdgcn_s_setprio(0);
@@ -336,29 +337,16 @@ __global__ __launch_bounds__(COMP ? 512 : 256, COMP ? 4 : 3) void int_outputs(Ou
           else
             load_first(stage_chunk(next));
         }
-      };
-      int p = (nd - 1) >> 1;
-      if constexpr (COMP) {
-        // (a loop for each kind of pair: as two branches of one loop the registers of both were in use at once, and spilled)
-        for (; p >= 0 && unit + 16 * p > LOW_PAIR; --p) {
-          v16i acc[R];
-          multiply(p, acc);
-          const double f = ldexp(sc[0], unit + 16 * p + (REF ? 8 * j : 0));
+        const int e = unit + 8 * (lo + 2 * p) + (REF ? 8 * j : 0);
+        if constexpr (COMP) {
 #pragma unroll
-          for (int v = 0; v < 16; ++v) add_compensated(y[0][v], low[0][v], f, (double)acc[0][v]);
-        }
-        for (; p >= 0; --p) {
-          v16i acc[R];
-          multiply(p, acc);
-          const double f = ldexp(sc[0], unit + 16 * p + (REF ? 8 * j : 0));
+          for (int r = 0; r < R; ++r) {
+            const double f = ldexp(sc[r], e);
 #pragma unroll
-          for (int v = 0; v < 16; ++v) low[0][v] = fma(f, (double)acc[0][v], low[0][v]);
-        }
-      } else {
-        for (; p >= 0; --p) {
-          v16i acc[R];
-          multiply(p, acc);
-          add_scaled<R>(y, acc, sc, unit + 8 * (lo + 2 * p) + (REF ? 8 * j : 0));
+            for (int v = 0; v < 16; ++v) add_compensated(y[r][v], low[r][v], f, (double)acc[r][v]);
+          }
+        } else {
+          add_scaled<R>(y, acc, sc, e);
         }
       }
     }

@@ -110,6 +110,42 @@ def test_the_difference_of_the_products_keeps_its_digits(slim, n, m, beta, bits,
     assert abs(float(got - exact)) <= 64 * 2.0 ** -53 * terms, float(got - exact) / terms
 
 
+def test_what_the_sums_round_away_is_kept_over_many_chunks(slim):
+    """Two thousand channels whose entries of G lie far below their column's largest, weights of one sign and on their quantiser's
+    values but for one channel: the loss is that channel's squared distance times its diagonal entry, and the two products share
+    everything else, also the sums over all chunks of the lowest digits."""
+    n, m, beta, bits = 16, 4096, 128, 5
+    rng = np.random.default_rng(m)
+    Q, far, big = 2 ** bits - 1, 5, m // 2
+    step, lowest = 3001, 2796                                                # delta = 3001 * 2^-22, the zero point -2796
+    W = step * (lowest + rng.integers(0, Q + 1, (n, m)))
+    W.reshape(n, m // beta, beta)[:, :, 0] = step * lowest
+    W.reshape(n, m // beta, beta)[:, :, 1] = step * (lowest + Q)
+    W[:, far] = step * (lowest + rng.integers(0, Q, n)) + step // 4
+    # the small entries: 24 bits from bit 0 .. 7 of a column's unit 2^-53 on
+    G = rng.integers(2 ** 23, 2 ** 24, (m, m)) * 2.0 ** rng.integers(-53, -45, (m, m))
+    G[big:, :] = 1.0                                                         # the largest of their columns, 2^53 units ...
+    G[:, big:] = 1.0
+    G[-1, :-1] = G[:-1, -1] = 2.0 ** -60                                     # ... because some entry has a digit below 2^-53
+    G = torch.from_numpy(np.triu(G) + np.triu(G, 1).T).to(torch.float32)
+    widths = torch.full((m // beta,), bits, dtype=torch.uint8, device="cuda")
+    # (sigmoid(60) = 1: the whole range, the loss before any step)
+    out = slim.lwc_quantize(torch.from_numpy(W * 2.0 ** -22).to(torch.float32).cuda(), G.cuda(), 2 * m, widths, beta, steps=0,
+                            init=60.0, want_what=torch.float64)
+    D = out["What"].cpu().numpy() - W * 2.0 ** -22
+    assert (D[:, far] == -(step // 4) * 2.0 ** -22).all() and not np.delete(D, far, axis=1).any()
+    exact = float((D[:, far] ** 2).sum()) * float(G[far, far])
+    # In units (of 2^-53): y starts from 1.5 * 2^80 and rounds by 2^27 at most, at each of the additions of 64 chunks, four pairs
+    # of digits of G and three digits of W, and fewer for the codes.  lo gathers these remainders, and rounds by 2^-53 of what it
+    # holds.  Remainders and roundings are uniform and independent: eight standard deviations.
+    adds = 2 * 64 * 4 * 3
+    lo = 2.0 ** 27 / 3 ** 0.5 * adds ** 0.5
+    sigma = adds ** 0.5 * lo * 2.0 ** -53 / 3 ** 0.5 * 2.0 ** -53
+    got = out["loss_curve"][0] * n * 2 * m
+    bound = 8 * sigma * float((D[:, far] ** 2).sum()) ** 0.5 + 64 * 2.0 ** -53 * exact
+    assert abs(got - exact) <= bound, (got - exact, bound, exact)
+
+
 @pytest.mark.parametrize("m,beta", [(64, 32), (60, 6)])
 @pytest.mark.parametrize("value", [float("nan"), float("inf")])
 def test_weights_that_are_not_finite(slim, m, beta, value):
