@@ -599,7 +599,8 @@ __global__ __launch_bounds__(NTHREADS, 256 / EDGE) void gram_kernel_ring(GramArg
     __syncthreads();
   };
   int ua = 0;                                      // unit of A of the current slab; B is the next one
-  // The small tile's sums are folded every 512 tokens, so that not splitting its tokens costs no precision.
+  // The small tile's sums are folded every 512 tokens, so that not splitting its tokens costs no precision (the tokens behind the
+  // last whole slab go to the last of them: at most 575 terms).
   constexpr int FOLD = 8;
   // Two diagonal tiles at once: their rows are the A and the B slabs, the operands of either product are the same slab, and of
   // the 16 tiles of 32 x 32 the ten on and above the diagonal are dealt to two wavefronts.  The loads of one workgroup and 5/4
