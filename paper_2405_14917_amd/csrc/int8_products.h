@@ -244,7 +244,8 @@ __device__ __forceinline__ int digits_x(int d) { return d & 7; }
 __device__ __forceinline__ int digits_w(int d) { return (d >> 3) & 7; }
 __device__ __forceinline__ int exponent_x(int d) { return d >> 6; }
 
-// A stage in one word: chunk, its first digit, digits (at most SI_STAGE_D), and whether it is the chunk's first.
+// A stage in one word: chunk, its first digit, digits (all of a chunk's at most), and whether it is the chunk's first.
+static_assert(SI_MAXD <= 7, "three bits hold a stage's digits");
 __device__ __forceinline__ int stage_word(int c, int lo, int nd, int first) { return (c << 8) | (first << 7) | (nd << 4) | lo; }
 __device__ __forceinline__ int stage_chunk(int w) { return w >> 8; }
 __device__ __forceinline__ int stage_nd(int w) { return (w >> 4) & 7; }

@@ -406,38 +406,38 @@ __device__ __forceinline__ void sqc_losses(const double* w, const double* sl, in
 
 // index of the first smallest of a row's losses (0 where none is below infinity), in lane 0
 __device__ __forceinline__ int first_minimum(const double* loss, int ncand, int lane) {
-        double best = INFINITY;
-        int bi = 0x7fffffff;
-        for (int c = lane; c < ncand; c += 64) {
-          const double L = loss[c];
-          if (L < best) {
-            best = L;
-            bi = c;
-          }
-        }
-#define SQF_ARGMIN_STEP(CTRL)                                                   \
-        {                                                                           \
-          const double ob = dpp_f64<CTRL>(best);                                    \
-          const int oi = dpp_b32<CTRL>(bi);                                         \
-          if (ob < best || (ob == best && oi < bi)) {                               \
-            best = ob;                                                              \
-            bi = oi;                                                                \
-          }                                                                         \
-        }
-        SQF_ARGMIN_STEP(DPP_XOR1)
-        SQF_ARGMIN_STEP(DPP_XOR2)
-        SQF_ARGMIN_STEP(DPP_HALF_MIRROR)
-        SQF_ARGMIN_STEP(DPP_MIRROR)
+  double best = INFINITY;
+  int bi = 0x7fffffff;
+  for (int c = lane; c < ncand; c += 64) {
+    const double L = loss[c];
+    if (L < best) {
+      best = L;
+      bi = c;
+    }
+  }
+#define SQF_ARGMIN_STEP(CTRL)                                                 \
+  {                                                                           \
+    const double ob = dpp_f64<CTRL>(best);                                    \
+    const int oi = dpp_b32<CTRL>(bi);                                         \
+    if (ob < best || (ob == best && oi < bi)) {                               \
+      best = ob;                                                              \
+      bi = oi;                                                                \
+    }                                                                         \
+  }
+  SQF_ARGMIN_STEP(DPP_XOR1)
+  SQF_ARGMIN_STEP(DPP_XOR2)
+  SQF_ARGMIN_STEP(DPP_HALF_MIRROR)
+  SQF_ARGMIN_STEP(DPP_MIRROR)
 #undef SQF_ARGMIN_STEP
 #pragma unroll
-        for (int src = 16; src < 64; src += 16) {
-          const double ob = read_lane_f64(best, src);
-          const int oi = __builtin_amdgcn_readlane(bi, src);
-          if (lane == 0 && (ob < best || (ob == best && oi < bi))) {
-            best = ob;
-            bi = oi;
-          }
-        }
+  for (int src = 16; src < 64; src += 16) {
+    const double ob = read_lane_f64(best, src);
+    const int oi = __builtin_amdgcn_readlane(bi, src);
+    if (lane == 0 && (ob < best || (ob == best && oi < bi))) {
+      best = ob;
+      bi = oi;
+    }
+  }
   return bi == 0x7fffffff ? 0 : bi;
 }
 
@@ -889,9 +889,8 @@ __global__ __launch_bounds__(1024) void gptq_sweep4(SweepArgs a) {
 // one goes on to sweep four rows from LDS.  Then all of them update the workgroup's own rows of the window, and sum up the next
 // block's, which saves the product's and the statistics' launches too: the product read U once per 64 rows, and this once per 16
 // from the L2, but waits for nothing.  Whole pass: 1000 x 1504 in groups of 32 2.23 -> 1.71 ms (2.01 without the update),
-// 4096 x 4096 in groups of 128 8.11 -> 7.50 ms (7.80), 256 x 256 415 -> 371 us.  With more rows than one round takes the two kernels stay:
-// the search shares a CU among 20 wavefronts there and the sweep one block of U among several sets of rows, and what the launch
-// costs is small beside their 110 and 70 us (28672 rows).
+// 4096 x 4096 in groups of 128 8.11 -> 7.50 ms (7.80), 256 x 256 415 -> 371 us.  With more rows than one round takes the two kernels
+// stay (fused_rows): the search shares a CU among 20 wavefronts there and the sweep one block of U among several sets of rows.
 // ------------------------------------------------------------------------------------------
 struct FusedArgs {
   SqcArgs c;
@@ -1205,6 +1204,13 @@ slim_status launch_stats_and_sqc(slim_ctx* ctx, SqcArgs a, double* stat_partial)
 // Rows per workgroup of calibrate_sweep, 0 where the two kernels take the group: groups wider than a block of the sweep, a loss
 // weight per element, more than 16 rows per compute unit, more candidates than fit beside the block of U in LDS, or rows of U further
 // apart than its 32-bit offsets reach.
+// The line is at one round of workgroups, up to which the one launch is ahead whatever the group.  Us per group of 2048 columns in
+// several launches / in one (16 rows per workgroup, 256 compute units), by group size:
+//   rows    1000      4096      4352      5120      8192        11008       13824       16384       28672
+//   32    23 / 17   34 / 20   39 / 33   40 / 33    51 / 37     63 / 54     79 / 71     87 / 74    144 / 134
+//   64    31 / 26   45 / 30   53 / 49   52 / 50    69 / 56     88 / 81    111 / 107   121 / 110   204 / 197
+//   128   49 / 44   70 / 52   85 / 87   86 / 88   108 / 98    147 / 141   182 / 190   196 / 194   337 / 344
+// Beyond it groups of 128 gain or lose with how full the last round is; groups of 32 and 64 would gain at every size measured.
 int fused_rows(const slim_ctx* ctx, int n, int beta, int weight_mode, int ncand, int64_t ldu) {
   if (beta > 128 || ldu >= (1 << 26) || (weight_mode != SLIM_WEIGHT_MASK_MEAN && weight_mode != SLIM_WEIGHT_UNIFORM)) return 0;
   int rows = 4;
