@@ -623,8 +623,10 @@ __global__ __launch_bounds__(512) void chol_link(LinkArgs g) {
 // columns of a block column j and keeps them in LDS, so that the whole group is one launch.  grid: 4 strips of each block column from
 // the second on, the longest chains first; 4 wavefronts, each 16 rows of the block in hand.
 //
-// What bounds it is the chain of a strip's MFMAs, 28 * 16 + 7 * 16 per wavefront at most, 15 us, on 28 CUs; merging inverted ranges
-// pairwise does the same work in six launches, each a row of load latencies: 78 us for 512 columns beside the factorisation, 65 alone.
+// What bounds it is the chain of a strip, on 28 CUs: 28 * 16 + 7 * 16 MFMAs per wavefront at most, 15 us by themselves, and the trips
+// to memory and barriers between them.  512 columns: 40 us on an otherwise idle chip, 76 on average in a pass of 4096 x 11008, under
+// the bulk products.  Merging inverted ranges pairwise does the same work in six launches, each a row of load latencies: 65 us
+// alone, six times 17 in that pass and the gaps between them.
 // The rows of R and U come 16 bytes per lane, a block of 64 x 64 ahead of the MFMAs: lane l has row l % 16 and four
 // consecutive k from 4 (l / 16), which are the k of four MFMAs (the contraction may run in any order as long as both operands agree).
 constexpr int GI_XS = 20;        // doubles per LDS row of 16 columns: the four rows that a wavefront reads lie in different banks

@@ -203,7 +203,7 @@ __device__ __forceinline__ double row_first(double v, int lane) {
 }
 
 // The (row, group)'s share of the loss and, with TRAIN, the derivatives of its two strengths, their AdamW step, and the
-// integers of the next product.  4096 x 4096 (20 steps 16 instead of 42 ms): this pass 78 us, the product 690 us; on the fp64
+// integers of the next product.  4096 x 4096 (20 steps 14 instead of 42 ms): this pass 78 us, the product 620 us; on the fp64
 // matrix cores the product took 1.9 ms, and the two passes over fp64 copies of W, W_hat - W and D G 0.2 ms.
 template <typename T, bool TRAIN, int V>
 __global__ __launch_bounds__(256) void lwc_step(const T* __restrict__ W, LwcArgs a) {
