@@ -323,8 +323,9 @@ __device__ __forceinline__ double fast_rcp(double d) {
   return r;
 }
 
-// The losses of candidates c0 .. c0 + CPT - 1 for one row, this lane's share: the pairs of weights p, p + 4, ... of w and the
-// salient weights p, p + 4, ... of sl.  L = wus * (sum over all) + wdiff * (sum over the salient ones).
+// calibrate_sweep's losses of candidates c0 .. c0 + CPT - 1 for one row (those of sqc_search_fast, bit for bit), this lane's share:
+// the pairs of weights p, p + 4, ... of w and the salient weights p, p + 4, ... of sl.  L = wus * (sum over all) + wdiff * (sum over
+// the salient ones).
 template <int CPT>
 __device__ __forceinline__ void sqc_losses(const double* w, const double* sl, int beta, int ns, int p, bool sign_mode, double delta0,
                                            double z, double alpha, double qmax, double wus, double wdiff, const double* tgrid, int c0,
@@ -590,10 +591,81 @@ __global__ __launch_bounds__(1024, 5) void sqc_search_fast(SqcArgs a) {
       const double* sl = sal + r * stride;
       const double* par = rp + r * 8;
       const int ns = reinterpret_cast<const int*>(par + 5)[0];
-      // L = wus * (sum over all) + (ws - wus) * (sum over the salient ones)
+      // L = wus * (sum over all) + (ws - wus) * (sum over the salient ones): the sums of sqc_losses, written out, because inlined from
+      // there they spill a register more and take 2.5 to 4 % longer (28672 rows, groups of 32: 66.5 us, so 64.6; of 128: 120.8, 117.7)
       const double wus = par[4], wdiff = par[3] - par[4];
-      double L[SQF_CPT];
-      sqc_losses<SQF_CPT>(w, sl, beta, ns, p, sign_mode, par[0], par[1], par[2], qmax, wus, wdiff, tgrid, c0, ncand, L);
+      double L[SQF_CPT], dl[SQF_CPT], rd[SQF_CPT];
+#pragma unroll
+      for (int i = 0; i < SQF_CPT; ++i) {
+        const double tc = tgrid[min(c0 + i, ncand - 1)];
+        L[i] = 0.0;
+        // SIGN: the level tau * alpha; otherwise the step tau * delta0 and its reciprocal.  The loss is continuous
+        // across a rounding tie (both neighbouring codes are equally far), so the candidate losses may use a
+        // reciprocal; the codes themselves are decided with a true division.
+        dl[i] = tc * (sign_mode ? par[2] : par[0]);
+        rd[i] = fast_rcp(dl[i]);
+      }
+      if (sign_mode) {
+        // |w - sign(w) level| = ||w| - level|
+        for (int j = 0; j < beta / 8; ++j) {
+          const double2v v2 = *reinterpret_cast<const double2v*>(w + (4 * j + p) * 2);
+#pragma unroll
+          for (int i = 0; i < SQF_CPT; ++i) {
+            const double e0 = fabs(v2.x) - dl[i], e1 = fabs(v2.y) - dl[i];
+            L[i] = fma(e0, e0, L[i]);
+            L[i] = fma(e1, e1, L[i]);
+          }
+        }
+#pragma unroll
+        for (int i = 0; i < SQF_CPT; ++i) L[i] *= wus;
+        for (int j = p; j < ns; j += 4) {
+          const double v = sl[j];
+#pragma unroll
+          for (int i = 0; i < SQF_CPT; ++i) {
+            const double e = fabs(v) - dl[i];
+            L[i] = fma(e * wdiff, e, L[i]);
+          }
+        }
+      } else {
+        // clamp(rint(x) + z, 0, qmax) - z == clamp(rint(x), -z, qmax - z): one add and one subtract less per element
+        const double z = par[1];
+        const double lo = -z, hi = qmax - z;
+        double2v nxt = *reinterpret_cast<const double2v*>(w + p * 2);
+        for (int j = 0; j < beta / 8; ++j) {
+          const double2v v2 = nxt;
+          nxt = *reinterpret_cast<const double2v*>(w + (4 * min(j + 1, beta / 8 - 1) + p) * 2);   // one pair ahead
+          // stage by stage over the five candidates' independent chains, so that a wavefront need not wait on
+          // its own results
+#pragma unroll
+          for (int h = 0; h < 2; ++h) {
+            const double v = h ? v2.y : v2.x;
+            double x[SQF_CPT];
+#pragma unroll
+            for (int i = 0; i < SQF_CPT; ++i) x[i] = v * rd[i];
+#pragma unroll
+            for (int i = 0; i < SQF_CPT; ++i) x[i] = rint(x[i]);
+#pragma unroll
+            for (int i = 0; i < SQF_CPT; ++i) x[i] = fmax(x[i], lo);
+#pragma unroll
+            for (int i = 0; i < SQF_CPT; ++i) x[i] = fmin(x[i], hi);
+#pragma unroll
+            for (int i = 0; i < SQF_CPT; ++i) x[i] = fma(-dl[i], x[i], v);
+#pragma unroll
+            for (int i = 0; i < SQF_CPT; ++i) L[i] = fma(x[i], x[i], L[i]);
+          }
+        }
+#pragma unroll
+        for (int i = 0; i < SQF_CPT; ++i) L[i] *= wus;
+        for (int j = p; j < ns; j += 4) {
+          const double v = sl[j];
+#pragma unroll
+          for (int i = 0; i < SQF_CPT; ++i) {
+            const double q = fmin(fmax(rint(v * rd[i]), lo), hi);
+            const double e = fma(-dl[i], q, v);
+            L[i] = fma(e * wdiff, e, L[i]);
+          }
+        }
+      }
 #pragma unroll
       for (int i = 0; i < SQF_CPT; ++i) {
         double t = L[i];                                   // this lane's share: the loss is linear in the sums
@@ -1207,9 +1279,9 @@ slim_status launch_stats_and_sqc(slim_ctx* ctx, SqcArgs a, double* stat_partial)
 // The line is at one round of workgroups, up to which the one launch is ahead whatever the group.  Us per group of 2048 columns in
 // several launches / in one (16 rows per workgroup, 256 compute units), by group size:
 //   rows    1000      4096      4352      5120      8192        11008       13824       16384       28672
-//   32    23 / 17   34 / 20   39 / 33   40 / 33    51 / 37     63 / 54     79 / 71     87 / 74    144 / 134
-//   64    31 / 26   45 / 30   53 / 49   52 / 50    69 / 56     88 / 81    111 / 107   121 / 110   204 / 197
-//   128   49 / 44   70 / 52   85 / 87   86 / 88   108 / 98    147 / 141   182 / 190   196 / 194   337 / 344
+//   32    23 / 17   33 / 20   39 / 33   40 / 34    50 / 37     62 / 54     78 / 72     86 / 74    142 / 134
+//   64    30 / 25   45 / 30   53 / 50   52 / 50    68 / 56     87 / 81    109 / 108   120 / 110   201 / 198
+//   128   49 / 44   71 / 52   85 / 87   86 / 88   107 / 98     145 / 142   180 / 190   194 / 195   334 / 343
 // Beyond it groups of 128 gain or lose with how full the last round is; groups of 32 and 64 would gain at every size measured.
 int fused_rows(const slim_ctx* ctx, int n, int beta, int weight_mode, int ncand, int64_t ldu) {
   if (beta > 128 || ldu >= (1 << 26) || (weight_mode != SLIM_WEIGHT_MASK_MEAN && weight_mode != SLIM_WEIGHT_UNIFORM)) return 0;
