@@ -293,11 +293,7 @@ slim_status dequant_matmul_tokens(slim_ctx* ctx, const char* fn, const uint32_t*
     if (st != SLIM_OK) return st;
     a.t_x = (int)t_x;
     const int splits = slim_dq_gemm_splits(n, m, beta, t_x, cus, a.gper);
-    if (hand && splits == 1) {
-      a.hand = hand;
-      a.ldh = ldh;
-      return slim_dq_gemm_launch(ctx, a, 1);
-    }
+    if (hand && splits == 1) return slim_dq_gemm_launch(ctx, a, 1, hand, ldh);
     st = dq_partials(ctx, fn, a, splits, fixed, fixed_floats);
     if (st == SLIM_OK) st = slim_dq_gemm_launch(ctx, a, splits);
     if (st == SLIM_OK) st = dq_reduce(ctx, a, splits, Y, ldy);

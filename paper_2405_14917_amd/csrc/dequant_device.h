@@ -33,8 +33,6 @@ struct DqArgs {
   int gper;              // groups per workgroup along grid.y
   float* out;            // Y (one split) or the partial sums [split][T][n]
   int64_t ldo;           // leading dimension of `out` per token
-  __half* hand = nullptr;      // instead of `out`, n x t_x: the results clamped and rounded to fp16 (one split)
-  int64_t ldh = 0;
   int64_t split_stride;  // elements between the partial sums of two splits (0 when writing Y)
 };
 
@@ -63,7 +61,8 @@ slim_status slim_dq_few_launch(slim_ctx* ctx, const slimdq::DqArgs& a, const sli
 bool slim_dq_gemm_takes(int64_t t_x, int m, int beta, const void* X, int64_t ldx);
 int slim_dq_gemm_splits(int n, int m, int beta, int64_t t_x, int cus, int& gper);
 size_t slim_dq_gemm_partials(int n, int m, int beta, int cus);
-slim_status slim_dq_gemm_launch(slim_ctx* ctx, const slimdq::DqArgs& a, int splits);
+// hand: instead of a.out, n x t_x (ldh): the results clamped and rounded to fp16 (one split)
+slim_status slim_dq_gemm_launch(slim_ctx* ctx, const slimdq::DqArgs& a, int splits, __half* hand = nullptr, int64_t ldh = 0);
 // out (cols x rows, fp16) = Y^T (fp32, rows x cols), clamped to fp16's range and rounded (handover.hip)
 slim_status slim_round_transpose(slim_ctx* ctx, const float* Y, int rows, int64_t cols, int64_t ldy, void* out, int64_t ldo);
 

@@ -33,6 +33,8 @@ constexpr int PG_MAXK = 16384;                   // groups: three stages (at mos
 struct PgArgs {
   DqArgs d;
   int tiles_r, tiles_t;                          // tiles along the layer's rows and along the tokens
+  __half* hand;                                  // HAND: n x t_x (ldh), in place of d.out
+  int64_t ldh;
 };
 
 __device__ __forceinline__ void load_lds16(unsigned lds_addr, unsigned voff, const char* gbase) {
@@ -209,7 +211,10 @@ struct Wave {
   }
 };
 
-template <int SLAB, int TOK, bool BF16, bool WIDE>
+// HAND: the next layer's calibration activations in place of the outputs.  (A kernel of its own, its arguments behind the others': as a
+// branch its stores, half as much code again, made the other form up to 1.5 % slower, 5000 x 11008 with 2000 tokens in groups of 32,
+// bf16, 609 -> 618 us.)
+template <int SLAB, int TOK, bool BF16, bool WIDE, bool HAND>
 __global__ __launch_bounds__(PG_THREADS, 2) void dequant_gemm(PgArgs pa) {
   using S = Stage<SLAB, TOK>;
   using W = Wave<SLAB, TOK, BF16>;
@@ -357,11 +362,11 @@ __global__ __launch_bounds__(PG_THREADS, 2) void dequant_gemm(PgArgs pa) {
   }
 
   const int l32 = lane & 31, h = lane >> 5, row = row0 + wave * 32 + l32;
-  if (row < a.n && a.hand) {
-    // the next layer's calibration activations: a lane has four consecutive tokens of its row at a time (both halves of the
-    // wavefront 16 bytes of a line, which meet in the L2)
-    __half* o = a.hand + (int64_t)row * a.ldh;
-    const bool wide = (reinterpret_cast<uintptr_t>(a.hand) & 7u) == 0 && a.ldh % 4 == 0;
+  if (row >= a.n) return;
+  if constexpr (HAND) {
+    // a lane has four consecutive tokens of its row at a time (both halves of the wavefront 16 bytes of a line, which meet in the L2)
+    __half* o = pa.hand + (int64_t)row * pa.ldh;
+    const bool wide = (reinterpret_cast<uintptr_t>(pa.hand) & 7u) == 0 && pa.ldh % 4 == 0;
 #pragma unroll
     for (int i = 0; i < TA; ++i)
 #pragma unroll
@@ -382,7 +387,7 @@ __global__ __launch_bounds__(PG_THREADS, 2) void dequant_gemm(PgArgs pa) {
             if (t + j < a.t_x) o[t + j] = v[j];
         }
       }
-  } else if (row < a.n) {
+  } else {
     float* o = a.out + (int64_t)blockIdx.y * a.split_stride + row;
 #pragma unroll
     for (int i = 0; i < TA; ++i)
@@ -394,13 +399,18 @@ __global__ __launch_bounds__(PG_THREADS, 2) void dequant_gemm(PgArgs pa) {
   }
 }
 
-template <int SLAB, int TOK, bool BF16, bool WIDE>
+template <int SLAB, int TOK, bool BF16, bool WIDE, bool HAND>
 slim_status launch(slim_ctx* ctx, const PgArgs& pa, dim3 grid) {
   const int smem = PG_STAGES * Stage<SLAB, TOK>::BYTES + (pa.d.gper * 4 + 15) / 16 * 16;
-  SLIM_HIP_TRY(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(dequant_gemm<SLAB, TOK, BF16, WIDE>),
+  SLIM_HIP_TRY(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(dequant_gemm<SLAB, TOK, BF16, WIDE, HAND>),
                                         hipFuncAttributeMaxDynamicSharedMemorySize, smem));
-  SLIM_LAUNCH(ctx, "dequant_matmul@dequant_gemm", (dequant_gemm<SLAB, TOK, BF16, WIDE>), grid, dim3(PG_THREADS), smem, pa);
+  SLIM_LAUNCH(ctx, "dequant_matmul@dequant_gemm", (dequant_gemm<SLAB, TOK, BF16, WIDE, HAND>), grid, dim3(PG_THREADS), smem, pa);
   return SLIM_OK;
+}
+
+template <int SLAB, int TOK, bool BF16, bool WIDE>
+slim_status launch(slim_ctx* ctx, const PgArgs& pa, dim3 grid) {
+  return pa.hand ? launch<SLAB, TOK, BF16, WIDE, true>(ctx, pa, grid) : launch<SLAB, TOK, BF16, WIDE, false>(ctx, pa, grid);
 }
 
 template <int SLAB, int TOK>
@@ -441,9 +451,11 @@ size_t slim_dq_gemm_partials(int n, int m, int beta, int cus) {
   return slim_dq_gemm_splits(n, m, beta, DQ_FEW_TOKENS + 1, cus, gper) > 1 ? sizeof(float) * SLIM_DEQUANT_NOALLOC_MAX_FLOATS : 0;
 }
 
-slim_status slim_dq_gemm_launch(slim_ctx* ctx, const DqArgs& d, int splits) {
+slim_status slim_dq_gemm_launch(slim_ctx* ctx, const DqArgs& d, int splits, __half* hand, int64_t ldh) {
   PgArgs pa;
   pa.d = d;
+  pa.hand = hand;
+  pa.ldh = ldh;
   const int tok = token_tile(d.n, d.t_x, std::max(1, ctx->num_cus));
   pa.tiles_r = slim_cdiv(d.n, PG_ROWS);
   pa.tiles_t = slim_cdiv(d.t_x, tok);
