@@ -200,6 +200,10 @@ def algorithmic_work(name, cfg, launches_per_step):
         "int_w_units": 2.0 * n * m,
         "sba_kl_ref": 4.0 * 8 * n * ts / L,              # the reference outputs: read twice, written once, read once
         "sqc_block_stats": 8.0 * n * beta,
+        # operands of rank-512 products as residues: fp64 in, 14 bytes out (per launch, on average)
+        "inv_panel_residues": 22.0 * 512 * m / 2,
+        "inv_trtri_residues": 22.0 * 512 * m / 2,
+        "gptq_trailing_residues": 22.0 * 512 * (n + m / 2) / 2,
     }
     if name in hbm:
         return "hbm", "hbm", hbm[name]

@@ -95,7 +95,11 @@ typedef struct slim_shape {
  * requirement of any single entry point (calls on one context run one after the other and reuse the workspace).
  * num_cus: compute units of the device (the split of the Gram matrix and of the linear layer depend on it); 0 = 256.
  * For several shapes take the largest answer: the requirement is not monotone in the sizes (a small Gram matrix
- * is split into more token ranges).  It does not depend on t_x from 16 on: that workspace serves every number of tokens. */
+ * is split into more token ranges).  It does not depend on t_x from 16 on: that workspace serves every number of tokens.
+ * The inverse and the sweep of large layers take the products of their updates from residues on the int8 matrix cores, and
+ * what that needs is part of the answer; in a workspace of the caller's without room for it, but with room for two m x m
+ * (n x m) fp64 matrices and what else is asked for, they take them on the fp64 matrix cores: slower, and a result may
+ * differ in its last bits. */
 size_t slim_workspace_query(const slim_shape* shape, int num_cus);
 
 /* Creates a context bound to `hip_stream` (a hipStream_t, may be NULL for the default stream) on

@@ -14,7 +14,7 @@ INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(HERE, "libslim.so")
 OBJ_DIR = os.path.join(HERE, "_build")
 
-SOURCES = ["ctx.hip", "util.hip", "dgemm.hip", "gram.hip", "inverse.hip", "salience.hip", "sba.hip", "quant.hip",
+SOURCES = ["ctx.hip", "util.hip", "dgemm.hip", "rgemm.hip", "gram.hip", "inverse.hip", "salience.hip", "sba.hip", "quant.hip",
            "pack.hip", "dequant.hip", "dequant_few.hip", "dequant_gemm.hip", "handover.hip", "int8_products.hip", "lwc.hip"]
 
 # packed-fp32 code generation is switched off for all device code (a device-compiler option; the host
@@ -37,6 +37,7 @@ EXTRA_FLAGS = {"dgemm.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
                "int8_products.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form", "-Wno-inline-asm"],
                # gram.hip and dequant_gemm.hip set M0 in inline asm (destination of its direct-to-LDS loads) and say so in the clobber
                # list, which the compiler remarks on
+               "rgemm.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form", "-Wno-inline-asm"],
                "gram.hip": ["-Wno-inline-asm"], "dequant_gemm.hip": ["-Wno-inline-asm"]}
 
 

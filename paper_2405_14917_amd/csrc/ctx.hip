@@ -40,6 +40,16 @@ slim_status slim_ws_reserve(slim_ctx* ctx, size_t bytes) {
   return SLIM_OK;
 }
 
+slim_status slim_ws_reserve_either(slim_ctx* ctx, size_t full, size_t base, bool& has_full) {
+  has_full = full > base && (!ctx->ws_external || full <= ctx->ws_bytes);
+  if (has_full) {
+    const slim_status st = slim_ws_reserve(ctx, full);
+    if (st != SLIM_ERR_ALLOC) return st;
+    has_full = false;
+  }
+  return slim_ws_reserve(ctx, base);
+}
+
 void* slim_ws_alloc(slim_ctx* ctx, size_t bytes) {
   size_t need = slim_ws_round(bytes);
   if (ctx->ws_off + need > ctx->ws_bytes) return nullptr;  // callers reserve the exact total first

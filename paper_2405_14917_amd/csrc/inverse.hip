@@ -12,6 +12,7 @@
 //        panel       R[0:J+1, J+1] = A[0:J+1, J+1] V^T of the block to the right, beside it
 //        update      rank-64 update with that panel of the columns from the start of block J's group on
 //      and once per group rank-512 updates of everything further left; see the schedule at the call site.
+//      (the large ones, and the terms of step 3, from residues on the int8 matrix cores: rgemm.hip)
 //   3. triangular inverse U = R^-1 group by group on a further stream, beside the factorisation: inside a group
 //      strip by strip of 16 columns from the inverted diagonal blocks upwards, in one launch, the
 //      rows right of the group from T = R[g, S] U[S, S], which is kept up to date for all rows above by one
@@ -738,10 +739,18 @@ __global__ __launch_bounds__(256) void colsum_finalize(const double* __restrict_
 
 }  // namespace
 
-size_t slim_ws_need_inverse(int m) {
+static size_t inverse_base_bytes(int m) {
   const int parts = slim_cdiv(m, 256);
   return 2 * slim_ws_round(sizeof(double) * (size_t)m * m) + slim_ws_round(sizeof(double) * (size_t)parts * m) + 256;
 }
+// The panels of a group and its rows of U as residues, where the rank-512 products of any group are taken that way.
+static bool far_pays(int gp, int K) { return slim_rg_pays((int64_t)gp * gp / 2, K); }
+static bool terms_pay(int g0, int m, int K) { return slim_rg_pays((int64_t)g0 * (m - g0), K); }
+static size_t inverse_residue_bytes(int m) {
+  const int g = GRP * NB;
+  return terms_pay(m / g / 2 * g, m, g) ? 3 * slim_rg_operand_bytes(m) : 0;
+}
+size_t slim_ws_need_inverse(int m) { return inverse_base_bytes(m) + inverse_residue_bytes(m); }
 
 extern "C" slim_status slim_hessian_inverse(slim_ctx* ctx, const float* G, int64_t ldg, int m, int64_t n_tokens,
                                             double percdamp, double* U, int64_t ldu, double* hinv_diag, int* info) {
@@ -761,12 +770,18 @@ extern "C" slim_status slim_hessian_inverse(slim_ctx* ctx, const float* G, int64
   // R: the factor, panel by panel (only the blocks above the diagonal are ever written or read).
   const size_t bytes_A = slim_ws_round(sizeof(double) * (size_t)m * m);
   const size_t bytes_part = slim_ws_round(sizeof(double) * (size_t)parts * m);
-  slim_status st = slim_ws_reserve(ctx, slim_ws_need_inverse(m));
+  bool residues = false;
+  slim_status st = slim_ws_reserve_either(ctx, slim_ws_need_inverse(m), inverse_base_bytes(m), residues);
   if (st != SLIM_OK) return st;
   double* A = static_cast<double*>(slim_ws_alloc(ctx, bytes_A));
   double* R = static_cast<double*>(slim_ws_alloc(ctx, bytes_A));
   double* partial = static_cast<double*>(slim_ws_alloc(ctx, bytes_part));
   double* lam = static_cast<double*>(slim_ws_alloc(ctx, 256));
+  slim_rg_operand panels[2] = {}, urows = {};
+  if (residues) {
+    for (slim_rg_operand& o : panels) o = slim_rg_carve(ctx, m);
+    urows = slim_rg_carve(ctx, m);
+  }
   int* flag = ctx->dflags + 1;
 
   const double s = 2.0 / (double)n_tokens;
@@ -807,6 +822,8 @@ extern "C" slim_status slim_hessian_inverse(slim_ctx* ctx, const float* G, int64
   hipStream_t s0 = ctx->stream, s1 = ctx->side, s2 = ctx->side2;
   hipEvent_t* ev_group = &ctx->ev[0];  // ring of 2: the links of a group are done
   hipEvent_t* ev_far = &ctx->ev[9];    // ring of 2
+  hipEvent_t* ev_terms = &ctx->ev[3];  // ring of 2: the terms that read a set of panels' residues are done
+  hipEvent_t ev_panels = ctx->ev[5];
   struct StreamSwap {
     slim_ctx* c;
     hipStream_t keep;
@@ -835,7 +852,8 @@ extern "C" slim_status slim_hessian_inverse(slim_ctx* ctx, const float* G, int64
   //                 columns right of it)
   //      T lives in A right of the group, where the panels' inputs lay: the last reader of those columns of A is the
   //      diagonal kernel of the block left of the group (its pending rank-64 update), which the caller waits for.
-  auto group_inverse = [&](int Gi) -> slim_status {
+  // `pr`: the panels of the group as residues (inv_panel_residues), or nullptr
+  auto group_inverse = [&](int Gi, const slim_rg_operand* pr) -> slim_status {
     const int64_t g0 = (int64_t)Gi * GRP * NB, g1 = std::min<int64_t>(m, g0 + GRP * NB);
     const int gw = (int)(g1 - g0);
     slim_status rs;
@@ -863,7 +881,13 @@ extern "C" slim_status slim_hessian_inverse(slim_ctx* ctx, const float* G, int64
       rs = slim_dgemm(ctx, "inv_trtri_rows_dgemm", 0, d);
       if (rs != SLIM_OK) return rs;
     }
-    if (g0 > 0) {
+    if (g0 > 0 && pr) {
+      const int cols = (int)(m - g0);
+      rs = slim_rg_residues(ctx, "inv_trtri_residues", urows, U + g0 * ldu + g0, ldu, cols, gw, true);
+      if (rs != SLIM_OK) return rs;
+      rs = slim_rgemm(ctx, "inv_trtri_terms_dgemm", {*pr, urows, (int)g0, cols, A + g0, lda, (int)g0, cols, 1.0, gw, false, true});
+      if (rs != SLIM_OK) return rs;
+    } else if (g0 > 0) {
       d.A = R + g0;
       d.lda = lda;
       d.B = U + g0 * ldu + g0;
@@ -904,7 +928,8 @@ extern "C" slim_status slim_hessian_inverse(slim_ctx* ctx, const float* G, int64
     ca.col_base = (int)j0;
     return ca;
   };
-  bool far_issued = false, tri_issued = false;
+  bool far_issued = false, tri_issued = false, terms_issued[2] = {false, false};
+  int panel_slot = 0;
   int last_far_slot = 0, group_slot = 0;
   SLIM_LAUNCH(ctx, "inv_chol_diag", chol_step, dim3(1), dim3(512), CHOL_LDS, block(nblk - 1));
   for (int J = nblk - 1; J > 0; --J) {
@@ -957,9 +982,22 @@ extern "C" slim_status slim_hessian_inverse(slim_ctx* ctx, const float* G, int64
     }
     if (!first) continue;
     // ---- s1: everything two or more groups to the left
-    if (g0 - GRP * NB > 0) {
+    const int gp = g0 - GRP * NB;
+    const bool far_r = residues && gp > 0 && far_pays(gp, g1 - g0), terms_r = residues && terms_pay(g0, m, g1 - g0);
+    if (far_r || terms_r) {
+      // the group's panels as residues, for the far update (both operands) and for the terms of the inverse, which may still
+      // be reading the other set
       StreamSwap swap(ctx, s1);
-      const int gp = g0 - GRP * NB;
+      SLIM_HIP_TRY(ctx, hipStreamWaitEvent(s1, ev_group[group_slot], 0));
+      panel_slot ^= 1;
+      if (terms_issued[panel_slot]) SLIM_HIP_TRY(ctx, hipStreamWaitEvent(s1, ev_terms[panel_slot], 0));
+      ctx->attach_event = ev_panels;
+      st = slim_rg_residues(ctx, "inv_panel_residues", panels[panel_slot], R + g0, lda, g0, g1 - g0, false);
+      if (st != SLIM_OK) return st;
+      SLIM_HIP_TRY(ctx, slim_attach_flush(ctx));
+    }
+    if (gp > 0) {
+      StreamSwap swap(ctx, s1);
       SLIM_HIP_TRY(ctx, hipStreamWaitEvent(s1, ev_group[group_slot], 0));
       slim_gemm_desc d;
       d.A = R + g0;                                 // R[0:gp, g0:g1]
@@ -980,7 +1018,10 @@ extern "C" slim_status slim_hessian_inverse(slim_ctx* ctx, const float* G, int64
       d.beta = 1.0;
       last_far_slot ^= 1;
       ctx->attach_event = ev_far[last_far_slot];
-      st = slim_dgemm(ctx, "inv_syrk_dgemm", 1, d);
+      if (far_r)
+        st = slim_rgemm(ctx, "inv_syrk_dgemm", {panels[panel_slot], panels[panel_slot], g0, g0, A, lda, gp, gp, -1.0, 0, true, true});
+      else
+        st = slim_dgemm(ctx, "inv_syrk_dgemm", 1, d);
       if (st != SLIM_OK) return st;
       SLIM_HIP_TRY(ctx, slim_attach_flush(ctx));
       far_issued = true;
@@ -989,8 +1030,13 @@ extern "C" slim_status slim_hessian_inverse(slim_ctx* ctx, const float* G, int64
     {
       StreamSwap swap(ctx, s2);
       SLIM_HIP_TRY(ctx, hipStreamWaitEvent(s2, ev_group[group_slot], 0));
-      st = group_inverse(G);
+      if (terms_r) SLIM_HIP_TRY(ctx, hipStreamWaitEvent(s2, ev_panels, 0));
+      st = group_inverse(G, terms_r ? &panels[panel_slot] : nullptr);
       if (st != SLIM_OK) return st;
+      if (terms_r) {
+        SLIM_HIP_TRY(ctx, hipEventRecord(ev_terms[panel_slot], s2));
+        terms_issued[panel_slot] = true;
+      }
       tri_issued = true;
     }
   }
@@ -1008,7 +1054,7 @@ extern "C" slim_status slim_hessian_inverse(slim_ctx* ctx, const float* G, int64
     SLIM_HIP_TRY(ctx, hipEventRecord(ev_tri, s2));
     SLIM_HIP_TRY(ctx, hipStreamWaitEvent(s0, ev_tri, 0));
   }
-  st = group_inverse(0);
+  st = group_inverse(0, nullptr);
   if (st != SLIM_OK) return st;
 
   SLIM_LAUNCH(ctx, "inv_diag_colsumsq", colsumsq_upper, dim3(slim_cdiv(m, 64), parts), dim3(256), 0, U, ldu, m, partial);

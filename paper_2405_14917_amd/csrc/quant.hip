@@ -1322,10 +1322,15 @@ slim_status check_params(slim_ctx* ctx, const slim_params* p, slim_params& out) 
 
 size_t slim_ws_need_sqc(int n) { return slim_ws_round(sizeof(double) * 2 * slim_cdiv(n, STAT_ROWS)); }
 
-size_t slim_ws_need_gptq(int n, int m) {
+static size_t gptq_base_bytes(int n, int m) {
   return slim_ws_round(sizeof(double) * (size_t)n * m) + slim_ws_round(sizeof(double) * (size_t)n * GPTQ_WINC) +
          slim_ws_round(sizeof(double) * 2 * slim_cdiv(n, STAT_ROWS)) + slim_ws_round(sizeof(double) * n);
 }
+// operands of the updates behind a window as residues, where any of them is taken that way
+static size_t gptq_residue_bytes(int n, int m) {
+  return m > GPTQ_WINC && slim_rg_pays((int64_t)n * (m - GPTQ_WINC), GPTQ_WINC) ? slim_rg_operand_bytes(n) + slim_rg_operand_bytes(m - GPTQ_WINC) : 0;
+}
+size_t slim_ws_need_gptq(int n, int m) { return gptq_base_bytes(n, m) + gptq_residue_bytes(n, m); }
 
 extern "C" slim_status slim_sqc_calibrate(slim_ctx* ctx, const double* Wblk, int64_t ldw, int n, int beta, int bits,
                                           const double* omega, const double* hinv_diag_blk,
@@ -1422,12 +1427,18 @@ extern "C" slim_status slim_gptq_quantize(slim_ctx* ctx, const void* W, slim_dty
   // WINC is a multiple of every supported group size, so a group never straddles a window and the calibration at
   // a group's first column sees columns that have received every earlier block's update.
   constexpr int WINC = GPTQ_WINC;
-  st = slim_ws_reserve(ctx, slim_ws_need_gptq(n, m));
+  bool residues = false;
+  st = slim_ws_reserve_either(ctx, slim_ws_need_gptq(n, m), gptq_base_bytes(n, m), residues);
   if (st != SLIM_OK) return st;
   double* Wc = static_cast<double*>(slim_ws_alloc(ctx, sizeof(double) * (size_t)n * m));
   double* E = static_cast<double*>(slim_ws_alloc(ctx, sizeof(double) * (size_t)n * WINC));
   double* stat_partial = static_cast<double*>(slim_ws_alloc(ctx, sizeof(double) * 2 * nstat));
   double* row_e2 = static_cast<double*>(slim_ws_alloc(ctx, sizeof(double) * n));
+  slim_rg_operand Er{}, Ur{};
+  if (residues) {
+    Er = slim_rg_carve(ctx, n);
+    Ur = slim_rg_carve(ctx, m - GPTQ_WINC);
+  }
 
   st = slim_widen_f64(ctx, "gptq_widen", W, w_dtype, n, m, ldw, Wc, (int64_t)m);
   if (st != SLIM_OK) return st;
@@ -1562,7 +1573,13 @@ extern "C" slim_status slim_gptq_quantize(slim_ctx* ctx, const void* W, slim_dty
       d.C = Wc + w1;
       d.N = m - w1;
       d.K = w1 - w0;
-      st = slim_dgemm(ctx, "gptq_trailing_dgemm", 0, d);
+      if (residues && slim_rg_pays((int64_t)d.M * d.N, d.K)) {
+        st = slim_rg_residues(ctx, "gptq_trailing_residues", Er, E, WINC, n, d.K, false);
+        if (st == SLIM_OK) st = slim_rg_residues(ctx, "gptq_trailing_residues", Ur, d.B, ldu, d.N, d.K, true);
+        if (st == SLIM_OK) st = slim_rgemm(ctx, "gptq_trailing_dgemm", {Er, Ur, n, d.N, d.C, d.ldc, n, d.N, -1.0, 0, false, false});
+      } else {
+        st = slim_dgemm(ctx, "gptq_trailing_dgemm", 0, d);
+      }
       if (st != SLIM_OK) return st;
     }
   }

@@ -79,6 +79,8 @@ slim_status slim_fail(slim_ctx* ctx, slim_status code, const char* fmt, ...);
 // alloc() hands out 256-byte aligned pieces of it.  reserve() may synchronise and reallocate.
 slim_status slim_ws_reserve(slim_ctx* ctx, size_t bytes);
 void* slim_ws_alloc(slim_ctx* ctx, size_t bytes);
+// Reserves `full` bytes, or `base` where a caller's workspace, or the device, has no room for them; `has_full`: which.
+slim_status slim_ws_reserve_either(slim_ctx* ctx, size_t full, size_t base, bool& has_full);
 inline size_t slim_ws_round(size_t bytes) { return (bytes + 255) & ~size_t(255); }
 
 // Bytes of workspace each entry point reserves for a layer of the given shape (host only; the entry points use the
@@ -172,6 +174,32 @@ struct slim_gemm_desc {
   double alpha, beta;
 };
 slim_status slim_dgemm(slim_ctx* ctx, const char* name, int trans_b, const slim_gemm_desc& d);
+
+// ---- fp64 products of rank up to 512 from residues on the int8 matrix cores (rgemm.hip) ----
+constexpr int SLIM_RG_PLANES = 14, SLIM_RG_K = 512;
+struct slim_rg_operand {
+  char* planes;        // SLIM_RG_PLANES matrices of bytes, rows padded to whole tiles, in operand order
+  double* scale;       // per row
+};
+size_t slim_rg_operand_bytes(int rows);
+bool slim_rg_pays(int64_t outputs, int K);
+slim_rg_operand slim_rg_carve(slim_ctx* ctx, int rows);
+// src: rows x K, or (columns) K x rows
+slim_status slim_rg_residues(slim_ctx* ctx, const char* name, const slim_rg_operand& o, const double* src, int64_t ld, int rows, int K,
+                             bool columns);
+// C = old C + alpha A B^T; columns below `fresh` have no old C; `upper`: only tiles that reach the diagonal or lie above it;
+// `beside`: a workgroup per tile, so that kernels of other streams get their turn (else one per CU, tile after tile)
+struct slim_rg_desc {
+  slim_rg_operand A, B;
+  int rowsA, rowsB;    // of the operands as they were converted
+  double* C;
+  int64_t ldc;
+  int M, N;
+  double alpha;
+  int fresh;
+  bool upper, beside;
+};
+slim_status slim_rgemm(slim_ctx* ctx, const char* name, const slim_rg_desc& d);
 
 // ---- small utilities (util.hip) -----------------------------------------------------------
 // dst (fp64, rows x cols, ldd) = exact widening of src (F16 / BF16 / F32 / F64, lds); cols % 4 == 0.
