@@ -153,9 +153,9 @@ __device__ __forceinline__ void store_digits(char* Wd, int64_t plane, int64_t ds
 constexpr int SI_STAGE_D = 4;      // digits per stage
 constexpr int SI_TAB = 1024;       // stages whose description is kept in LDS
 
-template <int KS, int R, int SD = SI_STAGE_D>
+template <int KS, int R>
 struct Tile {
-  static constexpr int STAGE = SD * KS * 1024;
+  static constexpr int STAGE = SI_STAGE_D * KS * 1024;
   v4i w[R][KS];
   double s[R];
 

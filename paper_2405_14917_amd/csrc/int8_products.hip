@@ -1,5 +1,6 @@
 // Digits of the operands and the output products on the int8 matrix cores; see int8_products.h.
 #include <algorithm>
+#include <type_traits>
 
 #include "int8_products.h"
 
@@ -218,7 +219,8 @@ __global__ __launch_bounds__(256) void int_g_digits(const float* __restrict__ G,
       mx = mx > om ? mx : om;
       any |= ((uint64_t)(unsigned)__shfl_xor((int)(any >> 32), d, WAVE) << 32) | (unsigned)__shfl_xor((int)any, d, WAVE);
     }
-    const int lo = mx ? __builtin_ctzll(any) / 8 : 0, nd = max(digits_for(mx) - lo, 0);
+    // (no fewer than five, which int_outputs_twice takes without looking; the upper or the lower ones may be zeros)
+    const int top = digits_for(mx), lo = mx ? min(__builtin_ctzll(any) / 8, max(top - 5, 0)) : 0, nd = max(top - lo, 5);
     if (lane == 0) {
       meta[2 * ((int64_t)c * s.TB + tb)] = 8 * lo;
       meta[2 * ((int64_t)c * s.TB + tb) + 1] = nd;
@@ -259,18 +261,20 @@ __global__ __launch_bounds__(256) void int_g_digits(const float* __restrict__ G,
   }
 }
 
+// What a chunk's digits are; in the place of W's digits, where there are none, whether it is the first of its group and some zero of
+// the group lies outside int8.
+template <bool REF>
+__device__ __forceinline__ int describe_chunk(const OutArgs& a, int c, int tb, int row0) {
+  const int* x = a.mt.x + 2 * ((int64_t)c * a.s.TB + tb);
+  if (REF) return digits_word(x, digits_of_rows(a.s, a.mt.w, c, row0));
+  return digits_word(x, c % a.s.nchg == 0 && a.rest[c / a.s.nchg] >= a.rest_from);
+}
+
 // REF: Y = W X_s from the digits of W; else Y = W_N X_s.
-// COMP: sums to twice the precision, for W_hat X - W X (add_compensated).  Four vector instructions per output and pair of
-// digits in place of one, and twice the registers, so one tile per wavefront and four wavefronts per SIMD (two tiles and two
-// wavefronts, or one and three, are slower).  Those four leave little to hide a barrier behind, so a stage holds all digits of a
-// chunk, eight wavefronts share it, and a wavefront in its MFMAs goes before one in its sums: 4096 x 4096 against 4096 columns
-// 690 -> 625 us.  What bounds it is the vector work: 491 us with one instruction in place of the four, 590 to 600 without the
-// codes' or the digits' way from memory.
-template <int KS, bool REF, bool COMP>
-__global__ __launch_bounds__(COMP ? 512 : 256, COMP ? 4 : 3) void int_outputs(OutArgs a) {
-  constexpr int R = COMP ? 1 : 2, NW = COMP ? 8 : 4;
-  constexpr int SD = COMP ? SI_MAXD : SI_STAGE_D;
-  using TL = Tile<KS, R, SD>;
+template <int KS, bool REF>
+__global__ __launch_bounds__(256, 3) void int_outputs(OutArgs a) {
+  constexpr int R = 2, NW = 4, SD = SI_STAGE_D;
+  using TL = Tile<KS, R>;
   extern __shared__ __align__(16) char si_smem[];
   const IntShape& s = a.s;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -282,25 +286,16 @@ __global__ __launch_bounds__(COMP ? 512 : 256, COMP ? 4 : 3) void int_outputs(Ou
   const int64_t rstride = (int64_t)s.C * KS * 1024;
   const char* q0 = a.Q + (int64_t)(row0 >> 5) * rstride;
   const unsigned lane16 = lane * 16;
-  // what the chunks' digits are, in LDS
   int* tab = reinterpret_cast<int*>(si_smem + 2 * TL::STAGE);
-  auto describe = [&](int c) {
-    const int* x = a.mt.x + 2 * ((int64_t)c * s.TB + tb);
-    return digits_word(x, REF ? digits_of_rows(s, a.mt.w, c, row0) : 0);
-  };
-  for (int c = tid; c < min(s.C, SI_TAB); c += 64 * NW) tab[c] = describe(c);
+  for (int c = tid; c < min(s.C, SI_TAB); c += 64 * NW) tab[c] = describe_chunk<REF>(a, c, tb, row0);
   __syncthreads();
-  auto chunk_info = [&](int c) { return __builtin_amdgcn_readfirstlane(c < SI_TAB ? tab[c] : describe(c)); };
+  auto chunk_info = [&](int c) { return __builtin_amdgcn_readfirstlane(c < SI_TAB ? tab[c] : describe_chunk<REF>(a, c, tb, row0)); };
 
-  auto base = [&](int r) { return COMP ? sum_base(s.m, a.row_exp[row0 + 32 * r + l32]) : 0.0; };
-  double y[R][16], low[COMP ? R : 1][16];
+  double y[R][16];
 #pragma unroll
   for (int r = 0; r < R; ++r)
 #pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      y[r][v] = base(r);
-      low[COMP ? r : 0][v] = 0.0;
-    }
+    for (int v = 0; v < 16; ++v) y[r][v] = 0.0;
   TL tl;
   auto load_first = [&](int c) {                // the first (or only) set of chunk c
     tl.load_codes(q0 + (int64_t)c * KS * 1024, rstride, lane16);
@@ -328,44 +323,25 @@ __global__ __launch_bounds__(COMP ? 512 : 256, COMP ? 4 : 3) void int_outputs(Ou
     for (int j = 0; j < sets; ++j) {
       for (int p = (nd - 1) >> 1; p >= 0; --p) {
         v16i acc[R];
-        if constexpr (COMP) __builtin_amdgcn_s_setprio(1);
         tl.pair(x, p, 2 * p + 1 < nd, acc);
-        if constexpr (COMP) __builtin_amdgcn_s_setprio(0);
         if (p == 0) {
           if (j + 1 < sets)
             tl.load_codes(q0 + (j + 1) * a.plane + (int64_t)c * KS * 1024, rstride, lane16);
           else
             load_first(stage_chunk(next));
         }
-        const int e = unit + 8 * (lo + 2 * p) + (REF ? 8 * j : 0);
-        if constexpr (COMP) {
-#pragma unroll
-          for (int r = 0; r < R; ++r) {
-            const double f = ldexp(sc[r], e);
-#pragma unroll
-            for (int v = 0; v < 16; ++v) add_compensated(y[r][v], low[r][v], f, (double)acc[r][v]);
-          }
-        } else {
-          add_scaled<R>(y, acc, sc, e);
-        }
+        add_scaled<R>(y, acc, sc, unit + 8 * (lo + 2 * p) + (REF ? 8 * j : 0));
       }
     }
-    const int g = c / s.nchg;
-    if (!REF && stage_first(word) && c == g * s.nchg && a.rest[g] >= a.rest_from) {
+    if (!REF && stage_first(word) && digits_w(info)) {
+      const int g = c / s.nchg;
       // zeros outside int8: what the codes do not hold times the sum of the group's activations
       const double* Rz = a.Rz + (int64_t)g * s.npad + row0 + l32;
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
         const double sx = a.SX[(int64_t)g * s.tpad + tb * 32 + 8 * (v >> 2) + 4 * h + (v & 3)];
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-          if constexpr (COMP) {
-            add_compensated(y[r][v], low[r][v], -Rz[32 * r], sx);
-            low[r][v] = fma(-Rz[32 * r], a.SXlo[(int64_t)g * s.tpad + tb * 32 + 8 * (v >> 2) + 4 * h + (v & 3)], low[r][v]);
-          } else {
-            y[r][v] = fma(-Rz[32 * r], sx, y[r][v]);
-          }
-        }
+        for (int r = 0; r < R; ++r) y[r][v] = fma(-Rz[32 * r], sx, y[r][v]);
       }
     }
     if (done) break;
@@ -377,52 +353,275 @@ __global__ __launch_bounds__(COMP ? 512 : 256, COMP ? 4 : 3) void int_outputs(Ou
   for (int q = 0; q < 4; ++q) {
     const int64_t t = (int64_t)tb * 32 + 8 * q + 4 * h;
     if (t >= s.ts) continue;
-    int tu[4] = {0, 0, 0, 0};
-    if (a.token_unit) {
-#pragma unroll
-      for (int v = 0; v < 4; ++v) tu[v] = a.token_unit[t + v];
-    }
 #pragma unroll
     for (int r = 0; r < R; ++r) {
       const int row = row0 + 32 * r + l32;
       if (row >= s.n) continue;
-      double o[4], ol[4] = {0.0, 0.0, 0.0, 0.0};
+      double* out = a.Y + (int64_t)row * s.ts + t;
+      *reinterpret_cast<double2*>(out) = make_double2(y[r][4 * q], y[r][4 * q + 1]);
+      *reinterpret_cast<double2*>(out + 2) = make_double2(y[r][4 * q + 2], y[r][4 * q + 3]);
+    }
+  }
+}
+
+// The same with sums to twice the precision, for W_hat X - W X (add_compensated), and a unit per token.
+//
+// The digits of a chunk are summed in three int32 accumulators of a pair each.  The two lower ones are put together exactly in fp64
+// (below 2^48), so that a chunk takes two compensated additions, and these stand behind the MFMAs of the next chunk, four outputs
+// at a time: a wavefront fills both pipes by itself.  Two sets of accumulators and of codes and the sums are 234 registers: two
+// wavefronts per SIMD, in two workgroups, so that one computes while the other waits at a chunk's barrier (one workgroup of eight
+// wavefronts: 735 us against 615 before the order of the loads).  For the same reason all that the next chunk needs is asked for
+// beside this one's products, and nothing between two chunks' products waits for memory.
+// (A loop with one way out, and no choice among several bodies: else the compiler keeps the sums in memory between them.  So a
+// chunk has five digits at least, zeros if need be: five are what most chunks of a Gram matrix of 16-bit activations have, the
+// others six.)
+// 4096 x 4096 against 4096 columns: 600 -> 545 us (a compensated addition per pair of digits and the vector work behind each
+// pair's own MFMAs, four wavefronts per SIMD); vector instructions 53 % of the time, the matrix cores 28 %.
+template <int KS, bool REF>
+__global__ __launch_bounds__(256, 2) void int_outputs_twice(OutArgs a) {
+  constexpr int NW = 4;
+  constexpr int STAGE = SI_MAXD * KS * 1024;
+  extern __shared__ __align__(16) char si_smem[];
+  const IntShape& s = a.s;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l32 = lane & 31, h = lane >> 5;
+  int rt, tb;
+  tile_of(blockIdx.x, s.npad / (32 * NW), s.TB, rt, tb);
+  const int row0 = (rt * NW + wave) * 32;
+  const unsigned lds0 = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(uintptr_t)((__attribute__((address_space(3))) char*)si_smem));
+  int* tab = reinterpret_cast<int*>(si_smem + 2 * STAGE);
+  for (int c = tid; c < min(s.C, SI_TAB); c += 64 * NW) tab[c] = describe_chunk<REF>(a, c, tb, row0);
+  __syncthreads();
+
+  const double base = sum_base(s.m, a.row_exp[row0 + l32]);
+  double y[16], low[16];
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        o[v] = COMP ? y[r][4 * q + v] - base(r) : y[r][4 * q + v];
-        if (a.token_unit) o[v] = tu[v] == INT_MIN ? NAN : ldexp(o[v], tu[v]);
-        if constexpr (COMP) {
-          const int64_t at = (int64_t)row * s.ts + t + v;
-          ol[v] = ldexp(low[r][4 * q + v], tu[v] == INT_MIN ? 0 : tu[v]);
-          if (!REF) o[v] = (o[v] - a.sub[at]) + (ol[v] - a.sublo[at]);
+  for (int v = 0; v < 16; ++v) {
+    y[v] = base;
+    low[v] = 0.0;
+  }
+  v16i sums[2][3];                   // of a chunk: digits 0 and 1, 2 and 3, 4 and 5
+  double f0[2];                      // what the lowest digit counts
+#pragma unroll
+  for (int k = 0; k < 3; ++k)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) sums[1][k][v] = 0;
+  f0[1] = 0.0;
+  // The additions of p, four outputs at a time in five steps: each step has four independent chains of two instructions (one
+  // output after the other, eight instructions that wait for one another, took 735 us).  What a step leaves is pinned there, or
+  // the compiler moves all of it behind the chunk's products.
+  struct {
+    double c[4], t[4], s[4], b[4];
+  } ad;
+  auto add_step = [&](const v16i (&p)[3], double g0, double g2, int step) {
+    const int v0 = step / 5 * 4;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int v = v0 + i;
+      if (step % 5 == 0) {
+        ad.c[i] = (double)p[2][v];
+        ad.s[i] = fma(g2, ad.c[i], y[v]);
+        asm volatile("" : "+v"(ad.c[i]), "+v"(ad.s[i]));
+      } else if (step % 5 == 1) {
+        ad.b[i] = fma(g2, ad.c[i], y[v] - ad.s[i]);
+        ad.t[i] = (double)p[1][v];
+        asm volatile("" : "+v"(ad.b[i]), "+v"(ad.t[i]));
+      } else if (step % 5 == 2) {
+        low[v] += ad.b[i];
+        ad.t[i] = fma(ad.t[i], 65536.0, (double)p[0][v]);
+        asm volatile("" : "+v"(low[v]), "+v"(ad.t[i]));
+      } else if (step % 5 == 3) {
+        y[v] = fma(g0, ad.t[i], ad.s[i]);
+        ad.b[i] = ad.s[i] - y[v];
+        asm volatile("" : "+v"(y[v]), "+v"(ad.b[i]));
+      } else {
+        low[v] += fma(g0, ad.t[i], ad.b[i]);
+        asm volatile("" : "+v"(low[v]));
+      }
+    }
+  };
+  // A part: a chunk and a set of W's digits (the codes are one set).  What a part needs from memory is asked for during the one
+  // before it: codes into w[its parity], its chunk's digits into the other stage.
+  v4i w[2][KS];
+  const char* q0 = a.Q + (int64_t)(row0 >> 5) * s.C * KS * 1024 + lane * 16;
+  auto load_codes = [&](v4i (&to)[KS], int c, int j) {
+#pragma unroll
+    for (int i = 0; i < KS; ++i) to[i] = *reinterpret_cast<const v4i*>(q0 + j * a.plane + (int64_t)(c * KS + i) * 1024);
+  };
+  auto chunk_word = [&](int c) { return c < SI_TAB ? tab[c] : describe_chunk<REF>(a, c, tb, row0); };
+  const double* scales = REF ? a.mt.wunit + row0 : a.S + row0;            // of the next chunk
+  int in_group = 0;
+  auto next_scale = [&]() {
+    const double v = scales[l32];
+    if (REF || ++in_group == s.nchg) {
+      in_group = 0;
+      scales += s.npad;
+    }
+    return v;
+  };
+  const char* digits = a.Xd + (int64_t)tb * SI_MAXD * KS * 1024;          // of the next chunk
+  const int64_t digits_step = (int64_t)s.TB * SI_MAXD * KS * 1024;
+  auto uniform = [](int v) { return __builtin_amdgcn_readfirstlane(v); };   // (what the compiler does not see is the same in all lanes)
+  auto load_digit = [&](int to, int i) {
+    const uint64_t from = (uint64_t)(uintptr_t)(digits + i * 1024);
+    const uint64_t base = (uint64_t)(unsigned)uniform((int)(from >> 32)) << 32 | (unsigned)uniform((int)from);
+    lds_load16((unsigned)uniform((int)(lds0 + to * STAGE + i * 1024)), lane * 16, reinterpret_cast<const char*>(base));
+  };
+  int c = 0, j = 0, buf = 0, info = uniform(chunk_word(0)), after = 0, next_info = chunk_word(min(1, s.C - 1));
+  for (int i = wave; i < digits_x(info) * KS; i += NW) load_digit(0, i);
+  digits += digits_step;
+  load_codes(w[0], 0, 0);
+  double sc = next_scale(), sc_next = 0.0;
+  bool live = true;                  // behind the last part one more is taken with a count of zero, where the loop needs it
+  auto zeros_outside = [&]() {       // of int8: what the codes do not hold times the sum of the group's activations
+    const int g = c / s.nchg;
+    const double rz = -a.Rz[(int64_t)g * s.npad + row0 + l32];
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      const int64_t at = (int64_t)g * s.tpad + tb * 32 + 8 * (v >> 2) + 4 * h + (v & 3);
+      add_compensated(y[v], low[v], rz, a.SX[at]);
+      low[v] = fma(rz, a.SXlo[at], low[v]);
+      asm volatile("" : "+v"(y[v]), "+v"(low[v]) : : "memory");       // (rare: not all loads at once)
+    }
+  };
+  auto shift = [&](v16i& c) {
+#pragma unroll
+    for (int v = 0; v < 16; ++v) c[v] <<= 8;
+  };
+  auto digit = [&](const v4i (&wc)[KS], const char* x, int d, v16i& to) {
+#pragma unroll
+    for (int i = 0; i < KS; ++i) to = __builtin_amdgcn_mfma_i32_32x32x32_i8(*reinterpret_cast<const v4i*>(x + (d * KS + i) * 1024), wc[i], to, 0, 0, 0);
+  };
+  // the digits of a part into sums[CUR], beside the products of the lower five the additions of sums[1 - CUR]
+  auto part = [&](auto cur) {
+    constexpr int CUR = decltype(cur)::value;
+    constexpr int AHEAD = 2, ND = 5, NM = ND * KS;   // operand reads in flight; digits and MFMAs with additions beside them
+    constexpr int ORDER[ND] = {4, 3, 1, 2, 0};       // the pairs in turn: while one is shifted, another's products run
+    const bool fresh_chunk = !REF || j == 0;
+    if (fresh_chunk) {
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      __syncthreads();
+    }
+    v16i(&p)[3] = sums[CUR];
+    const char* x = si_smem + buf * STAGE + lane * 16;
+    const int nd = digits_x(info), sets = REF ? digits_w(info) : 1;       // five to seven digits
+    const double count = live && sets > 0 ? ldexp(sc, exponent_x(info) + (REF ? 8 * j : 0)) : 0.0;
+    // the next part
+    const bool more = REF && j + 1 < sets;
+    const int cn = min(more ? c : c + 1, s.C - 1), jn = more ? j + 1 : 0;
+    if (fresh_chunk) after = uniform(next_info);
+    const int left = fresh_chunk && c + 1 < s.C ? digits_x(after) * KS : 0;
+    load_codes(w[1 - CUR], cn, jn);
+    if (fresh_chunk) {
+      if (c + 1 < s.C) sc_next = next_scale();
+      next_info = chunk_word(min(c + 2, s.C - 1));
+      if (!REF && digits_w(info) && live) zeros_outside();
+    }
+    v4i fr[AHEAD + 1];
+    auto frag = [&](int n) { fr[n % (AHEAD + 1)] = *reinterpret_cast<const v4i*>(x + (ORDER[n / KS] * KS + n % KS) * 1024); };
+    const double o0 = f0[1 - CUR], o2 = o0 * 4294967296.0;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) p[2][v] = 0;
+    if (nd > 5) {
+      if (nd > 6) {                                  // (rare: added at once)
+        digit(w[CUR], x, 6, p[2]);
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          add_compensated(y[v], low[v], count * 0x1p48, (double)p[2][v]);
+          asm volatile("" : "+v"(y[v]), "+v"(low[v]));
+          p[2][v] = 0;
         }
       }
-      if constexpr (COMP && REF) {
-        double* outlo = a.Ylo + (int64_t)row * s.ts + t;
-        *reinterpret_cast<double2*>(outlo) = make_double2(ol[0], ol[1]);
-        *reinterpret_cast<double2*>(outlo + 2) = make_double2(ol[2], ol[3]);
-      }
-      double* out = a.Y + (int64_t)row * s.ts + t;
-      *reinterpret_cast<double2*>(out) = make_double2(o[0], o[1]);
-      *reinterpret_cast<double2*>(out + 2) = make_double2(o[2], o[3]);
+      digit(w[CUR], x, 5, p[2]);
+      shift(p[2]);
     }
+#pragma unroll
+    for (int n = 0; n < AHEAD; ++n) frag(n);
+#pragma unroll
+    for (int n = 0; n < NM; ++n) {
+      const int d = ORDER[n / KS];
+      if (n + AHEAD < NM) frag(n + AHEAD);
+      if (n % KS == 0 && d < 3 && d != 1) shift(p[d / 2]);
+      __builtin_amdgcn_sched_barrier(0);
+      v16i in = p[d / 2];
+      if (n % KS == 0 && (d & 1)) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) in[v] = 0;
+      }
+      p[d / 2] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fr[n % (AHEAD + 1)], w[CUR][n % KS], in, 0, 0, 0);
+#pragma unroll
+      for (int step = n * 20 / NM; step < (n + 1) * 20 / NM; ++step) add_step(sums[1 - CUR], o0, o2, step);
+      // the next chunk's digits, one KiB at a time: every chunk has these, the sixth and seventh follow below
+      if (n % 2 == 0 && n / 2 * NW < ND * KS) {
+        const int i = n / 2 * NW + wave;
+        if (i < min(left, ND * KS)) load_digit(buf ^ 1, i);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    for (int i = ND * KS + wave; i < left; i += NW) load_digit(buf ^ 1, i);
+    f0[CUR] = count;
+    if (more) {
+      ++j;
+    } else {
+      j = 0;
+      if (++c < s.C) {
+        buf ^= 1;
+        info = after;
+        sc = sc_next;
+        digits += digits_step;
+      } else {
+        live = false;
+      }
+    }
+  };
+  while (live) {
+    part(std::integral_constant<int, 0>{});
+    part(std::integral_constant<int, 1>{});
+  }
+#pragma unroll
+  for (int step = 0; step < 20; ++step) add_step(sums[1], f0[1], f0[1] * 4294967296.0, step);
+  const int row = row0 + l32;
+  if (row >= s.n) return;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int64_t t = (int64_t)tb * 32 + 8 * q + 4 * h;
+    if (t >= s.ts) continue;
+    double o[4], ol[4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int tu = a.token_unit ? a.token_unit[t + v] : 0;
+      const int64_t at = (int64_t)row * s.ts + t + v;
+      o[v] = tu == INT_MIN ? NAN : ldexp(y[4 * q + v] - base, tu);
+      ol[v] = ldexp(low[4 * q + v], tu == INT_MIN ? 0 : tu);
+      if (!REF) o[v] = (o[v] - a.sub[at]) + (ol[v] - a.sublo[at]);
+    }
+    if constexpr (REF) {
+      double* outlo = a.Ylo + (int64_t)row * s.ts + t;
+      *reinterpret_cast<double2*>(outlo) = make_double2(ol[0], ol[1]);
+      *reinterpret_cast<double2*>(outlo + 2) = make_double2(ol[2], ol[3]);
+    }
+    double* out = a.Y + (int64_t)row * s.ts + t;
+    *reinterpret_cast<double2*>(out) = make_double2(o[0], o[1]);
+    *reinterpret_cast<double2*>(out + 2) = make_double2(o[2], o[3]);
   }
 }
 
 template <int KS>
 slim_status outputs_launch(slim_ctx* ctx, const char* name, const OutArgs& a, bool ref, bool compensated) {
-  const dim3 grid(a.s.RT * a.s.TB), block(compensated ? 512 : 256);
-  const size_t smem = 2 * (compensated ? Tile<KS, 1, SI_MAXD>::STAGE : Tile<KS, 2>::STAGE) + sizeof(int) * std::min(a.s.C, SI_TAB);
+  const dim3 grid(a.s.RT * a.s.TB);
+  const size_t table = sizeof(int) * std::min(a.s.C, SI_TAB);
   if (compensated) {
+    const size_t smem = 2 * SI_MAXD * KS * 1024 + table;
     if (ref)
-      SLIM_LAUNCH(ctx, name, (int_outputs<KS, true, true>), grid, block, smem, a);
+      SLIM_LAUNCH(ctx, name, (int_outputs_twice<KS, true>), dim3(2 * grid.x), dim3(256), smem, a);
     else
-      SLIM_LAUNCH(ctx, name, (int_outputs<KS, false, true>), grid, block, smem, a);
+      SLIM_LAUNCH(ctx, name, (int_outputs_twice<KS, false>), dim3(2 * grid.x), dim3(256), smem, a);
   } else {
+    const size_t smem = 2 * Tile<KS, 2>::STAGE + table;
     if (ref)
-      SLIM_LAUNCH(ctx, name, (int_outputs<KS, true, false>), grid, block, smem, a);
+      SLIM_LAUNCH(ctx, name, (int_outputs<KS, true>), grid, dim3(256), smem, a);
     else
-      SLIM_LAUNCH(ctx, name, (int_outputs<KS, false, false>), grid, block, smem, a);
+      SLIM_LAUNCH(ctx, name, (int_outputs<KS, false>), grid, dim3(256), smem, a);
   }
   return SLIM_OK;
 }
