@@ -271,6 +271,15 @@ __global__ __launch_bounds__(512, 2) void rgemm_kernel(RgArgs a) {
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
   frags(0, sm, 0);
+  // A whole tile's results stay in `lo` and are stored beside the first two planes of the next tile, one store per two MFMAs: a CU
+  // gets rid of 18 bytes per ns, and as one burst at the end the stores held up 7 of a tile's 45 us.
+  bool pending = false;
+  char* crow = nullptr;                        // the wavefront's part of the tile, at the row that is stored next
+  const unsigned clane = (unsigned)((4 * h * a.ldc + l32) * 8);
+  auto store = [&](int j, int v, bool inside) {                // in order: all v of one j, then of the other
+    if (inside) *reinterpret_cast<double*>(crow + 256 * j + clane) = lo[j][v];
+    crow += a.ldc * 8 * (v == 15 ? -27 : (v & 3) == 3 ? 5 : 1);
+  };
   for (int tile = blockIdx.x; tile < total; tile += gridDim.x) {
     int bi, bj;
     rg_tile(a, tile, bi, bj);
@@ -284,20 +293,29 @@ __global__ __launch_bounds__(512, 2) void rgemm_kernel(RgArgs a) {
       }
     };
     double old[2][16];
-    // one plane: its products into acc[P], the sums of the plane before it (acc[1 - P]) taken into hi and lo beside them
-    auto run_plane = [&](auto par, auto first, auto last, int p) {
-      constexpr int P = decltype(par)::value;
-      constexpr bool FIRST = decltype(first)::value, LAST = decltype(last)::value;
-      const int ch = FIRST ? 0 : d_crt.hi[p - 1];
-      const double cl = FIRST ? 0.0 : d_crt.lo[p - 1];
+    // one plane: its products into acc[NTH % 2], the sums of the plane before it taken into hi and lo beside them.  NTH: 0, 1, 2, or 3
+    // and 4 for the odd and the even ones behind them; LAST: the old values of C are asked for
+    auto run_plane = [&](auto nth, auto last, int p) {
+      constexpr int NTH = decltype(nth)::value, P = NTH % 2;
+      constexpr bool LAST = decltype(last)::value;
+      const int ch = NTH == 0 ? 0 : d_crt.hi[p - 1];
+      const double cl = NTH == 0 ? 0.0 : d_crt.lo[p - 1];
 #pragma unroll
       for (int kc = 0; kc < NS; ++kc) {
-        // stage s + 1 has landed in every wavefront, and every wavefront has read the last of stage s - 1.  (A tile's stages 0
-        // to 3 have landed before its loop: behind them are the stores of the last tile, which nothing waits for here.)
-        if (!FIRST || kc == NS - 1)
-          asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
-        else
+        // Stage s + 1 has landed in every wavefront, and every wavefront has read the last of stage s - 1.  A tile's stages 0 to
+        // 3 have landed before its loop.  What may still be on its way is newer: the loads of two stages and, where the last
+        // tile's results are being stored, up to twelve stores (four per stage, in the first eight).
+        constexpr int s = 4 * NTH;
+        if (NTH == 0 && kc < NS - 1)
           asm volatile("" ::: "memory");
+        else if (s + kc > 10 || !pending)
+          asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+        else if (s + kc == 10)
+          asm volatile("s_waitcnt vmcnt(12)" ::: "memory");
+        else if (s + kc == 9)
+          asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
+        else
+          asm volatile("s_waitcnt vmcnt(20)" ::: "memory");
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
         stage_load();                          // stage s + 4, into the unit of stage s - 1
@@ -322,49 +340,74 @@ __global__ __launch_bounds__(512, 2) void rgemm_kernel(RgArgs a) {
             }
             acc[P][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[b], fb[b][j], c, 0, 0, 0);
             const int el = (kc * 4 + ks) * 2 + j, ej = el / 16, ev = el % 16;
-            if constexpr (FIRST) {
-              hi[ej][ev] = 0;
-              lo[ej][ev] = 0.0;
-            } else {
-              const int s = acc[1 - P][ej][ev];
-              hi[ej][ev] += __mul24(s, ch);
-              lo[ej][ev] = fma((double)s, cl, lo[ej][ev]);
+            if (NTH < 2 && el % 2 == 0) {      // (an element is stored before its register takes the new tile's sums)
+              const int se = 16 * NTH + el / 2;
+              if (pending) store(se / 16, se % 16, true);
             }
-            asm volatile("" : "+v"(hi[ej][ev]), "+v"(lo[ej][ev]));   // (or the compiler moves all of them behind the plane's products)
+            if constexpr (NTH > 0) {
+              const int s32 = acc[1 - P][ej][ev];
+              if constexpr (NTH == 1) {
+                hi[ej][ev] = __mul24(s32, ch);
+                lo[ej][ev] = (double)s32 * cl;
+              } else {
+                hi[ej][ev] += __mul24(s32, ch);
+                lo[ej][ev] = fma((double)s32, cl, lo[ej][ev]);
+              }
+              asm volatile("" : "+v"(hi[ej][ev]), "+v"(lo[ej][ev]));   // (or the compiler moves all of them behind the plane's products)
+            }
             __builtin_amdgcn_sched_barrier(0);
           }
         }
       }
     };
-    using std::false_type;
-    using std::true_type;
-    constexpr std::integral_constant<int, 0> even{};
-    constexpr std::integral_constant<int, 1> odd{};
-    static_assert(NP % 2 == 0, "the last plane is an odd one");
-    run_plane(even, true_type{}, false_type{}, 0);
-    for (int p = 1; p + 2 < NP; p += 2) {
-      run_plane(odd, false_type{}, false_type{}, p);
-      run_plane(even, false_type{}, false_type{}, p + 1);
+    constexpr std::integral_constant<int, 3> odd{};
+    constexpr std::integral_constant<int, 4> even{};
+    static_assert(NP % 2 == 0 && NP > 4, "the last plane is an odd one");
+    run_plane(std::integral_constant<int, 0>{}, std::false_type{}, 0);
+    run_plane(std::integral_constant<int, 1>{}, std::false_type{}, 1);
+    run_plane(std::integral_constant<int, 2>{}, std::false_type{}, 2);
+    for (int p = 3; p + 2 < NP; p += 2) {
+      run_plane(odd, std::false_type{}, p);
+      run_plane(even, std::false_type{}, p + 1);
     }
-    run_plane(odd, false_type{}, true_type{}, NP - 1);
+    run_plane(odd, std::true_type{}, NP - 1);
     old_values(1, old[1]);
+    const int rowu = bi * BT + wr * 32, colu = bj * BT + wc * 64;
+    const double sa = a.sa[min(rowu + l32, a.M - 1)];          // of the lane's row of the wavefront's 32
+    double sb[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) sb[j] = a.sb[min(col0 + 32 * j, a.N - 1)] * a.alpha;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");           // (the next tile's first stages with them)
+    crow = reinterpret_cast<char*>(a.C + (int64_t)rowu * a.ldc + colu);
+    pending = bi * BT + BT <= a.M && bj * BT + BT <= a.N;
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int col = col0 + 32 * j;
-      const double sb = a.sb[min(col, a.N - 1)] * a.alpha;
+    for (int v = 0; v < 16; ++v) {
+      const int r = 8 * (v >> 2) + 4 * h + (v & 3);
+      const double sr = __hiloint2double(__shfl(__double2hiint(sa), r, 64), __shfl(__double2loint(sa), r, 64));
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int row = row0 + 8 * (v >> 2) + (v & 3);
+      for (int j = 0; j < 2; ++j) {
         const int s = acc[1][j][v];
         const int t = hi[j][v] + __mul24(s, d_crt.hi[NP - 1]);
         const double l = fma((double)s, d_crt.lo[NP - 1], lo[j][v]);
         double f = fma((double)(t << 8), 0x1p-32, l);
         f -= rint(f);
-        const double r = fma(f * a.sa[min(row, a.M - 1)], sb, old[j][v]);
-        if (row < a.M && col < a.N) a.C[(int64_t)row * a.ldc + col] = r;
+        lo[j][v] = fma(f * sr, sb[j], old[j][v]);
+        asm volatile("" : "+v"(lo[j][v]));
       }
     }
+    if (!pending) {
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int v = 0; v < 16; ++v)
+          store(j, v, row0 + 8 * (v >> 2) + (v & 3) < a.M && col0 + 32 * j < a.N);
+    }
+  }
+  if (pending) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) store(j, v, true);
   }
 }
 
