@@ -17,9 +17,9 @@
 //    lanes use, coalesced; a packed zero point is taken apart there.
 //  * The loads of a wavefront's next unit are in flight while it decodes the present one.
 //
-// What bounds it: decoding (14 vector instructions per MFMA and 16 x 32 codes; 24 over the whole kernel at 28672 x 8192, counters,
+// What bounds it: decoding (10 to 12 vector instructions per MFMA and 16 x 32 codes; about twice that over the whole kernel at 28672 x 8192,
 // with addresses, parameters and scaled sums) and the latency of a few loads in a row; a small layer is bound by the launch.  Against the kernels with ranges of groups (and
-// their reduction): 28672 x 8192 at 2 bits, fp16, 16 tokens: 55.0 -> 35.6 us (2.5 TB/s); 4096 x 11008 at 3 bits, bf16, packed
+// their reduction): 28672 x 8192 at 2 bits, fp16, 16 tokens: 55.0 -> 35.6, now 33.6 us (2.7 TB/s); 4096 x 11008 at 3 bits, bf16, packed
 // zero points, 5 tokens, which ran without matrix cores and unpacked the zero points in a launch of its own: 47.2 -> 15.2 us;
 // 4096 x 4096, one token: 12.9 -> 9.5 us, of which the way of the call through Python is 9.
 #include <algorithm>
@@ -50,19 +50,88 @@ __device__ __forceinline__ float4v mfma(const uint4& a, const uint4& b, float4v 
     return __builtin_amdgcn_mfma_f32_16x16x32_f16(*reinterpret_cast<const half8v*>(&a), *reinterpret_cast<const half8v*>(&b), c, 0, 0, 0);
 }
 
-// The 8 B-bit codes of a lane, from bit `s` of (w1 : w0) on -> pairs (1024 + c_{2j}, 1024 + c_{2j+1}) in packed fp16; B = 1:
-// 1024 + 2 c.  Even codes go to the low half of u, odd ones to the high half, so that one shift serves both.
+// The second operand of an MFMA: c_i - z of a lane's 8 B-bit codes, which start at byte s / 8 of (w1 : w0); width 1: 2 c_i - 2 z.
+// Bytes go to where they are wanted by v_perm (even codes in the low half, odd ones in the high half), a code stays at its bit of
+// the byte and is OR-ed into the mantissa of 1024.0 there, which makes it 1024 + w c with w up to 256, and one fma per
+// pair, exact, takes that to c - z: (1024 + w c) / w - (1024 / w + z).  Width 2: 10 instructions per 8 codes in place of 14 with the codes
+// shifted to bit 0, width 1: 10 for 13, width 3: 12 for 16, width 4: 12 for 15.  28672 x 8192 at 2 bits: 35.5 -> 33.7 us with 16 tokens.
+// The codes are shifted (SHIFT) at width 5, whose codes reach beyond the mantissa, in groups of 32, where the pairs' zeros are formed
+// anew for every chunk (4096 x 4096 11.2 -> 11.6 us), and where a wavefront has 64 rows x 32 tokens, whose registers they do not fit
+// into (11008 x 4096, 64 tokens: 34 -> 39 us).
 template <int B>
-__device__ __forceinline__ void spread(unsigned w0, unsigned w1, int s, unsigned one, unsigned (&t)[4]) {
-  if constexpr (B == 1) {
+struct Pairs;                                    // of the places of a pair's codes, as they repeat
+template <>
+struct Pairs<1> {                                // (one bit up: the operand is 2 c - 2 z)
+  static constexpr int CLASSES = 4;
+  static constexpr unsigned MASK[4] = {0x00040002u, 0x00100008u, 0x00400020u, 0x01000080u};
+  static constexpr int W[4][2] = {{2, 4}, {8, 16}, {32, 64}, {128, 256}};
+};
+template <>
+struct Pairs<2> {
+  static constexpr int CLASSES = 2;
+  static constexpr unsigned MASK[2] = {0x000c0003u, 0x00c00030u};
+  static constexpr int W[2][2] = {{1, 4}, {16, 64}};
+};
+template <>
+struct Pairs<3> {
+  static constexpr int CLASSES = 4;
+  static constexpr unsigned MASK[4] = {0x00380007u, 0x000e01c0u, 0x03800070u, 0x00e0001cu};
+  static constexpr int W[4][2] = {{1, 8}, {64, 2}, {16, 128}, {4, 32}};
+};
+template <>
+struct Pairs<4> {
+  static constexpr int CLASSES = 1;
+  static constexpr unsigned MASK[1] = {0x00f0000fu};
+  static constexpr int W[1][2] = {{1, 16}};
+};
+template <int B, bool SHIFT>
+constexpr int classes() {
+  if constexpr (SHIFT) return 1;
+  else return Pairs<B>::CLASSES;
+}
+
+// What a lane needs to place the codes of a width: v_perm selectors.
+template <int B>
+struct Places {
+  static constexpr int N = B == 3 || B == 4 ? 4 : 1;
+  unsigned sel[N];
+  __device__ __forceinline__ explicit Places(int s) {
+    const unsigned at = (unsigned)(s >> 3) * 0x01010101u;
+    if constexpr (B == 1) sel[0] = 0x0c000c00u + (at & 0x00ff00ffu);
+    if constexpr (B == 2) sel[0] = 0x01000100u + at;
+    if constexpr (B == 3) {
+      sel[0] = 0x01000100u + at;
+      sel[1] = 0x02010100u + at;
+      sel[2] = 0x02010201u + at;
+      sel[3] = 0x03020302u + at;
+    }
+    if constexpr (B == 4) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) sel[j] = 0x0c000c00u + 0x00010001u * j;
+    }
+  }
+};
+
+template <int B>
+__device__ __forceinline__ half2v pair_weight(int c) {
+  half2v m;
+  m[0] = (_Float16)((B == 1 ? 2.0f : 1.0f) / Pairs<B>::W[c][0]);
+  m[1] = (_Float16)((B == 1 ? 2.0f : 1.0f) / Pairs<B>::W[c][1]);
+  return m;
+}
+
+// (1024 + w c) pairs, class by class; SHIFT: w = 1 (width 1: 2)
+template <int B, bool SHIFT>
+__device__ __forceinline__ void spread(unsigned w0, unsigned w1, const Places<B>& p, int s, unsigned one, unsigned (&t)[4]) {
+  if constexpr (SHIFT && B == 1) {
     const unsigned v = w0 >> s, u = ((v << 1) & 0xffffu) | (v << 16);
 #pragma unroll
     for (int j = 0; j < 4; ++j) t[j] = ((u >> (2 * j)) & 0x00020002u) | one;
-  } else if constexpr (B == 2) {
+  } else if constexpr (SHIFT && B == 2) {
     const unsigned v = w0 >> s, u = (v & 0xffffu) | ((v << 14) & 0xffff0000u);
 #pragma unroll
     for (int j = 0; j < 4; ++j) t[j] = ((u >> (4 * j)) & 0x00030003u) | one;
-  } else {
+  } else if constexpr (SHIFT) {
     constexpr unsigned M = ((1u << B) - 1u) * 0x10001u;
     unsigned x[2];
     if constexpr (B == 5) {
@@ -79,15 +148,50 @@ __device__ __forceinline__ void spread(unsigned w0, unsigned w1, int s, unsigned
       t[2 * i] = (u & M) | one;
       t[2 * i + 1] = ((u >> (2 * B)) & M) | one;
     }
+  } else if constexpr (B == 1) {
+    const unsigned u = __builtin_amdgcn_perm(w1, w0, p.sel[0]) << 1;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) t[j] = (u & Pairs<1>::MASK[j]) | one;
+  } else if constexpr (B == 2) {
+    const unsigned u = __builtin_amdgcn_perm(w1, w0, p.sel[0]), v = u >> 8;
+    t[0] = (u & Pairs<2>::MASK[0]) | one;
+    t[1] = (u & Pairs<2>::MASK[1]) | one;
+    t[2] = (v & Pairs<2>::MASK[0]) | one;
+    t[3] = (v & Pairs<2>::MASK[1]) | one;
+  } else {
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      t[j] = (__builtin_amdgcn_perm(w1, w0, p.sel[j]) & Pairs<B>::MASK[j % Pairs<B>::CLASSES]) | one;
   }
 }
 
-template <bool BF16>
-__device__ __forceinline__ uint4 minus_zero(const unsigned (&t)[4], half2v zz) {
+// 1024 / w + z of the classes, from 1024 + z: integers of at most 2046, which fp16 holds
+template <int B, bool SHIFT>
+__device__ __forceinline__ void zeros_of(half2v zz, half2v (&z)[classes<B, SHIFT>()]) {
+  if constexpr (SHIFT) {
+    z[0] = zz;
+  } else {
+#pragma unroll
+    for (int c = 0; c < Pairs<B>::CLASSES; ++c) {
+      half2v d;
+      d[0] = (_Float16)(1024.0f - 1024.0f * (float)pair_weight<B>(c)[0]);
+      d[1] = (_Float16)(1024.0f - 1024.0f * (float)pair_weight<B>(c)[1]);
+      z[c] = zz - d;
+    }
+  }
+}
+
+template <int B, bool SHIFT, bool BF16>
+__device__ __forceinline__ uint4 minus_zero(const unsigned (&t)[4], const half2v (&z)[classes<B, SHIFT>()]) {
   unsigned o[4];
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
-    const half2v d = *reinterpret_cast<const half2v*>(&t[j]) - zz;
+    const half2v v = *reinterpret_cast<const half2v*>(&t[j]);
+    half2v d;
+    if constexpr (SHIFT)
+      d = v - z[0];
+    else
+      d = __builtin_elementwise_fma(v, pair_weight<B>(j % Pairs<B>::CLASSES), -z[j % Pairs<B>::CLASSES]);
     if constexpr (BF16) {
       // an integer of at most 256 (few_zmax), so the upper 16 bits of the float are the exact bf16 value
       const unsigned lo = __float_as_uint((float)d[0]), hi = __float_as_uint((float)d[1]);
@@ -131,13 +235,18 @@ struct Unit {
 template <int B, int UC, int RT, int TT, bool BF16>
 __device__ __forceinline__ void multiply(const Unit<UC, RT, TT>& u, int s, unsigned one, const half2v (&zz)[RT],
                                          float4v (&acc)[RT][TT]) {
+  const Places<B> p(s);
+  constexpr bool SHIFT = B == 5 || UC == 1 || RT * TT == 8;
+  half2v z[RT][classes<B, SHIFT>()];
+#pragma unroll
+  for (int r = 0; r < RT; ++r) zeros_of<B, SHIFT>(zz[r], z[r]);
 #pragma unroll
   for (int c = 0; c < UC; ++c)
 #pragma unroll
     for (int r = 0; r < RT; ++r) {
       unsigned t[4];
-      spread<B>(u.w0[c][r], u.w1[c][r], s, one, t);
-      const uint4 bf = minus_zero<BF16>(t, zz[r]);
+      spread<B, SHIFT>(u.w0[c][r], u.w1[c][r], p, s, one, t);
+      const uint4 bf = minus_zero<B, SHIFT, BF16>(t, z[r]);
 #pragma unroll
       for (int q = 0; q < TT; ++q) acc[r][q] = mfma<BF16>(u.x[c][q], bf, acc[r][q]);
     }
