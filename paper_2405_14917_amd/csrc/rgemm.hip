@@ -15,9 +15,9 @@
 // matrix cores give 7.5e-16 and 7.1e-16 to 1.0e-15.  (With 15 moduli 1.3e-16 and 7 % slower, with 13 it would be 1e-14.)
 //
 // What bounds it: power (some 1.7 GHz of 2.4 while it runs; the int8 products alone take two thirds of the time at that clock)
-// and the stores of C, 18 bytes per ns and CU.  us for the product / with both operands' residues / on the fp64 matrix cores:
-//   4096 x 1024  53 / 90 / 93    4096 x 2048  100 / 139 / 187    4096 x 3584  165 / 205 / 350    4096 x 10496  540 / 592 / 820
-//   28672 x 512  179 / 278 / 365    28672 x 4096  1500 / 1600 / 1920 (one launch after the other; by itself 1290)
+// and, where a launch has one tile per CU, the old values and the stores of C.  us for the product / with both operands' residues / on the fp64 matrix cores:
+//   4096 x 1024  47 / 85 / 84    4096 x 2048  85 / 124 / 171    4096 x 3584  151 / 191 / 360    4096 x 10496  478 / 531 / 846
+//   28672 x 4096  1447 / 1549 / 1956 (one launch after the other; by itself 1290)
 #include <algorithm>
 
 #include "slim_internal.h"
@@ -189,6 +189,7 @@ constexpr int NS = KMAX / STAGE_K;           // stages per plane
 constexpr int UNIT = 2 * BT * STAGE_K;       // bytes
 constexpr int UNITS = 5;
 constexpr size_t RG_LDS = size_t(UNITS) * UNIT;
+constexpr int RG_BESIDE = 64;                // CUs left to kernels of other streams
 
 // Tiles in bands of eight rows, column by column; rounds of `ncu` workgroups take consecutive tiles, XCD c (id mod 8) the c-th
 // eighth of them: a patch of 8 x 4 tiles, whose operands of a plane its L2 holds.
@@ -469,6 +470,10 @@ slim_status slim_rgemm(slim_ctx* ctx, const char* name, const slim_rg_desc& d) {
                                           (int)RG_LDS));
     done = true;
   }
-  SLIM_LAUNCH(ctx, slim_prof_name(name, "rgemm_kernel"), rgemm_kernel, dim3(d.beside ? total : std::min(total, a.ncu)), dim3(512), RG_LDS, a);
+  // Beside other streams' work the products leave some CUs alone: all of the inverse's on all CUs, tile after tile or a workgroup per
+  // tile, hold its chain of links up.  4096 x 11008 pass, us: a workgroup per tile 56200, all but 16 CUs 55500, all but 32 55700,
+  // all but 64 55400, all but 128 56500.
+  const int wgs = d.beside ? std::max(8, a.ncu - RG_BESIDE) : a.ncu;
+  SLIM_LAUNCH(ctx, slim_prof_name(name, "rgemm_kernel"), rgemm_kernel, dim3(std::min(total, wgs)), dim3(512), RG_LDS, a);
   return SLIM_OK;
 }

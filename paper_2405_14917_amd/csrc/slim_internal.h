@@ -188,7 +188,7 @@ slim_rg_operand slim_rg_carve(slim_ctx* ctx, int rows);
 slim_status slim_rg_residues(slim_ctx* ctx, const char* name, const slim_rg_operand& o, const double* src, int64_t ld, int rows, int K,
                              bool columns);
 // C = old C + alpha A B^T; columns below `fresh` have no old C; `upper`: only tiles that reach the diagonal or lie above it;
-// `beside`: a workgroup per tile, so that kernels of other streams get their turn (else one per CU, tile after tile)
+// `beside`: some CUs are left to kernels of other streams
 struct slim_rg_desc {
   slim_rg_operand A, B;
   int rowsA, rowsB;    // of the operands as they were converted
