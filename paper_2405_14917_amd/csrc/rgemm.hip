@@ -179,7 +179,7 @@ struct RgArgs {
 };
 
 // A workgroup of eight wavefronts has a tile of 128 x 128: a lane keeps the sums of 32 elements in 3 registers each beside two
-// sets of int32 accumulators, 248 registers in all, which is what bounds the tile.  The accumulators of one modulus fill while
+// sets of int32 accumulators, 252 registers in all, which is what bounds the tile.  The accumulators of one modulus fill while
 // those of the one before are added up, three vector instructions behind every MFMA, so that the matrix pipe never waits for
 // the vector work.  Operands go from memory to a ring of five 32 KiB stages in LDS (128 channels of both operands), four
 // stages ahead, from one tile into the next; one barrier per stage.
