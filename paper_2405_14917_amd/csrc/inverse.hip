@@ -12,7 +12,7 @@
 //        panel       R[0:J+1, J+1] = A[0:J+1, J+1] V^T of the block to the right, beside it
 //        update      rank-64 update with that panel of the columns from the start of block J's group on
 //      and once per group rank-512 updates of everything further left; see the schedule at the call site.
-//      (the large ones, and the terms of step 3, from residues on the int8 matrix cores: rgemm.hip)
+//      (the large ones, and the large terms of step 3, from residues on the int8 matrix cores: rgemm.hip)
 //   3. triangular inverse U = R^-1 group by group on a further stream, beside the factorisation: inside a group
 //      strip by strip of 16 columns from the inverted diagonal blocks upwards, in one launch, the
 //      rows right of the group from T = R[g, S] U[S, S], which is kept up to date for all rows above by one
@@ -745,10 +745,14 @@ static size_t inverse_base_bytes(int m) {
 }
 // The panels of a group and its rows of U as residues, where the rank-512 products of any group are taken that way.
 static bool far_pays(int gp, int K) { return slim_rg_pays((int64_t)gp * gp / 2, K); }
-static bool terms_pay(int g0, int m, int K) { return slim_rg_pays((int64_t)g0 * (m - g0), K); }
+static bool terms_pay(int g0, int right, int K) { return slim_rg_pays((int64_t)g0 * right, K); }
 static size_t inverse_residue_bytes(int m) {
   const int g = GRP * NB;
-  return terms_pay(m / g / 2 * g, m, g) ? 3 * slim_rg_operand_bytes(m) : 0;
+  for (int g0 = g; g0 < m; g0 += g) {
+    const int right = std::max(0, m - g0 - g), K = std::min(g, m - g0);
+    if (far_pays(g0 - g, K) || terms_pay(g0, right, K)) return 3 * slim_rg_operand_bytes(m);
+  }
+  return 0;
 }
 size_t slim_ws_need_inverse(int m) { return inverse_base_bytes(m) + inverse_residue_bytes(m); }
 
@@ -881,13 +885,9 @@ extern "C" slim_status slim_hessian_inverse(slim_ctx* ctx, const float* G, int64
       rs = slim_dgemm(ctx, "inv_trtri_rows_dgemm", 0, d);
       if (rs != SLIM_OK) return rs;
     }
-    if (g0 > 0 && pr) {
-      const int cols = (int)(m - g0);
-      rs = slim_rg_residues(ctx, "inv_trtri_residues", urows, U + g0 * ldu + g0, ldu, cols, gw, true);
-      if (rs != SLIM_OK) return rs;
-      rs = slim_rgemm(ctx, "inv_trtri_terms_dgemm", {*pr, urows, (int)g0, cols, A + g0, lda, (int)g0, cols, 1.0, gw, false, true});
-      if (rs != SLIM_OK) return rs;
-    } else if (g0 > 0) {
+    if (g0 > 0) {
+      // The columns of the group itself in fp64 always: column j has terms of the channels up to j alone, and residues, which keep
+      // 2^-55.5 of the norm over all of the group's channels, would lose digits of a small one beside a large later channel.
       d.A = R + g0;
       d.lda = lda;
       d.B = U + g0 * ldu + g0;
@@ -902,15 +902,22 @@ extern "C" slim_status slim_hessian_inverse(slim_ctx* ctx, const float* G, int64
       d.beta = 0.0;
       rs = slim_dgemm(ctx, "inv_trtri_terms_dgemm", 0, d);
       if (rs != SLIM_OK) return rs;
-      if (g1 < m) {
+    }
+    if (g0 > 0 && g1 < m) {
+      const int cols = (int)(m - g1);
+      if (pr) {
+        rs = slim_rg_residues(ctx, "inv_trtri_residues", urows, U + g0 * ldu + g1, ldu, cols, gw, true);
+        if (rs != SLIM_OK) return rs;
+        rs = slim_rgemm(ctx, "inv_trtri_terms_dgemm", {*pr, urows, (int)g0, cols, A + g1, lda, (int)g0, cols, 1.0, false, true});
+      } else {
         d.B = U + g0 * ldu + g1;
         d.C = A + g1;
-        d.N = (int)(m - g1);
+        d.N = cols;
         d.flags = 0;
         d.beta = 1.0;
         rs = slim_dgemm(ctx, "inv_trtri_terms_dgemm", 0, d);
-        if (rs != SLIM_OK) return rs;
       }
+      if (rs != SLIM_OK) return rs;
     }
     return SLIM_OK;
   };
@@ -983,7 +990,7 @@ extern "C" slim_status slim_hessian_inverse(slim_ctx* ctx, const float* G, int64
     if (!first) continue;
     // ---- s1: everything two or more groups to the left
     const int gp = g0 - GRP * NB;
-    const bool far_r = residues && gp > 0 && far_pays(gp, g1 - g0), terms_r = residues && terms_pay(g0, m, g1 - g0);
+    const bool far_r = residues && gp > 0 && far_pays(gp, g1 - g0), terms_r = residues && terms_pay(g0, m - g1, g1 - g0);
     if (far_r || terms_r) {
       // the group's panels as residues, for the far update (both operands) and for the terms of the inverse, which may still
       // be reading the other set
@@ -1019,7 +1026,7 @@ extern "C" slim_status slim_hessian_inverse(slim_ctx* ctx, const float* G, int64
       last_far_slot ^= 1;
       ctx->attach_event = ev_far[last_far_slot];
       if (far_r)
-        st = slim_rgemm(ctx, "inv_syrk_dgemm", {panels[panel_slot], panels[panel_slot], g0, g0, A, lda, gp, gp, -1.0, 0, true, true});
+        st = slim_rgemm(ctx, "inv_syrk_dgemm", {panels[panel_slot], panels[panel_slot], g0, g0, A, lda, gp, gp, -1.0, true, true});
       else
         st = slim_dgemm(ctx, "inv_syrk_dgemm", 1, d);
       if (st != SLIM_OK) return st;

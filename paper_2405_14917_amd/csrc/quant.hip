@@ -1576,7 +1576,7 @@ extern "C" slim_status slim_gptq_quantize(slim_ctx* ctx, const void* W, slim_dty
       if (residues && slim_rg_pays((int64_t)d.M * d.N, d.K)) {
         st = slim_rg_residues(ctx, "gptq_trailing_residues", Er, E, WINC, n, d.K, false);
         if (st == SLIM_OK) st = slim_rg_residues(ctx, "gptq_trailing_residues", Ur, d.B, ldu, d.N, d.K, true);
-        if (st == SLIM_OK) st = slim_rgemm(ctx, "gptq_trailing_dgemm", {Er, Ur, n, d.N, d.C, d.ldc, n, d.N, -1.0, 0, false, false});
+        if (st == SLIM_OK) st = slim_rgemm(ctx, "gptq_trailing_dgemm", {Er, Ur, n, d.N, d.C, d.ldc, n, d.N, -1.0, false, false});
       } else {
         st = slim_dgemm(ctx, "gptq_trailing_dgemm", 0, d);
       }

@@ -173,7 +173,6 @@ struct RgArgs {
   int64_t ldc;
   int M, N;
   double alpha;
-  int fresh;            // columns below this one: C's old values don't count
   int tiles_m, tiles_n, upper;
   int ncu;
 };
@@ -288,10 +287,7 @@ __global__ __launch_bounds__(512, 2) void rgemm_kernel(RgArgs a) {
     auto old_values = [&](int j, double (&old)[16]) {
       const int col = min(col0 + 32 * j, a.N - 1);
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        old[v] = 0.0;
-        if (col0 + 32 * j >= a.fresh) old[v] = a.C[(int64_t)min(row0 + 8 * (v >> 2) + (v & 3), a.M - 1) * a.ldc + col];
-      }
+      for (int v = 0; v < 16; ++v) old[v] = a.C[(int64_t)min(row0 + 8 * (v >> 2) + (v & 3), a.M - 1) * a.ldc + col];
     };
     double old[2][16];
     // one plane: its products into acc[NTH % 2], the sums of the plane before it taken into hi and lo beside them.  NTH: 0, 1, 2, or 3
@@ -458,7 +454,6 @@ slim_status slim_rgemm(slim_ctx* ctx, const char* name, const slim_rg_desc& d) {
   a.M = d.M;
   a.N = d.N;
   a.alpha = d.alpha * kM;
-  a.fresh = d.fresh;
   a.upper = d.upper ? 1 : 0;
   a.tiles_m = slim_cdiv(d.M, BT);
   a.tiles_n = slim_cdiv(d.N, BT);

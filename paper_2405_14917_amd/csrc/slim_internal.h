@@ -187,8 +187,8 @@ slim_rg_operand slim_rg_carve(slim_ctx* ctx, int rows);
 // src: rows x K, or (columns) K x rows
 slim_status slim_rg_residues(slim_ctx* ctx, const char* name, const slim_rg_operand& o, const double* src, int64_t ld, int rows, int K,
                              bool columns);
-// C = old C + alpha A B^T; columns below `fresh` have no old C; `upper`: only tiles that reach the diagonal or lie above it;
-// `beside`: some CUs are left to kernels of other streams
+// C += alpha A B^T; `upper`: only tiles that reach the diagonal or lie above it; `beside`: some CUs are left to kernels of other
+// streams
 struct slim_rg_desc {
   slim_rg_operand A, B;
   int rowsA, rowsB;    // of the operands as they were converted
@@ -196,7 +196,6 @@ struct slim_rg_desc {
   int64_t ldc;
   int M, N;
   double alpha;
-  int fresh;
   bool upper, beside;
 };
 slim_status slim_rgemm(slim_ctx* ctx, const char* name, const slim_rg_desc& d);

@@ -41,6 +41,11 @@ def base_sweep(n, m):
     return up(8 * n * m) + up(8 * n * 512) + up(16 * n) + up(8 * n)
 
 
+def steps(s):
+    """The launches of a profiled context, "<step>@<kernel>"."""
+    return {name.split("#")[0] for name in s.profile_collect()}
+
+
 # the smallest width that takes the path; a last group that is not whole, blocks and tiles that are not (65 tiles of 64, an odd
 # number of tiles of 128); several groups
 @pytest.mark.parametrize("m", [4352, 4480, 4930, 6400])
@@ -109,3 +114,24 @@ def test_rows_that_are_not_finite_stay_alone(contexts):
     keep[37] = keep[700] = False
     for key in ("codes", "scale", "zero"):
         assert torch.equal(a[key][keep], b[key][keep]), key
+
+
+@pytest.mark.parametrize("m,g0", [(6144, 3072), (6400, 2560)])
+def test_columns_of_a_group_beside_a_large_channel(contexts, m, g0):
+    """H = [[I + B B^T, B], [B^T, I]] over all integers, B one group's columns in the rows of the group above: U = [[I, -B], [0, I]],
+    every step of it exact in fp64.  One channel of B is 2^10 times the others, which must not cost the columns before it digits."""
+    binding, make = contexts
+    s = make(binding.workspace_query(0, m, 0))
+    B = torch.zeros((512, 512), dtype=torch.float64, device="cuda")
+    B[:, :8] = torch.arange(512 * 8, device="cuda").reshape(512, 8) % 15 - 7
+    B[:, 300] = 1024.0
+    H = torch.eye(m, dtype=torch.float64, device="cuda")
+    H[g0 - 512:g0, g0 - 512:g0] += B @ B.t()
+    H[g0 - 512:g0, g0:g0 + 512] = B
+    H[g0:g0 + 512, g0 - 512:g0] = B.t()
+    G = H.float()
+    assert torch.equal(G.double(), H)
+    s.profile_enable()
+    U, _ = s.hessian_inverse(G, 2, 0.0)
+    assert "inv_trtri_terms_dgemm@rgemm_kernel" in steps(s)
+    assert ((U[g0 - 512:g0, g0:g0 + 512] + B).abs() <= 4 * EPS * B.abs()).all()
