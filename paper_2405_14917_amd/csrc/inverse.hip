@@ -743,9 +743,16 @@ static size_t inverse_base_bytes(int m) {
   const int parts = slim_cdiv(m, 256);
   return 2 * slim_ws_round(sizeof(double) * (size_t)m * m) + slim_ws_round(sizeof(double) * (size_t)parts * m) + 256;
 }
-// The panels of a group and its rows of U as residues, where the rank-512 products of any group are taken that way.
-static bool far_pays(int gp, int K) { return slim_rg_pays((int64_t)gp * gp / 2, K); }
-static bool terms_pay(int g0, int right, int K) { return slim_rg_pays((int64_t)g0 * right, K); }
+// The panels of a group and its rows of U as residues, where the rank-512 products of any group are taken that way: from 2^21 results
+// on, and not for a narrow last group, whose fp64 product gets cheaper with its rank.  A product by itself gains from twice that on;
+// beside the chain of links it counts that the residue product leaves 64 CUs alone, and the panels are converted once for both
+// kinds of products.  The whole inverse, us, with all products in fp64 / from 2^22 / from 2^21 / from 2^20 (terms) results on: 3072
+// 1218 / 1217 / 1203 / 1210, 3584 1547 / 1548 / 1466 / 1479, 4096 1918 / 1898 / 1769 / 1779, 5120 3003 / 2673 / 2638 / 2635, 8192 8850 /
+// 7073 / 7110 / 7105.
+constexpr int64_t RESIDUE_RESULTS = (int64_t)1 << 21;
+constexpr int RESIDUE_RANK = 384;
+static bool far_pays(int gp, int K) { return K > RESIDUE_RANK && (int64_t)gp * gp / 2 >= RESIDUE_RESULTS; }
+static bool terms_pay(int g0, int right, int K) { return K > RESIDUE_RANK && (int64_t)g0 * right >= RESIDUE_RESULTS; }
 static size_t inverse_residue_bytes(int m) {
   const int g = GRP * NB;
   for (int g0 = g; g0 < m; g0 += g) {

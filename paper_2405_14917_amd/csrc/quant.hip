@@ -1328,7 +1328,9 @@ static size_t gptq_base_bytes(int n, int m) {
 }
 // operands of the updates behind a window as residues, where any of them is taken that way
 static size_t gptq_residue_bytes(int n, int m) {
-  return m > GPTQ_WINC && slim_rg_pays((int64_t)n * (m - GPTQ_WINC), GPTQ_WINC) ? slim_rg_operand_bytes(n) + slim_rg_operand_bytes(m - GPTQ_WINC) : 0;
+  for (int rest = m - GPTQ_WINC; rest > 0; rest -= GPTQ_WINC)
+    if (slim_rg_pays(n, rest)) return slim_rg_operand_bytes(n) + slim_rg_operand_bytes(m - GPTQ_WINC);
+  return 0;
 }
 size_t slim_ws_need_gptq(int n, int m) { return gptq_base_bytes(n, m) + gptq_residue_bytes(n, m); }
 
@@ -1573,7 +1575,7 @@ extern "C" slim_status slim_gptq_quantize(slim_ctx* ctx, const void* W, slim_dty
       d.C = Wc + w1;
       d.N = m - w1;
       d.K = w1 - w0;
-      if (residues && slim_rg_pays((int64_t)d.M * d.N, d.K)) {
+      if (residues && slim_rg_pays(d.M, d.N)) {
         st = slim_rg_residues(ctx, "gptq_trailing_residues", Er, E, WINC, n, d.K, false);
         if (st == SLIM_OK) st = slim_rg_residues(ctx, "gptq_trailing_residues", Ur, d.B, ldu, d.N, d.K, true);
         if (st == SLIM_OK) st = slim_rgemm(ctx, "gptq_trailing_dgemm", {Er, Ur, n, d.N, d.C, d.ldc, n, d.N, -1.0, false, false});

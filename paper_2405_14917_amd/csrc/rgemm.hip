@@ -410,9 +410,16 @@ __global__ __launch_bounds__(512, 2) void rgemm_kernel(RgArgs a) {
 
 }  // namespace
 
-// From 4096 x 1024 on (the table above), where the residues of both operands come to a quarter of the product's time.  A rank of
-// 384 or less costs what 512 does here, and fp64 products get cheaper with it.
-bool slim_rg_pays(int64_t outputs, int K) { return K > 384 && outputs >= (int64_t)1 << 22; }
+// A product by itself, of rank 512, with operands converted for it alone, against the fp64 form.  us: the kernel takes 27 per round of
+// 256 tiles and 12 per 256 tiles; converting takes 35 and 3 per 1000 rows of an operand beyond 4096; the fp64 form 0.27 to 0.33 per
+// tile.  Both sides measured, fp64 / residues: 256 tiles 4096 x 1024 82 / 81, 1024 x 4096 80 / 81; 384 4096 x 1536 110 / 109; 512
+// 4096 x 2048 152 / 121, 1024 x 8192 152 / 124, 8192 x 1024 157 / 121; but tall ones, whose rows' residues take their time:
+// 28672 x 256 142 / 198, 28672 x 512 288 / 279, 16384 x 512 150 / 142, 28672 x 1024 507 / 420.
+bool slim_rg_pays(int M, int N) {
+  const int tiles = slim_cdiv(M, BT) * slim_cdiv(N, BT);
+  const double convert = 35.0 + 3e-3 * (std::max(0, M - 4096) + std::max(0, N - 4096));
+  return 27.0 * slim_cdiv(tiles, 256) + 12.0 * tiles / 256 + convert < 0.27 * tiles;
+}
 
 size_t slim_rg_operand_bytes(int rows) {
   const int rp = slim_cdiv(rows, BT) * BT;

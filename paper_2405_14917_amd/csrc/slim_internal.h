@@ -182,7 +182,8 @@ struct slim_rg_operand {
   double* scale;       // per row
 };
 size_t slim_rg_operand_bytes(int rows);
-bool slim_rg_pays(int64_t outputs, int K);
+// whether an M x N product of rank 512, converting both operands, is faster than slim_dgemm
+bool slim_rg_pays(int M, int N);
 slim_rg_operand slim_rg_carve(slim_ctx* ctx, int rows);
 // src: rows x K, or (columns) K x rows
 slim_status slim_rg_residues(slim_ctx* ctx, const char* name, const slim_rg_operand& o, const double* src, int64_t ld, int rows, int K,

@@ -150,3 +150,13 @@ def test_workspace_of_the_linear_layer_serves_every_number_of_tokens(binding):
         need = [binding.workspace_query(n, m, beta, t_x=t, num_cus=256) for t in (16, 17, 64, 65, 100, 128, 500, 2048, 1 << 20)]
         assert len(set(need)) == 1, (n, m, beta, need)
         assert binding.workspace_query(n, m, beta, t_x=1, num_cus=256) <= need[0]
+
+
+def test_workspace_holds_residues_only_where_their_products_are_faster(binding):
+    """A sweep's updates behind a window are taken from residues by what the product and the conversions cost: not for a tall layer
+    with a narrow rest (160 columns), nor at one round of tiles (4096 x 1024 results), but for large ones."""
+    base = lambda n, m: 8 * n * m + 8 * n * 512
+    for n, m, beta, taken in ((28672, 672, 32, False), (9001, 1024, 512, False), (20480, 1024, 128, False), (16384, 2048, 128, True),
+                              (28672, 2048, 128, True)):
+        extra = binding.workspace_query(n, m, beta) - base(n, m)
+        assert (extra > 14 * 512 * n) if taken else (extra < 64 * n), (n, m, extra)
