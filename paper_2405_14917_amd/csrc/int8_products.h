@@ -300,11 +300,14 @@ slim_status slim_int_clear(slim_ctx* ctx, const slimint::IntMeta& mt, int* rest,
 slim_status slim_int_w_units(slim_ctx* ctx, const slimint::IntShape& s, const slimint::IntMeta& mt, const void* W, slim_dtype dt, int64_t ldw);
 slim_status slim_int_x_digits(slim_ctx* ctx, const slimint::IntShape& s, const slimint::IntMeta& mt, const void* X, slim_dtype dt, int64_t ldx,
                               char* Xd, double* SX);
-// The digits of a fp32 matrix with a unit per token (column): token_unit[ts]; work: 2 ts ints.
+// The digits of a fp32 matrix with a unit per token (column): token_unit[ts]; work: 2 ts ints, of which the first then holds what
+// sums by pairs of digits would cost (slim_int_pairs_pay).
 slim_status slim_int_g_digits(slim_ctx* ctx, const slimint::IntShape& s, const slimint::IntMeta& mt, const float* G, int64_t ldg,
                               int* work, int* token_unit, char* Xd, double* SX, double* SXlo);
-// Y = W X (ref: from the digits of W) or W_hat X (from codes and scales); `compensated`: Y and Ylo = W X to twice the
-// precision, or W_hat X minus (sub, sublo)
-slim_status slim_int_outputs(slim_ctx* ctx, const char* name, const slimint::OutArgs& a, bool ref, bool compensated);
+bool slim_int_pairs_pay(int cost);
+// Y = W X (ref: from the digits of W) or W_hat X (from codes and scales); `twice`, `by_pairs`: Y and Ylo = W X to twice the
+// precision, or W_hat X minus (sub, sublo), by the kernel for most G or the one for a G of few digits
+enum class slim_int_sums { plain, twice, by_pairs };
+slim_status slim_int_outputs(slim_ctx* ctx, const char* name, const slimint::OutArgs& a, bool ref, slim_int_sums sums);
 
 #endif

@@ -186,6 +186,12 @@ __global__ __launch_bounds__(256) void int_g_units(int64_t ts, const int* __rest
   token_unit[i] = mx == INT_MAX ? INT_MIN : block_unit((unsigned)mx, work[ts + i]);
 }
 
+// What int_outputs_twice takes of a chunk without looking: zeros where there are fewer.
+constexpr int TWICE_DIGITS = 5;
+// What a chunk costs there, and in int_outputs_by_pairs if it has digits and per pair of them (in about 1/20 us per product of 4096
+// outputs x 4096 columns)
+constexpr int TWICE_CHUNK = 26, PAIRS_CHUNK = 3, PAIRS_PAIR = 10;
+
 // grid (ceil(TB / 4), k): a wavefront finds the digits in use of 32 columns of every chunk of one group, and cuts them
 __global__ __launch_bounds__(256) void int_g_digits(const float* __restrict__ G, int64_t ldg, IntShape s, int* __restrict__ meta,
                                                     const int* __restrict__ token_unit, char* __restrict__ Xd, double* __restrict__ SX,
@@ -219,8 +225,7 @@ __global__ __launch_bounds__(256) void int_g_digits(const float* __restrict__ G,
       mx = mx > om ? mx : om;
       any |= ((uint64_t)(unsigned)__shfl_xor((int)(any >> 32), d, WAVE) << 32) | (unsigned)__shfl_xor((int)any, d, WAVE);
     }
-    // (no fewer than five, which int_outputs_twice takes without looking; the upper or the lower ones may be zeros)
-    const int top = digits_for(mx), lo = mx ? min(__builtin_ctzll(any) / 8, max(top - 5, 0)) : 0, nd = max(top - lo, 5);
+    const int lo = mx ? __builtin_ctzll(any) / 8 : 0, nd = max(digits_for(mx) - lo, 0);
     if (lane == 0) {
       meta[2 * ((int64_t)c * s.TB + tb)] = 8 * lo;
       meta[2 * ((int64_t)c * s.TB + tb) + 1] = nd;
@@ -234,14 +239,14 @@ __global__ __launch_bounds__(256) void int_g_digits(const float* __restrict__ G,
         csum += v;
         u[i] = digit_bytes(v) >> (8 * lo);
       }
-      for (int d = 0; d < nd; ++d) {
+      for (int d = 0; d < max(nd, TWICE_DIGITS); ++d) {
         unsigned w[4];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           w[q] = 0;
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
-            w[q] |= ((unsigned)u[4 * q + i] & 255u) << (8 * i);
+            w[q] |= (d < nd ? (unsigned)u[4 * q + i] & 255u : 0u) << (8 * i);
             u[4 * q + i] >>= 8;
           }
         }
@@ -259,6 +264,21 @@ __global__ __launch_bounds__(256) void int_g_digits(const float* __restrict__ G,
     SX[(int64_t)g * s.tpad + t] = sum;
     SXlo[(int64_t)g * s.tpad + t] = sumlo;
   }
+}
+
+// One workgroup: cost = what int_outputs_by_pairs would take for these digits (see there)
+__global__ __launch_bounds__(1024) void int_g_cost(const int* __restrict__ meta, int64_t chunks, int* __restrict__ cost) {
+  __shared__ unsigned sum;
+  if (threadIdx.x == 0) sum = 0;
+  __syncthreads();
+  unsigned mine = 0;
+  for (int64_t i = threadIdx.x; i < chunks; i += 1024) {
+    const int nd = meta[2 * i + 1];
+    mine += nd ? PAIRS_CHUNK + PAIRS_PAIR * ((nd + 1) >> 1) : 0;
+  }
+  atomicAdd(&sum, mine);
+  __syncthreads();
+  if (threadIdx.x == 0) *cost = (int)(sum / (unsigned)chunks);
 }
 
 // What a chunk's digits are; in the place of W's digits, where there are none, whether it is the first of its group and some zero of
@@ -364,6 +384,48 @@ __global__ __launch_bounds__(256, 3) void int_outputs(OutArgs a) {
   }
 }
 
+// Zeros outside int8 in sums to twice the precision: what the codes do not hold times the sum of the group's activations.
+__device__ __forceinline__ void add_zeros(const OutArgs& a, int c, int tb, int row0, int lane, double (&y)[16], double (&low)[16]) {
+  const int g = c / a.s.nchg;
+  const double rz = -a.Rz[(int64_t)g * a.s.npad + row0 + (lane & 31)];
+#pragma unroll
+  for (int v = 0; v < 16; ++v) {
+    const int64_t at = (int64_t)g * a.s.tpad + tb * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
+    add_compensated(y[v], low[v], rz, a.SX[at]);
+    low[v] = fma(rz, a.SXlo[at], low[v]);
+    asm volatile("" : "+v"(y[v]), "+v"(low[v]) : : "memory");       // (rare: not all loads at once)
+  }
+}
+// A wavefront's sums to twice the precision -> Y and Ylo, or Y = sums - (sub, sublo)
+template <bool REF>
+__device__ __forceinline__ void store_twice(const OutArgs& a, int row0, int tb, int lane, double base, const double (&y)[16], const double (&low)[16]) {
+  const IntShape& s = a.s;
+  const int row = row0 + (lane & 31), h = lane >> 5;
+  if (row >= s.n) return;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int64_t t = (int64_t)tb * 32 + 8 * q + 4 * h;
+    if (t >= s.ts) continue;
+    double o[4], ol[4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int tu = a.token_unit ? a.token_unit[t + v] : 0;
+      const int64_t at = (int64_t)row * s.ts + t + v;
+      o[v] = tu == INT_MIN ? NAN : ldexp(y[4 * q + v] - base, tu);
+      ol[v] = ldexp(low[4 * q + v], tu == INT_MIN ? 0 : tu);
+      if (!REF) o[v] = (o[v] - a.sub[at]) + (ol[v] - a.sublo[at]);
+    }
+    if constexpr (REF) {
+      double* outlo = a.Ylo + (int64_t)row * s.ts + t;
+      *reinterpret_cast<double2*>(outlo) = make_double2(ol[0], ol[1]);
+      *reinterpret_cast<double2*>(outlo + 2) = make_double2(ol[2], ol[3]);
+    }
+    double* out = a.Y + (int64_t)row * s.ts + t;
+    *reinterpret_cast<double2*>(out) = make_double2(o[0], o[1]);
+    *reinterpret_cast<double2*>(out + 2) = make_double2(o[2], o[3]);
+  }
+}
+
 // The same with sums to twice the precision, for W_hat X - W X (add_compensated), and a unit per token.
 //
 // The digits of a chunk are summed in three int32 accumulators of a pair each.  The two lower ones are put together exactly in fp64
@@ -374,13 +436,13 @@ __global__ __launch_bounds__(256, 3) void int_outputs(OutArgs a) {
 // beside this one's products, and nothing between two chunks' products waits for memory.
 // (A loop with one way out, and no choice among several bodies: else the compiler keeps the sums in memory between them.  So a
 // chunk has five digits at least, zeros if need be: five are what most chunks of a Gram matrix of 16-bit activations have, the
-// others six.)
+// others six.  A G of fewer is left to int_outputs_by_pairs.)
 // 4096 x 4096 against 4096 columns: 600 -> 545 us (a compensated addition per pair of digits and the vector work behind each
 // pair's own MFMAs, four wavefronts per SIMD); vector instructions 53 % of the time, the matrix cores 28 %.
 template <int KS, bool REF>
 __global__ __launch_bounds__(256, 2) void int_outputs_twice(OutArgs a) {
   constexpr int NW = 4;
-  constexpr int STAGE = SI_MAXD * KS * 1024;
+  constexpr int STAGE = SI_MAXD * KS * 1024, ND = TWICE_DIGITS;
   extern __shared__ __align__(16) char si_smem[];
   const IntShape& s = a.s;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -468,22 +530,11 @@ __global__ __launch_bounds__(256, 2) void int_outputs_twice(OutArgs a) {
     lds_load16((unsigned)uniform((int)(lds0 + to * STAGE + i * 1024)), lane * 16, reinterpret_cast<const char*>(base));
   };
   int c = 0, j = 0, buf = 0, info = uniform(chunk_word(0)), after = 0, next_info = chunk_word(min(1, s.C - 1));
-  for (int i = wave; i < digits_x(info) * KS; i += NW) load_digit(0, i);
+  for (int i = wave; i < max(digits_x(info), ND) * KS; i += NW) load_digit(0, i);
   digits += digits_step;
   load_codes(w[0], 0, 0);
   double sc = next_scale(), sc_next = 0.0;
   bool live = true;                  // behind the last part one more is taken with a count of zero, where the loop needs it
-  auto zeros_outside = [&]() {       // of int8: what the codes do not hold times the sum of the group's activations
-    const int g = c / s.nchg;
-    const double rz = -a.Rz[(int64_t)g * s.npad + row0 + l32];
-#pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const int64_t at = (int64_t)g * s.tpad + tb * 32 + 8 * (v >> 2) + 4 * h + (v & 3);
-      add_compensated(y[v], low[v], rz, a.SX[at]);
-      low[v] = fma(rz, a.SXlo[at], low[v]);
-      asm volatile("" : "+v"(y[v]), "+v"(low[v]) : : "memory");       // (rare: not all loads at once)
-    }
-  };
   auto shift = [&](v16i& c) {
 #pragma unroll
     for (int v = 0; v < 16; ++v) c[v] <<= 8;
@@ -495,7 +546,7 @@ __global__ __launch_bounds__(256, 2) void int_outputs_twice(OutArgs a) {
   // the digits of a part into sums[CUR], beside the products of the lower five the additions of sums[1 - CUR]
   auto part = [&](auto cur) {
     constexpr int CUR = decltype(cur)::value;
-    constexpr int AHEAD = 2, ND = 5, NM = ND * KS;   // operand reads in flight; digits and MFMAs with additions beside them
+    constexpr int AHEAD = 2, NM = ND * KS;           // operand reads in flight; MFMAs with additions beside them
     constexpr int ORDER[ND] = {4, 3, 1, 2, 0};       // the pairs in turn: while one is shifted, another's products run
     const bool fresh_chunk = !REF || j == 0;
     if (fresh_chunk) {
@@ -510,12 +561,12 @@ __global__ __launch_bounds__(256, 2) void int_outputs_twice(OutArgs a) {
     const bool more = REF && j + 1 < sets;
     const int cn = min(more ? c : c + 1, s.C - 1), jn = more ? j + 1 : 0;
     if (fresh_chunk) after = uniform(next_info);
-    const int left = fresh_chunk && c + 1 < s.C ? digits_x(after) * KS : 0;
+    const int left = fresh_chunk && c + 1 < s.C ? max(digits_x(after), ND) * KS : 0;
     load_codes(w[1 - CUR], cn, jn);
     if (fresh_chunk) {
       if (c + 1 < s.C) sc_next = next_scale();
       next_info = chunk_word(min(c + 2, s.C - 1));
-      if (!REF && digits_w(info) && live) zeros_outside();
+      if (!REF && digits_w(info) && live) add_zeros(a, c, tb, row0, lane, y, low);
     }
     v4i fr[AHEAD + 1];
     auto frag = [&](int n) { fr[n % (AHEAD + 1)] = *reinterpret_cast<const v4i*>(x + (ORDER[n / KS] * KS + n % KS) * 1024); };
@@ -580,37 +631,109 @@ __global__ __launch_bounds__(256, 2) void int_outputs_twice(OutArgs a) {
   }
 #pragma unroll
   for (int step = 0; step < 20; ++step) add_step(sums[1], f0[1], f0[1] * 4294967296.0, step);
-  const int row = row0 + l32;
-  if (row >= s.n) return;
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int64_t t = (int64_t)tb * 32 + 8 * q + 4 * h;
-    if (t >= s.ts) continue;
-    double o[4], ol[4];
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int tu = a.token_unit ? a.token_unit[t + v] : 0;
-      const int64_t at = (int64_t)row * s.ts + t + v;
-      o[v] = tu == INT_MIN ? NAN : ldexp(y[4 * q + v] - base, tu);
-      ol[v] = ldexp(low[4 * q + v], tu == INT_MIN ? 0 : tu);
-      if (!REF) o[v] = (o[v] - a.sub[at]) + (ol[v] - a.sublo[at]);
-    }
-    if constexpr (REF) {
-      double* outlo = a.Ylo + (int64_t)row * s.ts + t;
-      *reinterpret_cast<double2*>(outlo) = make_double2(ol[0], ol[1]);
-      *reinterpret_cast<double2*>(outlo + 2) = make_double2(ol[2], ol[3]);
-    }
-    double* out = a.Y + (int64_t)row * s.ts + t;
-    *reinterpret_cast<double2*>(out) = make_double2(o[0], o[1]);
-    *reinterpret_cast<double2*>(out + 2) = make_double2(o[2], o[3]);
+  store_twice<REF>(a, row0, tb, lane, base, y, low);
+}
+
+// The same for a G of few digits (diagonal, block diagonal, small integers): every pair of digits enters the sums by itself, and
+// chunks without digits are passed over.  Four wavefronts per SIMD, eight to a workgroup and its 256 outputs: with the 256 threads
+// and two wavefronts of int_outputs_twice most of the time is a chunk's barrier.  slim_lwc_quantize of 4096 x 4096, 20 steps, us,
+// int_outputs_twice / this: diagonal G 13660 / 5730, blocks of 512 13790 / 6640, two digits (activations to 3) 13930 / 10060, four
+// (to 200 and 2000) 14160 / 13420 and 14590 / 13910, a quarter of the channels dead 14220 / 13340; five 15000 / 16100.
+template <int KS, bool REF>
+__global__ __launch_bounds__(512, 4) void int_outputs_by_pairs(OutArgs a) {
+  constexpr int NW = 8, STAGE = SI_MAXD * KS * 1024;
+  extern __shared__ __align__(16) char si_smem[];
+  const IntShape& s = a.s;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l32 = lane & 31, h = lane >> 5;
+  int rt, tb;
+  tile_of(blockIdx.x, s.RT, s.TB, rt, tb);
+  const int row0 = rt * SI_ROWS + wave * 32;
+  const unsigned lds0 = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(uintptr_t)((__attribute__((address_space(3))) char*)si_smem));
+  int* tab = reinterpret_cast<int*>(si_smem + 2 * STAGE);
+  int outside = s.C > SI_TAB;        // (a table that holds all says whether any group has zeros outside int8)
+  for (int c = tid; c < min(s.C, SI_TAB); c += 64 * NW) {
+    tab[c] = describe_chunk<REF>(a, c, tb, row0);
+    outside |= digits_w(tab[c]);
   }
+  outside = __syncthreads_or(outside);
+  auto chunk_info = [&](int c) { return __builtin_amdgcn_readfirstlane(c < SI_TAB ? tab[c] : describe_chunk<REF>(a, c, tb, row0)); };
+  auto from = [&](int c, int& info) {              // the first chunk from c on with digits
+    for (; c < s.C; ++c) {
+      info = chunk_info(c);
+      if (digits_x(info) && (!REF || digits_w(info))) break;
+    }
+    return c;
+  };
+  const double base = sum_base(s.m, a.row_exp[row0 + l32]);
+  double y[16], low[16];
+#pragma unroll
+  for (int v = 0; v < 16; ++v) {
+    y[v] = base;
+    low[v] = 0.0;
+  }
+  const char* q0 = a.Q + (int64_t)(row0 >> 5) * s.C * KS * 1024;
+  Tile<KS, 1> tl;
+  auto load_first = [&](int c) {
+    tl.load_codes(q0 + (int64_t)c * KS * 1024, 0, lane * 16);
+    tl.load_scales(REF ? a.mt.wunit + (int64_t)c * s.npad + row0 : a.S + (int64_t)(c / s.nchg) * s.npad + row0, l32);
+  };
+  auto uniform = [](int v) { return __builtin_amdgcn_readfirstlane(v); };   // (what the compiler does not see is the same in all lanes)
+  auto stage = [&](int c, int info, int to) {
+    const char* src = a.Xd + ((int64_t)c * s.TB + tb) * SI_MAXD * KS * 1024;
+    for (int i = wave; i < digits_x(info) * KS; i += NW) lds_load16((unsigned)uniform((int)(lds0 + to * STAGE + i * 1024)), lane * 16, src + i * 1024);
+  };
+  int info = 0, next_info = 0, buf = 0, c = from(0, info);
+  if (c < s.C) {
+    stage(c, info, 0);
+    load_first(c);
+  }
+  while (c < s.C) {
+    const int nd = digits_x(info), sets = REF ? digits_w(info) : 1, next = from(c + 1, next_info);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (next < s.C) stage(next, next_info, buf ^ 1);
+    const char* x = si_smem + buf * STAGE + lane * 16;
+    const double sc = tl.s[0];
+    for (int j = 0; j < sets; ++j) {
+      for (int p = (nd - 1) >> 1; p >= 0; --p) {
+        v16i acc[1];
+        __builtin_amdgcn_s_setprio(1);
+        tl.pair(x, p, 2 * p + 1 < nd, acc);
+        __builtin_amdgcn_s_setprio(0);
+        if (p == 0) {
+          if (j + 1 < sets)
+            tl.load_codes(q0 + (j + 1) * a.plane + (int64_t)c * KS * 1024, 0, lane * 16);
+          else if (next < s.C)
+            load_first(next);
+        }
+        const double f = ldexp(sc, exponent_x(info) + 16 * p + (REF ? 8 * j : 0));
+#pragma unroll
+        for (int v = 0; v < 16; ++v) add_compensated(y[v], low[v], f, (double)acc[0][v]);
+      }
+    }
+    c = next;
+    info = next_info;
+    buf ^= 1;
+  }
+  if (!REF && outside) {
+    for (int c = 0; c < s.C; c += s.nchg)
+      if (digits_w(chunk_info(c))) add_zeros(a, c, tb, row0, lane, y, low);
+  }
+  store_twice<REF>(a, row0, tb, lane, base, y, low);
 }
 
 template <int KS>
-slim_status outputs_launch(slim_ctx* ctx, const char* name, const OutArgs& a, bool ref, bool compensated) {
+slim_status outputs_launch(slim_ctx* ctx, const char* name, const OutArgs& a, bool ref, slim_int_sums sums) {
   const dim3 grid(a.s.RT * a.s.TB);
   const size_t table = sizeof(int) * std::min(a.s.C, SI_TAB);
-  if (compensated) {
+  if (sums == slim_int_sums::by_pairs) {
+    const size_t smem = 2 * SI_MAXD * KS * 1024 + table;
+    if (ref)
+      SLIM_LAUNCH(ctx, slim_prof_name(name, "int_outputs_by_pairs"), (int_outputs_by_pairs<KS, true>), grid, dim3(512), smem, a);
+    else
+      SLIM_LAUNCH(ctx, slim_prof_name(name, "int_outputs_by_pairs"), (int_outputs_by_pairs<KS, false>), grid, dim3(512), smem, a);
+  } else if (sums == slim_int_sums::twice) {
     const size_t smem = 2 * SI_MAXD * KS * 1024 + table;
     if (ref)
       SLIM_LAUNCH(ctx, name, (int_outputs_twice<KS, true>), dim3(2 * grid.x), dim3(256), smem, a);
@@ -677,10 +800,12 @@ slim_status slim_int_g_digits(slim_ctx* ctx, const IntShape& s, const IntMeta& m
   SLIM_LAUNCH(ctx, "int_g_stats", int_g_stats, dim3(slim_cdiv(s.ts, 1024), std::min(s.m, 128)), block, 0, G, ldg, s, work);
   SLIM_LAUNCH(ctx, "int_g_units", int_g_units, tgrid, block, 0, s.ts, work, token_unit);
   SLIM_LAUNCH(ctx, "int_g_digits", int_g_digits, dim3(slim_cdiv(s.TB, 4), s.k), block, 0, G, ldg, s, mt.x, token_unit, Xd, SX, SXlo);
+  SLIM_LAUNCH(ctx, "int_g_cost", int_g_cost, dim3(1), dim3(1024), 0, mt.x, (int64_t)s.C * s.TB, work);
   return SLIM_OK;
 }
-slim_status slim_int_outputs(slim_ctx* ctx, const char* name, const OutArgs& a, bool ref, bool compensated) {
-  return a.s.ks == 1   ? outputs_launch<1>(ctx, name, a, ref, compensated)
-         : a.s.ks == 2 ? outputs_launch<2>(ctx, name, a, ref, compensated)
-                       : outputs_launch<4>(ctx, name, a, ref, compensated);
+bool slim_int_pairs_pay(int cost) { return cost < TWICE_CHUNK; }
+slim_status slim_int_outputs(slim_ctx* ctx, const char* name, const OutArgs& a, bool ref, slim_int_sums sums) {
+  return a.s.ks == 1   ? outputs_launch<1>(ctx, name, a, ref, sums)
+         : a.s.ks == 2 ? outputs_launch<2>(ctx, name, a, ref, sums)
+                       : outputs_launch<4>(ctx, name, a, ref, sums);
 }

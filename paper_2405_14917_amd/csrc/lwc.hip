@@ -375,8 +375,8 @@ size_t lwc_layout(int n, int m, int beta, int steps, char* base, LwcWorkspace& w
 }
 
 template <typename T, int V>
-slim_status lwc_run_v(slim_ctx* ctx, const LwcWorkspace& w, const T* W, LwcArgs& a, OutArgs& oa, const slim_gemm_desc& wide,
-                    int steps, double beta1, double beta2) {
+slim_status lwc_run_v(slim_ctx* ctx, const LwcWorkspace& w, const T* W, LwcArgs& a, OutArgs& oa, slim_int_sums sums,
+                      const slim_gemm_desc& wide, int steps, double beta1, double beta2) {
   const dim3 grid(w.blocks_x, w.blocks_y), block(256);
   SLIM_LAUNCH(ctx, "lwc_init", (lwc_init<T, V>), grid, block, 0, W, a);
   oa.Q = w.Wd;
@@ -384,7 +384,7 @@ slim_status lwc_run_v(slim_ctx* ctx, const LwcWorkspace& w, const T* W, LwcArgs&
   oa.Ylo = w.WGlo;
   oa.sub = oa.sublo = nullptr;
   slim_status st = SLIM_OK;
-  if (!a.D) st = slim_int_outputs(ctx, "lwc_wg_product", oa, true, true);
+  if (!a.D) st = slim_int_outputs(ctx, "lwc_wg_product", oa, true, sums);
   if (st != SLIM_OK) return st;
   oa.Q = w.Q;
   oa.Y = w.DG;
@@ -393,7 +393,7 @@ slim_status lwc_run_v(slim_ctx* ctx, const LwcWorkspace& w, const T* W, LwcArgs&
   oa.sublo = w.WGlo;
   for (int it = 1; it <= steps + 1; ++it) {
     oa.rest_from = it;
-    st = a.D ? slim_dgemm(ctx, "lwc_grad_dgemm", 0, wide) : slim_int_outputs(ctx, "lwc_grad_product", oa, false, true);
+    st = a.D ? slim_dgemm(ctx, "lwc_grad_dgemm", 0, wide) : slim_int_outputs(ctx, "lwc_grad_product", oa, false, sums);
     if (st != SLIM_OK) return st;
     if (it <= steps) {
       a.c1 = 1.0 - std::pow(beta1, (double)it);
@@ -410,10 +410,10 @@ slim_status lwc_run_v(slim_ctx* ctx, const LwcWorkspace& w, const T* W, LwcArgs&
   return SLIM_OK;
 }
 template <typename T>
-slim_status lwc_run(slim_ctx* ctx, const LwcWorkspace& w, const T* W, LwcArgs& a, OutArgs& oa, const slim_gemm_desc& wide,
-                    int steps, double beta1, double beta2) {
-  return a.s.beta % 4 == 0 ? lwc_run_v<T, 4>(ctx, w, W, a, oa, wide, steps, beta1, beta2)
-                           : lwc_run_v<T, 1>(ctx, w, W, a, oa, wide, steps, beta1, beta2);
+slim_status lwc_run(slim_ctx* ctx, const LwcWorkspace& w, const T* W, LwcArgs& a, OutArgs& oa, slim_int_sums sums,
+                    const slim_gemm_desc& wide, int steps, double beta1, double beta2) {
+  return a.s.beta % 4 == 0 ? lwc_run_v<T, 4>(ctx, w, W, a, oa, sums, wide, steps, beta1, beta2)
+                           : lwc_run_v<T, 1>(ctx, w, W, a, oa, sums, wide, steps, beta1, beta2);
 }
 
 }  // namespace
@@ -456,6 +456,7 @@ extern "C" slim_status slim_lwc_quantize(slim_ctx* ctx, const void* W, slim_dtyp
   LwcWorkspace w;
   lwc_layout(n, m, beta, steps, ctx->ws, w);
   const bool wide = beta % 4 != 0;
+  slim_int_sums sums = slim_int_sums::twice;
   slim_gemm_desc d;
   d.A = w.WG;
   d.lda = m;
@@ -477,6 +478,11 @@ extern "C" slim_status slim_lwc_quantize(slim_ctx* ctx, const void* W, slim_dtyp
     st = slim_int_clear(ctx, w.mt, w.rest, w.s.k + w.s.npad);
     if (st == SLIM_OK) st = slim_int_w_units(ctx, w.s, w.mt, W, w_dtype, ldw);
     if (st == SLIM_OK) st = slim_int_g_digits(ctx, w.s, w.mt, G, ldg, w.work, w.token_unit, w.Xd, w.SX, w.SXlo);
+    if (st != SLIM_OK) return st;
+    // which of the two products suits the digits of G: the host waits once more (some 15 us of the 20 ms of 20 steps on 4096 x 4096)
+    SLIM_HIP_TRY(ctx, hipMemcpyAsync(ctx->hpin, w.work, sizeof(int), hipMemcpyDeviceToHost, ctx->stream));
+    SLIM_HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
+    if (slim_int_pairs_pay(*reinterpret_cast<const int*>(ctx->hpin))) sums = slim_int_sums::by_pairs;
   }
   if (st != SLIM_OK) return st;
 
@@ -528,9 +534,9 @@ extern "C" slim_status slim_lwc_quantize(slim_ctx* ctx, const void* W, slim_dtyp
   oa.row_exp = w.row_exp;
   oa.rest_from = 1;
   oa.token_unit = w.token_unit;
-  st = w_dtype == SLIM_F16    ? lwc_run(ctx, w, static_cast<const __half*>(W), a, oa, d, steps, beta1, beta2)
-       : w_dtype == SLIM_BF16 ? lwc_run(ctx, w, static_cast<const __hip_bfloat16*>(W), a, oa, d, steps, beta1, beta2)
-                              : lwc_run(ctx, w, static_cast<const float*>(W), a, oa, d, steps, beta1, beta2);
+  st = w_dtype == SLIM_F16    ? lwc_run(ctx, w, static_cast<const __half*>(W), a, oa, sums, d, steps, beta1, beta2)
+       : w_dtype == SLIM_BF16 ? lwc_run(ctx, w, static_cast<const __hip_bfloat16*>(W), a, oa, sums, d, steps, beta1, beta2)
+                              : lwc_run(ctx, w, static_cast<const float*>(W), a, oa, sums, d, steps, beta1, beta2);
   if (st != SLIM_OK) return st;
   if (!loss_curve) return SLIM_OK;                 // nothing for the host: the call does not wait
   double* host = reinterpret_cast<double*>(ctx->hpin);

@@ -718,11 +718,11 @@ slim_status sba_rank_independent(slim_ctx* ctx, const SbaWorkspace& w, const voi
   oa.S = w.Sn;
   oa.Rz = w.Rn;
   oa.Y = w.Yt;
-  st = slim_int_outputs(ctx, "sba_reference_outputs", oa, true, false);
+  st = slim_int_outputs(ctx, "sba_reference_outputs", oa, true, slim_int_sums::plain);
   if (st != SLIM_OK) return st;
   oa.Q = w.Qn;
   oa.Y = w.Yc;
-  st = slim_int_outputs(ctx, "sba_outputs", oa, false, false);
+  st = slim_int_outputs(ctx, "sba_outputs", oa, false, slim_int_sums::plain);
   if (st != SLIM_OK) return st;
   if (objective == SLIM_OBJ_KL) {
     // reference side once: per-token maximum and log-sum-exp, then Y^T becomes P = softmax over the outputs
