@@ -5,7 +5,7 @@
 // product M is 2^110.27.  Modulo one of them both operands are bytes: fourteen int8 products, each exact in int32 (512 * 128 *
 // 128 = 2^23), in place of the 28 or more that splitting both operands into digits would take.
 // The Chinese remainder theorem gives sum / M = frac(sum over the moduli of S_i c_i) with c_i = (inverse of M / m_i mod m_i)
-// / m_i, so an element needs no more than that sum, mod 1: the first 24 binary places of c_i times S_i in a 32-bit integer
+// / m_i, so an element needs no more than that sum, mod 1: the first 24 binary places of c_i times S_i in an unsigned 32-bit integer
 // (whose overflow is what mod 1 drops), the places behind them times S_i in fp64.  The method is Ozaki, Uchino and Imamura's
 // (matrix products through the Chinese remainder theorem, 2025); kernels, scaling by norms and the sum mod 1 are this library's.
 //
@@ -73,7 +73,8 @@ __constant__ Crt d_crt = crt_constants();
 // A workgroup has 32 rows (or columns: `T`) of all KMAX channels, a wavefront 32 x 32 of them, one fragment per plane: the
 // lane's row l % 32, channels 16 (l / 32) .. + 15.  8 bytes in and 14 out per element: 28672 x 512 in 84 us (3.8 TB/s); fewer
 // than some 8000 rows leave CUs idle (4096 x 512 22 us).
-// A row with a value that is not finite has no residues: its scale is NaN, and so is what it is multiplied into.
+// A row with a value that is not finite has no residues: its scale is NaN, and so is what it is multiplied into.  (A row whose norm
+// is no normal number would lose digits of its scale; what comes from 32-bit weights and activations stays far above.)
 template <bool T>
 __global__ __launch_bounds__(1024) void rg_residues(const double* __restrict__ src, int64_t ld, int rows, int K, char* __restrict__ out,
                                                     int64_t plane, double* __restrict__ scale) {
@@ -259,7 +260,7 @@ __global__ __launch_bounds__(512, 2) void rgemm_kernel(RgArgs a) {
   const int offA = wr * (4 * FRAG) + lane * 16, offB = 4 * (4 * FRAG) + wc * (8 * FRAG) + lane * 16;
   int unit = 0;
   v16i acc[2][2];
-  int hi[2][16];
+  unsigned hi[2][16];                          // (modulo 2^32: the sums overflow on purpose)
   double lo[2][16];
   v4i fa[2], fb[2][2];
   auto frags = [&](int buf, const char* u, int ks) {
@@ -344,10 +345,10 @@ __global__ __launch_bounds__(512, 2) void rgemm_kernel(RgArgs a) {
             if constexpr (NTH > 0) {
               const int s32 = acc[1 - P][ej][ev];
               if constexpr (NTH == 1) {
-                hi[ej][ev] = __mul24(s32, ch);
+                hi[ej][ev] = (unsigned)__mul24(s32, ch);
                 lo[ej][ev] = (double)s32 * cl;
               } else {
-                hi[ej][ev] += __mul24(s32, ch);
+                hi[ej][ev] += (unsigned)__mul24(s32, ch);
                 lo[ej][ev] = fma((double)s32, cl, lo[ej][ev]);
               }
               asm volatile("" : "+v"(hi[ej][ev]), "+v"(lo[ej][ev]));   // (or the compiler moves all of them behind the plane's products)
@@ -384,9 +385,9 @@ __global__ __launch_bounds__(512, 2) void rgemm_kernel(RgArgs a) {
 #pragma unroll
       for (int j = 0; j < 2; ++j) {
         const int s = acc[1][j][v];
-        const int t = hi[j][v] + __mul24(s, d_crt.hi[NP - 1]);
+        const unsigned t = hi[j][v] + (unsigned)__mul24(s, d_crt.hi[NP - 1]);
         const double l = fma((double)s, d_crt.lo[NP - 1], lo[j][v]);
-        double f = fma((double)(t << 8), 0x1p-32, l);
+        double f = fma((double)(int)(t << 8), 0x1p-32, l);
         f -= rint(f);
         lo[j][v] = fma(f * sr, sb[j], old[j][v]);
         asm volatile("" : "+v"(lo[j][v]));

@@ -1,5 +1,9 @@
 """The rank-512 products of the inverse and the sweep from residues on the int8 matrix cores, against the same calls with the
 fp64 products (a caller's workspace without room for the residues takes those) and against the identity they solve."""
+import ctypes
+import math
+from fractions import Fraction
+
 import pytest
 import torch
 
@@ -146,3 +150,96 @@ def test_columns_of_a_group_beside_a_large_channel(contexts, m, g0):
     U, _ = s.hessian_inverse(G, 2, 0.0)
     assert "inv_trtri_terms_dgemm@rgemm_kernel" in steps(s)
     assert ((U[g0 - 512:g0, g0:g0 + 512] + B).abs() <= 4 * EPS * B.abs()).all()
+
+
+class Operand(ctypes.Structure):
+    _fields_ = [("planes", ctypes.c_void_p), ("scale", ctypes.c_void_p)]
+
+
+class Product(ctypes.Structure):
+    _fields_ = [("A", Operand), ("B", Operand), ("rowsA", ctypes.c_int), ("rowsB", ctypes.c_int), ("C", ctypes.c_void_p),
+                ("ldc", ctypes.c_int64), ("M", ctypes.c_int), ("N", ctypes.c_int), ("alpha", ctypes.c_double), ("upper", ctypes.c_bool),
+                ("beside", ctypes.c_bool)]
+
+
+def product(s, A, B, C, M, N, alpha, upper=False, beside=False):
+    """C[:M, :N] += alpha A B by the library's own two kernels; A rows x K, B K x cols (views of wider matrices)."""
+    residues = s.lib._Z16slim_rg_residuesP8slim_ctxPKcRK15slim_rg_operandPKdliib
+    rgemm = s.lib._Z10slim_rgemmP8slim_ctxPKcRK12slim_rg_desc
+    keep, ops = [], []
+    for X, rows, columns in ((A, A.shape[0], False), (B, B.shape[1], True)):
+        padded = -(-rows // 128) * 128
+        planes = torch.full((padded * 512 * 14,), 77, dtype=torch.uint8, device="cuda")
+        scale = torch.full((padded,), 3.0, dtype=torch.float64, device="cuda")
+        keep += [planes, scale]
+        ops.append(Operand(planes.data_ptr(), scale.data_ptr()))
+        assert residues(s.ctx, b"inv_panel_residues", ctypes.byref(ops[-1]), ctypes.c_void_p(X.data_ptr()), ctypes.c_int64(X.stride(0)),
+                        ctypes.c_int(rows), ctypes.c_int(A.shape[1]), ctypes.c_bool(columns)) == 0
+    d = Product(ops[0], ops[1], A.shape[0], B.shape[1], C.data_ptr(), C.stride(0), M, N, alpha, upper, beside)
+    assert rgemm(s.ctx, b"gptq_trailing_dgemm", ctypes.byref(d)) == 0
+    torch.cuda.synchronize()
+
+
+# a tile and less, one row or column more than tiles, ranks from the least to the most with every kind of remainder of 16 and 128, more
+# than one tile per workgroup, results narrower than the operands
+@pytest.mark.parametrize("M,N,K,extra,beside", [
+    (1, 2, 2, 0, False), (128, 128, 512, 0, False), (129, 257, 386, 0, True), (40, 300, 510, 0, False), (700, 130, 130, 0, False),
+    (257, 64, 16, 200, False), (2304, 2176, 100, 0, False), (2050, 2300, 504, 130, True)])
+def test_product_against_exact_sums(contexts, M, N, K, extra, beside):
+    binding, make = contexts
+    gen = torch.Generator(device="cuda").manual_seed(M + N + K)
+    rnd = lambda *shape: torch.randn(*shape, generator=gen, device="cuda", dtype=torch.float64)
+    # rows and columns of very different size, channels of different size in each; rows and columns of zeros, of tiny and of whole
+    # numbers, and of equal ones (the largest sums of residues)
+    A = rnd(M + extra, K + 2)[:, :K] * 2.0 ** (40.0 * rnd(M + extra, 1)) * 2.0 ** (4.0 * rnd(1, K))
+    B = rnd(K, N + extra) * 2.0 ** (40.0 * rnd(1, N + extra)) * 2.0 ** (4.0 * rnd(K, 1))
+    for r in range(5, M, 97):
+        A[r] = 0.0
+    if M > 30:
+        A[11] = torch.randint(-5, 6, (K,), generator=gen, device="cuda").double() * 2.0 ** -500
+        A[12] = 1.0
+        A[13] = -1.0
+    if N > 30:
+        B[:, 7] = 0.0
+        B[:, 8] = 1.0
+        B[:, 9] = torch.arange(K, device="cuda").double()
+    A = torch.nn.functional.pad(A, (0, K % 4 + 2))[:, :K]                        # an even leading dimension, 16-byte rows
+    old = rnd(M + 3, N + 5)
+    C = old.clone()
+    product(make(), A, B, C, M, N, -1.0, beside=beside)
+    assert torch.equal(C[M:], old[M:]) and torch.equal(C[:, N:], old[:, N:])
+    pick = lambda size, some: sorted({x for x in some if x < size} | {int(x) for x in torch.randint(0, size, (12,), generator=gen, device="cuda")})
+    rows, cols = pick(M, (0, 5, 11, 12, 13, M - 1)), pick(N, (0, 7, 8, 9, N - 1))
+    a, b = A[rows].tolist(), B[:, cols].t().tolist()
+    got, was = C[rows][:, cols].tolist(), old[rows][:, cols].tolist()
+    square = []
+    for i, x in enumerate(a):
+        fx = [Fraction(v) for v in x]
+        nx = math.sqrt(sum(v * v for v in fx)) if any(x) else 0.0
+        for j, y in enumerate(b):
+            ny = math.sqrt(sum(Fraction(v) ** 2 for v in y))
+            err = abs(float(Fraction(was[i][j]) - sum(p * Fraction(q) for p, q in zip(fx, y)) - Fraction(got[i][j])))
+            # an operand is rounded to half a unit of norm / 2^54.5 per channel, after a rounding of its own by 2^-53; the sum's fraction,
+            # the scales and the last fma round by 2^-53 each, the fma relative to the result
+            bound = nx * ny * ((math.sqrt(K) + 6.0) * 2.0 ** -54.5 + 4 * EPS) + EPS * abs(got[i][j])
+            assert err <= bound, (rows[i], cols[j], err, bound)
+            if nx * ny > 1e3 * abs(was[i][j]):
+                square.append((err / (nx * ny)) ** 2)
+    # over many elements: every rounding (of an element, of its scaled value, and the four of the sum) is off by 0.29 of its step
+    assert len(square) < 50 or math.sqrt(sum(square) / len(square)) <= EPS
+
+
+def test_product_of_the_upper_triangle(contexts):
+    """Only tiles that reach the diagonal, on which every element is right; those below it stay as they are."""
+    binding, make = contexts
+    n, K = 1100, 512
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    A = torch.randint(-9, 10, (n, K), generator=gen, device="cuda").double()
+    C = torch.randint(-99, 100, (n, n), generator=gen, device="cuda").double()
+    want = C + 2.0 * (A @ A.t())
+    old = C.clone()
+    product(make(), A, A.t().contiguous(), C, n, n, 2.0, upper=True, beside=True)
+    tile = torch.arange(n, device="cuda") // 128
+    upper = tile[:, None] <= tile[None, :]
+    assert ((C - want)[upper].abs() <= 1e-9).all()
+    assert torch.equal(C[~upper], old[~upper])
