@@ -37,14 +37,19 @@ slim_status slim_ws_reserve(slim_ctx* ctx, size_t bytes) {
   }
   ctx->ws = static_cast<char*>(p);
   ctx->ws_bytes = bytes;
+  if (bytes >= ctx->ws_refused) ctx->ws_refused = SIZE_MAX;      // (there is room again)
   return SLIM_OK;
 }
 
 slim_status slim_ws_reserve_either(slim_ctx* ctx, size_t full, size_t base, bool& has_full) {
-  has_full = full > base && (!ctx->ws_external || full <= ctx->ws_bytes);
+  // an own workspace asks the device once: what it has refused is not asked for again, since every try synchronises and gives
+  // the present workspace up first
+  has_full = full > base && (full <= ctx->ws_bytes || (!ctx->ws_external && full < ctx->ws_refused));
   if (has_full) {
     const slim_status st = slim_ws_reserve(ctx, full);
     if (st != SLIM_ERR_ALLOC) return st;
+    ctx->ws_refused = full;
+    ctx->err[0] = 0;
     has_full = false;
   }
   return slim_ws_reserve(ctx, base);

@@ -47,6 +47,7 @@ struct slim_ctx {
   char* ws = nullptr;
   size_t ws_bytes = 0;
   size_t ws_off = 0;
+  size_t ws_refused = SIZE_MAX;   // what the device had no room for (slim_ws_reserve_either)
   bool ws_external = false;       // the workspace is the caller's (given to slim_create): never grown, never freed
   // small fixed buffers
   double* tau_default = nullptr;  // device, SLIM_DEFAULT_NCAND doubles
@@ -79,7 +80,8 @@ slim_status slim_fail(slim_ctx* ctx, slim_status code, const char* fmt, ...);
 // alloc() hands out 256-byte aligned pieces of it.  reserve() may synchronise and reallocate.
 slim_status slim_ws_reserve(slim_ctx* ctx, size_t bytes);
 void* slim_ws_alloc(slim_ctx* ctx, size_t bytes);
-// Reserves `full` bytes, or `base` where a caller's workspace, or the device, has no room for them; `has_full`: which.
+// Reserves `full` bytes, or `base` where a caller's workspace, or the device, has no room for them (which the context remembers);
+// `has_full`: which.
 slim_status slim_ws_reserve_either(slim_ctx* ctx, size_t full, size_t base, bool& has_full);
 inline size_t slim_ws_round(size_t bytes) { return (bytes + 255) & ~size_t(255); }
 
