@@ -29,6 +29,7 @@ import torch
 from paper_2405_14917_amd import binding, pipeline, synth
 
 PEAK = {"mfma_f16": 2.5e15, "mfma_i8": 5.0e15, "mfma_f64": 78.6e12, "alu_f64": 78.6e12, "hbm": 8.0e12}
+PEAK["residues"] = PEAK["mfma_i8"] / 14      # fp64 flops as products modulo fourteen numbers on the int8 matrix cores
 # HBM bytes per launch of the dominant kernel function, from two `rocprofv3 --pmc` runs of this command (FETCH_SIZE,
 # then WRITE_SIZE, in KiB per dispatch), each scaled by what the same counter reads for the 64 MiB copy that this
 # program issues for that purpose; the files under profiles/ that are named here give the commands and the readings.
@@ -125,6 +126,23 @@ class Pass(pipeline.LayerPass):
         m_star = int(row_off[-1])                     # packed holds the rows of its capacity; the layer fills m_star
         nbytes = m_star * packed.shape[1] * 4 + gbits.numel() * 4 + row_off.numel() * 4 + scale.numel() * 8 + zero.numel() * 8
         return e0.elapsed_time(e1) * 1e3 / reps, nbytes
+
+
+def residue_flops(name, cfg, launches):
+    """The fp64 flops of a step's `launches` largest products: those that run on rgemm_kernel (the library takes the large ones)."""
+    n, m = cfg.n, cfg.m
+    w = 512
+    starts = range(0, m, w)
+    if name == "gptq_trailing_dgemm":
+        each = [2.0 * n * w * (m - w0 - w) for w0 in starts if w0 + w < m]
+    elif name == "inv_syrk_dgemm":
+        each = [float(g0 - w) * (g0 - w + 1) * (min(m, g0 + w) - g0) for g0 in starts if g0 >= 2 * w]
+    elif name == "inv_trtri_terms_dgemm":
+        each = [2.0 * g0 * w * (m - g0 - w) for g0 in starts if g0 and g0 + w < m]
+    else:
+        each = []
+    return sum(sorted(each, reverse=True)[:int(round(launches))])
+
 
 def algorithmic_work(name, cfg, launches_per_step):
     """(bound, peak key, work per launch) for every step of the path.  Work is ALGORITHMIC: distinct results
@@ -353,12 +371,17 @@ def main():
         k["avg_us"] = 1e3 * k["ms"] / k["cnt"]
         bound, peak_key, work = algorithmic_work(step, cfg, k["launches_per_step"])
         k["bound"], k["peak_key"], k["work_per_step"] = bound, peak_key, work * k["launches_per_step"]
+        res = [(ms, cnt) for fn, ms, cnt in k["parts"] if fn.startswith("rgemm_kernel")]
+        res_ms, k["residues_per_step"] = sum(ms for ms, _ in res), residue_flops(step, cfg, sum(cnt for _, cnt in res) / args.profile_steps)
         for fn, ms, cnt in k["parts"]:
-            f = functions.setdefault(fn, {"ms": 0.0, "cnt": 0, "work": 0.0, "bound": bound, "peak_key": peak_key})
+            by_residues = fn.startswith("rgemm_kernel")
+            f = functions.setdefault(fn, {"ms": 0.0, "cnt": 0, "work": 0.0, "bound": bound, "peak_key": "residues" if by_residues else peak_key})
             f["ms"] += ms
             f["cnt"] += cnt
-            # a step that ran on several kernel functions is credited to them in proportion to their time
-            f["work"] += k["work_per_step"] * args.profile_steps * (ms / k["ms"] if k["ms"] > 0 else 0.0)
+            # the products from residues are known one by one; the rest of a step that ran on several kernel functions is credited to them
+            # in proportion to their time
+            own, own_ms = (k["residues_per_step"], res_ms) if by_residues else (k["work_per_step"] - k["residues_per_step"], k["ms"] - res_ms)
+            f["work"] += own * args.profile_steps * (ms / own_ms if own_ms > 0 else 0.0)
     roofline = None
     if functions:
         dom = max(functions, key=lambda fn: functions[fn]["ms"])
@@ -387,7 +410,7 @@ def main():
         if k["bound"] == "latency":
             entry["latency"] = {"us_per_link": round(k["avg_us"], 2), "links": k["launches_per_step"]}
         if k["work_per_step"] > 0:
-            floor = k["work_per_step"] / PEAK[k["peak_key"]] * 1e3
+            floor = ((k["work_per_step"] - k["residues_per_step"]) / PEAK[k["peak_key"]] + k["residues_per_step"] / PEAK["residues"]) * 1e3
             floor_ms += floor
             entry["floor_ms"] = round(floor, 4)
             if k["bound"] != "latency":
@@ -402,7 +425,7 @@ def main():
         "n_gpus": 1, "steps": args.steps, "warmup": args.warmup, "ms_per_step": ms_per_step,
         "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
         "dtype": "f16 x f16 -> f32 (Gram MFMA), i8 x i8 -> i32 -> f64 (SBA products, exact), f64 (inverse, salience, SQC, GPTQ sweep; large products "
-                 "from exact i8 residue products, error no larger than f64), u8/u32 (pack)",
+                 "from exact i8 residue products, operands rounded to 2^-55.5 of the norm of their row or column), u8/u32 (pack)",
         "data": "synthetic",
         "config": {"workload": workload_text(cfg), "p_star": p_star, "m_star": m_star},
         "roofline": roofline,
@@ -417,8 +440,8 @@ def main():
                           "SBA's integer products on another): their durations overlap and their frac is not a fraction "
                           "of the chip",
             "*dgemm": "large products of these steps run on rgemm_kernel (fp64 results from residues on the int8 matrix "
-                      "cores); they are rated by their fp64 flops against the fp64 matrix peak all the same, so their frac "
-                      "may pass 1",
+                      "cores); these are rated by 14 int8 operations per fp64 flop against the int8 peak, the others by "
+                      "their fp64 flops against the fp64 peak",
             "hbm entries": "yardsticks on the same chip (plain PyTorch kernels, 1 to 4 GB): fill 6.9 TB/s, copy 4.9 to 5.3 TB/s "
                            "read plus written (0.61 to 0.66 of the peak), read-only sum 4.0 TB/s, fp16 -> fp64 conversion 3.2 TB/s",
             "gram_mfma_f16": "power-limited: the same kernel runs at 0.71 of the nominal peak on constant data and at "

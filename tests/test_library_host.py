@@ -135,6 +135,24 @@ def test_bench_inverse_work_formulas_add_up():
         assert 0.97 * whole < total < 1.03 * whole, (name, total / whole)
 
 
+def test_bench_rates_products_from_residues_apart():
+    """The products that a step can take from residues are part of the step's work, the largest first; all that is left of the
+    terms is the triangular product of a group's own columns."""
+    import bench
+    from paper_2405_14917_amd import synth
+    cfg = synth.CONFIGS["C3"]
+    for step in ("gptq_trailing_dgemm", "inv_syrk_dgemm", "inv_trtri_terms_dgemm"):
+        whole, all_of_them = bench.algorithmic_work(step, cfg, 1)[2], bench.residue_flops(step, cfg, 99)
+        one, two = bench.residue_flops(step, cfg, 1), bench.residue_flops(step, cfg, 2)
+        assert 0.0 == bench.residue_flops(step, cfg, 0) < one < two <= 2 * one and two < all_of_them
+        if step == "inv_trtri_terms_dgemm":
+            own = sum(float(g0) * (min(cfg.m, g0 + 512) - g0) ** 2 for g0 in range(0, cfg.m, 512))
+            assert abs(whole - all_of_them - own) < 1e-9 * whole
+        else:
+            assert abs(whole - all_of_them) < 1e-9 * whole
+    assert bench.residue_flops("inv_trtri_rows_dgemm", cfg, 5) == 0.0
+
+
 def test_bench_rates_only_steps_that_are_launched():
     import inspect
     import bench
