@@ -442,15 +442,8 @@ extern "C" slim_status slim_lwc_quantize(slim_ctx* ctx, const void* W, slim_dtyp
   if (What && what_dtype != SLIM_F32 && what_dtype != SLIM_F64)
     return slim_fail(ctx, SLIM_ERR_UNSUPPORTED, "slim_lwc_quantize: What must be F32 or F64");
   const int k = m / beta;
-  SLIM_REQUIRE(ctx, (size_t)k <= (size_t)SLIM_HPIN_BYTES && sizeof(double) * (size_t)(steps + 1) <= (size_t)SLIM_HPIN_BYTES,
+  SLIM_REQUIRE(ctx, (size_t)k <= (size_t)SLIM_HPIN_BYTES - sizeof(int) && sizeof(double) * (size_t)(steps + 1) <= (size_t)SLIM_HPIN_BYTES,
                "slim_lwc_quantize: too many groups or steps for the staging buffer");
-  // the widths are validated before anything is written (not a hot path: the host waits for them)
-  uint8_t* bits_h = reinterpret_cast<uint8_t*>(ctx->hpin);
-  SLIM_HIP_TRY(ctx, hipMemcpyAsync(bits_h, bits, k, hipMemcpyDeviceToHost, ctx->stream));
-  SLIM_HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
-  for (int g = 0; g < k; ++g)
-    SLIM_REQUIRE(ctx, bits_h[g] >= 1 && bits_h[g] <= 8, "slim_lwc_quantize: bits[%d] = %d is outside 1..8", g, (int)bits_h[g]);
-
   slim_status st = slim_ws_reserve(ctx, slim_ws_need_lwc(n, m, beta, steps));
   if (st != SLIM_OK) return st;
   LwcWorkspace w;
@@ -478,13 +471,18 @@ extern "C" slim_status slim_lwc_quantize(slim_ctx* ctx, const void* W, slim_dtyp
     st = slim_int_clear(ctx, w.mt, w.rest, w.s.k + w.s.npad);
     if (st == SLIM_OK) st = slim_int_w_units(ctx, w.s, w.mt, W, w_dtype, ldw);
     if (st == SLIM_OK) st = slim_int_g_digits(ctx, w.s, w.mt, G, ldg, w.work, w.token_unit, w.Xd, w.SX, w.SXlo);
-    if (st != SLIM_OK) return st;
-    // which of the two products suits the digits of G: the host waits once more (some 15 us of the 20 ms of 20 steps on 4096 x 4096)
-    SLIM_HIP_TRY(ctx, hipMemcpyAsync(ctx->hpin, w.work, sizeof(int), hipMemcpyDeviceToHost, ctx->stream));
-    SLIM_HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
-    if (slim_int_pairs_pay(*reinterpret_cast<const int*>(ctx->hpin))) sums = slim_int_sums::by_pairs;
   }
   if (st != SLIM_OK) return st;
+  // the widths are validated before anything but the workspace is written (not a hot path: the host waits for them); with them
+  // comes which of the two products suits the digits of G
+  constexpr int COST_AT = SLIM_HPIN_BYTES - (int)sizeof(int);
+  const uint8_t* bits_h = reinterpret_cast<const uint8_t*>(ctx->hpin);
+  SLIM_HIP_TRY(ctx, hipMemcpyAsync(ctx->hpin, bits, k, hipMemcpyDeviceToHost, ctx->stream));
+  if (!wide) SLIM_HIP_TRY(ctx, hipMemcpyAsync(ctx->hpin + COST_AT, w.work, sizeof(int), hipMemcpyDeviceToHost, ctx->stream));
+  SLIM_HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
+  for (int g = 0; g < k; ++g)
+    SLIM_REQUIRE(ctx, bits_h[g] >= 1 && bits_h[g] <= 8, "slim_lwc_quantize: bits[%d] = %d is outside 1..8", g, (int)bits_h[g]);
+  if (!wide && slim_int_pairs_pay(*reinterpret_cast<const int*>(ctx->hpin + COST_AT))) sums = slim_int_sums::by_pairs;
 
   LwcArgs a;
   a.s = w.s;
