@@ -98,8 +98,8 @@ typedef struct slim_shape {
  * is split into more token ranges).  It does not depend on t_x from 16 on: that workspace serves every number of tokens.
  * The inverse and the sweep of large layers take the products of their updates from residues on the int8 matrix cores, and
  * what that needs is part of the answer; in a workspace of the caller's without room for it, but with room for two m x m
- * (n x m) fp64 matrices and what else is asked for, they take them on the fp64 matrix cores: slower, and a result may
- * differ in its last bits. */
+ * (n x m) fp64 matrices and what else is asked for, and in the context's own where the device has no room for it, they take
+ * them on the fp64 matrix cores: slower, and a result may differ in its last bits. */
 size_t slim_workspace_query(const slim_shape* shape, int num_cus);
 
 /* Creates a context bound to `hip_stream` (a hipStream_t, may be NULL for the default stream) on

@@ -10,14 +10,18 @@
 // (matrix products through the Chinese remainder theorem, 2025); kernels, scaling by norms and the sum mod 1 are this library's.
 //
 // Precision: what is lost is the rounding of the operands to integers, 2^-55.5 of the norm of a row or column per element, and
-// the roundings of the fp64 part, about 2^-59 of M.  Against exact sums at K = 512, relative (2-norm): 4.2e-16 on normal
+// the roundings of the fp64 part, about 2^-59 of M.  Errors are small beside the norms of a row of A and a column of B, as those of a
+// factorisation are; an element that is small beside the rest of its row keeps fewer digits than fp64 has, so a product in which
+// such an element counts alone is not for these kernels.  Against exact sums at K = 512, relative (2-norm): 4.2e-16 on normal
 // values and 2.8e-16 to 4.3e-16 with channels of very different scale and outliers of sixty times the rest, where the fp64
 // matrix cores give 7.5e-16 and 7.1e-16 to 1.0e-15.  (With 15 moduli 1.3e-16 and 7 % slower, with 13 it would be 1e-14.)
 //
-// What bounds it: power (some 1.7 GHz of 2.4 while it runs; the int8 products alone take two thirds of the time at that clock)
-// and, where a launch has one tile per CU, the old values and the stores of C.  us for the product / with both operands' residues / on the fp64 matrix cores:
-//   4096 x 1024  47 / 85 / 84    4096 x 2048  85 / 124 / 171    4096 x 3584  151 / 191 / 360    4096 x 10496  478 / 531 / 846
-//   28672 x 4096  1447 / 1549 / 1956 (one launch after the other; by itself 1290)
+// What bounds it: no pipe alone.  A tile takes 29 k cycles of MFMA per SIMD, 1.8 MB from the L2 to LDS and 5.2 MiB from there to the
+// wavefronts (1.5 KiB per MFMA), which overlap in part: over a pass of 4096 x 11008 the matrix cores are busy 30 % of the cycles, the
+// vector issue 20 %, and the wavefronts wait 39 % of theirs, at some 1.7 GHz of 2.4 (power).  Where a launch has one tile per CU, the
+// old values and the stores of C come on top.  us for the product / with both operands' residues / on the fp64 matrix cores:
+//   4096 x 1024  45 / 81 / 84    4096 x 2048  84 / 122 / 151    4096 x 3584  147 / 188 / 276    4096 x 10496  437 / 488 / 708
+//   28672 x 4096  1234 / 1342 / 1838
 #include <algorithm>
 
 #include "slim_internal.h"
@@ -139,7 +143,7 @@ __global__ __launch_bounds__(1024) void rg_residues(const double* __restrict__ s
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const double v = x[4 * q + i];
-        const float r = (float)fma(-P, rint(v * (1.0 / P)), v);      // |r| <= P / 2 + 2^-17: exact, and a float
+        const float r = (float)fma(-P, rint(v * (1.0 / P)), v);      // exact, an integer of at most P / 2 and a few (v / P is rounded): a float
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
           if (3 * t + c > LAST) continue;
@@ -473,9 +477,10 @@ slim_status slim_rgemm(slim_ctx* ctx, const char* name, const slim_rg_desc& d) {
                                           (int)RG_LDS));
     done = true;
   }
-  // Beside other streams' work the products leave some CUs alone: all of the inverse's on all CUs, tile after tile or a workgroup per
-  // tile, hold its chain of links up.  4096 x 11008 pass, us: a workgroup per tile 56200, all but 16 CUs 55500, all but 32 55700,
-  // all but 64 55400, all but 128 56500.
+  // Beside other streams' work the products leave some CUs alone, or they hold the inverse's chain of links up; more than 64, and
+  // they get long themselves.  Left alone 0 / 16 / 32 / 64 / 96 / 128, medians of three runs of one box, which scatter by 0.5 %:
+  // inverse of 6144 columns 4000 / 3980 / 3950 / 3840 / 3800 / 3910 us, 8192 7490 / 7530 / 7450 / 7290 / 7310 / 7540, 11008 15540 / 15680
+  // / 15350 / 15160 / 15670 / 16130; up to 4096 no difference; pass of 4096 x 11008 56.0 / 56.3 / 56.0 / 55.7 / 55.9 / 56.4 ms.
   const int wgs = d.beside ? std::max(8, a.ncu - RG_BESIDE) : a.ncu;
   SLIM_LAUNCH(ctx, slim_prof_name(name, "rgemm_kernel"), rgemm_kernel, dim3(std::min(total, wgs)), dim3(512), RG_LDS, a);
   return SLIM_OK;
