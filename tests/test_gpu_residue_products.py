@@ -1,5 +1,6 @@
 """The rank-512 products of the inverse and the sweep from residues on the int8 matrix cores, against the same calls with the
-fp64 products (a caller's workspace without room for the residues takes those) and against the identity they solve."""
+fp64 products (a caller's workspace without room for the residues takes those) and against the identity they solve, and the two
+kernels by themselves against exact sums."""
 import ctypes
 import math
 from fractions import Fraction
